@@ -513,6 +513,9 @@ void qfc_tune(int32_t key, int32_t value) {
     if (key == 4) t.gemv_half = value;
     if (key == 5) t.attn_pair = value;
     if (key == 6) t.attn_chunks = value;
+    if (key == 7) t.skinny_waves = value;
+    if (key == 8) t.skinny_row_tiles = value;
+    if (key == 9) t.skinny_max_m = value;
 }
 
 }  // extern "C"

@@ -1,0 +1,528 @@
+// Products of few token rows (M = 9 .. 64: batches beyond the decode kernel's eight rows, short
+// prompts): y[m,n] = sum_k x[m,k] * s * Wq[n,k], with binary16 activations (weights dequantized in
+// registers) or int8 activations (exact int32 sums).
+//
+// What bounds them: the weight stream up to a few dozen rows, as in decode.  The tiles of the
+// prefill kernels (256 channels x 64 or 128 tokens) give 16 workgroups for a layer of 4096
+// channels, i.e. 16 of 256 compute units pull the weights.  Here, as in the decode kernel, a
+// workgroup owns 16 R output channels (R packed row tiles) and ALL token rows, and its
+// wavefronts split K; their partial sums meet in LDS in fixed order (deterministic, no atomics, no
+// traffic between workgroups, no workspace).
+//
+// Measured with the weights in HBM, 32 token rows, this kernel against the 256-channel tiles (us):
+//   channels x k            4096 x 4096   4096 x 14336   6144 x 4096   28672 x 4096   128256 x 4096
+//   int4 groups, binary16    7.7 / 46      18.5 / 142     9.1 / 46      21.7 / 49      89 / 119
+//   int8 x int8 (with the quantization kernel)
+//                           10.0 / 29      23.4 / 90     11.8 / 30      26.7 / 37     101 / 112
+// The narrow layers are bound by the token rows: every compute unit pulls all of x (2 M K bytes) through
+// its vector cache, seven times its share of the 4-bit weights at M = 32.  The wide ones are within 1.3
+// (8-bit) to 1.7 (4-bit) of the time a 5.1 TB/s copy of the weights takes.
+//
+// MFMA shape 16 x 16: token rows are the row operand, in blocks of 16, weights the columns (a lane's 16
+// bytes of a packed tile are one or more whole operands, loaded from memory straight into registers).
+#include <type_traits>
+#include <utility>
+
+#include "qfc_internal.h"
+
+namespace qfc {
+namespace {
+
+typedef _Float16 h2 __attribute__((ext_vector_type(2)));
+typedef _Float16 h4 __attribute__((ext_vector_type(4)));
+typedef _Float16 v8h __attribute__((ext_vector_type(8)));
+typedef float v4f __attribute__((ext_vector_type(4)));
+typedef int v4i __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+typedef __attribute__((address_space(3))) void *lptr_t;
+
+struct SkinnyArgs {
+    const u32x4 *w;       // packed row tiles
+    const u32x4 *x;       // binary16 [M, K], or tiled int8 (see actquant.hip)
+    const float *sw;      // per-channel scales [Np] (W8C, W4C)
+    const float *sx;      // int8: per-token scales
+    const _Float16 *res;  // [M, N] residual added before the rounding, or null
+    void *out;
+    int M, N, K, Kp, KT, RT;  // KT: packed k tiles per row tile, RT: row tiles
+    int rt_stride;
+    int steps_q, steps_rem;  // 128-k steps per wavefront: steps_q, one more for the first steps_rem
+    float sw_mul;            // int8 x 4-bit: sums are 16 times the definition's (see gemm_i8.hip)
+    int gated_act;
+};
+
+__device__ __forceinline__ h2 as_h2(uint32_t u) { return __builtin_bit_cast(h2, u); }
+
+// eight biased int4 codes -> eight binary16 values (k ascending), exactly; with SC times a group scale
+// (one binary16 rounding per weight, as in the large fp16 kernel)
+template <bool SC>
+__device__ __forceinline__ v8h dequant4(uint32_t w, h2 s) {
+    const h2 c1032 = {(_Float16)1032.0f, (_Float16)1032.0f};
+    const h2 c72 = {(_Float16)72.0f, (_Float16)72.0f};
+    const h2 c16th = {(_Float16)0.0625f, (_Float16)0.0625f};
+    const uint32_t lo = w & 0x0F0F0F0Fu, hi = w & 0xF0F0F0F0u;
+    h2 p0 = as_h2(__builtin_amdgcn_perm(0x64646464u, lo, 0x04010400u)) - c1032;
+    h2 p1 = as_h2(__builtin_amdgcn_perm(0x64646464u, lo, 0x04030402u)) - c1032;
+    h2 p2 = as_h2(__builtin_amdgcn_perm(0x64646464u, hi, 0x04010400u)) * c16th - c72;
+    h2 p3 = as_h2(__builtin_amdgcn_perm(0x64646464u, hi, 0x04030402u)) * c16th - c72;
+    if (SC) p0 *= s, p1 *= s, p2 *= s, p3 *= s;
+    return v8h{p0[0], p0[1], p1[0], p1[1], p2[0], p2[1], p3[0], p3[1]};
+}
+// eight int8 codes -> eight binary16 values, exactly
+__device__ __forceinline__ v8h dequant8(uint32_t lo, uint32_t hi) {
+    const h2 c1152 = {(_Float16)1152.0f, (_Float16)1152.0f};
+    const uint32_t a = lo ^ 0x80808080u, b = hi ^ 0x80808080u;
+    const h2 p0 = as_h2(__builtin_amdgcn_perm(0x64646464u, a, 0x04010400u)) - c1152;
+    const h2 p1 = as_h2(__builtin_amdgcn_perm(0x64646464u, a, 0x04030402u)) - c1152;
+    const h2 p2 = as_h2(__builtin_amdgcn_perm(0x64646464u, b, 0x04010400u)) - c1152;
+    const h2 p3 = as_h2(__builtin_amdgcn_perm(0x64646464u, b, 0x04030402u)) - c1152;
+    return v8h{p0[0], p0[1], p1[0], p1[1], p2[0], p2[1], p3[0], p3[1]};
+}
+
+// At most N vector-memory operations outstanding and no LDS operation; memory accesses do not move across.
+template <int N>
+__device__ __forceinline__ void wait_mem() {
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(N) : "memory");
+}
+__device__ __forceinline__ void wait_lds() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
+
+// The wavefronts' partial sums meet in LDS: red[wave][r][tb] = 16 tokens x 16 channels, the token rows
+// permuted (bits 3:2 and 1:0 exchanged) so that the four tokens a store instruction writes lie in
+// different banks.  (16 x 16 accumulator: lane = channel + 16 q holds tokens 4 q + e in register e.)
+__device__ __forceinline__ int red_row(int tile, int token) { return (tile * 16 + ((token >> 2) | ((token & 3) << 2))) * 16; }
+
+template <int R, int TB, typename T, typename ACC>
+__device__ __forceinline__ void put_partials(T *red, const ACC (&acc)[R][TB], int wave, int lane) {
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+#pragma unroll
+        for (int tb = 0; tb < TB; ++tb)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) red[red_row((wave * R + r) * TB + tb, 4 * (lane >> 4) + e) + (lane & 15)] = acc[r][tb][e];
+}
+
+// Sum over the wavefronts (in order) and store phase.  T: float or int; CH: per-channel scales.
+template <int R, int TB, typename T, bool CH>
+__device__ __forceinline__ void finish(const SkinnyArgs &a, const T *red, int nwaves, int rt0) {
+    constexpr bool kInt = std::is_same<T, int>::value;
+    typedef T t4 __attribute__((ext_vector_type(4)));
+    const bool gated = a.gated_act >= 0;
+    const int half = a.N / 2;
+    const int tiles = gated ? R / 2 : R;  // (gated: pairs of row tiles, R is even)
+    auto total = [&](int r, int tb, int token, int n4) {
+        t4 s = {0, 0, 0, 0};
+        for (int w = 0; w < nwaves; ++w) s += *reinterpret_cast<const t4 *>(red + red_row((w * R + r) * TB + tb, token) + 4 * n4);
+        return s;
+    };
+    auto scaled = [&](const t4 &s, int n, float sxm, float (&v)[4]) {
+        float4 c = make_float4(1.0f, 1.0f, 1.0f, 1.0f);
+        if (CH) c = *reinterpret_cast<const float4 *>(a.sw + n);
+        const float cs[4] = {c.x, c.y, c.z, c.w};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = kInt ? (float)s[e] * sxm * (cs[e] * a.sw_mul) : CH ? (float)s[e] * cs[e] : (float)s[e];
+    };
+    for (int i = threadIdx.x; i < tiles * TB * 64; i += blockDim.x) {
+        const int n4 = i & 3, m = (i >> 2) & 15, tb = (i >> 6) % TB, r = (i >> 6) / TB;
+        const int token = tb * 16 + m;
+        if (token >= a.M) continue;
+        const float sxm = kInt ? a.sx[token] : 1.0f;
+        if (gated) {
+            // physical row tiles 2 t and 2 t + 1 of a layer packed in pairs hold the gate's and the other
+            // branch's rows of the same 16 channels (operator fusion, section 3.6 of the paper)
+            const int n = (rt0 + 2 * r) * 16 + 4 * n4, o = n / 2 + 2 * n4;  // o = (rt0 / 2 + r) * 16 + 4 n4
+            if (o >= half) continue;
+            float g[4], u[4];
+            scaled(total(2 * r, tb, m, n4), n, sxm, g);
+            scaled(total(2 * r + 1, tb, m, n4), n + 16, sxm, u);
+            const GateCoeffs gc = gate_coeffs(a.gated_act);
+            h4 hv;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) hv[e] = (_Float16)(gate_activation(g[e], gc) * u[e]);
+            *reinterpret_cast<h4 *>(static_cast<_Float16 *>(a.out) + (size_t)token * half + o) = hv;
+            continue;
+        }
+        const int n = (rt0 + r) * 16 + 4 * n4;
+        if (n >= a.N) continue;
+        float v[4];
+        scaled(total(r, tb, m, n4), n, sxm, v);
+        _Float16 *y = static_cast<_Float16 *>(a.out) + (size_t)token * a.N + n;
+        const _Float16 *res = a.res ? a.res + (size_t)token * a.N + n : nullptr;
+        if ((a.N & 3) == 0) {
+            if (res) {
+                const h4 rv = *reinterpret_cast<const h4 *>(res);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[e] += (float)rv[e];
+            }
+            *reinterpret_cast<h4 *>(y) = h4{(_Float16)v[0], (_Float16)v[1], (_Float16)v[2], (_Float16)v[3]};
+        } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (n + e < a.N) y[e] = (_Float16)(res ? v[e] + (float)res[e] : v[e]);
+        }
+    }
+}
+
+// ---------------------------------------------------------------- binary16 activations
+// Per step of 128 k a wavefront holds its weights in registers (requested D steps ahead) and reads the
+// token rows from a private LDS ring of RING half steps (64 k: rows of 128 bytes, 16-byte octets
+// XOR-swizzled as in the large fp16 kernel: conflict-free operand reads).  The ring is filled by
+// direct memory -> LDS copies whose lanes cover whole 128-byte row pieces: fetching the operands from
+// memory in their own order (16 rows x 64 bytes per instruction) reaches 9 TB/s out of L2 on this chip,
+// row pieces 28 TB/s.  No workgroup barrier until the partial sums meet.
+// Waiting: copies into LDS and loads into registers share the counter and complete in order within their
+// own kind, so "at most the copies of RING - 1 stages outstanding" says that the oldest stage has
+// landed whatever else is in flight; the weight loads are the compiler's own, which waits for
+// them by their own count (the copies it does not see only make it wait earlier than needed).
+// Group scales multiply the weights (one binary16 rounding per weight), as in the large fp16 kernel.
+// XB: blocks of 8 token rows.
+template <int FMT, int XB, int R, int RING, int D, int MAXT>
+__global__ __launch_bounds__(MAXT) void skinny_f16_kernel(SkinnyArgs a) {
+    static_assert((RING == 2 || RING == 4 || RING == 8) && (2 * D) % RING == 0, "static ring slots");
+    constexpr int TB = (XB + 1) / 2;
+    constexpr int WV = FMT == kW8C ? 2 : 1;  // weight vectors per step and row tile
+    constexpr int SLOT = TB * 2048;          // bytes of a half step in LDS
+    static_assert((RING - 1) * XB <= 63, "6-bit wait counter");
+    extern __shared__ u32x4 lds[];
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int c = lane & 15, q = lane >> 4;
+    const int rt0 = blockIdx.x * R;  // first row tile
+
+    const int t0 = wave * a.steps_q + min(wave, a.steps_rem);
+    const int nt = a.steps_q + (wave < a.steps_rem ? 1 : 0);
+    const int nst = 2 * nt;
+
+    // (the last workgroup's row tiles may run past the layer's: they are clamped, results dropped)
+    const u32x4 *wrow[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) wrow[r] = a.w + (size_t)min(rt0 + r, a.RT - 1) * a.rt_stride * 64;
+    u32x4 wv[D][R][WV];
+    u32x2 sv[D][R];
+    auto load_w = [&](int slot, int t) __attribute__((always_inline)) {
+        const int u = t >> 3;
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            if (FMT == kW4G32) {
+                const int spos = min(8 * u + 8, a.KT) + u;  // scale tile of the unit
+                sv[slot][r] = reinterpret_cast<const u32x2 *>(wrow[r] + (size_t)spos * 64 + ((t & 7) >> 1) * 16 + c)[t & 1];
+            }
+#pragma unroll
+            for (int v = 0; v < WV; ++v)
+                wv[slot][r][v] = __builtin_nontemporal_load(wrow[r] + (size_t)(FMT == kW8C ? 2 * t + v : FMT == kW4G32 ? t + u : t) * 64 + lane);
+        }
+    };
+    // copies of a half step: KiB i = token rows 8 i .. 8 i + 7, lane = (row, octet position)
+    const char *xbase = reinterpret_cast<const char *>(a.x);
+    const int K8 = a.K / 8;
+    const uint32_t ring0 = (uint32_t)(uintptr_t)(lptr_t)lds + wave * (RING * SLOT);
+    auto copy_stage = [&](int s, int slot) __attribute__((always_inline)) {
+        const int o0 = (2 * t0 + s) * 8;
+        const bool tail = o0 + 8 > K8;  // octets beyond K: any octet of the row (they meet zero weights)
+#pragma unroll
+        for (int i = 0; i < XB; ++i) {
+            const int rl = 8 * i + (lane >> 3);
+            int o = o0 + ((lane & 7) ^ ((rl >> 1) & 7));
+            if (tail && o >= K8) o &= 3;
+            const uint32_t off = ((uint32_t)min(rl, a.M - 1) * (uint32_t)K8 + (uint32_t)o) * 16u;
+            copy16_to_lds(xbase, off, __builtin_amdgcn_readfirstlane(ring0 + slot * SLOT + i * 1024));
+        }
+    };
+
+    v4f acc[R][TB];
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+#pragma unroll
+        for (int tb = 0; tb < TB; ++tb) acc[r][tb] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
+
+#pragma unroll
+    for (int i = 0; i < D; ++i)
+        if (i < nt) load_w(i, t0 + i);
+#pragma unroll
+    for (int s = 0; s < RING; ++s)
+        if (s < nst) copy_stage(s, s);
+
+    const char *xread = reinterpret_cast<const char *>(lds) + wave * (RING * SLOT) + c * 128;
+    const int swz = (c >> 1) & 7;
+    for (int b = 0; b < nt; b += D) {
+#pragma unroll
+        for (int i = 0; i < D; ++i) {
+            if (b + i < nt) {
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const int s = 2 * (b + i) + h;
+                    const int slot = (2 * i + h) & (RING - 1);
+                    if (s + RING <= nst)
+                        wait_mem<(RING - 1) * XB>();
+                    else
+                        wait_mem<0>();
+                    v8h xv[2][TB];
+#pragma unroll
+                    for (int j = 0; j < 2; ++j) {
+                        const int oct = FMT == kW8C ? 2 * q + j : 4 * j + q;
+#pragma unroll
+                        for (int tb = 0; tb < TB; ++tb)
+                            xv[j][tb] = *reinterpret_cast<const v8h *>(xread + slot * SLOT + tb * 2048 + ((oct ^ swz) << 4));
+                    }
+                    wait_lds();  // the operands are in registers: their slot may be overwritten
+                    if (s + RING < nst) copy_stage(s + RING, slot);
+#pragma unroll
+                    for (int j = 0; j < 2; ++j) {
+#pragma unroll
+                        for (int r = 0; r < R; ++r) {
+                            v8h fa;
+                            h2 sc = {(_Float16)1.0f, (_Float16)1.0f};
+                            if (FMT == kW4G32) sc = as_h2(__builtin_amdgcn_perm(0u, sv[i][r][h], j ? 0x03020302u : 0x01000100u));
+                            if (FMT == kW8C)
+                                fa = dequant8(wv[i][r][h][2 * j], wv[i][r][h][2 * j + 1]);
+                            else
+                                fa = dequant4<FMT == kW4G32>(wv[i][r][0][2 * h + j], sc);
+#pragma unroll
+                            for (int tb = 0; tb < TB; ++tb) acc[r][tb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(xv[j][tb], fa, acc[r][tb], 0, 0, 0);
+                        }
+                    }
+                }
+                if (b + i + D < nt) load_w(i, t0 + b + i + D);
+            }
+        }
+    }
+    __syncthreads();  // every wavefront is done with its ring
+    float *red = reinterpret_cast<float *>(lds);
+    put_partials<R, TB>(red, acc, wave, lane);
+    __syncthreads();
+    finish<R, TB, float, FMT != kW4G32>(a, red, blockDim.x >> 6, rt0);
+}
+
+// ---------------------------------------------------------------- int8 activations
+// The quantized activations arrive in MFMA operand order (KiB tiles), so both operands go from memory
+// straight into registers, D steps of 128 k ahead, every load instruction one contiguous KiB.  Codes of
+// 4-bit weights are expanded as in gemm_i8.hip (sums times 16).
+template <bool W4, int TB, int R, int D, int MAXT>
+__global__ __launch_bounds__(MAXT) void skinny_i8_kernel(SkinnyArgs a) {
+    constexpr int WV = W4 ? 1 : 2;
+    extern __shared__ u32x4 lds[];
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int rt0 = blockIdx.x * R;
+    const int t0 = wave * a.steps_q + min(wave, a.steps_rem);
+    const int nt = a.steps_q + (wave < a.steps_rem ? 1 : 0);
+    const int XT = a.Kp / 64;
+
+    const u32x4 *wrow[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) wrow[r] = a.w + (size_t)min(rt0 + r, a.RT - 1) * a.rt_stride * 64;
+    u32x4 wv[D][R][WV], xv[D][TB][2];
+    auto load = [&](int slot, int t) __attribute__((always_inline)) {
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+#pragma unroll
+            for (int v = 0; v < WV; ++v) wv[slot][r][v] = __builtin_nontemporal_load(wrow[r] + (size_t)(W4 ? t : 2 * t + v) * 64 + lane);
+#pragma unroll
+        for (int tb = 0; tb < TB; ++tb)
+#pragma unroll
+            for (int v = 0; v < 2; ++v) xv[slot][tb][v] = a.x[((size_t)tb * XT + 2 * t + v) * 64 + lane];
+    };
+    v4i acc[R][TB];
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+#pragma unroll
+        for (int tb = 0; tb < TB; ++tb) acc[r][tb] = v4i{0, 0, 0, 0};
+#pragma unroll
+    for (int i = 0; i < D; ++i)
+        if (i < nt) load(i, t0 + i);
+    for (int b = 0; b < nt; b += D) {
+#pragma unroll
+        for (int i = 0; i < D; ++i) {
+            if (b + i < nt) {
+#pragma unroll
+                for (int v = 0; v < 2; ++v) {  // k steps of 64
+#pragma unroll
+                    for (int r = 0; r < R; ++r) {
+                        v4i fw;
+                        if (W4) {
+                            const uint32_t px = wv[i][r][0][2 * v], py = wv[i][r][0][2 * v + 1];
+                            fw[0] = (int)(((px << 4) & 0xF0F0F0F0u) ^ 0x80808080u);
+                            fw[1] = (int)((px & 0xF0F0F0F0u) ^ 0x80808080u);
+                            fw[2] = (int)(((py << 4) & 0xF0F0F0F0u) ^ 0x80808080u);
+                            fw[3] = (int)((py & 0xF0F0F0F0u) ^ 0x80808080u);
+                        } else {
+                            fw = __builtin_bit_cast(v4i, wv[i][r][W4 ? 0 : v]);
+                        }
+#pragma unroll
+                        for (int tb = 0; tb < TB; ++tb)
+                            acc[r][tb] = __builtin_amdgcn_mfma_i32_16x16x64_i8(__builtin_bit_cast(v4i, xv[i][tb][v]), fw, acc[r][tb], 0, 0, 0);
+                    }
+                }
+                if (b + i + D < nt) load(i, t0 + b + i + D);
+            }
+        }
+    }
+    int *red = reinterpret_cast<int *>(lds);
+    put_partials<R, TB>(red, acc, wave, lane);
+    __syncthreads();
+    finish<R, TB, int, true>(a, red, blockDim.x >> 6, rt0);
+}
+
+constexpr size_t kLdsLimit = 160 * 1024;
+
+void split_steps(SkinnyArgs &a, int steps, int waves) {
+    a.steps_q = steps / waves;
+    a.steps_rem = steps % waves;
+}
+
+// Wavefronts per workgroup: at most `most`, every one with the same number of steps if it divides.
+int waves_for(int steps, int most) {
+    const int forced = tuning().skinny_waves;
+    if (forced > 0 && forced < most) most = forced;
+    const int w = steps < most ? steps : most;
+    const int per = (steps + w - 1) / w;
+    return (steps + per - 1) / per;
+}
+
+template <int FMT, int XB, int R>
+hipError_t launch_f16(SkinnyArgs a, hipStream_t st) {
+    constexpr int TB = (XB + 1) / 2;
+    constexpr int RING = XB <= 2 ? 4 : 2;
+    constexpr int D0 = R == 1 ? 8 : R <= 3 ? 4 : 2, D = FMT == kW8C && D0 > 2 ? D0 / 2 : D0;
+    constexpr bool kWide = R == 1 && XB <= 4 && FMT != kW8C;  // few enough registers for 16 wavefronts
+    constexpr int MAXT = kWide ? 1024 : 512;
+    constexpr size_t ring = RING * TB * 2048, red = (size_t)R * TB * 1024, per_wave = ring > red ? ring : red;
+    constexpr int most = (int)(kLdsLimit / per_wave) < MAXT / 64 ? (int)(kLdsLimit / per_wave) : MAXT / 64;
+    const int steps = (a.K + 127) / 128, waves = waves_for(steps, most);
+    split_steps(a, steps, waves);
+    if (const hipError_t e = allow_dynamic_lds<skinny_f16_kernel<FMT, XB, R, RING, D, MAXT>>(kLdsLimit); e != hipSuccess) return e;
+    skinny_f16_kernel<FMT, XB, R, RING, D, MAXT><<<dim3((unsigned)((a.RT + R - 1) / R)), dim3((unsigned)(waves * 64)), waves * per_wave, st>>>(a);
+    return hipGetLastError();
+}
+
+template <bool W4, int TB, int R>
+hipError_t launch_i8(SkinnyArgs a, hipStream_t st) {
+    constexpr int VECS = R * (W4 ? 1 : 2) + 2 * TB;  // vectors per step
+    constexpr int D = VECS <= 4 ? 4 : VECS <= 6 ? 3 : VECS <= 14 ? 2 : R * TB >= 12 ? 1 : 2;
+    constexpr bool kWide = R == 1 && TB <= 2;
+    constexpr int MAXT = kWide ? 1024 : 512;
+    constexpr size_t per_wave = (size_t)R * TB * 1024;
+    const int steps = a.Kp / 128, waves = waves_for(steps, MAXT / 64);
+    split_steps(a, steps, waves);
+    if (const hipError_t e = allow_dynamic_lds<skinny_i8_kernel<W4, TB, R, D, MAXT>>(kLdsLimit); e != hipSuccess) return e;
+    skinny_i8_kernel<W4, TB, R, D, MAXT><<<dim3((unsigned)((a.RT + R - 1) / R)), dim3((unsigned)(waves * 64)), waves * per_wave, st>>>(a);
+    return hipGetLastError();
+}
+
+// Row tiles per workgroup, of the counts built: the busiest compute unit has `load` row tiles of weights
+// to pull from memory and load / r times the token rows from L2, which deliver a byte about
+// 2.5 times as fast (fitted to the sweep over r = 1 .. 8 of layers of 2304 to 28672 channels at 12 to 64 token rows).
+template <int... RS>
+int pick_row_tiles(const SkinnyArgs &a, float weight_bytes, float token_bytes, int num_cus, std::integer_sequence<int, RS...>) {
+    const int forced = tuning().skinny_row_tiles;
+    int best = 0;
+    float best_cost = 0.0f;
+    for (const int r : {RS...}) {
+        if (a.gated_act >= 0 && r % 2) continue;
+        if (forced == r) return r;
+        // many rounds: balance does not matter, fewer registers and more workgroups per compute unit do
+        // (128256 channels at 12 and 32 token rows, 4-bit weights: 54 and 61 us with 4, 61 and 69 us with 7 or 8)
+        if (r > 4 && a.RT >= 16 * num_cus) continue;
+        const long wgs = (a.RT + r - 1) / r, rounds = (wgs + num_cus - 1) / num_cus;
+        const float cost = (float)rounds * ((float)r * 16.0f * weight_bytes + 0.4f * (float)a.M * token_bytes);
+        if (best == 0 || cost < best_cost) best = r, best_cost = cost;
+    }
+    return best;
+}
+
+template <int FMT, int XB, int... RS>
+hipError_t f16_rows(const SkinnyArgs &a, int num_cus, hipStream_t st, std::integer_sequence<int, RS...> rs) {
+    const int pick = pick_row_tiles(a, FMT == kW8C ? 1.0f : FMT == kW4G32 ? 0.5625f : 0.5f, 2.0f, num_cus, rs);
+    hipError_t e = hipErrorInvalidValue;
+    ((pick == RS ? (void)(e = launch_f16<FMT, XB, RS>(a, st)) : (void)0), ...);
+    return e;
+}
+
+template <bool W4, int TB, int... RS>
+hipError_t i8_rows(const SkinnyArgs &a, int num_cus, hipStream_t st, std::integer_sequence<int, RS...> rs) {
+    const int pick = pick_row_tiles(a, W4 ? 0.5f : 1.0f, 1.0f, num_cus, rs);
+    hipError_t e = hipErrorInvalidValue;
+    ((pick == RS ? (void)(e = launch_i8<W4, TB, RS>(a, st)) : (void)0), ...);
+    return e;
+}
+
+// Row tiles per workgroup the kernels are built for (registers and LDS bound them: R * TB sums per lane)
+typedef std::integer_sequence<int, 1, 2, 3, 4, 5, 6, 7, 8> Rows2;  // up to 32 token rows
+typedef std::integer_sequence<int, 1, 2, 3, 4, 5, 6, 7> Rows2W8;
+typedef std::integer_sequence<int, 1, 2, 3, 4, 5, 6> Rows3;
+typedef std::integer_sequence<int, 1, 2, 3, 4> Rows4;
+
+template <int FMT>
+hipError_t f16_any(const SkinnyArgs &a, int num_cus, hipStream_t st) {
+    switch ((a.M + 7) / 8) {
+        case 2: return f16_rows<FMT, 2>(a, num_cus, st, Rows2());
+        case 3: case 4: return f16_rows<FMT, 4>(a, num_cus, st, std::conditional_t<FMT == kW8C, Rows2W8, Rows2>());
+        case 5: case 6: return f16_rows<FMT, 6>(a, num_cus, st, Rows3());
+        case 7: case 8: return f16_rows<FMT, 8>(a, num_cus, st, Rows4());
+    }
+    return hipErrorInvalidValue;
+}
+
+template <bool W4>
+hipError_t i8_any(const SkinnyArgs &a, int num_cus, hipStream_t st) {
+    switch ((a.M + 15) / 16) {
+        case 1: return i8_rows<W4, 1>(a, num_cus, st, Rows2());
+        case 2: return i8_rows<W4, 2>(a, num_cus, st, Rows2());
+        case 3: return i8_rows<W4, 3>(a, num_cus, st, Rows3());
+        case 4: return i8_rows<W4, 4>(a, num_cus, st, Rows4());
+    }
+    return hipErrorInvalidValue;
+}
+
+SkinnyArgs make_args(const Geometry &g, const void *packed, const void *x, const float *sx, int M, void *out,
+                     const void *residual, int gated_act) {
+    SkinnyArgs a;
+    a.w = static_cast<const u32x4 *>(packed);
+    a.x = static_cast<const u32x4 *>(x);
+    a.sw = reinterpret_cast<const float *>(static_cast<const char *>(packed) + g.scale_off);
+    a.sx = sx;
+    a.res = static_cast<const _Float16 *>(residual);
+    a.out = out;
+    a.M = M;
+    a.N = g.N;
+    a.K = g.K;
+    a.Kp = g.Kp;
+    a.KT = g.KT;
+    a.RT = g.RT;
+    a.rt_stride = g.rt_stride;
+    a.steps_q = a.steps_rem = 0;
+    a.sw_mul = 1.0f;
+    a.gated_act = g.pair_half ? gated_act : -1;
+    return a;
+}
+
+}  // namespace
+
+// Level with the large kernels' 256-channel tiles where those fill the chip: at 64 token rows 28672 channels
+// take 32 against 48 us (int4 groups, binary16 activations), 35.5 / 37.4 us (int8), 27.0 / 27.4 us (int4 x
+// int8); narrow layers are far apart (4096 x 14336: 27 / 142, 28 / 90, 24 / 68 us).  128256 channels
+// with int8 activations cross over at about 32 rows (8-bit weights 101 / 112 us at 32, 126 / 117 us at 64).
+bool skinny_product(const Geometry &g, int M, bool int8_activations, int num_cus) {
+    if (tuning().gemm_variant != 0) return false;  // a large kernel is asked for by name
+    const int forced = tuning().skinny_max_m;
+    const int most = forced >= 0 ? forced : int8_activations && g.RT >= 16 * num_cus ? 32 : kSkinnyMaxM;
+    return M <= most && M <= kSkinnyMaxM;
+}
+
+hipError_t launch_skinny_f16(const Geometry &g, const void *packed, const void *x, int M, void *y, const void *residual,
+                             int gated_act, int num_cus, hipStream_t st) {
+    const SkinnyArgs a = make_args(g, packed, x, nullptr, M, y, residual, gated_act);
+    if (g.fmt == kW8C) return f16_any<kW8C>(a, num_cus, st);
+    return g.fmt == kW4C ? f16_any<kW4C>(a, num_cus, st) : f16_any<kW4G32>(a, num_cus, st);
+}
+
+hipError_t launch_skinny_i8(const Geometry &g, const void *packed, const int8_t *xq_tiled, const float *sx, int M,
+                            void *y, const void *residual, int gated_act, int num_cus, hipStream_t st) {
+    SkinnyArgs a = make_args(g, packed, xq_tiled, sx, M, y, residual, gated_act);
+    if (g.fmt == kW4C) {
+        a.sw_mul = 0.0625f;
+        return i8_any<true>(a, num_cus, st);
+    }
+    return i8_any<false>(a, num_cus, st);
+}
+
+}  // namespace qfc

@@ -131,6 +131,9 @@ struct Tuning {
     Tunable act_quant_rows{0};  // 0: automatic
     Tunable attn_chunks{-1};    // prefill attention, walks cut into chunks: -1 automatic, 0 never, 1 always
     Tunable attn_pair{-1};      // prefill attention, two blocks per workgroup: -1 automatic, 0 never, 1 always
+    Tunable skinny_waves{0};    // few token rows: most wavefronts per workgroup (0: automatic)
+    Tunable skinny_row_tiles{0};  // few token rows: row tiles per workgroup (0: automatic)
+    Tunable skinny_max_m{-1};   // largest M of those kernels (-1: automatic; 0: never)
     Tunable gemv_half{-1};      // half-unit items of the decode kernel: -1 automatic, 0 never, 1 where possible
 };
 Tuning &tuning();
@@ -339,5 +342,13 @@ hipError_t launch_gemm_i8(const Geometry &g, const void *packed, const int8_t *x
 // Returns hipErrorNotSupported for a gated output when K is not a multiple of 128.
 hipError_t launch_gemm_f16(const Geometry &g, const void *packed, const void *x, int M, void *y,
                            const void *residual, int gated_act, int num_cus, hipStream_t st);
+
+// Few token rows (9 .. kSkinnyMaxM): see gemm_skinny.hip.  Arguments as the two launchers above.
+constexpr int kSkinnyMaxM = 64;
+bool skinny_product(const Geometry &g, int M, bool int8_activations, int num_cus);
+hipError_t launch_skinny_f16(const Geometry &g, const void *packed, const void *x, int M, void *y, const void *residual,
+                             int gated_act, int num_cus, hipStream_t st);
+hipError_t launch_skinny_i8(const Geometry &g, const void *packed, const int8_t *xq_tiled, const float *sx, int M,
+                            void *y, const void *residual, int gated_act, int num_cus, hipStream_t st);
 
 }  // namespace qfc

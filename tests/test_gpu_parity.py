@@ -1595,3 +1595,41 @@ def test_probe_mfma_runs_and_rejects_bad_arguments():
             binding.qfc_probe_mfma(*args, ticks)
     with pytest.raises(ValueError):
         binding.qfc_probe_mfma(0, True, 10, 4097, ticks)
+
+
+@pytest.mark.parametrize("fmt,mode", [("w4g32", None), ("w4c", None), ("w8c", binding.QFC_COMPUTE_FP16_DEQUANT),
+                                      ("w8c", None), ("w4c", binding.QFC_COMPUTE_INT8_ACT)])
+@pytest.mark.parametrize("M,N,K,row_tiles", [(9, 1, 32, 0), (16, 50, 160, 1), (17, 100, 96, 3), (33, 130, 416, 2),
+                                             (32, 1000, 1184, 7), (48, 264, 2304, 5), (64, 96, 14336, 4), (63, 300, 544, 0)])
+def test_few_token_rows_match_oracle(fmt, mode, M, N, K, row_tiles):
+    """The kernels for 9 to 64 token rows at the edges of their blocks of 8 and 16 rows, with K ending inside a step,
+    fewer steps than wavefronts, a last workgroup that is not full, and a residual."""
+    print(f"few token rows {fmt} mode={mode} M={M} N={N} K={K} row tiles={row_tiles}", flush=True)
+    wq, s = synth.weights(6000, M, N, synth.FC("t", K, N, fmt))
+    x = synth.activations(6000, M, N, M, K)
+    res = synth.activations(6000, M, N + 1, M, N)
+    layer = _layer(wq, s, fmt, max_m=M, mode=mode)
+    int8 = mode == binding.QFC_COMPUTE_INT8_ACT or (fmt == "w8c" and mode is None)
+    ref = oracle.fc_int8_act(x, wq, s)[3] if int8 else oracle.fc_weight_only(x, wq, s, _group(fmt))
+    xd, rd = torch.from_numpy(x).to(DEV), torch.from_numpy(res).to(DEV)
+    guard = torch.full((M + 1, N), 77.0, dtype=torch.float16, device=DEV)  # the row behind y stays as it is
+    y = guard[:M]
+    binding.qfc_tune(8, row_tiles)
+    try:
+        binding.qfc_forward(layer.handle, xd, y)
+        plain = y.cpu().numpy()
+        binding.qfc_forward_fused(layer.handle, xd, y, residual=rd)
+        torch.cuda.synchronize()
+    finally:
+        binding.qfc_tune(8, 0)
+    assert _E(plain, ref) <= TOL
+    assert _E(y.cpu().numpy(), ref + res.astype(np.float64)) <= TOL
+    assert bool((guard[M] == 77.0).all())
+    if int8:  # exact sums and the same rounding steps: the same bits as the large kernel
+        binding.qfc_tune(9, 0)
+        try:
+            big = _forward(layer, x)
+        finally:
+            binding.qfc_tune(9, -1)
+        assert np.array_equal(plain.view(np.uint16), big.view(np.uint16))
+    layer.close()
