@@ -34,11 +34,12 @@ constexpr float kNegBig = -1.0e30f;
 static_assert(kAttnMaxSplits <= 64, "the combine kernel takes one split per lane");
 
 // ---------------------------------------------------------------- rotary embedding + layouts
+// Few tokens (decode steps, short prompts): latency is all there is.
 // One thread per (b, s, head, i), i < d / 2: the pair (i, i + d / 2) of one head of one token.
-__global__ __launch_bounds__(256) void rope_qkv_kernel(const _Float16 *__restrict__ qkv, int B, int S, int h_q,
-                                                       int h_kv, int d, int C, int pos0, double log_base,
-                                                       _Float16 *__restrict__ q_out, _Float16 *__restrict__ kc,
-                                                       _Float16 *__restrict__ vc) {
+__global__ __launch_bounds__(256) void rope_qkv_few_kernel(const _Float16 *__restrict__ qkv, int B, int S, int h_q,
+                                                           int h_kv, int d, int C, int pos0, double log_base,
+                                                           _Float16 *__restrict__ q_out, _Float16 *__restrict__ kc,
+                                                           _Float16 *__restrict__ vc) {
     const int half = d / 2;
     const int heads = h_q + 2 * h_kv;
     const long total = (long)B * S * heads * half;
@@ -75,6 +76,113 @@ __global__ __launch_bounds__(256) void rope_qkv_kernel(const _Float16 *__restric
     }
     dst[i] = y0;
     dst[i + half] = y1;
+}
+
+// Bound: HBM (read once, written once), once the angles are out of the way: cos and sin in fp64 cost
+// more than everything else together when every head of a token evaluates them (S = 1024, 40 heads to
+// rotate: 38 us; 6000: 200 us, where reading and writing 147 MB takes 28).  So a workgroup takes T
+// tokens, evaluates their d / 2 angles once into LDS, and rotates all heads with them, 16 bytes of each half
+// of a head per thread (9 and ROPE_6000 us).  Few tokens: the heads are split over several workgroups.
+// Values: a workgroup takes the tokens of one block of 64 cache positions of one head, turns them in LDS and
+// writes runs of up to 128 bytes of the transposed cache instead of single values 128 bytes apart.
+typedef _Float16 rope_h2 __attribute__((ext_vector_type(2)));
+struct RopeArgs {
+    const _Float16 *qkv;
+    _Float16 *q_out, *kc, *vc;
+    int B, S, h_q, h_kv, d, C, pos0;
+    int T, rot_wgs, pblocks;  // tokens per workgroup, workgroups that rotate, cache blocks touched
+    double log_base;
+};
+__global__ __launch_bounds__(256) void rope_qkv_kernel(RopeArgs a) {
+    extern __shared__ double rope_lds[];
+    const int half = a.d / 2, heads = a.h_q + 2 * a.h_kv, g = a.h_q / a.h_kv;
+    if ((int)blockIdx.x < a.rot_wgs) {
+        const int tok0 = (int)blockIdx.x * a.T;
+        const int nt = min(a.T, a.B * a.S - tok0);
+        const int rot = a.h_q + a.h_kv, vecs = half / 8;
+        // thread = octet v of the heads r, r + rows, ... of the workgroup's tokens (no divisions in the loop)
+        const int rows = 256 / vecs, v = threadIdx.x % vecs;
+        int head = threadIdx.x / vecs, t = 0;
+        auto wrap = [&](int &h, int &tt) {
+            while (h >= rot) h -= rot, ++tt;
+        };
+        wrap(head, t);
+        const int b0 = tok0 / a.S, s0 = tok0 % a.S;
+        auto source = [&](int h, int tt) { return a.qkv + ((size_t)(tok0 + tt) * heads + h) * a.d + 8 * v; };
+        h8 x0, x1;  // of the thread's next item: requested before the angles are evaluated
+        if (t < nt) {
+            x0 = *reinterpret_cast<const h8 *>(source(head, t));
+            x1 = *reinterpret_cast<const h8 *>(source(head, t) + half);
+        }
+        // angle = pos * base^(-2 i / d), in double so that long contexts keep the low bits of the angle
+        for (int e = threadIdx.x; e < nt * half; e += 256) {
+            const int i = e % half, slot = e - i + (i % 8) * vecs + i / 8;  // (threads read the octet i / 8 side by side)
+            double sn, cs;
+            sincos((double)(a.pos0 + (tok0 + e / half) % a.S) * exp(-2.0 * (double)i / (double)a.d * a.log_base), &sn, &cs);
+            rope_lds[2 * slot] = cs;
+            rope_lds[2 * slot + 1] = sn;
+        }
+        __syncthreads();
+        while (t < nt) {
+            const h8 u0 = x0, u1 = x1;
+            int head1 = head + rows, t1 = t;
+            wrap(head1, t1);
+            if (t1 < nt) {
+                x0 = *reinterpret_cast<const h8 *>(source(head1, t1));
+                x1 = *reinterpret_cast<const h8 *>(source(head1, t1) + half);
+            }
+            int b = b0, s = s0 + t;
+            while (s >= a.S) s -= a.S, ++b;
+            const double *ang = rope_lds + 2 * (t * half + v);
+            h8 y0, y1;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const double cs = ang[2 * vecs * i], sn = ang[2 * vecs * i + 1], d0 = (double)(float)u0[i], d1 = (double)(float)u1[i];
+                y0[i] = (_Float16)(float)(d0 * cs - d1 * sn);
+                y1[i] = (_Float16)(float)(d1 * cs + d0 * sn);
+            }
+            _Float16 *dst;
+            if (head < a.h_q)
+                dst = a.q_out + ((size_t)(b * a.h_kv + head / g) * (a.S * g) + (s * g + head % g)) * a.d;
+            else
+                dst = a.kc + ((size_t)(b * a.h_kv + head - a.h_q) * a.C + (a.pos0 + s)) * a.d;
+            *reinterpret_cast<h8 *>(dst + 8 * v) = y0;
+            *reinterpret_cast<h8 *>(dst + half + 8 * v) = y1;
+            head = head1, t = t1;
+        }
+        return;
+    }
+    // value heads: workgroup = (b, kv, block of 64 cache positions, 64 values)
+    const int w = (int)blockIdx.x - a.rot_wgs, dc = a.d / 64;
+    const int d0 = (w % dc) * 64, pb = w / dc % a.pblocks, kv = w / (dc * a.pblocks) % a.h_kv, b = w / (dc * a.pblocks * a.h_kv);
+    const int p0 = (a.pos0 / 64 + pb) * 64;
+    const int first = max(a.pos0 - p0, 0), last = min(a.pos0 + a.S - p0, 64);  // columns of the block to write
+    // LDS rows of one token each, four bytes longer than 64 values: eight rows apart is eight banks apart
+    constexpr int pitch = 64 + 2;
+    _Float16 *tile = reinterpret_cast<_Float16 *>(rope_lds);
+    const _Float16 *src0 = a.qkv + ((size_t)b * a.S * heads + a.h_q + a.h_kv + kv) * a.d + d0;
+    for (int e = threadIdx.x; e < (last - first) * 8; e += 256) {
+        const int c = first + e / 8, v = e % 8;
+        const h8 x = *reinterpret_cast<const h8 *>(src0 + (size_t)(p0 + c - a.pos0) * heads * a.d + 8 * v);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) *reinterpret_cast<rope_h2 *>(tile + c * pitch + 8 * v + 2 * i) = rope_h2{x[2 * i], x[2 * i + 1]};
+    }
+    __syncthreads();
+    _Float16 *dst0 = a.vc + (((size_t)(b * a.h_kv + kv) * (a.C / 64) + p0 / 64) * a.d + d0) * 64;
+    const int o0 = first / 8, no = (last + 7) / 8 - o0;  // octets of columns
+    for (int e = threadIdx.x; e < 64 * no; e += 256) {
+        const int o = o0 + e % no, dd = e / no;
+        _Float16 *dst = dst0 + dd * 64 + 8 * o;
+        if (8 * o >= first && 8 * o + 8 <= last) {
+            h8 y;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) y[i] = tile[(8 * o + i) * pitch + dd];
+            *reinterpret_cast<h8 *>(dst) = y;
+        } else {
+            for (int i = 0; i < 8; ++i)
+                if (8 * o + i >= first && 8 * o + i < last) dst[i] = tile[(8 * o + i) * pitch + dd];
+        }
+    }
 }
 
 // cos and sin of the rotary angles of `positions` positions: table[(pos * d / 2 + i) * 2] = cos, + 1 = sin
@@ -793,10 +901,29 @@ size_t attn_prefill_workspace(int G, int M, int d, int num_cus) {
 
 hipError_t launch_rope_qkv(const void *qkv, int B, int S, int h_q, int h_kv, int d, int C, int pos0, float base,
                            void *q_out, void *kc, void *vc, hipStream_t st) {
-    const long total = (long)B * S * (h_q + 2 * h_kv) * (d / 2);
-    rope_qkv_kernel<<<(unsigned)((total + 255) / 256), 256, 0, st>>>(
-        static_cast<const _Float16 *>(qkv), B, S, h_q, h_kv, d, C, pos0, log((double)base),
-        static_cast<_Float16 *>(q_out), static_cast<_Float16 *>(kc), static_cast<_Float16 *>(vc));
+    const long total = (long)B * S;
+    if (total < 128) {  // (level at about 128 tokens: 77 tokens of 8 + 4 heads of 256 4.8 against 5.6 us)
+        const long pairs = total * (h_q + 2 * h_kv) * (d / 2);
+        rope_qkv_few_kernel<<<(unsigned)((pairs + 255) / 256), 256, 0, st>>>(
+            static_cast<const _Float16 *>(qkv), B, S, h_q, h_kv, d, C, pos0, log((double)base),
+            static_cast<_Float16 *>(q_out), static_cast<_Float16 *>(kc), static_cast<_Float16 *>(vc));
+        return hipGetLastError();
+    }
+    RopeArgs a;
+    a.qkv = static_cast<const _Float16 *>(qkv);
+    a.q_out = static_cast<_Float16 *>(q_out);
+    a.kc = static_cast<_Float16 *>(kc);
+    a.vc = static_cast<_Float16 *>(vc);
+    a.B = B, a.S = S, a.h_q = h_q, a.h_kv = h_kv, a.d = d, a.C = C, a.pos0 = pos0;
+    a.log_base = log((double)base);
+    // as many tokens per workgroup as one evaluation of an angle per thread covers, once that still gives
+    // several workgroups per compute unit
+    const int most = 512 / d;
+    a.T = total / 512 < 1 ? 1 : total / 512 > most ? most : (int)(total / 512);
+    a.rot_wgs = (int)((total + a.T - 1) / a.T);
+    a.pblocks = (pos0 + S - 1) / 64 - pos0 / 64 + 1;
+    const size_t angles = (size_t)a.T * d * sizeof(double), tile = (size_t)64 * 66 * 2;
+    rope_qkv_kernel<<<(unsigned)(a.rot_wgs + B * h_kv * a.pblocks * (d / 64)), 256, angles > tile ? angles : tile, st>>>(a);
     return hipGetLastError();
 }
 

@@ -1633,3 +1633,11 @@ def test_few_token_rows_match_oracle(fmt, mode, M, N, K, row_tiles):
             binding.qfc_tune(9, -1)
         assert np.array_equal(plain.view(np.uint16), big.view(np.uint16))
     layer.close()
+
+
+@pytest.mark.parametrize("B,S,h_q,h_kv,d,C,pos0", [(1, 128, 3, 1, 64, 192, 64), (1, 1100, 6, 2, 64, 1152, 13),
+                                                   (3, 50, 8, 2, 128, 128, 61), (2, 700, 4, 4, 128, 768, 7), (1, 257, 8, 4, 256, 320, 63)])
+def test_rope_qkv_many_tokens(B, S, h_q, h_kv, d, C, pos0):
+    """128 tokens and more share the evaluation of an angle among the heads of a token: one and several tokens per
+    workgroup, workgroups that span sequences, cache blocks that the tokens fill in part."""
+    test_rope_qkv_layout(B, S, h_q, h_kv, d, C, pos0)
