@@ -130,6 +130,15 @@ __device__ __forceinline__ u32x4 weighted_input8(const u32x4 &w, const u32x4 &x,
     return __builtin_bit_cast(u32x4, r);
 }
 
+// Sum over the 16 lanes of a row of the wavefront, in every one of them.
+__device__ __forceinline__ float row_sum16(float x) {
+    x += __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, x), 0x128, 0xf, 0xf, true));  // row_ror:8
+    x += __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, x), 0x124, 0xf, 0xf, true));
+    x += __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, x), 0x122, 0xf, 0xf, true));
+    x += __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, x), 0x121, 0xf, 0xf, true));
+    return x;
+}
+
 struct GemvArgs {
     const u32x4 *packed;
     const u32x4 *x;     // binary16 [M, K] as 16-byte vectors (8 values)
@@ -160,13 +169,15 @@ struct GemvArgs {
 // fusion, section 3.6 of the paper: element-wise operators of two branches merged into the
 // fully connected operator).  PRO = 2: RMS normalization merged into the layer: normalizing scales
 // a row by one number rs, which commutes with the product, so the row goes into LDS multiplied by
-// the normalization weight only and the output is multiplied by rs at the end; every workgroup
-// computes the rows' sums of squares for itself (one pass over x).
+// the normalization weight only and the output is multiplied by rs at the end.  The wavefronts of a
+// workgroup stage every value of the rows exactly once between them, so each adds up the squares of what
+// it stages: no pass over x of its own.
 template <int M, int FMT, int PRO, int OCT>  // OCT: octets (8 k) per item
 struct XStage {
     static constexpr int XV = M * OCT / 64;               // 16-byte vectors per lane per unit
+    static constexpr int GV = PRO == 1 ? XV : PRO == 2 ? OCT / 64 : 1;  // (the weight is the same for all rows)
     u32x4 v[XV];
-    u32x4 g[PRO ? XV : 1];
+    u32x4 g[GV];
 
     // global -> registers (zeros beyond K)
     __device__ __forceinline__ void load(const GemvArgs &a, int unit, int lane) {
@@ -179,7 +190,7 @@ struct XStage {
             const u32x4 zero = {0, 0, 0, 0};
             v[i] = o_base + o < K8 ? a.x[(size_t)m * K8 + o_base + o] : zero;
             if (PRO == 1) g[i] = o_base + o < K8 ? a.gate[(size_t)m * K8 + o_base + o] : zero;
-            if (PRO == 2) g[i] = o_base + o < K8 ? a.gate[o_base + o] : zero;
+            if (PRO == 2 && m == 0) g[i] = o_base + o < K8 ? a.gate[o_base + o] : zero;
         }
     }
     // global -> this wavefront's LDS region without passing registers (no prologue): vector p of
@@ -201,15 +212,24 @@ struct XStage {
             copy16_to_lds(a.x, off, __builtin_amdgcn_readfirstlane(lds_base + i * 1024));
         }
     }
-    // registers -> this wavefront's LDS region, A-operand order
-    __device__ __forceinline__ void store(u32x4 *lds, int lane, int act, float offset) const {
+    // registers -> this wavefront's LDS region, A-operand order; ss: sums of squares of the rows (PRO = 2)
+    __device__ __forceinline__ void store(u32x4 *lds, int lane, int act, float offset, float (&ss)[M]) const {
 #pragma unroll
         for (int i = 0; i < XV; ++i) {
             const int p = i * 64 + lane;
             const int m = p / OCT, o = p % OCT;
             int slot = o;
             if (FMT == kW8C) slot = (o & ~7) | ((o & 1) << 2) | ((o >> 1) & 3);
-            lds[slot * M + m] = PRO == 1 ? gated_input8(g[i], v[i], act) : PRO == 2 ? weighted_input8(g[i], v[i], offset) : v[i];
+            if constexpr (PRO == 1) {
+                lds[slot * M + m] = gated_input8(g[i], v[i], act);
+            } else if constexpr (PRO == 2) {
+                const v8h hx = __builtin_bit_cast(v8h, v[i]);
+#pragma unroll
+                for (int e = 0; e < 8; ++e) ss[i * 64 / OCT] = fmaf((float)hx[e], (float)hx[e], ss[i * 64 / OCT]);
+                lds[slot * M + m] = weighted_input8(g[i % GV], v[i], offset);
+            } else {
+                lds[slot * M + m] = v[i];
+            }
         }
     }
 };
@@ -254,39 +274,26 @@ __global__ __launch_bounds__(BIG ? 1024 : PRO && M > 4 ? 256 : 512) void gemv_ke
 #pragma unroll
         for (int i = 0; i < 4; ++i) acc[r][i] = 0.0f;
 
-    // Merged RMS normalization: the rows' sums of squares, by the whole workgroup (fp32; partial
-    // sums of the wavefronts are added in fixed order where they are used, at the end).
-    __shared__ float s_ss[PRO == 2 ? 8 : 1][M];
+    // Merged RMS normalization: the rows' sums of squares (fp32), 4 partial sums per wavefront, added in
+    // fixed order where they are used (rms_scale)
+    __shared__ v4f s_ss[PRO == 2 ? M : 1][PRO == 2 ? 8 : 1];
     static_assert(!(BIG && PRO), "up to 16 wavefronts only without a prologue");
-    if constexpr (PRO == 2) {
-        float ss[M];
+    float ss[M];
 #pragma unroll
-        for (int m = 0; m < M; ++m) ss[m] = 0.0f;
-        const int K8 = a.K / 8;
-        for (int v = threadIdx.x; v < M * K8; v += blockDim.x) {
-            const int m = v / K8;
-            const v8h hx = __builtin_bit_cast(v8h, a.x[v]);
-            float t = 0.0f;
-#pragma unroll
-            for (int i = 0; i < 8; ++i) t = fmaf((float)hx[i], (float)hx[i], t);
-#pragma unroll
-            for (int mm = 0; mm < M; ++mm)
-                if (mm == m) ss[mm] += t;
+    for (int m = 0; m < M; ++m) ss[m] = 0.0f;
+    auto rms_scale = [&](int m) {
+        float tot = 0.0f;
+        for (int w = 0; w < nwaves; ++w) {
+            const v4f p = s_ss[PRO == 2 ? m : 0][PRO == 2 ? w : 0];
+            tot += (p[0] + p[1]) + (p[2] + p[3]);
         }
-#pragma unroll
-        for (int m = 0; m < M; ++m) {
-            float t = ss[m];
-#pragma unroll
-            for (int off = 32; off > 0; off >>= 1) t += __shfl_xor(t, off, 64);
-            if (lane == 0) s_ss[wave][m] = t;
-        }
-        // (made visible to the other wavefronts by the barriers before the final reduction)
-    }
+        return 1.0f / sqrtf(tot / (float)a.K + a.norm_eps);
+    };
 
     // item = (unit, row tile); its vectors: (W4G32) 4 scale vectors, then weight tiles 0..nt-1.
     // `full` = all 8 tiles present: unconditional loads, so that the compiler can
     // count them and wait tile by tile instead of for everything.
-    auto load_item = [&](u32x4(&buf)[NV], int u, int r, auto full) {
+    auto load_item = [&](u32x4(&buf)[NV], int u, int r, auto full) __attribute__((always_inline)) {
         const int nt = full ? TILES : min(TILES, a.KT - TILES * u);
         const int U = HALF ? u >> 1 : u, h = HALF ? u & 1 : 0;  // unit, half of it
         const int ntU = HALF ? min(8, a.KT - 8 * U) : nt;       // weight tiles before the unit's scale tile
@@ -324,9 +331,9 @@ __global__ __launch_bounds__(BIG ? 1024 : PRO && M > 4 ? 256 : 512) void gemv_ke
             if (items > 1) load_item(nxt, R > 1 ? u0 : u0 + 1, R > 1 ? 1 : 0, kMaybePartial);
         }
     }
-    auto stage = [&]() {
+    auto stage = [&]() __attribute__((always_inline)) {
         // the wavefront's earlier LDS reads are done (same wavefront, in order)
-        xs.store(lds_x, lane, a.act, a.norm_offset);
+        xs.store(lds_x, lane, a.act, a.norm_offset, ss);
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
@@ -341,7 +348,7 @@ __global__ __launch_bounds__(BIG ? 1024 : PRO && M > 4 ? 256 : 512) void gemv_ke
         // D rows >= M are never used, so no masking or zeroing is needed.
         constexpr int XA = FMT == kW8C ? 2 : 4;
         const u32x4 *xrow = lds_x + q * M + (c % M);
-        auto load_xa = [&](v8h(&xa)[XA], int t) {
+        auto load_xa = [&](v8h(&xa)[XA], int t) __attribute__((always_inline)) {
 #pragma unroll
             for (int j = 0; j < XA; ++j)
                 xa[j] = __builtin_bit_cast(v8h, xrow[(FMT == kW8C ? t * 8 + j * 4 : (4 * t + j) * 4) * M]);
@@ -351,7 +358,7 @@ __global__ __launch_bounds__(BIG ? 1024 : PRO && M > 4 ? 256 : 512) void gemv_ke
         // step's dequantization instead of a stall.
         v4f d_prev = {0.0f, 0.0f, 0.0f, 0.0f};
         _Float16 s_prev = (_Float16)0.0f;
-        auto tile_math = [&](const v8h(&xa)[XA], int t) {
+        auto tile_math = [&](const v8h(&xa)[XA], int t) __attribute__((always_inline)) {
             if (FMT == kW4G32) {
                 const uint32_t wd[4] = {cur[t].x, cur[t].y, cur[t].z, cur[t].w};
 #pragma unroll
@@ -377,7 +384,7 @@ __global__ __launch_bounds__(BIG ? 1024 : PRO && M > 4 ? 256 : 512) void gemv_ke
                 accw = __builtin_amdgcn_mfma_f32_16x16x32_f16(xa[1], dequant_i8x8(cur[t].z, cur[t].w), accw, 0, 0, 0);
             }
         };
-        auto compute_full = [&]() {
+        auto compute_full = [&]() __attribute__((always_inline)) {
             // full unit: straight-line code, A operands fetched one tile ahead
             v8h xa[XA], xn[XA];
             load_xa(xa, 0);
@@ -389,7 +396,7 @@ __global__ __launch_bounds__(BIG ? 1024 : PRO && M > 4 ? 256 : 512) void gemv_ke
                 for (int j = 0; j < XA; ++j) xa[j] = xn[j];
             }
         };
-        auto compute_tail = [&]() {
+        auto compute_tail = [&]() __attribute__((always_inline)) {
 #pragma unroll
             for (int t = 0; t < TILES; ++t) {
                 if (t < nt) {
@@ -413,7 +420,7 @@ __global__ __launch_bounds__(BIG ? 1024 : PRO && M > 4 ? 256 : 512) void gemv_ke
                 else
                     xs.load(a, u, lane);
             }
-            auto staged = [&]() {
+            auto staged = [&]() __attribute__((always_inline)) {
                 if constexpr (COPY) {
                     wait_vmcnt<0>();  // only an empty counter says that the copies have landed
                     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -458,6 +465,13 @@ __global__ __launch_bounds__(BIG ? 1024 : PRO && M > 4 ? 256 : 512) void gemv_ke
         }
     }
 
+    if constexpr (PRO == 2) {
+#pragma unroll
+        for (int m = 0; m < M; ++m) {
+            const float t = row_sum16(ss[m]);
+            if (c == 0) reinterpret_cast<float *>(&s_ss[m][wave])[q] = t;
+        }
+    }
     // meet in LDS: red[wave][r][m][16 rows]; lane (c, q) holds token rows 4q .. 4q+3 of row c
     __syncthreads();
     float *red = reinterpret_cast<float *>(lds_all);
@@ -491,9 +505,7 @@ __global__ __launch_bounds__(BIG ? 1024 : PRO && M > 4 ? 256 : 512) void gemv_ke
                 s1 *= a.sw[n0 + halfd];
             }
             if constexpr (PRO == 2) {
-                float tot = 0.0f;
-                for (int w = 0; w < nwaves; ++w) tot += s_ss[w][m];
-                const float rs = 1.0f / sqrtf(tot / (float)a.K + a.norm_eps);
+                const float rs = rms_scale(m);
                 s0 *= rs;
                 s1 *= rs;
             }
@@ -536,9 +548,7 @@ __global__ __launch_bounds__(BIG ? 1024 : PRO && M > 4 ? 256 : 512) void gemv_ke
                     su *= a.sw[a.paired ? rt0 * 16 + 16 + cc : n + half];
                 }
                 if constexpr (PRO == 2) {
-                    float tot = 0.0f;
-                    for (int w = 0; w < nwaves; ++w) tot += s_ss[w][m];
-                    const float rs = 1.0f / sqrtf(tot / (float)a.K + a.norm_eps);
+                    const float rs = rms_scale(m);
                     sg *= rs;
                     su *= rs;
                 }
@@ -554,11 +564,7 @@ __global__ __launch_bounds__(BIG ? 1024 : PRO && M > 4 ? 256 : 512) void gemv_ke
         const int n = (rt0 + rr) * 16 + cc;
         if (n < a.N) {
             if (FMT != kW4G32) s *= a.sw[n];
-            if constexpr (PRO == 2) {
-                float tot = 0.0f;
-                for (int w = 0; w < nwaves; ++w) tot += s_ss[w][m];
-                s *= 1.0f / sqrtf(tot / (float)a.K + a.norm_eps);
-            }
+            if constexpr (PRO == 2) s *= rms_scale(m);
             if (a.res) s += (float)a.res[(size_t)m * a.N + n];
             a.y[(size_t)m * a.N + n] = (_Float16)s;
         }
