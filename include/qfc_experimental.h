@@ -32,7 +32,8 @@ extern "C" {
  *          qfc_attention_workspace_size follows the value set when it is called
  *   key 7  products of few token rows (9 .. 64): most wavefronts per workgroup (0 = automatic)
  *   key 8  the same: row tiles per workgroup (0 = automatic; 1 .. 8)
- *   key 9  the same: largest number of token rows they are used for (-1 automatic, 0 never) */
+ *   key 9  the same: largest number of token rows they are used for (-1 automatic, 0 never)
+ *   key 10 gated output at M <= 8: pairs of row tiles per decode workgroup (0 = automatic; 1, 2) */
 void qfc_tune(int32_t key, int32_t value);
 
 /* Measurement probe (bench.py --probe-mfma): `workgroups` workgroups of four wavefronts each issue

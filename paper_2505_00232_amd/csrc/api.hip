@@ -516,6 +516,7 @@ void qfc_tune(int32_t key, int32_t value) {
     if (key == 7) t.skinny_waves = value;
     if (key == 8) t.skinny_row_tiles = value;
     if (key == 9) t.skinny_max_m = value;
+    if (key == 10) t.gemv_pairs = value;
 }
 
 }  // extern "C"

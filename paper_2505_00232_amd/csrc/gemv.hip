@@ -35,27 +35,45 @@ Tuning &tuning() {
 // Wavefronts per workgroup at most.  Up to two token rows (and no prologue) the kernel needs few
 // enough registers for 16 wavefronts of a workgroup to be resident: a K of 9 to 16 units
 // (K = 14336: 14 units) then has one unit per wavefront and all its weight vectors in flight at
-// once, instead of two units per wavefront in turn.
-static int wave_cap(int M, bool plain, int KU) {
-    return M > 4 ? 4 : (M <= 2 && plain && KU > 8 && KU <= 16) ? 16 : 8;
+// once, instead of two units per wavefront in turn.  More than four rows: four (the staged rows fill
+// registers and LDS), but eight for 8-bit layers of up to 512 row tiles, whose workgroups hardly fill the
+// chip (M = 8, us with 4 / 8: 6144 x 4096 with rotary embedding 10.7 / 8.9, 4096 x 14336 15.9 / 14.5,
+// 2304 x 9216 11.5 / 9.9; wider ones lose: 18432 x 2304 13.3 / 17.4, 28672 x 4096 26.4 / 28.7).
+static int wave_cap(const Geometry &g, int M, int pro, int KU) {
+    if (M > 4) return pro != 1 && g.fmt == kW8C && g.RT <= 512 ? 8 : 4;
+    return M <= 2 && pro == 0 && KU > 8 && KU <= 16 ? 16 : 8;
 }
 
-GemvPlan plan_gemv(const Geometry &g, int M, int num_cus, int pro) {
-    (void)num_cus;
+GemvPlan plan_gemv(const Geometry &g, int M, int num_cus, int pro, bool gated) {
     const bool plain = pro == 0;
     const Tuning &t = tuning();
     GemvPlan p;
-    // Half-unit items (int4 formats, no prologue), where measured faster: launches of few
+    // Gated output of a wide layer: a workgroup takes both branches of 32 channels instead of 16, so that half
+    // as many workgroups stage the token rows (and, with a merged normalization, weight them), as long as
+    // enough wavefronts remain: 12 per compute unit up to four rows, 5 above, where a wavefront has more in
+    // flight.  With the normalization, 28672 x 4096, int4 groups, us with one / two pairs: M = 1 15.4 / 14.4,
+    // 4 19.2 / 15.8, 8 23.0 / 18.6; int8 at M = 8 26.3 / 23.2 (below five rows it loses: 21.4 / 25.7 at M = 2).
+    // 22016 x 4096 wins from five rows on only (M = 8 17.4 / 15.9, M = 1 13.0 / 13.1), 24576 x 3072
+    // and 18432 x 2304 lose.
+    const int pair_waves = M > 4 ? (g.KU < 4 ? g.KU : 4) : 2 * g.KU;
+    const bool can_pair = gated && pro != 1 && (M > 4 || (g.fmt != kW8C && g.KU <= 4));
+    const int forced = t.gemv_pairs;
+    p.pairs = gated && pro != 1 && (forced > 0 ? forced == 2
+                                               : can_pair && (long)(g.RT / 4) * pair_waves >= (M > 4 ? 5L : 12L) * num_cus)
+                  ? 2 : 1;
+    // Half-unit items (int4 formats), where measured faster: launches of few
     // wavefronts with a short K (O and QKV projections: twice the wavefronts, each with half the
     // serial work), and for M > 4 a long K, where a wavefront's staged token rows (16 KB of LDS per
-    // unit at M = 8) limit the wavefronts a compute unit holds.
+    // unit at M = 8) limit the wavefronts a compute unit holds; gated layers of short K at M = 1 (18432 x
+    // 2304 with the normalization 9.2 -> 8.3 us) and, up to four rows, those with two pairs per workgroup.
     const long full_waves = (long)g.RT * g.KU;
-    const bool gain = M > 4 ? (g.KU > 4 || full_waves <= 1024) : (g.KU <= 4 && full_waves <= 2048);
-    const bool can = g.fmt != kW8C && (plain || (pro > 0 && M <= 4));  // kernels built with half-unit items
+    const bool gain = M > 4 ? (g.KU > 4 ? plain : full_waves <= (plain ? 1024 : 2048))
+                            : g.KU <= 4 && (full_waves <= 2048 || (gated && pro != 1 && (M == 1 || p.pairs == 2)));
+    const bool can = g.fmt != kW8C && (plain || (pro > 0 && M <= 4) || pro == 2);  // kernels built with half-unit items
     p.half = can && (t.gemv_half >= 0 ? t.gemv_half != 0 : gain);
     p.copy = p.half && plain && M > 4 && g.KU > 4;  // long K at M > 4: token rows staged by direct copies
     p.units = p.half ? (g.KT + 3) / 4 : g.KU;
-    const int cap = p.half ? 8 : wave_cap(M, plain, p.units);
+    const int cap = p.half ? 8 : wave_cap(g, M, pro, p.units);
     const int per_wave = (p.units + cap - 1) / cap;  // items per wavefront and row tile
     p.waves = (p.units + per_wave - 1) / per_wave;
     const long waves_total = (long)g.RT * p.waves;
@@ -151,7 +169,8 @@ struct GemvArgs {
     const float *sw;    // per-channel scales [Np] (W8C, W4C)
     int N, K, RT, KT, KU, rt_stride;
     int row_tiles;           // R: row tiles per workgroup
-    int rt_step;             // distance between a workgroup's row tiles (1; RT / 2 for a gated output)
+    int rt_step, pair_step;  // row tile r of a workgroup is rt0 + (r / 2) pair_step + (r % 2) rt_step
+    int pairs;               // gated output: pairs of row tiles (both branches of 16 channels) per workgroup
     int gated_out;           // 1: rows [0, N/2) are the gate, rows [N/2, N) the other branch; y is [M, N/2]
     int paired;              // 1: the layer is packed in pairs (physical row tiles 2 t, 2 t + 1 = the two branches)
     int units_q, units_rem;  // KU = units_q * waves + units_rem
@@ -171,7 +190,8 @@ struct GemvArgs {
 // a row by one number rs, which commutes with the product, so the row goes into LDS multiplied by
 // the normalization weight only and the output is multiplied by rs at the end.  The wavefronts of a
 // workgroup stage every value of the rows exactly once between them, so each adds up the squares of what
-// it stages: no pass over x of its own.
+// it stages: no pass over x of its own (28672 channels of 4096 x int4, us with / without that pass: 15.7 / 15.4
+// at M = 1, 23.3 / 19.0 at M = 4; 6144 of int8: 15.7 / 11.1 at M = 8).
 template <int M, int FMT, int PRO, int OCT>  // OCT: octets (8 k) per item
 struct XStage {
     static constexpr int XV = M * OCT / 64;               // 16-byte vectors per lane per unit
@@ -243,7 +263,7 @@ struct XStage {
 // weight loads complete in order only among their own kind, so the wavefront waits for an empty
 // counter before its first tile: slower for short K, faster for the down projections (M = 8: -17 %).
 template <int M, int FMT, bool DB, int PRO, bool BIG = false, bool HALF = false, bool COPY = false>
-__global__ __launch_bounds__(BIG ? 1024 : PRO && M > 4 ? 256 : 512) void gemv_kernel(GemvArgs a) {
+__global__ __launch_bounds__(BIG ? 1024 : PRO == 1 && M > 4 ? 256 : 512) void gemv_kernel(GemvArgs a) {
     static_assert(!HALF || (FMT != kW8C && !DB), "half units: int4 formats, single buffer");
     static_assert(!COPY || (HALF && PRO == 0), "direct copies: half units without a prologue");
     constexpr int TILES = HALF ? 4 : 8;         // weight tiles per item
@@ -261,9 +281,9 @@ __global__ __launch_bounds__(BIG ? 1024 : PRO && M > 4 ? 256 : 512) void gemv_ke
     // (first row tile in the packed buffer: with the branches' tiles interleaved, the pair (2 b, 2 b + 1))
     // Rotary pairs: a workgroup owns the row tiles (t, t + d / 32) of one head, i.e. rows i and i + d / 2.
     const int rt0 = a.rope_per    ? (int)(blockIdx.x / a.rope_per) * (2 * a.rope_per) + (int)(blockIdx.x % a.rope_per)
-                    : a.gated_out ? (a.paired ? 2 * blockIdx.x : blockIdx.x)
+                    : a.gated_out ? (a.paired ? 2 * a.pairs * blockIdx.x : a.pairs * blockIdx.x)
                                   : blockIdx.x * a.row_tiles;
-    const int R = a.gated_out || a.rope_per ? 2 : min(a.row_tiles, a.RT - rt0);
+    const int R = a.rope_per ? 2 : a.gated_out ? 2 * min(a.pairs, a.RT / 2 - a.pairs * (int)blockIdx.x) : min(a.row_tiles, a.RT - rt0);
     const int u0 = wave * a.units_q + min(wave, a.units_rem);
     const int u1 = u0 + a.units_q + (wave < a.units_rem ? 1 : 0);
     u32x4 *lds_x = lds_all + wave * (OCT * M);
@@ -298,7 +318,7 @@ __global__ __launch_bounds__(BIG ? 1024 : PRO && M > 4 ? 256 : 512) void gemv_ke
         const int U = HALF ? u >> 1 : u, h = HALF ? u & 1 : 0;  // unit, half of it
         const int ntU = HALF ? min(8, a.KT - 8 * U) : nt;       // weight tiles before the unit's scale tile
         const int pos = FMT == kW4G32 ? 9 * U : 8 * U;
-        const u32x4 *base = a.packed + ((size_t)(rt0 + r * a.rt_step) * a.rt_stride + pos) * 64;
+        const u32x4 *base = a.packed + ((size_t)(rt0 + (r >> 1) * a.pair_step + (r & 1) * a.rt_step) * a.rt_stride + pos) * 64;
         // scales first: loads return in order, and the first tile's results need them
         if (FMT == kW4G32) {
 #pragma unroll
@@ -331,6 +351,8 @@ __global__ __launch_bounds__(BIG ? 1024 : PRO && M > 4 ? 256 : 512) void gemv_ke
             if (items > 1) load_item(nxt, R > 1 ? u0 : u0 + 1, R > 1 ? 1 : 0, kMaybePartial);
         }
     }
+    // (always_inline: left to itself the compiler calls the staging of 12 and more vectors as a function
+    // and keeps the vectors in scratch memory: 91.7 us instead of 21.3 for the gate+up layer at M = 8)
     auto stage = [&]() __attribute__((always_inline)) {
         // the wavefront's earlier LDS reads are done (same wavefront, in order)
         xs.store(lds_x, lane, a.act, a.norm_offset, ss);
@@ -338,80 +360,99 @@ __global__ __launch_bounds__(BIG ? 1024 : PRO && M > 4 ? 256 : 512) void gemv_ke
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     };
+    // A operands (token rows) of one tile; lanes whose row index is >= M read
+    // row c % M instead: an A row only feeds the D row of the same index, and
+    // D rows >= M are never used, so no masking or zeroing is needed.
+    constexpr int XA = FMT == kW8C ? 2 : 4;
+    const u32x4 *xrow = lds_x + q * M + (c % M);
+    auto load_xa = [&](v8h(&xa)[XA], int t) __attribute__((always_inline)) {
+#pragma unroll
+        for (int j = 0; j < XA; ++j)
+            xa[j] = __builtin_bit_cast(v8h, xrow[(FMT == kW8C ? t * 8 + j * 4 : (4 * t + j) * 4) * M]);
+    };
+    // Sums of one item: per-channel formats accumulate inside the MFMA (4-bit codes in two chains, so that
+    // MFMAs do not wait on each other).  Group scales: the scaled accumulation of an MFMA result is issued
+    // one step late, after the next MFMA has been started, so that its latency is covered by the next
+    // step's dequantization instead of a stall.
+    struct Sums {
+        float accr[4];
+        v4f accw, accw2, d_prev;
+        _Float16 s_prev;
+    };
+    auto clear = [&](Sums &z) __attribute__((always_inline)) {
+        const v4f zero = {0.0f, 0.0f, 0.0f, 0.0f};
+        z.accw = z.accw2 = z.d_prev = zero;
+        z.s_prev = (_Float16)0.0f;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) z.accr[i] = 0.0f;
+    };
+    auto tile_math = [&](const u32x4(&w)[NV], const v8h(&xa)[XA], int t, Sums &z) __attribute__((always_inline)) {
+        if constexpr (FMT == kW4G32) {
+            const uint32_t wd[4] = {w[t].x, w[t].y, w[t].z, w[t].w};
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const int gl = 4 * t + j;  // group inside the unit
+                const v8h wb = dequant8(wd[j]);
+                const v4f zero = {0.0f, 0.0f, 0.0f, 0.0f};
+                const v4f d = __builtin_amdgcn_mfma_f32_16x16x32_f16(xa[j], wb, zero, 0, 0, 0);
+#pragma unroll
+                for (int i = 0; i < MI; ++i) z.accr[i] = fmaf((float)z.s_prev, z.d_prev[i], z.accr[i]);
+                const u32x4 sv = w[TILES + gl / 8];
+                const uint32_t sd = sv[(gl % 8) / 2];
+                z.s_prev = __builtin_bit_cast(_Float16, (uint16_t)(sd >> (16 * (gl & 1))));
+                z.d_prev = d;
+            }
+        } else if constexpr (FMT == kW4C) {
+            z.accw = __builtin_amdgcn_mfma_f32_16x16x32_f16(xa[0], dequant8(w[t].x), z.accw, 0, 0, 0);
+            z.accw2 = __builtin_amdgcn_mfma_f32_16x16x32_f16(xa[1], dequant8(w[t].y), z.accw2, 0, 0, 0);
+            z.accw = __builtin_amdgcn_mfma_f32_16x16x32_f16(xa[2], dequant8(w[t].z), z.accw, 0, 0, 0);
+            z.accw2 = __builtin_amdgcn_mfma_f32_16x16x32_f16(xa[3], dequant8(w[t].w), z.accw2, 0, 0, 0);
+        } else {
+            z.accw = __builtin_amdgcn_mfma_f32_16x16x32_f16(xa[0], dequant_i8x8(w[t].x, w[t].y), z.accw, 0, 0, 0);
+            z.accw = __builtin_amdgcn_mfma_f32_16x16x32_f16(xa[1], dequant_i8x8(w[t].z, w[t].w), z.accw, 0, 0, 0);
+        }
+    };
+    auto compute_full = [&](const u32x4(&w)[NV], Sums &z) __attribute__((always_inline)) {
+        // full unit: straight-line code, A operands fetched one tile ahead
+        v8h xa[XA], xn[XA];
+        load_xa(xa, 0);
+#pragma unroll
+        for (int t = 0; t < TILES; ++t) {
+            if (t + 1 < TILES) load_xa(xn, t + 1);
+            tile_math(w, xa, t, z);
+#pragma unroll
+            for (int j = 0; j < XA; ++j) xa[j] = xn[j];
+        }
+    };
+    auto compute_tail = [&](const u32x4(&w)[NV], int nt, Sums &z) __attribute__((always_inline)) {
+#pragma unroll
+        for (int t = 0; t < TILES; ++t) {
+            if (t < nt) {
+                v8h xa[XA];
+                load_xa(xa, t);
+                tile_math(w, xa, t, z);
+            }
+        }
+    };
+    // adds an item's contribution to the accumulators of its row tile
+    auto add_item = [&](Sums &z, float(&to)[4]) __attribute__((always_inline)) {
+        if constexpr (FMT == kW4G32) {
+#pragma unroll
+            for (int i = 0; i < MI; ++i) z.accr[i] = fmaf((float)z.s_prev, z.d_prev[i], z.accr[i]);
+        }
+#pragma unroll
+        for (int i = 0; i < MI; ++i) to[i] += FMT == kW4G32 ? z.accr[i] : FMT == kW4C ? z.accw[i] + z.accw2[i] : z.accw[i];
+    };
     for (int it = 0; it < items; ++it) {
         const int nt = min(TILES, a.KT - TILES * u);
-        float accr[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-        v4f accw = {0.0f, 0.0f, 0.0f, 0.0f};
-        v4f accw2 = {0.0f, 0.0f, 0.0f, 0.0f};  // second chain (W4C), so that MFMAs do not wait on each other
-        // A operands (token rows) of one tile; lanes whose row index is >= M read
-        // row c % M instead: an A row only feeds the D row of the same index, and
-        // D rows >= M are never used, so no masking or zeroing is needed.
-        constexpr int XA = FMT == kW8C ? 2 : 4;
-        const u32x4 *xrow = lds_x + q * M + (c % M);
-        auto load_xa = [&](v8h(&xa)[XA], int t) __attribute__((always_inline)) {
-#pragma unroll
-            for (int j = 0; j < XA; ++j)
-                xa[j] = __builtin_bit_cast(v8h, xrow[(FMT == kW8C ? t * 8 + j * 4 : (4 * t + j) * 4) * M]);
-        };
-        // The scaled accumulation of an MFMA result is issued one step late, after the
-        // next MFMA has been started, so that its latency is covered by the next
-        // step's dequantization instead of a stall.
-        v4f d_prev = {0.0f, 0.0f, 0.0f, 0.0f};
-        _Float16 s_prev = (_Float16)0.0f;
-        auto tile_math = [&](const v8h(&xa)[XA], int t) __attribute__((always_inline)) {
-            if (FMT == kW4G32) {
-                const uint32_t wd[4] = {cur[t].x, cur[t].y, cur[t].z, cur[t].w};
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const int gl = 4 * t + j;  // group inside the unit
-                    const v8h wb = dequant8(wd[j]);
-                    const v4f zero = {0.0f, 0.0f, 0.0f, 0.0f};
-                    const v4f d = __builtin_amdgcn_mfma_f32_16x16x32_f16(xa[j], wb, zero, 0, 0, 0);
-#pragma unroll
-                    for (int i = 0; i < MI; ++i) accr[i] = fmaf((float)s_prev, d_prev[i], accr[i]);
-                    const u32x4 sv = cur[TILES + gl / 8];
-                    const uint32_t sd = sv[(gl % 8) / 2];
-                    s_prev = __builtin_bit_cast(_Float16, (uint16_t)(sd >> (16 * (gl & 1))));
-                    d_prev = d;
-                }
-            } else if (FMT == kW4C) {
-                accw = __builtin_amdgcn_mfma_f32_16x16x32_f16(xa[0], dequant8(cur[t].x), accw, 0, 0, 0);
-                accw2 = __builtin_amdgcn_mfma_f32_16x16x32_f16(xa[1], dequant8(cur[t].y), accw2, 0, 0, 0);
-                accw = __builtin_amdgcn_mfma_f32_16x16x32_f16(xa[2], dequant8(cur[t].z), accw, 0, 0, 0);
-                accw2 = __builtin_amdgcn_mfma_f32_16x16x32_f16(xa[3], dequant8(cur[t].w), accw2, 0, 0, 0);
-            } else {
-                accw = __builtin_amdgcn_mfma_f32_16x16x32_f16(xa[0], dequant_i8x8(cur[t].x, cur[t].y), accw, 0, 0, 0);
-                accw = __builtin_amdgcn_mfma_f32_16x16x32_f16(xa[1], dequant_i8x8(cur[t].z, cur[t].w), accw, 0, 0, 0);
-            }
-        };
-        auto compute_full = [&]() __attribute__((always_inline)) {
-            // full unit: straight-line code, A operands fetched one tile ahead
-            v8h xa[XA], xn[XA];
-            load_xa(xa, 0);
-#pragma unroll
-            for (int t = 0; t < TILES; ++t) {
-                if (t + 1 < TILES) load_xa(xn, t + 1);
-                tile_math(xa, t);
-#pragma unroll
-                for (int j = 0; j < XA; ++j) xa[j] = xn[j];
-            }
-        };
-        auto compute_tail = [&]() __attribute__((always_inline)) {
-#pragma unroll
-            for (int t = 0; t < TILES; ++t) {
-                if (t < nt) {
-                    v8h xa[XA];
-                    load_xa(xa, t);
-                    tile_math(xa, t);
-                }
-            }
-        };
+        Sums z;
+        clear(z);
         if constexpr (DB) {
             if (r == 0) stage();
             if (nt == TILES)
-                compute_full();
+                compute_full(cur, z);
             else
-                compute_tail();
+                compute_tail(cur, nt, z);
         } else {
             // single buffer: request, stage and compute inside one branch
             if (r == 0) {
@@ -433,24 +474,16 @@ __global__ __launch_bounds__(BIG ? 1024 : PRO && M > 4 ? 256 : 512) void gemv_ke
             if (nt == TILES) {
                 load_item(cur, u, r, kFull);
                 if (r == 0) staged();
-                compute_full();
+                compute_full(cur, z);
             } else {
                 load_item(cur, u, r, kMaybePartial);
                 if (r == 0) staged();
-                compute_tail();
+                compute_tail(cur, nt, z);
             }
         }
-        if (FMT == kW4G32) {
-#pragma unroll
-            for (int i = 0; i < MI; ++i) accr[i] = fmaf((float)s_prev, d_prev[i], accr[i]);
-        }
-        // add this item's contribution to the accumulators of its row tile
 #pragma unroll
         for (int rr = 0; rr < 4; ++rr)
-            if (rr == r) {
-#pragma unroll
-                for (int i = 0; i < MI; ++i) acc[rr][i] += FMT == kW4G32 ? accr[i] : FMT == kW4C ? accw[i] + accw2[i] : accw[i];
-            }
+            if (rr == r) add_item(z, acc[rr]);
         if (++r == R) {
             r = 0;
             ++u;
@@ -534,18 +567,18 @@ __global__ __launch_bounds__(BIG ? 1024 : PRO && M > 4 ? 256 : 512) void gemv_ke
         // into the fully connected operator that produces them)
         const GateCoeffs gc = gate_coeffs(a.act);
         const int half = a.N / 2;
-        for (int e = threadIdx.x; e < M * 16; e += blockDim.x) {
-            const int cc = e & 15, m = e >> 4;
+        for (int e = threadIdx.x; e < (R / 2) * M * 16; e += blockDim.x) {
+            const int cc = e & 15, m = (e >> 4) % M, pr = (e >> 4) / M;
             float sg = 0.0f, su = 0.0f;
             for (int w = 0; w < nwaves; ++w) {
-                sg += red[((w * 4 + 0) * M + m) * 16 + cc];
-                su += red[((w * 4 + 1) * M + m) * 16 + cc];
+                sg += red[((w * 4 + 2 * pr) * M + m) * 16 + cc];
+                su += red[((w * 4 + 2 * pr + 1) * M + m) * 16 + cc];
             }
-            const int n = (int)blockIdx.x * 16 + cc;  // channel of the gated output
+            const int n = ((int)blockIdx.x * a.pairs + pr) * 16 + cc;  // channel of the gated output
             if (n < half) {
                 if (FMT != kW4G32) {  // (the scales follow the packed row order)
-                    sg *= a.sw[a.paired ? rt0 * 16 + cc : n];
-                    su *= a.sw[a.paired ? rt0 * 16 + 16 + cc : n + half];
+                    sg *= a.sw[a.paired ? (rt0 + 2 * pr) * 16 + cc : n];
+                    su *= a.sw[a.paired ? (rt0 + 2 * pr) * 16 + 16 + cc : n + half];
                 }
                 if constexpr (PRO == 2) {
                     const float rs = rms_scale(m);
@@ -574,14 +607,15 @@ __global__ __launch_bounds__(BIG ? 1024 : PRO && M > 4 ? 256 : 512) void gemv_ke
 template <int M, int PRO>
 hipError_t launch_m(const Geometry &g, const GemvArgs &a, const GemvPlan &p, hipStream_t st) {
     const int waves = p.waves;
-    const dim3 grid((unsigned)(a.gated_out || a.rope_per ? g.RT / 2 : (g.RT + a.row_tiles - 1) / a.row_tiles));
+    const int rows = a.rope_per ? 2 : a.gated_out ? 2 * a.pairs : a.row_tiles;
+    const dim3 grid((unsigned)(a.rope_per ? g.RT / 2 : a.gated_out ? (g.RT / 2 + a.pairs - 1) / a.pairs : (g.RT + rows - 1) / rows));
     const dim3 block((unsigned)(waves * 64));
     const int oct = g.fmt == kW8C || p.half ? 64 : 128;
     size_t lds = (size_t)waves * oct * M * 16;
     const size_t red = (size_t)waves * 4 * M * 16 * sizeof(float);
     if (red > lds) lds = red;
     // long-lived wavefronts (>= 3 items each) get the double-buffered variant
-    const int items = ((p.units + waves - 1) / waves) * (a.gated_out || a.rope_per ? 2 : a.row_tiles);
+    const int items = ((p.units + waves - 1) / waves) * rows;
     if constexpr (PRO == 0 && M > 4) {
         if (p.half && p.copy) {
             if (g.fmt == kW4C)
@@ -591,7 +625,7 @@ hipError_t launch_m(const Geometry &g, const GemvArgs &a, const GemvPlan &p, hip
             return hipGetLastError();
         }
     }
-    if constexpr (PRO == 0 || M <= 4) {
+    if constexpr (PRO != 1 || M <= 4) {
         if (p.half) {
             if (g.fmt == kW4C)
                 gemv_kernel<M, kW4C, false, PRO, false, true><<<grid, block, lds, st>>>(a);
@@ -650,7 +684,7 @@ hipError_t launch_any_m(const Geometry &g, const GemvArgs &a, int M, const GemvP
 
 hipError_t launch_gemv(const Geometry &g, const void *packed, const void *x, int M, void *y,
                        const Fusion &f, int num_cus, hipStream_t st) {
-    const GemvPlan p = plan_gemv(g, M, num_cus, f.norm_gamma ? 2 : f.gate ? 1 : 0);
+    const GemvPlan p = plan_gemv(g, M, num_cus, f.norm_gamma ? 2 : f.gate ? 1 : 0, f.gated_output);
     GemvArgs a;
     a.packed = static_cast<const u32x4 *>(packed);
     a.x = static_cast<const u32x4 *>(x);
@@ -668,6 +702,8 @@ hipError_t launch_gemv(const Geometry &g, const void *packed, const void *x, int
     a.row_tiles = p.row_tiles;
     a.paired = g.pair_half ? 1 : 0;
     a.rt_step = f.gated_output && !a.paired ? g.RT / 2 : 1;
+    a.pair_step = f.gated_output && !a.paired ? 1 : 2;
+    a.pairs = p.pairs;
     a.gated_out = f.gated_output ? 1 : 0;
     a.rope_per = 0;
     a.rope_d = a.rope_hq = a.rope_hkv = a.rope_C = a.rope_pos = 0;
@@ -677,6 +713,7 @@ hipError_t launch_gemv(const Geometry &g, const void *packed, const void *x, int
         const RopeOut &r = *f.rope;
         a.rope_per = r.d / 32;
         a.rt_step = a.rope_per;
+        a.pair_step = 1;
         a.rope_d = r.d;
         a.rope_hq = r.h_q;
         a.rope_hkv = r.h_kv;

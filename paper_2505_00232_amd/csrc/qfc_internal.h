@@ -111,6 +111,7 @@ struct GemvPlan {
     bool half = false;  // items are half units (four weight tiles)
     bool copy = false;  // token rows staged by direct global -> LDS copies
     int units = 0;      // items per row tile along K
+    int pairs = 1;       // gated output: pairs of row tiles per workgroup
 };
 
 // Tunables (set through qfc_tune of qfc_experimental.h by tests and sweeps, read by the planners).
@@ -134,13 +135,14 @@ struct Tuning {
     Tunable skinny_waves{0};    // few token rows: most wavefronts per workgroup (0: automatic)
     Tunable skinny_row_tiles{0};  // few token rows: row tiles per workgroup (0: automatic)
     Tunable skinny_max_m{-1};   // largest M of those kernels (-1: automatic; 0: never)
+    Tunable gemv_pairs{0};      // gated output, pairs of row tiles per decode workgroup (0: automatic)
     Tunable gemv_half{-1};      // half-unit items of the decode kernel: -1 automatic, 0 never, 1 where possible
 };
 Tuning &tuning();
 
 // pro: the prologue fused into the launch (0 none, 1 gated input, 2 merged normalization); -1 for
 // the kernels that only take the basic plan
-GemvPlan plan_gemv(const Geometry &g, int M, int num_cus, int pro = -1);
+GemvPlan plan_gemv(const Geometry &g, int M, int num_cus, int pro = -1, bool gated = false);
 
 // Launchers.  Every one validates nothing (the C ABI layer did) and returns
 // the hipError_t of the launch.

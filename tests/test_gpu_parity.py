@@ -963,6 +963,45 @@ def test_prefill_gated_output(fmt, mode, M, N, K):
     layer.close()
 
 
+@pytest.mark.parametrize("fmt", ["w8c", "w4g32", "w4c"])
+@pytest.mark.parametrize("N,K", [(32, 96), (160, 1152), (224, 2304)])
+def test_decode_gated_output_two_pairs_per_workgroup(fmt, N, K):
+    """Decode workgroups that take two pairs of row tiles (the last one may own one): the same bits as with one
+    pair, both packings, with and without the merged normalization, whole and half units; and the oracle."""
+    print(f"two pairs {fmt} N={N} K={K}", flush=True)
+    fc = synth.FC("t", K, N, fmt)
+    wq, s = synth.weights(3650, N, K, fc)
+    gamma = (synth.activations(3651, N, K, 1, K)[0] * np.float16(0.25)).astype(np.float16)
+    gd = torch.from_numpy(gamma).to(DEV)
+    for paired in (False, True):
+        layer = binding.QuantLinear(wq, s, fmt, gated_pairs=paired)
+        for M in (1, 2, 3, 4, 5, 7, 8):
+            x = (synth.activations(3650, N, K + M, M, K) * np.float16(0.0625)).astype(np.float16)
+            xd = torch.from_numpy(x).to(DEV)
+            for norm in (False, True):
+                kw = dict(norm_gamma=gd, norm_eps=1e-5) if norm else {}
+                for half in (0, 1):
+                    ys = []
+                    for pairs in (1, 2):
+                        binding.qfc_tune(4, half)
+                        binding.qfc_tune(10, pairs)
+                        try:
+                            y = torch.full((M, N // 2), 77.0, dtype=torch.float16, device=DEV)
+                            binding.qfc_forward_fused(layer.handle, xd, y, activation=binding.QFC_ACT_SILU, gated_output=True, **kw)
+                            torch.cuda.synchronize()
+                        finally:
+                            binding.qfc_tune(4, -1)
+                            binding.qfc_tune(10, 0)
+                        ys.append(y.cpu().numpy())
+                    assert np.array_equal(ys[0].view(np.uint16), ys[1].view(np.uint16)), (paired, M, norm, half)
+                if norm:
+                    full = oracle.rms_scale(x, 1e-5)[:, None] * oracle.fc_weight_only(oracle.norm_weighted_input(x, gamma, 0.0), wq, s, _group(fmt))
+                else:
+                    full = oracle.fc_weight_only(x, wq, s, _group(fmt))
+                assert _E(ys[1], oracle.gated_output(full, oracle.SILU)) <= TOL, (paired, M, norm)
+        layer.close()
+
+
 def test_prefill_gated_output_llama_gate_up_sampled():
     """The gate+up layer of Llama-3.1-8B at M = 1024 (int8 activations, 8-bit and 4-bit per-channel weights)
     and of Gemma2-2B at M = 2048 (fp16, int4 group-32), packed in pairs: sampled rows and channels
