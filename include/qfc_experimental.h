@@ -30,10 +30,11 @@ extern "C" {
  *   key 5  two blocks per workgroup in prefill attention (-1 automatic, 0 never, 1 always)
  *   key 6  causal walks of prefill attention cut into chunks (-1 automatic, 0 never, 1 always);
  *          qfc_attention_workspace_size follows the value set when it is called
- *   key 7  products of few token rows (9 .. 64): most wavefronts per workgroup (0 = automatic)
+ *   key 7  products of few token rows (from 9): most wavefronts per workgroup (0 = automatic)
  *   key 8  the same: row tiles per workgroup (0 = automatic; 1 .. 8)
  *   key 9  the same: largest number of token rows they are used for (-1 automatic, 0 never)
- *   key 10 gated output at M <= 8: pairs of row tiles per decode workgroup (0 = automatic; 1, 2) */
+ *   key 10 gated output at M <= 8: pairs of row tiles per decode workgroup (0 = automatic; 1, 2)
+ *   key 11 as key 7: blocks the token rows are cut into at least (0 = automatic) */
 void qfc_tune(int32_t key, int32_t value);
 
 /* Measurement probe (bench.py --probe-mfma): `workgroups` workgroups of four wavefronts each issue

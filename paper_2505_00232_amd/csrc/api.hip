@@ -517,6 +517,7 @@ void qfc_tune(int32_t key, int32_t value) {
     if (key == 8) t.skinny_row_tiles = value;
     if (key == 9) t.skinny_max_m = value;
     if (key == 10) t.gemv_pairs = value;
+    if (key == 11) t.skinny_blocks = value;
 }
 
 }  // extern "C"

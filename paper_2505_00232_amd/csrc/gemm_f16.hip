@@ -761,7 +761,7 @@ hipError_t launch_gemm_f16(const Geometry &g, const void *packed, const void *x,
                            const void *residual, int gated_act, int num_cus, hipStream_t st) {
     // only the kernel that converts in registers has the merged gating (int4 formats, K a multiple of 128)
     if (gated_act >= 0 && (!g.pair_half || (g.K % 128) != 0 || g.fmt == kW8C)) return hipErrorNotSupported;
-    if (skinny_product(g, M, false, num_cus)) return launch_skinny_f16(g, packed, x, M, y, residual, gated_act, num_cus, st);
+    if (skinny_product(g, M, false, gated_act >= 0, num_cus)) return launch_skinny_f16(g, packed, x, M, y, residual, gated_act, num_cus, st);
     GemmF16Args a;
     a.w = static_cast<const uint4 *>(packed);
     a.x = static_cast<const uint4 *>(x);

@@ -904,7 +904,7 @@ hipError_t launch_gemm_i8(const Geometry &g, const void *packed, const int8_t *x
                           const float *sx, int M, int Mp, void *out, int out_mode, const void *residual,
                           int gated_act, int num_cus, hipStream_t st) {
     (void)Mp;
-    if (out_mode == 0 && skinny_product(g, M, true, num_cus)) return launch_skinny_i8(g, packed, xq_tiled, sx, M, out, residual, gated_act, num_cus, st);
+    if (out_mode == 0 && skinny_product(g, M, true, gated_act >= 0 && g.pair_half, num_cus)) return launch_skinny_i8(g, packed, xq_tiled, sx, M, out, residual, gated_act, num_cus, st);
     GemmI8Args a;
     a.w = static_cast<const uint4 *>(packed);
     a.x = reinterpret_cast<const uint4 *>(xq_tiled);

@@ -1,11 +1,11 @@
-// Products of few token rows (M = 9 .. 64: batches beyond the decode kernel's eight rows, short
-// prompts): y[m,n] = sum_k x[m,k] * s * Wq[n,k], with binary16 activations (weights dequantized in
+// Products of few token rows (from M = 9: batches beyond the decode kernel's eight rows, prompts of up to a
+// few hundred tokens, see skinny_product): y[m,n] = sum_k x[m,k] * s * Wq[n,k], with binary16 activations (weights dequantized in
 // registers) or int8 activations (exact int32 sums).
 //
 // What bounds them: the weight stream up to a few dozen rows, as in decode.  The tiles of the
 // prefill kernels (256 channels x 64 or 128 tokens) give 16 workgroups for a layer of 4096
 // channels, i.e. 16 of 256 compute units pull the weights.  Here, as in the decode kernel, a
-// workgroup owns 16 R output channels (R packed row tiles) and ALL token rows, and its
+// workgroup owns 16 R output channels (R packed row tiles) and all token rows (blocks of up to 64), and its
 // wavefronts split K; their partial sums meet in LDS in fixed order (deterministic, no atomics, no
 // traffic between workgroups, no workspace).
 //
@@ -45,6 +45,7 @@ struct SkinnyArgs {
     const _Float16 *res;  // [M, N] residual added before the rounding, or null
     void *out;
     int M, N, K, Kp, KT, RT;  // KT: packed k tiles per row tile, RT: row tiles
+    int block_rows, blocks;   // token rows per workgroup, blocks of them
     int rt_stride;
     int steps_q, steps_rem;  // 128-k steps per wavefront: steps_q, one more for the first steps_rem
     float sw_mul;            // int8 x 4-bit: sums are 16 times the definition's (see gemm_i8.hip)
@@ -91,6 +92,21 @@ __device__ __forceinline__ void wait_lds() { asm volatile("s_waitcnt lgkmcnt(0)"
 // different banks.  (16 x 16 accumulator: lane = channel + 16 q holds tokens 4 q + e in register e.)
 __device__ __forceinline__ int red_row(int tile, int token) { return (tile * 16 + ((token >> 2) | ((token & 3) << 2))) * 16; }
 
+// The workgroup's first row tile and token block.  Workgroups are dealt to the 8 XCDs round robin: the token
+// blocks of the same row tiles follow each other on one XCD, whose L2 then holds their weights.
+__device__ __forceinline__ bool place(const SkinnyArgs &a, int R, int &rt0, int &m0, int &rows) {
+    int group = blockIdx.x, block = 0;
+    if (a.blocks > 1) {
+        const int xcd = blockIdx.x % 8, j = blockIdx.x / 8;
+        group = j / a.blocks * 8 + xcd;
+        block = j % a.blocks;
+    }
+    rt0 = group * R;
+    m0 = block * a.block_rows;
+    rows = min(a.block_rows, a.M - m0);
+    return rt0 < a.RT;
+}
+
 template <int R, int TB, typename T, typename ACC>
 __device__ __forceinline__ void put_partials(T *red, const ACC (&acc)[R][TB], int wave, int lane) {
 #pragma unroll
@@ -103,7 +119,7 @@ __device__ __forceinline__ void put_partials(T *red, const ACC (&acc)[R][TB], in
 
 // Sum over the wavefronts (in order) and store phase.  T: float or int; CH: per-channel scales.
 template <int R, int TB, typename T, bool CH>
-__device__ __forceinline__ void finish(const SkinnyArgs &a, const T *red, int nwaves, int rt0) {
+__device__ __forceinline__ void finish(const SkinnyArgs &a, const T *red, int nwaves, int rt0, int m0, int rows) {
     constexpr bool kInt = std::is_same<T, int>::value;
     typedef T t4 __attribute__((ext_vector_type(4)));
     const bool gated = a.gated_act >= 0;
@@ -123,8 +139,8 @@ __device__ __forceinline__ void finish(const SkinnyArgs &a, const T *red, int nw
     };
     for (int i = threadIdx.x; i < tiles * TB * 64; i += blockDim.x) {
         const int n4 = i & 3, m = (i >> 2) & 15, tb = (i >> 6) % TB, r = (i >> 6) / TB;
-        const int token = tb * 16 + m;
-        if (token >= a.M) continue;
+        if (tb * 16 + m >= rows) continue;
+        const int token = m0 + tb * 16 + m;
         const float sxm = kInt ? a.sx[token] : 1.0f;
         if (gated) {
             // physical row tiles 2 t and 2 t + 1 of a layer packed in pairs hold the gate's and the other
@@ -186,7 +202,8 @@ __global__ __launch_bounds__(MAXT) void skinny_f16_kernel(SkinnyArgs a) {
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int c = lane & 15, q = lane >> 4;
-    const int rt0 = blockIdx.x * R;  // first row tile
+    int rt0, m0, rows;
+    if (!place(a, R, rt0, m0, rows)) return;  // (whole workgroups only)
 
     const int t0 = wave * a.steps_q + min(wave, a.steps_rem);
     const int nt = a.steps_q + (wave < a.steps_rem ? 1 : 0);
@@ -212,7 +229,7 @@ __global__ __launch_bounds__(MAXT) void skinny_f16_kernel(SkinnyArgs a) {
         }
     };
     // copies of a half step: KiB i = token rows 8 i .. 8 i + 7, lane = (row, octet position)
-    const char *xbase = reinterpret_cast<const char *>(a.x);
+    const char *xbase = reinterpret_cast<const char *>(a.x) + (size_t)m0 * a.K * 2;
     const int K8 = a.K / 8;
     const uint32_t ring0 = (uint32_t)(uintptr_t)(lptr_t)lds + wave * (RING * SLOT);
     auto copy_stage = [&](int s, int slot) __attribute__((always_inline)) {
@@ -223,7 +240,7 @@ __global__ __launch_bounds__(MAXT) void skinny_f16_kernel(SkinnyArgs a) {
             const int rl = 8 * i + (lane >> 3);
             int o = o0 + ((lane & 7) ^ ((rl >> 1) & 7));
             if (tail && o >= K8) o &= 3;
-            const uint32_t off = ((uint32_t)min(rl, a.M - 1) * (uint32_t)K8 + (uint32_t)o) * 16u;
+            const uint32_t off = ((uint32_t)min(rl, rows - 1) * (uint32_t)K8 + (uint32_t)o) * 16u;
             copy16_to_lds(xbase, off, __builtin_amdgcn_readfirstlane(ring0 + slot * SLOT + i * 1024));
         }
     };
@@ -289,7 +306,7 @@ __global__ __launch_bounds__(MAXT) void skinny_f16_kernel(SkinnyArgs a) {
     float *red = reinterpret_cast<float *>(lds);
     put_partials<R, TB>(red, acc, wave, lane);
     __syncthreads();
-    finish<R, TB, float, FMT != kW4G32>(a, red, blockDim.x >> 6, rt0);
+    finish<R, TB, float, FMT != kW4G32>(a, red, blockDim.x >> 6, rt0, m0, rows);
 }
 
 // ---------------------------------------------------------------- int8 activations
@@ -302,10 +319,15 @@ __global__ __launch_bounds__(MAXT) void skinny_i8_kernel(SkinnyArgs a) {
     extern __shared__ u32x4 lds[];
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int rt0 = blockIdx.x * R;
+    int rt0, m0, rows;
+    if (!place(a, R, rt0, m0, rows)) return;
     const int t0 = wave * a.steps_q + min(wave, a.steps_rem);
     const int nt = a.steps_q + (wave < a.steps_rem ? 1 : 0);
     const int XT = a.Kp / 64;
+    // (a block's last tiles of 16 rows may lie past the rows there are: clamped, results dropped)
+    const u32x4 *xtile[TB];
+#pragma unroll
+    for (int tb = 0; tb < TB; ++tb) xtile[tb] = a.x + (size_t)min(m0 / 16 + tb, (a.M - 1) / 16) * XT * 64;
 
     const u32x4 *wrow[R];
 #pragma unroll
@@ -319,7 +341,7 @@ __global__ __launch_bounds__(MAXT) void skinny_i8_kernel(SkinnyArgs a) {
 #pragma unroll
         for (int tb = 0; tb < TB; ++tb)
 #pragma unroll
-            for (int v = 0; v < 2; ++v) xv[slot][tb][v] = a.x[((size_t)tb * XT + 2 * t + v) * 64 + lane];
+            for (int v = 0; v < 2; ++v) xv[slot][tb][v] = xtile[tb][(size_t)(2 * t + v) * 64 + lane];
     };
     v4i acc[R][TB];
 #pragma unroll
@@ -359,7 +381,7 @@ __global__ __launch_bounds__(MAXT) void skinny_i8_kernel(SkinnyArgs a) {
     int *red = reinterpret_cast<int *>(lds);
     put_partials<R, TB>(red, acc, wave, lane);
     __syncthreads();
-    finish<R, TB, int, true>(a, red, blockDim.x >> 6, rt0);
+    finish<R, TB, int, true>(a, red, blockDim.x >> 6, rt0, m0, rows);
 }
 
 constexpr size_t kLdsLimit = 160 * 1024;
@@ -369,17 +391,31 @@ void split_steps(SkinnyArgs &a, int steps, int waves) {
     a.steps_rem = steps % waves;
 }
 
-// Wavefronts per workgroup: at most `most`, every one with the same number of steps if it divides.
-int waves_for(int steps, int most) {
+unsigned grid_for(const SkinnyArgs &a, int R) {
+    const int groups = (a.RT + R - 1) / R;
+    return (unsigned)(a.blocks > 1 ? round_up(groups, 8) * a.blocks : groups);
+}
+
+// Workgroups of the fullest XCD per compute unit of it (whose workgroups of one row group stay together).
+float load_per_cu(const SkinnyArgs &a, int R, int num_cus) {
+    const int groups = (a.RT + R - 1) / R;
+    return a.blocks > 1 ? (float)((groups + 7) / 8 * a.blocks) * 8.0f / (float)num_cus : (float)groups / (float)num_cus;
+}
+
+// Wavefronts per workgroup: at most `most`, every one with the same number of steps if it divides; four where
+// there are more workgroups than compute units, so that two share one and overlap (64 and 128 token rows, 18432 x
+// 2304: 24.2 / 19.3 and 34.2 / 26.2 us with eight / four; 28672 x 4096 32.1 / 29.0 and 57.0 / 49.7; level for K of 9216 and 14336).
+int waves_for(int steps, int most, unsigned workgroups, int num_cus) {
     const int forced = tuning().skinny_waves;
     if (forced > 0 && forced < most) most = forced;
+    if (forced == 0 && workgroups > (unsigned)num_cus && most > 4) most = 4;
     const int w = steps < most ? steps : most;
     const int per = (steps + w - 1) / w;
     return (steps + per - 1) / per;
 }
 
 template <int FMT, int XB, int R>
-hipError_t launch_f16(SkinnyArgs a, hipStream_t st) {
+hipError_t launch_f16(SkinnyArgs a, int num_cus, hipStream_t st) {
     constexpr int TB = (XB + 1) / 2;
     constexpr int RING = XB <= 2 ? 4 : 2;
     constexpr int D0 = R == 1 ? 8 : R <= 3 ? 4 : 2, D = FMT == kW8C && D0 > 2 ? D0 / 2 : D0;
@@ -387,24 +423,24 @@ hipError_t launch_f16(SkinnyArgs a, hipStream_t st) {
     constexpr int MAXT = kWide ? 1024 : 512;
     constexpr size_t ring = RING * TB * 2048, red = (size_t)R * TB * 1024, per_wave = ring > red ? ring : red;
     constexpr int most = (int)(kLdsLimit / per_wave) < MAXT / 64 ? (int)(kLdsLimit / per_wave) : MAXT / 64;
-    const int steps = (a.K + 127) / 128, waves = waves_for(steps, most);
+    const int steps = (a.K + 127) / 128, waves = waves_for(steps, most, grid_for(a, R), num_cus);
     split_steps(a, steps, waves);
     if (const hipError_t e = allow_dynamic_lds<skinny_f16_kernel<FMT, XB, R, RING, D, MAXT>>(kLdsLimit); e != hipSuccess) return e;
-    skinny_f16_kernel<FMT, XB, R, RING, D, MAXT><<<dim3((unsigned)((a.RT + R - 1) / R)), dim3((unsigned)(waves * 64)), waves * per_wave, st>>>(a);
+    skinny_f16_kernel<FMT, XB, R, RING, D, MAXT><<<dim3(grid_for(a, R)), dim3((unsigned)(waves * 64)), waves * per_wave, st>>>(a);
     return hipGetLastError();
 }
 
 template <bool W4, int TB, int R>
-hipError_t launch_i8(SkinnyArgs a, hipStream_t st) {
+hipError_t launch_i8(SkinnyArgs a, int num_cus, hipStream_t st) {
     constexpr int VECS = R * (W4 ? 1 : 2) + 2 * TB;  // vectors per step
     constexpr int D = VECS <= 4 ? 4 : VECS <= 6 ? 3 : VECS <= 14 ? 2 : R * TB >= 12 ? 1 : 2;
     constexpr bool kWide = R == 1 && TB <= 2;
     constexpr int MAXT = kWide ? 1024 : 512;
     constexpr size_t per_wave = (size_t)R * TB * 1024;
-    const int steps = a.Kp / 128, waves = waves_for(steps, MAXT / 64);
+    const int steps = a.Kp / 128, waves = waves_for(steps, MAXT / 64, grid_for(a, R), num_cus);
     split_steps(a, steps, waves);
     if (const hipError_t e = allow_dynamic_lds<skinny_i8_kernel<W4, TB, R, D, MAXT>>(kLdsLimit); e != hipSuccess) return e;
-    skinny_i8_kernel<W4, TB, R, D, MAXT><<<dim3((unsigned)((a.RT + R - 1) / R)), dim3((unsigned)(waves * 64)), waves * per_wave, st>>>(a);
+    skinny_i8_kernel<W4, TB, R, D, MAXT><<<dim3(grid_for(a, R)), dim3((unsigned)(waves * 64)), waves * per_wave, st>>>(a);
     return hipGetLastError();
 }
 
@@ -422,8 +458,7 @@ int pick_row_tiles(const SkinnyArgs &a, float weight_bytes, float token_bytes, i
         // many rounds: balance does not matter, fewer registers and more workgroups per compute unit do
         // (128256 channels at 12 and 32 token rows, 4-bit weights: 54 and 61 us with 4, 61 and 69 us with 7 or 8)
         if (r > 4 && a.RT >= 16 * num_cus) continue;
-        const long wgs = (a.RT + r - 1) / r, rounds = (wgs + num_cus - 1) / num_cus;
-        const float cost = (float)rounds * ((float)r * 16.0f * weight_bytes + 0.4f * (float)a.M * token_bytes);
+        const float cost = ceilf(load_per_cu(a, r, num_cus)) * ((float)r * 16.0f * weight_bytes + 0.4f * (float)a.block_rows * token_bytes);
         if (best == 0 || cost < best_cost) best = r, best_cost = cost;
     }
     return best;
@@ -433,7 +468,7 @@ template <int FMT, int XB, int... RS>
 hipError_t f16_rows(const SkinnyArgs &a, int num_cus, hipStream_t st, std::integer_sequence<int, RS...> rs) {
     const int pick = pick_row_tiles(a, FMT == kW8C ? 1.0f : FMT == kW4G32 ? 0.5625f : 0.5f, 2.0f, num_cus, rs);
     hipError_t e = hipErrorInvalidValue;
-    ((pick == RS ? (void)(e = launch_f16<FMT, XB, RS>(a, st)) : (void)0), ...);
+    ((pick == RS ? (void)(e = launch_f16<FMT, XB, RS>(a, num_cus, st)) : (void)0), ...);
     return e;
 }
 
@@ -441,7 +476,7 @@ template <bool W4, int TB, int... RS>
 hipError_t i8_rows(const SkinnyArgs &a, int num_cus, hipStream_t st, std::integer_sequence<int, RS...> rs) {
     const int pick = pick_row_tiles(a, W4 ? 0.5f : 1.0f, 1.0f, num_cus, rs);
     hipError_t e = hipErrorInvalidValue;
-    ((pick == RS ? (void)(e = launch_i8<W4, TB, RS>(a, st)) : (void)0), ...);
+    ((pick == RS ? (void)(e = launch_i8<W4, TB, RS>(a, num_cus, st)) : (void)0), ...);
     return e;
 }
 
@@ -451,9 +486,21 @@ typedef std::integer_sequence<int, 1, 2, 3, 4, 5, 6, 7> Rows2W8;
 typedef std::integer_sequence<int, 1, 2, 3, 4, 5, 6> Rows3;
 typedef std::integer_sequence<int, 1, 2, 3, 4> Rows4;
 
+// (the same choice as f16_any and i8_any make)
+int row_tiles_for(const SkinnyArgs &a, int fmt, bool int8_activations, int num_cus) {
+    const float wb = fmt == kW8C ? 1.0f : fmt == kW4G32 ? 0.5625f : 0.5f, xb = int8_activations ? 1.0f : 2.0f;
+    switch ((a.block_rows + 15) / 16) {
+        case 1: return pick_row_tiles(a, wb, xb, num_cus, Rows2());
+        case 2: return fmt == kW8C && !int8_activations ? pick_row_tiles(a, wb, xb, num_cus, Rows2W8()) : pick_row_tiles(a, wb, xb, num_cus, Rows2());
+        case 3: return pick_row_tiles(a, wb, xb, num_cus, Rows3());
+        case 4: return pick_row_tiles(a, wb, xb, num_cus, Rows4());
+    }
+    return 0;
+}
+
 template <int FMT>
 hipError_t f16_any(const SkinnyArgs &a, int num_cus, hipStream_t st) {
-    switch ((a.M + 7) / 8) {
+    switch ((a.block_rows + 7) / 8) {
         case 2: return f16_rows<FMT, 2>(a, num_cus, st, Rows2());
         case 3: case 4: return f16_rows<FMT, 4>(a, num_cus, st, std::conditional_t<FMT == kW8C, Rows2W8, Rows2>());
         case 5: case 6: return f16_rows<FMT, 6>(a, num_cus, st, Rows3());
@@ -464,7 +511,7 @@ hipError_t f16_any(const SkinnyArgs &a, int num_cus, hipStream_t st) {
 
 template <bool W4>
 hipError_t i8_any(const SkinnyArgs &a, int num_cus, hipStream_t st) {
-    switch ((a.M + 15) / 16) {
+    switch ((a.block_rows + 15) / 16) {
         case 1: return i8_rows<W4, 1>(a, num_cus, st, Rows2());
         case 2: return i8_rows<W4, 2>(a, num_cus, st, Rows2());
         case 3: return i8_rows<W4, 3>(a, num_cus, st, Rows3());
@@ -490,6 +537,11 @@ SkinnyArgs make_args(const Geometry &g, const void *packed, const void *x, const
     a.RT = g.RT;
     a.rt_stride = g.rt_stride;
     a.steps_q = a.steps_rem = 0;
+    // equal blocks of at most 64 token rows, whole tiles of 16
+    a.blocks = (M + kSkinnyRows - 1) / kSkinnyRows;
+    if (tuning().skinny_blocks > a.blocks) a.blocks = tuning().skinny_blocks;
+    a.block_rows = round_up((M + a.blocks - 1) / a.blocks, a.blocks > 1 ? 16 : 1);
+    a.blocks = (M + a.block_rows - 1) / a.block_rows;
     a.sw_mul = 1.0f;
     a.gated_act = g.pair_half ? gated_act : -1;
     return a;
@@ -497,15 +549,39 @@ SkinnyArgs make_args(const Geometry &g, const void *packed, const void *x, const
 
 }  // namespace
 
-// Level with the large kernels' 256-channel tiles where those fill the chip: at 64 token rows 28672 channels
-// take 32 against 48 us (int4 groups, binary16 activations), 35.5 / 37.4 us (int8), 27.0 / 27.4 us (int4 x
-// int8); narrow layers are far apart (4096 x 14336: 27 / 142, 28 / 90, 24 / 68 us).  128256 channels
-// with int8 activations cross over at about 32 rows (8-bit weights 101 / 112 us at 32, 126 / 117 us at 64).
-bool skinny_product(const Geometry &g, int M, bool int8_activations, int num_cus) {
+// Which products these kernels take.  Up to 64 token rows: all, but for layers of very many channels with int8
+// activations, whose 256-channel tiles fill the chip (us, these kernels / the tiles: 128256 x 4096 int4 57 / 64 at
+// 48 rows, 70 / 65 at 64; int8 107 / 110 at 64; 256000 x 2304 int4 66 / 74 at 32, 98 / 80 at 64).  More rows: the tiles of 64 or 128
+// tokens take the same time until they fill the chip, and long (they leave most of it idle); here the
+// rows are cut into blocks of 64, with the time growing with their number.  Both times are estimated
+// (us; fitted to layers of 1024 to 28672 channels, K of 2048 to 14336, 77 to 1000 rows, within about 20 %):
+//   here   load x (2 + 0.9 R + K (0.35 + 0.0128 rows + 0.33 R) / 1000)    binary16 activations
+//          load x (2.5 + 0.5 R + K (0.25 + 0.0102 rows + (0.27 | 0.15) R) / 1000)   int8 x (int8 | int4)
+//   tiles  9 + 9.3 K / 1000 a round; 5 + (4.4 | 3.85) K / 1000
+// Measured (us, tiles / here): 4096 x 14336 int4, binary16 activations, 77 rows 131 / 24, 300 131 / 64, 512 133 / 75;
+// 2304 x 9216 int4 groups 77 rows 96 / 17, 300 98 / 26, 1000 98 / 84; 18432 x 2304 77 rows 31 / 22, 200 31 / 38;
+// int8 x int8 6144 x 4096 77 rows 26 / 11, 300 25 / 21, 512 25 / 29; int8 x int4 4096 x 14336 77 rows 60 / 17, 512 60 / 47.
+bool skinny_product(const Geometry &g, int M, bool int8_activations, bool gated, int num_cus) {
     if (tuning().gemm_variant != 0) return false;  // a large kernel is asked for by name
-    const int forced = tuning().skinny_max_m;
-    const int most = forced >= 0 ? forced : int8_activations && g.RT >= 16 * num_cus ? 32 : kSkinnyMaxM;
-    return M <= most && M <= kSkinnyMaxM;
+    if (tuning().skinny_max_m >= 0) return M <= tuning().skinny_max_m;
+    if (M <= kSkinnyRows) return !(int8_activations && g.RT >= 16 * num_cus) || M <= (g.fmt == kW8C ? 64 : 48);
+    if (M > kSkinnyMaxM) return false;
+    const SkinnyArgs a = make_args(g, nullptr, nullptr, nullptr, M, nullptr, nullptr, gated ? 0 : -1);
+    const int R = row_tiles_for(a, g.fmt, int8_activations, num_cus);
+    if (R == 0) return false;
+    const float k = 1e-3f * (float)g.K, rows = (float)a.block_rows, r = (float)R;
+    const float load = fmaxf(1.0f, 0.95f * load_per_cu(a, R, num_cus));
+    const long n256 = (g.N + 255) / 256, m128 = (M + 127) / 128, m64 = (M + 63) / 64;
+    if (!int8_activations) {
+        const float here = load * (2.0f + 0.9f * r + k * (0.35f + 0.0128f * rows + 0.33f * r));
+        const bool staged = g.fmt == kW8C || g.K % 128 != 0;  // 128 x 128 tiles, two workgroups per compute unit
+        const float rounds = staged ? fmaxf(1.0f, (float)((g.N + 127) / 128 * m128) / (float)num_cus) : ceilf((float)(n256 * m128) / (float)num_cus);
+        return here < rounds * (9.0f + 9.3f * k);
+    }
+    const float here = load * (2.5f + 0.5f * r + k * (0.25f + 0.0102f * rows + (g.fmt == kW8C ? 0.27f : 0.15f) * r));
+    const bool wide = 4 * n256 * m128 >= 3L * num_cus;  // (their choice between 128 and 64 tokens)
+    const float tiles = 5.0f + (g.fmt == kW8C ? 4.4f : 3.85f) * k;
+    return here < 0.9f * tiles * (wide ? fmaxf(1.25f, 1.6f * (float)(n256 * m128) / (float)num_cus) : fmaxf(1.0f, 0.7f * (float)(n256 * m64) / (float)num_cus));
 }
 
 hipError_t launch_skinny_f16(const Geometry &g, const void *packed, const void *x, int M, void *y, const void *residual,

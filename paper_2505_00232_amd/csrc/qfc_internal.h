@@ -136,6 +136,7 @@ struct Tuning {
     Tunable skinny_row_tiles{0};  // few token rows: row tiles per workgroup (0: automatic)
     Tunable skinny_max_m{-1};   // largest M of those kernels (-1: automatic; 0: never)
     Tunable gemv_pairs{0};      // gated output, pairs of row tiles per decode workgroup (0: automatic)
+    Tunable skinny_blocks{0};   // blocks the token rows are cut into at least (0: automatic)
     Tunable gemv_half{-1};      // half-unit items of the decode kernel: -1 automatic, 0 never, 1 where possible
 };
 Tuning &tuning();
@@ -345,9 +346,10 @@ hipError_t launch_gemm_i8(const Geometry &g, const void *packed, const int8_t *x
 hipError_t launch_gemm_f16(const Geometry &g, const void *packed, const void *x, int M, void *y,
                            const void *residual, int gated_act, int num_cus, hipStream_t st);
 
-// Few token rows (9 .. kSkinnyMaxM): see gemm_skinny.hip.  Arguments as the two launchers above.
-constexpr int kSkinnyMaxM = 64;
-bool skinny_product(const Geometry &g, int M, bool int8_activations, int num_cus);
+// Few token rows (9 .. kSkinnyMaxM, where they are the faster ones): see gemm_skinny.hip.  Arguments as the two launchers above.
+constexpr int kSkinnyRows = 64;  // token rows per workgroup at most
+constexpr int kSkinnyMaxM = 1024;
+bool skinny_product(const Geometry &g, int M, bool int8_activations, bool gated, int num_cus);
 hipError_t launch_skinny_f16(const Geometry &g, const void *packed, const void *x, int M, void *y, const void *residual,
                              int gated_act, int num_cus, hipStream_t st);
 hipError_t launch_skinny_i8(const Geometry &g, const void *packed, const int8_t *xq_tiled, const float *sx, int M,

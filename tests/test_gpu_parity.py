@@ -1674,6 +1674,45 @@ def test_few_token_rows_match_oracle(fmt, mode, M, N, K, row_tiles):
     layer.close()
 
 
+@pytest.mark.parametrize("fmt,mode", [("w4g32", None), ("w4c", None), ("w8c", binding.QFC_COMPUTE_FP16_DEQUANT),
+                                      ("w8c", None), ("w4c", binding.QFC_COMPUTE_INT8_ACT)])
+@pytest.mark.parametrize("M,N,K,row_tiles,blocks", [(65, 40, 160, 0, 0), (77, 300, 2304, 2, 0), (96, 130, 416, 3, 0), (97, 130, 416, 4, 0),
+                                                    (129, 1000, 96, 1, 0), (250, 70, 544, 0, 6), (300, 264, 1184, 3, 0), (513, 96, 2048, 0, 0), (100, 200, 256, 8, 4)])
+def test_blocks_of_token_rows_match_oracle(fmt, mode, M, N, K, row_tiles, blocks):
+    """More than 64 token rows in blocks of equal size: blocks that end past the last row, a last block of few rows,
+    row groups that do not fill all XCDs; and the tiles of the large kernels at the same sizes."""
+    print(f"blocks of token rows {fmt} mode={mode} M={M} N={N} K={K} row tiles={row_tiles} blocks={blocks}", flush=True)
+    wq, s = synth.weights(6100, M, N, synth.FC("t", K, N, fmt))
+    x = synth.activations(6100, M, N, M, K)
+    res = synth.activations(6100, M, N + 1, M, N)
+    layer = _layer(wq, s, fmt, max_m=M, mode=mode)
+    int8 = mode == binding.QFC_COMPUTE_INT8_ACT or (fmt == "w8c" and mode is None)
+    ref = oracle.fc_int8_act(x, wq, s)[3] if int8 else oracle.fc_weight_only(x, wq, s, _group(fmt))
+    xd, rd = torch.from_numpy(x).to(DEV), torch.from_numpy(res).to(DEV)
+    outs = []
+    for max_m in (1024, 0):  # these kernels, the large ones
+        guard = torch.full((M + 1, N), 77.0, dtype=torch.float16, device=DEV)
+        y = guard[:M]
+        binding.qfc_tune(8, row_tiles)
+        binding.qfc_tune(9, max_m)
+        binding.qfc_tune(11, blocks)
+        try:
+            binding.qfc_forward(layer.handle, xd, y)
+            outs.append(y.cpu().numpy())
+            binding.qfc_forward_fused(layer.handle, xd, y, residual=rd)
+            torch.cuda.synchronize()
+        finally:
+            binding.qfc_tune(8, 0)
+            binding.qfc_tune(9, -1)
+            binding.qfc_tune(11, 0)
+        assert _E(outs[-1], ref) <= TOL, max_m
+        assert _E(y.cpu().numpy(), ref + res.astype(np.float64)) <= TOL, max_m
+        assert bool((guard[M] == 77.0).all())
+    if int8:
+        assert np.array_equal(outs[0].view(np.uint16), outs[1].view(np.uint16))
+    layer.close()
+
+
 @pytest.mark.parametrize("B,S,h_q,h_kv,d,C,pos0", [(1, 128, 3, 1, 64, 192, 64), (1, 1100, 6, 2, 64, 1152, 13),
                                                    (3, 50, 8, 2, 128, 128, 61), (2, 700, 4, 4, 128, 768, 7), (1, 257, 8, 4, 256, 320, 63)])
 def test_rope_qkv_many_tokens(B, S, h_q, h_kv, d, C, pos0):
