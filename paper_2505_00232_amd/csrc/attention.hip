@@ -438,15 +438,14 @@ __global__ __launch_bounds__(64) void attn_combine_kernel(AttnArgs a) {
     float o = 0.0f;
     const float *src = a.ws_o + row0 * D + col;
     const size_t step = (size_t)a.M * D;
-    int s = 0;
-    for (; s + 8 <= a.splits; s += 8) {  // eight loads in flight
+    // eight loads in flight, also at the end: splits past the last read the last one again, their factor is 0
+    for (int s = 0; s < a.splits; s += 8) {
         float v[8];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) v[u] = src[(size_t)(s + u) * step];
+        for (int u = 0; u < 8; ++u) v[u] = src[(size_t)min(s + u, a.splits - 1) * step];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) o = fmaf(__shfl(f, s + u, 64), v[u], o);
+        for (int u = 0; u < 8; ++u) o = fmaf(s + u < a.splits ? __shfl(f, s + u, 64) : 0.0f, v[u], o);
     }
-    for (; s < a.splits; ++s) o = fmaf(__shfl(f, s, 64), src[(size_t)s * step], o);
     a.out[((size_t)G * a.M + mm) * D + col] = (_Float16)(o / lsum);
 }
 
@@ -875,15 +874,25 @@ hipError_t launch_attn(const AttnArgs &a, int G, hipStream_t st) {
 
 }  // namespace
 
-// Workgroups per (batch, KV head) group: enough wavefronts to fill the chip, at least one block
-// of 32 positions per wavefront, at most kAttnMaxSplits.
-int attn_splits(int G, int n_ctx, int num_cus) {
-    const int nb = (n_ctx + 63) / 64;
-    int s = (8 * num_cus + 4 * G - 1) / (4 * G);
-    if (s > (nb + 3) / 4) s = (nb + 3) / 4;  // at least one step of 64 positions per wavefront
+// Decode: workgroups per (batch, KV head) group.  One workgroup per compute unit, as far as there are steps: a
+// compute unit pulls about 35 GB/s with the operands of four wavefronts in flight, so the cache is
+// spread over all of them even if only one wavefront of a workgroup has a step, and a second batch of workgroups
+// on some compute units is what the launch would wait for.  Not for up to four steps (one per wavefront of a single
+// workgroup, and no second launch), and beyond 24 only with two steps each (the combination gets
+// slower).  Where one workgroup per compute unit leaves more than 40 % of them idle: two per compute unit.
+// Measured (us, G = groups; 1 to 64 workgroups each, the best of them / this rule / 4 steps per workgroup as
+// long as there are 2 workgroups per compute unit): head size 128, G = 8: 1280 positions 8.0 / 8.0 / 9.5, 12001
+// 15.9 / 16.1 / 18.1; G = 56: 3000 21.5 / 21.5 / 25.8, 9000 51.3 / 51.3 / 61.0; G = 256: 300 11.6 / 11.6 /
+// 14.5; head size 256, G = 4: 1280 8.7 / 8.7 / 12.9; G = 20: 9000 40.1 / 40.1 / 51.8; G = 44: 1500 20.0 / 20.0 / 27.6.
+int attn_splits(int G, int d, int n_ctx, int num_cus) {
+    const int step = d <= 128 ? 64 : 32, steps = (n_ctx + step - 1) / step;
+    if (steps <= 4 || num_cus < 1) return 1;
+    int s = num_cus / G;
+    if (5L * G * s < 3L * num_cus) s = 2 * num_cus / G;
+    if (s > 24 && s > steps / 2) s = steps / 2 > 24 ? steps / 2 : 24;
+    if (s > steps) s = steps;
     if (s > kAttnMaxSplits) s = kAttnMaxSplits;
-    if (s < 1) s = 1;
-    return s;
+    return s < 1 ? 1 : s;
 }
 
 // The many-query-rows path needs partial results only where it may cut walks into chunks: launches
@@ -944,7 +953,7 @@ hipError_t launch_attention(const void *q, const void *kc, const void *vc, int G
     a.S = S;
     a.C = C;
     a.n_ctx = n_ctx;
-    a.splits = attn_splits(G, n_ctx, num_cus);
+    a.splits = tuning().attn_splits > 0 ? (int)tuning().attn_splits : attn_splits(G, d, n_ctx, num_cus);
     a.num_cus = num_cus > 0 ? num_cus : 1;
     {
         const long wgs = (long)((a.M + 127) / 128) * G;

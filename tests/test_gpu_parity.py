@@ -1261,6 +1261,36 @@ def test_attention_over_the_cache(B, S, h_q, h_kv, d, C, n_ctx):
     assert _E(got.reshape(G * M, d), ref.reshape(G * M, d)) <= TOL
 
 
+@pytest.mark.parametrize("B,S,h_q,h_kv,d,C,n_ctx", [(1, 1, 4, 1, 64, 640, 577), (2, 1, 8, 2, 128, 704, 700), (1, 3, 4, 1, 256, 384, 321)])
+def test_attention_any_number_of_workgroups_per_head(B, S, h_q, h_kv, d, C, n_ctx):
+    """The combination of 1 to 64 partial results (whole and broken groups of eight), workgroups with one step for
+    four wavefronts and with none; and the number the library picks."""
+    print(f"attention splits B={B} S={S} h_q={h_q} h_kv={h_kv} d={d} n_ctx={n_ctx}", flush=True)
+    G, M = B * h_kv, S * (h_q // h_kv)
+    rng = np.random.default_rng(n_ctx)
+    q = rng.standard_normal((G, M, d)).astype(np.float16)
+    K = rng.standard_normal((G, C, d)).astype(np.float16)
+    V = rng.standard_normal((G, d, C)).astype(np.float16)
+    K[:, 5] = (q[:, 0].astype(np.float32) * 2).astype(np.float16)
+    ref = oracle.attention(q, K, V, n_ctx, S)
+    K[:, n_ctx:] = np.float16(np.nan)
+    V[:, :, n_ctx:] = np.float16(np.inf)
+    shape = _attn_shape(B, h_q, h_kv, d, C)
+    ws = torch.empty(binding.qfc_attention_workspace_size(shape, S), dtype=torch.uint8, device=DEV)
+    qd, kd, vd = torch.from_numpy(q).to(DEV), torch.from_numpy(K).to(DEV), binding.vcache_physical(torch.from_numpy(V).to(DEV))
+    for splits in (0, 1, 2, 7, 8, 9, 11, 16, 17, 33, 63, 64):
+        out = torch.full((G, M, d), 9.0, dtype=torch.float16, device=DEV)
+        binding.qfc_tune(12, splits)
+        try:
+            binding.qfc_attention(qd, kd, vd, S, n_ctx, shape, ws, out)
+            torch.cuda.synchronize()
+        finally:
+            binding.qfc_tune(12, 0)
+        got = out.cpu().numpy()
+        assert np.all(np.isfinite(got)), splits
+        assert _E(got.reshape(G * M, d), ref.reshape(G * M, d)) <= TOL, splits
+
+
 @pytest.mark.parametrize("B,S,h_q,h_kv,d,C,n_ctx", [(1, 5, 8, 2, 64, 64, 5), (1, 40, 4, 4, 128, 128, 40),
                                                     (2, 33, 8, 2, 128, 192, 150), (1, 100, 8, 4, 256, 128, 100),
                                                     (1, 256, 32, 8, 128, 512, 300), (1, 64, 16, 1, 64, 1024, 1000),
