@@ -95,8 +95,7 @@ __global__ __launch_bounds__(256) void gemm_f16_w4_kernel(GemmF16Args a) {
     const int wn = wave & 1, wm = wave >> 1;
 
     const int total = a.n_tiles * a.m_tiles;
-    int logical = blockIdx.x;
-    if (total % 8 == 0) logical = (blockIdx.x % 8) * (total / 8) + blockIdx.x / 8;
+    const int logical = xcd_order(blockIdx.x, total);
     const int nt = logical / a.m_tiles;
     const int mt = logical % a.m_tiles;
 
@@ -391,8 +390,7 @@ __global__ __launch_bounds__(512) void gemm_f16_w4_direct_kernel(GemmF16Args a) 
         nt = (xcd & 1) * cn + j / cm;
         mt = (xcd >> 1) * cm + j % cm;
     } else {
-        int logical = blockIdx.x;
-        if (total % 8 == 0) logical = (blockIdx.x % 8) * (total / 8) + blockIdx.x / 8;
+        const int logical = xcd_order(blockIdx.x, total);
         nt = logical / a.m_tiles;
         mt = logical % a.m_tiles;
     }

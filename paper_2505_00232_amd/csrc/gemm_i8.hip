@@ -273,8 +273,7 @@ __global__ __launch_bounds__(256, (BN * BM > 128 * 256) ? 1 : 2) void gemm_i8_ke
     const int wn = wave & 1, wm = wave >> 1;
 
     const int total = a.n_tiles * a.m_tiles;
-    int logical = blockIdx.x;
-    if (total % 8 == 0) logical = (blockIdx.x % 8) * (total / 8) + blockIdx.x / 8;
+    const int logical = xcd_order(blockIdx.x, total);
     const int nt = logical / a.m_tiles;
     const int mt = logical % a.m_tiles;
     const int KT = a.Kp / 64;
@@ -396,8 +395,7 @@ __global__ __launch_bounds__(256, 2) void gemm_i8_w4_kernel(GemmI8Args a) {
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wn = wave & 1, wm = wave >> 1;
     const int total = a.n_tiles * a.m_tiles;
-    int logical = blockIdx.x;
-    if (total % 8 == 0) logical = (blockIdx.x % 8) * (total / 8) + blockIdx.x / 8;
+    const int logical = xcd_order(blockIdx.x, total);
     const int nt = logical / a.m_tiles;
     const int mt = logical % a.m_tiles;
     const int stages = a.Kp / 128;
@@ -534,8 +532,7 @@ __global__ __launch_bounds__(256, 2) void gemm_i8_dw_kernel(GemmI8Args a) {
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int total = a.n_tiles * a.m_tiles;
-    int logical = blockIdx.x;
-    if (total % 8 == 0) logical = (blockIdx.x % 8) * (total / 8) + blockIdx.x / 8;
+    const int logical = xcd_order(blockIdx.x, total);
     const int nt = logical / a.m_tiles, mt = logical % a.m_tiles;
     const int KT = a.Kp / 64;  // stages
 
@@ -702,8 +699,7 @@ __global__ __launch_bounds__(256, 2) void gemm_i8_dw4_kernel(GemmI8Args a) {
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int total = a.n_tiles * a.m_tiles;
-    int logical = blockIdx.x;
-    if (total % 8 == 0) logical = (blockIdx.x % 8) * (total / 8) + blockIdx.x / 8;
+    const int logical = xcd_order(blockIdx.x, total);
     const int nt = logical / a.m_tiles, mt = logical % a.m_tiles;
     const int KT = a.Kp / 128;  // stages
 
