@@ -35,7 +35,8 @@ extern "C" {
  *   key 9  the same: largest number of token rows they are used for (-1 automatic, 0 never)
  *   key 10 gated output at M <= 8: pairs of row tiles per decode workgroup (0 = automatic; 1, 2)
  *   key 11 as key 7: blocks the token rows are cut into at least (0 = automatic)
- *   key 12 attention with at most 16 query rows per KV head: workgroups per KV head (0 = automatic; 1 .. 64) */
+ *   key 12 attention with at most 16 query rows per KV head: workgroups per KV head (0 = automatic; 1 .. 64)
+ *   key 13 attention with more than 16 query rows per KV head: blocks of 16 (-1 automatic, 0 never, 1 always) */
 void qfc_tune(int32_t key, int32_t value);
 
 /* Measurement probe (bench.py --probe-mfma): `workgroups` workgroups of four wavefronts each issue

@@ -518,6 +518,7 @@ void qfc_tune(int32_t key, int32_t value) {
     if (key == 9) t.skinny_max_m = value;
     if (key == 10) t.gemv_pairs = value;
     if (key == 11) t.skinny_blocks = value;
+    if (key == 13) t.attn_few = value;
     if (key == 12) t.attn_splits = value < 0 ? 0 : value > kAttnMaxSplits ? kAttnMaxSplits : value;
 }
 

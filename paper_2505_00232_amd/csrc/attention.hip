@@ -216,7 +216,7 @@ struct AttnArgs {
     float scale;
 };
 
-// Workgroup = 4 wavefronts.  grid = (splits, G).  A step covers TP pairs of score tiles = 32 TP positions:
+// Workgroup = 4 wavefronts and up to 16 query rows.  grid = (splits, G, blocks of 16 query rows).  A step covers TP pairs of score tiles = 32 TP positions:
 // 64 for head sizes up to 128, 32 for 256 (whose operands of 64 positions would leave one wavefront per SIMD).
 // Two workgroups per compute unit (up to head size 128) are said in the launch bounds so that the accumulators stay in
 // ordinary registers (with the whole register file at its disposal the compiler parks them in
@@ -233,20 +233,22 @@ __global__ __launch_bounds__(256, D <= 128 ? 2 : 1) void attn_partial_kernel(Att
     const int m = lane & 15, r = lane >> 4;
     const int G = blockIdx.y;
     const int part = blockIdx.x, parts = a.splits;
-    const int nb = (a.n_ctx + SP - 1) / SP;  // steps
+    const int row0 = 16 * blockIdx.z, rows = min(16, a.M - row0);
+    const int n_end = a.n_ctx - a.S + (row0 + rows - 1) / a.g + 1;  // positions the block's last row sees
+    const int nb = (n_end + SP - 1) / SP;  // steps
     // the workgroup takes a contiguous range of steps; its wavefronts take every fourth step of it
     const int b0 = (int)((long)part * nb / parts) + wave, b1 = (int)((long)(part + 1) * nb / parts);
 
-    // Q^T operand: lane (m, r) holds Q[m][32 j + 8 r .. + 7]; rows >= M are zero
+    // Q^T operand: lane (m, r) holds Q[row0 + m][32 j + 8 r .. + 7]; rows past the last are zero
     u32x4 qf[DJ];
 #pragma unroll
     for (int j = 0; j < DJ; ++j) {
         const u32x4 zero = {0, 0, 0, 0};
-        qf[j] = m < a.M ? *reinterpret_cast<const u32x4 *>(a.q + ((size_t)G * a.M + m) * D + 32 * j + 8 * r) : zero;
+        qf[j] = m < rows ? *reinterpret_cast<const u32x4 *>(a.q + ((size_t)G * a.M + row0 + m) * D + 32 * j + 8 * r) : zero;
     }
     // positions a query row may see: those before the end of its own token
-    // (rows >= M are all-zero queries whose results are never stored: they see everything)
-    const int lim = m < a.M ? a.n_ctx - a.S + m / a.g + 1 : a.n_ctx;
+    // (rows past the last are all-zero queries whose results are never stored: they see everything)
+    const int lim = m < rows ? a.n_ctx - a.S + (row0 + m) / a.g + 1 : n_end;
 
     v4f acc[DT];
 #pragma unroll
@@ -309,7 +311,7 @@ __global__ __launch_bounds__(256, D <= 128 ? 2 : 1) void attn_partial_kernel(Att
         // reach past the first query token's horizon, masked
         float sc[8 * TP];
         float bmax = kNegBig;
-        const bool edge = k0 + SP > a.n_ctx - a.S + 1;  // same for the whole wavefront
+        const bool edge = k0 + SP > a.n_ctx - a.S + row0 / a.g + 1;  // same for the whole wavefront
         if (!edge) {
 #pragma unroll
             for (int e = 0; e < 8 * TP; ++e) {
@@ -344,7 +346,7 @@ __global__ __launch_bounds__(256, D <= 128 ? 2 : 1) void attn_partial_kernel(Att
         }
         run_sum = run_sum * corr + psum;
         // positions at or past the end of the context may hold anything (0 * NaN would poison the sum)
-        if (k0 + SP > a.n_ctx) {
+        if (k0 + SP > n_end) {
 #pragma unroll
             for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
@@ -353,8 +355,8 @@ __global__ __launch_bounds__(256, D <= 128 ? 2 : 1) void attn_partial_kernel(Att
                     uint32_t w[4] = {vf[dt][u].x, vf[dt][u].y, vf[dt][u].z, vf[dt][u].w};
 #pragma unroll
                     for (int e = 0; e < 4; ++e) {
-                        if (p0 + 2 * e >= a.n_ctx) w[e] &= 0xFFFF0000u;
-                        if (p0 + 2 * e + 1 >= a.n_ctx) w[e] &= 0x0000FFFFu;
+                        if (p0 + 2 * e >= n_end) w[e] &= 0xFFFF0000u;
+                        if (p0 + 2 * e + 1 >= n_end) w[e] &= 0x0000FFFFu;
                     }
                     vf[dt][u] = u32x4{w[0], w[1], w[2], w[3]};
                 }
@@ -389,7 +391,7 @@ __global__ __launch_bounds__(256, D <= 128 ? 2 : 1) void attn_partial_kernel(Att
         mine[D + 1] = run_sum;
     }
     __syncthreads();
-    for (int e = threadIdx.x; e < a.M * D; e += 256) {
+    for (int e = threadIdx.x; e < rows * D; e += 256) {
         const int mm = e / D, dd = e % D;
         float mx = kNegBig;
 #pragma unroll
@@ -403,9 +405,9 @@ __global__ __launch_bounds__(256, D <= 128 ? 2 : 1) void attn_partial_kernel(Att
             l += f * src[D + 1];
         }
         if (a.splits == 1) {
-            a.out[((size_t)G * a.M + mm) * D + dd] = (_Float16)(o / l);
+            a.out[((size_t)G * a.M + row0 + mm) * D + dd] = (_Float16)(o / l);
         } else {
-            const size_t p = ((size_t)G * a.splits + blockIdx.x) * a.M + mm;
+            const size_t p = ((size_t)G * a.splits + blockIdx.x) * a.M + row0 + mm;
             a.ws_o[p * D + dd] = o;
             if (dd == 0) {
                 a.ws_ml[p * 2] = mx;
@@ -865,7 +867,7 @@ template <int D>
 hipError_t launch_attn(const AttnArgs &a, int G, hipStream_t st) {
     const size_t lds = (size_t)4 * 16 * (D + 4) * sizeof(float);
     if (const hipError_t e = allow_dynamic_lds<attn_partial_kernel<D>>(lds); e != hipSuccess) return e;
-    attn_partial_kernel<D><<<dim3((unsigned)a.splits, (unsigned)G), 256, lds, st>>>(a);
+    attn_partial_kernel<D><<<dim3((unsigned)a.splits, (unsigned)G, (unsigned)((a.M + 15) / 16)), 256, lds, st>>>(a);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || a.splits == 1) return e;
     attn_combine_kernel<D><<<dim3((unsigned)a.M, (unsigned)G, D / 64), 64, 0, st>>>(a);
@@ -893,6 +895,33 @@ int attn_splits(int G, int d, int n_ctx, int num_cus) {
     if (s > steps) s = steps;
     if (s > kAttnMaxSplits) s = kAttnMaxSplits;
     return s < 1 ? 1 : s;
+}
+
+// More than 16 query rows (prompts): blocks of 16 rows in the decode kernel, or the kernel for blocks of 128.  That one
+// reads each position once per 128 rows, but from a few workgroups, each with a long walk: a short prompt
+// waits for it.  Here the positions are read once per 16 rows and the walks are split over wavefronts and
+// workgroups, which wins as long as the steps (of a wavefront: 16 rows x 64 positions) are few.  Measured
+// (us, 128-row blocks / 16-row blocks): head size 256, 4 groups of 2 heads, prompts of 77 tokens 13.8 / 8.9, of
+// 300 22.4 / 15.5, 77 behind 923 positions 22.2 / 15.8; head size 128, 8 groups of 4 heads, 41 behind 120 9.5 / 7.6, 100 8.3 /
+// 6.8, 37 behind 1071 (1440 steps) 14.9 / 16.0, 300 (3000 steps) 13.1 / 21.0; up to 32 positions the 128-row
+// kernel has one step and is level or faster.
+static bool few_row_blocks(int G, int M, int d, int n_ctx) {
+    return n_ctx > 32 && (long)G * ((M + 15) / 16) * ((n_ctx + 63) / 64) <= (d <= 128 ? 1200 : 2100);
+}
+
+// Workgroups per block of 16 query rows and KV head: the estimated time (us) of the walk and the combination.
+static int row_block_splits(int G, int M, int d, int n_ctx, int num_cus) {
+    const int step = d <= 128 ? 64 : 32, steps = (n_ctx + step - 1) / step, blocks = (M + 15) / 16;
+    const float step_us = d <= 64 ? 2.0f : 3.7f, slots = (float)num_cus * (d <= 128 ? 2.0f : 1.0f);
+    int best = 1;
+    float best_us = 0.0f;
+    for (int s = 1; s <= kPrefillMaxChunks; ++s) {
+        const float load = (float)G * (float)blocks * (float)s / slots;
+        float us = (load > 1.0f ? load : 1.0f) * (float)((steps + 4 * s - 1) / (4 * s)) * step_us;
+        if (s > 1) us += 2.2f + (float)G * (float)M * (float)s * (float)d * 8.0f / 0.7e6f;
+        if (s == 1 || us < best_us) best = s, best_us = us;
+    }
+    return best;
 }
 
 // The many-query-rows path needs partial results only where it may cut walks into chunks: launches
@@ -1017,7 +1046,17 @@ hipError_t launch_attention(const void *q, const void *kc, const void *vc, int G
     a.ws_o = static_cast<float *>(workspace);
     a.ws_ml = a.ws_o + (size_t)G * (a.M > 16 ? kPrefillMaxChunks : kAttnMaxSplits) * a.M * d;
     a.out = static_cast<_Float16 *>(out);
-    if (a.M > 16) {
+    bool few = a.M <= 16;
+    if (!few) {
+        const int forced = tuning().attn_few;
+        few = forced >= 0 ? forced != 0 : few_row_blocks(G, a.M, d, n_ctx);
+        if (few) {  // partial results fit the workspace of the chunks
+            const int most = prefill_may_chunk(G, a.M, num_cus) ? kPrefillMaxChunks : 1;
+            if (tuning().attn_splits == 0) a.splits = row_block_splits(G, a.M, d, n_ctx, a.num_cus);
+            if (a.splits > most) a.splits = most;
+        }
+    }
+    if (!few) {
         switch (d) {
             case 64: return launch_attn_prefill<64>(a, G, st);
             case 128: return launch_attn_prefill<128>(a, G, st);

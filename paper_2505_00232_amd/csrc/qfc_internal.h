@@ -137,6 +137,7 @@ struct Tuning {
     Tunable skinny_max_m{-1};   // largest M of those kernels (-1: automatic; 0: never)
     Tunable gemv_pairs{0};      // gated output, pairs of row tiles per decode workgroup (0: automatic)
     Tunable skinny_blocks{0};   // blocks the token rows are cut into at least (0: automatic)
+    Tunable attn_few{-1};       // attention, blocks of 16 query rows: -1 automatic, 0 above 16 rows never, 1 always
     Tunable attn_splits{0};     // decode attention: workgroups per KV head (0: automatic)
     Tunable gemv_half{-1};      // half-unit items of the decode kernel: -1 automatic, 0 never, 1 where possible
 };

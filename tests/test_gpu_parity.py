@@ -1347,6 +1347,42 @@ def test_attention_many_query_rows(B, S, h_q, h_kv, d, C, n_ctx):
         assert np.allclose(got[:, :g].astype(np.float64), np.repeat(V[:, None, :, 0], g, axis=1).astype(np.float64), rtol=2e-3, atol=2e-3)
 
 
+@pytest.mark.parametrize("B,S,h_q,h_kv,d,C,n_ctx", [(1, 17, 1, 1, 64, 64, 17), (1, 33, 2, 1, 64, 192, 160), (1, 41, 8, 2, 128, 192, 161),
+                                                    (2, 23, 6, 2, 128, 640, 600), (1, 77, 8, 4, 256, 128, 77), (1, 19, 4, 2, 256, 512, 450),
+                                                    (1, 150, 10, 2, 128, 192, 150)])
+def test_attention_blocks_of_sixteen_query_rows(B, S, h_q, h_kv, d, C, n_ctx):
+    """More than 16 query rows in blocks of 16, causal by token: tokens that straddle two blocks, a last block of few
+    rows, blocks whose walks end before others', one to eight partial results; against the oracle and
+    with what lies past the context poisoned."""
+    print(f"attention row blocks B={B} S={S} h_q={h_q} h_kv={h_kv} d={d} n_ctx={n_ctx}", flush=True)
+    G, M = B * h_kv, S * (h_q // h_kv)
+    rng = np.random.default_rng(n_ctx * 13 + S)
+    q = rng.standard_normal((G, M, d)).astype(np.float16)
+    K = rng.standard_normal((G, C, d)).astype(np.float16)
+    V = rng.standard_normal((G, d, C)).astype(np.float16)
+    K[:, 3] = (q[:, 0].astype(np.float32) * 2).astype(np.float16)
+    ref = oracle.attention(q, K, V, n_ctx, S)
+    K[:, n_ctx:] = np.float16(np.nan)
+    V[:, :, n_ctx:] = np.float16(np.inf)
+    shape = _attn_shape(B, h_q, h_kv, d, C)
+    ws = torch.empty(binding.qfc_attention_workspace_size(shape, S), dtype=torch.uint8, device=DEV)
+    qd, kd, vd = torch.from_numpy(q).to(DEV), torch.from_numpy(K).to(DEV), binding.vcache_physical(torch.from_numpy(V).to(DEV))
+    for few, splits in ((0, 0), (-1, 0), (1, 0), (1, 1), (1, 3), (1, 8)):
+        guard = torch.full((G + 1, M, d), 9.0, dtype=torch.float16, device=DEV)
+        binding.qfc_tune(12, splits)
+        binding.qfc_tune(13, few)
+        try:
+            binding.qfc_attention(qd, kd, vd, S, n_ctx, shape, ws, guard[:G])
+            torch.cuda.synchronize()
+        finally:
+            binding.qfc_tune(12, 0)
+            binding.qfc_tune(13, -1)
+        got = guard[:G].cpu().numpy()
+        assert np.all(np.isfinite(got)), (few, splits)
+        assert _E(got.reshape(G * M, d), ref.reshape(G * M, d)) <= TOL, (few, splits)
+        assert bool((guard[G] == 9.0).all())
+
+
 def test_attention_few_blocks_needs_the_larger_workspace():
     """Few blocks of query rows (fewer than compute units): the walks may be cut into chunks, whose
     partial results live in the workspace; the size query says how much, a smaller one is refused."""
