@@ -45,6 +45,7 @@ struct GemmF16Args {
     const _Float16 *res;  // [M, N] residual added before the rounding, or null
     const float *sw;  // W4C: fp32 scale per output channel [Np]
     int M, N, K, KT, rt_stride, n_tiles, m_tiles;
+    int by_tokens;  // order of the tiles (see xcd_tile)
     int gated_act = -1;  // QFC_ACT_*: the layer is packed in pairs and y [M, N/2] = fp16(act(gate) * other)
 };
 
@@ -94,10 +95,8 @@ __global__ __launch_bounds__(256) void gemm_f16_w4_kernel(GemmF16Args a) {
     const int wave = tid >> 6;
     const int wn = wave & 1, wm = wave >> 1;
 
-    const int total = a.n_tiles * a.m_tiles;
-    const int logical = xcd_order(blockIdx.x, total);
-    const int nt = logical / a.m_tiles;
-    const int mt = logical % a.m_tiles;
+    int nt, mt;
+    xcd_tile(blockIdx.x, a.n_tiles, a.m_tiles, a.by_tokens, nt, mt);
 
     // weights: thread -> two packed vectors per stage: row tile (tid / 64) and (tid / 64 + 4)
     const int c = lane & 15, q = lane >> 4;
@@ -390,9 +389,7 @@ __global__ __launch_bounds__(512) void gemm_f16_w4_direct_kernel(GemmF16Args a) 
         nt = (xcd & 1) * cn + j / cm;
         mt = (xcd >> 1) * cm + j % cm;
     } else {
-        const int logical = xcd_order(blockIdx.x, total);
-        nt = logical / a.m_tiles;
-        mt = logical % a.m_tiles;
+        xcd_tile(blockIdx.x, a.n_tiles, a.m_tiles, a.by_tokens, nt, mt);
     }
 
     const int KT = a.KT;  // packed weight tiles (128 k) per row tile; K is a multiple of 128 here
@@ -740,6 +737,7 @@ hipError_t launch_direct(GemmF16Args a, int M, hipStream_t st) {
     if (const hipError_t e = allow_dynamic_lds<gemm_f16_w4_direct_kernel<PC>>(kDirectLdsBytes); e != hipSuccess) return e;
     a.n_tiles = (a.N + DBN - 1) / DBN;
     a.m_tiles = (M + DBM - 1) / DBM;
+    a.by_tokens = walk_by_tokens(a.n_tiles, a.m_tiles, (PC ? 0.5f : 0.5625f) * DBN, 2.0f * DBM);
     gemm_f16_w4_direct_kernel<PC><<<dim3((unsigned)(a.n_tiles * a.m_tiles)), 512, kDirectLdsBytes, st>>>(a);
     return hipGetLastError();
 }
@@ -749,6 +747,7 @@ hipError_t launch_fallback(GemmF16Args a, int M, hipStream_t st) {
     if (const hipError_t e = allow_dynamic_lds<gemm_f16_w4_kernel<PC, W8>>(kLdsBytes); e != hipSuccess) return e;
     a.n_tiles = (a.N + BN - 1) / BN;
     a.m_tiles = (M + BM - 1) / BM;
+    a.by_tokens = walk_by_tokens(a.n_tiles, a.m_tiles, (W8 ? 1.0f : PC ? 0.5f : 0.5625f) * BN, 2.0f * BM);
     gemm_f16_w4_kernel<PC, W8><<<dim3((unsigned)(a.n_tiles * a.m_tiles)), 256, kLdsBytes, st>>>(a);
     return hipGetLastError();
 }
@@ -771,7 +770,7 @@ hipError_t launch_gemm_f16(const Geometry &g, const void *packed, const void *x,
     a.K = g.K;
     a.KT = g.KT;
     a.rt_stride = g.rt_stride;
-    a.n_tiles = a.m_tiles = 0;
+    a.n_tiles = a.m_tiles = a.by_tokens = 0;
     a.gated_act = gated_act;
     if (g.fmt == kW8C) return launch_fallback<true, true>(a, M, st);
     const bool pc = g.fmt == kW4C;

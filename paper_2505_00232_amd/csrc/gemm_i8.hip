@@ -40,6 +40,7 @@ struct GemmI8Args {
     const _Float16 *res;  // [M, N] residual added before the rounding, or null
     void *out;
     int M, N, Kp, n_tiles, m_tiles;
+    int by_tokens;  // order of the tiles (see xcd_tile)
     // 4-bit weights enter the MFMA as 16 q (the code's nibble in the top half of a byte): the sums are
     // 16 times the definition's, exactly; channel scales are multiplied by 1/16, raw sums shifted by 4
     float sw_mul = 1.0f;
@@ -272,10 +273,8 @@ __global__ __launch_bounds__(256, (BN * BM > 128 * 256) ? 1 : 2) void gemm_i8_ke
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wn = wave & 1, wm = wave >> 1;
 
-    const int total = a.n_tiles * a.m_tiles;
-    const int logical = xcd_order(blockIdx.x, total);
-    const int nt = logical / a.m_tiles;
-    const int mt = logical % a.m_tiles;
+    int nt, mt;
+    xcd_tile(blockIdx.x, a.n_tiles, a.m_tiles, a.by_tokens, nt, mt);
     const int KT = a.Kp / 64;
 
     // One wavefront instruction copies one KiB tile: tile t of the stage, t = wave,
@@ -394,10 +393,8 @@ __global__ __launch_bounds__(256, 2) void gemm_i8_w4_kernel(GemmI8Args a) {
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wn = wave & 1, wm = wave >> 1;
-    const int total = a.n_tiles * a.m_tiles;
-    const int logical = xcd_order(blockIdx.x, total);
-    const int nt = logical / a.m_tiles;
-    const int mt = logical % a.m_tiles;
+    int nt, mt;
+    xcd_tile(blockIdx.x, a.n_tiles, a.m_tiles, a.by_tokens, nt, mt);
     const int stages = a.Kp / 128;
 
     constexpr int NLOAD = (W_TILES + X_TILES) / 4;
@@ -531,9 +528,8 @@ __global__ __launch_bounds__(256, 2) void gemm_i8_dw_kernel(GemmI8Args a) {
     extern __shared__ uint4 lds[];  // NS stages of XT tiles x 64 vectors
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int total = a.n_tiles * a.m_tiles;
-    const int logical = xcd_order(blockIdx.x, total);
-    const int nt = logical / a.m_tiles, mt = logical % a.m_tiles;
+    int nt, mt;
+    xcd_tile(blockIdx.x, a.n_tiles, a.m_tiles, a.by_tokens, nt, mt);
     const int KT = a.Kp / 64;  // stages
 
     // weights: operand (i, ks) of a stage = rows 32 i + (lane & 31) of the wavefront's 64, k = 32 ks + 16 (lane >> 5) ..
@@ -677,6 +673,7 @@ hipError_t launch_dw(GemmI8Args a, hipStream_t st) {
     if (const hipError_t e = allow_dynamic_lds<gemm_i8_dw_kernel<NS, PW, TM, OUT_MODE, PIPE>>(lds_bytes); e != hipSuccess) return e;
     a.n_tiles = (a.N + 255) / 256;
     a.m_tiles = (a.M + 32 * TM - 1) / (32 * TM);
+    a.by_tokens = walk_by_tokens(a.n_tiles, a.m_tiles, 256.0f, 32.0f * TM);
     gemm_i8_dw_kernel<NS, PW, TM, OUT_MODE, PIPE><<<dim3((unsigned)(a.n_tiles * a.m_tiles)), 256, lds_bytes, st>>>(a);
     return hipGetLastError();
 }
@@ -698,9 +695,8 @@ __global__ __launch_bounds__(256, 2) void gemm_i8_dw4_kernel(GemmI8Args a) {
     extern __shared__ uint4 lds[];  // NS stages of XT tiles x 64 vectors
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int total = a.n_tiles * a.m_tiles;
-    const int logical = xcd_order(blockIdx.x, total);
-    const int nt = logical / a.m_tiles, mt = logical % a.m_tiles;
+    int nt, mt;
+    xcd_tile(blockIdx.x, a.n_tiles, a.m_tiles, a.by_tokens, nt, mt);
     const int KT = a.Kp / 128;  // stages
 
     // weights: vector v of operand row tile i = rows 32 i + (lane & 31) of the wavefront's 64, octet 2 v + lane / 32
@@ -820,6 +816,7 @@ hipError_t launch_dw4(GemmI8Args a, hipStream_t st) {
     if (const hipError_t e = allow_dynamic_lds<gemm_i8_dw4_kernel<NS, PW, TM, OUT_MODE>>(lds_bytes); e != hipSuccess) return e;
     a.n_tiles = (a.N + 255) / 256;
     a.m_tiles = (a.M + 32 * TM - 1) / (32 * TM);
+    a.by_tokens = walk_by_tokens(a.n_tiles, a.m_tiles, 128.0f, 32.0f * TM);
     gemm_i8_dw4_kernel<NS, PW, TM, OUT_MODE><<<dim3((unsigned)(a.n_tiles * a.m_tiles)), 256, lds_bytes, st>>>(a);
     return hipGetLastError();
 }
@@ -831,6 +828,7 @@ hipError_t launch_variant(GemmI8Args a, hipStream_t st) {
     if (const hipError_t e = allow_dynamic_lds<gemm_i8_kernel<BN, BM, KTS, NS, OUT_MODE>>(lds_bytes); e != hipSuccess) return e;
     a.n_tiles = (a.N + BN - 1) / BN;
     a.m_tiles = (a.M + BM - 1) / BM;
+    a.by_tokens = walk_by_tokens(a.n_tiles, a.m_tiles, (float)BN, (float)BM);
     gemm_i8_kernel<BN, BM, KTS, NS, OUT_MODE><<<dim3((unsigned)(a.n_tiles * a.m_tiles)), 256, lds_bytes, st>>>(a);
     return hipGetLastError();
 }
@@ -843,6 +841,7 @@ hipError_t launch_w4(GemmI8Args a, hipStream_t st) {
     if (const hipError_t e = allow_dynamic_lds<gemm_i8_w4_kernel<BN, BM, NS, OUT_MODE>>(lds_bytes); e != hipSuccess) return e;
     a.n_tiles = (a.N + BN - 1) / BN;
     a.m_tiles = (a.M + BM - 1) / BM;
+    a.by_tokens = walk_by_tokens(a.n_tiles, a.m_tiles, 0.5f * BN, (float)BM);
     gemm_i8_w4_kernel<BN, BM, NS, OUT_MODE><<<dim3((unsigned)(a.n_tiles * a.m_tiles)), 256, lds_bytes, st>>>(a);
     return hipGetLastError();
 }
@@ -911,7 +910,7 @@ hipError_t launch_gemm_i8(const Geometry &g, const void *packed, const int8_t *x
     a.M = M;
     a.N = g.N;
     a.Kp = g.Kp;
-    a.n_tiles = a.m_tiles = 0;
+    a.n_tiles = a.m_tiles = a.by_tokens = 0;
     a.gated_act = out_mode == 0 && g.pair_half ? gated_act : -1;
     if (g.fmt == kW4C) {
         a.sw_mul = 0.0625f;
