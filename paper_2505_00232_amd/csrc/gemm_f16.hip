@@ -774,7 +774,15 @@ hipError_t launch_gemm_f16(const Geometry &g, const void *packed, const void *x,
     a.gated_act = gated_act;
     if (g.fmt == kW8C) return launch_fallback<true, true>(a, M, st);
     const bool pc = g.fmt == kW4C;
-    if ((g.K % 128) == 0 && (tuning().gemm_variant != 9 || gated_act >= 0)) return pc ? launch_direct<true>(a, M, st) : launch_direct<false>(a, M, st);
+    if ((g.K % 128) == 0 && (tuning().gemm_variant != 9 || gated_act >= 0)) {
+        const int rest = skinny_tail_rows(g, M, gated_act >= 0, num_cus), most = M - rest;
+        a.M = most;
+        const hipError_t e = pc ? launch_direct<true>(a, most, st) : launch_direct<false>(a, most, st);
+        if (e != hipSuccess || rest == 0) return e;
+        const int n_out = gated_act >= 0 ? g.N / 2 : g.N;
+        return launch_skinny_f16(g, packed, static_cast<const _Float16 *>(x) + (size_t)most * g.K, rest, a.y + (size_t)most * n_out,
+                                 residual ? a.res + (size_t)most * g.N : nullptr, gated_act, num_cus, st);
+    }
     return pc ? launch_fallback<true>(a, M, st) : launch_fallback<false>(a, M, st);
 }
 

@@ -501,7 +501,7 @@ int row_tiles_for(const SkinnyArgs &a, int fmt, bool int8_activations, int num_c
 template <int FMT>
 hipError_t f16_any(const SkinnyArgs &a, int num_cus, hipStream_t st) {
     switch ((a.block_rows + 7) / 8) {
-        case 2: return f16_rows<FMT, 2>(a, num_cus, st, Rows2());
+        case 1: case 2: return f16_rows<FMT, 2>(a, num_cus, st, Rows2());
         case 3: case 4: return f16_rows<FMT, 4>(a, num_cus, st, std::conditional_t<FMT == kW8C, Rows2W8, Rows2>());
         case 5: case 6: return f16_rows<FMT, 6>(a, num_cus, st, Rows3());
         case 7: case 8: return f16_rows<FMT, 8>(a, num_cus, st, Rows4());
@@ -561,27 +561,47 @@ SkinnyArgs make_args(const Geometry &g, const void *packed, const void *x, const
 // Measured (us, tiles / here): 4096 x 14336 int4, binary16 activations, 77 rows 131 / 24, 300 131 / 64, 512 133 / 75;
 // 2304 x 9216 int4 groups 77 rows 96 / 17, 300 98 / 26, 1000 98 / 84; 18432 x 2304 77 rows 31 / 22, 200 31 / 38;
 // int8 x int8 6144 x 4096 77 rows 26 / 11, 300 25 / 21, 512 25 / 29; int8 x int4 4096 x 14336 77 rows 60 / 17, 512 60 / 47.
+static float skinny_us(const Geometry &g, int M, bool int8_activations, bool gated, int num_cus) {
+    const SkinnyArgs a = make_args(g, nullptr, nullptr, nullptr, M, nullptr, nullptr, gated ? 0 : -1);
+    const int R = row_tiles_for(a, g.fmt, int8_activations, num_cus);
+    if (R == 0) return 1e9f;
+    const float k = 1e-3f * (float)g.K, rows = (float)a.block_rows, r = (float)R;
+    const float load = fmaxf(1.0f, 0.95f * load_per_cu(a, R, num_cus));
+    if (!int8_activations) return load * (2.0f + 0.9f * r + k * (0.35f + 0.0128f * rows + 0.33f * r));
+    return load * (2.5f + 0.5f * r + k * (0.25f + 0.0102f * rows + (g.fmt == kW8C ? 0.27f : 0.15f) * r));
+}
+
+static float tile_round_us(const Geometry &g) { return 9.0f + 9.3e-3f * (float)g.K; }  // (binary16 activations)
+
 bool skinny_product(const Geometry &g, int M, bool int8_activations, bool gated, int num_cus) {
     if (tuning().gemm_variant != 0) return false;  // a large kernel is asked for by name
     if (tuning().skinny_max_m >= 0) return M <= tuning().skinny_max_m;
     if (M <= kSkinnyRows) return !(int8_activations && g.RT >= 16 * num_cus) || M <= (g.fmt == kW8C ? 64 : 48);
     if (M > kSkinnyMaxM) return false;
-    const SkinnyArgs a = make_args(g, nullptr, nullptr, nullptr, M, nullptr, nullptr, gated ? 0 : -1);
-    const int R = row_tiles_for(a, g.fmt, int8_activations, num_cus);
-    if (R == 0) return false;
-    const float k = 1e-3f * (float)g.K, rows = (float)a.block_rows, r = (float)R;
-    const float load = fmaxf(1.0f, 0.95f * load_per_cu(a, R, num_cus));
+    const float here = skinny_us(g, M, int8_activations, gated, num_cus);
     const long n256 = (g.N + 255) / 256, m128 = (M + 127) / 128, m64 = (M + 63) / 64;
     if (!int8_activations) {
-        const float here = load * (2.0f + 0.9f * r + k * (0.35f + 0.0128f * rows + 0.33f * r));
         const bool staged = g.fmt == kW8C || g.K % 128 != 0;  // 128 x 128 tiles, two workgroups per compute unit
         const float rounds = staged ? fmaxf(1.0f, (float)((g.N + 127) / 128 * m128) / (float)num_cus) : ceilf((float)(n256 * m128) / (float)num_cus);
-        return here < rounds * (9.0f + 9.3f * k);
+        return here < rounds * tile_round_us(g);
     }
-    const float here = load * (2.5f + 0.5f * r + k * (0.25f + 0.0102f * rows + (g.fmt == kW8C ? 0.27f : 0.15f) * r));
     const bool wide = 4 * n256 * m128 >= 3L * num_cus;  // (their choice between 128 and 64 tokens)
-    const float tiles = 5.0f + (g.fmt == kW8C ? 4.4f : 3.85f) * k;
+    const float tiles = 5.0f + (g.fmt == kW8C ? 4.4e-3f : 3.85e-3f) * (float)g.K;
     return here < 0.9f * tiles * (wide ? fmaxf(1.25f, 1.6f * (float)(n256 * m128) / (float)num_cus) : fmaxf(1.0f, 0.7f * (float)(n256 * m64) / (float)num_cus));
+}
+
+// Binary16 activations, 256 x 128 tiles, one workgroup per compute unit: a last round of few tiles costs as much as a
+// full one.  Rows to leave to the kernels here so that the tiles of the others end with a full round, if that is
+// estimated to save a twentieth or more; else 0.  Measured (us, tiles alone / like this): 2304 x 9216 3700 rows 231 / 161;
+// 28672 x 4096 270 rows 98 / 72; 6144 x 4096 1300 rows 111 / 75; 4096 x 14336 2200 rows 315 / 228; 18432 x 2304 900 rows 108 / 93.
+int skinny_tail_rows(const Geometry &g, int M, bool gated, int num_cus) {
+    if (tuning().gemm_variant != 0 || tuning().skinny_max_m >= 0) return 0;
+    const long n256 = (g.N + 255) / 256, m128 = (M + 127) / 128, rounds = (n256 * m128 + num_cus - 1) / num_cus;
+    const long keep = (rounds - 1) * num_cus / n256 * 128;  // rows whose tiles fill one round less
+    const long rest = M - keep;
+    if (rounds < 2 || keep < 128 || rest < 1 || rest > kSkinnyMaxM) return 0;
+    const float saved = tile_round_us(g) - skinny_us(g, (int)rest, false, gated, num_cus) - 3.0f;  // (3: a second launch)
+    return saved > 0.05f * (float)rounds * tile_round_us(g) ? (int)rest : 0;
 }
 
 hipError_t launch_skinny_f16(const Geometry &g, const void *packed, const void *x, int M, void *y, const void *residual,

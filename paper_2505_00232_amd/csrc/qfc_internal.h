@@ -377,6 +377,7 @@ hipError_t launch_gemm_f16(const Geometry &g, const void *packed, const void *x,
 constexpr int kSkinnyRows = 64;  // token rows per workgroup at most
 constexpr int kSkinnyMaxM = 1024;
 bool skinny_product(const Geometry &g, int M, bool int8_activations, bool gated, int num_cus);
+int skinny_tail_rows(const Geometry &g, int M, bool gated, int num_cus);
 hipError_t launch_skinny_f16(const Geometry &g, const void *packed, const void *x, int M, void *y, const void *residual,
                              int gated_act, int num_cus, hipStream_t st);
 hipError_t launch_skinny_i8(const Geometry &g, const void *packed, const int8_t *xq_tiled, const float *sx, int M,

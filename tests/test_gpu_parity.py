@@ -1779,6 +1779,31 @@ def test_blocks_of_token_rows_match_oracle(fmt, mode, M, N, K, row_tiles, blocks
     layer.close()
 
 
+@pytest.mark.parametrize("fmt,pairs,M", [("w4g32", False, 1100), ("w4c", True, 1030), ("w4c", False, 1025)])
+def test_last_round_of_tiles_left_to_the_token_row_kernels(fmt, pairs, M):
+    """9 x 32 tiles of 256 x 128 are one round of 256 workgroups and 32 more: the rows of the last are computed by the
+    kernels for few token rows, with the residual or the gated output of their rows."""
+    N, K = 8192, 128
+    print(f"tail rows {fmt} pairs={pairs} M={M}", flush=True)
+    wq, s = synth.weights(6200, M, N, synth.FC("t", K, N, fmt))
+    x = (synth.activations(6200, M, N, M, K) * np.float16(0.25)).astype(np.float16)
+    layer = binding.QuantLinear(wq, s, fmt, compute_mode=binding.QFC_COMPUTE_FP16_DEQUANT, max_m=M, gated_pairs=pairs)
+    full = oracle.fc_weight_only(x, wq, s, _group(fmt))
+    xd = torch.from_numpy(x).to(DEV)
+    guard = torch.full((M + 1, N // 2 if pairs else N), 77.0, dtype=torch.float16, device=DEV)
+    if pairs:
+        binding.qfc_forward_fused(layer.handle, xd, guard[:M], activation=binding.QFC_ACT_SILU, gated_output=True)
+        ref = oracle.gated_output(full, oracle.SILU)
+    else:
+        res = synth.activations(6201, M, N, M, N)
+        binding.qfc_forward_fused(layer.handle, xd, guard[:M], residual=torch.from_numpy(res).to(DEV))
+        ref = full + res.astype(np.float64)
+    torch.cuda.synchronize()
+    assert _E(guard[:M].cpu().numpy(), ref) <= TOL
+    assert bool((guard[M] == 77.0).all())
+    layer.close()
+
+
 @pytest.mark.parametrize("B,S,h_q,h_kv,d,C,pos0", [(1, 128, 3, 1, 64, 192, 64), (1, 1100, 6, 2, 64, 1152, 13),
                                                    (3, 50, 8, 2, 128, 128, 61), (2, 700, 4, 4, 128, 768, 7), (1, 257, 8, 4, 256, 320, 63)])
 def test_rope_qkv_many_tokens(B, S, h_q, h_kv, d, C, pos0):
