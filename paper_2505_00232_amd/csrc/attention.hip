@@ -80,9 +80,9 @@ __global__ __launch_bounds__(256) void rope_qkv_few_kernel(const _Float16 *__res
 
 // Bound: HBM (read once, written once), once the angles are out of the way: cos and sin in fp64 cost
 // more than everything else together when every head of a token evaluates them (S = 1024, 40 heads to
-// rotate: 38 us; 6000: 200 us, where reading and writing 147 MB takes 28).  So a workgroup takes T
+// rotate: 34 us; 6000: 165 us, where reading and writing 147 MB takes 28).  So a workgroup takes T
 // tokens, evaluates their d / 2 angles once into LDS, and rotates all heads with them, 16 bytes of each half
-// of a head per thread (9 and ROPE_6000 us).  Few tokens: the heads are split over several workgroups.
+// of a head per thread (13 and 46 us).  Few tokens: the heads are split over several workgroups.
 // Values: a workgroup takes the tokens of one block of 64 cache positions of one head, turns them in LDS and
 // writes runs of up to 128 bytes of the transposed cache instead of single values 128 bytes apart.
 typedef _Float16 rope_h2 __attribute__((ext_vector_type(2)));
