@@ -208,6 +208,7 @@ __global__ __launch_bounds__(MAXT) void skinny_f16_kernel(SkinnyArgs a) {
     const int t0 = wave * a.steps_q + min(wave, a.steps_rem);
     const int nt = a.steps_q + (wave < a.steps_rem ? 1 : 0);
     const int nst = 2 * nt;
+    const int nst_copy = min(nst, (a.K + 63) / 64 - 2 * t0);  // half steps that hold any k below K
 
     // (the last workgroup's row tiles may run past the layer's: they are clamped, results dropped)
     const u32x4 *wrow[R];
@@ -234,14 +235,33 @@ __global__ __launch_bounds__(MAXT) void skinny_f16_kernel(SkinnyArgs a) {
     const uint32_t ring0 = (uint32_t)(uintptr_t)(lptr_t)lds + wave * (RING * SLOT);
     auto copy_stage = [&](int s, int slot) __attribute__((always_inline)) {
         const int o0 = (2 * t0 + s) * 8;
-        const bool tail = o0 + 8 > K8;  // octets beyond K: any octet of the row (they meet zero weights)
-#pragma unroll
-        for (int i = 0; i < XB; ++i) {
-            const int rl = 8 * i + (lane >> 3);
-            int o = o0 + ((lane & 7) ^ ((rl >> 1) & 7));
-            if (tail && o >= K8) o &= 3;
+        auto copy = [&](int i) __attribute__((always_inline)) {
+            const int rl = 8 * i + (lane >> 3), o = o0 + ((lane & 7) ^ ((rl >> 1) & 7));
             const uint32_t off = ((uint32_t)min(rl, rows - 1) * (uint32_t)K8 + (uint32_t)o) * 16u;
             copy16_to_lds(xbase, off, __builtin_amdgcn_readfirstlane(ring0 + slot * SLOT + i * 1024));
+        };
+        if (o0 + 8 <= K8) {
+#pragma unroll
+            for (int i = 0; i < XB; ++i) copy(i);
+            return;
+        }
+        // octets beyond K: zeros (their weights are zero too, but zero times an infinity is not).  All eight, or
+        // (K is a multiple of 32) the upper four: of an even KiB the lanes with bit 2 set hold those, of an odd KiB the others.
+        auto clear = [&](int i) __attribute__((always_inline)) { lds[(wave * (RING * SLOT) + slot * SLOT + i * 1024) / 16 + lane] = u32x4{0, 0, 0, 0}; };
+        if (o0 >= K8) {
+#pragma unroll
+            for (int i = 0; i < XB; ++i) clear(i);
+        } else {
+#pragma unroll
+            for (int p = 0; p < 2; ++p) {
+                if (((lane >> 2) & 1) == p) {
+#pragma unroll
+                    for (int i = p; i < XB; i += 2) copy(i);
+                } else {
+#pragma unroll
+                    for (int i = p; i < XB; i += 2) clear(i);
+                }
+            }
         }
     };
 
@@ -268,7 +288,7 @@ __global__ __launch_bounds__(MAXT) void skinny_f16_kernel(SkinnyArgs a) {
                 for (int h = 0; h < 2; ++h) {
                     const int s = 2 * (b + i) + h;
                     const int slot = (2 * i + h) & (RING - 1);
-                    if (s + RING <= nst)
+                    if (s + RING <= nst_copy)
                         wait_mem<(RING - 1) * XB>();
                     else
                         wait_mem<0>();

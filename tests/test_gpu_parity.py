@@ -1740,6 +1740,34 @@ def test_few_token_rows_match_oracle(fmt, mode, M, N, K, row_tiles):
     layer.close()
 
 
+@pytest.mark.parametrize("fmt", ["w4g32", "w4c", "w8c"])
+@pytest.mark.parametrize("M,K", [(9, 160), (24, 64), (33, 352), (64, 544), (100, 160), (100, 224)])
+def test_few_token_rows_infinite_activations(fmt, M, K):
+    """An infinite activation gives its row the infinity the definition gives (NaN where its weight is zero), wherever
+    K ends in a step of 128, and leaves the other rows alone: also in the large kernels at the same sizes."""
+    print(f"infinite activations {fmt} M={M} K={K}", flush=True)
+    N = 90
+    wq, s = synth.weights(6050, M, K, synth.FC("t", K, N, fmt))
+    x = synth.activations(6050, M, K, M, K)
+    ref = oracle.fc_weight_only(x, wq, s, _group(fmt))
+    wq = np.asarray(wq)
+    for row, k, sign in ((0, 3, 1.0), (M // 2, K - 1, -1.0), (M - 1, 31, 1.0)):
+        x[row, k] = np.float16(sign * np.inf)
+        ref[row] = np.where(wq[:, k] == 0, np.nan, sign * np.sign(wq[:, k].astype(np.float64)) * np.inf)
+    layer = _layer(wq, s, fmt, max_m=M, mode=binding.QFC_COMPUTE_FP16_DEQUANT)
+    for max_m in (1024, 0):  # the kernels for few token rows, the large ones
+        binding.qfc_tune(9, max_m)
+        try:
+            y = _forward(layer, x).astype(np.float64)
+        finally:
+            binding.qfc_tune(9, -1)
+        finite = np.isfinite(ref).all(axis=1)
+        assert finite.sum() == M - 3
+        assert _E(y[finite], ref[finite]) <= TOL, max_m
+        assert np.array_equal(y[~finite], ref[~finite], equal_nan=True), max_m
+    layer.close()
+
+
 @pytest.mark.parametrize("fmt,mode", [("w4g32", None), ("w4c", None), ("w8c", binding.QFC_COMPUTE_FP16_DEQUANT),
                                       ("w8c", None), ("w4c", binding.QFC_COMPUTE_INT8_ACT)])
 @pytest.mark.parametrize("M,N,K,row_tiles,blocks", [(65, 40, 160, 0, 0), (77, 300, 2304, 2, 0), (96, 130, 416, 3, 0), (97, 130, 416, 4, 0),
