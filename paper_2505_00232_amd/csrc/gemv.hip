@@ -215,21 +215,29 @@ struct XStage {
     }
     // global -> this wavefront's LDS region without passing registers (no prologue): vector p of
     // the region (p = 64 i + lane = slot * M + m) is copied from wherever its token row keeps that
-    // octet.  Octets beyond K are read from the start of the row instead, each from its own place
-    // (finite values that only meet zero weights of the padding; not all from one place: many copies
-    // of the same line in flight have been seen to reach LDS after the counter said they were done).
+    // octet.  Octets beyond K are zeros, as in load() (they meet zero weights, but zero times an infinity is not zero).
     __device__ __forceinline__ void copy(const GemvArgs &a, int unit, int lane, u32x4 *lds) const {
         const int K8 = a.K / 8;
         const uint32_t lds_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void *)lds;
+        auto octet = [&](int p) {
+            const int slot = p / M;
+            return unit * OCT + (FMT == kW8C ? (slot & ~7) | ((slot >> 2) & 1) | ((slot & 3) << 1) : slot);
+        };
+        auto copy_kib = [&](int i, int p) __attribute__((always_inline)) {
+            copy16_to_lds(a.x, (uint32_t)(((size_t)(p % M) * K8 + octet(p)) * 16), __builtin_amdgcn_readfirstlane(lds_base + i * 1024));
+        };
+        if ((unit + 1) * OCT <= K8) {
+#pragma unroll
+            for (int i = 0; i < XV; ++i) copy_kib(i, i * 64 + lane);
+            return;
+        }
 #pragma unroll
         for (int i = 0; i < XV; ++i) {
             const int p = i * 64 + lane;
-            const int slot = p / M, m = p % M;
-            int o = slot;
-            if (FMT == kW8C) o = (slot & ~7) | ((slot >> 2) & 1) | ((slot & 3) << 1);
-            const int oo = unit * OCT + o;
-            const uint32_t off = (uint32_t)(((size_t)m * K8 + (oo < K8 ? oo : oo - K8)) * 16);
-            copy16_to_lds(a.x, off, __builtin_amdgcn_readfirstlane(lds_base + i * 1024));
+            if (octet(p) < K8)
+                copy_kib(i, p);
+            else
+                lds[p] = u32x4{0, 0, 0, 0};
         }
     }
     // registers -> this wavefront's LDS region, A-operand order; ss: sums of squares of the rows (PRO = 2)

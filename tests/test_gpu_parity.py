@@ -1740,6 +1740,37 @@ def test_few_token_rows_match_oracle(fmt, mode, M, N, K, row_tiles):
     layer.close()
 
 
+def _with_infinities(x, wq, ref):
+    """Puts an infinity into three rows of x (first octets, last element of K) and what the definition gives for it
+    (NaN where its weight is zero) into the same rows of ref; returns the rows that stay finite."""
+    M, K = x.shape
+    for row, k, sign in ((0, 3, 1.0), (M // 2, K - 1, -1.0), (M - 1, 31, 1.0)):
+        x[row, k] = np.float16(sign * np.inf)
+        w = np.asarray(wq)[:, k]
+        ref[row] = np.where(w == 0, np.nan, np.where((w > 0) == (sign > 0), np.inf, -np.inf))
+    return np.isfinite(ref).all(axis=1)
+
+
+@pytest.mark.parametrize("fmt", ["w4g32", "w4c", "w8c"])
+@pytest.mark.parametrize("K", [160, 4640, 5088])
+def test_decode_infinite_activations(fmt, K):
+    """An infinite activation gives its row the infinity the definition gives and leaves the other rows alone, wherever K ends in
+    a step of 128: staged through registers and by direct copies (five token rows and more, long K, 4-bit weights)."""
+    N = 90
+    for M in (4, 5, 8):
+        print(f"infinite activations, decode {fmt} M={M} K={K}", flush=True)
+        wq, s = synth.weights(6051, M, K, synth.FC("t", K, N, fmt))
+        x = synth.activations(6051, M, K, M, K)
+        ref = oracle.fc_weight_only(x, wq, s, _group(fmt))
+        finite = _with_infinities(x, wq, ref)
+        layer = _layer(wq, s, fmt, max_m=M, mode=binding.QFC_COMPUTE_FP16_DEQUANT)
+        y = _forward(layer, x).astype(np.float64)
+        assert finite.sum() == M - 3
+        assert _E(y[finite], ref[finite]) <= TOL, M
+        assert np.array_equal(y[~finite], ref[~finite], equal_nan=True), M
+        layer.close()
+
+
 @pytest.mark.parametrize("fmt", ["w4g32", "w4c", "w8c"])
 @pytest.mark.parametrize("M,K", [(9, 160), (24, 64), (33, 352), (64, 544), (100, 160), (100, 224)])
 def test_few_token_rows_infinite_activations(fmt, M, K):
@@ -1750,10 +1781,8 @@ def test_few_token_rows_infinite_activations(fmt, M, K):
     wq, s = synth.weights(6050, M, K, synth.FC("t", K, N, fmt))
     x = synth.activations(6050, M, K, M, K)
     ref = oracle.fc_weight_only(x, wq, s, _group(fmt))
-    wq = np.asarray(wq)
-    for row, k, sign in ((0, 3, 1.0), (M // 2, K - 1, -1.0), (M - 1, 31, 1.0)):
-        x[row, k] = np.float16(sign * np.inf)
-        ref[row] = np.where(wq[:, k] == 0, np.nan, sign * np.sign(wq[:, k].astype(np.float64)) * np.inf)
+    finite = _with_infinities(x, wq, ref)
+    assert finite.sum() == M - 3
     layer = _layer(wq, s, fmt, max_m=M, mode=binding.QFC_COMPUTE_FP16_DEQUANT)
     for max_m in (1024, 0):  # the kernels for few token rows, the large ones
         binding.qfc_tune(9, max_m)
@@ -1761,8 +1790,6 @@ def test_few_token_rows_infinite_activations(fmt, M, K):
             y = _forward(layer, x).astype(np.float64)
         finally:
             binding.qfc_tune(9, -1)
-        finite = np.isfinite(ref).all(axis=1)
-        assert finite.sum() == M - 3
         assert _E(y[finite], ref[finite]) <= TOL, max_m
         assert np.array_equal(y[~finite], ref[~finite], equal_nan=True), max_m
     layer.close()
