@@ -229,15 +229,22 @@ __global__ __launch_bounds__(MAXT) void skinny_f16_kernel(SkinnyArgs a) {
                 wv[slot][r][v] = __builtin_nontemporal_load(wrow[r] + (size_t)(FMT == kW8C ? 2 * t + v : FMT == kW4G32 ? t + u : t) * 64 + lane);
         }
     };
-    // copies of a half step: KiB i = token rows 8 i .. 8 i + 7, lane = (row, octet position)
-    const char *xbase = reinterpret_cast<const char *>(a.x) + (size_t)m0 * a.K * 2;
+    // copies of a half step: KiB i = token rows 8 i .. 8 i + 7, lane = (row, octet position).  Rows past the last (their
+    // products are dropped) take the data of rows `back` before them, of the block before where the block is less than half
+    // full: no line is copied by more than two instructions of a wavefront (many copies of the same lines in flight have been
+    // seen to reach LDS after the counter said they were done, see gemm_i8.hip; this ring is reused for the partial sums).
+    // (not copying them at all costs 3 to 20 %: lane masks, and a count of copies that is not a constant any more)
+    const bool own = rows >= 4 * XB || m0 == 0;
+    const int before = own ? 0 : a.block_rows, back = !own ? a.block_rows : m0 > 0 ? rows & ~7 : rows >= 16 ? 16 : 8;
+    const char *xbase = reinterpret_cast<const char *>(a.x) + (size_t)(m0 - before) * a.K * 2;
     const int K8 = a.K / 8;
     const uint32_t ring0 = (uint32_t)(uintptr_t)(lptr_t)lds + wave * (RING * SLOT);
     auto copy_stage = [&](int s, int slot) __attribute__((always_inline)) {
         const int o0 = (2 * t0 + s) * 8;
         auto copy = [&](int i) __attribute__((always_inline)) {
             const int rl = 8 * i + (lane >> 3), o = o0 + ((lane & 7) ^ ((rl >> 1) & 7));
-            const uint32_t off = ((uint32_t)min(rl, rows - 1) * (uint32_t)K8 + (uint32_t)o) * 16u;
+            const int row = before + (rl < rows ? rl : min(max(rl - back, -before), rows - 1));
+            const uint32_t off = ((uint32_t)row * (uint32_t)K8 + (uint32_t)o) * 16u;
             copy16_to_lds(xbase, off, __builtin_amdgcn_readfirstlane(ring0 + slot * SLOT + i * 1024));
         };
         if (o0 + 8 <= K8) {
