@@ -169,8 +169,7 @@ struct GemvArgs {
     const float *sw;    // per-channel scales [Np] (W8C, W4C)
     int N, K, RT, KT, KU, rt_stride;
     int row_tiles;           // R: row tiles per workgroup
-    int rt_step, pair_step;  // row tile r of a workgroup is rt0 + (r / 2) pair_step + (r % 2) rt_step
-    int pairs;               // gated output: pairs of row tiles (both branches of 16 channels) per workgroup
+    int rt_step;             // distance between a workgroup's row tiles (1; RT / 2 for a gated output)
     int gated_out;           // 1: rows [0, N/2) are the gate, rows [N/2, N) the other branch; y is [M, N/2]
     int paired;              // 1: the layer is packed in pairs (physical row tiles 2 t, 2 t + 1 = the two branches)
     int units_q, units_rem;  // KU = units_q * waves + units_rem
@@ -270,7 +269,10 @@ struct XStage {
 // through registers (a third of the registers of M = 8 otherwise hold them).  Such copies and the
 // weight loads complete in order only among their own kind, so the wavefront waits for an empty
 // counter before its first tile: slower for short K, faster for the down projections (M = 8: -17 %).
-template <int M, int FMT, bool DB, int PRO, bool BIG = false, bool HALF = false, bool COPY = false>
+// PAIRS (gated output): pairs of row tiles (both branches of 16 channels) per workgroup.  Not an argument of the
+// launch: every layer would pay for the indexing of pairs (4-bit weights, one token row: 6144 x 4096 5.43 us with it, 5.28
+// without, 4096 x 4096 4.49 / 4.36, 4096 x 14336 8.87 / 8.72).
+template <int M, int FMT, bool DB, int PRO, int PAIRS = 1, bool BIG = false, bool HALF = false, bool COPY = false>
 __global__ __launch_bounds__(BIG ? 1024 : PRO == 1 && M > 4 ? 256 : 512) void gemv_kernel(GemvArgs a) {
     static_assert(!HALF || (FMT != kW8C && !DB), "half units: int4 formats, single buffer");
     static_assert(!COPY || (HALF && PRO == 0), "direct copies: half units without a prologue");
@@ -289,9 +291,11 @@ __global__ __launch_bounds__(BIG ? 1024 : PRO == 1 && M > 4 ? 256 : 512) void ge
     // (first row tile in the packed buffer: with the branches' tiles interleaved, the pair (2 b, 2 b + 1))
     // Rotary pairs: a workgroup owns the row tiles (t, t + d / 32) of one head, i.e. rows i and i + d / 2.
     const int rt0 = a.rope_per    ? (int)(blockIdx.x / a.rope_per) * (2 * a.rope_per) + (int)(blockIdx.x % a.rope_per)
-                    : a.gated_out ? (a.paired ? 2 * a.pairs * blockIdx.x : a.pairs * blockIdx.x)
+                    : a.gated_out ? (a.paired ? 2 * PAIRS * blockIdx.x : PAIRS * blockIdx.x)
                                   : blockIdx.x * a.row_tiles;
-    const int R = a.rope_per ? 2 : a.gated_out ? 2 * min(a.pairs, a.RT / 2 - a.pairs * (int)blockIdx.x) : min(a.row_tiles, a.RT - rt0);
+    const int R = PAIRS > 1                   ? 2 * min(PAIRS, a.RT / 2 - PAIRS * (int)blockIdx.x)
+                  : a.gated_out || a.rope_per ? 2
+                                              : min(a.row_tiles, a.RT - rt0);
     const int u0 = wave * a.units_q + min(wave, a.units_rem);
     const int u1 = u0 + a.units_q + (wave < a.units_rem ? 1 : 0);
     u32x4 *lds_x = lds_all + wave * (OCT * M);
@@ -326,7 +330,7 @@ __global__ __launch_bounds__(BIG ? 1024 : PRO == 1 && M > 4 ? 256 : 512) void ge
         const int U = HALF ? u >> 1 : u, h = HALF ? u & 1 : 0;  // unit, half of it
         const int ntU = HALF ? min(8, a.KT - 8 * U) : nt;       // weight tiles before the unit's scale tile
         const int pos = FMT == kW4G32 ? 9 * U : 8 * U;
-        const u32x4 *base = a.packed + ((size_t)(rt0 + (r >> 1) * a.pair_step + (r & 1) * a.rt_step) * a.rt_stride + pos) * 64;
+        const u32x4 *base = a.packed + ((size_t)(rt0 + (PAIRS > 1 ? (r >> 1) * (a.paired ? 2 : 1) + (r & 1) * a.rt_step : r * a.rt_step)) * a.rt_stride + pos) * 64;
         // scales first: loads return in order, and the first tile's results need them
         if (FMT == kW4G32) {
 #pragma unroll
@@ -575,14 +579,14 @@ __global__ __launch_bounds__(BIG ? 1024 : PRO == 1 && M > 4 ? 256 : 512) void ge
         // into the fully connected operator that produces them)
         const GateCoeffs gc = gate_coeffs(a.act);
         const int half = a.N / 2;
-        for (int e = threadIdx.x; e < (R / 2) * M * 16; e += blockDim.x) {
-            const int cc = e & 15, m = (e >> 4) % M, pr = (e >> 4) / M;
+        for (int e = threadIdx.x; e < (PAIRS > 1 ? R / 2 : 1) * M * 16; e += blockDim.x) {
+            const int cc = e & 15, m = PAIRS > 1 ? (e >> 4) % M : e >> 4, pr = PAIRS > 1 ? (e >> 4) / M : 0;
             float sg = 0.0f, su = 0.0f;
             for (int w = 0; w < nwaves; ++w) {
                 sg += red[((w * 4 + 2 * pr) * M + m) * 16 + cc];
                 su += red[((w * 4 + 2 * pr + 1) * M + m) * 16 + cc];
             }
-            const int n = ((int)blockIdx.x * a.pairs + pr) * 16 + cc;  // channel of the gated output
+            const int n = ((int)blockIdx.x * PAIRS + pr) * 16 + cc;  // channel of the gated output
             if (n < half) {
                 if (FMT != kW4G32) {  // (the scales follow the packed row order)
                     sg *= a.sw[a.paired ? (rt0 + 2 * pr) * 16 + cc : n];
@@ -612,11 +616,11 @@ __global__ __launch_bounds__(BIG ? 1024 : PRO == 1 && M > 4 ? 256 : 512) void ge
     }
 }
 
-template <int M, int PRO>
-hipError_t launch_m(const Geometry &g, const GemvArgs &a, const GemvPlan &p, hipStream_t st) {
+template <int M, int PRO, int PAIRS>
+hipError_t launch_pairs(const Geometry &g, const GemvArgs &a, const GemvPlan &p, hipStream_t st) {
     const int waves = p.waves;
-    const int rows = a.rope_per ? 2 : a.gated_out ? 2 * a.pairs : a.row_tiles;
-    const dim3 grid((unsigned)(a.rope_per ? g.RT / 2 : a.gated_out ? (g.RT / 2 + a.pairs - 1) / a.pairs : (g.RT + rows - 1) / rows));
+    const int rows = a.rope_per ? 2 : a.gated_out ? 2 * PAIRS : a.row_tiles;
+    const dim3 grid((unsigned)(a.rope_per ? g.RT / 2 : a.gated_out ? (g.RT / 2 + PAIRS - 1) / PAIRS : (g.RT + rows - 1) / rows));
     const dim3 block((unsigned)(waves * 64));
     const int oct = g.fmt == kW8C || p.half ? 64 : 128;
     size_t lds = (size_t)waves * oct * M * 16;
@@ -627,50 +631,58 @@ hipError_t launch_m(const Geometry &g, const GemvArgs &a, const GemvPlan &p, hip
     if constexpr (PRO == 0 && M > 4) {
         if (p.half && p.copy) {
             if (g.fmt == kW4C)
-                gemv_kernel<M, kW4C, false, 0, false, true, true><<<grid, block, lds, st>>>(a);
+                gemv_kernel<M, kW4C, false, 0, PAIRS, false, true, true><<<grid, block, lds, st>>>(a);
             else
-                gemv_kernel<M, kW4G32, false, 0, false, true, true><<<grid, block, lds, st>>>(a);
+                gemv_kernel<M, kW4G32, false, 0, PAIRS, false, true, true><<<grid, block, lds, st>>>(a);
             return hipGetLastError();
         }
     }
     if constexpr (PRO != 1 || M <= 4) {
         if (p.half) {
             if (g.fmt == kW4C)
-                gemv_kernel<M, kW4C, false, PRO, false, true><<<grid, block, lds, st>>>(a);
+                gemv_kernel<M, kW4C, false, PRO, PAIRS, false, true><<<grid, block, lds, st>>>(a);
             else
-                gemv_kernel<M, kW4G32, false, PRO, false, true><<<grid, block, lds, st>>>(a);
+                gemv_kernel<M, kW4G32, false, PRO, PAIRS, false, true><<<grid, block, lds, st>>>(a);
             return hipGetLastError();
         }
     }
     if constexpr (M <= 2 && PRO == 0) {
         if (waves > 8) {
             if (g.fmt == kW8C)
-                gemv_kernel<M, kW8C, false, 0, true><<<grid, block, lds, st>>>(a);
+                gemv_kernel<M, kW8C, false, 0, PAIRS, true><<<grid, block, lds, st>>>(a);
             else if (g.fmt == kW4C)
-                gemv_kernel<M, kW4C, false, 0, true><<<grid, block, lds, st>>>(a);
+                gemv_kernel<M, kW4C, false, 0, PAIRS, true><<<grid, block, lds, st>>>(a);
             else
-                gemv_kernel<M, kW4G32, false, 0, true><<<grid, block, lds, st>>>(a);
+                gemv_kernel<M, kW4G32, false, 0, PAIRS, true><<<grid, block, lds, st>>>(a);
             return hipGetLastError();
         }
     }
     if constexpr (M <= 2) {
         if (items >= 3) {
             if (g.fmt == kW8C)
-                gemv_kernel<M, kW8C, true, PRO><<<grid, block, lds, st>>>(a);
+                gemv_kernel<M, kW8C, true, PRO, PAIRS><<<grid, block, lds, st>>>(a);
             else if (g.fmt == kW4C)
-                gemv_kernel<M, kW4C, true, PRO><<<grid, block, lds, st>>>(a);
+                gemv_kernel<M, kW4C, true, PRO, PAIRS><<<grid, block, lds, st>>>(a);
             else
-                gemv_kernel<M, kW4G32, true, PRO><<<grid, block, lds, st>>>(a);
+                gemv_kernel<M, kW4G32, true, PRO, PAIRS><<<grid, block, lds, st>>>(a);
             return hipGetLastError();
         }
     }
     if (g.fmt == kW8C)
-        gemv_kernel<M, kW8C, false, PRO><<<grid, block, lds, st>>>(a);
+        gemv_kernel<M, kW8C, false, PRO, PAIRS><<<grid, block, lds, st>>>(a);
     else if (g.fmt == kW4C)
-        gemv_kernel<M, kW4C, false, PRO><<<grid, block, lds, st>>>(a);
+        gemv_kernel<M, kW4C, false, PRO, PAIRS><<<grid, block, lds, st>>>(a);
     else
-        gemv_kernel<M, kW4G32, false, PRO><<<grid, block, lds, st>>>(a);
+        gemv_kernel<M, kW4G32, false, PRO, PAIRS><<<grid, block, lds, st>>>(a);
     return hipGetLastError();
+}
+
+template <int M, int PRO>
+hipError_t launch_m(const Geometry &g, const GemvArgs &a, const GemvPlan &p, hipStream_t st) {
+    if constexpr (PRO != 1) {
+        if (p.pairs == 2) return launch_pairs<M, PRO, 2>(g, a, p, st);
+    }
+    return launch_pairs<M, PRO, 1>(g, a, p, st);
 }
 
 template <int PRO>
@@ -710,8 +722,6 @@ hipError_t launch_gemv(const Geometry &g, const void *packed, const void *x, int
     a.row_tiles = p.row_tiles;
     a.paired = g.pair_half ? 1 : 0;
     a.rt_step = f.gated_output && !a.paired ? g.RT / 2 : 1;
-    a.pair_step = f.gated_output && !a.paired ? 1 : 2;
-    a.pairs = p.pairs;
     a.gated_out = f.gated_output ? 1 : 0;
     a.rope_per = 0;
     a.rope_d = a.rope_hq = a.rope_hkv = a.rope_C = a.rope_pos = 0;
@@ -721,7 +731,6 @@ hipError_t launch_gemv(const Geometry &g, const void *packed, const void *x, int
         const RopeOut &r = *f.rope;
         a.rope_per = r.d / 32;
         a.rt_step = a.rope_per;
-        a.pair_step = 1;
         a.rope_d = r.d;
         a.rope_hq = r.h_q;
         a.rope_hkv = r.h_kv;
