@@ -398,9 +398,19 @@ __global__ __launch_bounds__(BIG ? 1024 : PRO == 1 && M > 4 ? 256 : 512) void ge
 #pragma unroll
         for (int i = 0; i < 4; ++i) z.accr[i] = 0.0f;
     };
-    auto tile_math = [&](const u32x4(&w)[NV], const v8h(&xa)[XA], int t, Sums &z) __attribute__((always_inline)) {
+    // Vector v of the item.  The double-buffered form is given the buffer, the other one reads `cur` where it is: given
+    // the buffer, the compiler clears its registers first (0.1 us a launch: 4096 x 4096 with a gated input, 3 token rows 5.7
+    // against 6.0 us); without it, it splits the first loads of the double-buffered form into twice the branches (int8
+    // 2304 x 9216, one row 9.3 against 8.9 us).
+    auto vec = [&](const auto &w, int v) __attribute__((always_inline)) {
+        if constexpr (DB)
+            return w[v];
+        else
+            return cur[v];
+    };
+    auto tile_math = [&](const auto &w, const v8h(&xa)[XA], int t, Sums &z) __attribute__((always_inline)) {
         if constexpr (FMT == kW4G32) {
-            const uint32_t wd[4] = {w[t].x, w[t].y, w[t].z, w[t].w};
+            const uint32_t wd[4] = {vec(w, t).x, vec(w, t).y, vec(w, t).z, vec(w, t).w};
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 const int gl = 4 * t + j;  // group inside the unit
@@ -409,22 +419,22 @@ __global__ __launch_bounds__(BIG ? 1024 : PRO == 1 && M > 4 ? 256 : 512) void ge
                 const v4f d = __builtin_amdgcn_mfma_f32_16x16x32_f16(xa[j], wb, zero, 0, 0, 0);
 #pragma unroll
                 for (int i = 0; i < MI; ++i) z.accr[i] = fmaf((float)z.s_prev, z.d_prev[i], z.accr[i]);
-                const u32x4 sv = w[TILES + gl / 8];
+                const u32x4 sv = vec(w, TILES + gl / 8);
                 const uint32_t sd = sv[(gl % 8) / 2];
                 z.s_prev = __builtin_bit_cast(_Float16, (uint16_t)(sd >> (16 * (gl & 1))));
                 z.d_prev = d;
             }
         } else if constexpr (FMT == kW4C) {
-            z.accw = __builtin_amdgcn_mfma_f32_16x16x32_f16(xa[0], dequant8(w[t].x), z.accw, 0, 0, 0);
-            z.accw2 = __builtin_amdgcn_mfma_f32_16x16x32_f16(xa[1], dequant8(w[t].y), z.accw2, 0, 0, 0);
-            z.accw = __builtin_amdgcn_mfma_f32_16x16x32_f16(xa[2], dequant8(w[t].z), z.accw, 0, 0, 0);
-            z.accw2 = __builtin_amdgcn_mfma_f32_16x16x32_f16(xa[3], dequant8(w[t].w), z.accw2, 0, 0, 0);
+            z.accw = __builtin_amdgcn_mfma_f32_16x16x32_f16(xa[0], dequant8(vec(w, t).x), z.accw, 0, 0, 0);
+            z.accw2 = __builtin_amdgcn_mfma_f32_16x16x32_f16(xa[1], dequant8(vec(w, t).y), z.accw2, 0, 0, 0);
+            z.accw = __builtin_amdgcn_mfma_f32_16x16x32_f16(xa[2], dequant8(vec(w, t).z), z.accw, 0, 0, 0);
+            z.accw2 = __builtin_amdgcn_mfma_f32_16x16x32_f16(xa[3], dequant8(vec(w, t).w), z.accw2, 0, 0, 0);
         } else {
-            z.accw = __builtin_amdgcn_mfma_f32_16x16x32_f16(xa[0], dequant_i8x8(w[t].x, w[t].y), z.accw, 0, 0, 0);
-            z.accw = __builtin_amdgcn_mfma_f32_16x16x32_f16(xa[1], dequant_i8x8(w[t].z, w[t].w), z.accw, 0, 0, 0);
+            z.accw = __builtin_amdgcn_mfma_f32_16x16x32_f16(xa[0], dequant_i8x8(vec(w, t).x, vec(w, t).y), z.accw, 0, 0, 0);
+            z.accw = __builtin_amdgcn_mfma_f32_16x16x32_f16(xa[1], dequant_i8x8(vec(w, t).z, vec(w, t).w), z.accw, 0, 0, 0);
         }
     };
-    auto compute_full = [&](const u32x4(&w)[NV], Sums &z) __attribute__((always_inline)) {
+    auto compute_full = [&](const auto &w, Sums &z) __attribute__((always_inline)) {
         // full unit: straight-line code, A operands fetched one tile ahead
         v8h xa[XA], xn[XA];
         load_xa(xa, 0);
@@ -436,7 +446,7 @@ __global__ __launch_bounds__(BIG ? 1024 : PRO == 1 && M > 4 ? 256 : 512) void ge
             for (int j = 0; j < XA; ++j) xa[j] = xn[j];
         }
     };
-    auto compute_tail = [&](const u32x4(&w)[NV], int nt, Sums &z) __attribute__((always_inline)) {
+    auto compute_tail = [&](const auto &w, int nt, Sums &z) __attribute__((always_inline)) {
 #pragma unroll
         for (int t = 0; t < TILES; ++t) {
             if (t < nt) {
@@ -472,6 +482,10 @@ __global__ __launch_bounds__(BIG ? 1024 : PRO == 1 && M > 4 ? 256 : 512) void ge
                     xs.copy(a, u, lane, lds_x);
                 else
                     xs.load(a, u, lane);
+                // Gated input of 8-bit layers, 3 and 4 token rows: the activations first.  Behind the weight loads of the
+                // other wavefronts they are late for the gate's exponentials (4096 x 4096 6.2 and 6.6 us, like this
+                // 5.7 and 6.0; from 5 rows on the wait costs 2 to 4 %).
+                if constexpr (PRO == 1 && FMT == kW8C && (M == 3 || M == 4)) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             }
             auto staged = [&]() __attribute__((always_inline)) {
                 if constexpr (COPY) {
@@ -486,11 +500,11 @@ __global__ __launch_bounds__(BIG ? 1024 : PRO == 1 && M > 4 ? 256 : 512) void ge
             if (nt == TILES) {
                 load_item(cur, u, r, kFull);
                 if (r == 0) staged();
-                compute_full(cur, z);
+                compute_full(0, z);
             } else {
                 load_item(cur, u, r, kMaybePartial);
                 if (r == 0) staged();
-                compute_tail(cur, nt, z);
+                compute_tail(0, nt, z);
             }
         }
 #pragma unroll
