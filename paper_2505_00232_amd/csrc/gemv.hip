@@ -38,7 +38,10 @@ Tuning &tuning() {
 // once, instead of two units per wavefront in turn.  More than four rows: four (the staged rows fill
 // registers and LDS), but eight for 8-bit layers of up to 512 row tiles, whose workgroups hardly fill the
 // chip (M = 8, us with 4 / 8: 6144 x 4096 with rotary embedding 10.7 / 8.9, 4096 x 14336 15.9 / 14.5,
-// 2304 x 9216 11.5 / 9.9; wider ones lose: 18432 x 2304 13.3 / 17.4, 28672 x 4096 26.4 / 28.7).
+// 2304 x 9216 11.5 / 9.9; wider ones lose: 18432 x 2304 13.3 / 17.4, 28672 x 4096 26.4 / 28.7).  The same line
+// for the kernel that quantizes its activations (pro = -1, gemv_q8.hip), whose pass over the token rows is shared by the
+// wavefronts: M = 8 6144 x 4096 17.0 / 13.2, 8192 x 4096 18.0 / 14.4, 4096 x 14336 32.3 / 28.4, 2304 x 9216 23.1 / 21.1;
+// M = 5 6144 x 4096 13.0 / 10.8.
 static int wave_cap(const Geometry &g, int M, int pro, int KU) {
     if (M > 4) return pro != 1 && g.fmt == kW8C && g.RT <= 512 ? 8 : 4;
     return M <= 2 && pro == 0 && KU > 8 && KU <= 16 ? 16 : 8;
