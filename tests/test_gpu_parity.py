@@ -1834,6 +1834,18 @@ def test_blocks_of_token_rows_match_oracle(fmt, mode, M, N, K, row_tiles, blocks
     layer.close()
 
 
+def _launches(call):
+    """Kernels that `call` enqueues: the nodes of its captured graph."""
+    graph = torch.cuda.CUDAGraph(keep_graph=True)
+    call()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph):
+        call()
+    hip, n = ctypes.CDLL("libamdhip64.so"), ctypes.c_size_t(0)
+    assert hip.hipGraphGetNodes(ctypes.c_void_p(graph.raw_cuda_graph()), None, ctypes.byref(n)) == 0
+    return n.value
+
+
 @pytest.mark.parametrize("fmt,pairs,M", [("w4g32", False, 1100), ("w4c", True, 1030), ("w4c", False, 1025)])
 def test_last_round_of_tiles_left_to_the_token_row_kernels(fmt, pairs, M):
     """9 x 32 tiles of 256 x 128 are one round of 256 workgroups and 32 more: the rows of the last are computed by the
@@ -1847,12 +1859,21 @@ def test_last_round_of_tiles_left_to_the_token_row_kernels(fmt, pairs, M):
     xd = torch.from_numpy(x).to(DEV)
     guard = torch.full((M + 1, N // 2 if pairs else N), 77.0, dtype=torch.float16, device=DEV)
     if pairs:
-        binding.qfc_forward_fused(layer.handle, xd, guard[:M], activation=binding.QFC_ACT_SILU, gated_output=True)
+        call = lambda: binding.qfc_forward_fused(layer.handle, xd, guard[:M], activation=binding.QFC_ACT_SILU, gated_output=True)
         ref = oracle.gated_output(full, oracle.SILU)
     else:
         res = synth.activations(6201, M, N, M, N)
-        binding.qfc_forward_fused(layer.handle, xd, guard[:M], residual=torch.from_numpy(res).to(DEV))
+        rd = torch.from_numpy(res).to(DEV)
+        call = lambda: binding.qfc_forward_fused(layer.handle, xd, guard[:M], residual=rd)
         ref = full + res.astype(np.float64)
+    assert _launches(call) == 2  # the tiles, then the rows left over
+    binding.qfc_tune(9, 0)
+    try:
+        assert _launches(call) == 1
+    finally:
+        binding.qfc_tune(9, -1)
+    guard[:M] = 77.0
+    call()
     torch.cuda.synchronize()
     assert _E(guard[:M].cpu().numpy(), ref) <= TOL
     assert bool((guard[M] == 77.0).all())
@@ -1860,8 +1881,13 @@ def test_last_round_of_tiles_left_to_the_token_row_kernels(fmt, pairs, M):
 
 
 @pytest.mark.parametrize("B,S,h_q,h_kv,d,C,pos0", [(1, 128, 3, 1, 64, 192, 64), (1, 1100, 6, 2, 64, 1152, 13),
-                                                   (3, 50, 8, 2, 128, 128, 61), (2, 700, 4, 4, 128, 768, 7), (1, 257, 8, 4, 256, 320, 63)])
+                                                   (3, 50, 8, 2, 128, 128, 61), (2, 700, 4, 4, 128, 768, 7), (1, 257, 8, 4, 256, 320, 63),
+                                                   # 2, 3, 4, 8 and 2 tokens per workgroup, sequences that end inside one
+                                                   (2, 701, 4, 2, 128, 768, 7), (3, 515, 2, 1, 128, 576, 60), (3, 683, 3, 1, 128, 704, 21),
+                                                   (3, 1367, 2, 2, 64, 1408, 30), (3, 343, 4, 2, 256, 384, 1),
+                                                   # several whole sequences in a workgroup
+                                                   (700, 3, 2, 1, 64, 64, 5), (1030, 1, 2, 1, 128, 64, 63)])
 def test_rope_qkv_many_tokens(B, S, h_q, h_kv, d, C, pos0):
     """128 tokens and more share the evaluation of an angle among the heads of a token: one and several tokens per
-    workgroup, workgroups that span sequences, cache blocks that the tokens fill in part."""
+    workgroup (total / 512, at most 512 / d), workgroups that span sequences, cache blocks that the tokens fill in part."""
     test_rope_qkv_layout(B, S, h_q, h_kv, d, C, pos0)
