@@ -179,7 +179,7 @@ __device__ __forceinline__ void finish(const SkinnyArgs &a, const T *red, int nw
 }
 
 // ---------------------------------------------------------------- binary16 activations
-// Per step of 128 k a wavefront holds its weights in registers (requested D steps ahead) and reads the
+// Per step of 128 k a wavefront holds its weights in registers (requested D steps ahead, see below) and reads the
 // token rows from a private LDS ring of RING half steps (64 k: rows of 128 bytes, 16-byte octets
 // XOR-swizzled as in the large fp16 kernel: conflict-free operand reads).  The ring is filled by
 // direct memory -> LDS copies whose lanes cover whole 128-byte row pieces: fetching the operands from
@@ -189,6 +189,11 @@ __device__ __forceinline__ void finish(const SkinnyArgs &a, const T *red, int nw
 // own kind, so "at most the copies of RING - 1 stages outstanding" says that the oldest stage has
 // landed whatever else is in flight; the weight loads are the compiler's own, which waits for
 // them by their own count (the copies it does not see only make it wait earlier than needed).
+// The price: the count includes the weight loads, so such a wait is also one for every weight load but the
+// newest.  With a ring of two stages the loads issued at the end of a step have landed by the second half of the
+// next step (where a step has more of them than a stage has copies, some by its first half), so that beyond the
+// first D steps, which are requested together, the weights are about half a step ahead, whatever D is.
+// Long K at few rows is bound by that: 4096 x 14336 int4 groups, 32 rows, takes 18 us, 2 us a step.
 // Group scales multiply the weights (one binary16 rounding per weight), as in the large fp16 kernel.
 // XB: blocks of 8 token rows.
 template <int FMT, int XB, int R, int RING, int D, int MAXT>
