@@ -581,9 +581,31 @@ SkinnyArgs make_args(const Geometry &g, const void *packed, const void *x, const
 
 }  // namespace
 
-// Which products these kernels take.  Up to 64 token rows: all, but for layers of very many channels with int8
-// activations, whose 256-channel tiles fill the chip (us, these kernels / the tiles: 128256 x 4096 int4 57 / 64 at
-// 48 rows, 70 / 65 at 64; int8 107 / 110 at 64; 256000 x 2304 int4 66 / 74 at 32, 98 / 80 at 64).  More rows: the tiles of 64 or 128
+// 33 to 64 token rows, layers of so many channels that their 256-channel tiles fill half the compute units and more:
+// the largest K up to which those tiles are the faster ones (0: none), by the share of the compute units that
+// they fill.  Measured at 33 to 64 rows, 32768 to 256000 channels, K of 512 to 14336 (us at 64 rows, these kernels / the
+// tiles, int8 activations with the quantization kernel):
+//   int8 x int4  34000 x 2048 19.7 / 16.8, x 4096 28.4 / 28.8; 40000 x 1024 17.4 / 13.3, x 4096 32.9 / 29.6; 57000 x 8192 71.0 / 66.9
+//   int8 x int8  40000 x 1024 20.4 / 16.0, x 4096 45.1 / 43.6; 75000 x 512 23.6 / 20.2, x 1024 31.0 / 31.8; 100000 x 2048 57.0 / 51.5
+//   binary16     50000 x 512 int4 16.4 / 13.8, x 2048 32.1 / 29.7, x 4096 49.7 / 49.9; int4 groups x 1024 22.3 / 20.3, x 2048 33.1 / 32.6
+// and where the tiles start a second round, binary16 activations never (75000 x 1024 int4 27.4 / 34.4).
+static int tiles_up_to_k(const Geometry &g, int M, bool int8_activations, int num_cus) {
+    constexpr int kAll = 1 << 30;
+    const float fill = (float)((g.N + 255) / 256) / (float)num_cus;
+    const bool w8 = g.fmt == kW8C;
+    if (M <= 32 || fill < 0.5f) return 0;
+    if (int8_activations) {
+        if (M <= 48) return w8 ? 1024 : fill <= 1.0f ? 2048 : fill < 1.5f ? 0 : 512;
+        if (fill <= 1.0f) return fill < 0.6f ? 2048 : kAll;
+        return !w8 ? kAll : fill < 1.5f ? 512 : 3072;
+    }
+    if (fill < 0.6f || fill > 1.0f || (!w8 && g.K % 128 != 0)) return 0;  // (the 256-channel tiles need whole steps)
+    const bool wide = fill >= 0.75f;
+    if (M <= 48) return !wide ? 0 : g.fmt == kW4C ? 1024 : w8 ? 512 : 0;
+    return g.fmt == kW4C ? (wide ? 2048 : 1024) : w8 ? (wide ? 1024 : 512) : wide ? 1024 : 0;
+}
+
+// Which products these kernels take.  Up to 64 token rows: all but those.  More rows: the tiles of 64 or 128
 // tokens take the same time until they fill the chip, and long (they leave most of it idle); here the
 // rows are cut into blocks of 64, with the time growing with their number.  Both times are estimated
 // (us; fitted to layers of 1024 to 28672 channels, K of 2048 to 14336, 77 to 1000 rows, within about 20 %):
@@ -608,7 +630,7 @@ static float tile_round_us(const Geometry &g) { return 9.0f + 9.3e-3f * (float)g
 bool skinny_product(const Geometry &g, int M, bool int8_activations, bool gated, int num_cus) {
     if (tuning().gemm_variant != 0) return false;  // a large kernel is asked for by name
     if (tuning().skinny_max_m >= 0) return M <= tuning().skinny_max_m;
-    if (M <= kSkinnyRows) return !(int8_activations && g.RT >= 16 * num_cus) || M <= (g.fmt == kW8C ? 64 : 48);
+    if (M <= kSkinnyRows) return g.K > tiles_up_to_k(g, M, int8_activations, num_cus);
     if (M > kSkinnyMaxM) return false;
     const float here = skinny_us(g, M, int8_activations, gated, num_cus);
     const long n256 = (g.N + 255) / 256, m128 = (M + 127) / 128, m64 = (M + 63) / 64;

@@ -1834,6 +1834,33 @@ def test_blocks_of_token_rows_match_oracle(fmt, mode, M, N, K, row_tiles, blocks
     layer.close()
 
 
+@pytest.mark.parametrize("fmt,mode", [("w4g32", None), ("w4c", None), ("w8c", binding.QFC_COMPUTE_FP16_DEQUANT),
+                                      ("w8c", None), ("w4c", binding.QFC_COMPUTE_INT8_ACT)])
+@pytest.mark.parametrize("N,K", [(32512, 128), (32768, 160), (49152, 128), (65792, 96)])
+def test_wide_layers_of_few_token_rows(fmt, mode, N, K):
+    """On both sides of the lines (numbers of rows and channels) between the kernels for few token rows and the tiles
+    that fill half the chip and more: either kernel's result."""
+    print(f"wide layer {fmt} mode={mode} N={N} K={K}", flush=True)
+    wq, s = synth.weights(6300, N, K, synth.FC("t", K, N, fmt))
+    layer = _layer(wq, s, fmt, max_m=64, mode=mode)
+    int8 = mode == binding.QFC_COMPUTE_INT8_ACT or (fmt == "w8c" and mode is None)
+    for M in (32, 33, 48, 49, 64):
+        x = synth.activations(6300, M, N, M, K)
+        y = _forward(layer, x)
+        binding.qfc_tune(9, 64)
+        try:
+            few = _forward(layer, x)
+        finally:
+            binding.qfc_tune(9, -1)
+        ref = oracle.fc_int8_act(x, wq, s)[3] if int8 else oracle.fc_weight_only(x, wq, s, _group(fmt))
+        assert _E(y, ref) <= TOL, M
+        if int8:  # exact sums and the same rounding steps
+            assert np.array_equal(y.view(np.uint16), few.view(np.uint16)), M
+        else:
+            assert _E(few, ref) <= TOL, M
+    layer.close()
+
+
 def _launches(call):
     """Kernels that `call` enqueues: the nodes of its captured graph."""
     graph = torch.cuda.CUDAGraph(keep_graph=True)
