@@ -654,6 +654,10 @@ int skinny_tail_rows(const Geometry &g, int M, bool gated, int num_cus) {
     const long keep = (rounds - 1) * num_cus / n256 * 128;  // rows whose tiles fill one round less
     const long rest = M - keep;
     if (rounds < 2 || keep < 128 || rest < 1 || rest > kSkinnyMaxM) return 0;
+    // tiles that fill their two rounds or more badly save no round: workgroups of the next one fill the gaps anyway
+    // (us, tiles alone / like this, by that share: 28018 x 2048 808 rows 0.86 150 / 165, 19403 x 768 789 rows 0.89 71 / 77;
+    // 24000 x 2048 673 rows 0.92 95 / 85, 11000 x 768 1502 rows 0.92 48 / 46; one round: 11000 x 1024 720 rows 0.84 35 / 29)
+    if (rounds > 2 && 10 * (keep / 128) * n256 < 9 * (rounds - 1) * num_cus) return 0;
     const float saved = tile_round_us(g) - skinny_us(g, (int)rest, false, gated, num_cus) - 3.0f;  // (3: a second launch)
     return saved > 0.05f * (float)rounds * tile_round_us(g) ? (int)rest : 0;
 }
