@@ -637,7 +637,10 @@ bool skinny_product(const Geometry &g, int M, bool int8_activations, bool gated,
     if (!int8_activations) {
         const bool staged = g.fmt == kW8C || g.K % 128 != 0;  // 128 x 128 tiles, two workgroups per compute unit
         const float rounds = staged ? fmaxf(1.0f, (float)((g.N + 127) / 128 * m128) / (float)num_cus) : ceilf((float)(n256 * m128) / (float)num_cus);
-        return here < rounds * tile_round_us(g);
+        // (8-bit weights, the largest layers of long K: `here` is low by 25 to 40 %, which smaller ones can spare; 32768 x 14336
+        // 65 rows 178 / 165, 18529 x 12160 277 rows 233 / 227; 25698 x 10368 129 rows 142 / 182, 128256 x 4096 130 rows 271 / 293)
+        const bool low = g.fmt == kW8C && g.K >= 8192 && (long)g.N * g.K > 200L << 20;
+        return here < (low ? 0.88f : 1.0f) * rounds * tile_round_us(g);
     }
     const bool wide = 4 * n256 * m128 >= 3L * num_cus;  // (their choice between 128 and 64 tokens)
     const float tiles = 5.0f + (g.fmt == kW8C ? 4.4e-3f : 3.85e-3f) * (float)g.K;
