@@ -904,9 +904,17 @@ int attn_splits(int G, int d, int n_ctx, int num_cus) {
 // (us, 128-row blocks / 16-row blocks): head size 256, 4 groups of 2 heads, prompts of 77 tokens 13.8 / 8.9, of
 // 300 22.4 / 15.5, 77 behind 923 positions 22.2 / 15.8; head size 128, 8 groups of 4 heads, 41 behind 120 9.5 / 7.6, 100 8.3 /
 // 6.8, 37 behind 1071 (1440 steps) 14.9 / 16.0, 300 (3000 steps) 13.1 / 21.0; up to 32 positions the 128-row
-// kernel has one step and is level or faster.
-static bool few_row_blocks(int G, int M, int d, int n_ctx) {
-    return n_ctx > 32 && (long)G * ((M + 15) / 16) * ((n_ctx + 63) / 64) <= (d <= 128 ? 1200 : 2100);
+// kernel has one step and is level or faster.  And as long as the compute units hold the blocks at once: short
+// prompts of many sequences or heads are many blocks of one step each (head size 256, 32 groups, 46 tokens of 8 heads behind 43
+// 17.7 / 25.0, 49 tokens 16.3 / 26.8; 16 groups, 144 tokens of 4 heads 18.2 / 26.5; head size 128, 8 groups, 73 tokens of 8 heads 7.9 /
+// 8.7; head size 64, 16 groups, 71 tokens of 8 heads 6.1 / 6.7).  At head size 256, where one workgroup fills a
+// compute unit, also as long as a workgroup's share of the walk is short (4 groups of 2 heads, 266 tokens behind 601 26.8 / 30.9, behind
+// 234 25.1 / 20.9; 2 groups of 8 heads, 194 tokens behind 561 29.6 / 27.9).
+static bool few_row_blocks(int G, int M, int d, int n_ctx, int num_cus) {
+    const long blocks = (long)G * ((M + 15) / 16);
+    if (n_ctx <= 32 || blocks > (d <= 64 ? 2 : 1) * num_cus) return false;
+    if (d > 128 && n_ctx > 768 * (num_cus / blocks)) return false;
+    return blocks * ((n_ctx + 63) / 64) <= (d <= 128 ? 1200 : 2100);
 }
 
 // Workgroups per block of 16 query rows and KV head: the estimated time (us) of the walk and the combination.
@@ -1049,7 +1057,7 @@ hipError_t launch_attention(const void *q, const void *kc, const void *vc, int G
     bool few = a.M <= 16;
     if (!few) {
         const int forced = tuning().attn_few;
-        few = forced >= 0 ? forced != 0 : few_row_blocks(G, a.M, d, n_ctx);
+        few = forced >= 0 ? forced != 0 : few_row_blocks(G, a.M, d, n_ctx, a.num_cus);
         if (few) {  // partial results fit the workspace of the chunks
             const int most = prefill_may_chunk(G, a.M, num_cus) ? kPrefillMaxChunks : 1;
             if (tuning().attn_splits == 0) a.splits = row_block_splits(G, a.M, d, n_ctx, a.num_cus);
