@@ -57,9 +57,14 @@ GemvPlan plan_gemv(const Geometry &g, int M, int num_cus, int pro, bool gated) {
     // flight.  With the normalization, 28672 x 4096, int4 groups, us with one / two pairs: M = 1 15.4 / 14.4,
     // 4 19.2 / 15.8, 8 23.0 / 18.6; int8 at M = 8 26.3 / 23.2 (below five rows it loses: 21.4 / 25.7 at M = 2).
     // 22016 x 4096 wins from five rows on only (M = 8 17.4 / 15.9, M = 1 13.0 / 13.1), 24576 x 3072
-    // and 18432 x 2304 lose.
+    // and 18432 x 2304 lose.  From five rows on with 4-bit codes and more than four units, a compute unit holds two
+    // workgroups for a long time: two pairs win where one would leave a second round half empty or less and two fit in one,
+    // i.e. from 6 to 8 row tiles per compute unit (M = 5, us, one / two: 24768 x 7456 int4 groups 27.6 / 26.0, 26784 x 8448 int4 33.2 / 27.7;
+    // outside 23200 x 13440 38.8 / 44.0, 34944 x 13280 57.5 / 64.1, 22208 x 8800 int4 25.5 / 27.1).
     const int pair_waves = M > 4 ? (g.KU < 4 ? g.KU : 4) : 2 * g.KU;
-    const bool can_pair = gated && pro != 1 && (M > 4 || (g.fmt != kW8C && g.KU <= 4));
+    const bool two_held = M > 4 && g.fmt != kW8C && g.KU > 4;
+    const bool can_pair = gated && pro != 1 && (M > 4 || (g.fmt != kW8C && g.KU <= 4)) &&
+                          (!two_held || (g.RT >= 6 * num_cus && g.RT <= 8 * num_cus));
     const int forced = t.gemv_pairs;
     p.pairs = gated && pro != 1 && (forced > 0 ? forced == 2
                                                : can_pair && (long)(g.RT / 4) * pair_waves >= (M > 4 ? 5L : 12L) * num_cus)
