@@ -948,7 +948,11 @@ size_t attn_prefill_workspace(int G, int M, int d, int num_cus) {
 hipError_t launch_rope_qkv(const void *qkv, int B, int S, int h_q, int h_kv, int d, int C, int pos0, float base,
                            void *q_out, void *kc, void *vc, hipStream_t st) {
     const long total = (long)B * S;
-    if (total < 128) {  // (level at about 128 tokens: 77 tokens of 8 + 4 heads of 256 4.8 against 5.6 us)
+    // Few tokens, and more of them where their heads are few: a workgroup that shares the angles of a token has little else
+    // to do (us, this kernel / the other, tokens x heads x values: 400 x 3 x 64 4.0 / 7.7, 540 x 8 x 64 4.8 / 5.2, 328 x 6 x 128
+    // 4.5 / 5.0, 128 x 48 x 64 4.6 / 4.9, 400 x 4 x 256 5.1 / 5.2; 200 x 16 x 128 5.1 / 4.9, 540 x 6 x 128 5.5 / 5.1,
+    // 128 x 16 x 256 5.1 / 4.9, 200 x 48 x 64 5.7 / 5.0)
+    if (total < 128 || total * (h_q + 2 * h_kv) * d < (400L << 10)) {
         const long pairs = total * (h_q + 2 * h_kv) * (d / 2);
         rope_qkv_few_kernel<<<(unsigned)((pairs + 255) / 256), 256, 0, st>>>(
             static_cast<const _Float16 *>(qkv), B, S, h_q, h_kv, d, C, pos0, log((double)base),

@@ -1913,8 +1913,12 @@ def test_last_round_of_tiles_left_to_the_token_row_kernels(fmt, pairs, M):
                                                    (2, 701, 4, 2, 128, 768, 7), (3, 515, 2, 1, 128, 576, 60), (3, 683, 3, 1, 128, 704, 21),
                                                    (3, 1367, 2, 2, 64, 1408, 30), (3, 343, 4, 2, 256, 384, 1),
                                                    # several whole sequences in a workgroup
-                                                   (700, 3, 2, 1, 64, 64, 5), (1030, 1, 2, 1, 128, 64, 63)])
+                                                   (700, 3, 2, 1, 64, 64, 5), (1030, 1, 2, 1, 128, 64, 63),
+                                                   # one token per workgroup; both sides of the line by tokens, heads and values
+                                                   (3, 50, 16, 8, 128, 128, 61), (1, 128, 24, 8, 128, 192, 64), (1, 319, 8, 1, 128, 384, 9),
+                                                   (1, 321, 6, 2, 128, 384, 9)])
 def test_rope_qkv_many_tokens(B, S, h_q, h_kv, d, C, pos0):
-    """128 tokens and more share the evaluation of an angle among the heads of a token: one and several tokens per
-    workgroup (total / 512, at most 512 / d), workgroups that span sequences, cache blocks that the tokens fill in part."""
+    """128 tokens and more of at least 400 Ki values share the evaluation of an angle among the heads of a token: one and
+    several tokens per workgroup (total / 512, at most 512 / d), workgroups that span sequences, cache blocks that the
+    tokens fill in part; and the other kernel beside that line."""
     test_rope_qkv_layout(B, S, h_q, h_kv, d, C, pos0)
