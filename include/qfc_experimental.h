@@ -27,8 +27,8 @@ extern "C" {
  *   key 2  prefill kernel variant (0 = automatic)
  *   key 3  token rows per workgroup of the activation quantization kernel (0 = automatic; 2, 4, 8)
  *   key 4  half-unit items of the decode kernel (-1 automatic, 0 never, 1 where possible)
- *   key 5  two blocks per workgroup in prefill attention (-1 automatic, 0 never, 1 always)
- *   key 6  causal walks of prefill attention cut into chunks (-1 automatic, 0 never, 1 always);
+ *   key 5  (without effect)
+ *   key 6  causal walks of prefill attention cut into chunks (-1 automatic, 0 never, 1 always, 2, 3, 4, 6, 8 into so many);
  *          qfc_attention_workspace_size follows the value set when it is called
  *   key 7  products of few token rows (from 9): most wavefronts per workgroup (0 = automatic)
  *   key 8  the same: row tiles per workgroup (0 = automatic; 1 .. 8)
@@ -36,7 +36,8 @@ extern "C" {
  *   key 10 gated output at M <= 8: pairs of row tiles per decode workgroup (0 = automatic; 1, 2)
  *   key 11 as key 7: blocks the token rows are cut into at least (0 = automatic)
  *   key 12 attention with at most 16 query rows per KV head: workgroups per KV head (0 = automatic; 1 .. 64)
- *   key 13 attention with more than 16 query rows per KV head: blocks of 16 (-1 automatic, 0 never, 1 always) */
+ *   key 13 attention with more than 16 query rows per KV head: blocks of 16 (-1 automatic, 0 never, 1 always)
+ *   key 14 prefill attention: wavefronts that share the walk of the same query rows (0 = automatic; 1, 2) */
 void qfc_tune(int32_t key, int32_t value);
 
 /* Measurement probe (bench.py --probe-mfma): `workgroups` workgroups of four wavefronts each issue

@@ -18,6 +18,10 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-u
          # packed-fp32 code generation is switched off on purpose
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
 
+# Prefill attention holds the sums of the second product in accumulation registers, but its scores are vector operands at once:
+# with every MFMA writing accumulation registers they would be moved over one by one.
+SOURCE_FLAGS = {"attention.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]}
+
 
 # Kernels that load MFMA operands into registers with hand-written asynchronous loads and place the
 # waits themselves: the compiler takes a destination register to be valid right after the load
@@ -64,7 +68,7 @@ def build(force: bool = False, verbose: bool = False) -> str:
 
     def compile_one(src: str) -> str:
         obj = os.path.join(OBJ, src.replace(".hip", ".o"))
-        cmd = [cc, *FLAGS, "-c", os.path.join(CSRC, src), "-o", obj]
+        cmd = [cc, *FLAGS, *SOURCE_FLAGS.get(src, []), "-c", os.path.join(CSRC, src), "-o", obj]
         if src in NO_SPILL:
             cmd.append("-Rpass-analysis=kernel-resource-usage")
         r = subprocess.run(cmd, capture_output=True, text=True)

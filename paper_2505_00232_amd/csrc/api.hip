@@ -511,7 +511,6 @@ void qfc_tune(int32_t key, int32_t value) {
     if (key == 2) t.gemm_variant = value;
     if (key == 3) t.act_quant_rows = value;
     if (key == 4) t.gemv_half = value;
-    if (key == 5) t.attn_pair = value;
     if (key == 6) t.attn_chunks = value;
     if (key == 7) t.skinny_waves = value;
     if (key == 8) t.skinny_row_tiles = value;
@@ -519,6 +518,7 @@ void qfc_tune(int32_t key, int32_t value) {
     if (key == 10) t.gemv_pairs = value;
     if (key == 11) t.skinny_blocks = value;
     if (key == 13) t.attn_few = value;
+    if (key == 14) t.attn_shares = value;
     if (key == 12) t.attn_splits = value < 0 ? 0 : value > kAttnMaxSplits ? kAttnMaxSplits : value;
 }
 

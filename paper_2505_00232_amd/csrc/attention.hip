@@ -31,6 +31,8 @@ typedef float v4f __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr float kNegBig = -1.0e30f;
+// Maximum of a query row that has seen no position yet (prefill): above every masked score times the scale, below every real one
+constexpr float kFloorMax = -1.0e25f;
 static_assert(kAttnMaxSplits <= 64, "the combine kernel takes one split per lane");
 
 // ---------------------------------------------------------------- rotary embedding + layouts
@@ -209,12 +211,17 @@ struct AttnArgs {
     float *ws_ml;        // [G, splits, M, 2] partial (maximum, sum)
     _Float16 *out;       // [G, M, D]
     int M, g, S, C, n_ctx, splits;
-    int num_cus;
-    int pair;  // prefill: a workgroup takes blocks (last - i, i) in turn
+    int groups;       // prefill: workgroup i works on KV head i % groups
+    int block_rows;   // prefill: query rows per workgroup
     int chunk_steps;  // prefill: > 0 = walks are cut into chunks of this many steps (one workgroup each)
     int max_chunks;   // prefill: chunk slots per query row in the workspace
     float scale;
 };
+// prefill: steps of 32 positions that the walk of block j of `rows` query rows takes (the last row of the block sees most)
+__host__ __device__ inline int prefill_steps(const AttnArgs &a, int j, int rows) {
+    const int last = j * rows + rows - 1 < a.M - 1 ? j * rows + rows - 1 : a.M - 1;
+    return (a.n_ctx - a.S + last / a.g + 1 + 31) / 32;
+}
 
 // Workgroup = 4 wavefronts and up to 16 query rows.  grid = (splits, G, blocks of 16 query rows).  A step covers TP pairs of score tiles = 32 TP positions:
 // 64 for head sizes up to 128, 32 for 256 (whose operands of 64 positions would leave one wavefront per SIMD).
@@ -452,344 +459,369 @@ __global__ __launch_bounds__(64) void attn_combine_kernel(AttnArgs a) {
 }
 
 // ---------------------------------------------------------------- attention, many query rows (prefill)
-// More than 16 query rows per KV head.  A workgroup of 4 wavefronts owns 128 query rows, a
-// wavefront 32 of them (the columns of v_mfma_f32_32x32x16_f16), and they walk the positions the
-// block may see together, in steps of 32: the step's K rows and V block are copied once into LDS
-// (direct-to-LDS copies, ring of NS stages, one bare s_barrier per step) and every wavefront reads
-// its MFMA operands from there: S^T = K Q^T (32 positions x 32 queries), running maximum / sum per
-// query (a query's 16 scores of a step sit in two lanes), O^T += V P^T.  As in the decode kernel
-// the rows of the score tile are assigned to positions so that a lane's eight probabilities of an
-// MFMA step are eight contiguous positions (row i = 16 c + 8 b + 4 h + r is position
-// k0 + 16 c + 8 h + 4 b + r): P goes from the first product's result registers into the second
-// product's operand registers as it is, and a lane's V operand is one 16-byte read.
+// More than 16 query rows per KV head.  A wavefront owns 32 query rows (the columns of
+// v_mfma_f32_32x32x16_f16) and walks positions in steps of 32: S^T = K Q^T (32 positions x 32 queries),
+// running maximum and sum per query (a query's 16 scores of a step sit in two lanes), O^T += V P^T.  As in the
+// decode kernel the rows of the score tile are assigned to positions so that a lane's eight probabilities of
+// an MFMA step are eight contiguous positions (row i = 16 c + 8 b + 4 h + r is position
+// k0 + 16 c + 8 h + 4 b + r): P goes from the first product's result registers into the second product's
+// operand registers as it is, and a lane's V operand is one 16-byte read.
+// A workgroup is four wavefronts: PS of them share the same query rows and take every PS-th step of the walk
+// (their results meet in LDS at the end), 4 / PS own different rows.  Causal walks are of very different length and a
+// launch lasts as long as its longest: with PS = 2 that one is half as long, and there are twice as many workgroups to
+// spread.  A stage of LDS holds the PS steps the workgroup works on together.
 // LDS layouts (16-byte chunks, XOR-swizzled so that the operand reads are conflict free; the copy
 // writes LDS linearly, so the swizzle is applied to the address it reads from memory):
-//   K stage: row = position of the step (32), D / 8 chunks per row; chunk o of row p sits at o ^ swz(p)
-//   V stage: row = d (D), 4 chunks per row (32 positions); chunk c of row d sits at c ^ ((d >> 2) & 3)
+//   K step: row = position (32), D / 8 chunks per row; chunk o of row p sits at o ^ swz(p)
+//   V step: row = d (D), 4 chunks per row (32 positions); chunk c of row d sits at c ^ ((d >> 2) & 3)
 // Causal: rows of token s see positions 0 .. n_ctx - S + s; the block stops at the last position
-// its last row sees, rows that see less mask the rest.  grid = (blocks of 128 query rows, or pairs
-// of a long and a short block in large launches, G); which block a workgroup takes is decided at
-// the start of the kernel.
-template <int D>
+// its last row sees, rows that see less mask the rest.
+// Registers: up to head size 128 two workgroups per compute unit, everything in ordinary registers; at 256 one, whose
+// query operands and part of whose sums sit in accumulation registers (scores in ordinary ones: a flag of this file's build).
+// What bounds it: at 8192 tokens (head size 128) power: matrix cores busy 52 %, vector unit 57 % of the clocks, the clock at
+// 1.8 GHz; without the exponentials it is no faster.  Short walks: latency (a step of a workgroup alone on its compute unit
+// takes 0.75 us, of two together 1.2), 3 us before the first step, 2 us after the last.
+// Measured (us, 32 heads on 8 of 128; blocks of 128 rows with one walk each / this): 512 tokens 17.9 / 11.4, 1024 30.3 / 19.8, 2048
+// 58.7 / 52.5, 6000 367 / 320, 8192 636 / 570 (0.96 PFLOP/s), 130 behind 2870 positions 29.7 / 23.4, 300 behind 6000 57.3 / 52; head size
+// 64, 8 heads, 4096 tokens 48.8 / 35.2; head size 256, 8 heads on 4, 2048 tokens 54.6 / 50, 4096 172 / 110.
+template <int D, int PS>
 struct PrefillCfg {
-    static constexpr int CPR = D / 8;                   // 16-byte chunks per K row
-    static constexpr int KBYTES = 32 * D * 2;           // K rows of a step
-    static constexpr int STAGE = 2 * KBYTES;            // + the V block of the step
-    static constexpr int NS = 4;                        // LDS stages
-    static constexpr int HALVES = D > 128 ? 2 : 1;      // wavefronts that share 32 query rows (each a part of d)
-    static constexpr int NW = 4 * HALVES;               // wavefronts per workgroup
-    static constexpr int COPIES = STAGE / 1024 / NW;    // copies per wavefront and stage
+    static constexpr int CPR = D / 8;           // 16-byte chunks per K row
+    static constexpr int KB = 32 * D * 2;       // bytes of K (and of V) of a step
+    static constexpr int RW = 4 / PS;           // wavefronts that own different rows
+    static constexpr int ROWS = 32 * RW;        // query rows per workgroup
+    static constexpr int NB = 6 * PS * KB <= (D <= 128 ? 48 : 96) * 1024 ? 3 : 2;  // LDS stages
+    static constexpr int CK = PS * KB / 4096;   // copies per wavefront and stage, of K and of V
+    static constexpr int MERGE = PS > 1 ? 4 * ((D / 32) * 4096 + 256) : 0;  // bytes of the wavefronts' results
+    static constexpr int RING = 2 * NB * PS * KB;
+    static constexpr int LDS = RING > MERGE ? RING : MERGE;
+    static_assert(LDS <= (D <= 128 ? 80 : 160) * 1024 && 2 * CK * NB <= 63, "LDS, and the 6-bit counter of outstanding copies");
     __device__ static int swz(int p) { return D >= 128 ? (p & 15) : ((p >> 1) & 7); }
 };
+// maximum over the lanes l and l ^ 32
+__device__ __forceinline__ float both_halves_max(float x) {
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
 
-// (Two workgroups per compute unit up to head size 128: said in the launch bounds, so that the
-// accumulators stay in ordinary registers, where the softmax rescales them in place.)
-template <int D>
-__global__ __launch_bounds__(64 * PrefillCfg<D>::NW, 2) void attn_prefill_kernel(AttnArgs a) {
+template <int D, int PS>
+__global__ __launch_bounds__(256, D <= 128 ? 2 : 1) void attn_prefill_kernel(AttnArgs a) {
     typedef float v16f __attribute__((ext_vector_type(16)));
-    typedef PrefillCfg<D> Cfg;
+    typedef PrefillCfg<D, PS> Cfg;
     constexpr int DJ = D / 16;  // MFMA steps along d of the score product
-    // Head size 256: eight wavefronts; wavefronts w and w + 4 own the same 32 query rows and both
-    // compute their scores and probabilities, but each accumulates one half of the d range of O^T
-    // (with all of it a wavefront would need more than half the register file, i.e. one wavefront
-    // per SIMD with nothing to overlap with).
-    constexpr int HALVES = Cfg::HALVES, NW = Cfg::NW;
-    constexpr int DT = D / 32 / HALVES;  // row tiles of O^T of this wavefront
-    constexpr int NS = Cfg::NS, CP = Cfg::COPIES;
+    constexpr int DT = D / 32;  // row tiles of O^T
+    constexpr int NB = Cfg::NB, CK = Cfg::CK, KB = Cfg::KB, RW = Cfg::RW;
+    constexpr int KP = DJ < 8 ? DJ : 8;  // K operands of a step requested during the step before
     extern __shared__ uint4 lds_raw[];
+    char *const ldsb = reinterpret_cast<char *>(lds_raw);
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int rw = wave % RW, ps = wave / RW;
     const int q = lane & 31, h = lane >> 5;
-    const int G = blockIdx.y;
-    // Causal walks grow with the block index.  The first workgroups (one per compute unit) take the
-    // blocks longest walk first; the next batch, which joins them on the same compute units, takes
-    // them shortest first, and so on in turns: two workgroups that share a compute unit have
-    // about the same work together everywhere.
-    const int linear = (int)(blockIdx.y * gridDim.x + blockIdx.x);
-    const bool ascending = ((linear / a.num_cus) & 1) != 0;
-    // a.pair (launches of more than two workgroups per compute unit): a workgroup takes a long and a
-    // short block, one after the other, so that all workgroups have the same work and there are
-    // half as many (measured: S = 4096 231 -> 180 us, S = 8192 740 -> 645 us; slower for launches
-    // that are a single batch anyway).
-    const int nblocks = (a.M + 127) / 128;
-    const int reps = a.pair && 2 * (int)blockIdx.x + 1 < nblocks ? 2 : 1;
-    // a.chunk_steps > 0 (launches with fewer blocks than compute units): the walk of a block is cut
-    // into chunks of that many steps, one workgroup each, longest blocks first; a block with more
-    // than one chunk leaves unnormalized partial results that a second kernel combines.
-    int chunk_block = 0, chunk = 0, chunks = 1;
+    // (groups side by side: where 8 divides their number, the workgroups of one share the L2 of one XCD)
+    const int G = (int)blockIdx.x % a.groups, item = (int)blockIdx.x / a.groups;
+    const int nblocks = (a.M + Cfg::ROWS - 1) / Cfg::ROWS;
+    // Longest walks first: the compute units that finish theirs take the shorter ones.  a.chunk_steps > 0 (a multiple of
+    // PS; few blocks): the walk of a block is cut into chunks of that many steps, one workgroup
+    // each; a block with more than one chunk leaves unnormalized partial results that a second kernel combines.
+    int block = nblocks - 1 - item, chunk = 0, chunks = 1;
     if (a.chunk_steps > 0) {
-        int w = blockIdx.x;
-        for (int j = nblocks - 1;; --j) {
-            const int last = min(j * 128 + 127, a.M - 1);
-            const int cj = ((a.n_ctx - a.S + last / a.g + 1 + 31) / 32 + a.chunk_steps - 1) / a.chunk_steps;
-            if (w < cj || j == 0) {
-                chunk_block = j;
-                chunk = w;
-                chunks = cj;
-                break;
-            }
-            w -= cj;
+        int w = item;
+        for (block = nblocks - 1;; --block) {
+            chunks = (prefill_steps(a, block, Cfg::ROWS) + a.chunk_steps - 1) / a.chunk_steps;
+            if (w < chunks || block == 0) break;
+            w -= chunks;
         }
+        chunk = w;
         if (chunk >= chunks) return;  // (a grid larger than the chunk count: nothing to do)
     }
-  for (int rep = 0; rep < reps; ++rep) {
-    if (rep > 0) asm volatile("s_barrier" ::: "memory");  // every wavefront is done with the ring
-    const int block = a.chunk_steps > 0 ? chunk_block
-                      : a.pair ? (rep == 0 ? nblocks - 1 - (int)blockIdx.x : (int)blockIdx.x)
-                      : ascending ? (int)blockIdx.x : (int)gridDim.x - 1 - (int)blockIdx.x;
-    const int r0 = (block * 4 + (wave & 3)) * 32;             // first query row of the wavefront
+    const int r0 = block * Cfg::ROWS + rw * 32;  // first query row of the wavefront
     const int m = r0 + q;
     const bool real = m < a.M;
-    const int lim = real ? a.n_ctx - a.S + m / a.g + 1 : a.n_ctx;
     // (the same in every lane: said explicitly, the divisions would otherwise be carried out per lane
     // and drag the loop control and the copy addresses into vector registers)
     const int lo_full = __builtin_amdgcn_readfirstlane(a.n_ctx - a.S + min(r0, a.M - 1) / a.g + 1);  // positions every row of the wavefront sees
-    const int block_last = min(block * 128 + 127, a.M - 1);
-    const int nb_all = __builtin_amdgcn_readfirstlane((a.n_ctx - a.S + block_last / a.g + 1 + 31) / 32);  // steps of the block's walk
-    // the steps this workgroup takes: [sb, nb)
-    const int sb = a.chunk_steps > 0 ? chunk * a.chunk_steps : 0;
-    const int nb = a.chunk_steps > 0 ? min(nb_all, sb + a.chunk_steps) : nb_all;
+    const int nb_all = __builtin_amdgcn_readfirstlane(prefill_steps(a, block, Cfg::ROWS));
+    // the steps this workgroup takes: [sb, nb), in T stages
+    const int sb = chunk * a.chunk_steps;
+    const int nb = chunks > 1 ? min(nb_all, sb + a.chunk_steps) : nb_all;
+    const int T = (nb - sb + PS - 1) / PS;
+    const int lim = min(real ? a.n_ctx - a.S + m / a.g + 1 : a.n_ctx, 32 * nb);  // end of the positions the lane's row sees in them
 
     // Q^T operand: lane (q, h) holds Q[m][16 j + 8 h .. + 7]
-    u32x4 qf[DJ];
+    h8 qf[DJ];
 #pragma unroll
     for (int j = 0; j < DJ; ++j) {
-        const u32x4 zero = {0, 0, 0, 0};
-        qf[j] = real ? *reinterpret_cast<const u32x4 *>(a.q + ((size_t)G * a.M + m) * D + 16 * j + 8 * h) : zero;
+        const h8 zero = {0};
+        qf[j] = real ? *reinterpret_cast<const h8 *>(a.q + ((size_t)G * a.M + m) * D + 16 * j + 8 * h) : zero;
     }
-    v16f acc[DT];
+
+    // ---- copies.  Batch b = the K rows of stage b + 1 and the V blocks of stage b; the KiB pieces of a
+    // stage are dealt to the wavefronts in turn.  Both live in rings of NB stages.
+    const char *kbase = reinterpret_cast<const char *>(a.kc + (size_t)G * a.C * D);
+    const char *vbase = reinterpret_cast<const char *>(a.vc + (size_t)G * D * a.C);
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void *)lds_raw;
+    constexpr int PP = KB / 1024;  // pieces per step
+    static_assert(PP % 4 == 0, "the wavefronts' pieces of one round belong to the same step");
+    constexpr int NO = PP / 4;  // different pieces of a step a wavefront copies
+    uint32_t koffs[NO], voffs[NO];
+#pragma unroll
+    for (int i = 0; i < NO; ++i) {
+        const int L = (4 * i + wave) * 64 + lane;  // 16-byte chunk of the step
+        const int p = L / Cfg::CPR, o = (L % Cfg::CPR) ^ Cfg::swz(p);
+        koffs[i] = (uint32_t)(p * (2 * D) + o * 16);
+        const int d = L >> 2, c = (L & 3) ^ ((d >> 2) & 3);
+        voffs[i] = (uint32_t)(d * 128 + c * 16);
+    }
+    auto uniform = [](const char *p) {  // (the same in every lane: keeps the address in scalar registers)
+        const uint64_t x = reinterpret_cast<uint64_t>(p);
+        const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)x), hi = __builtin_amdgcn_readfirstlane((uint32_t)(x >> 32));
+        return reinterpret_cast<const void *>(((uint64_t)hi << 32) | lo);
+    };
+    // (BULK: the whole stage lies inside the walk.  Otherwise steps past its last copy that one again: within the cache, and masked.)
+    const uint32_t lds_wave = __builtin_amdgcn_readfirstlane(lds0 + wave * 1024);
+    auto issue_k = [&](int t, int slot, auto bulk_c) __attribute__((always_inline)) {
+        const int first = sb + t * PS;
+#pragma unroll
+        for (int i = 0; i < CK; ++i) {
+            const int p = i / NO, step = decltype(bulk_c)::value ? first + p : min(first + p, nb - 1);
+            copy16_to_lds_at(uniform(kbase + (size_t)step * KB), koffs[i % NO], lds_wave + slot * (PS * KB), 4096 * i);
+        }
+    };
+    auto issue_v = [&](int t, int slot, auto bulk_c) __attribute__((always_inline)) {
+        const int first = sb + t * PS;  // (even for PS = 2)
+#pragma unroll
+        for (int i = 0; i < CK; ++i) {
+            const int p = i / NO, step = decltype(bulk_c)::value ? first + p : min(first + p, nb - 1);
+            const char *src = PS == 2 && decltype(bulk_c)::value ? vbase + (size_t)(first / 2) * (D * 128) + p * 64
+                                                                 : vbase + (size_t)(step / 2) * (D * 128) + (step & 1) * 64;
+            copy16_to_lds_at(uniform(src), voffs[i % NO], lds_wave + (NB + slot) * (PS * KB), 4096 * i);
+        }
+    };
+
+    // operand read offsets of this lane inside the rings
+    const int pp = 16 * (q >> 4) + 8 * ((q >> 2) & 1) + 4 * ((q >> 3) & 1) + (q & 3);  // position of score-tile row q
+    int koff[DJ];
+#pragma unroll
+    for (int j = 0; j < DJ; ++j) koff[j] = ps * KB + pp * (2 * D) + (((2 * j + h) ^ Cfg::swz(pp)) * 16);
+    int voff[2];
+#pragma unroll
+    for (int c = 0; c < 2; ++c) voff[c] = NB * PS * KB + ps * KB + q * 64 + (((2 * c + h) ^ ((q >> 2) & 3)) * 16);
+    auto read_k = [&](int j, int slot) __attribute__((always_inline)) { return *reinterpret_cast<const h8 *>(ldsb + koff[j] + slot * (PS * KB)); };
+
+    v16f acc[DT], st;
+    float run_max = kFloorMax, run_sum = 0.0f;
+    float top;  // the lane's largest raw score of the step at hand
 #pragma unroll
     for (int t = 0; t < DT; ++t)
 #pragma unroll
         for (int e = 0; e < 16; ++e) acc[t][e] = 0.0f;
-    float run_max = kNegBig, run_sum = 0.0f;
-    float run_max_final = kNegBig;  // the maximum over the steps actually taken (run_max runs a step ahead)
-
-    // ---- copies: the stage's bytes are CP * 4 KiB pieces; wavefront w issues pieces w, w + 4, ..
-    const char *kbase = reinterpret_cast<const char *>(a.kc + (size_t)G * a.C * D);
-    const char *vbase = reinterpret_cast<const char *>(a.vc + (size_t)G * D * a.C);
-    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void *)lds_raw;
-    uint32_t src_off[CP];  // byte offset of this lane's 16 bytes inside the step's K rows / V block (step-invariant part)
+    h8 kf[KP];
+    // register e = 8 c + 4 b + r of lane (q, h): position k0 + 8 h + (16 c + 4 b + r)
+    auto mask = [&](v16f &s, int k0) __attribute__((always_inline)) {
 #pragma unroll
-    for (int i = 0; i < CP; ++i) {
-        const int piece = wave + NW * i;     // KiB piece of the stage
-        const int L = piece * 64 + lane;     // linear 16-byte chunk of the stage
-        if (piece < Cfg::KBYTES / 1024) {
-            const int p = L / Cfg::CPR, o = (L % Cfg::CPR) ^ Cfg::swz(p);
-            src_off[i] = (uint32_t)(p * (2 * D) + o * 16);
-        } else {
-            const int Lv = L - Cfg::KBYTES / 16;
-            const int d = Lv >> 2, c = (Lv & 3) ^ ((d >> 2) & 3);
-            src_off[i] = (uint32_t)(d * 128 + c * 16);
-        }
+        for (int e = 0; e < 16; ++e) s[e] = 16 * (e >> 3) + (e & 7) < lim - k0 - 8 * h ? s[e] : kNegBig;
+    };
+    auto largest = [&](const v16f &s) __attribute__((always_inline)) {
+        float x = fmaxf(s[0], s[1]);
+#pragma unroll
+        for (int e = 2; e < 16; e += 2) x = fmaxf(fmaxf(x, s[e]), s[e + 1]);
+        return x;
+    };
+    constexpr int CB = 2 * CK;  // copies of a batch
+    constexpr std::true_type kBulk;
+    constexpr std::false_type kEdge;
+
+    // ---- before the loop: the scores of stage 0
+    issue_k(0, 0, kEdge);
+#pragma unroll
+    for (int b = 0; b < NB - 1; ++b) {  // (copies past the walk's end: into slots that nothing reads)
+        issue_k(b + 1, (b + 1) % NB, kEdge);
+        issue_v(b, b % NB, kEdge);
     }
-    auto issue = [&](int blk) {
-        // past the end the walk's first steps are copied again (constant operation counts), into one
-        // spare KiB behind the ring that nothing reads (and from distinct sources: many copies of the
-        // same lines in flight had been seen in ring slots after the counter said they were done;
-        // the cause is not known, so a late copy gets no destination that anything reads)
-        const int bc = blk < nb ? blk : min(sb + (blk - nb), nb - 1);
-        const int p0 = bc * 32;
-        const char *ksrc = kbase + (size_t)p0 * (2 * D);
-        const char *vsrc = vbase + (size_t)(p0 / 64) * D * 128 + (p0 % 64) * 2;
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"((NB - 1) * CB) : "memory");
 #pragma unroll
-        for (int i = 0; i < CP; ++i) {
-            const int piece = wave + NW * i;
-            const bool is_k = piece < Cfg::KBYTES / 1024;
-            // (the address is the same in every lane; saying so keeps it in scalar registers for the copy)
-            const uint64_t addr = reinterpret_cast<uint64_t>(is_k ? ksrc : vsrc);
-            const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)addr);
-            const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(addr >> 32));
-            copy16_to_lds(reinterpret_cast<const void *>(((uint64_t)hi << 32) | lo), src_off[i],
-                          __builtin_amdgcn_readfirstlane(lds0 + (blk < nb ? (blk % NS) * Cfg::STAGE + piece * 1024 : NS * Cfg::STAGE)));
-        }
-    };
+    for (int j = 0; j < DJ; ++j) {
+        const v16f zero = {0};
+        st = __builtin_amdgcn_mfma_f32_32x32x16_f16(read_k(j, 0), qf[j], j == 0 ? zero : st, 0, 0, 0);
+    }
+    if (32 * (sb + ps) + 32 > lo_full || sb + ps >= nb) mask(st, 32 * (sb + ps));
+    top = largest(st);
+    // batch 0 is there, and K of stage 0 has been read by all
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"((NB - 2) * CB) : "memory");
+    if (NB - 1 < T) {
+        if (NB < T) issue_k(NB, 0, kEdge);
+        issue_v(NB - 1, NB - 1, kEdge);
+    }
+#pragma unroll
+    for (int j = 0; j < KP; ++j) kf[j] = read_k(j, 1 % NB);
 
-    // operand read offsets of this lane inside a stage
-    const int pp = 16 * (q >> 4) + 8 * ((q >> 2) & 1) + 4 * ((q >> 3) & 1) + (q & 3);  // position of score-tile row q
-    int koff[DJ];
-#pragma unroll
-    for (int j = 0; j < DJ; ++j) koff[j] = pp * (2 * D) + (((2 * j + h) ^ Cfg::swz(pp)) * 16);
-    int voff[DT][2];
-#pragma unroll
-    for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-        for (int c = 0; c < 2; ++c) {
-            const int d = 32 * (dt + (wave >> 2) * DT) + q;
-            voff[dt][c] = Cfg::KBYTES + d * 64 + (((2 * c + h) ^ ((d >> 2) & 3)) * 16);
-        }
-
-#pragma unroll
-    for (int p = 0; p < NS - 1; ++p) issue(sb + p);
-    // The scores of step blk + 1 are computed while the softmax of step blk runs: their MFMAs do
-    // not depend on it, so the matrix core works through them while the vector unit does the
-    // exponentials (from one wavefront the two would otherwise take turns).
-    auto scores = [&](int blk_) {
-        const char *stage_ = reinterpret_cast<const char *>(lds_raw) + (blk_ % NS) * Cfg::STAGE;
-        u32x4 kf[DJ];
-#pragma unroll
-        for (int j = 0; j < DJ; ++j) kf[j] = *reinterpret_cast<const u32x4 *>(stage_ + koff[j]);
-        v16f r;
-#pragma unroll
-        for (int e = 0; e < 16; ++e) r[e] = 0.0f;
-#pragma unroll
-        for (int j = 0; j < DJ; ++j)
-            r = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(h8, kf[j]), __builtin_bit_cast(h8, qf[j]), r, 0, 0, 0);
-        return r;
-    };
-    wait_vmcnt<(NS - 2) * CP>();
-    asm volatile("s_barrier" ::: "memory");
-    v16f st = scores(sb);
-    // The softmax of a step is cut in two.  Its first part (running maximum and the correction of
-    // the sums so far) only needs the step's scores, so it runs a step ahead, between the MFMAs of
-    // the previous step's second product; its second part (exponentials, sums, conversion) runs
-    // between the MFMAs of the next step's scores.  From one wavefront the matrix core and the
-    // vector unit would otherwise take turns.
-    // EDGE = some row of the wavefront does not see all 32 positions of the step (causal horizon or
-    // end of the context); the steps before a wavefront's first such step run branch-free bodies in
-    // which the compiler is told to issue the MFMAs one at a time between the vector instructions.
-    auto max_part = [&](const v16f &sv, int k0, auto edge_c) {
-        constexpr bool EDGE = decltype(edge_c)::value;
-        // register e = 8 c + 4 b + r of lane (q, h): position k0 + 8 h + (16 c + 4 b + r)
-        const int room = lim - k0 - 8 * h;
-        float bmax = kNegBig;
-#pragma unroll
-        for (int e = 0; e < 16; ++e) bmax = fmaxf(bmax, !EDGE || 16 * (e >> 3) + (e & 7) < room ? sv[e] : kNegBig);
-        bmax = fmaxf(bmax, __shfl_xor(bmax, 32, 64));
-        const float new_max = fmaxf(run_max, bmax * a.scale);  // kNegBig * scale stays hugely negative
-        const float c = __builtin_amdgcn_exp2f(run_max - new_max);
-        run_max = new_max;
-        return c;
-    };
-    float corr = max_part(st, sb * 32, std::true_type{});
-    auto step = [&](int blk, auto edge_c, auto edge_next_c) {
-        constexpr bool EDGE = decltype(edge_c)::value;
-        const int k0 = blk * 32;
-        // stage blk + 1 has landed (past the end: a copy of the last stage), and every wavefront is
-        // done with stage blk - 1, whose slot the next copies overwrite
-        wait_vmcnt<(NS - 3) * CP>();
-        asm volatile("s_barrier" ::: "memory");
-        issue(blk + NS - 1);
-        // (the one branch of a step comes first, so that the rest is one block for the scheduler)
-        if (__any(corr != 1.0f)) {
+    // ---- one step per stage.  Scores of the next step first (their MFMAs run beside the exponentials of this one),
+    // then, behind the barrier that hands over the next stage, the second product (beside the rest of the exponentials and
+    // the next step's maximum).  BULK: the next step exists and no row of the wavefront masks any of it, and so does
+    // the batch to issue: branch-free but for the rescaling, with an order of MFMAs and vector instructions asked of the scheduler.
+    auto step = [&](int t, int slot, auto bulk_c) __attribute__((always_inline)) {
+        constexpr bool BULK = decltype(bulk_c)::value;
+        const int k0 = 32 * (sb + t * PS + ps), slot1 = slot + 1 == NB ? 0 : slot + 1, slot2 = slot1 + 1 == NB ? 0 : slot1 + 1;
+        if (__any(top * a.scale > run_max)) {
+            const float nm = fmaxf(run_max, both_halves_max(top) * a.scale), corr = __builtin_amdgcn_exp2f(run_max - nm);
+            run_max = nm;
+            run_sum *= corr;
 #pragma unroll
             for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
                 for (int e = 0; e < 16; ++e) acc[dt][e] *= corr;
         }
-        const char *stage = reinterpret_cast<const char *>(lds_raw) + (blk % NS) * Cfg::STAGE;
-        u32x4 vf[DT][2];
+        v16f sn;
+        if (BULK || t + 1 < T) {
 #pragma unroll
-        for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-            for (int c = 0; c < 2; ++c) vf[dt][c] = *reinterpret_cast<const u32x4 *>(stage + voff[dt][c]);
-        const v16f st_next = scores(blk + 1);
-        // raw scores; the scale (in units of log 2) is applied inside the exponent: 2^(s scale - maximum)
-        const int room = lim - k0 - 8 * h;
-        const float cur_max = run_max;
-        run_max_final = cur_max;
-        float psum = 0.0f;
-        h8 pv[2];
-#pragma unroll
-        for (int e = 0; e < 16; ++e) {
-            float p = __builtin_amdgcn_exp2f(fmaf(st[e], a.scale, -cur_max));
-            if (EDGE) p = 16 * (e >> 3) + (e & 7) < room ? p : 0.0f;
-            psum += p;
-            pv[e >> 3][e & 7] = (_Float16)p;
+            for (int j = 0; j < DJ; ++j) {
+                const v16f zero = {0};
+                sn = __builtin_amdgcn_mfma_f32_32x32x16_f16(j < KP ? kf[j < KP ? j : 0] : read_k(j, slot1), qf[j], j == 0 ? zero : sn, 0, 0, 0);
+            }
         }
-        run_sum = run_sum * corr + psum;
-        if (EDGE && k0 + 32 > a.n_ctx) {  // positions past the context may hold anything
-#pragma unroll
-            for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-                for (int c = 0; c < 2; ++c) {
-                    const int p0 = k0 + 16 * c + 8 * h;
-                    uint32_t w[4] = {vf[dt][c].x, vf[dt][c].y, vf[dt][c].z, vf[dt][c].w};
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        if (p0 + 2 * e >= a.n_ctx) w[e] &= 0xFFFF0000u;
-                        if (p0 + 2 * e + 1 >= a.n_ctx) w[e] &= 0x0000FFFFu;
-                    }
-                    vf[dt][c] = u32x4{w[0], w[1], w[2], w[3]};
-                }
-        }
-        __builtin_amdgcn_s_setprio(1);
-        // (positions 0..15 of the step first: their probabilities are ready first)
+        h8 vf[DT][2];
 #pragma unroll
         for (int c = 0; c < 2; ++c)
 #pragma unroll
+            for (int dt = 0; dt < DT; ++dt) vf[dt][c] = *reinterpret_cast<const h8 *>(ldsb + voff[c] + dt * 2048 + slot * (PS * KB));
+        if (!BULK && k0 + 32 > a.n_ctx) {  // positions past the context may hold anything
+#pragma unroll
             for (int dt = 0; dt < DT; ++dt)
-                acc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(h8, vf[dt][c]), pv[c], acc[dt], 0, 0, 0);
-        // first part of the next step's softmax (past the last step: of scores nobody uses)
-        corr = max_part(st_next, k0 + 32, edge_next_c);
-        __builtin_amdgcn_s_setprio(0);
-        if (!EDGE && !decltype(edge_next_c)::value) {
-            // order asked of the scheduler: the operand reads, then every score MFMA followed by a
-            // share of the exponential part, then every MFMA of the second product followed by a
-            // share of the maximum part
-            if (HALVES == 1) __builtin_amdgcn_sched_group_barrier(0x100, DJ + 2 * DT, 0);
 #pragma unroll
-            for (int j = 0; j < DJ; ++j) {  // score MFMAs, the exponentials of the step's first 16 positions
+                for (int c = 0; c < 2; ++c)
+#pragma unroll
+                    for (int e = 0; e < 8; ++e)
+                        if (k0 + 16 * c + 8 * h + e >= a.n_ctx) vf[dt][c][e] = (_Float16)0.0f;
+        }
+        h8 pv[2];
+        float sum4[4];
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+            // raw scores; the scale (in units of log 2) is applied inside the exponent: 2^(s scale - maximum); masked ones
+            // give 0 (the maximum of a row that has seen nothing is far above them)
+            const float p = __builtin_amdgcn_exp2f(fmaf(st[e], a.scale, -run_max));
+            sum4[e & 3] = e < 4 ? p : sum4[e & 3] + p;
+            pv[e >> 3][e & 7] = (_Float16)p;
+        }
+        run_sum += (sum4[0] + sum4[1]) + (sum4[2] + sum4[3]);
+        // the next batch has landed for everyone, and everyone has read this stage's V and the next one's K
+        // (one asm: the operand reads above are issued before it, and none may be in flight when the barrier opens)
+        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(BULK ? (NB - 2) * CB : 0) : "memory");
+        if (BULK || t + NB + 1 < T) issue_k(t + NB + 1, slot1, bulk_c);
+        if (BULK || t + NB < T) issue_v(t + NB, slot, bulk_c);
+        if (BULK || t + 2 < T) {
+#pragma unroll
+            for (int j = 0; j < KP; ++j) kf[j] = read_k(j, slot2);
+        }
+#pragma unroll
+        for (int c = 0; c < 2; ++c)
+#pragma unroll
+            for (int dt = 0; dt < DT; ++dt) acc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_f16(vf[dt][c], pv[c], acc[dt], 0, 0, 0);
+        if (BULK || t + 1 < T) {
+            if (!BULK && (k0 + 32 * PS + 32 > lo_full || sb + (t + 1) * PS + ps >= nb)) mask(sn, k0 + 32 * PS);
+            top = largest(sn);
+            st = sn;
+        }
+        if (BULK) {  // every MFMA followed by its share of the vector instructions (56 of the exponentials, 8 of the maximum)
+#pragma unroll
+            for (int j = 0; j < DJ; ++j) {
                 __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-                __builtin_amdgcn_sched_group_barrier(0x002, 32 / DJ, 0);
+                __builtin_amdgcn_sched_group_barrier(0x002, 5, 0);
             }
 #pragma unroll
-            for (int j = 0; j < DT; ++j) {  // second product over those positions, the other exponentials
+            for (int j = 0; j < DT; ++j) {
                 __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-                __builtin_amdgcn_sched_group_barrier(0x002, 32 / DT, 0);
+                __builtin_amdgcn_sched_group_barrier(0x002, 4, 0);
             }
 #pragma unroll
-            for (int j = 0; j < DT; ++j) {  // second product over the rest, the next step's maximum part
+            for (int j = 0; j < DT; ++j) {
                 __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-                __builtin_amdgcn_sched_group_barrier(0x002, 16 / DT, 0);
+                __builtin_amdgcn_sched_group_barrier(0x002, 3, 0);
             }
         }
-        st = st_next;
     };
-    const int nfull = min(nb, lo_full / 32);  // steps in which every row of the wavefront sees all positions
-    int blk = sb;
-    for (; blk < nfull - 1; ++blk) step(blk, std::false_type{}, std::false_type{});
-    for (; blk < nfull; ++blk) step(blk, std::false_type{}, std::true_type{});
-    for (; blk < nb; ++blk) step(blk, std::true_type{}, std::true_type{});
-    wait_vmcnt<0>();  // the redundant copies past the end have landed before the workgroup leaves
-    run_sum += __shfl_xor(run_sum, 32, 64);
-    if (real && chunks > 1) {
-        // partial result of this chunk: unnormalized O^T column, maximum (in units of log 2) and sum
-        const size_t slot = ((size_t)G * a.M + m) * a.max_chunks + chunk;
-        float *dst = a.ws_o + slot * D;
+    // stages whose successor is unmasked for this wavefront, and inside the walk with all that is issued
+    const int full = lo_full / 32 - 1 - sb - ps;  // (steps up to lo_full / 32 - 1 are unmasked)
+    const int bulk = min(full < 0 ? 0 : full / PS, T - NB - 1);
+    int t = 0;
+    for (; t + NB <= bulk; t += NB)
 #pragma unroll
-        for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-            for (int b = 0; b < 4; ++b)
-                *reinterpret_cast<v4f *>(dst + 32 * (dt + (wave >> 2) * DT) + 8 * b + 4 * h) =
-                    v4f{acc[dt][4 * b + 0], acc[dt][4 * b + 1], acc[dt][4 * b + 2], acc[dt][4 * b + 3]};
-        if (h == 0 && wave < 4) {
-            a.ws_ml[slot * 2] = run_max_final;
-            a.ws_ml[slot * 2 + 1] = run_sum;
-        }
-    } else if (real) {
-        const float inv = 1.0f / run_sum;
-        // lane (q, h) holds O^T rows d = 32 dt + 8 b + 4 h + r of column q: four consecutive d per b
-        _Float16 *dst = a.out + ((size_t)G * a.M + m) * D;
-#pragma unroll
-        for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-            for (int b = 0; b < 4; ++b) {
-                const h4 v = {(_Float16)(acc[dt][4 * b + 0] * inv), (_Float16)(acc[dt][4 * b + 1] * inv),
-                              (_Float16)(acc[dt][4 * b + 2] * inv), (_Float16)(acc[dt][4 * b + 3] * inv)};
-                *reinterpret_cast<h4 *>(dst + 32 * (dt + (wave >> 2) * DT) + 8 * b + 4 * h) = v;
-            }
+        for (int s = 0; s < NB; ++s) step(t + s, s, kBulk);
+    for (int slot = 0; t < T; ++t) {  // (t is a multiple of NB here)
+        step(t, slot, kEdge);
+        slot = slot + 1 == NB ? 0 : slot + 1;
     }
-  }
-}
+    run_sum += __shfl_xor(run_sum, 32, 64);
 
-// steps of the walk of block j, and the chunks it is cut into (host side of what the kernels compute)
-inline int prefill_steps(const AttnArgs &a, int j) {
-    const int last = (j * 128 + 127 < a.M - 1) ? j * 128 + 127 : a.M - 1;
-    return (a.n_ctx - a.S + last / a.g + 1 + 31) / 32;
-}
-inline int prefill_chunks(const AttnArgs &a, int j) {
-    return (prefill_steps(a, j) + a.chunk_steps - 1) / a.chunk_steps;
+    // ---- the PS wavefronts of the same rows meet in LDS; each then finishes the d tiles dt = ps, ps + PS, ...
+    if constexpr (PS > 1) {
+        constexpr int PER_WAVE = DT * 4096;
+        float *ml = reinterpret_cast<float *>(ldsb + 4 * PER_WAVE);  // [wave][q]: maximum, sum
+        asm volatile("s_barrier" ::: "memory");  // everyone is done with the rings
+        if (h == 0) {
+            ml[(wave * 32 + q) * 2] = run_max;
+            ml[(wave * 32 + q) * 2 + 1] = run_sum;
+        }
+#pragma unroll
+        for (int dt = 0; dt < DT; ++dt)
+            if (dt % PS != ps)
+#pragma unroll
+                for (int b = 0; b < 4; ++b)
+                    *reinterpret_cast<v4f *>(ldsb + wave * PER_WAVE + (dt * 4 + b) * 1024 + lane * 16) =
+                        v4f{acc[dt][4 * b], acc[dt][4 * b + 1], acc[dt][4 * b + 2], acc[dt][4 * b + 3]};
+        __syncthreads();
+        float f[PS], own = 0.0f;
+        run_max = kFloorMax;
+#pragma unroll
+        for (int w = 0; w < PS; ++w) run_max = fmaxf(run_max, ml[((w * RW + rw) * 32 + q) * 2]);
+        run_sum = 0.0f;
+#pragma unroll
+        for (int w = 0; w < PS; ++w) {
+            const float *src = ml + ((w * RW + rw) * 32 + q) * 2;
+            f[w] = __builtin_amdgcn_exp2f(src[0] - run_max);
+            run_sum += f[w] * src[1];
+            own = w == ps ? f[w] : own;
+        }
+#pragma unroll
+        for (int dt = 0; dt < DT; ++dt) {
+            if (dt % PS != ps) continue;
+#pragma unroll
+            for (int e = 0; e < 16; ++e) acc[dt][e] *= own;
+#pragma unroll
+            for (int w = 0; w < PS; ++w) {
+                if (w == ps) continue;
+#pragma unroll
+                for (int b = 0; b < 4; ++b) {
+                    const v4f o = *reinterpret_cast<const v4f *>(ldsb + (w * RW + rw) * PER_WAVE + (dt * 4 + b) * 1024 + lane * 16);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) acc[dt][4 * b + e] = fmaf(f[w], o[e], acc[dt][4 * b + e]);
+                }
+            }
+        }
+    }
+    if (!real) return;
+    // lane (q, h) holds O^T rows d = 32 dt + 8 b + 4 h + r of column q: four consecutive d per b
+    const size_t slot = ((size_t)G * a.max_chunks + chunk) * a.M + m;  // (rows side by side: 4 KiB apart they meet in one memory channel)
+    const float inv = 1.0f / run_sum;
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt) {
+        if (PS > 1 && dt % PS != ps) continue;
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+            const int d = 32 * dt + 8 * b + 4 * h;
+            const v4f o = {acc[dt][4 * b], acc[dt][4 * b + 1], acc[dt][4 * b + 2], acc[dt][4 * b + 3]};
+            if (chunks > 1)  // partial result: unnormalized O^T column, maximum (in units of log 2) and sum
+                *reinterpret_cast<v4f *>(a.ws_o + slot * D + d) = o;
+            else
+                *reinterpret_cast<h4 *>(a.out + ((size_t)G * a.M + m) * D + d) =
+                    h4{(_Float16)(o[0] * inv), (_Float16)(o[1] * inv), (_Float16)(o[2] * inv), (_Float16)(o[3] * inv)};
+        }
+    }
+    if (chunks > 1 && h == 0 && ps == 0) {
+        a.ws_ml[slot * 2] = run_max;
+        a.ws_ml[slot * 2 + 1] = run_sum;
+    }
 }
 
 // Chunked walks: the rows of blocks with more than one chunk.  One wavefront per query row; lane l
@@ -798,24 +830,26 @@ template <int D>
 __global__ __launch_bounds__(256) void attn_prefill_combine_kernel(AttnArgs a) {
     constexpr int PER = D / 64;
     const int lane = threadIdx.x & 63;
-    const int m = blockIdx.x * 4 + (threadIdx.x >> 6);
+    const int m = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + (threadIdx.x >> 6));
     const int G = blockIdx.y;
     if (m >= a.M) return;
-    const int last = min((m / 128) * 128 + 127, a.M - 1);
-    const int chunks = ((a.n_ctx - a.S + last / a.g + 1 + 31) / 32 + a.chunk_steps - 1) / a.chunk_steps;
+    const int chunks = (prefill_steps(a, m / a.block_rows, a.block_rows) + a.chunk_steps - 1) / a.chunk_steps;
     if (chunks <= 1) return;  // written by the first kernel
-    const size_t slot0 = ((size_t)G * a.M + m) * a.max_chunks;
+    const size_t slot0 = (size_t)G * a.max_chunks * a.M + m;  // chunk c's: slot0 + c * M
     // lane c < chunks holds chunk c's (maximum, sum); all loads of the row are requested at once
     static_assert(kPrefillMaxChunks == 8, "the reductions below cover eight lanes");
     float mx = kNegBig, l = 0.0f;
     if (lane < chunks) {
-        mx = a.ws_ml[(slot0 + lane) * 2];
-        l = a.ws_ml[(slot0 + lane) * 2 + 1];
+        mx = a.ws_ml[(slot0 + (size_t)lane * a.M) * 2];
+        l = a.ws_ml[(slot0 + (size_t)lane * a.M) * 2 + 1];
     }
     float part[kPrefillMaxChunks][PER];
 #pragma unroll
     for (int c = 0; c < kPrefillMaxChunks; ++c) {
-        const float *src = a.ws_o + (slot0 + min(c, chunks - 1)) * D + lane * PER;
+#pragma unroll
+        for (int e = 0; e < PER; ++e) part[c][e] = 0.0f;
+        if (c >= chunks) continue;  // (the same for the whole wavefront)
+        const float *src = a.ws_o + (slot0 + (size_t)c * a.M) * D + lane * PER;
 #pragma unroll
         for (int e = 0; e < PER; ++e) part[c][e] = src[e];
     }
@@ -833,7 +867,7 @@ __global__ __launch_bounds__(256) void attn_prefill_combine_kernel(AttnArgs a) {
     for (int e = 0; e < PER; ++e) o[e] = 0.0f;
 #pragma unroll
     for (int c = 0; c < kPrefillMaxChunks; ++c) {
-        const float fc = __shfl(f, c, 64);  // 0 for c >= chunks (whose loads repeated the last chunk)
+        const float fc = __shfl(f, c, 64);  // 0 for c >= chunks
 #pragma unroll
         for (int e = 0; e < PER; ++e) o[e] = fmaf(fc, part[c][e], o[e]);
     }
@@ -843,23 +877,21 @@ __global__ __launch_bounds__(256) void attn_prefill_combine_kernel(AttnArgs a) {
     for (int e = 0; e < PER; ++e) dst[e] = (_Float16)(o[e] * inv);
 }
 
-template <int D>
-hipError_t launch_attn_prefill(const AttnArgs &a, int G, hipStream_t st) {
-    constexpr size_t lds = (size_t)PrefillCfg<D>::NS * PrefillCfg<D>::STAGE + 1024;  // the ring and the spare KiB
-    static_assert(lds <= 160 * 1024, "LDS budget");
-    static_assert((PrefillCfg<D>::NS - 1) * PrefillCfg<D>::COPIES <= 63, "outstanding copies must fit the 6-bit counter");
-    if (const hipError_t e = allow_dynamic_lds<attn_prefill_kernel<D>>(lds); e != hipSuccess) return e;
-    const int nblocks = (a.M + 127) / 128;
+template <int D, int PS>
+hipError_t launch_attn_prefill(const AttnArgs &a, hipStream_t st) {
+    constexpr int rows = PrefillCfg<D, PS>::ROWS, lds = PrefillCfg<D, PS>::LDS;
+    if (a.block_rows != rows) return hipErrorInvalidValue;
+    if (const hipError_t e = allow_dynamic_lds<attn_prefill_kernel<D, PS>>(lds); e != hipSuccess) return e;
+    const int nblocks = (a.M + rows - 1) / rows;
+    int items = nblocks;
     if (a.chunk_steps > 0) {
-        int total = 0;
-        for (int j = 0; j < nblocks; ++j) total += prefill_chunks(a, j);
-        attn_prefill_kernel<D><<<dim3((unsigned)total, (unsigned)G), 64 * PrefillCfg<D>::NW, lds, st>>>(a);
-        const hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-        attn_prefill_combine_kernel<D><<<dim3((unsigned)((a.M + 3) / 4), (unsigned)G), 256, 0, st>>>(a);
-        return hipGetLastError();
+        items = 0;
+        for (int j = 0; j < nblocks; ++j) items += (prefill_steps(a, j, rows) + a.chunk_steps - 1) / a.chunk_steps;
     }
-    attn_prefill_kernel<D><<<dim3((unsigned)(a.pair ? (nblocks + 1) / 2 : nblocks), (unsigned)G), 64 * PrefillCfg<D>::NW, lds, st>>>(a);
+    attn_prefill_kernel<D, PS><<<dim3((unsigned)(items * a.groups)), 256, lds, st>>>(a);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess || a.chunk_steps == 0) return e;
+    attn_prefill_combine_kernel<D><<<dim3((unsigned)((a.M + 3) / 4), (unsigned)a.groups), 256, 0, st>>>(a);
     return hipGetLastError();
 }
 
@@ -897,24 +929,19 @@ int attn_splits(int G, int d, int n_ctx, int num_cus) {
     return s < 1 ? 1 : s;
 }
 
-// More than 16 query rows (prompts): blocks of 16 rows in the decode kernel, or the kernel for blocks of 128.  That one
-// reads each position once per 128 rows, but from a few workgroups, each with a long walk: a short prompt
-// waits for it.  Here the positions are read once per 16 rows and the walks are split over wavefronts and
-// workgroups, which wins as long as the steps (of a wavefront: 16 rows x 64 positions) are few.  Measured
-// (us, 128-row blocks / 16-row blocks): head size 256, 4 groups of 2 heads, prompts of 77 tokens 13.8 / 8.9, of
-// 300 22.4 / 15.5, 77 behind 923 positions 22.2 / 15.8; head size 128, 8 groups of 4 heads, 41 behind 120 9.5 / 7.6, 100 8.3 /
-// 6.8, 37 behind 1071 (1440 steps) 14.9 / 16.0, 300 (3000 steps) 13.1 / 21.0; up to 32 positions the 128-row
-// kernel has one step and is level or faster.  And as long as the compute units hold the blocks at once: short
-// prompts of many sequences or heads are many blocks of one step each (head size 256, 32 groups, 46 tokens of 8 heads behind 43
-// 17.7 / 25.0, 49 tokens 16.3 / 26.8; 16 groups, 144 tokens of 4 heads 18.2 / 26.5; head size 128, 8 groups, 73 tokens of 8 heads 7.9 /
-// 8.7; head size 64, 16 groups, 71 tokens of 8 heads 6.1 / 6.7).  At head size 256, where one workgroup fills a
-// compute unit, also as long as a workgroup's share of the walk is short (4 groups of 2 heads, 266 tokens behind 601 26.8 / 30.9, behind
-// 234 25.1 / 20.9; 2 groups of 8 heads, 194 tokens behind 561 29.6 / 27.9).
+// More than 16 query rows (prompts): blocks of 16 rows in the decode kernel, or the kernel for blocks of 64 and 128.  That one
+// reads each position once per block, but takes 4 to 7 us before its first and behind its last step.
+// Here the positions are read once per 16 rows and the walks are split over wavefronts and
+// workgroups, which wins as long as there is little to walk (blocks x 64 positions) and the compute units hold the
+// blocks at once; up to 32 positions the other kernel has one step and is level or faster (head size 256: with one block of rows).  Measured (us, blocks of 64 or 128 / of 16):
+// head size 64, 8 groups, 242 tokens 7.0 / 5.9, 422 8.5 / 7.4, 4 groups, 27 tokens of 8 heads behind 1357 9.8 / 10.6; head size 128, 50
+// tokens of 8 heads behind 39 8.6 / 7.4, 207 tokens of 4 behind 58 9.4 / 10.1, 17 of 2 behind 3201 12.6 / 14.7; head size 256, 4 groups of 2 heads,
+// 77 tokens 11.3 / 9.0, 113 11.1 / 10.6, 348 14.3 / 16.5, 8 groups of 4, 119 tokens behind 367 23 / 21, 76 of 2 behind 1925 23 / 43.
 static bool few_row_blocks(int G, int M, int d, int n_ctx, int num_cus) {
-    const long blocks = (long)G * ((M + 15) / 16);
-    if (n_ctx <= 32 || blocks > (d <= 64 ? 2 : 1) * num_cus) return false;
-    if (d > 128 && n_ctx > 768 * (num_cus / blocks)) return false;
-    return blocks * ((n_ctx + 63) / 64) <= (d <= 128 ? 1200 : 2100);
+    const long blocks = (long)G * ((M + 15) / 16), steps = (n_ctx + 63) / 64;
+    if ((n_ctx <= 32 && (d <= 128 || M <= 32)) || blocks > (d <= 64 ? 2 : 1) * num_cus) return false;
+    if (d <= 64) return blocks * steps <= (steps <= 9 ? 2500 : 1100);
+    return steps <= 3 || (steps <= 16 && blocks * steps <= (d <= 128 ? 250 : 160));
 }
 
 // Workgroups per block of 16 query rows and KV head: the estimated time (us) of the walk and the combination.
@@ -938,6 +965,54 @@ static bool prefill_may_chunk(int G, int M, int num_cus) {
     const long wgs = (long)((M + 127) / 128) * G;
     const int forced = tuning().attn_chunks;
     return forced >= 0 ? forced != 0 : wgs <= num_cus;
+}
+
+// Prefill: wavefronts that share a walk (returned) and chunks of the walks (a.chunk_steps, a.block_rows), the combination with
+// the shortest estimated time (us).  Stages a workgroup takes one after the other: `longest` for the last one to finish,
+// `total` per compute unit.  Per stage: alone on its compute unit / as one of two (times two: head size 256 has the unit for itself); fixed: before the first and
+// behind the last stage.  Chunks cost a second launch and the partial results, written and read.  Fitted to, and chosen like this
+// within 6 % (few of them 10 to 15) of the best combination, 17 to 8192 tokens behind 0 to 6000 positions, 2 to 8 groups of 1 to 4 heads of 64, 128 and 256.
+static int plan_prefill(AttnArgs &a, int d, int num_cus) {
+    const int forced_shares = tuning().attn_shares, forced_chunks = tuning().attn_chunks;
+    const bool may_chunk = prefill_may_chunk(a.groups, a.M, num_cus);
+    const float alone[2] = {d <= 64 ? 0.43f : d <= 128 ? 0.58f : 1.15f, d <= 64 ? 0.45f : d <= 128 ? 0.65f : 1.37f};
+    const float busy[2] = {d <= 64 ? 0.50f : d <= 128 ? 0.79f : 1.15f, d <= 64 ? 0.52f : d <= 128 ? 0.95f : 1.37f};
+    const float shared[2] = {d <= 64 ? 0.40f : d <= 128 ? 0.57f : 1.15f, d <= 64 ? 0.44f : d <= 128 ? 0.63f : 1.5f};
+    const float fixed[2] = {d <= 128 ? 4.0f : 6.0f, d <= 128 ? 4.5f : 7.0f};
+    const long slots = (long)num_cus * (d <= 128 ? 2 : 1);
+    const int exactly = forced_chunks > kPrefillMaxChunks ? kPrefillMaxChunks : forced_chunks;  // (from 2 on)
+    const float second = fminf(7.0f, 2.5f + (float)((long)a.groups * a.M) / 520.0f);  // the second launch
+    int best = 0;
+    float best_us = 0.0f;
+    for (int ps = 1; ps <= 2; ++ps) {
+        if (forced_shares > 0 && ps != forced_shares) continue;
+        const int rows = 128 / ps, nblocks = (a.M + rows - 1) / rows, longest = prefill_steps(a, nblocks - 1, rows);
+        if (best == 0) best = ps, best_us = 1e30f, a.block_rows = rows, a.chunk_steps = 0;
+        int last_len = 0;
+        for (const int k : {1, 2, 3, 4, 6, 8}) {
+            if (exactly > 1 ? k != exactly : exactly == 1 ? k == 1 : k > 1 && (!may_chunk || best_us < fixed[ps - 1] + second + 4.0f * alone[ps - 1])) continue;
+            const int len = ((longest + k - 1) / k + ps - 1) / ps * ps;
+            if (len == last_len || (k > 1 && (len < 4 || len >= longest))) continue;
+            last_len = len;
+            long items = 0, total = 0;
+            double partial_bytes = 0.0;
+            for (int j = 0; j < nblocks; ++j) {
+                const int steps = prefill_steps(a, j, rows), c = (steps + len - 1) / len;
+                items += c;
+                total += (steps + ps - 1) / ps;
+                if (c > 1) partial_bytes += (double)rows * c * d * 8.0 * a.groups;
+            }
+            if (k > 1 && items * a.groups > slots && forced_chunks <= 0) break;  // (a second round of chunks)
+            const float per_cu = (float)items * (float)a.groups / (float)num_cus, stages = (float)(len / ps);
+            float us = fixed[ps - 1];
+            if (k > 1)
+                us += (per_cu > 1.0f ? 2.0f * shared[ps - 1] : alone[ps - 1]) * stages + second + (float)(partial_bytes / 7.0e6);
+            else
+                us += fmaxf((per_cu > 1.0f ? busy : alone)[ps - 1] * stages, shared[ps - 1] * (float)total * (float)a.groups / (float)num_cus);
+            if (us < best_us) best = ps, best_us = us, a.block_rows = rows, a.chunk_steps = k > 1 ? len : 0;
+        }
+    }
+    return best;
 }
 
 size_t attn_prefill_workspace(int G, int M, int d, int num_cus) {
@@ -995,65 +1070,10 @@ hipError_t launch_attention(const void *q, const void *kc, const void *vc, int G
     a.C = C;
     a.n_ctx = n_ctx;
     a.splits = tuning().attn_splits > 0 ? (int)tuning().attn_splits : attn_splits(G, d, n_ctx, num_cus);
-    a.num_cus = num_cus > 0 ? num_cus : 1;
-    {
-        const long wgs = (long)((a.M + 127) / 128) * G;
-        const int forced = tuning().attn_pair;
-        a.pair = forced >= 0 ? forced : (wgs > 2L * a.num_cus ? 1 : 0);
-        // fewer blocks than compute units: cut the walks into chunks (at most kPrefillMaxChunks per
-        // block, at least 4 steps each) that fill the chip in one batch
-        a.chunk_steps = 0;
-        a.max_chunks = kPrefillMaxChunks;
-        if (a.M > 16 && prefill_may_chunk(G, a.M, a.num_cus)) {
-            const int nblocks = (a.M + 127) / 128;
-            long steps_total = 0;
-            int longest = 0;
-            for (int j = 0; j < nblocks; ++j) {
-                const int last = (j * 128 + 127 < a.M - 1) ? j * 128 + 127 : a.M - 1;
-                const int nbj = (n_ctx - S + last / g + 1 + 31) / 32;
-                steps_total += nbj;
-                if (nbj > longest) longest = nbj;
-            }
-            // the shortest chunk length whose chunks are all resident at once (two workgroups per
-            // compute unit up to head size 128, one above)
-            const long slots = (long)a.num_cus * (d <= 128 ? 2 : 1);
-            long len = (steps_total * G + slots - 1) / slots;
-            const int floor_len = (longest + kPrefillMaxChunks - 1) / kPrefillMaxChunks;
-            if (len < floor_len) len = floor_len;
-            if (len < 4) len = 4;
-            for (; len < longest; ++len) {
-                long total = 0;
-                for (int j = 0; j < nblocks; ++j) {
-                    const int last = (j * 128 + 127 < a.M - 1) ? j * 128 + 127 : a.M - 1;
-                    const int nbj = (n_ctx - S + last / g + 1 + 31) / 32;
-                    total += (nbj + len - 1) / len;
-                }
-                if (total * G <= slots) break;
-            }
-            if (len < longest) {  // else every block is one chunk anyway
-                // Worth it?  The launch ends with its longest walk: chunks save (longest - len) steps
-                // of a workgroup (measured: about 0.6 / 0.9 / 1.4 us per step at head size 64 / 128 /
-                // 256) and cost a second launch plus the partial results written and read again
-                // (taken at 4 TB/s).  Many query heads per KV head with short heads lose, few heads
-                // with long ones (one step is twice the work) win by up to 2x.
-                double partial_bytes = 0.0;
-                for (int j = 0; j < nblocks; ++j) {
-                    const int last = (j * 128 + 127 < a.M - 1) ? j * 128 + 127 : a.M - 1;
-                    const int nbj = (n_ctx - S + last / g + 1 + 31) / 32;
-                    const long cj = (nbj + len - 1) / len;
-                    if (cj > 1) partial_bytes += (double)(last - j * 128 + 1) * cj * (d + 2) * 8.0;
-                }
-                partial_bytes *= G;
-                const double step_us = d <= 64 ? 0.6 : d <= 128 ? 0.9 : 1.4;
-                const double gain_us = (double)(longest - len) * step_us;
-                const double cost_us = 3.0 + partial_bytes / 4.0e6;
-                if (tuning().attn_chunks > 0 || gain_us > 1.2 * cost_us) {
-                    a.chunk_steps = (int)len;
-                    a.pair = 0;
-                }
-            }
-        }
-    }
+    if (num_cus < 1) num_cus = 1;
+    a.groups = G;
+    a.max_chunks = kPrefillMaxChunks;
+    const int shares = a.M > 16 ? plan_prefill(a, d, num_cus) : 1;
     a.scale = 1.4426950408889634f / sqrtf((float)d);  // scores in units of log 2
     a.ws_o = static_cast<float *>(workspace);
     a.ws_ml = a.ws_o + (size_t)G * (a.M > 16 ? kPrefillMaxChunks : kAttnMaxSplits) * a.M * d;
@@ -1061,18 +1081,18 @@ hipError_t launch_attention(const void *q, const void *kc, const void *vc, int G
     bool few = a.M <= 16;
     if (!few) {
         const int forced = tuning().attn_few;
-        few = forced >= 0 ? forced != 0 : few_row_blocks(G, a.M, d, n_ctx, a.num_cus);
+        few = forced >= 0 ? forced != 0 : few_row_blocks(G, a.M, d, n_ctx, num_cus);
         if (few) {  // partial results fit the workspace of the chunks
             const int most = prefill_may_chunk(G, a.M, num_cus) ? kPrefillMaxChunks : 1;
-            if (tuning().attn_splits == 0) a.splits = row_block_splits(G, a.M, d, n_ctx, a.num_cus);
+            if (tuning().attn_splits == 0) a.splits = row_block_splits(G, a.M, d, n_ctx, num_cus);
             if (a.splits > most) a.splits = most;
         }
     }
     if (!few) {
         switch (d) {
-            case 64: return launch_attn_prefill<64>(a, G, st);
-            case 128: return launch_attn_prefill<128>(a, G, st);
-            case 256: return launch_attn_prefill<256>(a, G, st);
+            case 64: return shares == 1 ? launch_attn_prefill<64, 1>(a, st) : launch_attn_prefill<64, 2>(a, st);
+            case 128: return shares == 1 ? launch_attn_prefill<128, 1>(a, st) : launch_attn_prefill<128, 2>(a, st);
+            case 256: return shares == 1 ? launch_attn_prefill<256, 1>(a, st) : launch_attn_prefill<256, 2>(a, st);
             default: return hipErrorInvalidValue;
         }
     }

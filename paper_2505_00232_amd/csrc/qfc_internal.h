@@ -130,8 +130,8 @@ struct Tuning {
     Tunable gemv_max_row_tiles{0};  // 0: automatic (2 up to two token rows, 4 above)
     Tunable gemm_variant{0};
     Tunable act_quant_rows{0};  // 0: automatic
-    Tunable attn_chunks{-1};    // prefill attention, walks cut into chunks: -1 automatic, 0 never, 1 always
-    Tunable attn_pair{-1};      // prefill attention, two blocks per workgroup: -1 automatic, 0 never, 1 always
+    Tunable attn_chunks{-1};    // prefill attention, walks cut into chunks: -1 automatic, 0 never, 1 always, 2, 3, 4, 6, 8 into so many
+    Tunable attn_shares{0};     // prefill attention: wavefronts that share the walk of the same rows (0: automatic)
     Tunable skinny_waves{0};    // few token rows: most wavefronts per workgroup (0: automatic)
     Tunable skinny_row_tiles{0};  // few token rows: row tiles per workgroup (0: automatic)
     Tunable skinny_max_m{-1};   // largest M of those kernels (-1: automatic; 0: never)
@@ -189,6 +189,12 @@ __device__ __forceinline__ void wait_vmcnt() {
 __device__ __forceinline__ void copy16_to_lds(const void *base, uint32_t lane_offset, uint32_t lds_base) {
     asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(lane_offset), "s"(base), "s"(lds_base)
                  : "memory", "m0");
+}
+
+// The same with a constant added to the LDS address (one scalar instruction per copy).
+__device__ __forceinline__ void copy16_to_lds_at(const void *base, uint32_t lane_offset, uint32_t lds_base, int constant) {
+    asm volatile("s_add_u32 m0, %2, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(lane_offset), "s"(base), "s"(lds_base), "i"(constant)
+                 : "memory", "m0", "scc");
 }
 
 // Tile of workgroup `b` of a product, in an order whose neighbours run on one XCD (workgroups are dealt to the 8

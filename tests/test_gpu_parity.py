@@ -1383,6 +1383,45 @@ def test_attention_blocks_of_sixteen_query_rows(B, S, h_q, h_kv, d, C, n_ctx):
         assert bool((guard[G] == 9.0).all())
 
 
+@pytest.mark.parametrize("B,S,h_q,h_kv,d,C,n_ctx", [(1, 17, 1, 1, 64, 64, 33), (1, 64, 2, 1, 128, 64, 64), (1, 129, 3, 1, 64, 192, 161),
+                                                    (2, 43, 6, 2, 128, 640, 577), (1, 200, 4, 4, 256, 256, 200), (1, 33, 2, 1, 256, 640, 609),
+                                                    (1, 131, 8, 1, 128, 448, 419)])
+def test_attention_walks_shared_by_wavefronts(B, S, h_q, h_kv, d, C, n_ctx):
+    """Prefill with one or two wavefronts per walk, whole walks and walks in chunks: odd numbers of steps (a stage with one step
+    too many), walks of fewer steps than the pipeline has stages, last blocks of few rows; keys that grow along the walk, so
+    that the maximum moves in every step; a row of equal scores; everything past the context poisoned."""
+    print(f"attention shared walks B={B} S={S} h_q={h_q} h_kv={h_kv} d={d} n_ctx={n_ctx}", flush=True)
+    G, M = B * h_kv, S * (h_q // h_kv)
+    rng = np.random.default_rng(n_ctx * 29 + S)
+    q = rng.standard_normal((G, M, d)).astype(np.float16)
+    K = (rng.standard_normal((G, C, d)) * np.linspace(0.2, 1.5, C)[None, :, None]).astype(np.float16)
+    V = rng.standard_normal((G, d, C)).astype(np.float16)
+    q[:, M // 2] = 0
+    ref = oracle.attention(q, K, V, n_ctx, S)
+    K[:, n_ctx:] = np.float16(np.nan)
+    V[:, :, n_ctx:] = np.float16(np.nan)
+    shape = _attn_shape(B, h_q, h_kv, d, C)
+    ws = torch.empty(binding.qfc_attention_workspace_size(shape, S), dtype=torch.uint8, device=DEV)
+    qd, kd, vd = torch.from_numpy(q).to(DEV), torch.from_numpy(K).to(DEV), binding.vcache_physical(torch.from_numpy(V).to(DEV))
+    binding.qfc_tune(13, 0)
+    try:
+        for shares in (0, 1, 2):
+            for chunks in (-1, 0, 2, 3, 8):
+                guard = torch.full((G + 1, M, d), 9.0, dtype=torch.float16, device=DEV)
+                binding.qfc_tune(14, shares)
+                binding.qfc_tune(6, chunks)
+                binding.qfc_attention(qd, kd, vd, S, n_ctx, shape, ws, guard[:G])
+                torch.cuda.synchronize()
+                got = guard[:G].cpu().numpy()
+                assert np.all(np.isfinite(got)), (shares, chunks)
+                assert _E(got.reshape(G * M, d), ref.reshape(G * M, d)) <= TOL, (shares, chunks)
+                assert bool((guard[G] == 9.0).all())
+    finally:
+        binding.qfc_tune(13, -1)
+        binding.qfc_tune(14, 0)
+        binding.qfc_tune(6, -1)
+
+
 def test_attention_few_blocks_needs_the_larger_workspace():
     """Few blocks of query rows (fewer than compute units): the walks may be cut into chunks, whose
     partial results live in the workspace; the size query says how much, a smaller one is refused."""
