@@ -552,6 +552,44 @@ hipError_t i8_any(const SkinnyArgs &a, int num_cus, hipStream_t st) {
     return hipErrorInvalidValue;
 }
 
+// Estimated time in us with R row tiles per workgroup, fitted to a sweep over formats, 2304 to 28672 channels, K of 2048 to
+// 14336, 12 to 300 token rows in blocks of 16 to 64 and R of 1 to 8 (standard deviation 13 %).
+float estimate_us(const SkinnyArgs &a, int fmt, bool int8_activations, int R, int num_cus) {
+    const float l = load_per_cu(a, R, num_cus), k = 1e-3f * (float)a.K, r = (float)R, rows = (float)round_up(a.block_rows, 16);
+    const float load = fmaxf(1.0f, 0.5f * (l + ceilf(l)));
+    if (int8_activations) return load * (2.0f + 0.28f * r + k * (0.16f + 0.0118f * rows + (fmt == kW8C ? 0.23f : 0.08f) * r + 0.0023f * r * rows));
+    const float w = fmt == kW8C ? 0.27f : fmt == kW4G32 ? 0.24f : 0.13f;
+    return load * (1.9f + 0.45f * r + k * (0.21f + 0.0148f * rows + w * r + 0.0031f * r * rows));
+}
+
+// Equal blocks of whole tiles of 16 token rows (one block: all of them)
+void cut_rows(SkinnyArgs &a, int blocks) {
+    a.block_rows = round_up((a.M + blocks - 1) / blocks, blocks > 1 ? 16 : 1);
+    a.blocks = (a.M + a.block_rows - 1) / a.block_rows;
+}
+
+// Blocks the token rows are cut into: as few as there can be, or more of 48, 32 or 16 rows where that is estimated to save a
+// twentieth.  Every compute unit pulls its block of x through its vector cache; a layer of few row tiles leaves
+// compute units idle, or gives each one row tile for up to 64 rows, and more blocks with more row tiles each pull fewer bytes:
+// x falls with the blocks, weights (once per block, from the XCD's L2) rise.  us, fewest blocks / like this:
+// int4 groups, binary16  4096 x 14336 64 rows 28.4 / 22.7; 2304 x 9216 77 rows 17.4 / 15.2, 128 20.6 / 17.7, 200 24.4 / 21.4
+// int8, binary16         2304 x 9216 77 rows 19.1 / 16.3, 200 26.3 / 23.1
+// int8 x int8            2304 x 9216 48 rows 13.0 / 10.8, 77 14.7 / 12.8; 6144 x 4096 64 rows 10.9 / 10.1
+// int8 x int4            4096 x 14336 20 rows 13.6 / 12.1, 64 19.2 / 15.3; 6144 x 4096 64 rows 9.3 / 7.7; 2304 x 9216 77 rows 11.9 / 9.3
+// (none slower by more than 3 %; wide layers keep the fewest blocks: 28672 x 4096 int4 groups, 64 rows 30.9 / 34.9 with two.)
+void choose_blocks(SkinnyArgs &a, int fmt, bool int8_activations, int num_cus) {
+    if (tuning().skinny_blocks > 0) return;
+    const SkinnyArgs fewest = a;
+    float limit = 0.95f * estimate_us(a, fmt, int8_activations, row_tiles_for(a, fmt, int8_activations, num_cus), num_cus);
+    for (const int rows : {48, 32, 16}) {
+        SkinnyArgs b = fewest;
+        cut_rows(b, (a.M + rows - 1) / rows);
+        if (b.blocks <= fewest.blocks) continue;
+        const float us = estimate_us(b, fmt, int8_activations, row_tiles_for(b, fmt, int8_activations, num_cus), num_cus);
+        if (us < limit) a = b, limit = us;
+    }
+}
+
 SkinnyArgs make_args(const Geometry &g, const void *packed, const void *x, const float *sx, int M, void *out,
                      const void *residual, int gated_act) {
     SkinnyArgs a;
@@ -569,11 +607,8 @@ SkinnyArgs make_args(const Geometry &g, const void *packed, const void *x, const
     a.RT = g.RT;
     a.rt_stride = g.rt_stride;
     a.steps_q = a.steps_rem = 0;
-    // equal blocks of at most 64 token rows, whole tiles of 16
-    a.blocks = (M + kSkinnyRows - 1) / kSkinnyRows;
-    if (tuning().skinny_blocks > a.blocks) a.blocks = tuning().skinny_blocks;
-    a.block_rows = round_up((M + a.blocks - 1) / a.blocks, a.blocks > 1 ? 16 : 1);
-    a.blocks = (M + a.block_rows - 1) / a.block_rows;
+    const int fewest = (M + kSkinnyRows - 1) / kSkinnyRows, forced = tuning().skinny_blocks;
+    cut_rows(a, forced > fewest ? forced : fewest);
     a.sw_mul = 1.0f;
     a.gated_act = g.pair_half ? gated_act : -1;
     return a;
@@ -667,7 +702,8 @@ int skinny_tail_rows(const Geometry &g, int M, bool gated, int num_cus) {
 
 hipError_t launch_skinny_f16(const Geometry &g, const void *packed, const void *x, int M, void *y, const void *residual,
                              int gated_act, int num_cus, hipStream_t st) {
-    const SkinnyArgs a = make_args(g, packed, x, nullptr, M, y, residual, gated_act);
+    SkinnyArgs a = make_args(g, packed, x, nullptr, M, y, residual, gated_act);
+    choose_blocks(a, g.fmt, false, num_cus);
     if (g.fmt == kW8C) return f16_any<kW8C>(a, num_cus, st);
     return g.fmt == kW4C ? f16_any<kW4C>(a, num_cus, st) : f16_any<kW4G32>(a, num_cus, st);
 }
@@ -675,6 +711,7 @@ hipError_t launch_skinny_f16(const Geometry &g, const void *packed, const void *
 hipError_t launch_skinny_i8(const Geometry &g, const void *packed, const int8_t *xq_tiled, const float *sx, int M,
                             void *y, const void *residual, int gated_act, int num_cus, hipStream_t st) {
     SkinnyArgs a = make_args(g, packed, xq_tiled, sx, M, y, residual, gated_act);
+    choose_blocks(a, g.fmt, true, num_cus);
     if (g.fmt == kW4C) {
         a.sw_mul = 0.0625f;
         return i8_any<true>(a, num_cus, st);

@@ -1875,6 +1875,35 @@ def test_blocks_of_token_rows_match_oracle(fmt, mode, M, N, K, row_tiles, blocks
 
 @pytest.mark.parametrize("fmt,mode", [("w4g32", None), ("w4c", None), ("w8c", binding.QFC_COMPUTE_FP16_DEQUANT),
                                       ("w8c", None), ("w4c", binding.QFC_COMPUTE_INT8_ACT)])
+@pytest.mark.parametrize("N,K", [(645, 4128), (2304, 1024)])
+def test_narrow_layers_in_more_blocks_than_needed(fmt, mode, N, K):
+    """Layers of few row tiles, whose token rows the library cuts into blocks of 16 to 48 by itself: numbers of rows whose last
+    block is one row, nearly full or full."""
+    wq, s = synth.weights(6400, N, K, synth.FC("t", K, N, fmt))
+    layer = _layer(wq, s, fmt, max_m=144, mode=mode)
+    int8 = mode == binding.QFC_COMPUTE_INT8_ACT or (fmt == "w8c" and mode is None)
+    for M in (17, 31, 33, 48, 64, 65, 97, 144):
+        print(f"narrow layer {fmt} mode={mode} N={N} K={K} M={M}", flush=True)
+        x = synth.activations(6400, M, N, M, K)
+        guard = torch.full((M + 1, N), 77.0, dtype=torch.float16, device=DEV)
+        binding.qfc_forward(layer.handle, torch.from_numpy(x).to(DEV), guard[:M])
+        y = guard[:M].cpu().numpy()
+        if int8:
+            assert _E(y, oracle.fc_int8_act(x, wq, s)[3]) <= TOL, M
+            binding.qfc_tune(9, 0)
+            try:
+                large = _forward(layer, x)
+            finally:
+                binding.qfc_tune(9, -1)
+            assert np.array_equal(y.view(np.uint16), np.asarray(large).view(np.uint16)), M
+        else:
+            assert _E(y, oracle.fc_weight_only(x, wq, s, _group(fmt))) <= TOL, M
+        assert bool((guard[M] == 77.0).all()), M
+    layer.close()
+
+
+@pytest.mark.parametrize("fmt,mode", [("w4g32", None), ("w4c", None), ("w8c", binding.QFC_COMPUTE_FP16_DEQUANT),
+                                      ("w8c", None), ("w4c", binding.QFC_COMPUTE_INT8_ACT)])
 @pytest.mark.parametrize("N,K", [(32512, 128), (32768, 160), (49152, 128), (65792, 96)])
 def test_wide_layers_of_few_token_rows(fmt, mode, N, K):
     """On both sides of the lines (numbers of rows and channels) between the kernels for few token rows and the tiles
