@@ -857,8 +857,7 @@ hipError_t launch_mode(const GemmI8Args &a, int num_cus, hipStream_t st) {
     // operands stay selectable for experiments.
     int variant = tuning().gemm_variant;
     if (variant == 0) {
-        const long big_tiles = (long)((a.N + 255) / 256) * ((a.M + 127) / 128);
-        variant = 4 * big_tiles >= 3L * num_cus ? 10 : 12;
+        variant = tiles_of_128_tokens(a.N, a.M, num_cus) ? 10 : 12;
     }
     switch (variant) {
         case 1: return launch_variant<256, 256, 1, 4, OUT_MODE>(a, st);
@@ -881,8 +880,7 @@ hipError_t launch_mode_w4(const GemmI8Args &a, int num_cus, hipStream_t st) {
     int variant = tuning().gemm_variant;
     const int stages = a.Kp / 128;
     if (variant == 0) {
-        const long big_tiles = (long)((a.N + 255) / 256) * ((a.M + 127) / 128);
-        variant = stages % 2 != 0 ? 20 : 4 * big_tiles >= 3L * num_cus ? 21 : 23;
+        variant = stages % 2 != 0 ? 20 : tiles_of_128_tokens(a.N, a.M, num_cus) ? 21 : 23;
     }
     switch (variant) {
         case 21: return launch_dw4<4, 2, 4, OUT_MODE>(a, st);

@@ -642,22 +642,19 @@ static int tiles_up_to_k(const Geometry &g, int M, bool int8_activations, int nu
 
 // Which products these kernels take.  Up to 64 token rows: all but those.  More rows: the tiles of 64 or 128
 // tokens take the same time until they fill the chip, and long (they leave most of it idle); here the
-// rows are cut into blocks of 64, with the time growing with their number.  Both times are estimated
-// (us; fitted to layers of 1024 to 28672 channels, K of 2048 to 14336, 77 to 1000 rows, within about 20 %):
-//   here   load x (2 + 0.9 R + K (0.35 + 0.0128 rows + 0.33 R) / 1000)    binary16 activations
-//          load x (2.5 + 0.5 R + K (0.25 + 0.0102 rows + (0.27 | 0.15) R) / 1000)   int8 x (int8 | int4)
-//   tiles  9 + 9.3 K / 1000 a round; 5 + (4.4 | 3.85) K / 1000
+// rows are cut into blocks, with the time growing with their number.  Both times are estimated: here see estimate_us, which is
+// 2 to 10 % high at 65 to 1024 rows of layers of 1500 to 28672 channels, K of 1024 to 14336 (hence the 1.05); tiles
+//   9 + 9.3 K / 1000 a round (binary16 activations); 4.5 + 4.85 K / 1000 and 4.8 + 4.1 K / 1000 (64 tokens, int8 x int8 and int4)
 // Measured (us, tiles / here): 4096 x 14336 int4, binary16 activations, 77 rows 131 / 24, 300 131 / 64, 512 133 / 75;
-// 2304 x 9216 int4 groups 77 rows 96 / 17, 300 98 / 26, 1000 98 / 84; 18432 x 2304 77 rows 31 / 22, 200 31 / 38;
-// int8 x int8 6144 x 4096 77 rows 26 / 11, 300 25 / 21, 512 25 / 29; int8 x int4 4096 x 14336 77 rows 60 / 17, 512 60 / 47.
+// 2304 x 9216 int4 groups 77 rows 96 / 15, 300 98 / 26, 1000 98 / 84; 18432 x 2304 77 rows 31 / 22, 200 31 / 38;
+// 11000 x 3008 300 rows 52 / 40; int8, binary16 18432 x 2304 150 rows 42 / 36, 14336 x 4096 640 rows 132 / 114;
+// int8 x int8  6144 x 4096 240 rows 25.4 / 19.5, 300 25.2 / 22.2, 500 25 / 31; 4096 x 14336 384 rows 73 / 59; 8192 x 2304 150 rows 17.9 / 13.5
+// int8 x int4  6144 x 4096 300 rows 21.4 / 17.4; 2304 x 9216 800 rows 44.7 / 34.6; 18432 x 2304 80 rows 15.5 / 13.4, 150 15.6 / 19.3
+// (over 13 such layers, 13 numbers of rows and all formats the choice is 0.5 % slower than the faster one of both).
 static float skinny_us(const Geometry &g, int M, bool int8_activations, bool gated, int num_cus) {
-    const SkinnyArgs a = make_args(g, nullptr, nullptr, nullptr, M, nullptr, nullptr, gated ? 0 : -1);
-    const int R = row_tiles_for(a, g.fmt, int8_activations, num_cus);
-    if (R == 0) return 1e9f;
-    const float k = 1e-3f * (float)g.K, rows = (float)a.block_rows, r = (float)R;
-    const float load = fmaxf(1.0f, 0.95f * load_per_cu(a, R, num_cus));
-    if (!int8_activations) return load * (2.0f + 0.9f * r + k * (0.35f + 0.0128f * rows + 0.33f * r));
-    return load * (2.5f + 0.5f * r + k * (0.25f + 0.0102f * rows + (g.fmt == kW8C ? 0.27f : 0.15f) * r));
+    SkinnyArgs a = make_args(g, nullptr, nullptr, nullptr, M, nullptr, nullptr, gated ? 0 : -1);
+    choose_blocks(a, g.fmt, int8_activations, num_cus);
+    return estimate_us(a, g.fmt, int8_activations, row_tiles_for(a, g.fmt, int8_activations, num_cus), num_cus);
 }
 
 static float tile_round_us(const Geometry &g) { return 9.0f + 9.3e-3f * (float)g.K; }  // (binary16 activations)
@@ -668,18 +665,20 @@ bool skinny_product(const Geometry &g, int M, bool int8_activations, bool gated,
     if (M <= kSkinnyRows) return g.K > tiles_up_to_k(g, M, int8_activations, num_cus);
     if (M > kSkinnyMaxM) return false;
     const float here = skinny_us(g, M, int8_activations, gated, num_cus);
-    const long n256 = (g.N + 255) / 256, m128 = (M + 127) / 128, m64 = (M + 63) / 64;
+    const long n256 = (g.N + 255) / 256, m128 = (M + 127) / 128;
     if (!int8_activations) {
         const bool staged = g.fmt == kW8C || g.K % 128 != 0;  // 128 x 128 tiles, two workgroups per compute unit
         const float rounds = staged ? fmaxf(1.0f, (float)((g.N + 127) / 128 * m128) / (float)num_cus) : ceilf((float)(n256 * m128) / (float)num_cus);
         // (8-bit weights, the largest layers of long K: `here` is low by 25 to 40 %, which smaller ones can spare; 32768 x 14336
         // 65 rows 178 / 165, 18529 x 12160 277 rows 233 / 227; 25698 x 10368 129 rows 142 / 182, 128256 x 4096 130 rows 271 / 293)
         const bool low = g.fmt == kW8C && g.K >= 8192 && (long)g.N * g.K > 200L << 20;
-        return here < (low ? 0.88f : 1.0f) * rounds * tile_round_us(g);
+        return here < (low ? 0.88f : 1.05f) * rounds * tile_round_us(g);
     }
-    const bool wide = 4 * n256 * m128 >= 3L * num_cus;  // (their choice between 128 and 64 tokens)
-    const float tiles = 5.0f + (g.fmt == kW8C ? 4.4e-3f : 3.85e-3f) * (float)g.K;
-    return here < 0.9f * tiles * (wide ? fmaxf(1.25f, 1.6f * (float)(n256 * m128) / (float)num_cus) : fmaxf(1.0f, 0.7f * (float)(n256 * m64) / (float)num_cus));
+    const float k = 1e-3f * (float)g.K;
+    const bool w8 = g.fmt == kW8C;
+    const float tiles = tiles_of_128_tokens(g.N, M, num_cus) ? (w8 ? 6.5f + 5.8f * k : 6.0f + 5.2f * k) * fmaxf(1.0f, 1.1f * (float)(n256 * m128) / (float)num_cus)
+                                                             : (w8 ? 4.5f + 4.85f * k : 4.8f + 4.1f * k);
+    return here < 1.05f * tiles;
 }
 
 // Binary16 activations, 256 x 128 tiles, one workgroup per compute unit: a last round of few tiles costs as much as a
