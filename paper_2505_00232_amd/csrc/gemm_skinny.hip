@@ -644,13 +644,13 @@ static int tiles_up_to_k(const Geometry &g, int M, bool int8_activations, int nu
 // tokens take the same time until they fill the chip, and long (they leave most of it idle); here the
 // rows are cut into blocks, with the time growing with their number.  Both times are estimated: here see estimate_us, which is
 // 2 to 10 % high at 65 to 1024 rows of layers of 1500 to 28672 channels, K of 1024 to 14336 (hence the 1.05); tiles
-//   9 + 9.3 K / 1000 a round (binary16 activations); 4.5 + 4.85 K / 1000 and 4.8 + 4.1 K / 1000 (64 tokens, int8 x int8 and int4)
+//   9 + 9.3 K / 1000 a round (binary16 activations, 256 x 128), 10 + 10.3 K / 1000 (128 x 128); 4.5 + 4.85 K / 1000 and 4.8 + 4.1 K / 1000 (64 tokens, int8 x int8 and int4)
 // Measured (us, tiles / here): 4096 x 14336 int4, binary16 activations, 77 rows 131 / 24, 300 131 / 64, 512 133 / 75;
 // 2304 x 9216 int4 groups 77 rows 96 / 15, 300 98 / 26, 1000 98 / 84; 18432 x 2304 77 rows 31 / 22, 200 31 / 38;
 // 11000 x 3008 300 rows 52 / 40; int8, binary16 18432 x 2304 150 rows 42 / 36, 14336 x 4096 640 rows 132 / 114;
 // int8 x int8  6144 x 4096 240 rows 25.4 / 19.5, 300 25.2 / 22.2, 500 25 / 31; 4096 x 14336 384 rows 73 / 59; 8192 x 2304 150 rows 17.9 / 13.5
 // int8 x int4  6144 x 4096 300 rows 21.4 / 17.4; 2304 x 9216 800 rows 44.7 / 34.6; 18432 x 2304 80 rows 15.5 / 13.4, 150 15.6 / 19.3
-// (over 13 such layers, 13 numbers of rows and all formats the choice is 0.5 % slower than the faster one of both).
+// (over 13 such layers, 13 numbers of rows and all formats the choice is 1 % slower than the faster one of both).
 static float skinny_us(const Geometry &g, int M, bool int8_activations, bool gated, int num_cus) {
     SkinnyArgs a = make_args(g, nullptr, nullptr, nullptr, M, nullptr, nullptr, gated ? 0 : -1);
     choose_blocks(a, g.fmt, int8_activations, num_cus);
@@ -667,12 +667,13 @@ bool skinny_product(const Geometry &g, int M, bool int8_activations, bool gated,
     const float here = skinny_us(g, M, int8_activations, gated, num_cus);
     const long n256 = (g.N + 255) / 256, m128 = (M + 127) / 128;
     if (!int8_activations) {
-        const bool staged = g.fmt == kW8C || g.K % 128 != 0;  // 128 x 128 tiles, two workgroups per compute unit
-        const float rounds = staged ? fmaxf(1.0f, (float)((g.N + 127) / 128 * m128) / (float)num_cus) : ceilf((float)(n256 * m128) / (float)num_cus);
+        if (g.fmt != kW8C && g.K % 128 == 0) return here < 1.05f * ceilf((float)(n256 * m128) / (float)num_cus) * tile_round_us(g);
+        // 128 x 128 tiles, two workgroups per compute unit; the second one's make a round a quarter longer at once
+        const float fill = (float)((g.N + 127) / 128 * m128) / (float)num_cus;
         // (8-bit weights, the largest layers of long K: `here` is low by 25 to 40 %, which smaller ones can spare; 32768 x 14336
         // 65 rows 178 / 165, 18529 x 12160 277 rows 233 / 227; 25698 x 10368 129 rows 142 / 182, 128256 x 4096 130 rows 271 / 293)
-        const bool low = g.fmt == kW8C && g.K >= 8192 && (long)g.N * g.K > 200L << 20;
-        return here < (low ? 0.88f : 1.05f) * rounds * tile_round_us(g);
+        if (g.fmt == kW8C && g.K >= 8192 && (long)g.N * g.K > 200L << 20) return here < 0.88f * fmaxf(1.0f, fill) * tile_round_us(g);
+        return here < 1.05f * (fill <= 1.0f ? 1.0f : fmaxf(1.25f, fill)) * (10.0f + 10.3e-3f * (float)g.K);
     }
     const float k = 1e-3f * (float)g.K;
     const bool w8 = g.fmt == kW8C;
