@@ -398,24 +398,35 @@ __global__ __launch_bounds__(256, D <= 128 ? 2 : 1) void attn_partial_kernel(Att
         mine[D + 1] = run_sum;
     }
     __syncthreads();
-    for (int e = threadIdx.x; e < rows * D; e += 256) {
-        const int mm = e / D, dd = e % D;
-        float mx = kNegBig;
-#pragma unroll
-        for (int w = 0; w < 4; ++w) mx = fmaxf(mx, lds[(size_t)w * 16 * PITCH + (size_t)mm * PITCH + D]);
-        float o = 0.0f, l = 0.0f;
+    // A thread takes four columns of a row: maxima, factors and sum once for the four.  Latency-bound where a workgroup has 16
+    // rows (us, one column per thread / four: 77 tokens, 8 heads on 4 of 256 values 9.3 / 7.5, 32 on 8 of 128 7.0 / 5.9; one token,
+    // 1280 positions 9.0 / 8.8 and 8.2 / 8.0 with the combination).
+    for (int e = threadIdx.x; e < rows * (D / 4); e += 256) {
+        const int mm = e / (D / 4), dd = 4 * (e % (D / 4));
+        const float *row = lds + (size_t)mm * PITCH;
+        float f[4], mx = kNegBig, l = 0.0f;
 #pragma unroll
         for (int w = 0; w < 4; ++w) {
-            const float *src = lds + (size_t)w * 16 * PITCH + (size_t)mm * PITCH;
-            const float f = __builtin_amdgcn_exp2f(src[D] - mx);
-            o += f * src[dd];
-            l += f * src[D + 1];
+            f[w] = row[(size_t)w * 16 * PITCH + D];
+            mx = fmaxf(mx, f[w]);
+        }
+        v4f o = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+            const v4f part_o = *reinterpret_cast<const v4f *>(row + (size_t)w * 16 * PITCH + dd);
+            f[w] = __builtin_amdgcn_exp2f(f[w] - mx);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) o[i] += f[w] * part_o[i];
+            l += f[w] * row[(size_t)w * 16 * PITCH + D + 1];
         }
         if (a.splits == 1) {
-            a.out[((size_t)G * a.M + row0 + mm) * D + dd] = (_Float16)(o / l);
+            h4 y;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) y[i] = (_Float16)(o[i] / l);
+            *reinterpret_cast<h4 *>(a.out + ((size_t)G * a.M + row0 + mm) * D + dd) = y;
         } else {
             const size_t p = ((size_t)G * a.splits + blockIdx.x) * a.M + row0 + mm;
-            a.ws_o[p * D + dd] = o;
+            *reinterpret_cast<v4f *>(a.ws_o + p * D + dd) = o;
             if (dd == 0) {
                 a.ws_ml[p * 2] = mx;
                 a.ws_ml[p * 2 + 1] = l;
