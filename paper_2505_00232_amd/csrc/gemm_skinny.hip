@@ -50,6 +50,7 @@ struct SkinnyArgs {
     int steps_q, steps_rem;  // 128-k steps per wavefront: steps_q, one more for the first steps_rem
     float sw_mul;            // int8 x 4-bit: sums are 16 times the definition's (see gemm_i8.hip)
     int gated_act;
+    int turned;  // int8: workgroups begin their k ranges at different steps
 };
 
 __device__ __forceinline__ h2 as_h2(uint32_t u) { return __builtin_bit_cast(h2, u); }
@@ -356,6 +357,8 @@ __global__ __launch_bounds__(MAXT) void skinny_i8_kernel(SkinnyArgs a) {
     const int t0 = wave * a.steps_q + min(wave, a.steps_rem);
     const int nt = a.steps_q + (wave < a.steps_rem ? 1 : 0);
     const int XT = a.Kp / 64;
+    const int first = a.turned ? rt0 / R / 8 % nt : 0;  // (whole row groups, so that token blocks still share weights in L2)
+    auto step = [&](int i) __attribute__((always_inline)) { return t0 + (i + first < nt ? i + first : i + first - nt); };
     // (a block's last tiles of 16 rows may lie past the rows there are: clamped, results dropped)
     const u32x4 *xtile[TB];
 #pragma unroll
@@ -382,7 +385,7 @@ __global__ __launch_bounds__(MAXT) void skinny_i8_kernel(SkinnyArgs a) {
         for (int tb = 0; tb < TB; ++tb) acc[r][tb] = v4i{0, 0, 0, 0};
 #pragma unroll
     for (int i = 0; i < D; ++i)
-        if (i < nt) load(i, t0 + i);
+        if (i < nt) load(i, step(i));
     for (int b = 0; b < nt; b += D) {
 #pragma unroll
         for (int i = 0; i < D; ++i) {
@@ -406,7 +409,7 @@ __global__ __launch_bounds__(MAXT) void skinny_i8_kernel(SkinnyArgs a) {
                             acc[r][tb] = __builtin_amdgcn_mfma_i32_16x16x64_i8(__builtin_bit_cast(v4i, xv[i][tb][v]), fw, acc[r][tb], 0, 0, 0);
                     }
                 }
-                if (b + i + D < nt) load(i, t0 + b + i + D);
+                if (b + i + D < nt) load(i, step(b + i + D));
             }
         }
     }
@@ -610,6 +613,7 @@ SkinnyArgs make_args(const Geometry &g, const void *packed, const void *x, const
     const int fewest = (M + kSkinnyRows - 1) / kSkinnyRows, forced = tuning().skinny_blocks;
     cut_rows(a, forced > fewest ? forced : fewest);
     a.sw_mul = 1.0f;
+    a.turned = 0;
     a.gated_act = g.pair_half ? gated_act : -1;
     return a;
 }
@@ -714,6 +718,12 @@ hipError_t launch_skinny_i8(const Geometry &g, const void *packed, const int8_t 
     choose_blocks(a, g.fmt, true, num_cus);
     if (g.fmt == kW4C) {
         a.sw_mul = 0.0625f;
+        // Row tiles a multiple of 32 KiB apart: with every workgroup at the same k the weight stream comes from few memory
+        // channels at a time.  us, same k / turned, 9 and 32 rows: 28672 x 4096 16.7 / 13.8 and 18.4 / 15.7, 20000 x 4096 11.4 / 10.2
+        // and 13.2 / 12.2, 65536 x 4096 25.7 / 24.2 and 30.6 / 28.3, 6144 x 4096 6.1 / 5.7 and 6.8 / 6.7, 22016 x 8192 18.1 / 17.5
+        // and 20.7 / 20.4; 64 rows level.  Other K level (28672 x 3072 1 % slower); 8-bit weights from 12 % faster (65536 x 4096)
+        // to 5 % slower (12288 x 4096): not turned.
+        a.turned = a.rt_stride % 32 == 0;
         return i8_any<true>(a, num_cus, st);
     }
     return i8_any<false>(a, num_cus, st);

@@ -1875,10 +1875,10 @@ def test_blocks_of_token_rows_match_oracle(fmt, mode, M, N, K, row_tiles, blocks
 
 @pytest.mark.parametrize("fmt,mode", [("w4g32", None), ("w4c", None), ("w8c", binding.QFC_COMPUTE_FP16_DEQUANT),
                                       ("w8c", None), ("w4c", binding.QFC_COMPUTE_INT8_ACT)])
-@pytest.mark.parametrize("N,K", [(645, 4128), (2304, 1024)])
+@pytest.mark.parametrize("N,K", [(645, 4128), (2304, 1024), (2100, 4096)])
 def test_narrow_layers_in_more_blocks_than_needed(fmt, mode, N, K):
     """Layers of few row tiles, whose token rows the library cuts into blocks of 16 to 48 by itself: numbers of rows whose last
-    block is one row, nearly full or full."""
+    block is one row, nearly full or full.  (K = 4096: with int4 codes and int8 activations workgroups begin at different k.)"""
     wq, s = synth.weights(6400, N, K, synth.FC("t", K, N, fmt))
     layer = _layer(wq, s, fmt, max_m=144, mode=mode)
     int8 = mode == binding.QFC_COMPUTE_INT8_ACT or (fmt == "w8c" and mode is None)
