@@ -21,6 +21,7 @@
 #include <type_traits>
 
 #include "qfc_internal.h"
+#include "attention_walk.h"
 
 namespace qfc {
 namespace {
@@ -515,11 +516,11 @@ struct PrefillCfg {
     static constexpr int RW = 4 / PS;           // wavefronts that own different rows
     static constexpr int ROWS = 32 * RW;        // query rows per workgroup
     static constexpr int NB = 6 * PS * KB <= (D <= 128 ? 48 : 96) * 1024 ? 3 : 2;  // LDS stages
-    static constexpr int CK = PS * KB / 4096;   // copies per wavefront and stage, of K and of V
+    static constexpr int COPIES = KB / 4096;    // copies per wavefront and step, of K and of V
     static constexpr int MERGE = PS > 1 ? 4 * ((D / 32) * 4096 + 256) : 0;  // bytes of the wavefronts' results
     static constexpr int RING = 2 * NB * PS * KB;
     static constexpr int LDS = RING > MERGE ? RING : MERGE;
-    static_assert(LDS <= (D <= 128 ? 80 : 160) * 1024 && 2 * CK * NB <= 63, "LDS, and the 6-bit counter of outstanding copies");
+    static_assert(LDS <= (D <= 128 ? 80 : 160) * 1024 && 2 * PS * COPIES * NB <= 63, "LDS, and the 6-bit counter of outstanding copies");
     __device__ static int swz(int p) { return D >= 128 ? (p & 15) : ((p >> 1) & 7); }
 };
 // maximum over the lanes l and l ^ 32
@@ -534,7 +535,7 @@ __global__ __launch_bounds__(256, D <= 128 ? 2 : 1) void attn_prefill_kernel(Att
     typedef PrefillCfg<D, PS> Cfg;
     constexpr int DJ = D / 16;  // MFMA steps along d of the score product
     constexpr int DT = D / 32;  // row tiles of O^T
-    constexpr int NB = Cfg::NB, CK = Cfg::CK, KB = Cfg::KB, RW = Cfg::RW;
+    constexpr int NB = Cfg::NB, KB = Cfg::KB, RW = Cfg::RW;
     constexpr int KP = DJ < 8 ? DJ : 8;  // K operands of a step requested during the step before
     extern __shared__ uint4 lds_raw[];
     char *const ldsb = reinterpret_cast<char *>(lds_raw);
@@ -566,10 +567,9 @@ __global__ __launch_bounds__(256, D <= 128 ? 2 : 1) void attn_prefill_kernel(Att
     // and drag the loop control and the copy addresses into vector registers)
     const int lo_full = __builtin_amdgcn_readfirstlane(a.n_ctx - a.S + min(r0, a.M - 1) / a.g + 1);  // positions every row of the wavefront sees
     const int nb_all = __builtin_amdgcn_readfirstlane(prefill_steps(a, block, Cfg::ROWS));
-    // the steps this workgroup takes: [sb, nb), in T stages
+    // the steps this workgroup takes: [sb, nb), in stages of PS
     const int sb = chunk * a.chunk_steps;
     const int nb = chunks > 1 ? min(nb_all, sb + a.chunk_steps) : nb_all;
-    const int T = (nb - sb + PS - 1) / PS;
     const int lim = min(real ? a.n_ctx - a.S + m / a.g + 1 : a.n_ctx, 32 * nb);  // end of the positions the lane's row sees in them
 
     // Q^T operand: lane (q, h) holds Q[m][16 j + 8 h .. + 7]
@@ -580,14 +580,13 @@ __global__ __launch_bounds__(256, D <= 128 ? 2 : 1) void attn_prefill_kernel(Att
         qf[j] = real ? *reinterpret_cast<const h8 *>(a.q + ((size_t)G * a.M + m) * D + 16 * j + 8 * h) : zero;
     }
 
-    // ---- copies.  Batch b = the K rows of stage b + 1 and the V blocks of stage b; the KiB pieces of a
-    // stage are dealt to the wavefronts in turn.  Both live in rings of NB stages.
+    // ---- copies: the KiB pieces of a step are dealt to the wavefronts in turn
     const char *kbase = reinterpret_cast<const char *>(a.kc + (size_t)G * a.C * D);
     const char *vbase = reinterpret_cast<const char *>(a.vc + (size_t)G * D * a.C);
     const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void *)lds_raw;
     constexpr int PP = KB / 1024;  // pieces per step
     static_assert(PP % 4 == 0, "the wavefronts' pieces of one round belong to the same step");
-    constexpr int NO = PP / 4;  // different pieces of a step a wavefront copies
+    constexpr int NO = Cfg::COPIES;
     uint32_t koffs[NO], voffs[NO];
 #pragma unroll
     for (int i = 0; i < NO; ++i) {
@@ -602,25 +601,21 @@ __global__ __launch_bounds__(256, D <= 128 ? 2 : 1) void attn_prefill_kernel(Att
         const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)x), hi = __builtin_amdgcn_readfirstlane((uint32_t)(x >> 32));
         return reinterpret_cast<const void *>(((uint64_t)hi << 32) | lo);
     };
-    // (BULK: the whole stage lies inside the walk.  Otherwise steps past its last copy that one again: within the cache, and masked.)
     const uint32_t lds_wave = __builtin_amdgcn_readfirstlane(lds0 + wave * 1024);
-    auto issue_k = [&](int t, int slot, auto bulk_c) __attribute__((always_inline)) {
-        const int first = sb + t * PS;
+    auto copy_k = [&](int t, int p, int to, int slot) __attribute__((always_inline)) {
+        const char *src = kbase + (size_t)(sb + t * PS + p) * KB;
 #pragma unroll
-        for (int i = 0; i < CK; ++i) {
-            const int p = i / NO, step = decltype(bulk_c)::value ? first + p : min(first + p, nb - 1);
-            copy16_to_lds_at(uniform(kbase + (size_t)step * KB), koffs[i % NO], lds_wave + slot * (PS * KB), 4096 * i);
-        }
+        for (int i = 0; i < NO; ++i) copy16_to_lds_at(uniform(src), koffs[i], lds_wave + slot * (PS * KB), to * KB + 4096 * i);
     };
-    auto issue_v = [&](int t, int slot, auto bulk_c) __attribute__((always_inline)) {
+    auto copy_v = [&](int t, int p, int to, int slot) __attribute__((always_inline)) {
         const int first = sb + t * PS;  // (even for PS = 2)
+        const char *src = PS == 2 ? vbase + (size_t)(first / 2) * (D * 128) + p * 64 : vbase + (size_t)(first / 2) * (D * 128) + (first & 1) * 64;
 #pragma unroll
-        for (int i = 0; i < CK; ++i) {
-            const int p = i / NO, step = decltype(bulk_c)::value ? first + p : min(first + p, nb - 1);
-            const char *src = PS == 2 && decltype(bulk_c)::value ? vbase + (size_t)(first / 2) * (D * 128) + p * 64
-                                                                 : vbase + (size_t)(step / 2) * (D * 128) + (step & 1) * 64;
-            copy16_to_lds_at(uniform(src), voffs[i % NO], lds_wave + (NB + slot) * (PS * KB), 4096 * i);
-        }
+        for (int i = 0; i < NO; ++i) copy16_to_lds_at(uniform(src), voffs[i], lds_wave + (NB + slot) * (PS * KB), to * KB + 4096 * i);
+    };
+    auto wait = [](auto n) __attribute__((always_inline)) {
+        // (one asm: the operand reads before it are issued before it, and none may be in flight when the barrier opens)
+        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(decltype(n)::value) : "memory");
     };
 
     // operand read offsets of this lane inside the rings
@@ -652,41 +647,29 @@ __global__ __launch_bounds__(256, D <= 128 ? 2 : 1) void attn_prefill_kernel(Att
         for (int e = 2; e < 16; e += 2) x = fmaxf(fmaxf(x, s[e]), s[e + 1]);
         return x;
     };
-    constexpr int CB = 2 * CK;  // copies of a batch
-    constexpr std::true_type kBulk;
-    constexpr std::false_type kEdge;
+    v16f sn;
+    h8 vf[DT][2], pv[2];
 
-    // ---- before the loop: the scores of stage 0
-    issue_k(0, 0, kEdge);
+    // ---- the walk (its order: attention_walk.h).  Before the loop: the scores of stage 0
+    auto first = [&]() __attribute__((always_inline)) {
 #pragma unroll
-    for (int b = 0; b < NB - 1; ++b) {  // (copies past the walk's end: into slots that nothing reads)
-        issue_k(b + 1, (b + 1) % NB, kEdge);
-        issue_v(b, b % NB, kEdge);
-    }
-    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"((NB - 1) * CB) : "memory");
+        for (int j = 0; j < DJ; ++j) {
+            const v16f zero = {0};
+            st = __builtin_amdgcn_mfma_f32_32x32x16_f16(read_k(j, 0), qf[j], j == 0 ? zero : st, 0, 0, 0);
+        }
+        if (32 * (sb + ps) + 32 > lo_full || sb + ps >= nb) mask(st, 32 * (sb + ps));
+        top = largest(st);
+    };
+    auto request_k = [&](int slot) __attribute__((always_inline)) {
 #pragma unroll
-    for (int j = 0; j < DJ; ++j) {
-        const v16f zero = {0};
-        st = __builtin_amdgcn_mfma_f32_32x32x16_f16(read_k(j, 0), qf[j], j == 0 ? zero : st, 0, 0, 0);
-    }
-    if (32 * (sb + ps) + 32 > lo_full || sb + ps >= nb) mask(st, 32 * (sb + ps));
-    top = largest(st);
-    // batch 0 is there, and K of stage 0 has been read by all
-    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"((NB - 2) * CB) : "memory");
-    if (NB - 1 < T) {
-        if (NB < T) issue_k(NB, 0, kEdge);
-        issue_v(NB - 1, NB - 1, kEdge);
-    }
-#pragma unroll
-    for (int j = 0; j < KP; ++j) kf[j] = read_k(j, 1 % NB);
-
-    // ---- one step per stage.  Scores of the next step first (their MFMAs run beside the exponentials of this one),
-    // then, behind the barrier that hands over the next stage, the second product (beside the rest of the exponentials and
-    // the next step's maximum).  BULK: the next step exists and no row of the wavefront masks any of it, and so does
-    // the batch to issue: branch-free but for the rescaling, with an order of MFMAs and vector instructions asked of the scheduler.
-    auto step = [&](int t, int slot, auto bulk_c) __attribute__((always_inline)) {
+        for (int j = 0; j < KP; ++j) kf[j] = read_k(j, slot);
+    };
+    // One step per stage.  Scores of the next step first (their MFMAs run beside the exponentials of this one), then, behind
+    // the barrier that hands over the next stage, the second product (beside the rest of the exponentials and the next step's
+    // maximum).  BULK: branch-free but for the rescaling, with an order of MFMAs and vector instructions asked of the scheduler.
+    auto head = [&](int t, int slot, int slot1, auto bulk_c, bool next) __attribute__((always_inline)) {
         constexpr bool BULK = decltype(bulk_c)::value;
-        const int k0 = 32 * (sb + t * PS + ps), slot1 = slot + 1 == NB ? 0 : slot + 1, slot2 = slot1 + 1 == NB ? 0 : slot1 + 1;
+        const int k0 = 32 * (sb + t * PS + ps);
         if (__any(top * a.scale > run_max)) {
             const float nm = fmaxf(run_max, both_halves_max(top) * a.scale), corr = __builtin_amdgcn_exp2f(run_max - nm);
             run_max = nm;
@@ -696,15 +679,13 @@ __global__ __launch_bounds__(256, D <= 128 ? 2 : 1) void attn_prefill_kernel(Att
 #pragma unroll
                 for (int e = 0; e < 16; ++e) acc[dt][e] *= corr;
         }
-        v16f sn;
-        if (BULK || t + 1 < T) {
+        if (next) {
 #pragma unroll
             for (int j = 0; j < DJ; ++j) {
                 const v16f zero = {0};
                 sn = __builtin_amdgcn_mfma_f32_32x32x16_f16(j < KP ? kf[j < KP ? j : 0] : read_k(j, slot1), qf[j], j == 0 ? zero : sn, 0, 0, 0);
             }
         }
-        h8 vf[DT][2];
 #pragma unroll
         for (int c = 0; c < 2; ++c)
 #pragma unroll
@@ -718,7 +699,6 @@ __global__ __launch_bounds__(256, D <= 128 ? 2 : 1) void attn_prefill_kernel(Att
                     for (int e = 0; e < 8; ++e)
                         if (k0 + 16 * c + 8 * h + e >= a.n_ctx) vf[dt][c][e] = (_Float16)0.0f;
         }
-        h8 pv[2];
         float sum4[4];
 #pragma unroll
         for (int e = 0; e < 16; ++e) {
@@ -729,21 +709,16 @@ __global__ __launch_bounds__(256, D <= 128 ? 2 : 1) void attn_prefill_kernel(Att
             pv[e >> 3][e & 7] = (_Float16)p;
         }
         run_sum += (sum4[0] + sum4[1]) + (sum4[2] + sum4[3]);
-        // the next batch has landed for everyone, and everyone has read this stage's V and the next one's K
-        // (one asm: the operand reads above are issued before it, and none may be in flight when the barrier opens)
-        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(BULK ? (NB - 2) * CB : 0) : "memory");
-        if (BULK || t + NB + 1 < T) issue_k(t + NB + 1, slot1, bulk_c);
-        if (BULK || t + NB < T) issue_v(t + NB, slot, bulk_c);
-        if (BULK || t + 2 < T) {
-#pragma unroll
-            for (int j = 0; j < KP; ++j) kf[j] = read_k(j, slot2);
-        }
+    };
+    auto tail = [&](int t, auto bulk_c, bool next) __attribute__((always_inline)) {
+        constexpr bool BULK = decltype(bulk_c)::value;
+        const int k1 = 32 * (sb + (t + 1) * PS + ps);  // first position of the next step
 #pragma unroll
         for (int c = 0; c < 2; ++c)
 #pragma unroll
             for (int dt = 0; dt < DT; ++dt) acc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_f16(vf[dt][c], pv[c], acc[dt], 0, 0, 0);
-        if (BULK || t + 1 < T) {
-            if (!BULK && (k0 + 32 * PS + 32 > lo_full || sb + (t + 1) * PS + ps >= nb)) mask(sn, k0 + 32 * PS);
+        if (next) {
+            if (!BULK && (k1 + 32 > lo_full || k1 >= 32 * nb)) mask(sn, k1);
             top = largest(sn);
             st = sn;
         }
@@ -765,17 +740,8 @@ __global__ __launch_bounds__(256, D <= 128 ? 2 : 1) void attn_prefill_kernel(Att
             }
         }
     };
-    // stages whose successor is unmasked for this wavefront, and inside the walk with all that is issued
     const int full = lo_full / 32 - 1 - sb - ps;  // (steps up to lo_full / 32 - 1 are unmasked)
-    const int bulk = min(full < 0 ? 0 : full / PS, T - NB - 1);
-    int t = 0;
-    for (; t + NB <= bulk; t += NB)
-#pragma unroll
-        for (int s = 0; s < NB; ++s) step(t + s, s, kBulk);
-    for (int slot = 0; t < T; ++t) {  // (t is a multiple of NB here)
-        step(t, slot, kEdge);
-        slot = slot + 1 == NB ? 0 : slot + 1;
-    }
+    prefill_walk<NB, PS, Cfg::COPIES>(nb - sb, full < 0 ? 0 : full / PS, copy_k, copy_v, wait, first, request_k, head, tail);
     run_sum += __shfl_xor(run_sum, 32, 64);
 
     // ---- the PS wavefronts of the same rows meet in LDS; each then finishes the d tiles dt = ps, ps + PS, ...

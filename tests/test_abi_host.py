@@ -146,3 +146,14 @@ def test_build_refuses_spills_in_kernels_with_hand_placed_loads():
     frag = build.NO_SPILL["gemm_i8.hip"]
     assert build._spilling_kernels(clean + other, frag) == []
     assert build._spilling_kernels(clean + bad + other, frag) == ["_ZN3qfc17gemm_i8_dw_kernelILi9ELi4ELi4ELi0ELb1EEEv"]
+
+
+def test_prefill_walk_copies_land_before_they_are_read_and_end_with_the_walk(tmp_path):
+    """The order in which the prefill attention kernel issues its copies, waits and reads, run on the host for every
+    instance's rings, 1 to 25 steps and any share of unmasked stages: no copy past the walk, no line in flight
+    more than twice, no slot overwritten while it is read or read before it is filled, nothing in flight at the end."""
+    exe = str(tmp_path / "attention_walk")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-w", "-D__host__=", "-D__device__=", "-D__forceinline__=inline", "-I", build.CSRC,
+                    os.path.join(ROOT, "tests", "attention_walk.cpp"), "-o", exe], check=True)
+    r = subprocess.run([exe], capture_output=True, text=True)
+    assert r.returncode == 0, r.stdout[-2000:]
