@@ -602,16 +602,16 @@ __global__ __launch_bounds__(256, D <= 128 ? 2 : 1) void attn_prefill_kernel(Att
         return reinterpret_cast<const void *>(((uint64_t)hi << 32) | lo);
     };
     const uint32_t lds_wave = __builtin_amdgcn_readfirstlane(lds0 + wave * 1024);
-    auto copy_k = [&](int t, int p, int to, int slot) __attribute__((always_inline)) {
+    auto copy_k = [&](int t, int p, int slot) __attribute__((always_inline)) {
         const char *src = kbase + (size_t)(sb + t * PS + p) * KB;
 #pragma unroll
-        for (int i = 0; i < NO; ++i) copy16_to_lds_at(uniform(src), koffs[i], lds_wave + slot * (PS * KB), to * KB + 4096 * i);
+        for (int i = 0; i < NO; ++i) copy16_to_lds_at(uniform(src), koffs[i], lds_wave + slot * (PS * KB), p * KB + 4096 * i);
     };
-    auto copy_v = [&](int t, int p, int to, int slot) __attribute__((always_inline)) {
+    auto copy_v = [&](int t, int p, int slot) __attribute__((always_inline)) {
         const int first = sb + t * PS;  // (even for PS = 2)
         const char *src = PS == 2 ? vbase + (size_t)(first / 2) * (D * 128) + p * 64 : vbase + (size_t)(first / 2) * (D * 128) + (first & 1) * 64;
 #pragma unroll
-        for (int i = 0; i < NO; ++i) copy16_to_lds_at(uniform(src), voffs[i], lds_wave + (NB + slot) * (PS * KB), to * KB + 4096 * i);
+        for (int i = 0; i < NO; ++i) copy16_to_lds_at(uniform(src), voffs[i], lds_wave + (NB + slot) * (PS * KB), p * KB + 4096 * i);
     };
     auto wait = [](auto n) __attribute__((always_inline)) {
         // (one asm: the operand reads before it are issued before it, and none may be in flight when the barrier opens)
@@ -713,10 +713,12 @@ __global__ __launch_bounds__(256, D <= 128 ? 2 : 1) void attn_prefill_kernel(Att
     auto tail = [&](int t, auto bulk_c, bool next) __attribute__((always_inline)) {
         constexpr bool BULK = decltype(bulk_c)::value;
         const int k1 = 32 * (sb + (t + 1) * PS + ps);  // first position of the next step
+        if (BULK || PS == 1 || k1 - 32 * PS < 32 * nb) {  // (a step that the last stage lacks: its V operands are anything)
 #pragma unroll
-        for (int c = 0; c < 2; ++c)
+            for (int c = 0; c < 2; ++c)
 #pragma unroll
-            for (int dt = 0; dt < DT; ++dt) acc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_f16(vf[dt][c], pv[c], acc[dt], 0, 0, 0);
+                for (int dt = 0; dt < DT; ++dt) acc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_f16(vf[dt][c], pv[c], acc[dt], 0, 0, 0);
+        }
         if (next) {
             if (!BULK && (k1 + 32 > lo_full || k1 >= 32 * nb)) mask(sn, k1);
             top = largest(sn);

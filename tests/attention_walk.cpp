@@ -29,14 +29,14 @@ Notes run(int steps, int unmasked, int ps) {
     Notes n;
     const int T = (steps + PS - 1) / PS;
     std::deque<size_t> flying;  // (one entry per step copied: COPIES instructions)
-    auto copy = [&](char kind, int t, int p, int to, int slot) {
+    auto copy = [&](char kind, int t, int p, int slot) {
         const int step = t * PS + p, same = 1 + (int)std::count_if(flying.begin(), flying.end(), [&](size_t i) {
             return n.copies[i].kind == kind && n.copies[i].step == step; });
         n.most_of_a_line = std::max(n.most_of_a_line, same);
         if (t >= T || step >= steps) printf("steps %d: a copy of step %d\n", steps, step), ++faults;
-        if (slot < 0 || slot >= NB || to < 0 || to >= PS) printf("steps %d: a copy into slot %d.%d\n", steps, slot, to), ++faults;
+        if (slot < 0 || slot >= NB || p < 0 || p >= PS) printf("steps %d: a copy into slot %d.%d\n", steps, slot, p), ++faults;
         flying.push_back(n.copies.size());
-        n.copies.push_back({kind, step, slot * PS + to, n.epochs, -1});
+        n.copies.push_back({kind, step, slot * PS + p, n.epochs, -1});
     };
     auto read = [&](char kind, int t, int slot) {
         const int step = t * PS + ps;
@@ -46,8 +46,8 @@ Notes run(int steps, int unmasked, int ps) {
     n.scored.assign(steps, 0), n.added.assign(steps, 0);
     auto count = [&](std::vector<int> &of, int t) { if (t * PS + ps < steps) ++of[t * PS + ps]; };
     qfc::prefill_walk<NB, PS, COPIES>(
-        steps, unmasked, [&](int t, int p, int to, int slot) { copy('K', t, p, to, slot); },
-        [&](int t, int p, int to, int slot) { copy('V', t, p, to, slot); },
+        steps, unmasked, [&](int t, int p, int slot) { copy('K', t, p, slot); },
+        [&](int t, int p, int slot) { copy('V', t, p, slot); },
         [&](auto left) {
             while (flying.size() * COPIES > (size_t)decltype(left)::value) n.copies[flying.front()].landed = n.epochs, flying.pop_front();
             ++n.epochs;
@@ -76,7 +76,7 @@ void check(int steps, const std::vector<int> &unmasked) {
         const int ps = i / (4 / PS);
         if (w[i].epochs != w[0].epochs) fault("another number of barriers", i);
         if (w[i].outstanding) fault("copies in flight behind the walk", i);
-        if (w[i].most_of_a_line > 2) fault("a line in flight more than twice", i);
+        if (w[i].most_of_a_line > 1 || w[i].copies.size() != 2 * (size_t)steps) fault("a step not copied exactly once", i);
         for (int s = 0; s < steps; ++s)
             if (w[i].scored[s] != (s % PS == ps) || w[i].added[s] != (s % PS == ps)) fault("a step not taken exactly once", i);
         for (const Read &r : w[i].reads)

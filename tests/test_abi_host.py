@@ -150,8 +150,8 @@ def test_build_refuses_spills_in_kernels_with_hand_placed_loads():
 
 def test_prefill_walk_copies_land_before_they_are_read_and_end_with_the_walk(tmp_path):
     """The order in which the prefill attention kernel issues its copies, waits and reads, run on the host for every
-    instance's rings, 1 to 25 steps and any share of unmasked stages: no copy past the walk, no line in flight
-    more than twice, no slot overwritten while it is read or read before it is filled, nothing in flight at the end."""
+    instance's rings, 1 to 25 steps and any share of unmasked stages: no copy past the walk, every step
+    copied once, no slot overwritten while it is read or read before it is filled, nothing in flight at the end."""
     exe = str(tmp_path / "attention_walk")
     subprocess.run(["g++", "-std=c++17", "-O1", "-w", "-D__host__=", "-D__device__=", "-D__forceinline__=inline", "-I", build.CSRC,
                     os.path.join(ROOT, "tests", "attention_walk.cpp"), "-o", exe], check=True)

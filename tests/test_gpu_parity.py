@@ -1422,6 +1422,46 @@ def test_attention_walks_shared_by_wavefronts(B, S, h_q, h_kv, d, C, n_ctx):
         binding.qfc_tune(6, -1)
 
 
+@pytest.mark.parametrize("S,h_q,h_kv,d,n_ctx,at", [(20, 2, 1, 64, 155, 135), (17, 6, 2, 128, 21, 4), (9, 4, 1, 256, 90, 81),
+                                                   (200, 1, 1, 64, 360, 199), (150, 2, 1, 128, 278, 140), (90, 4, 2, 256, 190, 110),
+                                                   (300, 2, 1, 128, 310, 20)])
+def test_attention_of_prompts_keeps_infinite_values(S, h_q, h_kv, d, n_ctx, at):
+    """Infinite values at position `at`: infinities in those columns of the rows that see it, all other columns as if they were not
+    there; walks of odd and even numbers of steps by one or two wavefronts, whole and in chunks, that end at `at` and behind it, at the
+    end of the context and before it."""
+    print(f"attention infinite values S={S} h_q={h_q} h_kv={h_kv} d={d} n_ctx={n_ctx} at={at}", flush=True)
+    g = h_q // h_kv
+    C, M = 448, S * g
+    rng = np.random.default_rng(n_ctx * 31 + S)
+    q = rng.standard_normal((h_kv, M, d)).astype(np.float16)
+    K = rng.standard_normal((h_kv, C, d)).astype(np.float16)
+    V = rng.standard_normal((h_kv, d, C)).astype(np.float16)
+    ref = oracle.attention(q, K, V, n_ctx, S)
+    V[:, 3, at], V[:, d - 1, at] = np.float16(np.inf), np.float16(-np.inf)
+    seen = max(0, at - (n_ctx - S)) * g  # first row that sees it
+    shape = _attn_shape(1, h_q, h_kv, d, C)
+    qd, kd, vd = torch.from_numpy(q).to(DEV), torch.from_numpy(K).to(DEV), binding.vcache_physical(torch.from_numpy(V).to(DEV))
+    rest = [c for c in range(d) if c not in (3, d - 1)]
+    wrong = []
+    binding.qfc_tune(13, 0)
+    try:
+        for shares, chunks in ((1, 0), (2, 0), (1, 2), (2, 2), (1, 3), (2, 3), (2, 8)):
+            binding.qfc_tune(14, shares)
+            binding.qfc_tune(6, chunks)
+            ws = torch.empty(binding.qfc_attention_workspace_size(shape, S), dtype=torch.uint8, device=DEV)
+            out = torch.empty((h_kv, M, d), dtype=torch.float16, device=DEV)
+            binding.qfc_attention(qd, kd, vd, S, n_ctx, shape, ws, out)
+            got = out.cpu().numpy()
+            if not (np.all(got[:, seen:, 3] == np.inf) and np.all(got[:, seen:, d - 1] == -np.inf) and np.all(np.isfinite(got[..., rest])) and
+                    _E(got[..., rest].reshape(h_kv * M, d - 2), ref[..., rest].reshape(h_kv * M, d - 2)) <= TOL):
+                wrong.append((shares, chunks))
+    finally:
+        binding.qfc_tune(13, -1)
+        binding.qfc_tune(14, 0)
+        binding.qfc_tune(6, -1)
+    assert wrong == []
+
+
 def test_attention_few_blocks_needs_the_larger_workspace():
     """Few blocks of query rows (fewer than compute units): the walks may be cut into chunks, whose
     partial results live in the workspace; the size query says how much, a smaller one is refused."""
