@@ -445,7 +445,8 @@ __global__ __launch_bounds__(64) void attn_combine_kernel(AttnArgs a) {
     const int col = 64 * blockIdx.z + lane;
     const size_t row0 = ((size_t)G * a.splits) * a.M + mm;  // partial row of split s: row0 + s * M
     // The first 32 splits' columns are requested before the factors are known (splits past the last read the last one
-    // again, their factor is 0): one trip to memory instead of one for the pairs and one for every eight splits.
+    // again and count as 0: their factor is 0, but the last one may be infinite): one trip to memory instead of one for the
+    // pairs and one for every eight splits.
     // us, walk and combination, before / after: 8 heads on 4 of 256 values, 1280 positions 8.7 / 8.0; 32 on 8 of 128, 1280 7.8 / 7.2,
     // 12001 17.1 / 16.0; head size 64, 4000 positions 8.4 / 7.6.
     float v[4][8];
@@ -476,7 +477,7 @@ __global__ __launch_bounds__(64) void attn_combine_kernel(AttnArgs a) {
         for (int k = 0; k < 4; ++k) {
             if (s + 8 * k >= a.splits) break;
 #pragma unroll
-            for (int u = 0; u < 8; ++u) o = fmaf(__shfl(f, s + 8 * k + u, 64), v[k][u], o);
+            for (int u = 0; u < 8; ++u) o = fmaf(__shfl(f, s + 8 * k + u, 64), s + 8 * k + u < a.splits ? v[k][u] : 0.0f, o);
             if (s + 8 * k + 32 < a.splits) fetch(k, s + 8 * k + 32);
         }
     }

@@ -1462,6 +1462,39 @@ def test_attention_of_prompts_keeps_infinite_values(S, h_q, h_kv, d, n_ctx, at):
     assert wrong == []
 
 
+@pytest.mark.parametrize("B,S,h_q,h_kv,d,n_ctx", [(1, 1, 8, 2, 64, 400), (2, 1, 32, 8, 128, 290), (1, 2, 4, 1, 256, 448), (1, 20, 4, 2, 128, 411)])
+def test_attention_of_few_rows_keeps_infinite_values(B, S, h_q, h_kv, d, n_ctx):
+    """The same at the first position of the last token and at position 0 for walks split over workgroups: any number of partial
+    results, of which the combination takes eight at a time."""
+    print(f"attention infinite values, few rows B={B} S={S} h_q={h_q} h_kv={h_kv} d={d} n_ctx={n_ctx}", flush=True)
+    C, G, M = 448, B * h_kv, S * (h_q // h_kv)
+    rng = np.random.default_rng(n_ctx * 37 + S)
+    q = rng.standard_normal((G, M, d)).astype(np.float16)
+    K = rng.standard_normal((G, C, d)).astype(np.float16)
+    V = rng.standard_normal((G, d, C)).astype(np.float16)
+    ref = oracle.attention(q, K, V, n_ctx, S)
+    V[:, 3, n_ctx - S], V[:, d - 1, 0] = np.float16(np.inf), np.float16(-np.inf)
+    shape = _attn_shape(B, h_q, h_kv, d, C)
+    qd, kd, vd = torch.from_numpy(q).to(DEV), torch.from_numpy(K).to(DEV), binding.vcache_physical(torch.from_numpy(V).to(DEV))
+    rest = [c for c in range(d) if c not in (3, d - 1)]
+    wrong = []
+    try:
+        for splits in (0, 1, 2, 3, 7):
+            binding.qfc_tune(12, splits)
+            binding.qfc_tune(13, 1)
+            ws = torch.empty(binding.qfc_attention_workspace_size(shape, S), dtype=torch.uint8, device=DEV)
+            out = torch.empty((G, M, d), dtype=torch.float16, device=DEV)
+            binding.qfc_attention(qd, kd, vd, S, n_ctx, shape, ws, out)
+            got = out.cpu().numpy()
+            if not (np.all(got[..., 3] == np.inf) and np.all(got[..., d - 1] == -np.inf) and np.all(np.isfinite(got[..., rest])) and
+                    _E(got[..., rest].reshape(G * M, d - 2), ref[..., rest].reshape(G * M, d - 2)) <= TOL):
+                wrong.append(splits)
+    finally:
+        binding.qfc_tune(12, 0)
+        binding.qfc_tune(13, -1)
+    assert wrong == []
+
+
 def test_attention_few_blocks_needs_the_larger_workspace():
     """Few blocks of query rows (fewer than compute units): the walks may be cut into chunks, whose
     partial results live in the workspace; the size query says how much, a smaller one is refused."""
