@@ -52,12 +52,17 @@ def _hipcc() -> str:
     raise RuntimeError("hipcc not found")
 
 
+def _deps() -> list[str]:
+    """What the library is built from: the sources, the public headers, and this file with its flags."""
+    include = os.path.join(HERE, "..", "include")
+    return [os.path.join(d, f) for d in (CSRC, include) for f in os.listdir(d)] + [os.path.abspath(__file__)]
+
+
 def _deps_newer(target: str) -> bool:
     if not os.path.exists(target):
         return True
     t = os.path.getmtime(target)
-    deps = [os.path.join(CSRC, f) for f in os.listdir(CSRC)] + [os.path.join(HERE, "..", "include", "qfc.h")]
-    return any(os.path.getmtime(d) > t for d in deps)
+    return any(os.path.getmtime(d) > t for d in _deps())
 
 
 def build(force: bool = False, verbose: bool = False) -> str:

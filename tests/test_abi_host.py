@@ -148,6 +148,19 @@ def test_build_refuses_spills_in_kernels_with_hand_placed_loads():
     assert build._spilling_kernels(clean + bad + other, frag) == ["_ZN3qfc17gemm_i8_dw_kernelILi9ELi4ELi4ELi0ELb1EEEv"]
 
 
+def test_build_sees_changes_of_its_flags_and_headers(tmp_path, monkeypatch):
+    """A library older than any source, public header or the build's own file is built again."""
+    include = os.path.join(ROOT, "include")
+    for changed in [build.__file__] + [os.path.join(include, f) for f in os.listdir(include)] + [os.path.join(build.CSRC, "attention_walk.h")]:
+        real = os.path.getmtime
+        newest = str(tmp_path / "lib")
+        open(newest, "w").close()
+        monkeypatch.setattr(build.os.path, "getmtime", lambda p: 3 if os.path.realpath(p) == os.path.realpath(changed) else 2 if p == newest else 1)
+        stale = build._deps_newer(newest)
+        monkeypatch.setattr(build.os.path, "getmtime", real)
+        assert stale, changed
+
+
 def test_prefill_walk_copies_land_before_they_are_read_and_end_with_the_walk(tmp_path):
     """The order in which the prefill attention kernel issues its copies, waits and reads, run on the host for every
     instance's rings, 1 to 25 steps and any share of unmasked stages: no copy past the walk, every step
