@@ -846,6 +846,21 @@ hipError_t launch_w4(GemmI8Args a, hipStream_t st) {
     return hipGetLastError();
 }
 
+// Tiles of 256 channels: 128 tokens each where those tiles are for three quarters of the compute units and more, or where tiles of
+// 64 would start a second round that costs more than the larger tiles' idle compute units.  With int8 weights it does at once (us, 64 /
+// 128 tokens: 18432 x 2304 240 rows, 288 tiles of 64, 31.3 / 23.8; 2304 x 9216 1826 rows, 261 tiles, 70 / 63, 2274 rows 80 / 63;
+// 11000 x 3008 500 rows 37.3 / 26.9), with int4 weights from a quarter of a round on (5120 x 9216 802 rows, 260 tiles, 52 / 56, 1152
+// rows, 360 tiles, 59 / 56; 1536 x 14336 2722 rows, 258 tiles, 82 / 88).  Outputs that are stored as they lie in the registers
+// (accumulators; rows that are no multiple of 16 bytes) take longer than the round from 128-token tiles: with int4 weights
+// always (4100 x 4096 1211 rows 34.9 / 38.7, 9001 x 1024 600 rows 26.0 / 31.8), with int8 weights below K of 4096 (4100 x 1024 1211 rows
+// 19.0 / 22.6, 9001 x 2304 600 rows 36.2 / 39.4, x 4096 52.7 / 49.1).
+bool tiles_of_128_tokens(const GemmI8Args &a, bool w4, bool staged_store, int num_cus) {
+    const long n256 = (a.N + 255) / 256, m128 = (a.M + 127) / 128, m64 = (a.M + 63) / 64;
+    if (4 * n256 * m128 >= 3L * num_cus) return true;
+    if (w4) return staged_store && 4 * n256 * m64 > 5L * num_cus;
+    return n256 * m64 > num_cus && (staged_store || a.Kp >= 4096);
+}
+
 template <int OUT_MODE>
 hipError_t launch_mode(const GemmI8Args &a, int num_cus, hipStream_t st) {
     // Tile shapes measured on MI355X.  The direct-weights kernel with the 256 x 128 tile is used
@@ -857,7 +872,7 @@ hipError_t launch_mode(const GemmI8Args &a, int num_cus, hipStream_t st) {
     // operands stay selectable for experiments.
     int variant = tuning().gemm_variant;
     if (variant == 0) {
-        variant = tiles_of_128_tokens(a.N, a.M, num_cus) ? 10 : 12;
+        variant = tiles_of_128_tokens(a, false, OUT_MODE == 0 && a.N % 8 == 0, num_cus) ? 10 : 12;
     }
     switch (variant) {
         case 1: return launch_variant<256, 256, 1, 4, OUT_MODE>(a, st);
@@ -880,7 +895,7 @@ hipError_t launch_mode_w4(const GemmI8Args &a, int num_cus, hipStream_t st) {
     int variant = tuning().gemm_variant;
     const int stages = a.Kp / 128;
     if (variant == 0) {
-        variant = stages % 2 != 0 ? 20 : tiles_of_128_tokens(a.N, a.M, num_cus) ? 21 : 23;
+        variant = stages % 2 != 0 ? 20 : tiles_of_128_tokens(a, true, OUT_MODE == 0 && a.N % 8 == 0, num_cus) ? 21 : 23;
     }
     switch (variant) {
         case 21: return launch_dw4<4, 2, 4, OUT_MODE>(a, st);

@@ -681,8 +681,9 @@ bool skinny_product(const Geometry &g, int M, bool int8_activations, bool gated,
     }
     const float k = 1e-3f * (float)g.K;
     const bool w8 = g.fmt == kW8C;
-    const float tiles = tiles_of_128_tokens(g.N, M, num_cus) ? (w8 ? 6.5f + 5.8f * k : 6.0f + 5.2f * k) * fmaxf(1.0f, 1.1f * (float)(n256 * m128) / (float)num_cus)
-                                                             : (w8 ? 4.5f + 4.85f * k : 4.8f + 4.1f * k);
+    const bool large = 4 * n256 * m128 >= 3L * num_cus || n256 * ((M + 63) / 64) > num_cus;  // tiles of 128 tokens, or two rounds of 64
+    const float tiles = large ? (w8 ? 6.5f + 5.8f * k : 6.0f + 5.2f * k) * fmaxf(1.0f, 1.1f * (float)(n256 * m128) / (float)num_cus)
+                              : (w8 ? 4.5f + 4.85f * k : 4.8f + 4.1f * k);
     return here < 1.05f * tiles;
 }
 

@@ -382,13 +382,6 @@ hipError_t launch_gemm_f16(const Geometry &g, const void *packed, const void *x,
 // Few token rows (9 .. kSkinnyMaxM, where they are the faster ones): see gemm_skinny.hip.  Arguments as the two launchers above.
 constexpr int kSkinnyRows = 64;  // token rows per workgroup at most
 constexpr int kSkinnyMaxM = 1024;
-// int8 activations, tiles of 256 channels: 128 tokens each where those tiles are for three quarters of the compute units and
-// more, or where tiles of 64 would start a second round (us, 64 / 128 tokens, int8 x int8: 18432 x 2304 240 rows, 288 tiles of
-// 64, 31.3 / 23.8; 11000 x 3008 500 rows 37.3 / 26.9; 14336 x 4096 384 rows 42.5 / 32.9; 150 rows, 168 tiles, 28 / 33).
-inline bool tiles_of_128_tokens(int N, int M, int num_cus) {
-    const long n256 = (N + 255) / 256, m128 = (M + 127) / 128, m64 = (M + 63) / 64;
-    return 4 * n256 * m128 >= 3L * num_cus || n256 * m64 > num_cus;
-}
 bool skinny_product(const Geometry &g, int M, bool int8_activations, bool gated, int num_cus);
 int skinny_tail_rows(const Geometry &g, int M, bool gated, int num_cus);
 hipError_t launch_skinny_f16(const Geometry &g, const void *packed, const void *x, int M, void *y, const void *residual,
