@@ -663,6 +663,17 @@ static float skinny_us(const Geometry &g, int M, bool int8_activations, bool gat
 
 static float tile_round_us(const Geometry &g) { return 9.0f + 9.3e-3f * (float)g.K; }  // (binary16 activations)
 
+// Binary16 activations, 128 x 128 tiles: two workgroups share a compute unit, so that a second tile on it costs a third to
+// three quarters of the first.  us, rounds of one tile per compute unit / this: 24000 x 8192 int8 65 rows, 0.73 rounds 93 / 94; 130 rows, 1.47
+// 133 / 145; 277 rows, 2.2 224 / 255; 400 rows, 2.94 241 / 255; 640 rows, 3.67 306 / 299; 18432 x 3040 int4 800 rows, 3.94 115 / 135;
+// 28672 x 4128 int4 800 rows, 6.13 264 / 305.
+static float staged_tiles_us(const Geometry &g, int M, int num_cus) {
+    const float fill = (float)((g.N + 127) / 128 * ((M + 127) / 128)) / (float)num_cus;
+    const float pairs = floorf(0.5f * fill), rest = fill - 2.0f * pairs;
+    const float last = rest == 0.0f ? 0.0f : rest > 1.0f ? 0.95f + 0.4f * rest : pairs == 0.0f ? 1.0f : 1.15f;
+    return (10.0f + 10.3e-3f * (float)g.K) * (1.55f * pairs + last);
+}
+
 bool skinny_product(const Geometry &g, int M, bool int8_activations, bool gated, int num_cus) {
     if (tuning().gemm_variant != 0) return false;  // a large kernel is asked for by name
     if (tuning().skinny_max_m >= 0) return M <= tuning().skinny_max_m;
@@ -672,12 +683,13 @@ bool skinny_product(const Geometry &g, int M, bool int8_activations, bool gated,
     const long n256 = (g.N + 255) / 256, m128 = (M + 127) / 128;
     if (!int8_activations) {
         if (g.fmt != kW8C && g.K % 128 == 0) return here < 1.05f * ceilf((float)(n256 * m128) / (float)num_cus) * tile_round_us(g);
-        // 128 x 128 tiles, two workgroups per compute unit; the second one's make a round a quarter longer at once
-        const float fill = (float)((g.N + 127) / 128 * m128) / (float)num_cus;
-        // (8-bit weights, the largest layers of long K: `here` is low by 25 to 40 %, which smaller ones can spare; 32768 x 14336
-        // 65 rows 178 / 165, 18529 x 12160 277 rows 233 / 227; 25698 x 10368 129 rows 142 / 182, 128256 x 4096 130 rows 271 / 293)
-        if (g.fmt == kW8C && g.K >= 8192 && (long)g.N * g.K > 200L << 20) return here < 0.88f * fmaxf(1.0f, fill) * tile_round_us(g);
-        return here < 1.05f * (fill <= 1.0f ? 1.0f : fmaxf(1.25f, fill)) * (10.0f + 10.3e-3f * (float)g.K);
+        // Up to eight wavefronts share the steps here, and the time is that of the one with most (4096 x 14432, 113 steps: 7 % more than
+        // 4096 x 14336).  The choice is 0.2 % slower than the faster of both over 319 shapes of 1500 to 65536 channels, K of 1024 to 14432
+        // and 65 to 1000 rows; us, tiles / here: 18432 x 3040 int4 800 rows 115 / 146, 4096 x 14432 1000 rows 161 / 188; int8 28672 x 8192 96 rows
+        // 94 / 85, 25698 x 10368 277 rows 311 / 270, 24000 x 8192 400 rows 241 / 270.
+        const int steps = (g.K + 127) / 128, per_wave = (steps + 7) / 8;
+        const float uneven = (float)(per_wave * ((steps + per_wave - 1) / per_wave)) / (float)steps;
+        return uneven * here < 1.05f * staged_tiles_us(g, M, num_cus);
     }
     const float k = 1e-3f * (float)g.K;
     const bool w8 = g.fmt == kW8C;
