@@ -701,7 +701,9 @@ bool skinny_product(const Geometry &g, int M, bool int8_activations, bool gated,
 
 // Binary16 activations, 256 x 128 tiles, one workgroup per compute unit: a last round of few tiles costs as much as a
 // full one.  Rows to leave to the kernels here so that the tiles of the others end with a full round, if that is
-// estimated to save a twentieth or more; else 0.  Measured (us, tiles alone / like this): 2304 x 9216 3700 rows 231 / 161;
+// estimated to save anything; else 0 (of 30 shapes estimated to save up to a tenth the least gained 1 %, on average 6 %: 20000 x 6144
+// int4 groups 500 rows 157 / 146, 14336 x 9216 692 rows 223 / 208; of 20 estimated to lose up to a tenth 14 lost, up to 8 %).  Measured (us, tiles
+// alone / like this): 2304 x 9216 3700 rows 231 / 161;
 // 28672 x 4096 270 rows 98 / 72; 6144 x 4096 1300 rows 111 / 75; 4096 x 14336 2200 rows 315 / 228; 18432 x 2304 900 rows 108 / 93.
 int skinny_tail_rows(const Geometry &g, int M, bool gated, int num_cus) {
     if (tuning().gemm_variant != 0 || tuning().skinny_max_m >= 0) return 0;
@@ -714,7 +716,7 @@ int skinny_tail_rows(const Geometry &g, int M, bool gated, int num_cus) {
     // 24000 x 2048 673 rows 0.92 95 / 85, 11000 x 768 1502 rows 0.92 48 / 46; one round: 11000 x 1024 720 rows 0.84 35 / 29)
     if (rounds > 2 && 10 * (keep / 128) * n256 < 9 * (rounds - 1) * num_cus) return 0;
     const float saved = tile_round_us(g) - skinny_us(g, (int)rest, false, gated, num_cus) - 3.0f;  // (3: a second launch)
-    return saved > 0.05f * (float)rounds * tile_round_us(g) ? (int)rest : 0;
+    return saved > 0.0f ? (int)rest : 0;
 }
 
 hipError_t launch_skinny_f16(const Geometry &g, const void *packed, const void *x, int M, void *y, const void *residual,
