@@ -674,6 +674,34 @@ static float staged_tiles_us(const Geometry &g, int M, int num_cus) {
     return (10.0f + 10.3e-3f * (float)g.K) * (1.55f * pairs + last);
 }
 
+// Binary16 activations, 256 x 128 tiles, one workgroup per compute unit: a last round of few tiles costs as much as a
+// full one.  Rows to leave to the kernels here so that the tiles of the others end with a full round, if that is
+// estimated to save anything; else 0 (of 30 shapes estimated to save up to a tenth the least gained 1 %, on average 6 %: 20000 x 6144
+// int4 groups 500 rows 157 / 146, 14336 x 9216 692 rows 223 / 208; of 20 estimated to lose up to a tenth 14 lost, up to 8 %).  Measured (us, tiles
+// alone / like this): 2304 x 9216 3700 rows 231 / 161;
+// 28672 x 4096 270 rows 98 / 72; 6144 x 4096 1300 rows 111 / 75; 4096 x 14336 2200 rows 315 / 228; 18432 x 2304 900 rows 108 / 93.
+static int tail_rows(const Geometry &g, int M, bool gated, int num_cus, float *saved_us) {
+    *saved_us = 0.0f;
+    if (tuning().gemm_variant != 0 || tuning().skinny_max_m >= 0) return 0;
+    const long n256 = (g.N + 255) / 256, m128 = (M + 127) / 128, rounds = (n256 * m128 + num_cus - 1) / num_cus;
+    const long keep = (rounds - 1) * num_cus / n256 * 128;  // rows whose tiles fill one round less
+    const long rest = M - keep;
+    if (rounds < 2 || keep < 128 || rest < 1 || rest > kSkinnyMaxM) return 0;
+    // tiles that fill their two rounds or more badly save no round: workgroups of the next one fill the gaps anyway
+    // (us, tiles alone / like this, by that share: 28018 x 2048 808 rows 0.86 150 / 165, 19403 x 768 789 rows 0.89 71 / 77;
+    // 24000 x 2048 673 rows 0.92 95 / 85, 11000 x 768 1502 rows 0.92 48 / 46; one round: 11000 x 1024 720 rows 0.84 35 / 29)
+    if (rounds > 2 && 10 * (keep / 128) * n256 < 9 * (rounds - 1) * num_cus) return 0;
+    const float saved = tile_round_us(g) - skinny_us(g, (int)rest, false, gated, num_cus) - 3.0f;  // (3: a second launch)
+    if (saved <= 0.0f) return 0;
+    *saved_us = saved;
+    return (int)rest;
+}
+
+int skinny_tail_rows(const Geometry &g, int M, bool gated, int num_cus) {
+    float saved;
+    return tail_rows(g, M, gated, num_cus, &saved);
+}
+
 bool skinny_product(const Geometry &g, int M, bool int8_activations, bool gated, int num_cus) {
     if (tuning().gemm_variant != 0) return false;  // a large kernel is asked for by name
     if (tuning().skinny_max_m >= 0) return M <= tuning().skinny_max_m;
@@ -682,7 +710,11 @@ bool skinny_product(const Geometry &g, int M, bool int8_activations, bool gated,
     const float here = skinny_us(g, M, int8_activations, gated, num_cus);
     const long n256 = (g.N + 255) / 256, m128 = (M + 127) / 128;
     if (!int8_activations) {
-        if (g.fmt != kW8C && g.K % 128 == 0) return here < 1.05f * ceilf((float)(n256 * m128) / (float)num_cus) * tile_round_us(g);
+        if (g.fmt != kW8C && g.K % 128 == 0) {
+            float saved;  // (with their last rows left to the kernels here: 11008 x 9216 int4 660 rows, all here 180, all tiles 200, both 130)
+            tail_rows(g, M, gated, num_cus, &saved);
+            return here < 1.05f * (ceilf((float)(n256 * m128) / (float)num_cus) * tile_round_us(g) - saved);
+        }
         // Up to eight wavefronts share the steps here, and the time is that of the one with most (4096 x 14432, 113 steps: 7 % more than
         // 4096 x 14336).  The choice is 0.2 % slower than the faster of both over 319 shapes of 1500 to 65536 channels, K of 1024 to 14432
         // and 65 to 1000 rows; us, tiles / here: 18432 x 3040 int4 800 rows 115 / 146, 4096 x 14432 1000 rows 161 / 188; int8 28672 x 8192 96 rows
@@ -697,26 +729,6 @@ bool skinny_product(const Geometry &g, int M, bool int8_activations, bool gated,
     const float tiles = large ? (w8 ? 6.5f + 5.8f * k : 6.0f + 5.2f * k) * fmaxf(1.0f, 1.1f * (float)(n256 * m128) / (float)num_cus)
                               : (w8 ? 4.5f + 4.85f * k : 4.8f + 4.1f * k);
     return here < 1.05f * tiles;
-}
-
-// Binary16 activations, 256 x 128 tiles, one workgroup per compute unit: a last round of few tiles costs as much as a
-// full one.  Rows to leave to the kernels here so that the tiles of the others end with a full round, if that is
-// estimated to save anything; else 0 (of 30 shapes estimated to save up to a tenth the least gained 1 %, on average 6 %: 20000 x 6144
-// int4 groups 500 rows 157 / 146, 14336 x 9216 692 rows 223 / 208; of 20 estimated to lose up to a tenth 14 lost, up to 8 %).  Measured (us, tiles
-// alone / like this): 2304 x 9216 3700 rows 231 / 161;
-// 28672 x 4096 270 rows 98 / 72; 6144 x 4096 1300 rows 111 / 75; 4096 x 14336 2200 rows 315 / 228; 18432 x 2304 900 rows 108 / 93.
-int skinny_tail_rows(const Geometry &g, int M, bool gated, int num_cus) {
-    if (tuning().gemm_variant != 0 || tuning().skinny_max_m >= 0) return 0;
-    const long n256 = (g.N + 255) / 256, m128 = (M + 127) / 128, rounds = (n256 * m128 + num_cus - 1) / num_cus;
-    const long keep = (rounds - 1) * num_cus / n256 * 128;  // rows whose tiles fill one round less
-    const long rest = M - keep;
-    if (rounds < 2 || keep < 128 || rest < 1 || rest > kSkinnyMaxM) return 0;
-    // tiles that fill their two rounds or more badly save no round: workgroups of the next one fill the gaps anyway
-    // (us, tiles alone / like this, by that share: 28018 x 2048 808 rows 0.86 150 / 165, 19403 x 768 789 rows 0.89 71 / 77;
-    // 24000 x 2048 673 rows 0.92 95 / 85, 11000 x 768 1502 rows 0.92 48 / 46; one round: 11000 x 1024 720 rows 0.84 35 / 29)
-    if (rounds > 2 && 10 * (keep / 128) * n256 < 9 * (rounds - 1) * num_cus) return 0;
-    const float saved = tile_round_us(g) - skinny_us(g, (int)rest, false, gated, num_cus) - 3.0f;  // (3: a second launch)
-    return saved > 0.0f ? (int)rest : 0;
 }
 
 hipError_t launch_skinny_f16(const Geometry &g, const void *packed, const void *x, int M, void *y, const void *residual,
