@@ -748,9 +748,11 @@ hipError_t launch_skinny_i8(const Geometry &g, const void *packed, const int8_t 
         // Row tiles a multiple of 32 KiB apart: with every workgroup at the same k the weight stream comes from few memory
         // channels at a time.  us, same k / turned, 9 and 32 rows: 28672 x 4096 16.7 / 13.8 and 18.4 / 15.7, 20000 x 4096 11.4 / 10.2
         // and 13.2 / 12.2, 65536 x 4096 25.7 / 24.2 and 30.6 / 28.3, 6144 x 4096 6.1 / 5.7 and 6.8 / 6.7, 22016 x 8192 18.1 / 17.5
-        // and 20.7 / 20.4; 64 rows level.  Other K level (28672 x 3072 1 % slower); 8-bit weights from 12 % faster (65536 x 4096)
-        // to 5 % slower (12288 x 4096): not turned.
-        a.turned = a.rt_stride % 32 == 0;
+        // and 20.7 / 20.4; 8192 x 4096 32 and 65 rows 8.4 / 7.2 and 11.5 / 9.7.  From about 256 rows on the blocks of a row group no longer run
+        // at the same time and share the weights in L2 less well when each begins elsewhere (4096 x 4096 400 rows 16.7 / 17.4, 1536 x 8192
+        // 640 rows 16.3 / 18.0; over nine layers 1 % slower at 300, 3 at 400, 4 at 500).  Other K level (28672 x 3072 1 % slower);
+        // 8-bit weights from 12 % faster (65536 x 4096) to 5 % slower (12288 x 4096): not turned.
+        a.turned = a.rt_stride % 32 == 0 && M <= 256;
         return i8_any<true>(a, num_cus, st);
     }
     return i8_any<false>(a, num_cus, st);
