@@ -725,6 +725,13 @@ bool skinny_product(const Geometry &g, int M, bool int8_activations, bool gated,
     }
     const float k = 1e-3f * (float)g.K;
     const bool w8 = g.fmt == kW8C;
+    if (!w8 && g.Kp / 128 % 2 != 0) {
+        // 128 x 128 tiles with both operands staged: two share a compute unit at an eighth more than one (us, tiles / here: 28672 x 4224 65 rows
+        // 44 / 30, 240 rows, 1.75 per compute unit 47 / 53, 384 rows, 2.6 88 / 81, 1000 rows, 7 172 / 220; 11000 x 9600 240 rows 93 / 49, 384 rows
+        // 94 / 67; 6144 x 2944 384 rows 30 / 16).  The choice is 0.3 % slower than the faster of both over 220 such shapes.
+        const float fill = (float)((g.N + 127) / 128 * m128) / (float)num_cus;
+        return here < 1.04f * (3.5f + 9.3f * k) * (fill <= 1.0f ? 1.0f : 0.12f + ceilf(0.5f * fill));
+    }
     const bool large = 4 * n256 * m128 >= 3L * num_cus || n256 * ((M + 63) / 64) > num_cus;  // tiles of 128 tokens, or two rounds of 64
     const float tiles = large ? (w8 ? 6.5f + 5.8f * k : 6.0f + 5.2f * k) * fmaxf(1.0f, 1.1f * (float)(n256 * m128) / (float)num_cus)
                               : (w8 ? 4.5f + 4.85f * k : 4.8f + 4.1f * k);
