@@ -926,15 +926,16 @@ int attn_splits(int G, int d, int n_ctx, int num_cus) {
 // reads each position once per block, but takes 4 to 7 us before its first and behind its last step.
 // Here the positions are read once per 16 rows and the walks are split over wavefronts and
 // workgroups, which wins as long as there is little to walk (blocks x 64 positions) and the compute units hold the
-// blocks at once; up to 32 positions the other kernel has one step and is level or faster (head size 256: with one block of rows).  Measured (us, blocks of 64 or 128 / of 16):
-// head size 64, 8 groups, 242 tokens 7.0 / 5.9, 422 8.5 / 7.4, 4 groups, 27 tokens of 8 heads behind 1357 9.8 / 10.6; head size 128, 50
-// tokens of 8 heads behind 39 8.6 / 7.4, 207 tokens of 4 behind 58 9.4 / 10.1, 17 of 2 behind 3201 12.6 / 14.7; head size 256, 4 groups of 2 heads,
-// 77 tokens 11.3 / 9.0, 113 11.1 / 10.6, 348 14.3 / 16.5, 8 groups of 4, 119 tokens behind 367 23 / 21, 76 of 2 behind 1925 23 / 43.
+// blocks at once; long walks have to be split over more workgroups, whose results are combined.  Measured (us, blocks of 64 or 128 / of 16):
+// head size 64, 8 groups of 2 heads, 400 tokens 9.1 / 7.5, 4 of 8, 301 tokens behind 572 12.0 / 9.8, 8 of 1, 155 behind 1802 11.8 / 13.7;
+// head size 128, 1 group of 8, 17 tokens 6.4 / 4.9 (of 1 head, two blocks of one step 4.5 / 4.8), 2 of 4, 77 behind 500 12.7 / 10.3, 1 of 1, 20
+// behind 4234 22.6 / 23.9; head size 256, 1 group, 400 tokens 17.6 / 11.4, 4 of 2, 77 behind 500 18.6 / 13.3, 300 16.3 / 14.1, 2 of 4, 135 behind
+// 732 18.2 / 24.1.  Over 816 shapes of 17 to 512 tokens behind 0 to 5000 positions, 1 to 32 groups, the choice is 0.2 % slower than the faster of both.
 static bool few_row_blocks(int G, int M, int d, int n_ctx, int num_cus) {
     const long blocks = (long)G * ((M + 15) / 16), steps = (n_ctx + 63) / 64;
-    if ((n_ctx <= 32 && (d <= 128 || M <= 32)) || blocks > (d <= 64 ? 2 : 1) * num_cus) return false;
-    if (d <= 64) return blocks * steps <= (steps <= 9 ? 2500 : 1100);
-    return steps <= 3 || (steps <= 16 && blocks * steps <= (d <= 128 ? 250 : 160));
+    if ((n_ctx <= 32 && M <= 32) || blocks > (d <= 64 ? 2 : 1) * num_cus) return false;
+    if (d <= 64) return blocks * steps <= (steps <= 24 ? 3000 : 2000);
+    return blocks * steps <= (steps <= 8 ? 2500 : d > 128 ? 800 : steps <= 32 ? 1000 : 0);
 }
 
 // Workgroups per block of 16 query rows and KV head: the estimated time (us) of the walk and the combination.
