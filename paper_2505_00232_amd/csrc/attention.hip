@@ -964,15 +964,16 @@ static bool prefill_may_chunk(int G, int M, int num_cus) {
 // Prefill: wavefronts that share a walk (returned) and chunks of the walks (a.chunk_steps, a.block_rows), the combination with
 // the shortest estimated time (us).  Stages a workgroup takes one after the other: `longest` for the last one to finish,
 // `total` per compute unit.  Per stage: alone on its compute unit / as one of two (times two: head size 256 has the unit for itself); fixed: before the first and
-// behind the last stage.  Chunks cost a second launch and the partial results, written and read.  Fitted to, and chosen like this
-// within 6 % (few of them 10 to 15) of the best combination, 17 to 8192 tokens behind 0 to 6000 positions, 2 to 8 groups of 1 to 4 heads of 64, 128 and 256.
+// behind the last stage.  Chunks cost a second launch and the partial results, written and read.  Over 290
+// shapes (17 to 6000 tokens behind 0 to 6000 positions, 1 to 64 groups of 1 to 8 heads of 64, 128 and 256) the choice is 0.9 % slower than the
+// best combination where this kernel runs (head size 64 1.2, 128 1.0, 256 0.3), 6 shapes more than 6 %, the worst 16.
 static int plan_prefill(AttnArgs &a, int d, int num_cus) {
     const int forced_shares = tuning().attn_shares, forced_chunks = tuning().attn_chunks;
     const bool may_chunk = prefill_may_chunk(a.groups, a.M, num_cus);
-    const float alone[2] = {d <= 64 ? 0.43f : d <= 128 ? 0.58f : 1.15f, d <= 64 ? 0.45f : d <= 128 ? 0.65f : 1.37f};
-    const float busy[2] = {d <= 64 ? 0.50f : d <= 128 ? 0.79f : 1.15f, d <= 64 ? 0.52f : d <= 128 ? 0.95f : 1.37f};
-    const float shared[2] = {d <= 64 ? 0.40f : d <= 128 ? 0.57f : 1.15f, d <= 64 ? 0.44f : d <= 128 ? 0.63f : 1.5f};
-    const float fixed[2] = {d <= 128 ? 4.0f : 6.0f, d <= 128 ? 4.5f : 7.0f};
+    const float alone[2] = {d <= 64 ? 0.43f : d <= 128 ? 0.58f : 1.13f, d <= 64 ? 0.45f : d <= 128 ? 0.65f : 1.55f};
+    const float busy[2] = {d <= 64 ? 0.50f : d <= 128 ? 0.79f : 1.13f, d <= 64 ? 0.52f : d <= 128 ? 0.95f : 1.55f};
+    const float shared[2] = {d <= 64 ? 0.40f : d <= 128 ? 0.57f : 1.13f, d <= 64 ? 0.44f : d <= 128 ? 0.63f : 1.85f};
+    const float fixed[2] = {d <= 128 ? 4.0f : 6.0f, d <= 128 ? 4.5f : 6.0f};
     const long slots = (long)num_cus * (d <= 128 ? 2 : 1);
     const int exactly = forced_chunks > kPrefillMaxChunks ? kPrefillMaxChunks : forced_chunks;  // (from 2 on)
     const float second = fminf(7.0f, 2.5f + (float)((long)a.groups * a.M) / 520.0f);  // the second launch
