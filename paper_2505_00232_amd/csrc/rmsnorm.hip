@@ -72,10 +72,10 @@ __global__ __launch_bounds__(128 * ROWS) void rmsnorm_kernel(RmsDev a) {
         }
     }
     // The weights of the first steps are requested before the rows' sums are known (few tokens: all latency;
-    // us, rows x k, behind the sums / like this: 9 x 4096 4.24 / 3.82, 32 x 4096 4.35 / 3.91, 300 x 4096 5.0 / 4.8, 1024 x 4096 7.8 / 7.5).
-    // Not with eight rows: 16 wavefronts would no longer fit a compute unit twice.
-    constexpr int PRE = ROWS <= 4 ? 3 : 0;
-    uint4 gpre[PRE > 0 ? PRE : 1][2];
+    // us, rows x k, behind the sums / like this: 9 x 4096 4.24 / 3.82, 32 x 4096 4.35 / 3.91, 300 x 4096 5.0 / 4.8, 1024 x 4096 7.8 / 7.5;
+    // eight rows: 4096 x 2304 15.7 / 15.3, 8192 x 2304 27.9 / 27.0, 6000 x 4096 30.0 / 29.6, 3000 x 14336 level).
+    constexpr int PRE = 3;
+    uint4 gpre[PRE][2];
 #pragma unroll
     for (int i = 0; i < PRE; ++i) {
         if (i < steps) {
