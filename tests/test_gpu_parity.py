@@ -1319,16 +1319,24 @@ def test_attention_many_query_rows(B, S, h_q, h_kv, d, C, n_ctx):
     got = out.cpu().numpy()
     assert np.all(np.isfinite(got))
     assert _E(got.reshape(G * M, d), ref.reshape(G * M, d)) <= TOL
-    # the launch form of large grids (a workgroup takes a long and a short block of query rows in
-    # turn), forced on this small case: every row is computed as before, so the bits are the same
-    out2 = torch.full((G, M, d), 9.0, dtype=torch.float16, device=DEV)
-    binding.qfc_tune(5, 1)
-    try:
-        binding.qfc_attention(qd, kd, vd, S, n_ctx, shape, ws, out2)
-        torch.cuda.synchronize()
-    finally:
-        binding.qfc_tune(5, -1)
-    assert torch.equal(out, out2)
+    # whole walks by one wavefront and by two, as launches of many blocks take them, and each of them twice with the same bits
+    for shares in (1, 2):
+        binding.qfc_tune(13, 0)
+        binding.qfc_tune(6, 0)
+        binding.qfc_tune(14, shares)
+        try:
+            outs = [torch.full((G, M, d), 9.0, dtype=torch.float16, device=DEV) for _ in range(2)]
+            for o in outs:
+                binding.qfc_attention(qd, kd, vd, S, n_ctx, shape, ws, o)
+            torch.cuda.synchronize()
+        finally:
+            binding.qfc_tune(13, -1)
+            binding.qfc_tune(6, -1)
+            binding.qfc_tune(14, 0)
+        got2 = outs[0].cpu().numpy()
+        assert np.all(np.isfinite(got2)), shares
+        assert _E(got2.reshape(G * M, d), ref.reshape(G * M, d)) <= TOL, shares
+        assert torch.equal(outs[0], outs[1]), shares
     # the launch form of few blocks (walks cut into chunks, partial results combined by a second
     # kernel), forced on: same values within the tolerance, finite, and nothing from past the context
     binding.qfc_tune(6, 1)
@@ -1385,10 +1393,10 @@ def test_attention_blocks_of_sixteen_query_rows(B, S, h_q, h_kv, d, C, n_ctx):
 
 @pytest.mark.parametrize("B,S,h_q,h_kv,d,C,n_ctx", [(1, 17, 1, 1, 64, 64, 33), (1, 64, 2, 1, 128, 64, 64), (1, 129, 3, 1, 64, 192, 161),
                                                     (2, 43, 6, 2, 128, 640, 577), (1, 200, 4, 4, 256, 256, 200), (1, 33, 2, 1, 256, 640, 609),
-                                                    (1, 131, 8, 1, 128, 448, 419)])
+                                                    (1, 131, 8, 1, 128, 448, 419), (1, 50, 2, 1, 64, 640, 577), (1, 600, 2, 2, 64, 1024, 1000)])
 def test_attention_walks_shared_by_wavefronts(B, S, h_q, h_kv, d, C, n_ctx):
-    """Prefill with one or two wavefronts per walk, whole walks and walks in chunks: odd numbers of steps (a stage with one step
-    too many), walks of fewer steps than the pipeline has stages, last blocks of few rows; keys that grow along the walk, so
+    """Prefill with one or two wavefronts per walk, whole walks and walks in chunks: odd numbers of steps (a last stage that lacks
+    one), walks of fewer steps than the pipeline has stages and, at each head size, of enough for its branch-free loop, last blocks of few rows; keys that grow along the walk, so
     that the maximum moves in every step; a row of equal scores; everything past the context poisoned."""
     print(f"attention shared walks B={B} S={S} h_q={h_q} h_kv={h_kv} d={d} n_ctx={n_ctx}", flush=True)
     G, M = B * h_kv, S * (h_q // h_kv)
