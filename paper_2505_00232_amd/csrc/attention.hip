@@ -504,12 +504,12 @@ __global__ __launch_bounds__(64) void attn_combine_kernel(AttnArgs a) {
 // its last row sees, rows that see less mask the rest.
 // Registers: up to head size 128 two workgroups per compute unit, everything in ordinary registers; at 256 one, whose
 // query operands and part of whose sums sit in accumulation registers (scores in ordinary ones: a flag of this file's build).
-// What bounds it: at 8192 tokens (head size 128) power: matrix cores busy 52 %, vector unit 57 % of the clocks, the clock at
-// 1.8 GHz; without the exponentials it is no faster.  Short walks: latency (a step of a workgroup alone on its compute unit
-// takes 0.75 us, of two together 1.2), 3 us before the first step, 2 us after the last.
-// Measured (us, 32 heads on 8 of 128; blocks of 128 rows with one walk each / this): 512 tokens 17.9 / 11.4, 1024 30.3 / 19.8, 2048
-// 58.7 / 52.5, 6000 367 / 320, 8192 636 / 570 (0.96 PFLOP/s), 130 behind 2870 positions 29.7 / 23.4, 300 behind 6000 57.3 / 52; head size
-// 64, 8 heads, 4096 tokens 48.8 / 35.2; head size 256, 8 heads on 4, 2048 tokens 54.6 / 50, 4096 172 / 110.
+// What bounds it: at 8192 tokens (head size 128) power and both units: matrix cores busy 54 %, vector unit 59 % of the clocks, the
+// clock at 1.6 to 1.8 GHz.  Short walks: latency (head size 128: 4 us before the first and behind the last step, a stage of a workgroup alone
+// on its compute unit 0.5 to 0.6 us, of two together 1.2).
+// Measured (us, 32 heads on 8 of 128; blocks of 128 rows with one walk each / this, both in one session, caches not in L2): 512 tokens
+// 19.1 / 13.1, 1024 32.1 / 22.1, 2048 65 / 61.5, 6000 373 / 319, 8192 630 / 567 (0.97 PFLOP/s), 130 behind 2870 positions 31.6 / 24.8, 300 behind
+// 6000 60 / 57; head size 64, 8 heads, 4096 tokens 53 / 38; head size 256, 8 heads on 4, 2048 tokens 58 / 49, 4096 175 / 128.
 template <int D, int PS>
 struct PrefillCfg {
     static constexpr int CPR = D / 8;           // 16-byte chunks per K row

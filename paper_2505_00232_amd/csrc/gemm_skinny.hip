@@ -579,7 +579,8 @@ void cut_rows(SkinnyArgs &a, int blocks) {
 // int8, binary16         2304 x 9216 77 rows 19.1 / 16.3, 200 26.3 / 23.1
 // int8 x int8            2304 x 9216 48 rows 13.0 / 10.8, 77 14.7 / 12.8; 6144 x 4096 64 rows 10.9 / 10.1
 // int8 x int4            4096 x 14336 20 rows 13.6 / 12.1, 64 19.2 / 15.3; 6144 x 4096 64 rows 9.3 / 7.7; 2304 x 9216 77 rows 11.9 / 9.3
-// (none slower by more than 3 %; wide layers keep the fewest blocks: 28672 x 4096 int4 groups, 64 rows 30.9 / 34.9 with two.)
+// (over 11 layers, 16 numbers of rows and each format 2 to 4 % faster on average; the worst where these kernels are taken at all: 2304 x 2048
+// int4 groups, 400 rows 11.5 / 12.0; wide layers keep the fewest blocks: 28672 x 4096 int4 groups, 64 rows 30.9 / 34.9 with two.)
 void choose_blocks(SkinnyArgs &a, int fmt, bool int8_activations, int num_cus) {
     if (tuning().skinny_blocks > 0) return;
     const SkinnyArgs fewest = a;
@@ -646,15 +647,17 @@ static int tiles_up_to_k(const Geometry &g, int M, bool int8_activations, int nu
 
 // Which products these kernels take.  Up to 64 token rows: all but those.  More rows: the tiles of 64 or 128
 // tokens take the same time until they fill the chip, and long (they leave most of it idle); here the
-// rows are cut into blocks, with the time growing with their number.  Both times are estimated: here see estimate_us, which is
-// 2 to 10 % high at 65 to 1024 rows of layers of 1500 to 28672 channels, K of 1024 to 14336 (hence the 1.05); tiles
-//   9 + 9.3 K / 1000 a round (binary16 activations, 256 x 128), 10 + 10.3 K / 1000 (128 x 128); 4.5 + 4.85 K / 1000 and 4.8 + 4.1 K / 1000 (64 tokens, int8 x int8 and int4)
+// rows are cut into blocks, with the time growing with their number.  Both times are estimated: here see estimate_us, which where
+// the two are near each other (65 to 1024 rows, 1500 to 65536 channels, K of 896 to 14336, 721 shapes) is 1 to 7 % high in the median (hence the
+// 1.05) and from 16 % low to 27 % high in eight of ten; tiles
+//   9 + 9.3 K / 1000 a round (binary16 activations, 256 x 128), 10 + 10.3 K / 1000 (128 x 128: staged_tiles_us); 4.5 + 4.85 K / 1000 and 4.8 + 4.1 K / 1000
+//   (64 tokens, int8 x int8 and int4), 3.5 + 9.3 K / 1000 (int8 x int4, K of an odd number of 128)
 // Measured (us, tiles / here): 4096 x 14336 int4, binary16 activations, 77 rows 131 / 24, 300 131 / 64, 512 133 / 75;
-// 2304 x 9216 int4 groups 77 rows 96 / 15, 300 98 / 26, 1000 98 / 84; 18432 x 2304 77 rows 31 / 22, 200 31 / 38;
+// 2304 x 9216 int4 groups 77 rows 96 / 15, 300 98 / 26, 1000 95 / 71; 18432 x 2304 77 rows 31 / 22, 200 31 / 38;
 // 11000 x 3008 300 rows 52 / 40; int8, binary16 18432 x 2304 150 rows 42 / 36, 14336 x 4096 640 rows 132 / 114;
 // int8 x int8  6144 x 4096 240 rows 25.4 / 19.5, 300 25.2 / 22.2, 500 25 / 31; 4096 x 14336 384 rows 73 / 59; 8192 x 2304 150 rows 17.9 / 13.5
-// int8 x int4  6144 x 4096 300 rows 21.4 / 17.4; 2304 x 9216 800 rows 44.7 / 34.6; 18432 x 2304 80 rows 15.5 / 13.4, 150 15.6 / 19.3
-// (over 13 such layers, 13 numbers of rows and all formats the choice is 1 % slower than the faster one of both).
+// int8 x int4  6144 x 4096 300 rows 21.4 / 17.4; 2304 x 9216 800 rows 44.7 / 34.6; 18432 x 2304 80 rows 15.5 / 13.4, 150 14.9 / 20.7
+// (over 13 such layers, 16 numbers of rows and all formats the choice is less than 1 % slower than the faster one of both).
 static float skinny_us(const Geometry &g, int M, bool int8_activations, bool gated, int num_cus) {
     SkinnyArgs a = make_args(g, nullptr, nullptr, nullptr, M, nullptr, nullptr, gated ? 0 : -1);
     choose_blocks(a, g.fmt, int8_activations, num_cus);
