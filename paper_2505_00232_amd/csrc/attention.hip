@@ -476,8 +476,13 @@ __global__ __launch_bounds__(64) void attn_combine_kernel(AttnArgs a) {
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
             if (s + 8 * k >= a.splits) break;
+            if (s + 8 * k + 8 > a.splits) {  // (us, 1280 positions, the select in every group / in the last one only: 3.58 / 3.42)
 #pragma unroll
-            for (int u = 0; u < 8; ++u) o = fmaf(__shfl(f, s + 8 * k + u, 64), s + 8 * k + u < a.splits ? v[k][u] : 0.0f, o);
+                for (int u = 0; u < 8; ++u)
+                    if (s + 8 * k + u >= a.splits) v[k][u] = 0.0f;
+            }
+#pragma unroll
+            for (int u = 0; u < 8; ++u) o = fmaf(__shfl(f, s + 8 * k + u, 64), v[k][u], o);
             if (s + 8 * k + 32 < a.splits) fetch(k, s + 8 * k + 32);
         }
     }
