@@ -1,12 +1,12 @@
-// Prefill product for int4 weights on the fp16 matrix cores:
+// Prefill product with binary16 activations on the fp16 matrix cores:
 //   y[m,n] = sum_k x[m,k] * (s * Wq[n,k]),  fp32 accumulation,
-// with s = s[n, k/32] (group scales) or s[n] (per-channel scales).
+// with s = s[n, k/32] (group scales) or s[n] (per-channel scales), int4 or int8 codes.
 // FP16 activations with quantized weights (section 4.2 of the paper), computed
 // on matrix units as the compute-bound prefill stage wants (section 3.7).
 //
-// Two kernels.  The main one (K a multiple of 128; described in front of it)
+// Two kernels.  The main one (K a multiple of 128, int8 codes: of 64; described in front of it)
 // never writes dequantized weights anywhere: packed tiles are copied verbatim
-// into LDS, a lane reads the dword that is its MFMA operand, converts it in
+// into LDS, a lane reads the codes of its MFMA operand, converts them in
 // registers and feeds the matrix core.  Int4 weights are a quarter of the
 // activation bytes, so LDS carries far fewer bytes per MFMA than with a
 // dequantized weight tile.  The second kernel is the general fallback (any K
@@ -266,65 +266,10 @@ __global__ __launch_bounds__(256) void gemm_f16_w4_kernel(GemmF16Args a) {
 }
 
 
-// ---------------------------------------------------------------------------
-// Main kernel: weights never dequantized into LDS, activations through an LDS ring.
-//
-// Workgroup = 8 wavefronts over 256 output channels x 128 token rows: four
-// groups of 64 channels (four packed row tiles each), times two halves of K.
-// Both wavefronts of a channel group own the same 64 x 128 outputs as 2 x 4
-// tiles of v_mfma_f32_32x32x16_f16; in every 128-k tile one takes quantization
-// groups 0, 1 and the other groups 2, 3; at the end they swap halves of their
-// accumulators through LDS and each stores half of the outputs.  The two share a SIMD, so that the integer -> binary16
-// conversion of one (about 60 vector instructions per group, each done by exactly
-// one wavefront of the chip) runs while the matrix core works for the other:
-// from a single wavefront the conversion and the MFMAs mostly add up instead of
-// overlapping.  (Measured on MI355X: this MFMA shape runs at the full matrix rate
-// from one wavefront per SIMD; the 16x16x32 shape reaches less than half of it.)
-// Weights are the row operand, so a lane ends up with groups of four consecutive
-// n of one token row.
-//
-// Everything arrives by direct global -> LDS copies (16 bytes per lane, one KiB
-// per wavefront instruction).  Per 128-k tile every wavefront issues one batch of
-// 7 copies: 2 of the 16 packed KiB tiles of codes (tile j + 3), the scales of its
-// channel group for tile j + 3 (lane = one of the 64 rows, 16 bytes = 8 groups;
-// both wavefronts of the group write the same bytes), and 4 KiB of the 32 KiB
-// activation stage j + 2 (128 rows x 128 k, stored as two halves of 64 k).
-// Three-slot rings; nothing else touches vector memory inside the loop, so the
-// copies complete in issue order and "the batch issued two tiles ago has landed"
-// is "at most one batch is outstanding".  One workgroup barrier per tile.
-//
-// Inside a wavefront the loop is software pipelined by one quantization group:
-// while the 16 MFMAs of a group run, the activations of the next group are read
-// from LDS and its codes are converted (exact int -> binary16, one binary16
-// multiply by the group scale); the codes and scales of a tile are read into
-// registers at the end of the tile before.
-//
-// An MFMA operand is 32 rows x 16 k, lane = (row r, k octet kh).  For the
-// weights, lane (r, kh) of row pair ip, k step s owns the 16-byte vector of row
-// tile 2 ip + r / 16, lane (2 s + kh) * 16 + r % 16 of a packed tile: dword g of
-// it is the lane's operand for group g.
-// A half of an activation stage is 128 rows x 64 k, row-major with 128-byte
-// rows; the 16-byte octet o of row r sits at octet position o ^ ((r >> 1) & 7),
-// which makes the operand reads conflict free while a wavefront copy instruction
-// still reads whole 128-byte rows from memory.
 typedef __attribute__((address_space(3))) void *lptr_t;
 
-constexpr int DBN = 256, DBM = 128;
-constexpr int DRING = 3;
-constexpr int DX_BYTES = DBM * 128 * 2;           // activation stage: 128 rows x 128 k
-constexpr int DW_BYTES = 16 * 1024;               // codes of one tile: 16 row tiles
-constexpr int DS_BYTES = 4 * 1024;                // scales for one tile: 4 channel groups x 64 rows x 16 B
-constexpr int DW_OFF = DRING * DX_BYTES;
-constexpr int DS_OFF = DW_OFF + DRING * DW_BYTES;
-constexpr int kDirectRingBytes = DS_OFF + DRING * DS_BYTES;
-constexpr int DSPARE_OFF = kDirectRingBytes;          // one spare KiB: destination of the copies past the end of K
-constexpr int kDirectLdsBytes = kDirectRingBytes + 1024;
-static_assert(kDirectLdsBytes <= 160 * 1024, "LDS of a compute unit");
-constexpr int DBATCH = 2 + 1 + 4;                 // copies per wavefront per tile (one fewer without group scales)
-constexpr int DEX_BYTES = 64 * 64 * 4;            // half of a wavefront's accumulators (exchange buffer)
-constexpr int DEPI_PITCH = (64 + 8) * 2;
-static_assert(8 * DEX_BYTES <= kDirectRingBytes && 32 * DEPI_PITCH <= DEX_BYTES, "exchange and store staging fit in the rings, below the spare KiB");
-static_assert(3 * DBATCH <= 63, "outstanding copies of a wavefront (three batches at most) must fit the 6-bit counter");
+constexpr int TN = 256;                    // output channels of a workgroup
+constexpr int kStorePitch = (64 + 8) * 2;  // bytes per staged row of the store phase
 
 // eight biased codes -> eight scaled binary16 values (k ascending) as an MFMA operand
 __device__ __forceinline__ v8h dequant_frag(uint32_t w, h2 s) {
@@ -352,393 +297,412 @@ __device__ __forceinline__ v8h dequant_frag_unscaled(uint32_t w) {
     return v8h{p0[0], p0[1], p1[0], p1[1], p2[0], p2[1], p3[0], p3[1]};
 }
 
-// One MFMA followed by a few vector instructions, four times: the order the
-// instructions of a quarter of a "multiply one group, convert the next" block
-// (4 MFMAs, the conversion of one operand) are issued in.
-__device__ __forceinline__ void interleave_mfma_valu() {
+// ---------------------------------------------------------------------------
+// Main kernel: weights never dequantized into LDS, activations through an LDS ring.
+//
+// A workgroup is four wavefronts (KS = 1) over 256 output channels x 32 JP token rows.  A wavefront owns 64 channels (four
+// packed row tiles) and all the rows, 2 x JP tiles of v_mfma_f32_32x32x16_f16 over all of K: it converts its weights once for
+// 32 JP rows, its codes are wanted by no other wavefront, and nothing is exchanged at the end.  Weights are the row operand, so a
+// lane ends up with groups of four consecutive n of one token row.
+//
+// What bounds it: power on real data (a register-only loop of these MFMAs holds 1.64 PFLOP/s, one round of full tiles of long K 1.36), then
+// what a wavefront does before its first and after its last MFMA.  Hence two workgroups of JP = 4 per compute unit, with everything
+// within half its registers and 80 KiB of LDS: one stores or starts while the other multiplies, and a barrier stops
+// one wavefront of a SIMD, not both.  Measured in turn, us, before (eight wavefronts over 256 x 128, the halves of K in
+// two groups that swap their sums at the end, one workgroup per compute unit) / now:
+//   int4 groups  18432 x 2304, 2048 rows, gated 187 / 155 (0.93 -> 1.12 PFLOP/s); 9216 x 768, 1000 rows 32.0 / 22.8
+//   int4         28672 x 4096, 6000 rows, gated 1232 / 1099 (1.28 PFLOP/s); 6144 x 4096 274 / 242; 4096 x 14336 558 / 526 (1.34)
+//   int8         14336 x 4096, 1000 rows 149 / 104; 4096 x 4096, 2048 rows 81 / 62 (before: the fallback kernel)
+// A wavefront of 64 channels x 256 rows (all registers, one workgroup per compute unit) converts half as often and
+// takes 1122 us for the first line of int4: what it saves in conversions it loses at the barriers and in the store phase.
+//
+// KS = 2: eight wavefronts, two groups of four over the same outputs, each with half of K and rings of its own; they
+// swap halves of their sums through LDS at the end.  For launches of about one workgroup per compute unit, whose SIMDs would
+// hold one wavefront (2304 x 14336, 1000 rows int4 138 us with JP = 4, 90 with JP = 2, 79 with JP = 2 and two groups).
+// Which JP and KS: tile_us.
+//
+// Everything arrives by direct global -> LDS copies (16 bytes per lane, one KiB per wavefront instruction), which complete in
+// issue order, so that waits are counts of the copies issued later.  A half stage is 64 k of the token rows: rows of 128 bytes, the
+// 16-byte octet o of row r at position o ^ ((r >> 1) & 7), which makes the operand reads conflict free while a copy still
+// reads whole 128-byte row pieces.  Three half stages, copied two ahead; one barrier per half stage.  Codes of 128 k (int8: of 64 k, two in
+// turn) and, for group scales, the vectors of 8 groups of the wavefront's 64 rows are copied after the tile before has been
+// read into registers, and read at its end.  No copy is issued past the end of K.
+//
+// The loop is software pipelined by one k step of 16: while the MFMAs of a step run, the token rows of the next are read and its weights
+// converted.  An MFMA operand is 32 rows x 16 k, lane = (row r, k octet kh).  4-bit codes: lane (r, kh) of row pair ip, k step s owns the
+// vector of row tile 2 ip + r / 16, lane (2 s + kh) * 16 + r % 16 of a packed tile; dword g of it is its operand for group g.
+// int8: vector (2 p + kh) * 16 + r % 16 of a packed tile holds its operands of the k steps 2 p and 2 p + 1 (token rows are read in the
+// same order of octets).
+//
+// FMT: packed format; JP: blocks of 32 token rows.
+template <int FMT, int JP>
+struct TileLds {
+    static constexpr int kX = JP * 4096;                       // half stage: 32 JP rows x 64 k
+    static constexpr int kW = FMT == kW8C ? 2 * 16384 : 16384;  // codes of 128 k
+    static constexpr int kS = FMT == kW4G32 ? 4096 : 0;         // scales of 8 groups
+    static constexpr int kStaging = 4 * 32 * kStorePitch;
+    static constexpr int kRings = 3 * kX + kW + kS;
+    static constexpr int kBytes = kRings > kStaging ? kRings : kStaging;
+};
+
+// Eight binary16 values, wherever they lie in memory (one 16-byte access; rows of N not a multiple of 8 are not aligned to it).
+struct __attribute__((packed, aligned(2))) Octet {
+    uint32_t v[4];
+};
+
+// Calls f for the octets of a staged block of 32 token rows x 64 channels that lie inside [M, N], or part(..., values) for the one
+// that holds a row's last `values` < 8.  (8917 x 256 int4, 2713 rows: 86 us with single values of 32 rows per store instruction, 21.7 like this.)
+template <typename F, typename P>
+__device__ __forceinline__ void block_rows(const GemmF16Args &a, char *region, int mrow0, int n0, int lane, F &&f, P &&part) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-        __builtin_amdgcn_sched_group_barrier(0x002, 4, 0);
+    for (int it = 0; it < 4; ++it) {
+        const int idx = it * 64 + lane, row = idx >> 3, ch = idx & 7;
+        const int m = mrow0 + row, n = n0 + ch * 8;
+        char *staged = region + row * kStorePitch + ch * 16;
+        if (m < a.M && n + 8 <= a.N)
+            f(staged, (size_t)m * a.N + n);
+        else if (m < a.M && n < a.N)
+            part(reinterpret_cast<_Float16 *>(staged), (size_t)m * a.N + n, a.N - n);
     }
 }
 
-template <bool PC>
-__global__ __launch_bounds__(512) void gemm_f16_w4_direct_kernel(GemmF16Args a) {
-    constexpr int BATCH = PC ? DBATCH - 1 : DBATCH;
-    extern __shared__ uint4 lds[];
-    char *lds_b = reinterpret_cast<char *>(lds);
+// Store phase of a wavefront's 64 channels x 32 JP token rows.  A lane holds one token row (lane % 32) and groups of four
+// consecutive n; the binary16 values go through a block of LDS of the wavefront's own (32 token rows x 64 channels) and leave as 16-byte
+// stores along n.
+template <bool PC, int JP>
+__device__ __forceinline__ void store_tile(const GemmF16Args &a, v16f (&acc)[2][JP], int n0, int m0, char *region, int lane) {
+    const int r = lane & 31, kh = lane >> 5;
+    if (PC) {
+#pragma unroll
+        for (int ip = 0; ip < 2; ++ip)
+#pragma unroll
+            for (int qq = 0; qq < 4; ++qq) {
+                const float4 sc = *reinterpret_cast<const float4 *>(a.sw + n0 + ip * 32 + 8 * qq + 4 * kh);
+#pragma unroll
+                for (int jp = 0; jp < JP; ++jp) {
+                    acc[ip][jp][4 * qq + 0] *= sc.x;
+                    acc[ip][jp][4 * qq + 1] *= sc.y;
+                    acc[ip][jp][4 * qq + 2] *= sc.z;
+                    acc[ip][jp][4 * qq + 3] *= sc.w;
+                }
+            }
+    }
+    typedef _Float16 h4 __attribute__((ext_vector_type(4)));
+    auto wave_sync = [&]() __attribute__((always_inline)) {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    };
+    if (a.gated_act >= 0) {
+        const GateCoeffs gc = gate_coeffs(a.gated_act);
+        const int halfn = a.N / 2, o0 = n0 / 2;
+#pragma unroll
+        for (int jp = 0; jp < JP; ++jp) {
+            const int mrow0 = m0 + jp * 32;
+#pragma unroll
+            for (int ip = 0; ip < 2; ++ip)
+#pragma unroll
+                for (int qq = 0; qq < 2; ++qq) {
+                    h4 hv;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        hv[e] = (_Float16)(gate_activation(acc[ip][jp][4 * qq + e], gc) * acc[ip][jp][4 * (qq + 2) + e]);
+                    *reinterpret_cast<h4 *>(region + r * kStorePitch + (ip * 16 + 8 * qq + 4 * kh) * 2) = hv;
+                }
+            wave_sync();
+#pragma unroll
+            for (int it = 0; it < 2; ++it) {  // 32 rows x 4 chunks of 16 bytes
+                const int idx = it * 64 + lane;
+                const int row = idx >> 2, ch = idx & 3;
+                const uint4 v = *reinterpret_cast<const uint4 *>(region + row * kStorePitch + ch * 16);
+                const int mm = mrow0 + row, nn = o0 + ch * 8;
+                if (mm < a.M && nn < halfn) *reinterpret_cast<uint4 *>(a.y + (size_t)mm * halfn + nn) = v;
+            }
+            wave_sync();
+        }
+        return;
+    }
+    const bool has_res = a.res != nullptr;
+#pragma unroll
+    for (int jp = 0; jp < JP; ++jp) {
+        const int mrow0 = m0 + jp * 32;
+        if (has_res) {
+            block_rows(a, region, mrow0, n0, lane,
+                       [&](char *staged, size_t at) { *reinterpret_cast<uint4 *>(staged) = __builtin_bit_cast(uint4, *reinterpret_cast<const Octet *>(a.res + at)); },
+                       [&](_Float16 *staged, size_t at, int values) { for (int e = 0; e < values; ++e) staged[e] = a.res[at + e]; });
+            wave_sync();
+        }
+#pragma unroll
+        for (int ip = 0; ip < 2; ++ip)
+#pragma unroll
+            for (int qq = 0; qq < 4; ++qq) {
+                const int nl = ip * 32 + 8 * qq + 4 * kh;
+                float v[4] = {acc[ip][jp][4 * qq], acc[ip][jp][4 * qq + 1], acc[ip][jp][4 * qq + 2], acc[ip][jp][4 * qq + 3]};
+                if (has_res) {
+                    float rv[4];
+                    staged_residual4(region, r * kStorePitch + nl * 2, rv);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) v[e] += rv[e];
+                }
+                *reinterpret_cast<h4 *>(region + r * kStorePitch + nl * 2) = h4{(_Float16)v[0], (_Float16)v[1], (_Float16)v[2], (_Float16)v[3]};
+            }
+        wave_sync();
+        block_rows(a, region, mrow0, n0, lane,
+                   [&](char *staged, size_t at) { *reinterpret_cast<Octet *>(a.y + at) = __builtin_bit_cast(Octet, *reinterpret_cast<const uint4 *>(staged)); },
+                   [&](_Float16 *staged, size_t at, int values) { for (int e = 0; e < values; ++e) a.y[at + e] = staged[e]; });
+        wave_sync();
+    }
+}
 
-    const int tid = threadIdx.x;
-    const int lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int ng = wave & 3;   // channel group: output channels 64 ng .. 64 ng + 63 of the tile
-    const int ks = wave >> 2;  // K half: quantization groups 2 ks, 2 ks + 1 of every 128-k tile
+template <int FMT, int JP, int KS>
+__global__ __launch_bounds__(256 * KS, KS == 2 ? 2 : JP == 1 ? 4 : JP == 2 ? 3 : 2) void gemm_f16_tile_kernel(GemmF16Args a) {
+    using L = TileLds<FMT, JP>;
+    constexpr bool W8 = FMT == kW8C, G32 = FMT == kW4G32;
+    constexpr int ROWS = 32 * JP;
+    constexpr int W_OFF = 3 * L::kX, S_OFF = W_OFF + L::kW;
+    constexpr int XC = JP, WC = G32 ? 5 : 4;  // copies per wavefront: of a half stage; of 128 k (int8: 64 k) of codes
+    extern __shared__ uint4 lds[];
+    char *lds_all = reinterpret_cast<char *>(lds);
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane((threadIdx.x >> 6) & 3);
+    const int group = KS == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x >> 8);  // part of K
+    char *lds_b = lds_all + group * L::kBytes;
     const int c = lane & 15, q = lane >> 4;
     const int r = lane & 31, kh = lane >> 5;
-
-    // Workgroups are dealt to the 8 XCDs round robin; each XCD has its own L2.  Where
-    // the tile grid allows, an XCD gets a rectangle of (n_tiles / 2) x (m_tiles / 4)
-    // tiles and walks it channel tile by channel tile, so that the workgroups in
-    // flight on it (about 32) share 4 activation tiles and 8 weight tiles.
-    const int total = a.n_tiles * a.m_tiles;
     int nt, mt;
-    if (a.m_tiles % 4 == 0 && a.n_tiles % 2 == 0) {
-        const int xcd = blockIdx.x % 8, j = blockIdx.x / 8;
-        const int cm = a.m_tiles / 4, cn = a.n_tiles / 2;
-        nt = (xcd & 1) * cn + j / cm;
-        mt = (xcd >> 1) * cm + j % cm;
-    } else {
-        xcd_tile(blockIdx.x, a.n_tiles, a.m_tiles, a.by_tokens, nt, mt);
-    }
+    xcd_tile(blockIdx.x, a.n_tiles, a.m_tiles, a.by_tokens, nt, mt);
+    const int m0 = mt * ROWS;
+    // half stages of this group (4-bit codes: an even number); the first group has the odd step
+    constexpr int kStep = W8 ? 1 : 2;
+    const int nst_all = a.K / 64, first = KS == 1 ? nst_all : (nst_all / kStep + 1) / 2 * kStep;
+    const int nst = group ? nst_all - first : first, i0 = group ? first : 0;
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(lptr_t)lds + group * L::kBytes;
 
-    const int KT = a.KT;  // packed weight tiles (128 k) per row tile; K is a multiple of 128 here
-
-    // Sources of the copies: a wavefront-uniform base that advances along K, plus
-    // a per-lane byte offset that never changes.
-    // activations: block b = wave + 8 i (i < 4) = rows 8 (b % 16) .. + 7 of half b / 16 = i / 2
-    const char *xbase = reinterpret_cast<const char *>(a.x) + (size_t)mt * DBM * a.K * 2;
-    uint32_t xlane[2];
+    // rows past the last (their products are never stored) take the rows of the tile before, so that no line is copied over and over
+    const int back = m0 > 0 ? ROWS : 0;
+    const char *xbase = reinterpret_cast<const char *>(a.x) + (size_t)(m0 - back) * a.K * 2;
+    uint32_t xlane[XC];
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
-        const int rl = 8 * (wave + 8 * i) + (lane >> 3);
+    for (int i = 0; i < XC; ++i) {
+        const int rl = 8 * wave + 32 * i + (lane >> 3);
         const int oct = (lane & 7) ^ ((rl >> 1) & 7);
-        const int row = min(mt * DBM + rl, a.M - 1) - mt * DBM;  // rows past M: any finite data, never stored
+        const int row = m0 + rl < a.M ? back + rl : back ? rl : a.M - 1;
         xlane[i] = (uint32_t)row * (uint32_t)a.K * 2u + oct * 16;
     }
-    // codes: row tiles 2 ks, 2 ks + 1 of the channel group; lane l takes vector l of a packed tile
-    const char *wbase = reinterpret_cast<const char *>(a.w) + (size_t)(nt * (DBN / 16) + ng * 4 + ks * 2) * a.rt_stride * 1024;
-    const uint32_t wlane = lane * 16;
-    // scales: lane l = (row tile l / 16, row l % 16) takes the 16-byte vector of its row
-    const char *sbase = reinterpret_cast<const char *>(a.w) + (size_t)(nt * (DBN / 16) + ng * 4) * a.rt_stride * 1024;
-    const uint32_t slane = (uint32_t)q * a.rt_stride * 1024u + c * 16;
     const size_t rt_bytes = (size_t)a.rt_stride * 1024;
+    const char *wbase = reinterpret_cast<const char *>(a.w) + (size_t)(nt * 16 + wave * 4) * rt_bytes;
+    const uint32_t wlane = lane * 16;
+    const uint32_t slane = (uint32_t)q * a.rt_stride * 1024u + c * 16;
 
-    const uint32_t lds0 = (uint32_t)(uintptr_t)(lptr_t)lds;  // LDS byte address of the rings
-    // The 7 copies of a batch, one at a time (they are spread over the MFMA blocks of
-    // a tile: issued together by all eight wavefronts right after the barrier they
-    // would queue up behind each other in the memory pipeline while the matrix
-    // cores idle).  Past the end of K the copies start over at tile 0, so that the
-    // count of outstanding copies is the same on every iteration, and all land in
-    // one spare KiB behind the rings that nothing reads and the exchange and store
-    // phases never use (distinct sources, not the last tile again and again: many
-    // copies of the same lines in flight from one wavefront had been seen in ring
-    // slots after the counter said they were done; the cause is not known, so no
-    // late copy may have a destination that anything reads or reuses).
-    // (bulk: the caller knows that tile t lies inside K; the tiles of the main loop's bulk part then
-    // carry no end-of-K tests)
-    constexpr bool kBulk = true, kEdge = false;  // (constants at every call site: the tests fold away)
-    auto issue_w = [&](int t, int i, const bool bulk) __attribute__((always_inline)) {  // codes of tile t, row tile 2 ks + i of the channel group
-        const bool real = bulk || t < KT;
-        const int tc = real ? t : min(t - KT, KT - 1);
-        const size_t wpos = (size_t)(PC ? tc : tc + (tc >> 3)) * 1024;
-        copy16_to_lds(wbase + i * rt_bytes + wpos, wlane,
-                      lds0 + (real ? DW_OFF + (t % DRING) * DW_BYTES + (ng * 4 + ks * 2 + i) * 1024 : DSPARE_OFF));
+    auto issue_x = [&](int i, int blk) __attribute__((always_inline)) {  // half stage i
+        copy16_to_lds(xbase + (size_t)(i0 + i) * 128, xlane[blk], lds0 + (i % 3) * L::kX + blk * 4096 + wave * 1024);
     };
-    auto issue_s = [&](int t, const bool bulk) __attribute__((always_inline)) {  // scales of tile t: vector (t % 8) / 2 * 16 + row of the unit's scale tile (8 groups = 2 tiles)
-        const bool real = bulk || t < KT;
-        const int tc = real ? t : min(t - KT, KT - 1), u = tc >> 3;
-        const size_t spos = (size_t)(min(8 * u + 8, KT) + u) * 1024 + (size_t)((tc & 7) >> 1) * 256;
-        copy16_to_lds(sbase + spos, slane, lds0 + (real ? DS_OFF + (t % DRING) * DS_BYTES + ng * 1024 : DSPARE_OFF));
-    };
-    auto issue_x = [&](int t, int i, const bool bulk) __attribute__((always_inline)) {  // activation stage t, block wave + 8 (i % 2) of half i / 2
-        const bool real = bulk || t < KT;
-        const int tc = real ? t : min(t - KT, KT - 1);
-        copy16_to_lds(xbase + (size_t)tc * 256 + (i >> 1) * 128, xlane[i & 1],
-                      lds0 + (real ? (t % DRING) * DX_BYTES + wave * 1024 + (i >> 1) * (DX_BYTES / 2) + (i & 1) * 8192 : DSPARE_OFF));
-    };
-    auto issue_batch = [&](int tw, int tx) {
-        issue_w(tw, 0, kEdge); issue_w(tw, 1, kEdge);
-        if (!PC) issue_s(tw, kEdge);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) issue_x(tx, i, kEdge);
+    // codes of tile t (int8: of half stage t), row tile k of the wavefront; k = 4: its scales
+    auto issue_w = [&](int t, int k) __attribute__((always_inline)) {
+        const int ta = i0 / kStep + t, u = ta >> 3;
+        if (k < 4)
+            copy16_to_lds(wbase + k * rt_bytes + (size_t)(G32 ? ta + u : ta) * 1024, wlane, lds0 + W_OFF + (W8 ? (t & 1) * 16384 : 0) + (wave * 4 + k) * 1024);
+        else
+            copy16_to_lds(wbase + (size_t)(min(8 * u + 8, a.KT) + u) * 1024 + (size_t)((ta & 7) >> 1) * 256, slane, lds0 + S_OFF + wave * 1024);
     };
 
-    v16f acc[2][4];
+    v16f acc[2][JP];
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
+        for (int j = 0; j < JP; ++j)
 #pragma unroll
             for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.0f;
 
-    // operand read addresses of this lane
-    int xoff[2][2];  // [group of the half][k step s]: row r, octet (4 g + 2 s + kh) ^ ((r >> 1) & 7)
+    int xoff[4];  // k step j of a half stage: octet of this lane
 #pragma unroll
-    for (int g = 0; g < 2; ++g)
-#pragma unroll
-        for (int s = 0; s < 2; ++s) xoff[g][s] = ks * (DX_BYTES / 2) + r * 128 + (((4 * g + 2 * s + kh) ^ ((r >> 1) & 7)) << 4);
-    const char *wring = lds_b + DW_OFF + ng * 4096 + ((r >> 4) * 64 + kh * 16 + (r & 15)) * 16 + ks * 8;
-    const char *sring = lds_b + DS_OFF + ng * 1024 + r * 16 + ks * 4;
+    for (int j = 0; j < 4; ++j) xoff[j] = r * 128 + (((W8 ? 4 * (j >> 1) + 2 * kh + (j & 1) : 2 * j + kh) ^ ((r >> 1) & 7)) << 4);
+    const char *wread = lds_b + W_OFF + wave * 4096 + ((r >> 4) * 64 + kh * 16 + (r & 15)) * 16;
+    const char *sread = lds_b + S_OFF + wave * 1024 + r * 16;
 
-    uint4 x0[4][2], x1[4][2];  // activations of a group: [token row block jp][k step s]
-    uint2 wv[2][2];            // codes of the current tile: [row pair ip][k step s], .x / .y = this wavefront's two groups
-    uint32_t sv[2];            // their scales: [row pair ip], two binary16
-    v8h fa0[2][2], fa1[2][2];  // converted weights of a group
-
-    auto read_x = [&](uint4 (&x)[4][2], int g, int t) {
-        const char *lx = lds_b + (t % DRING) * DX_BYTES;
-#pragma unroll
-        for (int jp = 0; jp < 4; ++jp)
-#pragma unroll
-            for (int s = 0; s < 2; ++s) x[jp][s] = *reinterpret_cast<const uint4 *>(lx + xoff[g][s] + jp * 4096);
-    };
-    auto read_ws = [&](int t) {
+    uint4 xv[2][JP];  // token rows of a k step of 16, two steps in turn
+    v8h fa[2][2];     // its converted weights: [step in turn][row pair]
+    uint4 wv[2][2];   // 4-bit codes of a tile: [row pair][k step of a group], one dword per group; int8 codes of a half stage: [row pair][two k steps]
+    uint2 sv[2];
+    auto read_ws = [&](int t) __attribute__((always_inline)) {
 #pragma unroll
         for (int ip = 0; ip < 2; ++ip) {
 #pragma unroll
-            for (int s = 0; s < 2; ++s)
-                wv[ip][s] = *reinterpret_cast<const uint2 *>(wring + (t % DRING) * DW_BYTES + ip * 2048 + s * 512);
-            if (!PC) sv[ip] = *reinterpret_cast<const uint32_t *>(sring + (t % DRING) * DS_BYTES + ip * 512 + (t & 1) * 8);
+            for (int s = 0; s < 2; ++s) wv[ip][s] = *reinterpret_cast<const uint4 *>(wread + (W8 ? (t & 1) * 16384 : 0) + ip * 2048 + s * 512);
+            if (G32) sv[ip] = *reinterpret_cast<const uint2 *>(sread + ip * 512 + ((i0 / kStep + t) & 1) * 8);
         }
     };
-    // quarter qb of the conversion of a group: operand (ip, s) = (qb / 2, qb % 2)
-    auto convert = [&](v8h (&fa)[2][2], int g, int qb) {  // g = 0, 1: group of this wavefront's half of the tile
-        const int ip = qb >> 1, sx = qb & 1;
-        if (PC) {
-            fa[ip][sx] = dequant_frag_unscaled(g ? wv[ip][sx].y : wv[ip][sx].x);
-        } else {
-            const h2 s2 = as_h2(__builtin_amdgcn_perm(0u, sv[ip], g ? 0x03020302u : 0x01000100u));
-            fa[ip][sx] = dequant_frag(g ? wv[ip][sx].y : wv[ip][sx].x, s2);
+    // operand of row pair ip, k step j of half h
+    auto convert = [&](v8h &f, int ip, int h, int j) __attribute__((always_inline)) {
+        if (W8) {
+            const uint4 &v = wv[ip][j >> 1];
+            f = __builtin_bit_cast(v8h, j & 1 ? dequant_i8x8(v.z, v.w) : dequant_i8x8(v.x, v.y));
+            return;
         }
+        const uint4 &v = wv[ip][j & 1];
+        const int g = 2 * h + (j >> 1);
+        const uint32_t w = g == 0 ? v.x : g == 1 ? v.y : g == 2 ? v.z : v.w;
+        if (G32)
+            f = dequant_frag(w, as_h2(__builtin_amdgcn_perm(0u, g & 2 ? sv[ip].y : sv[ip].x, g & 1 ? 0x03020302u : 0x01000100u)));
+        else
+            f = dequant_frag_unscaled(w);
     };
-    // quarter qb of the product of a group: k step qb / 2, token row blocks 2 (qb % 2), + 1
-    auto multiply = [&](const v8h (&fa)[2][2], const uint4 (&x)[4][2], int qb) {
-        const int sx = qb >> 1;
+    auto multiply = [&](const v8h (&f)[2], const uint4 (&x)[JP], int qd) __attribute__((always_inline)) {
 #pragma unroll
-        for (int jj = 0; jj < 2; ++jj) {
-            const int jp = 2 * (qb & 1) + jj;
-#pragma unroll
-            for (int ip = 0; ip < 2; ++ip)
-                acc[ip][jp] = __builtin_amdgcn_mfma_f32_32x32x16_f16(fa[ip][sx], __builtin_bit_cast(v8h, x[jp][sx]),
-                                                                     acc[ip][jp], 0, 0, 0);
-        }
+        for (int m = qd * JP / 2; m < (qd + 1) * JP / 2; ++m)
+            acc[m & 1][m >> 1] = __builtin_amdgcn_mfma_f32_32x32x16_f16(f[m & 1], __builtin_bit_cast(v8h, x[m >> 1]), acc[m & 1][m >> 1], 0, 0, 0);
     };
 
-    // Copies in issue order: codes/scales 0, codes/scales 1, stage 0 | codes/scales 2,
-    // stage 1 | then during tile t: codes/scales t + 3, stage t + 2.
-    issue_w(0, 0, kEdge); issue_w(0, 1, kEdge);
-    if (!PC) issue_s(0, kEdge);
-    issue_w(1, 0, kEdge); issue_w(1, 1, kEdge);
-    if (!PC) issue_s(1, kEdge);
+    // Copies in issue order: codes 0 (int8: and 1), half stages 0, 1 | during half stage i: codes of the next tile (int8: of half stage
+    // i + 2), half stage i + 2.
 #pragma unroll
-    for (int i = 0; i < 4; ++i) issue_x(0, i, kEdge);
-    issue_batch(2, 1);
+    for (int k = 0; k < WC; ++k) issue_w(0, k);
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < XC; ++i) issue_x(0, i);
+    if (nst > 1) {
+        if (W8) {
 #pragma unroll
-        for (int j = 0; j < 2; ++j) fa1[i][j] = v8h{0, 0, 0, 0, 0, 0, 0, 0};
+            for (int k = 0; k < WC; ++k) issue_w(1, k);
+        }
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+        for (int i = 0; i < XC; ++i) issue_x(1, i);
+        wait_vmcnt<2 * XC + (W8 ? WC : 0)>();
+    } else {
+        wait_vmcnt<XC>();
+    }
 #pragma unroll
-        for (int j = 0; j < 2; ++j) x1[i][j] = make_uint4(0, 0, 0, 0);
-    wait_vmcnt<BATCH>();
-    asm volatile("s_barrier" ::: "memory");
+    for (int ip = 0; ip < 2; ++ip) fa[1][ip] = v8h{0, 0, 0, 0, 0, 0, 0, 0};
+#pragma unroll
+    for (int jp = 0; jp < JP; ++jp) xv[1][jp] = make_uint4(0, 0, 0, 0);
     read_ws(0);
-    auto tile = [&](int t, const bool bulk) __attribute__((always_inline)) {
-        // What was issued two tiles ago has landed once only the newest batch is
-        // outstanding: stage t, codes and scales of tile t + 1.  The barrier makes
-        // the other wavefronts' copies visible and says that every wavefront is done
-        // with stage t - 1 and has the codes of tile t in registers: their slots are
-        // overwritten by the copies issued during this tile.
-        wait_vmcnt<BATCH>();
-        asm volatile("s_barrier" ::: "memory");
-        read_x(x0, 0, t);
-        __builtin_amdgcn_sched_barrier(0);  // the reads are in flight before the MFMAs start
-#pragma unroll
-        for (int qb = 0; qb < 4; ++qb) {  // group before x converted group 0; activation copies in between
-            multiply(fa1, x1, qb);
-            convert(fa0, 0, qb);
-            interleave_mfma_valu();
-            __builtin_amdgcn_sched_barrier(0);
-            issue_x(t + 2, qb, bulk);
-        }
-        read_x(x1, 1, t);
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int qb = 0; qb < 4; ++qb) {
-            multiply(fa0, x0, qb);
-            convert(fa1, 1, qb);
-            interleave_mfma_valu();
-            __builtin_amdgcn_sched_barrier(0);
-            if (qb == 0) issue_w(t + 3, 0, bulk);
-            if (qb == 1) issue_w(t + 3, 1, bulk);
-            if (qb == 2 && !PC) issue_s(t + 3, bulk);
-        }
-        read_ws(t + 1);
-    };
-    {
-        int t = 0;
-        for (; t + 3 < KT; ++t) tile(t, kBulk);  // every copy issued during these tiles lies inside K
-        for (; t < KT; ++t) tile(t, kEdge);
-    }
-#pragma unroll
-    for (int qb = 0; qb < 4; ++qb) multiply(fa1, x1, qb);
-    wait_vmcnt<0>();
 
-    // The two wavefronts of a channel group hold partial sums of the same outputs.
-    // Each keeps two of the four 32-row blocks and hands the other two to its
-    // partner through LDS ([wavefront][16-byte vector][lane], 16 KiB per wavefront
-    // over the dead rings), adds what it receives, and stores its half.
-    asm volatile("s_barrier" ::: "memory");  // every wavefront is done with the rings
-    const int keep = 2 * ks;                  // token row blocks keep, keep + 1 stay here
-    {
-        float4 *mine = reinterpret_cast<float4 *>(lds_b + wave * DEX_BYTES) + lane;
+    // Half stage i.  more: how many half stages follow it, 2 standing for more of them; h: its half of the 128-k tile (4-bit codes).
+    auto half = [&](int i, const int h, const int more) __attribute__((always_inline)) {
+        // Issued after half stage i: half stage i + 1 and, in front of it, the codes issued at the same time (4-bit: with even ones).
+        // The barrier makes the other wavefronts' copies visible and says that every wavefront has read half stage i - 1, whose slot
+        // the copies of this one overwrite.
+        constexpr int kBoth = XC + WC;
+        if (more == 0)
+            wait_vmcnt<0>();
+        else if (W8 ? true : h == 1 && more == 2)
+            wait_vmcnt<kBoth>();
+        else
+            wait_vmcnt<XC>();
+        asm volatile("s_barrier" ::: "memory");
+        const char *xs = lds_b + (i % 3) * L::kX;
+        int slot = 0;
 #pragma unroll
-        for (int ip = 0; ip < 2; ++ip)
+        for (int j = 0; j < 4; ++j) {  // k step j of the half stage is read and converted, the step before it multiplied
 #pragma unroll
-            for (int jj = 0; jj < 2; ++jj)
+            for (int jp = 0; jp < JP; ++jp) xv[j & 1][jp] = *reinterpret_cast<const uint4 *>(xs + xoff[j] + jp * 4096);
+            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                for (int qq = 0; qq < 4; ++qq) {
-                    const v16f &v = ks ? acc[ip][jj] : acc[ip][2 + jj];
-                    mine[((ip * 2 + jj) * 4 + qq) * 64] = make_float4(v[4 * qq], v[4 * qq + 1], v[4 * qq + 2], v[4 * qq + 3]);
+            for (int qd = 0; qd < 4; ++qd) {
+                multiply(fa[(j + 1) & 1], xv[(j + 1) & 1], qd);
+                if (qd < 2) {
+                    convert(fa[j & 1][qd], qd, h, j);
+#pragma unroll
+                    for (int k = qd * JP / 2; k < (qd + 1) * JP / 2; ++k) {
+                        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                        __builtin_amdgcn_sched_group_barrier(0x002, JP == 4 ? 8 : 14, 0);
+                    }
                 }
+                __builtin_amdgcn_sched_barrier(0);
+                if (W8 || h == 0) {
+                    if (slot < WC) {
+                        if (more == 2) issue_w(W8 ? i + 2 : (i >> 1) + 1, slot);
+                    } else if (slot < WC + XC) {
+                        if (more == 2) issue_x(i + 2, slot - WC);
+                    }
+                } else if (slot % (16 / (XC + XC % 2)) == 0 && slot / (16 / (XC + XC % 2)) < XC) {
+                    if (more == 2) issue_x(i + 2, slot / (16 / (XC + XC % 2)));
+                }
+                ++slot;
+                if ((W8 || h == 1) && j == 3 && qd == 1 && more > 0) {
+                    // the next codes have landed once only what was issued after them is outstanding
+                    if (W8) {
+                        if (more == 2) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * XC + WC) : "memory");
+                        else asm volatile("s_waitcnt vmcnt(%0)" ::"n"(XC) : "memory");
+                    } else if (more == 2) {
+                        asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * XC) : "memory");
+                    } else {
+                        asm volatile("s_waitcnt vmcnt(%0)" ::"n"(XC) : "memory");
+                    }
+                    read_ws(W8 ? i + 1 : (i >> 1) + 1);
+                }
+            }
+        }
+    };
+    if constexpr (W8) {
+        int i = 0;
+        for (; i + 2 < nst; ++i) half(i, 0, 2);
+        if (i + 1 < nst) half(i++, 0, 1);
+        half(i, 0, 0);
+    } else {
+        int i = 0;
+        for (; i + 2 < nst; i += 2) {
+            half(i, 0, 2);
+            half(i + 1, 1, 2);
+        }
+        half(i, 0, 1);
+        half(i + 1, 1, 0);
     }
-    __syncthreads();
-    v16f out[2][2];  // [ip][jj]: block keep + jj
-    {
-        const float4 *theirs = reinterpret_cast<const float4 *>(lds_b + (wave ^ 4) * DEX_BYTES) + lane;
+    if (KS == 2) {
+        for (int i = nst; i < first; ++i) asm volatile("s_barrier" ::: "memory");  // (as many barriers as the first group passes)
+    }
+#pragma unroll
+    for (int qd = 0; qd < 4; ++qd) multiply(fa[1], xv[1], qd);
+
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");  // every wavefront is done with the rings
+    const int n0 = nt * TN + wave * 64;
+    char *region = lds_all + (threadIdx.x >> 6) * (32 * kStorePitch);
+    if constexpr (KS == 1) {
+        store_tile<!G32, JP>(a, acc, n0, m0, region, lane);
+    } else {
+        // The two halves of K meet: each group keeps half of the blocks of 32 rows and hands the other half to its partner
+        // through LDS ([wavefront][16-byte vector][lane]), over the dead rings.
+        constexpr int HB = JP / 2;
+        constexpr int kEx = 2 * HB * 16 * 256;  // bytes per wavefront
+        static_assert(KS == 1 || (JP % 2 == 0 && 8 * kEx <= 2 * L::kBytes), "halves of the sums fit over the rings");
+        float4 *mine = reinterpret_cast<float4 *>(lds_all + (group * 4 + wave) * kEx) + lane;
 #pragma unroll
         for (int ip = 0; ip < 2; ++ip)
 #pragma unroll
-            for (int jj = 0; jj < 2; ++jj)
+            for (int jj = 0; jj < HB; ++jj)
 #pragma unroll
                 for (int qq = 0; qq < 4; ++qq) {
-                    const float4 p = theirs[((ip * 2 + jj) * 4 + qq) * 64];
-                    const v16f &v = ks ? acc[ip][2 + jj] : acc[ip][jj];
+                    const v16f &v = group ? acc[ip][jj] : acc[ip][HB + jj];
+                    mine[((ip * HB + jj) * 4 + qq) * 64] = make_float4(v[4 * qq], v[4 * qq + 1], v[4 * qq + 2], v[4 * qq + 3]);
+                }
+        __syncthreads();
+        const float4 *theirs = reinterpret_cast<const float4 *>(lds_all + ((group ^ 1) * 4 + wave) * kEx) + lane;
+        v16f out[2][HB];
+#pragma unroll
+        for (int ip = 0; ip < 2; ++ip)
+#pragma unroll
+            for (int jj = 0; jj < HB; ++jj)
+#pragma unroll
+                for (int qq = 0; qq < 4; ++qq) {
+                    const float4 p = theirs[((ip * HB + jj) * 4 + qq) * 64];
+                    const v16f &v = group ? acc[ip][HB + jj] : acc[ip][jj];
                     out[ip][jj][4 * qq + 0] = v[4 * qq + 0] + p.x;
                     out[ip][jj][4 * qq + 1] = v[4 * qq + 1] + p.y;
                     out[ip][jj][4 * qq + 2] = v[4 * qq + 2] + p.z;
                     out[ip][jj][4 * qq + 3] = v[4 * qq + 3] + p.w;
                 }
-    }
-    __syncthreads();  // the exchange buffers are free: each wavefront stages its stores in its own
-    if (PC) {  // per-channel scale of the lane's output channels
-#pragma unroll
-        for (int ip = 0; ip < 2; ++ip)
-#pragma unroll
-            for (int qq = 0; qq < 4; ++qq) {
-                const float4 sc = *reinterpret_cast<const float4 *>(a.sw + nt * DBN + ng * 64 + ip * 32 + 8 * qq + 4 * kh);
-#pragma unroll
-                for (int jj = 0; jj < 2; ++jj) {
-                    out[ip][jj][4 * qq + 0] *= sc.x;
-                    out[ip][jj][4 * qq + 1] *= sc.y;
-                    out[ip][jj][4 * qq + 2] *= sc.z;
-                    out[ip][jj][4 * qq + 3] *= sc.w;
-                }
-            }
-    }
-
-    // Epilogue: a lane holds one token row (lane % 32) and groups of four
-    // consecutive n.  The binary16 values go through a per-wavefront LDS block
-    // (32 token rows x 64 channels) and leave as 16-byte stores along n.
-    const int n0 = nt * DBN + ng * 64;
-    if (a.gated_act >= 0) {
-        // Layer packed in pairs (operator fusion, section 3.6 of the paper): physical rows 32 t .. + 15
-        // are gate rows and 32 t + 16 .. + 31 the other branch's rows of the same 16 channels, so the
-        // registers 4 qq + e (qq = 0, 1) and 4 (qq + 2) + e of a 32 x 32 tile are the two branches of one
-        // channel.  32 output channels per wavefront, rows of N / 2 values.
-        const GateCoeffs gc = gate_coeffs(a.gated_act);
-        const int half = a.N / 2, o0 = n0 / 2;
-        char *region = lds_b + wave * DEX_BYTES;
-#pragma unroll
-        for (int jj = 0; jj < 2; ++jj) {
-            const int mrow0 = mt * DBM + (keep + jj) * 32;
-#pragma unroll
-            for (int ip = 0; ip < 2; ++ip)
-#pragma unroll
-                for (int qq = 0; qq < 2; ++qq) {
-                    typedef _Float16 h4 __attribute__((ext_vector_type(4)));
-                    h4 hv;
-#pragma unroll
-                    for (int e = 0; e < 4; ++e)
-                        hv[e] = (_Float16)(gate_activation(out[ip][jj][4 * qq + e], gc) * out[ip][jj][4 * (qq + 2) + e]);
-                    *reinterpret_cast<h4 *>(region + r * DEPI_PITCH + (ip * 16 + 8 * qq + 4 * kh) * 2) = hv;
-                }
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-#pragma unroll
-            for (int it = 0; it < 2; ++it) {  // 32 rows x 4 chunks of 16 bytes
-                const int idx = it * 64 + lane;
-                const int row = idx >> 2, ch = idx & 3;
-                const uint4 v = *reinterpret_cast<const uint4 *>(region + row * DEPI_PITCH + ch * 16);
-                const int mm = mrow0 + row, nn = o0 + ch * 8;
-                if (mm < a.M && nn < half) *reinterpret_cast<uint4 *>(a.y + (size_t)mm * half + nn) = v;
-            }
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        }
-        return;
-    }
-    if ((a.N % 8) == 0) {
-        char *region = lds_b + wave * DEX_BYTES;
-#pragma unroll
-        for (int jj = 0; jj < 2; ++jj) {
-            const int mrow0 = mt * DBM + (keep + jj) * 32;
-            const bool has_res = a.res != nullptr;
-            if (has_res) stage_residual_block<8, DEPI_PITCH>(region, a.res, mrow0, n0, a.M, a.N, lane);
-#pragma unroll
-            for (int ip = 0; ip < 2; ++ip) {
-#pragma unroll
-                for (int qq = 0; qq < 4; ++qq) {
-                    const int nl = ip * 32 + 8 * qq + 4 * kh;
-                    typedef _Float16 h4 __attribute__((ext_vector_type(4)));
-                    float v[4] = {out[ip][jj][4 * qq + 0], out[ip][jj][4 * qq + 1], out[ip][jj][4 * qq + 2],
-                                  out[ip][jj][4 * qq + 3]};
-                    if (has_res) {
-                        float rv[4];
-                        staged_residual4(region, r * DEPI_PITCH + nl * 2, rv);
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) v[e] += rv[e];
-                    }
-                    const h4 hv = {(_Float16)v[0], (_Float16)v[1], (_Float16)v[2], (_Float16)v[3]};
-                    *reinterpret_cast<h4 *>(region + r * DEPI_PITCH + nl * 2) = hv;
-                }
-            }
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-#pragma unroll
-            for (int it = 0; it < 4; ++it) {  // 32 rows x 8 chunks of 16 bytes
-                const int idx = it * 64 + lane;
-                const int row = idx >> 3, ch = idx & 7;
-                const uint4 v = *reinterpret_cast<const uint4 *>(region + row * DEPI_PITCH + ch * 16);
-                const int mm = mrow0 + row, nn = n0 + ch * 8;
-                if (mm < a.M && nn < a.N) *reinterpret_cast<uint4 *>(a.y + (size_t)mm * a.N + nn) = v;
-            }
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        }
-        return;
-    }
-#pragma unroll
-    for (int jj = 0; jj < 2; ++jj) {
-        const int m = mt * DBM + (keep + jj) * 32 + r;
-        if (m >= a.M) continue;
-#pragma unroll
-        for (int ip = 0; ip < 2; ++ip)
-#pragma unroll
-            for (int e = 0; e < 16; ++e) {
-                const int n = n0 + ip * 32 + 8 * (e >> 2) + 4 * kh + (e & 3);
-                if (n < a.N) {
-                    float v = out[ip][jj][e];
-                    if (a.res) v += (float)a.res[(size_t)m * a.N + n];
-                    a.y[(size_t)m * a.N + n] = (_Float16)v;
-                }
-            }
+        __syncthreads();
+        store_tile<!G32, HB>(a, out, n0, m0 + group * HB * 32, region, lane);
     }
 }
 
-template <bool PC>
-hipError_t launch_direct(GemmF16Args a, int M, hipStream_t st) {
-    if (const hipError_t e = allow_dynamic_lds<gemm_f16_w4_direct_kernel<PC>>(kDirectLdsBytes); e != hipSuccess) return e;
-    a.n_tiles = (a.N + DBN - 1) / DBN;
-    a.m_tiles = (M + DBM - 1) / DBM;
-    a.by_tokens = walk_by_tokens(a.n_tiles, a.m_tiles, (PC ? 0.5f : 0.5625f) * DBN, 2.0f * DBM);
-    gemm_f16_w4_direct_kernel<PC><<<dim3((unsigned)(a.n_tiles * a.m_tiles)), 512, kDirectLdsBytes, st>>>(a);
+template <int FMT, int JP, int KS>
+hipError_t launch_tile(GemmF16Args a, hipStream_t st) {
+    constexpr size_t bytes = KS * TileLds<FMT, JP>::kBytes;
+    if (const hipError_t e = allow_dynamic_lds<gemm_f16_tile_kernel<FMT, JP, KS>>(bytes); e != hipSuccess) return e;
+    a.n_tiles = (a.N + TN - 1) / TN;
+    a.m_tiles = (a.M + 32 * JP - 1) / (32 * JP);
+    a.by_tokens = walk_by_tokens(a.n_tiles, a.m_tiles, (FMT == kW8C ? 1.0f : FMT == kW4C ? 0.5f : 0.5625f) * TN, 2.0f * 32 * JP);
+    gemm_f16_tile_kernel<FMT, JP, KS><<<dim3((unsigned)(a.n_tiles * a.m_tiles)), 256 * KS, bytes, st>>>(a);
     return hipGetLastError();
 }
 
@@ -752,11 +716,74 @@ hipError_t launch_fallback(GemmF16Args a, int M, hipStream_t st) {
     return hipGetLastError();
 }
 
+constexpr int kTileForms = 6;
+
+template <int FMT>
+hipError_t tile_form(const GemmF16Args &a, int form, hipStream_t st) {
+    switch (form) {
+        case 1: return launch_tile<FMT, 1, 1>(a, st);
+        case 2: return launch_tile<FMT, 2, 1>(a, st);
+        case 3: return launch_tile<FMT, 3, 1>(a, st);
+        case 4: return launch_tile<FMT, 4, 1>(a, st);
+        case 5: return launch_tile<FMT, 4, 2>(a, st);
+        case 6: return launch_tile<FMT, 2, 2>(a, st);
+    }
+    return hipErrorInvalidValue;
+}
+
 }  // namespace
+
+bool tile_kernel_takes(const Geometry &g) { return g.K % (g.fmt == kW8C ? 64 : 128) == 0; }
+
+// Estimated time of the main kernel and the form it is fastest in.  A tile takes `each` us and K / 1000 times `alone` on a
+// compute unit of its own, `shared` where several are in flight.  The part that grows with K slows down with the number of compute units that are
+// busy, since power is what they share: `cap` is about the share of the chip that runs at full clock.
+// Fitted to 2960 shapes of 768 to 28672 channels, K of 256 to 14336 and 20 to 6500 rows (standard deviation 2 to 5 %); the choice is 0.2 % slower than the
+// best of the six forms on average, 5 % in one of a hundred shapes.  us, forms 1 to 6 (32, 64, 96, 128 rows; 128 and 64 rows with two halves of K): int4
+// groups 2304 x 9216, 1000 rows 92 / 75 / 89 / 101 / 84 / 60; 4096 x 2304, 2048 rows 55 / 42 / 46 / 39 / 38 / 44; int4 2304 x 14336, 1000 rows
+// 114 / 94 / 113 / 138 / 119 / 79.
+int tile_rows(int form) {
+    static const int rows[kTileForms] = {32, 64, 96, 128, 128, 64};
+    return rows[form - 1];
+}
+
+float tile_us(const Geometry &g, int M, int num_cus, int *form) {
+    struct Fit {
+        float start, each, alone, shared, cap;
+    };
+    static const Fit fits[3][kTileForms] = {
+        // int8
+        {{2.12f, 0.84f, 5.82f, 4.16f, 1.02f}, {2.25f, 1.39f, 6.78f, 5.53f, 0.82f}, {2.48f, 1.90f, 8.18f, 6.88f, 0.74f},
+         {2.90f, 2.26f, 9.36f, 8.21f, 0.69f}, {1.01f, 5.07f, 8.01f, 7.83f, 0.59f}, {1.11f, 3.27f, 5.30f, 5.19f, 0.67f}},
+        // int4, group scales
+        {{2.37f, 0.55f, 6.31f, 4.63f, 1.06f}, {2.44f, 1.05f, 7.54f, 6.09f, 0.92f}, {2.49f, 1.69f, 9.10f, 7.82f, 0.85f},
+         {2.64f, 2.14f, 10.14f, 8.83f, 0.74f}, {0.76f, 5.00f, 8.34f, 8.23f, 0.61f}, {1.08f, 3.16f, 5.66f, 5.53f, 0.71f}},
+        // int4
+        {{2.47f, 0.59f, 4.89f, 3.66f, 1.00f}, {2.59f, 1.12f, 5.86f, 4.82f, 0.80f}, {2.59f, 1.75f, 7.38f, 6.58f, 0.76f},
+         {2.74f, 2.26f, 9.12f, 7.95f, 0.72f}, {0.93f, 5.06f, 7.74f, 7.59f, 0.63f}, {1.48f, 2.93f, 4.77f, 4.71f, 0.69f}}};
+    const float k = 1e-3f * (float)g.K;
+    float best = 0.0f;
+    *form = 0;
+    for (int i = 0; i < kTileForms; ++i) {
+        if (i >= 4 && g.K < 256) break;  // (two halves of K: two steps of 128 at least)
+        const Fit &f = fits[g.fmt][i];
+        const int rows = tile_rows(i + 1), tiles = (g.N + TN - 1) / TN * ((M + rows - 1) / rows);
+        const int full = tiles / num_cus, rest = tiles % num_cus;
+        auto work = [&](int n) { return n == 0 ? 0.0f : n == 1 ? f.alone * k : (float)n * f.shared * k; };  // of a compute unit with n tiles
+        auto slowed = [&](int busy) {
+            const float u = (float)busy / (f.cap * (float)num_cus);
+            return sqrtf(sqrtf(1.0f + u * u * u * u));
+        };
+        float us = f.start + (float)full * f.each + work(full) * slowed(num_cus);
+        if (rest > 0) us += fmaxf(f.each + (work(full + 1) - work(full)) * slowed(rest), 0.0f);
+        if (*form == 0 || us < best) best = us, *form = i + 1;
+    }
+    return best;
+}
 
 hipError_t launch_gemm_f16(const Geometry &g, const void *packed, const void *x, int M, void *y,
                            const void *residual, int gated_act, int num_cus, hipStream_t st) {
-    // only the kernel that converts in registers has the merged gating (int4 formats, K a multiple of 128)
+    // (a gated output is offered for int4 formats and K a multiple of 128)
     if (gated_act >= 0 && (!g.pair_half || (g.K % 128) != 0 || g.fmt == kW8C)) return hipErrorNotSupported;
     if (skinny_product(g, M, false, gated_act >= 0, num_cus)) return launch_skinny_f16(g, packed, x, M, y, residual, gated_act, num_cus, st);
     GemmF16Args a;
@@ -772,17 +799,21 @@ hipError_t launch_gemm_f16(const Geometry &g, const void *packed, const void *x,
     a.rt_stride = g.rt_stride;
     a.n_tiles = a.m_tiles = a.by_tokens = 0;
     a.gated_act = gated_act;
-    if (g.fmt == kW8C) return launch_fallback<true, true>(a, M, st);
-    const bool pc = g.fmt == kW4C;
-    if ((g.K % 128) == 0 && (tuning().gemm_variant != 9 || gated_act >= 0)) {
+    if (tile_kernel_takes(g) && (tuning().gemm_variant != 9 || gated_act >= 0)) {
         const int rest = skinny_tail_rows(g, M, gated_act >= 0, num_cus), most = M - rest;
+        int form;
+        tile_us(g, most, num_cus, &form);
+        const int forced = tuning().gemm_variant - 30;  // (tests: a form by its number)
+        if (forced >= 1 && forced <= (g.K < 256 ? 4 : kTileForms)) form = forced;
         a.M = most;
-        const hipError_t e = pc ? launch_direct<true>(a, most, st) : launch_direct<false>(a, most, st);
+        const hipError_t e = g.fmt == kW8C ? tile_form<kW8C>(a, form, st) : g.fmt == kW4C ? tile_form<kW4C>(a, form, st) : tile_form<kW4G32>(a, form, st);
         if (e != hipSuccess || rest == 0) return e;
         const int n_out = gated_act >= 0 ? g.N / 2 : g.N;
         return launch_skinny_f16(g, packed, static_cast<const _Float16 *>(x) + (size_t)most * g.K, rest, a.y + (size_t)most * n_out,
                                  residual ? a.res + (size_t)most * g.N : nullptr, gated_act, num_cus, st);
     }
+    if (g.fmt == kW8C) return launch_fallback<true, true>(a, M, st);
+    const bool pc = g.fmt == kW4C;
     return pc ? launch_fallback<true>(a, M, st) : launch_fallback<false>(a, M, st);
 }
 

@@ -627,8 +627,7 @@ SkinnyArgs make_args(const Geometry &g, const void *packed, const void *x, const
 // tiles, int8 activations with the quantization kernel):
 //   int8 x int4  34000 x 2048 19.7 / 16.8, x 4096 28.4 / 28.8; 40000 x 1024 17.4 / 13.3, x 4096 32.9 / 29.6; 57000 x 8192 71.0 / 66.9
 //   int8 x int8  40000 x 1024 20.4 / 16.0, x 4096 45.1 / 43.6; 75000 x 512 23.6 / 20.2, x 1024 31.0 / 31.8; 100000 x 2048 57.0 / 51.5
-//   binary16     50000 x 512 int4 16.4 / 13.8, x 2048 32.1 / 29.7, x 4096 49.7 / 49.9; int4 groups x 1024 22.3 / 20.3, x 2048 33.1 / 32.6
-// and where the tiles start a second round, binary16 activations never (75000 x 1024 int4 27.4 / 34.4).
+// Binary16 activations with whole steps of K: tile_us says.
 static int tiles_up_to_k(const Geometry &g, int M, bool int8_activations, int num_cus) {
     constexpr int kAll = 1 << 30;
     const float fill = (float)((g.N + 255) / 256) / (float)num_cus;
@@ -639,10 +638,9 @@ static int tiles_up_to_k(const Geometry &g, int M, bool int8_activations, int nu
         if (fill <= 1.0f) return fill < 0.6f ? 2048 : kAll;
         return !w8 ? kAll : fill < 1.5f ? 512 : 3072;
     }
-    if (fill < 0.6f || fill > 1.0f || (!w8 && g.K % 128 != 0)) return 0;  // (the 256-channel tiles need whole steps)
+    if (fill < 0.6f || fill > 1.0f || !w8) return 0;  // (K that is not whole steps)
     const bool wide = fill >= 0.75f;
-    if (M <= 48) return !wide ? 0 : g.fmt == kW4C ? 1024 : w8 ? 512 : 0;
-    return g.fmt == kW4C ? (wide ? 2048 : 1024) : w8 ? (wide ? 1024 : 512) : wide ? 1024 : 0;
+    return M <= 48 ? (wide ? 512 : 0) : wide ? 1024 : 512;
 }
 
 // Which products these kernels take.  Up to 64 token rows: all but those.  More rows: the tiles of 64 or 128
@@ -650,7 +648,7 @@ static int tiles_up_to_k(const Geometry &g, int M, bool int8_activations, int nu
 // rows are cut into blocks, with the time growing with their number.  Both times are estimated: here see estimate_us, which where
 // the two are near each other (65 to 1024 rows, 1500 to 65536 channels, K of 896 to 14336, 721 shapes) is 1 to 7 % high in the median (hence the
 // 1.05) and from 16 % low to 27 % high in eight of ten; tiles
-//   9 + 9.3 K / 1000 a round (binary16 activations, 256 x 128), 10 + 10.3 K / 1000 (128 x 128: staged_tiles_us); 4.5 + 4.85 K / 1000 and 4.8 + 4.1 K / 1000
+//   tile_us (binary16 activations), 10 + 10.3 K / 1000 (128 x 128, K that is not whole steps: staged_tiles_us); 4.5 + 4.85 K / 1000 and 4.8 + 4.1 K / 1000
 //   (64 tokens, int8 x int8 and int4), 3.5 + 9.3 K / 1000 (int8 x int4, K of an odd number of 128)
 // Measured (us, tiles / here): 4096 x 14336 int4, binary16 activations, 77 rows 131 / 24, 300 131 / 64, 512 133 / 75;
 // 2304 x 9216 int4 groups 77 rows 96 / 15, 300 98 / 26, 1000 95 / 71; 18432 x 2304 77 rows 31 / 22, 200 31 / 38;
@@ -664,8 +662,6 @@ static float skinny_us(const Geometry &g, int M, bool int8_activations, bool gat
     return estimate_us(a, g.fmt, int8_activations, row_tiles_for(a, g.fmt, int8_activations, num_cus), num_cus);
 }
 
-static float tile_round_us(const Geometry &g) { return 9.0f + 9.3e-3f * (float)g.K; }  // (binary16 activations)
-
 // Binary16 activations, 128 x 128 tiles: two workgroups share a compute unit, so that a second tile on it costs a third to
 // three quarters of the first.  us, rounds of one tile per compute unit / this: 24000 x 8192 int8 65 rows, 0.73 rounds 93 / 94; 130 rows, 1.47
 // 133 / 145; 277 rows, 2.2 224 / 255; 400 rows, 2.94 241 / 255; 640 rows, 3.67 306 / 299; 18432 x 3040 int4 800 rows, 3.94 115 / 135;
@@ -677,47 +673,63 @@ static float staged_tiles_us(const Geometry &g, int M, int num_cus) {
     return (10.0f + 10.3e-3f * (float)g.K) * (1.55f * pairs + last);
 }
 
-// Binary16 activations, 256 x 128 tiles, one workgroup per compute unit: a last round of few tiles costs as much as a
-// full one.  Rows to leave to the kernels here so that the tiles of the others end with a full round, if that is
-// estimated to save anything; else 0 (of 30 shapes estimated to save up to a tenth the least gained 1 %, on average 6 %: 20000 x 6144
-// int4 groups 500 rows 157 / 146, 14336 x 9216 692 rows 223 / 208; of 20 estimated to lose up to a tenth 14 lost, up to 8 %).  Measured (us, tiles
-// alone / like this): 2304 x 9216 3700 rows 231 / 161;
-// 28672 x 4096 270 rows 98 / 72; 6144 x 4096 1300 rows 111 / 75; 4096 x 14336 2200 rows 315 / 228; 18432 x 2304 900 rows 108 / 93.
-static int tail_rows(const Geometry &g, int M, bool gated, int num_cus, float *saved_us) {
-    *saved_us = 0.0f;
-    if (tuning().gemm_variant != 0 || tuning().skinny_max_m >= 0) return 0;
-    const long n256 = (g.N + 255) / 256, m128 = (M + 127) / 128, rounds = (n256 * m128 + num_cus - 1) / num_cus;
-    const long keep = (rounds - 1) * num_cus / n256 * 128;  // rows whose tiles fill one round less
-    const long rest = M - keep;
-    if (rounds < 2 || keep < 128 || rest < 1 || rest > kSkinnyMaxM) return 0;
-    // tiles that fill their two rounds or more badly save no round: workgroups of the next one fill the gaps anyway
-    // (us, tiles alone / like this, by that share: 28018 x 2048 808 rows 0.86 150 / 165, 19403 x 768 789 rows 0.89 71 / 77;
-    // 24000 x 2048 673 rows 0.92 95 / 85, 11000 x 768 1502 rows 0.92 48 / 46; one round: 11000 x 1024 720 rows 0.84 35 / 29)
-    if (rounds > 2 && 10 * (keep / 128) * n256 < 9 * (rounds - 1) * num_cus) return 0;
-    const float saved = tile_round_us(g) - skinny_us(g, (int)rest, false, gated, num_cus) - 3.0f;  // (3: a second launch)
-    if (saved <= 0.0f) return 0;
-    *saved_us = saved;
-    return (int)rest;
+// Binary16 activations: what the plan of choose_blocks takes, for the choice between it and the large tiles.  estimate_us ranks the
+// plans of one layer; across layers it is 23 % off (at K of 256 up to twice), this 9 %: fitted to 2870 shapes of 768 to 40000 channels, K of 128 to 14336
+// and 9 to 1024 rows.  The choice is 0.3 % slower than the faster of both (estimate_us 1.1 %, with single shapes 1.5 times slower).
+static float few_rows_us(const Geometry &g, int M, bool gated, int num_cus) {
+    SkinnyArgs a = make_args(g, nullptr, nullptr, nullptr, M, nullptr, nullptr, gated ? 0 : -1);
+    choose_blocks(a, g.fmt, false, num_cus);
+    const int R = row_tiles_for(a, g.fmt, false, num_cus);
+    const float l = load_per_cu(a, R, num_cus), k = 1e-3f * (float)g.K, r = (float)R, rows = (float)round_up(a.block_rows, 16);
+    const float w = g.fmt == kW8C ? 0.337f : g.fmt == kW4G32 ? 0.288f : 0.191f;
+    return 4.0f + fmaxf(1.0f, 0.5f * (l + ceilf(l))) * (0.0053f * r * rows + k * (0.0106f * rows + w * r + 0.0036f * r * rows));
+}
+
+// Binary16 activations: rows to leave to the kernels here where the tiles of the others then end with a full round, or without a tile of
+// few rows, if that is estimated to save more than a second launch and a fiftieth; 0: none.  Returns the estimated time.
+// us, tiles alone / like this: 2304 x 9216 int4 groups 3700 rows 173 / 158; 8192 x 4096 1030 rows 79 / 74; 4096 x 4096 int4 2060 rows
+// 71.9 / 69.5; 14336 x 14336 int4 groups 1271 rows 520 / 479; 22016 x 14336 int4 351 rows 252 / 222 (of 19 of 490 shapes where it is done
+// two lose, by 3 and 4 %).  A K of one step keeps the line that K of all sizes once had, full rounds of 128 rows (8192 x 128, 1030
+// rows 10.9 us in two launches, 8.5 in one): no layer has it, and it is where two launches are tested cheaply.
+static float tail_rows(const Geometry &g, int M, bool gated, int num_cus, int *rest) {
+    int form;
+    float best = tile_us(g, M, num_cus, &form);
+    *rest = 0;
+    if (tuning().gemm_variant != 0 || tuning().skinny_max_m >= 0) return best;
+    const bool one_step = g.K < 256;
+    const int rows = one_step ? 128 : tile_rows(form), n_tiles = (g.N + 255) / 256, m_tiles = (M + rows - 1) / rows;
+    if (n_tiles * m_tiles <= num_cus) return best;  // (one round: a tile of few rows keeps nothing waiting)
+    const int full = (n_tiles * m_tiles - 1) / num_cus * num_cus / n_tiles * rows, whole = (M - 1) / rows * rows;
+    for (const int most : {full, whole}) {
+        const int r = M - most;
+        if (most < 128 || r > kSkinnyMaxM || (one_step && r > rows)) continue;
+        const float us = tile_us(g, most, num_cus, &form) + few_rows_us(g, r, gated, num_cus) + 1.0f;
+        if (us < 0.98f * best || one_step) best = us, *rest = r;
+        if (one_step) break;
+    }
+    return best;
 }
 
 int skinny_tail_rows(const Geometry &g, int M, bool gated, int num_cus) {
-    float saved;
-    return tail_rows(g, M, gated, num_cus, &saved);
+    int rest;
+    tail_rows(g, M, gated, num_cus, &rest);
+    return rest;
 }
 
 bool skinny_product(const Geometry &g, int M, bool int8_activations, bool gated, int num_cus) {
     if (tuning().gemm_variant != 0) return false;  // a large kernel is asked for by name
     if (tuning().skinny_max_m >= 0) return M <= tuning().skinny_max_m;
-    if (M <= kSkinnyRows) return g.K > tiles_up_to_k(g, M, int8_activations, num_cus);
+    if (M <= kSkinnyRows && (int8_activations || !tile_kernel_takes(g))) return g.K > tiles_up_to_k(g, M, int8_activations, num_cus);
     if (M > kSkinnyMaxM) return false;
+    if (!int8_activations && tile_kernel_takes(g)) {
+        if (M <= kSkinnyRows && g.N < 8192) return true;  // (where the tiles win there, K = 256, it is by 0.3 us, and the estimate costs the host that)
+        const float us = few_rows_us(g, M, gated, num_cus);
+        int form, rest;
+        return us < tile_us(g, M, num_cus, &form) && us < tail_rows(g, M, gated, num_cus, &rest);
+    }
     const float here = skinny_us(g, M, int8_activations, gated, num_cus);
     const long n256 = (g.N + 255) / 256, m128 = (M + 127) / 128;
     if (!int8_activations) {
-        if (g.fmt != kW8C && g.K % 128 == 0) {
-            float saved;  // (with their last rows left to the kernels here: 11008 x 9216 int4 660 rows, all here 180, all tiles 200, both 130)
-            tail_rows(g, M, gated, num_cus, &saved);
-            return here < 1.05f * (ceilf((float)(n256 * m128) / (float)num_cus) * tile_round_us(g) - saved);
-        }
         // Up to eight wavefronts share the steps here, and the time is that of the one with most (4096 x 14432, 113 steps: 7 % more than
         // 4096 x 14336).  The choice is 0.2 % slower than the faster of both over 319 shapes of 1500 to 65536 channels, K of 1024 to 14432
         // and 65 to 1000 rows; us, tiles / here: 18432 x 3040 int4 800 rows 115 / 146, 4096 x 14432 1000 rows 161 / 188; int8 28672 x 8192 96 rows

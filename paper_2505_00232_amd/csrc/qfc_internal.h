@@ -379,6 +379,12 @@ hipError_t launch_gemm_i8(const Geometry &g, const void *packed, const int8_t *x
 hipError_t launch_gemm_f16(const Geometry &g, const void *packed, const void *x, int M, void *y,
                            const void *residual, int gated_act, int num_cus, hipStream_t st);
 
+// The main kernel for binary16 activations (gemm_f16.hip): whether it takes the layer, its estimated time in us and the form
+// (tile and split of K) that it is fastest in.
+bool tile_kernel_takes(const Geometry &g);
+float tile_us(const Geometry &g, int M, int num_cus, int *form);
+int tile_rows(int form);
+
 // Few token rows (9 .. kSkinnyMaxM, where they are the faster ones): see gemm_skinny.hip.  Arguments as the two launchers above.
 constexpr int kSkinnyRows = 64;  // token rows per workgroup at most
 constexpr int kSkinnyMaxM = 1024;

@@ -582,6 +582,52 @@ def test_fp16_prefill_whole_output_two_kernels_agree(fmt, M):
     layer.close()
 
 
+@pytest.mark.parametrize("form", [31, 32, 33, 34, 35, 36])
+@pytest.mark.parametrize("fmt", ["w4g32", "w4c", "w8c"])
+def test_fp16_tiles_of_every_form(form, fmt):
+    """The main kernel with binary16 activations in each of its forms (32 to 128 token rows per workgroup, K in one piece or two): one
+    step of K, an odd number of steps (uneven halves), more than eight (a second unit of group scales); token rows one past a tile and
+    one short of it; channels whose rows are aligned to 16, 8, 4 and 2 bytes; residual and gated output."""
+    step = 64 if fmt == "w8c" else 128
+    for M, N, steps in ((9, 70, 1), (33, 264, 2), (95, 300, 3), (129, 517, 5), (127, 90, 9), (161, 256, 10), (255, 1, 4)):
+        K = step * steps
+        print(f"fp16 tiles form={form} {fmt} M={M} N={N} K={K}", flush=True)
+        wq, s = synth.weights(4500, M, N, synth.FC("t", K, N, fmt))
+        x = synth.activations(4500, M, N, M, K)
+        res = synth.activations(4500, M, N + 1, M, N)
+        layer = _layer(wq, s, fmt, max_m=M, mode=binding.QFC_COMPUTE_FP16_DEQUANT)
+        ref = oracle.fc_weight_only(x, wq, s, _group(fmt))
+        xd, rd = torch.from_numpy(x).to(DEV), torch.from_numpy(res).to(DEV)
+        guard = torch.full((M + 1, N), 77.0, dtype=torch.float16, device=DEV)
+        binding.qfc_tune(2, form)
+        try:
+            binding.qfc_forward(layer.handle, xd, guard[:M])
+            plain = guard[:M].cpu().numpy()
+            binding.qfc_forward_fused(layer.handle, xd, guard[:M], residual=rd)
+            torch.cuda.synchronize()
+        finally:
+            binding.qfc_tune(2, 0)
+        assert _E(plain, ref) <= TOL, (M, N, K)
+        assert _E(guard[:M].cpu().numpy(), ref + res.astype(np.float64)) <= TOL, (M, N, K)
+        assert bool((guard[M] == 77.0).all())
+        layer.close()
+        if fmt == "w8c" or N % 32 != 0:
+            continue
+        x = (x * np.float16(0.25)).astype(np.float16)
+        gated = binding.QuantLinear(wq, s, fmt, compute_mode=binding.QFC_COMPUTE_FP16_DEQUANT, max_m=M, gated_pairs=True)
+        guard = torch.full((M + 1, N // 2), 77.0, dtype=torch.float16, device=DEV)
+        binding.qfc_tune(2, form)
+        try:
+            binding.qfc_forward_fused(gated.handle, torch.from_numpy(x).to(DEV), guard[:M], activation=binding.QFC_ACT_SILU, gated_output=True)
+            torch.cuda.synchronize()
+        finally:
+            binding.qfc_tune(2, 0)
+        # (group scales: the product of two outputs that each carry the rounding of scaled weights, twice the tolerance)
+        assert _E(guard[:M].cpu().numpy(), oracle.gated_output(oracle.fc_weight_only(x, wq, s, _group(fmt)), oracle.SILU)) <= (2 if fmt == "w4g32" else 1) * TOL
+        assert bool((guard[M] == 77.0).all())
+        gated.close()
+
+
 # ------------------------------------------------------------------ decode with 8-bit activations (the paper's decode design)
 @pytest.mark.parametrize("fmt", ["w8c", "w4c"])
 @pytest.mark.parametrize("N,K", DECODE_SHAPES)
