@@ -31,6 +31,7 @@ namespace {
 typedef _Float16 h2 __attribute__((ext_vector_type(2)));
 typedef _Float16 v8h __attribute__((ext_vector_type(8)));
 typedef float v16f __attribute__((ext_vector_type(16)));
+typedef float v4f __attribute__((ext_vector_type(4)));
 
 constexpr int BN = 128, BM = 128, BK = 128;
 constexpr int OCT = BK / 8;      // 16-byte octets (8 binary16) per row per stage
@@ -271,68 +272,62 @@ typedef __attribute__((address_space(3))) void *lptr_t;
 constexpr int TN = 256;                    // output channels of a workgroup
 constexpr int kStorePitch = (64 + 8) * 2;  // bytes per staged row of the store phase
 
-// eight biased codes -> eight scaled binary16 values (k ascending) as an MFMA operand
-__device__ __forceinline__ v8h dequant_frag(uint32_t w, h2 s) {
+// Half of an MFMA operand, as two dwords of binary16 values (k ascending): of eight biased int4 codes the low (HI = 0) or the high nibbles,
+// exactly, times the group scale if there is one; of four int8 codes, exactly.
+template <bool HI, bool SC>
+__device__ __forceinline__ uint2 dequant4_half(uint32_t w, h2 s) {
     const h2 c1032 = {(_Float16)1032.0f, (_Float16)1032.0f};
     const h2 c72 = {(_Float16)72.0f, (_Float16)72.0f};
     const h2 c16th = {(_Float16)0.0625f, (_Float16)0.0625f};
-    const uint32_t lo = w & 0x0F0F0F0Fu, hi = w & 0xF0F0F0F0u;
-    const h2 p0 = (as_h2(__builtin_amdgcn_perm(0x64646464u, lo, 0x04010400u)) - c1032) * s;
-    const h2 p1 = (as_h2(__builtin_amdgcn_perm(0x64646464u, lo, 0x04030402u)) - c1032) * s;
-    const h2 p2 = (as_h2(__builtin_amdgcn_perm(0x64646464u, hi, 0x04010400u)) * c16th - c72) * s;
-    const h2 p3 = (as_h2(__builtin_amdgcn_perm(0x64646464u, hi, 0x04030402u)) * c16th - c72) * s;
-    return v8h{p0[0], p0[1], p1[0], p1[1], p2[0], p2[1], p3[0], p3[1]};
+    const uint32_t v = w & (HI ? 0xF0F0F0F0u : 0x0F0F0F0Fu);
+    h2 p0 = as_h2(__builtin_amdgcn_perm(0x64646464u, v, 0x04010400u)), p1 = as_h2(__builtin_amdgcn_perm(0x64646464u, v, 0x04030402u));
+    if (HI)
+        p0 = p0 * c16th - c72, p1 = p1 * c16th - c72;
+    else
+        p0 -= c1032, p1 -= c1032;
+    if (SC) p0 *= s, p1 *= s;
+    return make_uint2(as_u32(p0), as_u32(p1));
 }
-
-// the same without a scale: the integer values themselves (W4C; the scale is applied to the output)
-__device__ __forceinline__ v8h dequant_frag_unscaled(uint32_t w) {
-    const h2 c1032 = {(_Float16)1032.0f, (_Float16)1032.0f};
-    const h2 c72 = {(_Float16)72.0f, (_Float16)72.0f};
-    const h2 c16th = {(_Float16)0.0625f, (_Float16)0.0625f};
-    const uint32_t lo = w & 0x0F0F0F0Fu, hi = w & 0xF0F0F0F0u;
-    const h2 p0 = as_h2(__builtin_amdgcn_perm(0x64646464u, lo, 0x04010400u)) - c1032;
-    const h2 p1 = as_h2(__builtin_amdgcn_perm(0x64646464u, lo, 0x04030402u)) - c1032;
-    const h2 p2 = as_h2(__builtin_amdgcn_perm(0x64646464u, hi, 0x04010400u)) * c16th - c72;
-    const h2 p3 = as_h2(__builtin_amdgcn_perm(0x64646464u, hi, 0x04030402u)) * c16th - c72;
-    return v8h{p0[0], p0[1], p1[0], p1[1], p2[0], p2[1], p3[0], p3[1]};
+__device__ __forceinline__ uint2 dequant8_half(uint32_t w) {
+    const h2 c1152 = {(_Float16)1152.0f, (_Float16)1152.0f};
+    const uint32_t v = w ^ 0x80808080u;
+    return make_uint2(as_u32(as_h2(__builtin_amdgcn_perm(0x64646464u, v, 0x04010400u)) - c1152),
+                      as_u32(as_h2(__builtin_amdgcn_perm(0x64646464u, v, 0x04030402u)) - c1152));
 }
 
 // ---------------------------------------------------------------------------
 // Main kernel: weights never dequantized into LDS, activations through an LDS ring.
 //
 // A workgroup is four wavefronts (KS = 1) over 256 output channels x 32 JP token rows.  A wavefront owns 64 channels (four
-// packed row tiles) and all the rows, 2 x JP tiles of v_mfma_f32_32x32x16_f16 over all of K: it converts its weights once for
+// packed row tiles) and all the rows, 4 x 2 JP tiles of v_mfma_f32_16x16x32_f16 over all of K: it converts its weights once for
 // 32 JP rows, its codes are wanted by no other wavefront, and nothing is exchanged at the end.  Weights are the row operand, so a
-// lane ends up with groups of four consecutive n of one token row.
+// lane ends up with four consecutive n of one token row of each tile.
 //
-// What bounds it: power on real data (a register-only loop of these MFMAs holds 1.64 PFLOP/s, one round of full tiles of long K 1.36), then
-// what a wavefront does before its first and after its last MFMA.  Hence two workgroups of JP = 4 per compute unit, with everything
-// within half its registers and 80 KiB of LDS: one stores or starts while the other multiplies, and a barrier stops
-// one wavefront of a SIMD, not both.  Measured in turn, us, before (eight wavefronts over 256 x 128, the halves of K in
-// two groups that swap their sums at the end, one workgroup per compute unit) / now:
-//   int4 groups  18432 x 2304, 2048 rows, gated 187 / 155 (0.93 -> 1.12 PFLOP/s); 9216 x 768, 1000 rows 32.0 / 22.8
-//   int4         28672 x 4096, 6000 rows, gated 1232 / 1099 (1.28 PFLOP/s); 6144 x 4096 274 / 242; 4096 x 14336 558 / 526 (1.34)
-//   int8         14336 x 4096, 1000 rows 149 / 104; 4096 x 4096, 2048 rows 81 / 62 (before: the fallback kernel)
-// A wavefront of 64 channels x 256 rows (all registers, one workgroup per compute unit) converts half as often and
-// takes 1122 us for the first line of int4: what it saves in conversions it loses at the barriers and in the store phase.
+// What bounds it: power on real data, then what a wavefront does before its first and after its last MFMA.  Hence two workgroups of JP
+// = 4 per compute unit, with everything within half its registers and 80 KiB of LDS: one stores or starts while the other
+// multiplies, and a barrier stops one wavefront of a SIMD, not both.  Hence also the 16 x 16 shape: register-only loops over a
+// wavefront's tile (normal data, int4 codes; one / two wavefronts per SIMD) hold 2.19 / 2.18 PFLOP/s with it, 1.82 / 1.30 with
+// v_mfma_f32_32x32x16_f16 (two wavefronts do not even overlap on constant data: 1.63 of 2.46).
+// us, one workgroup of eight wavefronts and 32 x 32 MFMAs per compute unit / this, in one session: int4 in groups of 32 18432 x 2304 gated
+// 2048 rows 188 / 151, 9216 x 768 1000 rows 29.3 / 20.5; int4 codes 28672 x 4096 gated 6000 rows 1239 / 1011, 6144 x 4096 279 / 221, 4096 x 14336
+// 548 / 467; int8 codes (then dequantized into LDS) 14336 x 4096 1000 rows 147 / 99, 4096 x 4096 2048 rows 80 / 58.
 //
 // KS = 2: eight wavefronts, two groups of four over the same outputs, each with half of K and rings of its own; they
 // swap halves of their sums through LDS at the end.  For launches of about one workgroup per compute unit, whose SIMDs would
-// hold one wavefront (2304 x 14336, 1000 rows int4 138 us with JP = 4, 90 with JP = 2, 79 with JP = 2 and two groups).
-// Which JP and KS: tile_us.
+// hold one wavefront.  Which JP and KS: tile_us.
 //
 // Everything arrives by direct global -> LDS copies (16 bytes per lane, one KiB per wavefront instruction), which complete in
 // issue order, so that waits are counts of the copies issued later.  A half stage is 64 k of the token rows: rows of 128 bytes, the
 // 16-byte octet o of row r at position o ^ ((r >> 1) & 7), which makes the operand reads conflict free while a copy still
 // reads whole 128-byte row pieces.  Three half stages, copied two ahead; one barrier per half stage.  Codes of 128 k (int8: of 64 k, two in
 // turn) and, for group scales, the vectors of 8 groups of the wavefront's 64 rows are copied after the tile before has been
-// read into registers, and read at its end.  No copy is issued past the end of K.
+// read into registers.  No copy is issued past the end of K.
 //
-// The loop is software pipelined by one k step of 16: while the MFMAs of a step run, the token rows of the next are read and its weights
-// converted.  An MFMA operand is 32 rows x 16 k, lane = (row r, k octet kh).  4-bit codes: lane (r, kh) of row pair ip, k step s owns the
-// vector of row tile 2 ip + r / 16, lane (2 s + kh) * 16 + r % 16 of a packed tile; dword g of it is its operand for group g.
-// int8: vector (2 p + kh) * 16 + r % 16 of a packed tile holds its operands of the k steps 2 p and 2 p + 1 (token rows are read in the
-// same order of octets).
+// Inside a wavefront: a k step of 32 multiplies row tiles 0 and 1 with all blocks of 16 token rows, then 2 and 3; the weights of 2 and 3 are
+// converted during the first pass, those of 0 and 1 of the next step during the second, in which each block of token rows is
+// replaced by the next step's as soon as it has been multiplied.  (Converting a whole step ahead needs 16 registers more: with group
+// scales the loop then spills.)  An MFMA operand is 16 rows x 32 k, lane = (row c, octet q): with 4-bit codes dword g of the
+// lane's vector of a packed tile for group g; with int8 codes half of it, and the token rows are read in the same order of octets.
 //
 // FMT: packed format; JP: blocks of 32 token rows.
 template <int FMT, int JP>
@@ -366,48 +361,41 @@ __device__ __forceinline__ void block_rows(const GemmF16Args &a, char *region, i
     }
 }
 
-// Store phase of a wavefront's 64 channels x 32 JP token rows.  A lane holds one token row (lane % 32) and groups of four
-// consecutive n; the binary16 values go through a block of LDS of the wavefront's own (32 token rows x 64 channels) and leave as 16-byte
-// stores along n.
-template <bool PC, int JP>
-__device__ __forceinline__ void store_tile(const GemmF16Args &a, v16f (&acc)[2][JP], int n0, int m0, char *region, int lane) {
-    const int r = lane & 31, kh = lane >> 5;
+// Store phase of a wavefront's 64 channels x 16 NJ token rows.  A lane holds one token row (lane % 16) of a block of 16 and four
+// consecutive n (4 (lane / 16) + e) of each row tile; the binary16 values go through a block of LDS of the wavefront's own (32 token rows x 64
+// channels) and leave as 16-byte stores along n.
+template <bool PC, int NJ>
+__device__ __forceinline__ void store_tile(const GemmF16Args &a, v4f (&acc)[4][NJ], int n0, int m0, char *region, int lane) {
+    typedef _Float16 h4 __attribute__((ext_vector_type(4)));
+    const int c = lane & 15, q = lane >> 4;
     if (PC) {
 #pragma unroll
-        for (int ip = 0; ip < 2; ++ip)
+        for (int i = 0; i < 4; ++i) {
+            const v4f sc = *reinterpret_cast<const v4f *>(a.sw + n0 + 16 * i + 4 * q);
 #pragma unroll
-            for (int qq = 0; qq < 4; ++qq) {
-                const float4 sc = *reinterpret_cast<const float4 *>(a.sw + n0 + ip * 32 + 8 * qq + 4 * kh);
-#pragma unroll
-                for (int jp = 0; jp < JP; ++jp) {
-                    acc[ip][jp][4 * qq + 0] *= sc.x;
-                    acc[ip][jp][4 * qq + 1] *= sc.y;
-                    acc[ip][jp][4 * qq + 2] *= sc.z;
-                    acc[ip][jp][4 * qq + 3] *= sc.w;
-                }
-            }
+            for (int j = 0; j < NJ; ++j) acc[i][j] *= sc;
+        }
     }
-    typedef _Float16 h4 __attribute__((ext_vector_type(4)));
     auto wave_sync = [&]() __attribute__((always_inline)) {
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     };
     if (a.gated_act >= 0) {
+        // Layer packed in pairs (operator fusion, section 3.6 of the paper): row tiles 2 t and 2 t + 1 are the gate's and the other
+        // branch's rows of the same 16 channels.  32 output channels per wavefront, rows of N / 2 values.
         const GateCoeffs gc = gate_coeffs(a.gated_act);
         const int halfn = a.N / 2, o0 = n0 / 2;
 #pragma unroll
-        for (int jp = 0; jp < JP; ++jp) {
-            const int mrow0 = m0 + jp * 32;
+        for (int jp = 0; jp < NJ; jp += 2) {
 #pragma unroll
-            for (int ip = 0; ip < 2; ++ip)
+            for (int jj = 0; jj < 2; ++jj)
 #pragma unroll
-                for (int qq = 0; qq < 2; ++qq) {
+                for (int i = 0; i < 4; i += 2) {
                     h4 hv;
 #pragma unroll
-                    for (int e = 0; e < 4; ++e)
-                        hv[e] = (_Float16)(gate_activation(acc[ip][jp][4 * qq + e], gc) * acc[ip][jp][4 * (qq + 2) + e]);
-                    *reinterpret_cast<h4 *>(region + r * kStorePitch + (ip * 16 + 8 * qq + 4 * kh) * 2) = hv;
+                    for (int e = 0; e < 4; ++e) hv[e] = (_Float16)(gate_activation(acc[i][jp + jj][e], gc) * acc[i + 1][jp + jj][e]);
+                    *reinterpret_cast<h4 *>(region + (16 * jj + c) * kStorePitch + (8 * i + 4 * q) * 2) = hv;
                 }
             wave_sync();
 #pragma unroll
@@ -415,7 +403,7 @@ __device__ __forceinline__ void store_tile(const GemmF16Args &a, v16f (&acc)[2][
                 const int idx = it * 64 + lane;
                 const int row = idx >> 2, ch = idx & 3;
                 const uint4 v = *reinterpret_cast<const uint4 *>(region + row * kStorePitch + ch * 16);
-                const int mm = mrow0 + row, nn = o0 + ch * 8;
+                const int mm = m0 + jp * 16 + row, nn = o0 + ch * 8;
                 if (mm < a.M && nn < halfn) *reinterpret_cast<uint4 *>(a.y + (size_t)mm * halfn + nn) = v;
             }
             wave_sync();
@@ -424,8 +412,8 @@ __device__ __forceinline__ void store_tile(const GemmF16Args &a, v16f (&acc)[2][
     }
     const bool has_res = a.res != nullptr;
 #pragma unroll
-    for (int jp = 0; jp < JP; ++jp) {
-        const int mrow0 = m0 + jp * 32;
+    for (int jp = 0; jp < NJ; jp += 2) {
+        const int mrow0 = m0 + jp * 16;
         if (has_res) {
             block_rows(a, region, mrow0, n0, lane,
                        [&](char *staged, size_t at) { *reinterpret_cast<uint4 *>(staged) = __builtin_bit_cast(uint4, *reinterpret_cast<const Octet *>(a.res + at)); },
@@ -433,18 +421,18 @@ __device__ __forceinline__ void store_tile(const GemmF16Args &a, v16f (&acc)[2][
             wave_sync();
         }
 #pragma unroll
-        for (int ip = 0; ip < 2; ++ip)
+        for (int jj = 0; jj < 2; ++jj)
 #pragma unroll
-            for (int qq = 0; qq < 4; ++qq) {
-                const int nl = ip * 32 + 8 * qq + 4 * kh;
-                float v[4] = {acc[ip][jp][4 * qq], acc[ip][jp][4 * qq + 1], acc[ip][jp][4 * qq + 2], acc[ip][jp][4 * qq + 3]};
+            for (int i = 0; i < 4; ++i) {
+                const int at = (16 * jj + c) * kStorePitch + (16 * i + 4 * q) * 2;
+                v4f v = acc[i][jp + jj];
                 if (has_res) {
                     float rv[4];
-                    staged_residual4(region, r * kStorePitch + nl * 2, rv);
+                    staged_residual4(region, at, rv);
 #pragma unroll
                     for (int e = 0; e < 4; ++e) v[e] += rv[e];
                 }
-                *reinterpret_cast<h4 *>(region + r * kStorePitch + nl * 2) = h4{(_Float16)v[0], (_Float16)v[1], (_Float16)v[2], (_Float16)v[3]};
+                *reinterpret_cast<h4 *>(region + at) = h4{(_Float16)v[0], (_Float16)v[1], (_Float16)v[2], (_Float16)v[3]};
             }
         wave_sync();
         block_rows(a, region, mrow0, n0, lane,
@@ -468,7 +456,6 @@ __global__ __launch_bounds__(256 * KS, KS == 2 ? 2 : JP == 1 ? 4 : JP == 2 ? 3 :
     const int group = KS == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x >> 8);  // part of K
     char *lds_b = lds_all + group * L::kBytes;
     const int c = lane & 15, q = lane >> 4;
-    const int r = lane & 31, kh = lane >> 5;
     int nt, mt;
     xcd_tile(blockIdx.x, a.n_tiles, a.m_tiles, a.by_tokens, nt, mt);
     const int m0 = mt * ROWS;
@@ -506,192 +493,202 @@ __global__ __launch_bounds__(256 * KS, KS == 2 ? 2 : JP == 1 ? 4 : JP == 2 ? 3 :
             copy16_to_lds(wbase + (size_t)(min(8 * u + 8, a.KT) + u) * 1024 + (size_t)((ta & 7) >> 1) * 256, slane, lds0 + S_OFF + wave * 1024);
     };
 
-    v16f acc[2][JP];
+    constexpr int NJ = 2 * JP;  // blocks of 16 token rows
+    v4f acc[4][NJ];
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < 4; ++i)
 #pragma unroll
-        for (int j = 0; j < JP; ++j)
-#pragma unroll
-            for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.0f;
+        for (int j = 0; j < NJ; ++j) acc[i][j] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
 
-    int xoff[4];  // k step j of a half stage: octet of this lane
+    int xoff[2];  // k step s of a half stage: octet of this lane
 #pragma unroll
-    for (int j = 0; j < 4; ++j) xoff[j] = r * 128 + (((W8 ? 4 * (j >> 1) + 2 * kh + (j & 1) : 2 * j + kh) ^ ((r >> 1) & 7)) << 4);
-    const char *wread = lds_b + W_OFF + wave * 4096 + ((r >> 4) * 64 + kh * 16 + (r & 15)) * 16;
-    const char *sread = lds_b + S_OFF + wave * 1024 + r * 16;
+    for (int s = 0; s < 2; ++s) xoff[s] = c * 128 + (((W8 ? 2 * q + s : 4 * s + q) ^ ((c >> 1) & 7)) << 4);
+    const char *wread = lds_b + W_OFF + wave * 4096 + lane * 16;
+    const char *sread = lds_b + S_OFF + wave * 1024 + c * 16;
 
-    uint4 xv[2][JP];  // token rows of a k step of 16, two steps in turn
-    v8h fa[2][2];     // its converted weights: [step in turn][row pair]
-    uint4 wv[2][2];   // 4-bit codes of a tile: [row pair][k step of a group], one dword per group; int8 codes of a half stage: [row pair][two k steps]
-    uint2 sv[2];
+    uint4 xv[NJ];     // token rows of a k step of 32; each block is replaced by the next step's once it has been multiplied
+    uint2 fa[4][2];   // converted weights: [row tile][half], of a step's first two row tiles ahead of it, of the others during it
+    uint4 wv[4];      // codes: of 128 k, one dword per k step (int8: of 64 k, half of it per k step)
+    uint2 sv[4];
+    auto read_x = [&](int i, int s, int j) __attribute__((always_inline)) {
+        xv[j] = *reinterpret_cast<const uint4 *>(lds_b + (i % 3) * L::kX + xoff[s] + j * 2048);
+    };
     auto read_ws = [&](int t) __attribute__((always_inline)) {
 #pragma unroll
-        for (int ip = 0; ip < 2; ++ip) {
-#pragma unroll
-            for (int s = 0; s < 2; ++s) wv[ip][s] = *reinterpret_cast<const uint4 *>(wread + (W8 ? (t & 1) * 16384 : 0) + ip * 2048 + s * 512);
-            if (G32) sv[ip] = *reinterpret_cast<const uint2 *>(sread + ip * 512 + ((i0 / kStep + t) & 1) * 8);
+        for (int i = 0; i < 4; ++i) {
+            wv[i] = *reinterpret_cast<const uint4 *>(wread + (W8 ? (t & 1) * 16384 : 0) + i * 1024);
+            if (G32) sv[i] = *reinterpret_cast<const uint2 *>(sread + i * 256 + ((i0 / kStep + t) & 1) * 8);
         }
     };
-    // operand of row pair ip, k step j of half h
-    auto convert = [&](v8h &f, int ip, int h, int j) __attribute__((always_inline)) {
+    // half p of the operand of row tile i, k step s of half h
+    auto convert = [&](int i, int p, int h, int s) __attribute__((always_inline)) {
+        const uint4 &v = wv[i];
         if (W8) {
-            const uint4 &v = wv[ip][j >> 1];
-            f = __builtin_bit_cast(v8h, j & 1 ? dequant_i8x8(v.z, v.w) : dequant_i8x8(v.x, v.y));
+            fa[i][p] = dequant8_half(s ? (p ? v.w : v.z) : p ? v.y : v.x);
             return;
         }
-        const uint4 &v = wv[ip][j & 1];
-        const int g = 2 * h + (j >> 1);
+        const int g = 2 * h + s;
         const uint32_t w = g == 0 ? v.x : g == 1 ? v.y : g == 2 ? v.z : v.w;
-        if (G32)
-            f = dequant_frag(w, as_h2(__builtin_amdgcn_perm(0u, g & 2 ? sv[ip].y : sv[ip].x, g & 1 ? 0x03020302u : 0x01000100u)));
-        else
-            f = dequant_frag_unscaled(w);
+        h2 sc = {(_Float16)1.0f, (_Float16)1.0f};
+        if (G32) sc = as_h2(__builtin_amdgcn_perm(0u, g & 2 ? sv[i].y : sv[i].x, g & 1 ? 0x03020302u : 0x01000100u));
+        fa[i][p] = p ? dequant4_half<true, G32>(w, sc) : dequant4_half<false, G32>(w, sc);
     };
-    auto multiply = [&](const v8h (&f)[2], const uint4 (&x)[JP], int qd) __attribute__((always_inline)) {
+    auto multiply = [&](int pair, int j) __attribute__((always_inline)) {  // row tiles 2 pair, 2 pair + 1
 #pragma unroll
-        for (int m = qd * JP / 2; m < (qd + 1) * JP / 2; ++m)
-            acc[m & 1][m >> 1] = __builtin_amdgcn_mfma_f32_32x32x16_f16(f[m & 1], __builtin_bit_cast(v8h, x[m >> 1]), acc[m & 1][m >> 1], 0, 0, 0);
-    };
-
-    // Copies in issue order: codes 0 (int8: and 1), half stages 0, 1 | during half stage i: codes of the next tile (int8: of half stage
-    // i + 2), half stage i + 2.
-#pragma unroll
-    for (int k = 0; k < WC; ++k) issue_w(0, k);
-#pragma unroll
-    for (int i = 0; i < XC; ++i) issue_x(0, i);
-    if (nst > 1) {
-        if (W8) {
-#pragma unroll
-            for (int k = 0; k < WC; ++k) issue_w(1, k);
+        for (int i = 2 * pair; i < 2 * pair + 2; ++i) {
+            const uint4 f = make_uint4(fa[i][0].x, fa[i][0].y, fa[i][1].x, fa[i][1].y);
+            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(v8h, f), __builtin_bit_cast(v8h, xv[j]), acc[i][j], 0, 0, 0);
         }
-#pragma unroll
-        for (int i = 0; i < XC; ++i) issue_x(1, i);
-        wait_vmcnt<2 * XC + (W8 ? WC : 0)>();
-    } else {
-        wait_vmcnt<XC>();
-    }
-#pragma unroll
-    for (int ip = 0; ip < 2; ++ip) fa[1][ip] = v8h{0, 0, 0, 0, 0, 0, 0, 0};
-#pragma unroll
-    for (int jp = 0; jp < JP; ++jp) xv[1][jp] = make_uint4(0, 0, 0, 0);
-    read_ws(0);
+    };
 
-    // Half stage i.  more: how many half stages follow it, 2 standing for more of them; h: its half of the 128-k tile (4-bit codes).
-    auto half = [&](int i, const int h, const int more) __attribute__((always_inline)) {
-        // Issued after half stage i: half stage i + 1 and, in front of it, the codes issued at the same time (4-bit: with even ones).
-        // The barrier makes the other wavefronts' copies visible and says that every wavefront has read half stage i - 1, whose slot
-        // the copies of this one overwrite.
-        constexpr int kBoth = XC + WC;
-        if (more == 0)
+    // Copies in issue order: codes 0, half stage 0 (int8: codes 1), half stage 1, codes 1 (int8: 2), half stage 2; then behind half stage i's barrier the
+    // codes of the tile after the next (4-bit: i odd; int8: of half stage i + 3) and half stage i + 3.
+    const int tiles = nst / kStep;
+    auto codes = [&](int t) __attribute__((always_inline)) {
+#pragma unroll
+        for (int k = 0; k < WC; ++k) issue_w(t, k);
+    };
+    auto rows = [&](int i) __attribute__((always_inline)) {
+#pragma unroll
+        for (int k = 0; k < XC; ++k) issue_x(i, k);
+    };
+    if (nst > 0) {
+        codes(0);
+        rows(0);
+        if (W8 && tiles > 1) codes(1);
+        if (nst > 1) rows(1);
+        if (tiles <= 1)
             wait_vmcnt<0>();
-        else if (W8 ? true : h == 1 && more == 2)
-            wait_vmcnt<kBoth>();
         else
-            wait_vmcnt<XC>();
+            wait_vmcnt<2 * XC + (W8 ? WC : 0)>();
+        read_ws(0);
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // the codes are in registers: their slot may be overwritten
+        if (tiles > (W8 ? 2 : 1)) codes(W8 ? 2 : 1);
+        if (nst > 2) rows(2);
+        if (nst > 2)
+            wait_vmcnt<2 * XC + (W8 ? 2 * WC : WC)>();
+        else
+            wait_vmcnt<0>();
         asm volatile("s_barrier" ::: "memory");
-        const char *xs = lds_b + (i % 3) * L::kX;
-        int slot = 0;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {  // k step j of the half stage is read and converted, the step before it multiplied
+        for (int j = 0; j < NJ; ++j) read_x(0, 0, j);
 #pragma unroll
-            for (int jp = 0; jp < JP; ++jp) xv[j & 1][jp] = *reinterpret_cast<const uint4 *>(xs + xoff[j] + jp * 4096);
-            __builtin_amdgcn_sched_barrier(0);
+        for (int k = 0; k < 4; ++k) convert(k >> 1, k & 1, 0, 0);
+    }
+
+    // Half stage i, h: its half of the 128-k tile (4-bit codes).  after: half stages that follow it, 3 standing for more of them.
+    auto half = [&](int i, const int h, const int after) __attribute__((always_inline)) {
+        constexpr int kFirst = NJ >= 8 ? 2 : 1;  // blocks multiplied ahead of the barrier
 #pragma unroll
-            for (int qd = 0; qd < 4; ++qd) {
-                multiply(fa[(j + 1) & 1], xv[(j + 1) & 1], qd);
-                if (qd < 2) {
-                    convert(fa[j & 1][qd], qd, h, j);
+        for (int s = 0; s < 2; ++s) {
+            int slot = 0;
 #pragma unroll
-                    for (int k = qd * JP / 2; k < (qd + 1) * JP / 2; ++k) {
-                        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-                        __builtin_amdgcn_sched_group_barrier(0x002, JP == 4 ? 8 : 14, 0);
-                    }
+            for (int j = 0; j < NJ; ++j) {  // row tiles 0 and 1; 2 and 3 are converted
+                multiply(0, j);
+#pragma unroll
+                for (int k = j * 4 / NJ; k < (j + 1) * 4 / NJ; ++k) convert(2 + (k >> 1), k & 1, h, s);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            if (s == 1 && (W8 || h == 1) && after > 0) {
+                // the next codes have landed once only what was issued after them is outstanding
+                if (W8 && after >= 2)
+                    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * XC + WC) : "memory");
+                else
+                    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(W8 ? XC : 2 * XC) : "memory");
+                read_ws(W8 ? i + 1 : (i >> 1) + 1);
+            }
+#pragma unroll
+            for (int j = 0; j < NJ; ++j) {  // row tiles 2 and 3; 0 and 1 of the next step are converted, its token rows read
+                if (s == 1 && j == kFirst && after > 0) {
+                    // Half stage i + 1 has landed once only what was issued for i + 2 is outstanding; this wavefront has read all of half stage i.
+                    // The barrier says the same of the others: half stage i + 1 may be read, the slot of i overwritten.
+                    if (after == 1)
+                        wait_vmcnt<0>();
+                    else if (W8 || h == 0)
+                        wait_vmcnt<XC + WC>();
+                    else
+                        wait_vmcnt<XC>();
+                    asm volatile("s_barrier" ::: "memory");
+#pragma unroll
+                    for (int jj = 0; jj < kFirst; ++jj) read_x(i + 1, 0, jj);
+                }
+                multiply(1, j);
+                if (s == 0) {
+#pragma unroll
+                    for (int k = j * 4 / NJ; k < (j + 1) * 4 / NJ; ++k) convert(k >> 1, k & 1, h, 1);
+                } else if (after > 0 && j >= kFirst) {
+#pragma unroll
+                    for (int k = (j - kFirst) * 4 / (NJ - kFirst); k < (j - kFirst + 1) * 4 / (NJ - kFirst); ++k) convert(k >> 1, k & 1, (h + 1) & 1, 0);
                 }
                 __builtin_amdgcn_sched_barrier(0);
-                if (W8 || h == 0) {
-                    if (slot < WC) {
-                        if (more == 2) issue_w(W8 ? i + 2 : (i >> 1) + 1, slot);
-                    } else if (slot < WC + XC) {
-                        if (more == 2) issue_x(i + 2, slot - WC);
+                if (s == 0)
+                    read_x(i, 1, j);
+                else if (after > 0 && j >= kFirst)
+                    read_x(i + 1, 0, j);
+                if (s == 1 && j >= kFirst && after >= 3) {
+                    constexpr int kPer = (WC + XC + NJ - kFirst - 1) / (NJ - kFirst);
+#pragma unroll
+                    for (int k = 0; k < kPer; ++k, ++slot) {
+                        const int n = slot - (W8 || h == 1 ? WC : 0);
+                        if (n < 0)
+                            issue_w(W8 ? i + 3 : (i >> 1) + 2, slot);
+                        else if (n < XC)
+                            issue_x(i + 3, n);
                     }
-                } else if (slot % (16 / (XC + XC % 2)) == 0 && slot / (16 / (XC + XC % 2)) < XC) {
-                    if (more == 2) issue_x(i + 2, slot / (16 / (XC + XC % 2)));
-                }
-                ++slot;
-                if ((W8 || h == 1) && j == 3 && qd == 1 && more > 0) {
-                    // the next codes have landed once only what was issued after them is outstanding
-                    if (W8) {
-                        if (more == 2) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * XC + WC) : "memory");
-                        else asm volatile("s_waitcnt vmcnt(%0)" ::"n"(XC) : "memory");
-                    } else if (more == 2) {
-                        asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * XC) : "memory");
-                    } else {
-                        asm volatile("s_waitcnt vmcnt(%0)" ::"n"(XC) : "memory");
-                    }
-                    read_ws(W8 ? i + 1 : (i >> 1) + 1);
                 }
             }
         }
     };
     if constexpr (W8) {
         int i = 0;
-        for (; i + 2 < nst; ++i) half(i, 0, 2);
+        for (; i + 3 < nst; ++i) half(i, 0, 3);
+        if (i + 2 < nst) half(i++, 0, 2);
         if (i + 1 < nst) half(i++, 0, 1);
-        half(i, 0, 0);
+        if (i < nst) half(i, 0, 0);
     } else {
         int i = 0;
-        for (; i + 2 < nst; i += 2) {
-            half(i, 0, 2);
-            half(i + 1, 1, 2);
+        for (; i + 4 < nst; i += 2) {
+            half(i, 0, 3);
+            half(i + 1, 1, 3);
         }
-        half(i, 0, 1);
-        half(i + 1, 1, 0);
+        if (i + 2 < nst) {
+            half(i, 0, 3);
+            half(i + 1, 1, 2);
+            i += 2;
+        }
+        if (i < nst) {
+            half(i, 0, 1);
+            half(i + 1, 1, 0);
+        }
     }
     if (KS == 2) {
         for (int i = nst; i < first; ++i) asm volatile("s_barrier" ::: "memory");  // (as many barriers as the first group passes)
     }
-#pragma unroll
-    for (int qd = 0; qd < 4; ++qd) multiply(fa[1], xv[1], qd);
 
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");  // every wavefront is done with the rings
     const int n0 = nt * TN + wave * 64;
     char *region = lds_all + (threadIdx.x >> 6) * (32 * kStorePitch);
     if constexpr (KS == 1) {
-        store_tile<!G32, JP>(a, acc, n0, m0, region, lane);
+        store_tile<!G32, NJ>(a, acc, n0, m0, region, lane);
     } else {
-        // The two halves of K meet: each group keeps half of the blocks of 32 rows and hands the other half to its partner
-        // through LDS ([wavefront][16-byte vector][lane]), over the dead rings.
-        constexpr int HB = JP / 2;
-        constexpr int kEx = 2 * HB * 16 * 256;  // bytes per wavefront
+        // The two halves of K meet: each group keeps half of the token rows and hands the other half to its partner through LDS
+        // ([wavefront][16-byte vector][lane]), over the dead rings.
+        constexpr int kEx = 4 * JP * 1024;  // bytes per wavefront
         static_assert(KS == 1 || (JP % 2 == 0 && 8 * kEx <= 2 * L::kBytes), "halves of the sums fit over the rings");
-        float4 *mine = reinterpret_cast<float4 *>(lds_all + (group * 4 + wave) * kEx) + lane;
+        v4f *mine = reinterpret_cast<v4f *>(lds_all + (group * 4 + wave) * kEx) + lane;
 #pragma unroll
-        for (int ip = 0; ip < 2; ++ip)
+        for (int i = 0; i < 4; ++i)
 #pragma unroll
-            for (int jj = 0; jj < HB; ++jj)
-#pragma unroll
-                for (int qq = 0; qq < 4; ++qq) {
-                    const v16f &v = group ? acc[ip][jj] : acc[ip][HB + jj];
-                    mine[((ip * HB + jj) * 4 + qq) * 64] = make_float4(v[4 * qq], v[4 * qq + 1], v[4 * qq + 2], v[4 * qq + 3]);
-                }
+            for (int j = 0; j < JP; ++j) mine[(i * JP + j) * 64] = group ? acc[i][j] : acc[i][JP + j];
         __syncthreads();
-        const float4 *theirs = reinterpret_cast<const float4 *>(lds_all + ((group ^ 1) * 4 + wave) * kEx) + lane;
-        v16f out[2][HB];
+        const v4f *theirs = reinterpret_cast<const v4f *>(lds_all + ((group ^ 1) * 4 + wave) * kEx) + lane;
+        v4f out[4][JP];
 #pragma unroll
-        for (int ip = 0; ip < 2; ++ip)
+        for (int i = 0; i < 4; ++i)
 #pragma unroll
-            for (int jj = 0; jj < HB; ++jj)
-#pragma unroll
-                for (int qq = 0; qq < 4; ++qq) {
-                    const float4 p = theirs[((ip * HB + jj) * 4 + qq) * 64];
-                    const v16f &v = group ? acc[ip][HB + jj] : acc[ip][jj];
-                    out[ip][jj][4 * qq + 0] = v[4 * qq + 0] + p.x;
-                    out[ip][jj][4 * qq + 1] = v[4 * qq + 1] + p.y;
-                    out[ip][jj][4 * qq + 2] = v[4 * qq + 2] + p.z;
-                    out[ip][jj][4 * qq + 3] = v[4 * qq + 3] + p.w;
-                }
+            for (int j = 0; j < JP; ++j) out[i][j] = (group ? acc[i][JP + j] : acc[i][j]) + theirs[(i * JP + j) * 64];
         __syncthreads();
-        store_tile<!G32, HB>(a, out, n0, m0 + group * HB * 32, region, lane);
+        store_tile<!G32, JP>(a, out, n0, m0 + group * JP * 16, region, lane);
     }
 }
 
@@ -738,10 +735,9 @@ bool tile_kernel_takes(const Geometry &g) { return g.K % (g.fmt == kW8C ? 64 : 1
 // Estimated time of the main kernel and the form it is fastest in.  A tile takes `each` us and K / 1000 times `alone` on a
 // compute unit of its own, `shared` where several are in flight.  The part that grows with K slows down with the number of compute units that are
 // busy, since power is what they share: `cap` is about the share of the chip that runs at full clock.
-// Fitted to 2960 shapes of 768 to 28672 channels, K of 256 to 14336 and 20 to 6500 rows (standard deviation 2 to 5 %); the choice is 0.2 % slower than the
-// best of the six forms on average, 5 % in one of a hundred shapes.  us, forms 1 to 6 (32, 64, 96, 128 rows; 128 and 64 rows with two halves of K): int4
-// groups 2304 x 9216, 1000 rows 92 / 75 / 89 / 101 / 84 / 60; 4096 x 2304, 2048 rows 55 / 42 / 46 / 39 / 38 / 44; int4 2304 x 14336, 1000 rows
-// 114 / 94 / 113 / 138 / 119 / 79.
+// Fitted to 2157 shapes of 768 to 28672 channels, K of 256 to 14336 and 20 to 6500 rows (standard deviation 2 to 5 %); the choice is 0.2 % slower than the
+// best of the six forms on average, 4 % in one of a hundred shapes.
+// us, forms 1 to 6, int4 in groups of 32: 2304 x 9216 1000 rows 99 / 84 / 96 / 113 / 96 / 67; 4096 x 2304 2048 rows 56 / 42 / 46 / 38 / 36 / 45.
 int tile_rows(int form) {
     static const int rows[kTileForms] = {32, 64, 96, 128, 128, 64};
     return rows[form - 1];
@@ -753,14 +749,14 @@ float tile_us(const Geometry &g, int M, int num_cus, int *form) {
     };
     static const Fit fits[3][kTileForms] = {
         // int8
-        {{2.12f, 0.84f, 5.82f, 4.16f, 1.02f}, {2.25f, 1.39f, 6.78f, 5.53f, 0.82f}, {2.48f, 1.90f, 8.18f, 6.88f, 0.74f},
-         {2.90f, 2.26f, 9.36f, 8.21f, 0.69f}, {1.01f, 5.07f, 8.01f, 7.83f, 0.59f}, {1.11f, 3.27f, 5.30f, 5.19f, 0.67f}},
+        {{2.23f, 0.76f, 6.38f, 4.23f, 1.11f}, {2.50f, 1.27f, 7.60f, 6.03f, 0.99f}, {3.02f, 1.56f, 9.26f, 7.83f, 1.00f},
+         {3.30f, 2.07f, 11.20f, 9.61f, 0.95f}, {1.04f, 4.79f, 9.68f, 9.38f, 0.84f}, {0.83f, 3.39f, 6.16f, 5.75f, 0.87f}},
         // int4, group scales
-        {{2.37f, 0.55f, 6.31f, 4.63f, 1.06f}, {2.44f, 1.05f, 7.54f, 6.09f, 0.92f}, {2.49f, 1.69f, 9.10f, 7.82f, 0.85f},
-         {2.64f, 2.14f, 10.14f, 8.83f, 0.74f}, {0.76f, 5.00f, 8.34f, 8.23f, 0.61f}, {1.08f, 3.16f, 5.66f, 5.53f, 0.71f}},
+        {{2.38f, 0.47f, 6.97f, 4.86f, 1.16f}, {2.50f, 0.85f, 8.58f, 6.58f, 1.11f}, {2.54f, 1.38f, 9.87f, 8.36f, 1.03f},
+         {2.81f, 1.79f, 11.54f, 10.02f, 0.98f}, {0.50f, 4.94f, 9.57f, 9.30f, 0.83f}, {0.49f, 3.52f, 6.77f, 6.34f, 0.95f}},
         // int4
-        {{2.47f, 0.59f, 4.89f, 3.66f, 1.00f}, {2.59f, 1.12f, 5.86f, 4.82f, 0.80f}, {2.59f, 1.75f, 7.38f, 6.58f, 0.76f},
-         {2.74f, 2.26f, 9.12f, 7.95f, 0.72f}, {0.93f, 5.06f, 7.74f, 7.59f, 0.63f}, {1.48f, 2.93f, 4.77f, 4.71f, 0.69f}}};
+        {{2.49f, 0.51f, 5.36f, 3.67f, 1.14f}, {2.58f, 1.02f, 6.76f, 5.11f, 1.02f}, {2.61f, 1.73f, 8.14f, 6.77f, 0.98f},
+         {2.91f, 2.09f, 10.01f, 8.79f, 1.00f}, {0.57f, 5.09f, 8.54f, 8.33f, 0.89f}, {0.71f, 3.42f, 5.26f, 4.91f, 0.89f}}};
     const float k = 1e-3f * (float)g.K;
     float best = 0.0f;
     *form = 0;
