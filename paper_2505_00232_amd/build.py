@@ -28,7 +28,7 @@ SOURCE_FLAGS = {"attention.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]}
 # waits themselves: the compiler takes a destination register to be valid right after the load
 # instruction, so if it spilled one it would save the stale value.  The build refuses any spill
 # in these kernels (mangled-name fragments per source file).
-NO_SPILL = {"gemm_i8.hip": ("gemm_i8_dw_kernel", "gemm_i8_dw4_kernel")}
+NO_SPILL = {"gemm_i8.hip": ("gemm_i8_dw_kernel",)}
 
 
 def _spilling_kernels(remarks: list[str], fragments: tuple[str, ...]) -> list[str]:
