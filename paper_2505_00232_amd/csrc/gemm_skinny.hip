@@ -419,7 +419,85 @@ __global__ __launch_bounds__(MAXT) void skinny_i8_kernel(SkinnyArgs a) {
     finish<R, TB, int, true>(a, red, blockDim.x >> 6, rt0, m0, rows);
 }
 
+constexpr int kStreamSteps = 4, kStreamTiles = 2;
+
+// The same products for up to 32 token rows and many channels: the workgroups stay (one grid of them fills the chip), a wavefront keeps
+// its 512 k of the token rows in registers for good and walks over row tiles, two at a time.  A vector of weights is requested
+// again, for the next tile, as soon as it has been multiplied, so that the weights' stream does not stop between tiles, and it is the
+// only one: the token rows are read once per workgroup instead of once per four row tiles or so.
+// What bounds it: the stream, which a barrier per group and the store phase still hold up (5.9 to 6.2 TB/s with K of 4096 and 8192). us, 24
+// token rows, skinny_i8_kernel / this: 65536 x 4096 57.7 / 46.0; 128256 x 4096 103 / 90 (9 rows 98 / 84); 256000 x 4096 196 / 181; 65536 x
+// 8192 105 / 88; 100000 x 1024 27.7 / 21.5.  Two row tiles at a time: with one the compiler has no registers left for requests in flight
+// across the store phase.  4-bit weights, half the bytes in flight: 128256 x 4096 32 rows 49 / 53, not built.
+template <int TB>
+__global__ __launch_bounds__(1024) void skinny_i8_stream_kernel(SkinnyArgs a) {
+    constexpr int R = kStreamTiles, KS = 2 * kStreamSteps;  // KS: k steps of 64 of a wavefront
+    extern __shared__ u32x4 lds[];
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int waves = blockDim.x >> 6, XT = a.Kp / 64, s0 = wave * KS;
+    v4i xv[KS][TB];
+#pragma unroll
+    for (int s = 0; s < KS; ++s)
+#pragma unroll
+        for (int tb = 0; tb < TB; ++tb) {
+            // (token rows past the last tile of 16: clamped, results dropped)
+            xv[s][tb] = __builtin_bit_cast(v4i, a.x[((size_t)min(tb, (a.M - 1) / 16) * XT + s0 + s) * 64 + lane]);
+        }
+    u32x4 wv[KS];
+    auto load = [&](int s, int tile) __attribute__((always_inline)) {
+        wv[s] = __builtin_nontemporal_load(a.w + ((size_t)min(tile, a.RT - 1) * a.rt_stride + s0 + s) * 64 + lane);
+    };
+    int tile = blockIdx.x * R, buf = 0;
+    const int stride = gridDim.x * R;
+#pragma unroll
+    for (int s = 0; s < KS; ++s) load(s, tile);
+    auto group = [&](auto more) __attribute__((always_inline)) {
+        v4i acc[R][TB];
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+#pragma unroll
+            for (int tb = 0; tb < TB; ++tb) acc[r][tb] = v4i{0, 0, 0, 0};
+#pragma unroll
+            for (int s = 0; s < KS; ++s) {
+#pragma unroll
+                for (int tb = 0; tb < TB; ++tb)
+                    acc[r][tb] = __builtin_amdgcn_mfma_i32_16x16x64_i8(xv[s][tb], __builtin_bit_cast(v4i, wv[s]), acc[r][tb], 0, 0, 0);
+                if (r + 1 < R || decltype(more)::value) load(s, r + 1 < R ? tile + r + 1 : tile + stride);
+            }
+        }
+        int *red = reinterpret_cast<int *>(lds) + buf * (waves * R * TB * 256);
+        put_partials<R, TB>(red, acc, wave, lane);
+        // (two buffers: whoever writes this one again has passed the barrier of the group in between, behind which nobody reads it.  The
+        // requests of weights stay in flight.)
+        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        finish<R, TB, int, true>(a, red, waves, tile, 0, a.M);
+        buf ^= 1;
+    };
+    for (; tile + stride < a.RT; tile += stride) group(std::true_type());
+    group(std::false_type());
+}
+
 constexpr size_t kLdsLimit = 160 * 1024;
+
+unsigned stream_grid(const SkinnyArgs &a, int waves, int num_cus) {  // (16 wavefronts of 128 registers fill a compute unit)
+    return min((unsigned)((a.RT + kStreamTiles - 1) / kStreamTiles), (unsigned)(16 / waves * num_cus));
+}
+
+// Which int8 layers skinny_i8_stream_kernel takes (8-bit weights).  K of whole multiples of 4096: there the other kernel's workgroups are 64 KiB apart
+// and meet in few memory channels, while here those of a compute unit spread over K.  us, that one / this, 24 rows: 32768 x 4096 26.9 / 25.3,
+// 100000 x 4096 84.8 / 72.5, x 8192 161 / 136.  At other K both are level (65536 x 3072 36.6 / 36.1, x 5120 57.8 / 56.6, x 6144 66.2 / 67.5) or
+// this loses (202048 x 2048 72 / 78; x 2560, five wavefronts on four SIMDs, 89 / 104).  From two rounds of the grid on, the last
+// at least partly full: 28672 x 4096 20 rows 23.6 / 23.9, 50304 x 8192, 3.07 rounds, 68.7 / 72.6.  K of 512 and 1024: the other kernel's wavefronts have one or
+// two steps (152064 x 512 20.9 / 18.4; 65536 x 1024 19.8 / 15.1, 256000 x 1024 59.1 / 53.6).
+bool stream_takes(const SkinnyArgs &a, int num_cus) {
+    if (a.M > 32 || tuning().skinny_waves > 0 || tuning().skinny_row_tiles > 0 || tuning().skinny_blocks > 0) return false;
+    const int steps = a.Kp / 128, waves = steps / kStreamSteps;
+    if (steps % kStreamSteps != 0 || waves > 16) return false;
+    const int groups = (a.RT + kStreamTiles - 1) / kStreamTiles, grid = 16 / waves * num_cus;
+    if (a.Kp <= 1024) return groups >= grid;
+    return a.Kp % 4096 == 0 && groups >= 2 * grid && 5 * groups >= 4 * ((groups + grid - 1) / grid * grid);
+}
 
 void split_steps(SkinnyArgs &a, int steps, int waves) {
     a.steps_q = steps / waves;
@@ -476,6 +554,15 @@ hipError_t launch_i8(SkinnyArgs a, int num_cus, hipStream_t st) {
     split_steps(a, steps, waves);
     if (const hipError_t e = allow_dynamic_lds<skinny_i8_kernel<W4, TB, R, D, MAXT>>(kLdsLimit); e != hipSuccess) return e;
     skinny_i8_kernel<W4, TB, R, D, MAXT><<<dim3(grid_for(a, R)), dim3((unsigned)(waves * 64)), waves * per_wave, st>>>(a);
+    return hipGetLastError();
+}
+
+template <int TB>
+hipError_t launch_i8_stream(const SkinnyArgs &a, int num_cus, hipStream_t st) {
+    const int waves = a.Kp / 128 / kStreamSteps;
+    const size_t bytes = (size_t)2 * waves * kStreamTiles * TB * 1024;  // (at most 128 KiB)
+    if (const hipError_t e = allow_dynamic_lds<skinny_i8_stream_kernel<TB>>(kLdsLimit); e != hipSuccess) return e;
+    skinny_i8_stream_kernel<TB><<<dim3(stream_grid(a, waves, num_cus)), dim3((unsigned)(waves * 64)), bytes, st>>>(a);
     return hipGetLastError();
 }
 
@@ -769,6 +856,7 @@ hipError_t launch_skinny_f16(const Geometry &g, const void *packed, const void *
 hipError_t launch_skinny_i8(const Geometry &g, const void *packed, const int8_t *xq_tiled, const float *sx, int M,
                             void *y, const void *residual, int gated_act, int num_cus, hipStream_t st) {
     SkinnyArgs a = make_args(g, packed, xq_tiled, sx, M, y, residual, gated_act);
+    if (g.fmt == kW8C && stream_takes(a, num_cus)) return M <= 16 ? launch_i8_stream<1>(a, num_cus, st) : launch_i8_stream<2>(a, num_cus, st);
     choose_blocks(a, g.fmt, true, num_cus);
     if (g.fmt == kW4C) {
         a.sw_mul = 0.0625f;

@@ -320,6 +320,39 @@ def test_int8_prefill_int4_weights_llama_ffn_shapes_sampled():
         layer.close()
 
 
+@pytest.mark.parametrize("N,K,M,residual", [(65564, 1024, 9, False), (65535, 992, 17, True), (40961, 4096, 32, False), (40964, 4064, 16, True), (32768, 8192, 25, False)])
+def test_int8_few_rows_of_many_channels(N, K, M, residual):
+    """Layers whose workgroups stay and walk over row tiles (odd counts of them, ragged channels, k and rows): the sums are whole numbers,
+    so the outputs are those of the kernel with one workgroup per few row tiles, bit for bit, and right where the oracle looks."""
+    print(f"int8 few rows of many channels N={N} K={K} M={M} residual={residual}", flush=True)
+    gen = torch.Generator().manual_seed(N + K + M)
+    wq = torch.randint(-127, 128, (N, K), generator=gen, dtype=torch.int8)
+    sw = torch.rand(N, generator=gen) * 1e-3 + 1e-4
+    x = torch.randn((M, K), generator=gen).half()
+    res = torch.randn((M, N), generator=gen).half() if residual else None
+    layer = binding.QuantLinear(wq.to(DEV), sw.to(DEV), "w8c", compute_mode=1, max_m=M)
+    xd, rd = x.to(DEV), res.to(DEV) if residual else None
+    outs = []
+    try:
+        for blocks in (0, 1):  # 1: the other kernel
+            binding.qfc_tune(11, blocks)
+            y = torch.full((M, N), 9.0, dtype=torch.float16, device=DEV)
+            if residual:
+                binding.qfc_forward_fused(layer.handle, xd, y, residual=rd)
+            else:
+                binding.qfc_forward(layer.handle, xd, y)
+            outs.append(y)
+        torch.cuda.synchronize()
+    finally:
+        binding.qfc_tune(11, 0)
+        layer.close()
+    assert torch.equal(outs[0], outs[1])
+    if not residual:
+        cols = np.unique(np.concatenate([np.arange(40), np.arange(N - 70, N), np.random.default_rng(N).integers(0, N, 200)]))
+        y_ref = oracle.fc_int8_act(x.numpy(), wq.numpy()[cols], sw.numpy()[cols])[3]
+        assert _E(outs[0].cpu().numpy()[:, cols], y_ref) <= TOL
+
+
 @pytest.mark.parametrize("variant", [1, 4, 5, 6, 10, 11, 12, 13, 14, 15])
 def test_int8_prefill_other_tile_shapes_bit_exact(variant):
     """The tile shapes the dispatcher picks for larger problems (and the selectable ones),
