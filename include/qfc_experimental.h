@@ -24,7 +24,7 @@ extern "C" {
  * key, never a torn one).  Unknown keys are ignored.
  *   key 0  target number of wavefronts of a decode launch (0 = automatic: 8192 up to two token rows, 2048 above)
  *   key 1  most row tiles a decode workgroup walks (0 = automatic: 2 up to two token rows, 4 above)
- *   key 2  prefill kernel variant (0 = automatic; binary16 activations: 9 the kernel for any K, 31 .. 36 the forms of the main
+ *   key 2  prefill kernel variant (0 = automatic; binary16 activations: 9 the kernel for any K, 31 .. 37 the forms of the main
  *          kernel: 32, 64, 96, 128 token rows per workgroup, 128 and 64 with K in two halves)
  *   key 3  token rows per workgroup of the activation quantization kernel (0 = automatic; 2, 4, 8)
  *   key 4  half-unit items of the decode kernel (-1 automatic, 0 never, 1 where possible)

@@ -671,24 +671,41 @@ __global__ __launch_bounds__(256 * KS, KS == 2 ? 2 : JP == 1 ? 4 : JP == 2 ? 3 :
     if constexpr (KS == 1) {
         store_tile<!G32, NJ>(a, acc, n0, m0, region, lane);
     } else {
-        // The two halves of K meet: each group keeps half of the token rows and hands the other half to its partner through LDS
-        // ([wavefront][16-byte vector][lane]), over the dead rings.
-        constexpr int kEx = 4 * JP * 1024;  // bytes per wavefront
-        static_assert(KS == 1 || (JP % 2 == 0 && 8 * kEx <= 2 * L::kBytes), "halves of the sums fit over the rings");
-        v4f *mine = reinterpret_cast<v4f *>(lds_all + (group * 4 + wave) * kEx) + lane;
+        // The two halves of K meet: the first group keeps the first H0 blocks of 16 token rows, the other the rest (an even number each), and each hands
+        // the other's over through LDS ([group][wavefront][16-byte vector][lane]), over the dead rings.
+        constexpr int H0 = (JP + 1) / 2 * 2, H1 = 2 * JP - H0;
+        static_assert(16 * 2 * JP * 1024 <= 2 * L::kBytes, "the sums handed over fit over the rings");
+        v4f *const to0 = reinterpret_cast<v4f *>(lds_all) + wave * (4 * H0 * 64) + lane;
+        v4f *const to1 = reinterpret_cast<v4f *>(lds_all) + 16 * H0 * 64 + wave * (4 * H1 * 64) + lane;
+        if (group) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
+            for (int i = 0; i < 4; ++i)
 #pragma unroll
-            for (int j = 0; j < JP; ++j) mine[(i * JP + j) * 64] = group ? acc[i][j] : acc[i][JP + j];
+                for (int j = 0; j < H0; ++j) to0[(i * H0 + j) * 64] = acc[i][j];
+        } else {
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int j = 0; j < H1; ++j) to1[(i * H1 + j) * 64] = acc[i][H0 + j];
+        }
         __syncthreads();
-        const v4f *theirs = reinterpret_cast<const v4f *>(lds_all + ((group ^ 1) * 4 + wave) * kEx) + lane;
-        v4f out[4][JP];
+        if (group) {
+            v4f out[4][H1];
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
+            for (int i = 0; i < 4; ++i)
 #pragma unroll
-            for (int j = 0; j < JP; ++j) out[i][j] = (group ? acc[i][JP + j] : acc[i][j]) + theirs[(i * JP + j) * 64];
-        __syncthreads();
-        store_tile<!G32, JP>(a, out, n0, m0 + group * JP * 16, region, lane);
+                for (int j = 0; j < H1; ++j) out[i][j] = acc[i][H0 + j] + to1[(i * H1 + j) * 64];
+            __syncthreads();
+            store_tile<!G32, H1>(a, out, n0, m0 + H0 * 16, region, lane);
+        } else {
+            v4f out[4][H0];
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int j = 0; j < H0; ++j) out[i][j] = acc[i][j] + to0[(i * H0 + j) * 64];
+            __syncthreads();
+            store_tile<!G32, H0>(a, out, n0, m0, region, lane);
+        }
     }
 }
 
@@ -713,7 +730,7 @@ hipError_t launch_fallback(GemmF16Args a, int M, hipStream_t st) {
     return hipGetLastError();
 }
 
-constexpr int kTileForms = 6;
+constexpr int kTileForms = 7;
 
 template <int FMT>
 hipError_t tile_form(const GemmF16Args &a, int form, hipStream_t st) {
@@ -724,6 +741,7 @@ hipError_t tile_form(const GemmF16Args &a, int form, hipStream_t st) {
         case 4: return launch_tile<FMT, 4, 1>(a, st);
         case 5: return launch_tile<FMT, 4, 2>(a, st);
         case 6: return launch_tile<FMT, 2, 2>(a, st);
+        case 7: return launch_tile<FMT, 3, 2>(a, st);
     }
     return hipErrorInvalidValue;
 }
@@ -736,10 +754,13 @@ bool tile_kernel_takes(const Geometry &g) { return g.K % (g.fmt == kW8C ? 64 : 1
 // compute unit of its own, `shared` where several are in flight.  The part that grows with K slows down with the number of compute units that are
 // busy, since power is what they share: `cap` is about the share of the chip that runs at full clock.
 // Fitted to 2157 shapes of 768 to 28672 channels, K of 256 to 14336 and 20 to 6500 rows (standard deviation 2 to 5 %); the choice is 0.2 % slower than the
-// best of the six forms on average, 4 % in one of a hundred shapes.
+// best of the first six forms on average, 4 % in one of a hundred shapes.  Form 7 lies between 5 and 6, and so do its numbers: within 3 % on 1562 more
+// shapes of 150 to 4096 rows, the choice among all 0.05 % slower than the best (without form 7 1.1 %).
 // us, forms 1 to 6, int4 in groups of 32: 2304 x 9216 1000 rows 99 / 84 / 96 / 113 / 96 / 67; 4096 x 2304 2048 rows 56 / 42 / 46 / 38 / 36 / 45.
+// Forms 3 / 5 / 7: 2304 x 9216 2048 rows 97 / 96 / 89, x 2048 25.6 / 26.2 / 23.4; int4 4096 x 14336 1500 rows 139 / 141 / 130; int8 4096 x 4096 1400
+// rows 48.4 / 48.4 / 45.6; 4096 x 2304 2048 rows, 256 tiles of 128 and 352 of 96, - / 35.8 / 50.4.
 int tile_rows(int form) {
-    static const int rows[kTileForms] = {32, 64, 96, 128, 128, 64};
+    static const int rows[kTileForms] = {32, 64, 96, 128, 128, 64, 96};
     return rows[form - 1];
 }
 
@@ -750,13 +771,13 @@ float tile_us(const Geometry &g, int M, int num_cus, int *form) {
     static const Fit fits[3][kTileForms] = {
         // int8
         {{2.23f, 0.76f, 6.38f, 4.23f, 1.11f}, {2.50f, 1.27f, 7.60f, 6.03f, 0.99f}, {3.02f, 1.56f, 9.26f, 7.83f, 1.00f},
-         {3.30f, 2.07f, 11.20f, 9.61f, 0.95f}, {1.04f, 4.79f, 9.68f, 9.38f, 0.84f}, {0.83f, 3.39f, 6.16f, 5.75f, 0.87f}},
+         {3.30f, 2.07f, 11.20f, 9.61f, 0.95f}, {1.04f, 4.79f, 9.68f, 9.38f, 0.84f}, {0.83f, 3.39f, 6.16f, 5.75f, 0.87f}, {0.93f, 4.1f, 7.92f, 7.56f, 0.86f}},
         // int4, group scales
         {{2.38f, 0.47f, 6.97f, 4.86f, 1.16f}, {2.50f, 0.85f, 8.58f, 6.58f, 1.11f}, {2.54f, 1.38f, 9.87f, 8.36f, 1.03f},
-         {2.81f, 1.79f, 11.54f, 10.02f, 0.98f}, {0.50f, 4.94f, 9.57f, 9.30f, 0.83f}, {0.49f, 3.52f, 6.77f, 6.34f, 0.95f}},
+         {2.81f, 1.79f, 11.54f, 10.02f, 0.98f}, {0.50f, 4.94f, 9.57f, 9.30f, 0.83f}, {0.49f, 3.52f, 6.77f, 6.34f, 0.95f}, {0.5f, 4.2f, 8.17f, 7.82f, 0.9f}},
         // int4
         {{2.49f, 0.51f, 5.36f, 3.67f, 1.14f}, {2.58f, 1.02f, 6.76f, 5.11f, 1.02f}, {2.61f, 1.73f, 8.14f, 6.77f, 0.98f},
-         {2.91f, 2.09f, 10.01f, 8.79f, 1.00f}, {0.57f, 5.09f, 8.54f, 8.33f, 0.89f}, {0.71f, 3.42f, 5.26f, 4.91f, 0.89f}}};
+         {2.91f, 2.09f, 10.01f, 8.79f, 1.00f}, {0.57f, 5.09f, 8.54f, 8.33f, 0.89f}, {0.71f, 3.42f, 5.26f, 4.91f, 0.89f}, {0.64f, 4.25f, 6.9f, 6.62f, 0.89f}}};
     const float k = 1e-3f * (float)g.K;
     float best = 0.0f;
     *form = 0;

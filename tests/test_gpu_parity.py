@@ -615,7 +615,7 @@ def test_fp16_prefill_whole_output_two_kernels_agree(fmt, M):
     layer.close()
 
 
-@pytest.mark.parametrize("form", [31, 32, 33, 34, 35, 36])
+@pytest.mark.parametrize("form", [31, 32, 33, 34, 35, 36, 37])
 @pytest.mark.parametrize("fmt", ["w4g32", "w4c", "w8c"])
 def test_fp16_tiles_of_every_form(form, fmt):
     """The main kernel with binary16 activations in each of its forms (32 to 128 token rows per workgroup, K in one piece or two): one
