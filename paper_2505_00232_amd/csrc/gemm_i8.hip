@@ -515,13 +515,11 @@ __global__ __launch_bounds__(256, 2) void gemm_i8_dw_kernel(GemmI8Args a) {
 #pragma unroll
     for (int i = 0; i < TN; ++i) wsrc[i] = a.w + ((size_t)(nt * (BN / 16) + 4 * wave + i) * KT) * (64 * WV) + lane;
     v4i wreg[PW][TN][WV];
-    auto load_w = [&](int slot, int kt, const bool bulk) __attribute__((always_inline)) {  // bulk: kt < KT is known
+    auto load_w = [&](int slot, int kt, int v, const bool bulk) __attribute__((always_inline)) {  // vector v of the row tiles; bulk: kt < KT is known
         const int kc = bulk || kt < KT ? kt : min(kt - KT, KT - 1);
 #pragma unroll
         for (int i = 0; i < TN; ++i)
-#pragma unroll
-            for (int v = 0; v < WV; ++v)
-                asm volatile("global_load_dwordx4 %0, %1, off" : "=&v"(wreg[slot][i][v]) : "v"(wsrc[i] + (size_t)(WV * kc + v) * 64) : "memory");
+            asm volatile("global_load_dwordx4 %0, %1, off" : "=&v"(wreg[slot][i][v]) : "v"(wsrc[i] + (size_t)(WV * kc + v) * 64) : "memory");
     };
     // activations: tile t = 2 g + e of a stage is half e of the stage's 128 k for token rows 16 g ..
     const uint32_t lds0 = (uint32_t)(uintptr_t)(lptr_t)lds;
@@ -546,7 +544,9 @@ __global__ __launch_bounds__(256, 2) void gemm_i8_dw_kernel(GemmI8Args a) {
 
     constexpr bool kBulk = true, kEdge = false;
 #pragma unroll
-    for (int p = 0; p < PW; ++p) load_w(p, p, kEdge);
+    for (int p = 0; p < PW; ++p)
+#pragma unroll
+        for (int v = 0; v < WV; ++v) load_w(p, p, v, kEdge);
 #pragma unroll
     for (int p = 0; p < NS - 1; ++p) issue_x(p, kEdge);
 
@@ -602,8 +602,8 @@ __global__ __launch_bounds__(256, 2) void gemm_i8_dw_kernel(GemmI8Args a) {
                         fb[j] = __builtin_bit_cast(v4i, lx[(2 * j + 1) * 64 + lane]);
                     }
                 }
+                if (!W4 || ks == 1) load_w(u, kt + PW, W4 ? 0 : ks, bulk);  // (the vectors that this step was the last to use)
             }
-            load_w(u, kt + PW, bulk);
         }
     };
     constexpr int kAhead = NS - 1 > PW ? NS - 1 : PW;  // how far past kt a pass issues
