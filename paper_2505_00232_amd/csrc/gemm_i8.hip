@@ -666,12 +666,12 @@ hipError_t launch_w4(GemmI8Args a, hipStream_t st) {
 
 // Tiles of 256 channels: 128 tokens each where those tiles are for three quarters of the compute units and more, or where tiles of
 // 64 would start a second round that costs more than the larger tiles' idle compute units.  With int8 weights it does at once (us, 64 /
-// 128 tokens: 18432 x 2304 240 rows, 288 tiles of 64, 31.3 / 23.8; 2304 x 9216 1826 rows, 261 tiles, 70 / 63, 2274 rows 80 / 63;
-// 11000 x 3008 500 rows 37.3 / 26.9), with int4 weights from a quarter of a round on (5120 x 9216 802 rows, 260 tiles, 52 / 56, 1152
-// rows, 360 tiles, 59 / 56; 1536 x 14336 2722 rows, 258 tiles, 82 / 88).  Outputs that are stored as they lie in the registers
+// 128 tokens: 18432 x 2304 240 rows, 288 tiles of 64, 24.9 / 21.1; 2304 x 9216 1826 rows, 261 tiles, 81 / 60, 2274 rows 93 / 65;
+// 11000 x 3008 500 rows 30.5 / 25.9), with int4 weights from a quarter of a round on (5120 x 9216 802 rows, 260 tiles, 62.1 / 62.4, 1152
+// rows, 360 tiles, 66 / 64; 1536 x 14336 2722 rows, 258 tiles, 97 / 99).  Outputs that are stored as they lie in the registers
 // (accumulators; rows that are no multiple of 16 bytes) take longer than the round from 128-token tiles: with int4 weights
-// always (4100 x 4096 1211 rows 34.9 / 38.7, 9001 x 1024 600 rows 26.0 / 31.8), with int8 weights below K of 4096 (4100 x 1024 1211 rows
-// 19.0 / 22.6, 9001 x 2304 600 rows 36.2 / 39.4, x 4096 52.7 / 49.1).
+// always (4100 x 4096 1211 rows 39.2 / 43.7, 9001 x 1024 600 rows 25.2 / 31.5), with int8 weights below K of 4096 (4100 x 1024 1211 rows
+// 21.7 / 24.9, 9001 x 2304 600 rows 36.4 / 38.5, x 4096 48.4 / 46.1).
 bool tiles_of_128_tokens(const GemmI8Args &a, bool w4, bool staged_store, int num_cus) {
     const long n256 = (a.N + 255) / 256, m128 = (a.M + 127) / 128, m64 = (a.M + 63) / 64;
     if (4 * n256 * m128 >= 3L * num_cus) return true;
