@@ -558,9 +558,9 @@ __global__ __launch_bounds__(256 * KS, KS == 2 ? 2 : JP == 1 ? 4 : JP == 2 ? 3 :
         if (W8 && tiles > 1) codes(1);
         if (nst > 1) rows(1);
         if (tiles <= 1)
-            wait_vmcnt<0>();
+            wait_copies<0>();
         else
-            wait_vmcnt<2 * XC + (W8 ? WC : 0)>();
+            wait_copies<2 * XC + (W8 ? WC : 0)>();
         read_ws(0);
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // the codes are in registers: their slot may be overwritten
         if (tiles > (W8 ? 2 : 1)) codes(W8 ? 2 : 1);

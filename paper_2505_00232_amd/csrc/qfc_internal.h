@@ -180,6 +180,13 @@ template <int N>
 __device__ __forceinline__ void wait_vmcnt() {
     __builtin_amdgcn_s_waitcnt((N & 0xF) | ((N >> 4) << 14) | (0x7 << 4) | (0x0 << 8));
 }
+// The same in front of reads of what was copied, where no barrier or fence follows.  Nothing defines the builtin as an access to
+// memory (loads from global memory have been seen to move from behind it to before it): the clobber keeps the reads behind it.
+template <int N>
+__device__ __forceinline__ void wait_copies() {
+    wait_vmcnt<N>();
+    asm volatile("" ::: "memory");
+}
 
 // Direct global -> LDS copy of one wavefront: lane l moves 16 bytes from base + lane_offset(l) to
 // LDS byte address lds_base + 16 l.  Written as assembly because the compiler, when it knows

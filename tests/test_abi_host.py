@@ -170,3 +170,25 @@ def test_prefill_walk_copies_land_before_they_are_read_and_end_with_the_walk(tmp
                     os.path.join(ROOT, "tests", "attention_walk.cpp"), "-o", exe], check=True)
     r = subprocess.run([exe], capture_output=True, text=True)
     assert r.returncode == 0, r.stdout[-2000:]
+
+
+def test_reads_of_lds_stay_behind_the_wait_for_copies(tmp_path):
+    """A kernel that reads a slot of LDS, waits for the copies into it and reads it again: two reads in the compiled code, one on
+    each side of the wait."""
+    from paper_2505_00232_amd import build
+    src, out = tmp_path / "wait.hip", tmp_path / "wait.s"
+    src.write_text("""#include "qfc_internal.h"
+__global__ void k(uint32_t *y) {
+    __shared__ uint32_t lds[256];
+    qfc::copy16_to_lds(y, threadIdx.x * 16, (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void *)lds);
+    const uint32_t before = lds[threadIdx.x];
+    qfc::wait_copies<3>();
+    y[threadIdx.x] = before - lds[threadIdx.x];
+}
+""")
+    subprocess.run([build._hipcc(), *build.FLAGS, "-w", "-I", build.CSRC, "--cuda-device-only", "-S", str(src), "-o", str(out)], check=True)
+    code = [l.strip() for l in out.read_text().splitlines()]
+    waits = [i for i, l in enumerate(code) if l.startswith("s_waitcnt") and "vmcnt(3)" in l]
+    reads = [i for i, l in enumerate(code) if l.startswith("ds_read")]
+    assert len(waits) == 1 and len(reads) == 2, (waits, reads)
+    assert reads[0] < waits[0] < reads[1]
