@@ -24,6 +24,7 @@
 #include <type_traits>
 
 #include "qfc_internal.h"
+#include "tile_rows.h"
 
 namespace qfc {
 namespace {
@@ -465,16 +466,13 @@ __global__ __launch_bounds__(256 * KS, KS == 2 ? 2 : JP == 1 ? 4 : JP == 2 ? 3 :
     const int nst = group ? nst_all - first : first, i0 = group ? first : 0;
     const uint32_t lds0 = (uint32_t)(uintptr_t)(lptr_t)lds + group * L::kBytes;
 
-    // rows past the last (their products are never stored) take the rows of the tile before, so that no line is copied over and over
-    const int back = m0 > 0 ? ROWS : 0;
-    const char *xbase = reinterpret_cast<const char *>(a.x) + (size_t)(m0 - back) * a.K * 2;
+    const char *xbase = reinterpret_cast<const char *>(a.x) + (size_t)(m0 - rows_in_front(m0, ROWS)) * a.K * 2;
     uint32_t xlane[XC];
 #pragma unroll
     for (int i = 0; i < XC; ++i) {
-        const int rl = 8 * wave + 32 * i + (lane >> 3);
+        const int rl = 32 * i + 8 * wave + (lane >> 3);
         const int oct = (lane & 7) ^ ((rl >> 1) & 7);
-        const int row = m0 + rl < a.M ? back + rl : back ? rl : a.M - 1;
-        xlane[i] = (uint32_t)row * (uint32_t)a.K * 2u + oct * 16;
+        xlane[i] = (uint32_t)source_row(i, wave, lane >> 3, m0, a.M, ROWS) * (uint32_t)a.K * 2u + oct * 16;
     }
     const size_t rt_bytes = (size_t)a.rt_stride * 1024;
     const char *wbase = reinterpret_cast<const char *>(a.w) + (size_t)(nt * 16 + wave * 4) * rt_bytes;

@@ -192,3 +192,33 @@ __global__ void k(uint32_t *y) {
     reads = [i for i, l in enumerate(code) if l.startswith("ds_read")]
     assert len(waits) == 1 and len(reads) == 2, (waits, reads)
     assert reads[0] < waits[0] < reads[1]
+
+
+def test_tiles_copy_no_line_over_and_over(tmp_path):
+    """The token rows that the binary16 tiles copy, for 9 to 400 rows and every number of rows per tile: the rows there are from their own
+    place, the rows past the last from rows there are, and none of a wavefront's copies of a half stage more than twice from the same
+    row (with 16 and 8 rows that the others may take: three and five times)."""
+    src, exe = tmp_path / "rows.cpp", str(tmp_path / "rows")
+    src.write_text("""#include "tile_rows.h"
+#include <cstdio>
+#include <map>
+int main() {
+    for (int rows = 32; rows <= 128; rows += 32)
+        for (int M = 9; M <= 400; ++M)
+            for (int m0 = 0; m0 < M; m0 += rows)
+                for (int wave = 0; wave < 4; ++wave) {
+                    std::map<int, int> copies;
+                    for (int i = 0; i < rows / 32; ++i)
+                        for (int r = 0; r < 8; ++r) {
+                            const int at = m0 + 32 * i + 8 * wave + r, row = m0 - qfc::rows_in_front(m0, rows) + qfc::source_row(i, wave, r, m0, M, rows);
+                            const int most = M >= 32 ? 2 : 1 + rows / (M >= 16 ? 64 : 32);
+                            if (row < 0 || row >= M || (at < M && row != at) || ++copies[row] > most)
+                                return printf("rows %d M %d m0 %d wave %d row %d from %d, copy %d\\n", rows, M, m0, wave, at, row, copies[row]), 1;
+                        }
+                }
+    return 0;
+}
+""")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-D__host__=", "-D__device__=", "-D__forceinline__=inline", "-I", build.CSRC, str(src), "-o", exe], check=True)
+    r = subprocess.run([exe], capture_output=True, text=True)
+    assert r.returncode == 0, r.stdout[-2000:]
