@@ -775,26 +775,23 @@ static float few_rows_us(const Geometry &g, int M, bool gated, int num_cus) {
 // Binary16 activations: rows to leave to the kernels here where the tiles of the others then end with a full round, or without a tile of
 // few rows, if that is estimated to save more than a second launch and a fiftieth; 0: none.  Returns the estimated time.
 // us, tiles alone / like this: 2304 x 9216 int4 groups 3700 rows 164 / 137; 8192 x 4096 int8 1030 rows 69 / 67; 4096 x 4096 int4 2060 rows
-// 63 / 55; 6144 x 4096 int4 3100 rows 131 / 119; 14336 x 14336 int4 groups 1271 rows 495 / 444 (of 1500 random shapes the worst loses 6 %;
-// 22016 x 14336 int4 351 rows 205 / 222).  A K of one step keeps the line that K of all sizes once had, full rounds of 128 rows (8192 x 128, 1030
-// rows 10.9 us in two launches, 8.5 in one): no layer has it, and it is where two launches are tested cheaply.
+// 63 / 55; 6144 x 4096 int4 3100 rows 131 / 119; 14336 x 14336 int4 groups 1271 rows 495 / 444.  Of 1500 random shapes the worst lost 6 %; a worse
+// one is 22016 x 14336 int4 351 rows, 207 / 220.
 static float tail_rows(const Geometry &g, int M, bool gated, int num_cus, int *rest) {
     int form;
     float best = tile_us(g, M, num_cus, &form);
     *rest = 0;
     if (tuning().gemm_variant != 0 || tuning().skinny_max_m >= 0) return best;
-    const bool one_step = g.K < 256;
-    const int n_tiles = (g.N + 255) / 256, form_rows = one_step ? 128 : tile_rows(form);
+    const int n_tiles = (g.N + 255) / 256, form_rows = tile_rows(form);
     if (n_tiles * ((M + form_rows - 1) / form_rows) <= num_cus) return best;  // (one round: a tile of few rows keeps nothing waiting)
     for (const int rows : {form_rows, 128}) {  // (128: the best where no rows are left over)
         const int m_tiles = (M + rows - 1) / rows;
         const int full = (n_tiles * m_tiles - 1) / num_cus * num_cus / n_tiles * rows, whole = (M - 1) / rows * rows;
         for (const int most : {full, whole}) {
             const int r = M - most;
-            if (most < 128 || r > kSkinnyMaxM || (one_step && r > rows)) continue;
+            if (most < 128 || r > kSkinnyMaxM) continue;
             const float us = tile_us(g, most, num_cus, &form) + few_rows_us(g, r, gated, num_cus) + 1.0f;
-            if (us < 0.98f * best || one_step) best = us, *rest = r;
-            if (one_step) return best;
+            if (us < 0.98f * best) best = us, *rest = r;
         }
         if (rows == 128) break;
     }

@@ -222,3 +222,31 @@ int main() {
     subprocess.run(["g++", "-std=c++17", "-O1", "-D__host__=", "-D__device__=", "-D__forceinline__=inline", "-I", build.CSRC, str(src), "-o", exe], check=True)
     r = subprocess.run([exe], capture_output=True, text=True)
     assert r.returncode == 0, r.stdout[-2000:]
+
+
+# What the dispatch chooses for layers with binary16 activations on 256 compute units: format (0 int8, 1 int4 in groups, 2 int4), channels, K, token rows,
+# rows left to the token-row kernels in a second launch (-1: they take them all)
+CHOICES = [
+    # K of less than 256: one launch (us, two / one: 8192 x 128 1030 rows 10.9 / 8.5, 10807 x 128 706 rows 20.0 / 7.8, int8 10501 x 64 1001 rows 19.4 / 9.4)
+    (1, 8192, 128, 1030, 0), (2, 8192, 128, 1030, 0), (2, 10807, 128, 706, 0), (0, 10501, 64, 1001, 0), (0, 8192, 192, 1030, 0),
+    # two launches where those are the faster ones
+    (2, 4096, 4096, 2060, 12), (1, 2304, 9216, 3700, 116), (1, 3072, 1536, 2698, 10), (0, 2048, 1536, 4100, 4),
+]
+
+
+def test_choice_of_kernels_for_binary16_activations(tmp_path):
+    src, exe = tmp_path / "choice.hip", str(tmp_path / "choice")
+    src.write_text("""#include "qfc_internal.h"
+#include <cstdio>
+int main() {
+    for (int fmt, N, K, M; scanf("%d %d %d %d", &fmt, &N, &K, &M) == 4;) {
+        const qfc::Geometry g = qfc::make_geometry(N, K, fmt);
+        printf("%d\\n", qfc::skinny_product(g, M, false, false, 256) ? -1 : qfc::skinny_tail_rows(g, M, false, 256));
+    }
+}
+""")
+    binding.lib()
+    where = os.path.dirname(build.LIB)
+    subprocess.run([build._hipcc(), "-std=c++17", "-w", "--offload-arch=gfx950", "-I", build.CSRC, str(src), "-o", exe, "-L", where, "-lqfc", "-Wl,-rpath," + where], check=True)
+    r = subprocess.run([exe], input="\n".join(" ".join(map(str, c[:4])) for c in CHOICES), capture_output=True, text=True, check=True)
+    assert [int(v) for v in r.stdout.split()] == [c[4] for c in CHOICES]
