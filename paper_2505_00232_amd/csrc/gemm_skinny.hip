@@ -810,11 +810,18 @@ bool skinny_product(const Geometry &g, int M, bool int8_activations, bool gated,
     if (M <= kSkinnyRows && (int8_activations || !tile_kernel_takes(g))) return g.K > tiles_up_to_k(g, M, int8_activations, num_cus);
     if (M > kSkinnyMaxM) return false;
     if (!int8_activations && tile_kernel_takes(g)) {
-        if (M <= kSkinnyRows && g.N < 8192) return true;  // (where the tiles win there, K = 256, it is by 0.3 us, and the estimate costs the host that)
-        const float us = few_rows_us(g, M, gated, num_cus);
-        int form, rest;
-        // (1.05: where both estimates are level the kernels here are the faster more often; 0.18 % behind the best of all, 0.25 % without)
-        return us < 1.05f * tile_us(g, M, num_cus, &form) && us < 1.05f * tail_rows(g, M, gated, num_cus, &rest);
+        // (Fewer than 8192 channels: where the tiles win there, K = 256, it is by 0.3 us, and the estimate costs the host that.  Up to 32
+        // rows, K of 512 and more: the tiles are 1 % faster at most and up to 2.3 times slower, int8 9360 x 1024 12 rows 9.2 / 3.9, 29780 x 512 28 rows
+        // 6.6 / 5.5; at K of 256 the other way round, int4 groups 25938 x 256 21 rows 4.6 / 7.1.)
+        if (M <= kSkinnyRows && (g.N < 8192 || (M <= 32 && g.K >= 512))) return true;
+        int rest;
+        const float here = few_rows_us(g, M, gated, num_cus), tiles = tail_rows(g, M, gated, num_cus, &rest);
+        // (1.05: where both estimates are level the kernels here are the faster more often.  Half a microsecond: at K of 512 and less, where
+        // the products are little more than launches, they are by up to 1.1: us, tiles / here: int8 1404 x 192 73 rows 4.5 / 3.7, 9887 x 256 26 rows
+        // 5.3 / 4.8, int4 311 x 256 442 rows 5.2 / 4.1, int4 groups 3527 x 256 69 rows 5.2 / 4.8.  700 shapes with K of 64 to 1536: 0.36 % behind the faster
+        // of both, 0.46 % without.  420 shapes whose estimates are within a fifth of each other, K of 640 to 14336: 0.5 % behind, the
+        // worst int8 19937 x 11520 68 rows, tiles 76, here 90, and the other way round int8 4404 x 2304 394 rows 19.0 / 17.6)
+        return here < fmaxf(1.05f * tiles, tiles + 0.5f);
     }
     const float here = skinny_us(g, M, int8_activations, gated, num_cus);
     const long n256 = (g.N + 255) / 256, m128 = (M + 127) / 128;
