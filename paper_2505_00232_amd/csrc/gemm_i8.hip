@@ -473,20 +473,28 @@ __global__ __launch_bounds__(256, 2) void gemm_i8_w4_kernel(GemmI8Args a) {
 // at TM = 4) and loads only its own weights, PW stages of 128 k ahead, into a ring of registers (slot = stage % PW,
 // refilled right after the MFMAs that consumed it).  Activation stages: ring of NS LDS stages of two KiB tiles per 16 token rows (4-bit
 // weights: in the k order of the packed dwords), CP tile copies per wavefront and stage.  A block of 16 token rows of a k step is replaced by the
-// next step's as soon as it has been multiplied.  4-bit codes are expanded as in the kernel above.  Copies and loads past the end of K start
+// next step's as soon as it has been multiplied.  4-bit codes are expanded as in the kernel above, those of a stage's second k step during the MFMAs
+// of the first.  Copies and loads past the end of K start
 // over at stage 0, so that every iteration issues the same number of operations and the waits are
 // constants.  Such copies go to a spare KiB behind the ring that is never read (and their sources
 // are distinct stages, not one stage over and over: with about ten copies of the same lines in
 // flight from one wavefront, data had been seen in ring slots after the counter had dropped to zero;
 // the cause is not known, so no late copy may have a destination that anything reads or reuses).
-// The number of stages must be a multiple of PW.
+// The number of stages must be even.
 // TM = 4: 256 x 128 tile; TM = 2: 256 x 64 tile (twice the tiles for small outputs, twice the weight
 // loads per MFMA).
+// PIPE: the first operands of a stage are read during the MFMAs of the stage before, so its copies must have landed a stage
+// earlier.  For int8 weights in tiles of 64 tokens, which run where a compute unit has one of them: nothing else fills the time between the barrier
+// and the first MFMA.  With 4-bit weights the wait, which then covers more, costs more than it saves (540 x 9984 1434 rows 50.0 / 51.5 us, 4096 x
+// 4096 700 rows 25.5 / 26.1).
 //
-// What bounds it: power on real data (see the MFMA rates above), then the operand paths.  us with quantization, 32 x 32 MFMAs (int8 weights: stages of
-// 64 k) / this, both in one session: 28672 x 4096 int8, 1024 rows 116.3 / 105.0, 4096 rows 461 / 445; int4 gated, 1024 rows 110.5 / 98.1,
-// 300 rows 49.8 / 46.9; 6144 x 4096 int8, 1024 rows 35.8 / 32.9; 64-token tiles, 1024 rows: 4096 x 4096 int8 27.8 / 26.9, 4096 x 14336 int8
-// 68.8 / 66.5, int4 67.6 / 66.2.
+// What bounds it: power on real data (see the MFMA rates above), then the operand paths; where the tiles leave most of the chip idle, the latency of a
+// stage.  us with the quantization kernel, 32 x 32 MFMAs (int8 weights: stages of
+// 64 k) / this, both in one session: 28672 x 4096 int8, 1024 rows 119.6 / 107.6, 4096 rows 461 / 442; int4 gated, 1024 rows 109.0 / 97.0,
+// 300 rows 50.2 / 47.0; 6144 x 4096 int8, 1024 rows 35.0 / 32.1; 64-token tiles, 1024 rows: 4096 x 4096 int8 26.7 / 25.6, 4096 x 14336 int8
+// 67.9 / 64.8, int4 66.0 / 60.5; 457 x 8960 int8, 1714 rows 49.1 / 49.7, 540 x 9984 int4, 1434 rows 48.2 / 48.2.  (240 shapes of 200 to 32768 channels and
+// 300 to 4096 rows: 0.958 of the time, the worst narrow ones 767 x 4096 int8 1568 rows 33.4 / 34.2 and 1055 x 6144 1049 rows 39.8 / 40.6.  Without reading and
+// expanding ahead, and with four stages of weights only where those divide K: 0.964, 457 x 8960 51.8, 540 x 9984 50.9.)
 //
 // The weight loads carry no streaming hint: the workgroups of the same weight tile (one per token tile)
 // run side by side on one XCD, and with the lines marked evict-first the later ones miss in L2
@@ -502,6 +510,7 @@ __global__ __launch_bounds__(256, 2) void gemm_i8_dw_kernel(GemmI8Args a) {
     constexpr int XT = BM / 16 * 2;  // activation tiles (KiB) per stage
     constexpr int CP = XT / 4;       // copies per wavefront and stage
     constexpr int XJ = 2 * TM;   // blocks of 16 token rows
+    constexpr bool PIPE = !W4 && TM == 2;
     static_assert(NS >= 3 && (TM == 2 || TM == 4), "tile shapes");
     extern __shared__ uint4 lds[];  // NS stages of XT tiles x 64 vectors
     const int lane = threadIdx.x & 63;
@@ -556,50 +565,69 @@ __global__ __launch_bounds__(256, 2) void gemm_i8_dw_kernel(GemmI8Args a) {
     // a wavefront has issued, after the copies of stage kt, the copies of NS - 2 later stages (CP each),
     // and after the loads of stage kt the loads of PW - 1 later stages - from iteration 0 on,
     // thanks to the prologue.  If at most kAllowed operations are outstanding, neither stage kt's copies nor its loads can be
-    // among them: an unfinished copy would have all later copies behind it, an unfinished load all later loads.
-    constexpr int kAfterCopies = CP * (NS - 2), kAfterLoads = 4 * WV * (PW - 1);
+    // among them: an unfinished copy would have all later copies behind it, an unfinished load all later loads.  With PIPE it is stage kt + 1
+    // whose copies must have landed, which has one stage fewer behind it.
+    constexpr int kAfterCopies = CP * (NS - (PIPE ? 3 : 2)), kAfterLoads = 4 * WV * (PW - 1);
     constexpr int kAllowed = kAfterCopies < kAfterLoads ? kAfterCopies : kAfterLoads;
     // (the most operations a wavefront ever has outstanding: right after the refills of an iteration)
     static_assert(CP * (NS - 1) + 4 * WV * PW <= 63, "wait counts must fit the 6-bit counter");
 
-    auto stages_pw = [&](int kt0, const bool bulk) __attribute__((always_inline)) {
+    v4i fb[XJ];  // (token rows of a k step of 64: a block is replaced by the next step's once it has been multiplied)
+    auto read_x = [&](int kt, int ks, int j) __attribute__((always_inline)) {
+        fb[j] = __builtin_bit_cast(v4i, lds[(kt % NS) * (XT * 64) + (2 * j + ks) * 64 + lane]);
+    };
+    if (PIPE) {
+        wait_vmcnt<CP * (NS - 2)>();
+        asm volatile("s_barrier" ::: "memory");
 #pragma unroll
-        for (int u = 0; u < PW; ++u) {
+        for (int j = 0; j < XJ; ++j) read_x(0, 0, j);
+    }
+    auto stages_pw = [&](int kt0, const int count, const bool bulk) __attribute__((always_inline)) {  // count: PW, or 2
+#pragma unroll
+        for (int u = 0; u < count; ++u) {
             const int kt = kt0 + u;
-            wait_vmcnt<kAllowed>();
+            if (PIPE)
+                asm volatile("s_waitcnt vmcnt(%0)" ::"n"(kAllowed) : "memory");  // (not the LDS counter: operand reads stay in flight)
+            else
+                wait_vmcnt<kAllowed>();
             asm volatile("s_barrier" ::: "memory");
 #pragma unroll
             for (int i = 0; i < TN; ++i)
 #pragma unroll
                 for (int v = 0; v < WV; ++v) asm volatile("" : "+v"(wreg[u][i][v]));
             issue_x(kt + NS - 1, bulk);
-            const uint4 *lx = lds + (kt % NS) * (XT * 64);
-            v4i fb[XJ];  // (token rows of a k step of 64: a block is replaced by the next step's once it has been multiplied)
+            if (!PIPE) {
 #pragma unroll
-            for (int j = 0; j < XJ; ++j) fb[j] = __builtin_bit_cast(v4i, lx[2 * j * 64 + lane]);
+                for (int j = 0; j < XJ; ++j) read_x(kt, 0, j);
+            }
+            v4i fa[2][TN];
+            auto operand = [&](int ks, int i) __attribute__((always_inline)) {
+                if (!W4) {
+                    fa[ks][i] = wreg[u][i][W4 ? 0 : ks];
+                    return;
+                }
+                const uint32_t px = (uint32_t)wreg[u][i][0][2 * ks], py = (uint32_t)wreg[u][i][0][2 * ks + 1];
+                fa[ks][i][0] = (int)(((px << 4) & 0xF0F0F0F0u) ^ 0x80808080u);
+                fa[ks][i][1] = (int)((px & 0xF0F0F0F0u) ^ 0x80808080u);
+                fa[ks][i][2] = (int)(((py << 4) & 0xF0F0F0F0u) ^ 0x80808080u);
+                fa[ks][i][3] = (int)((py & 0xF0F0F0F0u) ^ 0x80808080u);
+            };
+#pragma unroll
+            for (int i = 0; i < TN; ++i) operand(0, i);
 #pragma unroll
             for (int ks = 0; ks < 2; ++ks) {
-                v4i fa[TN];
-#pragma unroll
-                for (int i = 0; i < TN; ++i) {
-                    if (!W4) {
-                        fa[i] = wreg[u][i][W4 ? 0 : ks];
-                        continue;
-                    }
-                    const uint32_t px = (uint32_t)wreg[u][i][0][2 * ks], py = (uint32_t)wreg[u][i][0][2 * ks + 1];
-                    fa[i][0] = (int)(((px << 4) & 0xF0F0F0F0u) ^ 0x80808080u);
-                    fa[i][1] = (int)((px & 0xF0F0F0F0u) ^ 0x80808080u);
-                    fa[i][2] = (int)(((py << 4) & 0xF0F0F0F0u) ^ 0x80808080u);
-                    fa[i][3] = (int)((py & 0xF0F0F0F0u) ^ 0x80808080u);
-                }
 #pragma unroll
                 for (int j = 0; j < XJ; ++j) {
 #pragma unroll
                     for (int i = 0; i < TN; ++i)
-                        acc[i][j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(fa[i], fb[j], acc[i][j], 0, 0, 0);
-                    if (ks == 0) {
+                        acc[i][j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(fa[ks][i], fb[j], acc[i][j], 0, 0, 0);
+                    if (ks == 0 && j < TN) operand(1, j);
+                    if (ks == 0 || PIPE) {
                         __builtin_amdgcn_sched_barrier(0);
-                        fb[j] = __builtin_bit_cast(v4i, lx[(2 * j + 1) * 64 + lane]);
+                        if (ks == 0)
+                            read_x(kt, 1, j);
+                        else
+                            read_x(kt + 1, 0, j);
                     }
                 }
                 if (!W4 || ks == 1) load_w(u, kt + PW, W4 ? 0 : ks, bulk);  // (the vectors that this step was the last to use)
@@ -608,19 +636,28 @@ __global__ __launch_bounds__(256, 2) void gemm_i8_dw_kernel(GemmI8Args a) {
     };
     constexpr int kAhead = NS - 1 > PW ? NS - 1 : PW;  // how far past kt a pass issues
     int kt0 = 0;
-    for (; kt0 + PW - 1 + kAhead < KT; kt0 += PW) stages_pw(kt0, kBulk);
-    for (; kt0 < KT; kt0 += PW) stages_pw(kt0, kEdge);
-    wait_vmcnt<0>();
-    // The loads issued past the end of K are still writing their destination registers until this
+    for (; kt0 + PW - 1 + kAhead < KT; kt0 += PW) stages_pw(kt0, PW, kBulk);
+    for (; kt0 + PW <= KT; kt0 += PW) stages_pw(kt0, PW, kEdge);
+    // The loads issued past the end of K are still writing their destination registers until the
     // wait returns, and the compiler does not know (it sees registers that nobody reads any more).
-    // Naming them as inputs here keeps them allocated until after the wait, and the memory clobber
-    // keeps the store phase's own loads from being moved above it.
+    // Naming them as inputs behind it keeps them allocated until after the wait, and the memory clobber
+    // keeps the store phase's own loads from being moved above it.  (On either way to the end, so that none of them is
+    // the same value on both, which the compiler might move to another register while its load is in flight.)
+    auto drain = [&]() __attribute__((always_inline)) {
+        wait_vmcnt<0>();
 #pragma unroll
-    for (int p = 0; p < PW; ++p)
+        for (int p = 0; p < PW; ++p)
 #pragma unroll
-        for (int i = 0; i < TN; ++i)
+            for (int i = 0; i < TN; ++i)
 #pragma unroll
-            for (int v = 0; v < WV; ++v) asm volatile("" ::"v"(wreg[p][i][v]) : "memory");
+                for (int v = 0; v < WV; ++v) asm volatile("" ::"v"(wreg[p][i][v]) : "memory");
+    };
+    if (PW > 2 && kt0 < KT) {
+        stages_pw(kt0, 2, kEdge);
+        drain();
+    } else {
+        drain();
+    }
     epilogue<OUT_MODE, TN, XJ>(a, acc, lds, nt * BN + wave * 64, mt * BM, wave, lane);
 }
 
@@ -630,7 +667,8 @@ hipError_t launch_dw(GemmI8Args a, hipStream_t st) {
     constexpr size_t lds_bytes = ring_bytes + 1024;
     static_assert(ring_bytes >= 4 * 32 * (64 + 8) * 2, "the store phase stages its blocks inside the ring, below the spare KiB");
     static_assert(lds_bytes <= 80 * 1024, "two workgroups per compute unit");
-    if ((a.Kp / 128) % PW != 0) return hipErrorInvalidValue;
+    static_assert(PW == 2 || PW == 4, "an even number of stages is passes of PW and two more");
+    if ((a.Kp / 128) % 2 != 0) return hipErrorInvalidValue;
     if (const hipError_t e = allow_dynamic_lds<gemm_i8_dw_kernel<W4, NS, PW, TM, OUT_MODE>>(lds_bytes); e != hipSuccess) return e;
     a.n_tiles = (a.N + 255) / 256;
     a.m_tiles = (a.M + 32 * TM - 1) / (32 * TM);
@@ -665,13 +703,13 @@ hipError_t launch_w4(GemmI8Args a, hipStream_t st) {
 }
 
 // Tiles of 256 channels: 128 tokens each where those tiles are for three quarters of the compute units and more, or where tiles of
-// 64 would start a second round that costs more than the larger tiles' idle compute units.  With int8 weights it does at once (us, 64 /
-// 128 tokens: 18432 x 2304 240 rows, 288 tiles of 64, 24.9 / 21.1; 2304 x 9216 1826 rows, 261 tiles, 81 / 60, 2274 rows 93 / 65;
-// 11000 x 3008 500 rows 30.5 / 25.9), with int4 weights from a quarter of a round on (5120 x 9216 802 rows, 260 tiles, 62.1 / 62.4, 1152
-// rows, 360 tiles, 66 / 64; 1536 x 14336 2722 rows, 258 tiles, 97 / 99).  Outputs that are stored as they lie in the registers
+// 64 would start a second round that costs more than the larger tiles' idle compute units.  With int8 weights it does at once (us with the
+// quantization kernel, 64 / 128 tokens: 18432 x 2304 240 rows, 288 tiles of 64, 25.0 / 21.9; 2304 x 9216 1826 rows, 261 tiles, 80 / 61, 2274 rows 93 / 64;
+// 11000 x 3008 500 rows 30.5 / 26.0), with int4 weights from a quarter of a round on (5120 x 9216 802 rows, 260 tiles, 61.4 / 61.2, 1152
+// rows, 360 tiles, 63.7 / 62.5; 1536 x 14336 2722 rows, 258 tiles, 95 / 97).  Outputs that are stored as they lie in the registers
 // (accumulators; rows that are no multiple of 16 bytes) take longer than the round from 128-token tiles: with int4 weights
-// always (4100 x 4096 1211 rows 39.2 / 43.7, 9001 x 1024 600 rows 25.2 / 31.5), with int8 weights below K of 4096 (4100 x 1024 1211 rows
-// 21.7 / 24.9, 9001 x 2304 600 rows 36.4 / 38.5, x 4096 48.4 / 46.1).
+// always (4100 x 4096 1211 rows 38.4 / 43.2, 9001 x 1024 600 rows 24.8 / 31.3), with int8 weights below K of 4096 (4100 x 1024 1211 rows
+// 21.0 / 24.7, 9001 x 2304 600 rows 34.8 / 38.5, x 4096 47.6 / 46.5).
 bool tiles_of_128_tokens(const GemmI8Args &a, bool w4, bool staged_store, int num_cus) {
     const long n256 = (a.N + 255) / 256, m128 = (a.M + 127) / 128, m64 = (a.M + 63) / 64;
     if (4 * n256 * m128 >= 3L * num_cus) return true;
@@ -679,11 +717,12 @@ bool tiles_of_128_tokens(const GemmI8Args &a, bool w4, bool staged_store, int nu
     return n256 * m64 > num_cus && (staged_store || a.Kp >= 4096);
 }
 
-// Tiles of 64 tokens hold the weights of four stages instead of two where K allows it: an operation more in flight is an
-// operation that the wait of a stage need not see done.  us, two / four: int4 1536 x 6144 1024 rows 32.5 / 31.7, 4096 x 4096 700
-// rows 25.3 / 24.9; int8 375 x 12288 2136 rows 67.7 / 65.4, 4096 x 14336 1024 rows 69.3 / 68.3.  With int8 weights the longer start
-// shows at small K: 1344 x 1024 1503 rows 13.3 / 13.5, 4096 x 4096 1024 rows 26.6 / 26.8.
-bool weights_four_stages_ahead(const GemmI8Args &a, bool w4) { return a.Kp % 512 == 0 && (w4 || a.Kp >= 6144); }
+// Tiles of 64 tokens hold the weights of four stages instead of two: an operation more in flight is an
+// operation that the wait of a stage need not see done.  us with the quantization kernel, two / four: int4 4096 x 4096 700 rows 25.3 / 24.4, 3101 x 8192
+// 840 rows 48.9 / 46.6 (the worst 2210 x 512 2197 rows 21.6 / 22.0); int8 375 x 12288 2136 rows 66.1 / 65.4, 1966 x 7680 1399 rows 50.5 / 49.3.  With int8
+// weights the longer start shows at small K: 699 x 768 2364 rows 18.3 / 19.4, 2233 x 1152 2642 rows 28.1 / 29.4, 1344 x 1024 1503 rows 12.8 / 13.1,
+// 4096 x 4096 1024 rows 26.0 / 26.0.
+bool weights_four_stages_ahead(const GemmI8Args &a, bool w4) { return w4 || a.Kp >= 6144; }
 
 template <int OUT_MODE>
 hipError_t launch_mode(const GemmI8Args &a, int num_cus, hipStream_t st) {

@@ -403,6 +403,31 @@ def test_int8_prefill_int4_weights_tile_shapes_bit_exact(variant):
     layer.close()
 
 
+@pytest.mark.parametrize("fmt,K", [("w4c", 256), ("w4c", 512), ("w4c", 768), ("w4c", 2304), ("w4c", 2560), ("w8c", 256), ("w8c", 512), ("w8c", 2400), ("w8c", 6144), ("w8c", 6400), ("w8c", 7168), ("w8c", 7392)])
+def test_int8_tiles_of_64_tokens_any_even_number_of_stages(fmt, K):
+    """The 64-token tiles, which hold the weights of four stages of 128 k (int8 codes with K of less than 6144: of two): whole passes of four, two
+    stages more, only two, and K that ends inside a stage; three channel tiles and three token tiles, the last ones ragged; bit for bit,
+    and the same again with warm caches."""
+    M, N = 131, 600
+    print(f"int8 tiles of 64 tokens {fmt} K={K}", flush=True)
+    wq, sw = synth.weights(4650, M, K, synth.FC("t", K, N, fmt))
+    x = synth.activations(4650, M, K, M, K)
+    xq_ref, sx_ref, acc_ref, y_ref = oracle.fc_int8_act(x, wq, sw)
+    layer = _layer(wq, sw, fmt, max_m=M, mode=binding.QFC_COMPUTE_INT8_ACT)
+    xq_d = torch.from_numpy(xq_ref).to(DEV)
+    binding.qfc_tune(2, 12 if fmt == "w8c" else 23)
+    try:
+        for rep in range(3):
+            acc = torch.full((M, N), -1, dtype=torch.int32, device=DEV)
+            binding.qfc_forward_acc_i32(layer.handle, xq_d, acc)
+            y = _forward(layer, x)
+            assert np.array_equal(acc.cpu().numpy().astype(np.int64), acc_ref), rep
+            assert _E(y, y_ref) <= TOL, rep
+    finally:
+        binding.qfc_tune(2, 0)
+    layer.close()
+
+
 def test_int8_prefill_config4_shapes_sampled():
     """Llama layer at M = 1024, int8 per-channel weights: accumulators of a
     sample of (token, channel) pairs against the exact integer contraction."""
