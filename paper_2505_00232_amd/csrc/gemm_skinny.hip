@@ -488,15 +488,24 @@ unsigned stream_grid(const SkinnyArgs &a, int waves, int num_cus) {  // (16 wave
 // and meet in few memory channels, while here those of a compute unit spread over K.  us, that one / this, 24 rows: 32768 x 4096 26.9 / 25.3,
 // 100000 x 4096 84.8 / 72.5, x 8192 161 / 136.  At other K both are level (65536 x 3072 36.6 / 36.1, x 5120 57.8 / 56.6, x 6144 66.2 / 67.5) or
 // this loses (202048 x 2048 72 / 78; x 2560, five wavefronts on four SIMDs, 89 / 104).  From two rounds of the grid on, the last
-// at least partly full: 28672 x 4096 20 rows 23.6 / 23.9, 50304 x 8192, 3.07 rounds, 68.7 / 72.6.  K of 512 and 1024: the other kernel's wavefronts have one or
-// two steps (152064 x 512 20.9 / 18.4; 65536 x 1024 19.8 / 15.1, 256000 x 1024 59.1 / 53.6).
+// at least four fifths full: 28672 x 4096 20 rows 23.6 / 23.9; with K of 8192, where one workgroup fills a compute unit and nothing runs beside
+// its last round, nine tenths from the fourth round on: 33000, 4.03 rounds, 16 rows 46.6 / 49.4, 26624, 3.25 rounds, 24 rows 40.4 / 41.7, 50304, 6.14
+// rounds, 69.5 / 72.3, but 31104, 3.8 rounds, 51.4 / 47.8; up to 16 rows with K of 4096, whose stream leaves less to hide it in, from the fifth
+// (99936, 6.1 rounds, 9 rows 66.8 / 69.4, 131758, 8.04 rounds, 10 rows 86.6 / 89.2; 57344, 3.5 rounds, 41.5 / 38.9).  K of 512 and 1024: the other kernel's
+// wavefronts have one or
+// two steps (152064 x 512 20.9 / 18.4; 65536 x 1024 19.8 / 15.1, 256000 x 1024 59.1 / 53.6).  There one or two wavefronts store a row tile, and that shows
+// with many channels: up to 16 rows from about 160000 on (250000 x 512 9 rows 25.3 / 26.3, 164748 x 992 10 rows 31.5 / 32.5, 200000 x 1024 36.6 / 37.9;
+// 140000 x 512 17.0 / 15.7), rows of single values earlier (131070 x 512 16 rows 16.6 / 18.0, 200001 x 1024 32 rows 50.4 / 55.4; 100002 24 rows 26.6 /
+// 25.5).  Weights in HBM; both move by up to 10 % with where the weights lie, 152064 x 4096 12 rows 99.4 / 103.4 and 113 / 99 in two processes.
 bool stream_takes(const SkinnyArgs &a, int num_cus) {
     if (a.M > 32 || tuning().skinny_waves > 0 || tuning().skinny_row_tiles > 0 || tuning().skinny_blocks > 0) return false;
     const int steps = a.Kp / 128, waves = steps / kStreamSteps;
     if (steps % kStreamSteps != 0 || waves > 16) return false;
     const int groups = (a.RT + kStreamTiles - 1) / kStreamTiles, grid = 16 / waves * num_cus;
-    if (a.Kp <= 1024) return groups >= grid;
-    return a.Kp % 4096 == 0 && groups >= 2 * grid && 5 * groups >= 4 * ((groups + grid - 1) / grid * grid);
+    if (a.Kp <= 1024) return groups >= grid && (a.N % 4 != 0 ? a.N < 110000 : a.M > 16 || a.N < 155000);
+    const int rounded = (groups + grid - 1) / grid * grid;
+    const bool four_fifths = a.Kp == 4096 ? a.M > 16 || groups <= 4 * grid : groups <= 3 * grid;
+    return a.Kp % 4096 == 0 && groups >= 2 * grid && (four_fifths ? 5 * groups >= 4 * rounded : 10 * groups >= 9 * rounded);
 }
 
 void split_steps(SkinnyArgs &a, int steps, int waves) {

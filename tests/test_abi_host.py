@@ -224,7 +224,7 @@ int main() {
     assert r.returncode == 0, r.stdout[-2000:]
 
 
-# What the dispatch chooses for layers with binary16 activations on 256 compute units: format (0 int8, 1 int4 in groups, 2 int4), channels, K, token rows,
+# What the dispatch chooses on 256 compute units.  Binary16 activations: format (0 int8, 1 int4 in groups, 2 int4), channels, K, token rows,
 # rows left to the token-row kernels in a second launch (-1: they take them all)
 CHOICES = [
     # K of less than 256: one launch (us, two / one: 8192 x 128 1030 rows 10.9 / 8.5, 10807 x 128 706 rows 20.0 / 7.8, int8 10501 x 64 1001 rows 19.4 / 9.4)
@@ -234,21 +234,35 @@ CHOICES = [
     # two launches where those are the faster ones
     (2, 4096, 4096, 2060, 12), (1, 2304, 9216, 3700, 116), (1, 3072, 1536, 2698, 10), (0, 2048, 1536, 4100, 4),
 ]
+# int8 activations and weights: channels, K, token rows, whether the workgroups stay and walk over row tiles
+STREAMS = [(128256, 4096, 24, 1), (65536, 8192, 9, 1), (31104, 8192, 24, 1), (152064, 512, 24, 1), (140000, 512, 9, 1), (250000, 512, 24, 1), (65535, 992, 17, 1), (57344, 4096, 9, 1), (99936, 4096, 24, 1), (128256, 4096, 9, 1),
+           # not: a last round of few workgroups with K of 8192; K of 512 and 1024, many channels and up to 16 rows, or rows of single values
+           (33000, 8192, 16, 0), (50304, 8192, 24, 0), (28672, 4096, 20, 0), (250000, 512, 9, 0), (200000, 1024, 16, 0), (131070, 512, 32, 0), (200001, 1024, 32, 0),
+           (164748, 992, 10, 0), (99936, 4096, 9, 0), (131758, 4096, 10, 0), (202048, 2048, 24, 0), (128256, 4096, 33, 0)]
 
 
-def test_choice_of_kernels_for_binary16_activations(tmp_path):
-    src, exe = tmp_path / "choice.hip", str(tmp_path / "choice")
-    src.write_text("""#include "qfc_internal.h"
+def test_choice_of_kernels(tmp_path):
+    """The dispatch's own functions, compiled for the host, on both sides of its lines (times of both beside the rules)."""
+    src, obj, exe = tmp_path / "choice.hip", str(tmp_path / "choice.o"), str(tmp_path / "choice")
+    src.write_text("""#include "gemm_skinny.hip"
 #include <cstdio>
 int main() {
-    for (int fmt, N, K, M; scanf("%d %d %d %d", &fmt, &N, &K, &M) == 4;) {
+    for (int kind, fmt, N, K, M; scanf("%d %d %d %d %d", &kind, &fmt, &N, &K, &M) == 5;) {
         const qfc::Geometry g = qfc::make_geometry(N, K, fmt);
-        printf("%d\\n", qfc::skinny_product(g, M, false, false, 256) ? -1 : qfc::skinny_tail_rows(g, M, false, 256));
+        if (kind == 0)
+            printf("%d\\n", qfc::skinny_product(g, M, false, false, 256) ? -1 : qfc::skinny_tail_rows(g, M, false, 256));
+        else
+            printf("%d\\n", (int)qfc::stream_takes(qfc::make_args(g, nullptr, nullptr, nullptr, M, nullptr, nullptr, -1), 256));
     }
 }
 """)
     binding.lib()
     where = os.path.dirname(build.LIB)
-    subprocess.run([build._hipcc(), "-std=c++17", "-w", "--offload-arch=gfx950", "-I", build.CSRC, str(src), "-o", exe, "-L", where, "-lqfc", "-Wl,-rpath," + where], check=True)
-    r = subprocess.run([exe], input="\n".join(" ".join(map(str, c[:4])) for c in CHOICES), capture_output=True, text=True, check=True)
-    assert [int(v) for v in r.stdout.split()] == [c[4] for c in CHOICES]
+    subprocess.run([build._hipcc(), "-std=c++17", "-w", "-O1", "-fPIC", "--offload-arch=gfx950", "--cuda-host-only", "-I", build.CSRC, "-c", str(src), "-o", obj], check=True)
+    # (no device code: the kernels' images are never looked up)
+    subprocess.run([build._hipcc(), obj, "-o", exe, "-Wl,--unresolved-symbols=ignore-all", "-L", where, "-lqfc", "-Wl,-rpath," + where], check=True)
+    asked = [(0, *c[:4]) for c in CHOICES] + [(1, 0, *s[:3]) for s in STREAMS]
+    r = subprocess.run([exe], input="\n".join(" ".join(map(str, c)) for c in asked), capture_output=True, text=True, check=True)
+    got = [int(v) for v in r.stdout.split()]
+    assert got[:len(CHOICES)] == [c[4] for c in CHOICES]
+    assert got[len(CHOICES):] == [s[3] for s in STREAMS]
