@@ -249,10 +249,12 @@ __device__ __forceinline__ void epilogue(const GemmI8Args &a, v4i (&acc)[TN][TM]
     }
 }
 
-// KTS = KiB k tiles (64 k each) per stage, NS = LDS stages (prefetch distance NS - 1)
-template <int BN, int BM, int KTS, int NS, int OUT_MODE>
-__global__ __launch_bounds__(256, (BN * BM > 128 * 256) ? 1 : 2) void gemm_i8_kernel(GemmI8Args a) {
-    constexpr int BK = KTS * 64;
+// Both operands staged.  No layer's automatic choice: 128 x 128 tiles are level with the direct-weights kernel below at best (us, this / that:
+// 475 x 2112 2243 rows 28.7 / 28.7, 457 x 8960 1714 rows 65 / 50).  Kept, at one shape, as the second opinion that tests compare that
+// kernel's large launches with.  Stages of two KiB k tiles (64 k each); NS = LDS stages (prefetch distance NS - 1)
+template <int BN, int BM, int NS, int OUT_MODE>
+__global__ __launch_bounds__(256, 2) void gemm_i8_kernel(GemmI8Args a) {
+    constexpr int KTS = 2, BK = KTS * 64;
     constexpr int WN = BN / 2, WM = BM / 2;    // per-wavefront tile
     constexpr int TN = WN / 16, TM = WM / 16;  // 16x16 MFMA tiles per wavefront
     constexpr int W_TILES = BN / 16 * KTS, X_TILES = BM / 16 * KTS;  // KiB tiles per stage
@@ -345,17 +347,9 @@ __global__ __launch_bounds__(256, (BN * BM > 128 * 256) ? 1 : 2) void gemm_i8_ke
                 acc[i][j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(fa[set][i], fb[set][j], acc[i][j], 0, 0, 0);
         __builtin_amdgcn_sched_barrier(0);
     };
-    if constexpr (KS == 2) {
-        for (int kt = 0; kt < stages; ++kt) {
-            step(kt, 0, 0);
-            step(kt, 1, 1);
-        }
-    } else {
-        static_assert(KS == 1 || KS == 2, "one or two k steps per stage");
-        for (int kt = 0; kt < stages; kt += 2) {
-            step(kt, 0, 0);
-            if (kt + 1 < stages) step(kt + 1, 0, 1);
-        }
+    for (int kt = 0; kt < stages; ++kt) {
+        step(kt, 0, 0);
+        step(kt, 1, 1);
     }
 
     epilogue<OUT_MODE, TN, TM>(a, acc, lds, nt * BN + wn * WN, mt * BM + wm * WM, wave, lane);
@@ -677,15 +671,15 @@ hipError_t launch_dw(GemmI8Args a, hipStream_t st) {
     return hipGetLastError();
 }
 
-template <int BN, int BM, int KTS, int NS, int OUT_MODE>
-hipError_t launch_variant(GemmI8Args a, hipStream_t st) {
-    constexpr size_t lds_bytes = (size_t)NS * ((BN + BM) / 16 * KTS) * 1024;
+template <int BN, int BM, int NS, int OUT_MODE>
+hipError_t launch_staged(GemmI8Args a, hipStream_t st) {
+    constexpr size_t lds_bytes = (size_t)NS * ((BN + BM) / 16 * 2) * 1024;
     static_assert(lds_bytes <= 160 * 1024, "LDS budget");
-    if (const hipError_t e = allow_dynamic_lds<gemm_i8_kernel<BN, BM, KTS, NS, OUT_MODE>>(lds_bytes); e != hipSuccess) return e;
+    if (const hipError_t e = allow_dynamic_lds<gemm_i8_kernel<BN, BM, NS, OUT_MODE>>(lds_bytes); e != hipSuccess) return e;
     a.n_tiles = (a.N + BN - 1) / BN;
     a.m_tiles = (a.M + BM - 1) / BM;
     a.by_tokens = walk_by_tokens(a.n_tiles, a.m_tiles, (float)BN, (float)BM);
-    gemm_i8_kernel<BN, BM, KTS, NS, OUT_MODE><<<dim3((unsigned)(a.n_tiles * a.m_tiles)), 256, lds_bytes, st>>>(a);
+    gemm_i8_kernel<BN, BM, NS, OUT_MODE><<<dim3((unsigned)(a.n_tiles * a.m_tiles)), 256, lds_bytes, st>>>(a);
     return hipGetLastError();
 }
 
@@ -722,38 +716,27 @@ bool tiles_of_128_tokens(const GemmI8Args &a, bool w4, bool staged_store, int nu
 // 840 rows 48.9 / 46.6 (the worst 2210 x 512 2197 rows 21.6 / 22.0); int8 375 x 12288 2136 rows 66.1 / 65.4, 1966 x 7680 1399 rows 50.5 / 49.3.  With int8
 // weights the longer start shows at small K: 699 x 768 2364 rows 18.3 / 19.4, 2233 x 1152 2642 rows 28.1 / 29.4, 1344 x 1024 1503 rows 12.8 / 13.1,
 // 4096 x 4096 1024 rows 26.0 / 26.0.
-bool weights_four_stages_ahead(const GemmI8Args &a, bool w4) { return w4 || a.Kp >= 6144; }
+bool weights_four_stages_ahead(const GemmI8Args &a) { return a.Kp >= 6144; }
 
+// The kernel is chosen by size, or by number for tests: 4, 10, 12 (int8 weights), 20, 21, 23 (int4).  A number that names none of the call's
+// kernels leaves the choice.
 template <int OUT_MODE>
 hipError_t launch_mode(const GemmI8Args &a, int num_cus, hipStream_t st) {
-    // The direct-weights kernel; the ones that stage both operands stay selectable for experiments.
     int variant = tuning().gemm_variant;
-    if (variant == 0) {
-        variant = tiles_of_128_tokens(a, false, OUT_MODE == 0 && a.N % 8 == 0, num_cus) ? 10 : 12;
-    }
-    switch (variant) {
-        case 2: return launch_variant<256, 128, 1, 4, OUT_MODE>(a, st);
-        case 4: return launch_variant<128, 128, 2, 3, OUT_MODE>(a, st);
-        case 5: return launch_variant<128, 256, 1, 3, OUT_MODE>(a, st);
-        case 6: return launch_variant<256, 128, 1, 3, OUT_MODE>(a, st);
-        case 10: return launch_dw<false, 4, 2, 4, OUT_MODE>(a, st);
-        case 12: return weights_four_stages_ahead(a, false) ? launch_dw<false, 8, 4, 2, OUT_MODE>(a, st) : launch_dw<false, 8, 2, 2, OUT_MODE>(a, st);
-        default: return launch_variant<128, 128, 1, 4, OUT_MODE>(a, st);
-    }
+    if (variant != 4 && variant != 10 && variant != 12) variant = tiles_of_128_tokens(a, false, OUT_MODE == 0 && a.N % 8 == 0, num_cus) ? 10 : 12;
+    if (variant == 4) return launch_staged<128, 128, 3, OUT_MODE>(a, st);
+    if (variant == 10) return launch_dw<false, 4, 2, 4, OUT_MODE>(a, st);
+    return weights_four_stages_ahead(a) ? launch_dw<false, 8, 4, 2, OUT_MODE>(a, st) : launch_dw<false, 8, 2, 2, OUT_MODE>(a, st);
 }
 
 template <int OUT_MODE>
 hipError_t launch_mode_w4(const GemmI8Args &a, int num_cus, hipStream_t st) {
     int variant = tuning().gemm_variant;
-    const int stages = a.Kp / 128;
-    if (variant == 0) {
-        variant = stages % 2 != 0 ? 20 : tiles_of_128_tokens(a, true, OUT_MODE == 0 && a.N % 8 == 0, num_cus) ? 21 : 23;
+    if (variant != 20 && variant != 21 && variant != 23) {
+        variant = (a.Kp / 128) % 2 != 0 ? 20 : tiles_of_128_tokens(a, true, OUT_MODE == 0 && a.N % 8 == 0, num_cus) ? 21 : 23;
     }
-    switch (variant) {
-        case 21: return launch_dw<true, 4, 2, 4, OUT_MODE>(a, st);
-        case 23: return weights_four_stages_ahead(a, true) ? launch_dw<true, 8, 4, 2, OUT_MODE>(a, st) : launch_dw<true, 8, 2, 2, OUT_MODE>(a, st);
-        default: return launch_w4<128, 128, 3, OUT_MODE>(a, st);
-    }
+    if (variant == 20) return launch_w4<128, 128, 3, OUT_MODE>(a, st);
+    return variant == 21 ? launch_dw<true, 4, 2, 4, OUT_MODE>(a, st) : launch_dw<true, 8, 4, 2, OUT_MODE>(a, st);
 }
 
 }  // namespace

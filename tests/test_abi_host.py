@@ -140,12 +140,12 @@ def test_build_refuses_spills_in_kernels_with_hand_placed_loads():
         return [pre + f"Function Name: {name}" + suf, pre + "    VGPRs: 220" + suf,
                 pre + f"    ScratchSize [bytes/lane]: {scratch}" + suf, pre + "    SGPRs Spill: 0" + suf,
                 pre + f"    VGPRs Spill: {vspill}" + suf]
-    clean = remarks("_ZN3qfc18gemm_i8_dw4_kernelILi4ELi2ELi4ELi0EEEv", 0, 0)
+    clean = remarks("_ZN3qfc17gemm_i8_dw_kernelILb1ELi8ELi4ELi2ELi0EEEv", 0, 0)
     other = remarks("_ZN3qfc14gemm_i8_kernelILi128ELi128EEEv", 76, 18)   # not one of the guarded kernels
-    bad = remarks("_ZN3qfc17gemm_i8_dw_kernelILi9ELi4ELi4ELi0ELb1EEEv", 76, 18)
+    bad = remarks("_ZN3qfc17gemm_i8_dw_kernelILb0ELi4ELi2ELi4ELi0EEEv", 76, 18)
     frag = build.NO_SPILL["gemm_i8.hip"]
     assert build._spilling_kernels(clean + other, frag) == []
-    assert build._spilling_kernels(clean + bad + other, frag) == ["_ZN3qfc17gemm_i8_dw_kernelILi9ELi4ELi4ELi0ELb1EEEv"]
+    assert build._spilling_kernels(clean + bad + other, frag) == ["_ZN3qfc17gemm_i8_dw_kernelILb0ELi4ELi2ELi4ELi0EEEv"]
 
 
 def test_build_sees_changes_of_its_flags_and_headers(tmp_path, monkeypatch):

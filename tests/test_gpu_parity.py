@@ -353,10 +353,10 @@ def test_int8_few_rows_of_many_channels(N, K, M, residual):
         assert _E(outs[0].cpu().numpy()[:, cols], y_ref) <= TOL
 
 
-@pytest.mark.parametrize("variant", [1, 4, 5, 6, 10, 11, 12, 13, 14, 15])
+@pytest.mark.parametrize("variant", [4, 10, 12])
 def test_int8_prefill_other_tile_shapes_bit_exact(variant):
-    """The tile shapes the dispatcher picks for larger problems (and the selectable ones),
-    forced on a ragged shape."""
+    """The kernels of the int8 product (both operands staged; weights straight into registers with 128 and 64 token rows per
+    workgroup), forced on a ragged shape."""
     print(f"int8 prefill tile variant {variant}", flush=True)
     M, N, K = 300, 520, 1152
     fc = synth.FC("t", K, N, "w8c")
@@ -379,10 +379,10 @@ def test_int8_prefill_other_tile_shapes_bit_exact(variant):
     layer.close()
 
 
-@pytest.mark.parametrize("variant", [20, 21, 22, 23, 24])
+@pytest.mark.parametrize("variant", [20, 21, 23])
 def test_int8_prefill_int4_weights_tile_shapes_bit_exact(variant):
     """The kernels of the int8 x int4 product (both operands staged; weights straight into registers
-    with two tile widths and two prefetch depths), forced on a ragged shape."""
+    with 128 and 64 token rows per workgroup), forced on a ragged shape."""
     print(f"int8 x int4 prefill tile variant {variant}", flush=True)
     M, N, K = 300, 520, 1024
     fc = synth.FC("t", K, N, "w4c")
@@ -645,10 +645,13 @@ def test_fp16_prefill_whole_output_two_kernels_agree(fmt, M):
 def test_fp16_tiles_of_every_form(form, fmt):
     """The main kernel with binary16 activations in each of its forms (32 to 128 token rows per workgroup, K in one piece or two): one
     step of K, an odd number of steps (uneven halves), more than eight (a second unit of group scales); token rows one past a tile and
-    one short of it; channels whose rows are aligned to 16, 8, 4 and 2 bytes; residual and gated output."""
+    one short of it; channels whose rows are aligned to 16, 8, 4 and 2 bytes; residual; gated output over whole and ragged channel tiles, even and
+    uneven halves of K."""
     step = 64 if fmt == "w8c" else 128
-    for M, N, steps in ((9, 70, 1), (33, 264, 2), (95, 300, 3), (129, 517, 5), (127, 90, 9), (161, 256, 10), (255, 1, 4)):
+    for M, N, steps in ((9, 70, 1), (33, 264, 2), (95, 300, 3), (129, 517, 5), (127, 90, 9), (161, 256, 10), (255, 1, 4), (97, 288, 5), (40, 96, 3), (130, 544, 9)):
         K = step * steps
+        if form >= 35 and K < 256:
+            continue  # (K in two halves is built for 256 and more; the number would leave the choice to the dispatch)
         print(f"fp16 tiles form={form} {fmt} M={M} N={N} K={K}", flush=True)
         wq, s = synth.weights(4500, M, N, synth.FC("t", K, N, fmt))
         x = synth.activations(4500, M, N, M, K)
