@@ -65,27 +65,29 @@ def main():
 
     if args.probe_mfma:
         out = {}
-        for kind, name, ops in ((0, "int8 v_mfma_i32_32x32x32_i8", 65536.0), (1, "fp16 v_mfma_f32_32x32x16_f16", 32768.0)):
-            for random_operands in (False, True):
-                wgs, iters = 512, 20000  # two wavefronts per SIMD; about 10 ms per launch at full rate
-                ticks = torch.zeros((wgs, 2), dtype=torch.int64, device=dev)
-                launch = lambda: binding.qfc_probe_mfma(kind, random_operands, iters, wgs, ticks)
-                for _ in range(15):  # 150 ms and more of the same load first
-                    launch()
-                torch.cuda.synchronize()
-                e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
-                e0.record()
-                for _ in range(5):
-                    launch()
-                e1.record()
-                torch.cuda.synchronize()
-                ms = e0.elapsed_time(e1) / 5
-                t = ticks.cpu().numpy().astype(np.float64)
-                out[f"{name}, {'random' if random_operands else 'constant'} operands"] = {
-                    "Tops": round(ops * 32 * iters * wgs * 4 / (ms * 1e-3) / 1e12, 1),
-                    "shader_clock_MHz": round(float((t[:, 0] / (t[:, 1] / 100.0)).mean()), 1),
-                    "ms_per_launch": round(ms, 3)}
-        print(json.dumps({"probe": "register-only MFMA loop, 512 workgroups x 4 wavefronts, 640000 MFMAs per wavefront", "results": out}))
+        for kind, name, ops in ((0, "int8 v_mfma_i32_32x32x32_i8", 65536.0), (1, "fp16 v_mfma_f32_32x32x16_f16", 32768.0),
+                                (4, "int8 v_mfma_i32_16x16x64_i8", 32768.0), (5, "fp16 v_mfma_f32_16x16x32_f16", 16384.0)):
+            for operands, what in ((0, "constant"), (1, "random"), (2, "normal"), (3, "int4 codes x normal")):
+                for wgs in (256, 512):  # one and two wavefronts per SIMD
+                    iters = 20000 if kind < 4 else 40000  # about 10 ms per launch at full rate
+                    ticks = torch.zeros((wgs, 2), dtype=torch.int64, device=dev)
+                    launch = lambda: binding.qfc_probe_mfma(kind, operands, iters, wgs, ticks)
+                    for _ in range(15):  # 150 ms and more of the same load first
+                        launch()
+                    torch.cuda.synchronize()
+                    e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+                    e0.record()
+                    for _ in range(5):
+                        launch()
+                    e1.record()
+                    torch.cuda.synchronize()
+                    ms = e0.elapsed_time(e1) / 5
+                    t = ticks.cpu().numpy().astype(np.float64)
+                    out[f"{name}, {what} operands, {wgs // 256} wavefront{'s' if wgs > 256 else ''} per SIMD"] = {
+                        "Tops": round(ops * 32 * iters * wgs * 4 / (ms * 1e-3) / 1e12, 1),
+                        "shader_clock_MHz": round(float((t[:, 0] / (t[:, 1] / 100.0)).mean()), 1),
+                        "ms_per_launch": round(ms, 3)}
+        print(json.dumps({"probe": "register-only MFMA loop, 256 and 512 workgroups x 4 wavefronts, 640000 (16 x 16: 1280000) MFMAs per wavefront", "results": out}))
         return
 
     def event_ms(fn, reps):

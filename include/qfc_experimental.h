@@ -46,8 +46,10 @@ void qfc_tune(int32_t key, int32_t value);
 
 /* Measurement probe (bench.py --probe-mfma): `workgroups` workgroups of four wavefronts each issue
  * 32 * iters back-to-back MFMAs from registers, no memory traffic (kind 0: v_mfma_i32_32x32x32_i8,
- * 65536 operations each; kind 1: v_mfma_f32_32x32x16_f16, 32768 each), with constant operands
- * (random_operands = 0) or operands of random bits used in rotation (1).  ticks (device, 8-byte
+ * 65536 operations each; 1: v_mfma_f32_32x32x16_f16, 32768; 4: v_mfma_i32_16x16x64_i8, 32768; 5:
+ * v_mfma_f32_16x16x32_f16, 16384), with constant operands (random_operands = 0), operands of random
+ * bits used in rotation (1), codes of normal values (int8) or normal values (binary16) (2), or the
+ * same with int4 codes as the first operand (3).  ticks (device, 8-byte
  * aligned, 2 * workgroups entries, written by the kernel): per workgroup the shader-clock ticks
  * and the ticks of the constant 100 MHz counter over the loop.  The caller times the launch.
  * Errors: QFC_ERR_INVALID_ARG (kind, iters outside 1 .. 2^22, workgroups outside 1 .. 4096, null),

@@ -417,10 +417,10 @@ def qfc_tune(key: int, value: int):
     lib().qfc_tune(key, value)
 
 
-def qfc_probe_mfma(kind: int, random_operands: bool, iters: int, workgroups: int, ticks):
+def qfc_probe_mfma(kind: int, random_operands: int, iters: int, workgroups: int, ticks):
     """Measurement probe of qfc_experimental.h: ticks = int64 device tensor [workgroups, 2]."""
     _want(ticks, torch.int64, (workgroups, 2), "ticks")
-    _check(lib().qfc_probe_mfma(kind, int(bool(random_operands)), iters, workgroups, _ptr(ticks), _stream()),
+    _check(lib().qfc_probe_mfma(kind, int(random_operands), iters, workgroups, _ptr(ticks), _stream()),
            "qfc_probe_mfma")
 
 

@@ -306,9 +306,9 @@ __device__ __forceinline__ uint2 dequant8_half(uint32_t w) {
 //
 // What bounds it: power on real data, then what a wavefront does before its first and after its last MFMA.  Hence two workgroups of JP
 // = 4 per compute unit, with everything within half its registers and 80 KiB of LDS: one stores or starts while the other
-// multiplies, and a barrier stops one wavefront of a SIMD, not both.  Hence also the 16 x 16 shape: register-only loops over a
-// wavefront's tile (normal data, int4 codes; one / two wavefronts per SIMD) hold 2.19 / 2.18 PFLOP/s with it, 1.82 / 1.30 with
-// v_mfma_f32_32x32x16_f16 (two wavefronts do not even overlap on constant data: 1.63 of 2.46).
+// multiplies, and a barrier stops one wavefront of a SIMD, not both.  Hence also the 16 x 16 shape: register-only loops (probe.hip; int4 codes
+// and normal activations; one / two wavefronts per SIMD) hold 2.07 / 2.11 PFLOP/s with it, 1.67 / 1.68 with
+// v_mfma_f32_32x32x16_f16, whose MFMAs take more power for the same products.
 // us, one workgroup of eight wavefronts and 32 x 32 MFMAs per compute unit / this, in one session: int4 in groups of 32 18432 x 2304 gated
 // 2048 rows 188 / 151, 9216 x 768 1000 rows 29.3 / 20.5; int4 codes 28672 x 4096 gated 6000 rows 1239 / 1011, 6144 x 4096 279 / 221, 4096 x 14336
 // 548 / 467; int8 codes (then dequantized into LDS) 14336 x 4096 1000 rows 147 / 99, 4096 x 4096 2048 rows 80 / 58.

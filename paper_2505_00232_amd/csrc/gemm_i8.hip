@@ -15,8 +15,8 @@
 //
 // Workgroup: 4 wavefronts in a 2 x 2 grid over a BN x BM tile (weight rows x
 // token rows); each wavefront owns (BN/2) x (BM/2) outputs as 16x16 tiles of
-// v_mfma_i32_16x16x64_i8 (register-only loops on normally distributed codes, all compute units: 4.13 POP/s,
-// v_mfma_i32_32x32x32_i8 3.53; one operand 16 x int4 4.65 / 3.73: power).  The weights are the row operand of the MFMA so that
+// v_mfma_i32_16x16x64_i8 (register-only loops of probe.hip on codes of normal values, all compute units: 4.09 POP/s,
+// v_mfma_i32_32x32x32_i8 3.35; one operand 16 x int4 4.54 / 3.54: power).  The weights are the row operand of the MFMA so that
 // a lane ends up with 4 consecutive n of one token row (8-byte fp16 stores
 // along the contiguous axis of y).  Tile ids are dealt so that every XCD works
 // on a contiguous range of (weight tile, token tile) pairs and the token tiles

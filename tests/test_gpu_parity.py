@@ -1915,9 +1915,9 @@ def test_probe_mfma_runs_and_rejects_bad_arguments():
     """The measurement probe of qfc_experimental.h: a short run writes both counters of every
     workgroup; arguments outside its documented ranges are refused before any launch."""
     print("mfma probe", flush=True)
-    for kind in (0, 1):
+    for kind, operands in ((0, True), (1, True), (4, 0), (4, 1), (4, 2), (4, 3), (5, 0), (5, 1), (5, 2), (5, 3)):
         ticks = torch.zeros((8, 2), dtype=torch.int64, device=DEV)
-        binding.qfc_probe_mfma(kind, True, 10, 8, ticks)
+        binding.qfc_probe_mfma(kind, operands, 10, 8, ticks)
         torch.cuda.synchronize()
         t = ticks.cpu().numpy()
         assert (t > 0).all()
