@@ -819,18 +819,17 @@ bool skinny_product(const Geometry &g, int M, bool int8_activations, bool gated,
     if (M <= kSkinnyRows && (int8_activations || !tile_kernel_takes(g))) return g.K > tiles_up_to_k(g, M, int8_activations, num_cus);
     if (M > kSkinnyMaxM) return false;
     if (!int8_activations && tile_kernel_takes(g)) {
-        // (Fewer than 8192 channels: where the tiles win there, K = 256, it is by 0.3 us, and the estimate costs the host that.  Up to 32
-        // rows, K of 512 and more: the tiles are 1 % faster at most and up to 2.3 times slower, int8 9360 x 1024 12 rows 9.2 / 3.9, 29780 x 512 28 rows
-        // 6.6 / 5.5; at K of 256 the other way round, int4 groups 25938 x 256 21 rows 4.6 / 7.1.)
-        if (M <= kSkinnyRows && (g.N < 8192 || (M <= 32 && g.K >= 512))) return true;
+        if (M <= kSkinnyRows && g.N < 8192) return true;  // (where the tiles win there, K = 256, it is by 0.3 us, and the estimate costs the host that)
         int rest;
         const float here = few_rows_us(g, M, gated, num_cus), tiles = tail_rows(g, M, gated, num_cus, &rest);
-        // (1.05: where both estimates are level the kernels here are the faster more often.  Half a microsecond: at K of 512 and less, where
-        // the products are little more than launches, they are by up to 1.1: us, tiles / here: int8 1404 x 192 73 rows 4.5 / 3.7, 9887 x 256 26 rows
-        // 5.3 / 4.8, int4 311 x 256 442 rows 5.2 / 4.1, int4 groups 3527 x 256 69 rows 5.2 / 4.8.  700 shapes with K of 64 to 1536: 0.36 % behind the faster
-        // of both, 0.46 % without.  420 shapes whose estimates are within a fifth of each other, K of 640 to 14336: 0.5 % behind, the
-        // worst int8 19937 x 11520 68 rows, tiles 76, here 90, and the other way round int8 4404 x 2304 394 rows 19.0 / 17.6)
-        return here < fmaxf(1.05f * tiles, tiles + 0.5f);
+        // (1.05: where both estimates are level the kernels here are the faster more often; up to 16 rows, whose blocks are half empty, 1.1.
+        // Half a microsecond: at K of 512 and less, where the products are little more than launches, the estimate here is high by up to 1.1. us, tiles /
+        // here, weights in HBM: int8 1404 x 192 73 rows 4.8 / 3.6, 345 x 256 146 rows 5.2 / 3.0, int4 311 x 256 442 rows 5.5 / 3.9, int4 groups 3527 x 256 69
+        // rows 5.4 / 5.0, 80000 x 1024 9 rows 26 / 22; the other way round int4 4258 x 256 122 rows 5.0 / 7.4, 28000 x 512 20 rows 6.4 / 7.6 (in the
+        // cache 5.7 / 6.0), int4 groups 128256 x 4096 32 rows 68 / 79.  612 shapes whose estimates are near each other, weights in HBM: 0.55 % behind the faster
+        // of both, 0.73 % with 1.05 alone; the worst int8 2338 x 128 81 rows, tiles 4.3, here 6.0, int8 19937 x 11520 68 rows 76 / 90, and the other
+        // way round 221 x 128 95 rows 4.7 / 3.9, 4404 x 2304 394 rows 20.6 / 18.9)
+        return here < fmaxf((M <= 16 ? 1.1f : 1.05f) * tiles, tiles + 0.5f);
     }
     const float here = skinny_us(g, M, int8_activations, gated, num_cus);
     const long n256 = (g.N + 255) / 256, m128 = (M + 127) / 128;

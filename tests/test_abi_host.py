@@ -229,8 +229,10 @@ int main() {
 CHOICES = [
     # K of less than 256: one launch (us, two / one: 8192 x 128 1030 rows 10.9 / 8.5, 10807 x 128 706 rows 20.0 / 7.8, int8 10501 x 64 1001 rows 19.4 / 9.4)
     (1, 8192, 128, 1030, 0), (2, 8192, 128, 1030, 0), (2, 10807, 128, 706, 0), (0, 10501, 64, 1001, 0), (0, 8192, 192, 1030, 0),
-    # K of 512 and less, few tiles, and the token-row kernels half a microsecond faster or more (28 to 442 rows)
-    (0, 29780, 512, 28, -1), (0, 34177, 512, 12, -1), (0, 1404, 192, 73, -1), (2, 311, 256, 442, -1), (1, 3527, 256, 69, -1), (0, 9668, 256, 24, -1),
+    # K of 512 and less, few tiles, and the token-row kernels half a microsecond faster or more; up to 16 rows
+    (0, 1404, 192, 73, -1), (2, 311, 256, 442, -1), (1, 3527, 256, 69, -1), (0, 9668, 256, 24, -1), (0, 345, 256, 146, -1), (0, 34177, 512, 12, -1), (1, 80000, 1024, 9, -1),
+    # more rows and many channels: the tiles
+    (2, 28000, 512, 20, 0), (1, 128256, 4096, 32, 0), (0, 29780, 512, 28, 0),
     # two launches where those are the faster ones
     (2, 4096, 4096, 2060, 12), (1, 2304, 9216, 3700, 116), (1, 3072, 1536, 2698, 10), (0, 2048, 1536, 4100, 4),
 ]
