@@ -11,9 +11,9 @@
 //
 // Measured with the weights in HBM, 32 token rows, this kernel against the 256-channel tiles (us):
 //   channels x k            4096 x 4096   4096 x 14336   6144 x 4096   28672 x 4096   128256 x 4096
-//   int4 groups, binary16    7.7 / 46      18.5 / 142     9.1 / 46      21.7 / 49      89 / 119
+//   int4 groups, binary16    7.8 / 32      18.3 / 107     9.0 / 32      22.0 / 34      79 / 68
 //   int8 x int8 (with the quantization kernel)
-//                           10.0 / 29      23.4 / 90     11.8 / 30      26.7 / 37     101 / 112
+//                           10.1 / 26      23.9 / 91     12.0 / 30      25.5 / 36      95 / 106
 // The narrow layers are bound by the token rows: every compute unit pulls all of x (2 M K bytes) through
 // its vector cache, seven times its share of the 4-bit weights at M = 32.  The wide ones are within 1.3
 // (8-bit) to 1.7 (4-bit) of the time a 5.1 TB/s copy of the weights takes.
@@ -721,8 +721,9 @@ SkinnyArgs make_args(const Geometry &g, const void *packed, const void *x, const
 // the largest K up to which those tiles are the faster ones (0: none), by the share of the compute units that
 // they fill.  Measured at 33 to 64 rows, 32768 to 256000 channels, K of 512 to 14336 (us at 64 rows, these kernels / the
 // tiles, int8 activations with the quantization kernel):
-//   int8 x int4  34000 x 2048 19.7 / 16.8, x 4096 28.4 / 28.8; 40000 x 1024 17.4 / 13.3, x 4096 32.9 / 29.6; 57000 x 8192 71.0 / 66.9
-//   int8 x int8  40000 x 1024 20.4 / 16.0, x 4096 45.1 / 43.6; 75000 x 512 23.6 / 20.2, x 1024 31.0 / 31.8; 100000 x 2048 57.0 / 51.5
+//   int8 x int4  34000 x 2048 18.4 / 17.5, x 4096 27.3 / 26.0; 40000 x 1024 17.3 / 13.3, x 4096 32.0 / 27.1; 57000 x 8192 68.8 / 64.8
+//   int8 x int8  40000 x 1024 19.8 / 17.5, x 4096 42.8 / 42.6; 75000 x 512 22.7 / 21.3, x 1024 29.5 / 30.9; 100000 x 2048 53.0 / 50.5
+// (Drawn for int8 tiles with 32 x 32 MFMAs: the present ones are a few percent faster, so that a line by them would lie a little higher.)
 // Binary16 activations with whole steps of K: tile_us says.
 static int tiles_up_to_k(const Geometry &g, int M, bool int8_activations, int num_cus) {
     constexpr int kAll = 1 << 30;
@@ -746,12 +747,13 @@ static int tiles_up_to_k(const Geometry &g, int M, bool int8_activations, int nu
 // 1.05) and from 16 % low to 27 % high in eight of ten; tiles
 //   tile_us (binary16 activations), 10 + 10.3 K / 1000 (128 x 128, K that is not whole steps: staged_tiles_us); 4.5 + 4.85 K / 1000 and 4.8 + 4.1 K / 1000
 //   (64 tokens, int8 x int8 and int4), 3.5 + 9.3 K / 1000 (int8 x int4, K of an odd number of 128)
-// Measured (us, tiles / here): 4096 x 14336 int4, binary16 activations, 77 rows 131 / 24, 300 131 / 64, 512 133 / 75;
-// 2304 x 9216 int4 groups 77 rows 96 / 15, 300 98 / 26, 1000 95 / 71; 18432 x 2304 77 rows 31 / 22, 200 31 / 38;
-// 11000 x 3008 300 rows 52 / 40; int8, binary16 18432 x 2304 150 rows 42 / 36, 14336 x 4096 640 rows 132 / 114;
-// int8 x int8  6144 x 4096 240 rows 25.4 / 19.5, 300 25.2 / 22.2, 500 25 / 31; 4096 x 14336 384 rows 73 / 59; 8192 x 2304 150 rows 17.9 / 13.5
-// int8 x int4  6144 x 4096 300 rows 21.4 / 17.4; 2304 x 9216 800 rows 44.7 / 34.6; 18432 x 2304 80 rows 15.5 / 13.4, 150 14.9 / 20.7
-// (over 13 such layers, 16 numbers of rows and all formats the choice is less than 1 % slower than the faster one of both).
+// Measured (us, weights in HBM, tiles / here): 4096 x 14336 int4, binary16 activations, 77 rows 83 / 24, 300 83 / 63, 512 83 / 76;
+// 2304 x 9216 int4 groups 77 rows 65 / 15, 300 66 / 26, 1000 67 / 65; 18432 x 2304 77 rows 20.3 / 20.2, 200 29 / 40;
+// 11000 x 3008 300 rows 50 / 37; int8, binary16 18432 x 2304 150 rows 24 / 35, 14336 x 4096 640 rows 78 / 118;
+// int8 x int8  6144 x 4096 240 rows 30 / 23, 300 31 / 26, 500 31 / 35; 4096 x 14336 384 rows 85 / 67; 8192 x 2304 150 rows 20.6 / 16.2
+// int8 x int4  6144 x 4096 300 rows 22.0 / 21.2; 2304 x 9216 800 rows 41 / 44; 18432 x 2304 80 rows 17.1 / 16.1, 150 17.6 / 24.0
+// (the estimates of the int8 tiles are of kernels with 32 x 32 MFMAs, which took a few percent longer than the present ones: near the line these
+// kernels are taken where they are up to 8 % slower, as in the second int8 x int4 example).
 static float skinny_us(const Geometry &g, int M, bool int8_activations, bool gated, int num_cus) {
     SkinnyArgs a = make_args(g, nullptr, nullptr, nullptr, M, nullptr, nullptr, gated ? 0 : -1);
     choose_blocks(a, g.fmt, int8_activations, num_cus);
@@ -845,9 +847,9 @@ bool skinny_product(const Geometry &g, int M, bool int8_activations, bool gated,
     const float k = 1e-3f * (float)g.K;
     const bool w8 = g.fmt == kW8C;
     if (!w8 && g.Kp / 128 % 2 != 0) {
-        // 128 x 128 tiles with both operands staged: two share a compute unit at an eighth more than one (us, tiles / here: 28672 x 4224 65 rows
-        // 44 / 30, 240 rows, 1.75 per compute unit 47 / 53, 384 rows, 2.6 88 / 81, 1000 rows, 7 172 / 220; 11000 x 9600 240 rows 93 / 49, 384 rows
-        // 94 / 67; 6144 x 2944 384 rows 30 / 16).  The choice is 0.3 % slower than the faster of both over 220 such shapes.
+        // 128 x 128 tiles with both operands staged: two share a compute unit at an eighth more than one (us, weights in HBM, tiles / here: 28672 x 4224 65
+        // rows 49 / 32, 240 rows, 1.75 per compute unit 53 / 57, 384 rows, 2.6 93 / 85, 1000 rows, 7 181 / 225; 11000 x 9600 240 rows 100 / 55, 384 rows
+        // 101 / 76; 6144 x 2944 384 rows 31 / 20).  The choice was 0.3 % slower than the faster of both over 220 such shapes, weights in the cache.
         const float fill = (float)((g.N + 127) / 128 * m128) / (float)num_cus;
         return here < 1.04f * (3.5f + 9.3f * k) * (fill <= 1.0f ? 1.0f : 0.12f + ceilf(0.5f * fill));
     }
