@@ -81,14 +81,33 @@ __global__ __launch_bounds__(256) void rope_qkv_few_kernel(const _Float16 *__res
     dst[i + half] = y1;
 }
 
-// Bound: HBM (read once, written once), once the angles are out of the way: cos and sin in fp64 cost
+// Bound: HBM (read once, written once), once the angles and the fp64 products are out of the way: cos and sin in fp64 cost
 // more than everything else together when every head of a token evaluates them (S = 1024, 40 heads to
 // rotate: 34 us; 6000: 165 us, where reading and writing 147 MB takes 28).  So a workgroup takes T
 // tokens, evaluates their d / 2 angles once into LDS, and rotates all heads with them, 16 bytes of each half
-// of a head per thread (13 and 46 us).  Few tokens: the heads are split over several workgroups.
+// of a head per thread.  The rotation itself is done in pairs of fp32 (rotate_pair): with fp64 products, whose conversions and
+// operations kept the vector unit busy for half of the time, the same kernel takes, us, fp64 / fp32 pairs: 1024 tokens of 48 heads of 128
+// 11.8 / 5.7, 6000 42.3 / 19.5 (a copy of the same bytes 19.0), 2048 tokens of 16 heads of 256 14.2 / 7.6, 300 tokens of 48 heads of 128 6.8 / 4.0.
+// Few tokens: the heads are split over several workgroups.
 // Values: a workgroup takes the tokens of one block of 64 cache positions of one head, turns them in LDS and
 // writes runs of up to 128 bytes of the transposed cache instead of single values 128 bytes apart.
 typedef _Float16 rope_h2 __attribute__((ext_vector_type(2)));
+// An fp64 value as the sum of two fp32 values, the second at most half a unit in the last place of the first (48 bits and the sign)
+__device__ __forceinline__ float2 split_f64(double v) {
+    const float hi = (float)v;
+    return make_float2(hi, (float)(v - (double)hi));
+}
+// x0 cos - x1 sin and x1 cos + x0 sin, cos = (t.x, t.y), sin = (t.z, t.w): the product that a fused multiply-add rounds is taken again for its
+// error (difference of products after Kahan), so that cancellation costs nothing and the result is within a unit in the last
+// place of fp32.  An infinite x makes the correction NaN: then the plain result stands, as it does in fp64.
+__device__ __forceinline__ void rotate_pair(float x0, float x1, const float4 &t, float &y0, float &y1) {
+    const float w0 = x1 * t.z, w1 = x1 * t.x;
+    const float f0 = fmaf(x0, t.x, -w0), f1 = fmaf(x0, t.z, w1);
+    const float r0 = f0 + fmaf(x0, t.y, fmaf(-x1, t.w, fmaf(-x1, t.z, w0)));
+    const float r1 = f1 + fmaf(x0, t.w, fmaf(x1, t.y, fmaf(x1, t.x, -w1)));
+    y0 = r0 == r0 ? r0 : f0;
+    y1 = r1 == r1 ? r1 : f1;
+}
 struct RopeArgs {
     const _Float16 *qkv;
     _Float16 *q_out, *kc, *vc;
@@ -97,7 +116,7 @@ struct RopeArgs {
     double log_base;
 };
 __global__ __launch_bounds__(256) void rope_qkv_kernel(RopeArgs a) {
-    extern __shared__ double rope_lds[];
+    extern __shared__ float4 rope_lds[];  // (cos, its rest, sin, its rest)
     const int half = a.d / 2, heads = a.h_q + 2 * a.h_kv, g = a.h_q / a.h_kv;
     if ((int)blockIdx.x < a.rot_wgs) {
         const int tok0 = (int)blockIdx.x * a.T;
@@ -122,8 +141,8 @@ __global__ __launch_bounds__(256) void rope_qkv_kernel(RopeArgs a) {
             const int i = e % half, slot = e - i + (i % 8) * vecs + i / 8;  // (threads read the octet i / 8 side by side)
             double sn, cs;
             sincos((double)(a.pos0 + (tok0 + e / half) % a.S) * exp(-2.0 * (double)i / (double)a.d * a.log_base), &sn, &cs);
-            rope_lds[2 * slot] = cs;
-            rope_lds[2 * slot + 1] = sn;
+            const float2 c = split_f64(cs), n = split_f64(sn);
+            rope_lds[slot] = make_float4(c.x, c.y, n.x, n.y);
         }
         __syncthreads();
         while (t < nt) {
@@ -136,13 +155,14 @@ __global__ __launch_bounds__(256) void rope_qkv_kernel(RopeArgs a) {
             }
             int b = b0, s = s0 + t;
             while (s >= a.S) s -= a.S, ++b;
-            const double *ang = rope_lds + 2 * (t * half + v);
+            const float4 *ang = rope_lds + t * half + v;
             h8 y0, y1;
 #pragma unroll
             for (int i = 0; i < 8; ++i) {
-                const double cs = ang[2 * vecs * i], sn = ang[2 * vecs * i + 1], d0 = (double)(float)u0[i], d1 = (double)(float)u1[i];
-                y0[i] = (_Float16)(float)(d0 * cs - d1 * sn);
-                y1[i] = (_Float16)(float)(d1 * cs + d0 * sn);
+                float r0, r1;
+                rotate_pair((float)u0[i], (float)u1[i], ang[vecs * i], r0, r1);
+                y0[i] = (_Float16)r0;
+                y1[i] = (_Float16)r1;
             }
             _Float16 *dst;
             if (head < a.h_q)
@@ -1023,11 +1043,11 @@ size_t attn_prefill_workspace(int G, int M, int d, int num_cus) {
 hipError_t launch_rope_qkv(const void *qkv, int B, int S, int h_q, int h_kv, int d, int C, int pos0, float base,
                            void *q_out, void *kc, void *vc, hipStream_t st) {
     const long total = (long)B * S;
-    // Few tokens, and more of them where their heads are few: a workgroup that shares the angles of a token has little else
-    // to do (us, this kernel / the other, tokens x heads x values: 400 x 3 x 64 4.0 / 7.7, 540 x 8 x 64 4.8 / 5.2, 328 x 6 x 128
-    // 4.5 / 5.0, 128 x 48 x 64 4.6 / 4.9, 400 x 4 x 256 5.1 / 5.2; 200 x 16 x 128 5.1 / 4.9, 540 x 6 x 128 5.5 / 5.1,
-    // 128 x 16 x 256 5.1 / 4.9, 200 x 48 x 64 5.7 / 5.0)
-    if (total < 128 || total * (h_q + 2 * h_kv) * d < (400L << 10)) {
+    // Few values, and batches of few tokens each (whose values go to the cache one by one anyway): a workgroup that shares the angles
+    // of a token has little else to do (us, this kernel / the other, tokens x heads x values: 400 x 3 x 64 3.1 / 4.3, 17 x 48 x 128 2.9 / 3.7,
+    // 40 x 48 x 128 3.3 / 3.7, 64 sequences of one token x 48 x 128 4.5 / 4.8; 60 x 16 x 256 3.35 / 3.2, 77 x 16 x 256 3.9 / 3.2, 64 x 48 x 128
+    // 3.9 / 3.7, 540 x 8 x 64 4.0 / 3.5, 200 x 48 x 64 5.2 / 3.2; 2000 x 3 x 64 4.4 / 4.6)
+    if (total * (h_q + 2 * h_kv) * d < (240L << 10) || (S < 32 && total < 128)) {
         const long pairs = total * (h_q + 2 * h_kv) * (d / 2);
         rope_qkv_few_kernel<<<(unsigned)((pairs + 255) / 256), 256, 0, st>>>(
             static_cast<const _Float16 *>(qkv), B, S, h_q, h_kv, d, C, pos0, log((double)base),
@@ -1041,13 +1061,16 @@ hipError_t launch_rope_qkv(const void *qkv, int B, int S, int h_q, int h_kv, int
     a.vc = static_cast<_Float16 *>(vc);
     a.B = B, a.S = S, a.h_q = h_q, a.h_kv = h_kv, a.d = d, a.C = C, a.pos0 = pos0;
     a.log_base = log((double)base);
-    // as many tokens per workgroup as one evaluation of an angle per thread covers, once that still gives
-    // several workgroups per compute unit
-    const int most = 512 / d;
-    a.T = total / 512 < 1 ? 1 : total / 512 > most ? most : (int)(total / 512);
+    // at most as many tokens per workgroup as one evaluation of an angle per thread covers; fewer, so that there are about four workgroups per
+    // compute unit (1024 tokens x 48 x 128, 1 / 2 / 4 tokens: 5.7 / 6.2 / 6.5 us), unless their heads are too few to keep the threads
+    // busy (2000 x 3 x 64, 1 / 2 / 8 tokens: 7.7 / 5.0 / 4.7)
+    const long most = 512 / d, busy = (256 + (h_q + h_kv) * (d / 16) - 1) / ((h_q + h_kv) * (d / 16));
+    long T = busy < total / 256 ? busy : total / 256;
+    if (T < total / 1024) T = total / 1024;
+    a.T = T < 1 ? 1 : T > most ? (int)most : (int)T;
     a.rot_wgs = (int)((total + a.T - 1) / a.T);
     a.pblocks = (pos0 + S - 1) / 64 - pos0 / 64 + 1;
-    const size_t angles = (size_t)a.T * d * sizeof(double), tile = (size_t)64 * 66 * 2;
+    const size_t angles = (size_t)a.T * (d / 2) * sizeof(float4), tile = (size_t)64 * 66 * 2;
     rope_qkv_kernel<<<(unsigned)(a.rot_wgs + B * h_kv * a.pblocks * (d / 64)), 256, angles > tile ? angles : tile, st>>>(a);
     return hipGetLastError();
 }

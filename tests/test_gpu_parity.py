@@ -2183,7 +2183,38 @@ def test_last_round_of_tiles_left_to_the_token_row_kernels(fmt, pairs, M, N, K, 
                                                    (3, 50, 16, 8, 128, 128, 61), (1, 128, 24, 8, 128, 192, 64), (1, 319, 8, 1, 128, 384, 9),
                                                    (1, 321, 6, 2, 128, 384, 9)])
 def test_rope_qkv_many_tokens(B, S, h_q, h_kv, d, C, pos0):
-    """128 tokens and more of at least 400 Ki values share the evaluation of an angle among the heads of a token: one and
-    several tokens per workgroup (total / 512, at most 512 / d), workgroups that span sequences, cache blocks that the
+    """Calls of many values share the evaluation of an angle among the heads of a token: one and
+    several tokens per workgroup (at most 512 / d), workgroups that span sequences, cache blocks that the
     tokens fill in part; and the other kernel beside that line."""
     test_rope_qkv_layout(B, S, h_q, h_kv, d, C, pos0)
+
+
+# the line at 240 Ki values (60 x 16 x 256 and one token fewer), sequences of 31 and 32 tokens, several tokens per workgroup for want of heads
+@pytest.mark.parametrize("B,S,h_q,h_kv,d,C,pos0", [(1, 59, 8, 4, 256, 128, 30), (1, 60, 8, 4, 256, 128, 30), (4, 31, 8, 4, 128, 64, 3),
+                                                   (4, 32, 16, 8, 128, 64, 3), (1, 2000, 1, 1, 64, 2048, 1), (1, 520, 4, 2, 64, 576, 50)])
+def test_rope_qkv_line_between_kernels(B, S, h_q, h_kv, d, C, pos0):
+    test_rope_qkv_layout(B, S, h_q, h_kv, d, C, pos0)
+
+
+def test_rope_qkv_infinite_values():
+    """An infinite or NaN value leaves the rotation as it leaves the definition's: the correction terms of the fp32 pairs
+    must not turn an infinity into NaN, not even at position 0, where the sine and its rest are zero."""
+    B, S, h_q, h_kv, d, C = 1, 128, 16, 4, 128, 128
+    g, W = h_q // h_kv, (h_q + 2 * h_kv) * d
+    qkv = synth.activations(3801, 0, 0, S, W).reshape(B, S, W)
+    rng = np.random.default_rng(5)
+    at = rng.integers(0, qkv.size, 400)
+    qkv.reshape(-1)[at] = rng.choice(np.array([np.inf, -np.inf, np.nan, 65504.0, -65504.0], dtype=np.float16), 400)
+    q_out = torch.zeros((B * h_kv, S * g, d), dtype=torch.float16, device=DEV)
+    kc = torch.zeros((B * h_kv, C, d), dtype=torch.float16, device=DEV)
+    vc = torch.zeros((B * h_kv, C // 64, d, 64), dtype=torch.float16, device=DEV)
+    binding.qfc_rope_qkv(torch.from_numpy(qkv).to(DEV), 0, _attn_shape(B, h_q, h_kv, d, C), 500000.0, q_out, kc, vc)
+    torch.cuda.synchronize()
+    with np.errstate(all="ignore"):
+        q_ref, k_ref, _ = oracle.rope_qkv_layout(qkv, 0, h_q, h_kv, d, 500000.0)
+    for got, ref in ((q_out, q_ref), (kc, k_ref)):
+        got = got.cpu().numpy().astype(np.float64).reshape(-1)
+        ref = ref.astype(np.float64).reshape(-1)
+        odd = ~np.isfinite(ref)
+        assert odd.any() and np.array_equal(np.isnan(got), np.isnan(ref))
+        assert np.array_equal(got[odd & ~np.isnan(ref)], ref[odd & ~np.isnan(ref)])
