@@ -41,6 +41,7 @@ struct GemmI8Args {
     void *out;
     int M, N, Kp, n_tiles, m_tiles;
     int by_tokens;  // order of the tiles (see xcd_tile)
+    int share;      // token tiles that divide the prefetch of the weights among them
     // 4-bit weights enter the MFMA as 16 q (the code's nibble in the top half of a byte): the sums are
     // 16 times the definition's, exactly; channel scales are multiplied by 1/16, raw sums shifted by 4
     float sw_mul = 1.0f;
@@ -475,8 +476,15 @@ __global__ __launch_bounds__(256, 2) void gemm_i8_w4_kernel(GemmI8Args a) {
 // flight from one wavefront, data had been seen in ring slots after the counter had dropped to zero;
 // the cause is not known, so no late copy may have a destination that anything reads or reuses).
 // The number of stages must be even.
-// TM = 4: 256 x 128 tile; TM = 2: 256 x 64 tile (twice the tiles for small outputs, twice the weight
-// loads per MFMA).
+// CG wavefronts side by side: tiles of 64 CG channels x 32 TM tokens, 256 or 128 x 128 or 64.  KS groups of them share K (an even number of stages each) and
+// hand their sums over through LDS at the end.  Which form: int8_tile_us.
+// PF: a compute unit has only so many cache lines on their way to it (about 45 KB: 57 GB/s of weights that come from HBM, 126 out of L2), so what bounds a
+// layer of one round of tiles is how long a line is on its way, not the rate of HBM or of the matrix cores (4096 x 14336, 1024 rows, tiles of 256 x 64:
+// 88 us, and 88 without its MFMAs).  The token tiles of the same weights therefore divide among them an early touch of every line, PW + NS - 1 stages
+// ahead, one instruction per wavefront and stage, and the weights' own loads then find them in L2: 128 x 128 tiles in two parts of K 73.9 / 68.1 us, 2304 x 9216
+// 1024 rows 48.8 / 44.6.  Tiles of 128 x 128 read 3.7 MB each where 256 x 64 read 4.6 (the same shapes 88 / 74 and 57 / 49 without the touch); for 4-bit weights,
+// whose bytes are half as many, 256 x 64 stays the better one and the touch costs more than it saves (62.4 / 63.6).  A touch is a copy into the
+// spare KiB like those past the end of K.
 // PIPE: the first operands of a stage are read during the MFMAs of the stage before, so its copies must have landed a stage
 // earlier.  For int8 weights in tiles of 64 tokens, which run where a compute unit has one of them: nothing else fills the time between the barrier
 // and the first MFMA.  With 4-bit weights the wait, which then covers more, costs more than it saves (540 x 9984 1434 rows 50.0 / 51.5 us, 4096 x
@@ -498,45 +506,62 @@ __global__ __launch_bounds__(256, 2) void gemm_i8_w4_kernel(GemmI8Args a) {
 // waits, and with the copies in between those waits would drain most of the prefetch.  A load's
 // destination registers are handed back to the compiler (an empty asm that "redefines" them) right
 // after the explicit wait that covers the load, so that no MFMA can be scheduled ahead of that wait.
-template <bool W4, int NS, int PW, int TM, int OUT_MODE>
-__global__ __launch_bounds__(256, 2) void gemm_i8_dw_kernel(GemmI8Args a) {
-    constexpr int BN = 256, BM = 32 * TM, TN = 4, WV = W4 ? 1 : 2;  // (WV: weight vectors per row tile and stage)
+template <bool W4, int NS, int PW, int TM, int CG, int KS, bool PF, int OUT_MODE>
+__global__ __launch_bounds__(CG * KS * 64, 2) void gemm_i8_dw_kernel(GemmI8Args a) {
+    constexpr int BN = 64 * CG, BM = 32 * TM, TN = 4, WV = W4 ? 1 : 2;  // (WV: weight vectors per row tile and stage)
     constexpr int XT = BM / 16 * 2;  // activation tiles (KiB) per stage
-    constexpr int CP = XT / 4;       // copies per wavefront and stage
+    constexpr int CP = XT / CG;      // copies per wavefront and stage
     constexpr int XJ = 2 * TM;   // blocks of 16 token rows
     constexpr bool PIPE = !W4 && TM == 2;
     static_assert(NS >= 3 && (TM == 2 || TM == 4), "tile shapes");
     extern __shared__ uint4 lds[];  // NS stages of XT tiles x 64 vectors
     const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int group = KS == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) / CG;  // which part of K
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) - group * CG;
     int nt, mt;
     xcd_tile(blockIdx.x, a.n_tiles, a.m_tiles, a.by_tokens, nt, mt);
-    const int KT = a.Kp / 128;  // stages
+    // stages: of the layer, before the group's, of the group (an even number; the first groups may have two more)
+    const int all = a.Kp / 128, pairs = all / 2, first = 2 * (group * (pairs / KS) + min(group, pairs % KS));
+    const int KT = KS == 1 ? all : 2 * (pairs / KS + (group < pairs % KS ? 1 : 0));
 
-    // weights: row tile i of the wavefront's four, a whole packed KiB tile
-    const uint4 *wsrc[TN];
+    // weights: row tile i of the wavefront's four, whole packed KiB tiles, at offset woff[i] from the stage's base
+    const uint4 *const wsrc = a.w + ((size_t)(nt * (BN / 16) + 4 * wave) * all + first) * (64 * WV);
+    uint32_t woff[TN];
 #pragma unroll
-    for (int i = 0; i < TN; ++i) wsrc[i] = a.w + ((size_t)(nt * (BN / 16) + 4 * wave + i) * KT) * (64 * WV) + lane;
+    for (int i = 0; i < TN; ++i) woff[i] = (uint32_t)(i * all * WV * 1024 + lane * 16);
     v4i wreg[PW][TN][WV];
     auto load_w = [&](int slot, int kt, int v, const bool bulk) __attribute__((always_inline)) {  // vector v of the row tiles; bulk: kt < KT is known
         const int kc = bulk || kt < KT ? kt : min(kt - KT, KT - 1);
 #pragma unroll
         for (int i = 0; i < TN; ++i)
-            asm volatile("global_load_dwordx4 %0, %1, off" : "=&v"(wreg[slot][i][v]) : "v"(wsrc[i] + (size_t)(WV * kc + v) * 64) : "memory");
+            asm volatile("global_load_dwordx4 %0, %1, %2 offset:%3" : "=&v"(wreg[slot][i][v]) : "v"(woff[i]), "s"(wsrc + (size_t)(WV * kc) * 64), "n"(v * 1024) : "memory");
     };
     // activations: tile t = 2 g + e of a stage is half e of the stage's 128 k for token rows 16 g ..
     const uint32_t lds0 = (uint32_t)(uintptr_t)(lptr_t)lds;
-    const uint4 *xsrc = a.x + ((size_t)(mt * (BM / 16)) * 2 * KT) * 64;
-    constexpr uint32_t kSpare = NS * XT * 1024;  // copies past the end of K land here; nothing reads it
+    const uint32_t ring0 = lds0 + group * (NS * XT * 1024);
+    const uint4 *const ring = lds + group * (NS * XT * 64);
+    const uint4 *xsrc = a.x + ((size_t)(mt * (BM / 16)) * 2 * all + 2 * first) * 64;
+    constexpr uint32_t kSpare = KS * NS * XT * 1024;  // copies past the end of K land here; nothing reads it
     auto issue_x = [&](int kt, const bool bulk) __attribute__((always_inline)) {
         const bool real = bulk || kt < KT;
         const int kc = real ? kt : min(kt - KT, KT - 1);
 #pragma unroll
         for (int h = 0; h < CP; ++h) {
-            const int t = wave + 4 * h;
-            copy16_to_lds(xsrc + ((size_t)(t >> 1) * 2 * KT + 2 * kc + (t & 1)) * 64, lane * 16,
-                          lds0 + (real ? ((kt % NS) * XT + t) * 1024 : kSpare));
+            const int t = wave + CG * h;
+            copy16_to_lds(xsrc + ((size_t)(t >> 1) * 2 * all + 2 * kc + (t & 1)) * 64, lane * 16,
+                          real ? ring0 + ((kt % NS) * XT + t) * 1024 : lds0 + kSpare);
         }
+    };
+
+    // the touch of the weights of a stage far ahead (PF): of the 128-byte lines of the wavefront's row tiles, those that fall to this token tile
+    constexpr int PFN = PF ? 1 : 0, kLines = 32 * WV;
+    const int per = (kLines + a.share - 1) / a.share, pidx = min((mt % a.share) * per + lane % per, kLines - 1);
+    const uint32_t poff = (uint32_t)((pidx / (8 * WV)) * all * WV * 1024 + (pidx % (8 * WV)) * 128);
+    constexpr int kPrefetch = NS - 1 + PW;
+    auto prefetch = [&](int kt, const bool bulk) __attribute__((always_inline)) {
+        if (!PF) return;
+        const int kc = bulk || kt < KT ? kt : KT - 1;
+        asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dword %0, %1" ::"v"(poff), "s"(wsrc + (size_t)(WV * kc) * 64), "s"(lds0 + kSpare) : "memory", "m0");
     };
 
     v4i acc[TN][XJ];
@@ -551,7 +576,10 @@ __global__ __launch_bounds__(256, 2) void gemm_i8_dw_kernel(GemmI8Args a) {
 #pragma unroll
         for (int v = 0; v < WV; ++v) load_w(p, p, v, kEdge);
 #pragma unroll
-    for (int p = 0; p < NS - 1; ++p) issue_x(p, kEdge);
+    for (int p = 0; p < NS - 1; ++p) {
+        issue_x(p, kEdge);
+        prefetch(PW + p, kEdge);
+    }
 
     // Waiting.  Copies into LDS and loads into registers share one counter (vmcnt) but do NOT complete
     // in order relative to each other - only within their own kind (measured: with waits that assumed
@@ -561,17 +589,17 @@ __global__ __launch_bounds__(256, 2) void gemm_i8_dw_kernel(GemmI8Args a) {
     // thanks to the prologue.  If at most kAllowed operations are outstanding, neither stage kt's copies nor its loads can be
     // among them: an unfinished copy would have all later copies behind it, an unfinished load all later loads.  With PIPE it is stage kt + 1
     // whose copies must have landed, which has one stage fewer behind it.
-    constexpr int kAfterCopies = CP * (NS - (PIPE ? 3 : 2)), kAfterLoads = 4 * WV * (PW - 1);
+    constexpr int kAfterCopies = (CP + PFN) * (NS - (PIPE ? 3 : 2)), kAfterLoads = 4 * WV * (PW - 1);
     constexpr int kAllowed = kAfterCopies < kAfterLoads ? kAfterCopies : kAfterLoads;
     // (the most operations a wavefront ever has outstanding: right after the refills of an iteration)
-    static_assert(CP * (NS - 1) + 4 * WV * PW <= 63, "wait counts must fit the 6-bit counter");
+    static_assert((CP + PFN) * (NS - 1) + 4 * WV * PW <= 63, "wait counts must fit the 6-bit counter");
 
     v4i fb[XJ];  // (token rows of a k step of 64: a block is replaced by the next step's once it has been multiplied)
     auto read_x = [&](int kt, int ks, int j) __attribute__((always_inline)) {
-        fb[j] = __builtin_bit_cast(v4i, lds[(kt % NS) * (XT * 64) + (2 * j + ks) * 64 + lane]);
+        fb[j] = __builtin_bit_cast(v4i, ring[(kt % NS) * (XT * 64) + (2 * j + ks) * 64 + lane]);
     };
     if (PIPE) {
-        wait_vmcnt<CP * (NS - 2)>();
+        wait_vmcnt<(CP + PFN) * (NS - 2)>();
         asm volatile("s_barrier" ::: "memory");
 #pragma unroll
         for (int j = 0; j < XJ; ++j) read_x(0, 0, j);
@@ -590,6 +618,7 @@ __global__ __launch_bounds__(256, 2) void gemm_i8_dw_kernel(GemmI8Args a) {
 #pragma unroll
                 for (int v = 0; v < WV; ++v) asm volatile("" : "+v"(wreg[u][i][v]));
             issue_x(kt + NS - 1, bulk);
+            prefetch(kt + kPrefetch, bulk);
             if (!PIPE) {
 #pragma unroll
                 for (int j = 0; j < XJ; ++j) read_x(kt, 0, j);
@@ -628,7 +657,7 @@ __global__ __launch_bounds__(256, 2) void gemm_i8_dw_kernel(GemmI8Args a) {
             }
         }
     };
-    constexpr int kAhead = NS - 1 > PW ? NS - 1 : PW;  // how far past kt a pass issues
+    constexpr int kAhead = PF ? NS - 1 + PW : NS - 1 > PW ? NS - 1 : PW;  // how far past kt a pass issues
     int kt0 = 0;
     for (; kt0 + PW - 1 + kAhead < KT; kt0 += PW) stages_pw(kt0, PW, kBulk);
     for (; kt0 + PW <= KT; kt0 += PW) stages_pw(kt0, PW, kEdge);
@@ -652,22 +681,63 @@ __global__ __launch_bounds__(256, 2) void gemm_i8_dw_kernel(GemmI8Args a) {
     } else {
         drain();
     }
-    epilogue<OUT_MODE, TN, XJ>(a, acc, lds, nt * BN + wave * 64, mt * BM, wave, lane);
+    if constexpr (KS == 1) {
+        epilogue<OUT_MODE, TN, XJ>(a, acc, lds, nt * BN + wave * 64, mt * BM, wave, lane);
+    } else {
+        // The parts of K meet (whole numbers: in any order): group 0 keeps the first half of the token rows, group 1 the second, and everybody
+        // hands over what it does not keep, [half][group][wavefront][16-byte vector][lane] over the dead rings, below the spare KiB.
+        constexpr int H = XJ / 2;
+        static_assert(2 * (KS - 1) * CG * TN * H <= KS * NS * XT, "the sums handed over fit over the rings");
+        v4i *const given = reinterpret_cast<v4i *>(lds);
+        auto slot = [&](int half, int from) { return given + (((half * (KS - 1) + from) * CG + wave) * (TN * H)) * 64 + lane; };
+        for (int i = KT; i < 2 * ((pairs + KS - 1) / KS); ++i) asm volatile("s_barrier" ::: "memory");  // (as many as the first group's stages)
+        asm volatile("s_barrier" ::: "memory");  // every wavefront has read its last stage and all its copies have landed (drain)
+#pragma unroll
+        for (int half = 0; half < 2; ++half) {
+            if (group == half) continue;
+            v4i *to = slot(half, group > half ? group - 1 : group);
+#pragma unroll
+            for (int i = 0; i < TN; ++i)
+#pragma unroll
+                for (int j = 0; j < H; ++j) to[(i * H + j) * 64] = acc[i][half * H + j];
+        }
+        __syncthreads();
+        v4i out[TN][H];
+#pragma unroll
+        for (int half = 0; half < 2; ++half) {
+            if (group != half) continue;
+#pragma unroll
+            for (int i = 0; i < TN; ++i)
+#pragma unroll
+                for (int j = 0; j < H; ++j) {
+                    out[i][j] = acc[i][half * H + j];
+#pragma unroll
+                    for (int from = 0; from < KS - 1; ++from) out[i][j] += slot(half, from)[(i * H + j) * 64];
+                }
+        }
+        __syncthreads();
+        if (group >= 2) {  // nothing to store: the one barrier that the others pass in their store phase
+            asm volatile("s_barrier" ::: "memory");
+            return;
+        }
+        epilogue<OUT_MODE, TN, H>(a, out, lds, nt * BN + wave * 64, mt * BM + group * (H * 16), group * CG + wave, lane);
+    }
 }
 
-template <bool W4, int NS, int PW, int TM, int OUT_MODE>
+template <bool W4, int NS, int PW, int TM, int CG, int KS, bool PF, int OUT_MODE>
 hipError_t launch_dw(GemmI8Args a, hipStream_t st) {
-    constexpr size_t ring_bytes = (size_t)NS * (4 * TM) * 1024;  // + one spare KiB for the copies past the end of K
+    constexpr size_t ring_bytes = (size_t)KS * NS * (4 * TM) * 1024;  // + one spare KiB for the copies past the end of K
     constexpr size_t lds_bytes = ring_bytes + 1024;
-    static_assert(ring_bytes >= 4 * 32 * (64 + 8) * 2, "the store phase stages its blocks inside the ring, below the spare KiB");
-    static_assert(lds_bytes <= 80 * 1024, "two workgroups per compute unit");
+    static_assert(ring_bytes >= (size_t)CG * (KS > 1 ? 2 : 1) * 32 * (64 + 8) * 2, "the store phase stages its blocks inside the ring, below the spare KiB");
+    static_assert(lds_bytes <= (KS > 1 || NS > 8 ? 160 : 80) * 1024, "two workgroups per compute unit, or one");
     static_assert(PW == 2 || PW == 4, "an even number of stages is passes of PW and two more");
-    if ((a.Kp / 128) % 2 != 0) return hipErrorInvalidValue;
-    if (const hipError_t e = allow_dynamic_lds<gemm_i8_dw_kernel<W4, NS, PW, TM, OUT_MODE>>(lds_bytes); e != hipSuccess) return e;
-    a.n_tiles = (a.N + 255) / 256;
+    if ((a.Kp / 128) % 2 != 0 || a.Kp / 128 < 2 * KS) return hipErrorInvalidValue;
+    if (const hipError_t e = allow_dynamic_lds<gemm_i8_dw_kernel<W4, NS, PW, TM, CG, KS, PF, OUT_MODE>>(lds_bytes); e != hipSuccess) return e;
+    a.n_tiles = (a.N + 64 * CG - 1) / (64 * CG);
     a.m_tiles = (a.M + 32 * TM - 1) / (32 * TM);
-    a.by_tokens = walk_by_tokens(a.n_tiles, a.m_tiles, W4 ? 128.0f : 256.0f, 32.0f * TM);
-    gemm_i8_dw_kernel<W4, NS, PW, TM, OUT_MODE><<<dim3((unsigned)(a.n_tiles * a.m_tiles)), 256, lds_bytes, st>>>(a);
+    a.by_tokens = walk_by_tokens(a.n_tiles, a.m_tiles, (W4 ? 32.0f : 64.0f) * CG, 32.0f * TM);
+    a.share = a.m_tiles < 16 ? a.m_tiles : 16;
+    gemm_i8_dw_kernel<W4, NS, PW, TM, CG, KS, PF, OUT_MODE><<<dim3((unsigned)(a.n_tiles * a.m_tiles)), CG * KS * 64, lds_bytes, st>>>(a);
     return hipGetLastError();
 }
 
@@ -696,50 +766,80 @@ hipError_t launch_w4(GemmI8Args a, hipStream_t st) {
     return hipGetLastError();
 }
 
-// Tiles of 256 channels: 128 tokens each where those tiles are for three quarters of the compute units and more, or where tiles of
-// 64 would start a second round that costs more than the larger tiles' idle compute units.  With int8 weights it does at once (us with the
-// quantization kernel, 64 / 128 tokens: 18432 x 2304 240 rows, 288 tiles of 64, 25.0 / 21.9; 2304 x 9216 1826 rows, 261 tiles, 80 / 61, 2274 rows 93 / 64;
-// 11000 x 3008 500 rows 30.5 / 26.0), with int4 weights from a quarter of a round on (5120 x 9216 802 rows, 260 tiles, 61.4 / 61.2, 1152
-// rows, 360 tiles, 63.7 / 62.5; 1536 x 14336 2722 rows, 258 tiles, 95 / 97).  Outputs that are stored as they lie in the registers
-// (accumulators; rows that are no multiple of 16 bytes) take longer than the round from 128-token tiles: with int4 weights
-// always (4100 x 4096 1211 rows 38.4 / 43.2, 9001 x 1024 600 rows 24.8 / 31.3), with int8 weights below K of 4096 (4100 x 1024 1211 rows
-// 21.0 / 24.7, 9001 x 2304 600 rows 34.8 / 38.5, x 4096 47.6 / 46.5).
-bool tiles_of_128_tokens(const GemmI8Args &a, bool w4, bool staged_store, int num_cus) {
-    const long n256 = (a.N + 255) / 256, m128 = (a.M + 127) / 128, m64 = (a.M + 63) / 64;
-    if (4 * n256 * m128 >= 3L * num_cus) return true;
-    if (w4) return staged_store && 4 * n256 * m64 > 5L * num_cus;
-    return n256 * m64 > num_cus && (staged_store || a.Kp >= 4096);
-}
-
-// Tiles of 64 tokens hold the weights of four stages instead of two: an operation more in flight is an
+// Tiles of 256 channels x 64 tokens hold the weights of four stages instead of two: an operation more in flight is an
 // operation that the wait of a stage need not see done.  us with the quantization kernel, two / four: int4 4096 x 4096 700 rows 25.3 / 24.4, 3101 x 8192
 // 840 rows 48.9 / 46.6 (the worst 2210 x 512 2197 rows 21.6 / 22.0); int8 375 x 12288 2136 rows 66.1 / 65.4, 1966 x 7680 1399 rows 50.5 / 49.3.  With int8
 // weights the longer start shows at small K: 699 x 768 2364 rows 18.3 / 19.4, 2233 x 1152 2642 rows 28.1 / 29.4, 1344 x 1024 1503 rows 12.8 / 13.1,
 // 4096 x 4096 1024 rows 26.0 / 26.0.
 bool weights_four_stages_ahead(const GemmI8Args &a) { return a.Kp >= 6144; }
 
-// The kernel is chosen by size, or by number for tests: 4, 10, 12 (int8 weights), 20, 21, 23 (int4).  A number that names none of the call's
-// kernels leaves the choice.
+bool parts_fit(int Kp, int parts) { return Kp / 128 >= 2 * parts; }
+
+// The kernel is chosen by size (int8_tile_us), or by number for tests: 4, 10, 12, 13, 14 (int8 weights), 20, 21, 23, 24, 25 (int4).  A number that
+// names none of the call's kernels leaves the choice.
+// Tiles of 256 x 128 ask for weights ahead of their loads from 16 token tiles on (us without / with: 28672 x 4096 4096 rows 446 / 424, 2304 x 9216 2048
+// rows 71.4 / 65.3, 6144 x 4096 2048 rows 61.0 / 59.9; with fewer tiles, a larger share each, 28672 x 4096 1024 rows 114.1 / 116.3, 11808 x 9216 863 rows 6 % slower).
 template <int OUT_MODE>
-hipError_t launch_mode(const GemmI8Args &a, int num_cus, hipStream_t st) {
+hipError_t launch_mode(const GemmI8Args &a, int chosen, hipStream_t st) {
     int variant = tuning().gemm_variant;
-    if (variant != 4 && variant != 10 && variant != 12) variant = tiles_of_128_tokens(a, false, OUT_MODE == 0 && a.N % 8 == 0, num_cus) ? 10 : 12;
-    if (variant == 4) return launch_staged<128, 128, 3, OUT_MODE>(a, st);
-    if (variant == 10) return launch_dw<false, 4, 2, 4, OUT_MODE>(a, st);
-    return weights_four_stages_ahead(a) ? launch_dw<false, 8, 4, 2, OUT_MODE>(a, st) : launch_dw<false, 8, 2, 2, OUT_MODE>(a, st);
+    if (variant != 4 && variant != 10 && variant != 12 && ((variant != 13 && variant != 14) || !parts_fit(a.Kp, 2))) variant = chosen;
+    switch (variant) {
+        case 4: return launch_staged<128, 128, 3, OUT_MODE>(a, st);
+        case 10: return a.M > 15 * 128 ? launch_dw<false, 4, 2, 4, 4, 1, true, OUT_MODE>(a, st) : launch_dw<false, 4, 2, 4, 4, 1, false, OUT_MODE>(a, st);
+        case 13: return launch_dw<false, 4, 2, 4, 2, 2, true, OUT_MODE>(a, st);
+        case 14: return launch_dw<false, 4, 2, 2, 2, 2, true, OUT_MODE>(a, st);
+    }
+    return weights_four_stages_ahead(a) ? launch_dw<false, 8, 4, 2, 4, 1, false, OUT_MODE>(a, st) : launch_dw<false, 8, 2, 2, 4, 1, false, OUT_MODE>(a, st);
 }
 
 template <int OUT_MODE>
-hipError_t launch_mode_w4(const GemmI8Args &a, int num_cus, hipStream_t st) {
+hipError_t launch_mode_w4(const GemmI8Args &a, int chosen, hipStream_t st) {
     int variant = tuning().gemm_variant;
-    if (variant != 20 && variant != 21 && variant != 23) {
-        variant = (a.Kp / 128) % 2 != 0 ? 20 : tiles_of_128_tokens(a, true, OUT_MODE == 0 && a.N % 8 == 0, num_cus) ? 21 : 23;
+    if (variant != 20 && variant != 21 && variant != 23 && (variant != 24 || !parts_fit(a.Kp, 2)) && (variant != 25 || !parts_fit(a.Kp, 4))) variant = chosen;
+    if ((a.Kp / 128) % 2 != 0) variant = 20;
+    switch (variant) {
+        case 20: return launch_w4<128, 128, 3, OUT_MODE>(a, st);
+        case 21: return launch_dw<true, 4, 2, 4, 4, 1, false, OUT_MODE>(a, st);
+        case 24: return launch_dw<true, 4, 4, 2, 2, 2, false, OUT_MODE>(a, st);
+        case 25: return launch_dw<true, 4, 4, 2, 2, 4, false, OUT_MODE>(a, st);
     }
-    if (variant == 20) return launch_w4<128, 128, 3, OUT_MODE>(a, st);
-    return variant == 21 ? launch_dw<true, 4, 2, 4, OUT_MODE>(a, st) : launch_dw<true, 8, 4, 2, OUT_MODE>(a, st);
+    return launch_dw<true, 8, 4, 2, 4, 1, false, OUT_MODE>(a, st);
 }
 
 }  // namespace
+
+// Estimated time of the direct-weights kernel (with the quantization of the rows, but for what of it grows with the rows) and the form that it is fastest
+// in, by its number.  A tile takes `each` us and K / 1000 times `alone` on a compute unit of its own, `shared` where several are in flight; of a last
+// round that is not full, the part that grows with K takes at least the share `idle` of a full one's.  Fitted to 290 shapes of 768 to 28672 channels, K of 256 to
+// 14336 and 65 to 4096 rows; the choice is 0.25 % slower than the fastest of the four forms, with int8 weights 1.16 times at worst (20128 x 5632 175
+// rows), int4 1.07.  us, 256 x 128 / 256 x 64 / in parts of K 128 x 128 / 128 x 64, int8 weights: 4096 x 14336 1024 rows 98 / 87 / 68 / 87, 512 rows 96 / 82 / 64 /
+// 55, 2048 rows 110 / 156 / 133 / 171; 2304 x 9216 990 rows 65 / 57 / 45 / 51; 6144 x 4096 1024 rows 34.0 / 45.5 / 44.5 / 42.1; int4 (256 x 128 / 256 x 64 /
+// 128 x 64 in two / in four parts): 2304 x 9216 814 rows 59 / 40 / 32.4 / 30.5, 4096 x 4096 512 rows 31 / 21.9 / 17.7 / 19.0.
+// Outputs that are stored as they lie in the registers (accumulators; rows that are no multiple of 16 bytes) cost tiles of 256 x 128 about 4 us
+// more (int4 9001 x 1024 600 rows, 256 x 128 / 256 x 64, 31.1 / 24.9; int8 4100 x 1024 1211 rows 24.7 / 21.4).
+float int8_tile_us(const Geometry &g, int M, bool staged_store, int num_cus, int *form) {
+    struct Fit {
+        int number, channels, tokens, parts;
+        float start, each, alone, shared, idle;
+    };
+    static const Fit fits[2][4] = {{{10, 256, 128, 1, 3.58f, 4.74f, 7.78f, 5.94f, 0.75f}, {12, 256, 64, 1, 3.88f, 2.73f, 6.21f, 4.43f, 0.81f},
+                                    {13, 128, 128, 2, 2.58f, 6.57f, 4.40f, 3.88f, 0.95f}, {14, 128, 64, 2, 5.34f, 1.75f, 3.68f, 2.85f, 0.94f}},
+                                   {{21, 256, 128, 1, 5.69f, 2.80f, 6.72f, 5.43f, 0.75f}, {23, 256, 64, 1, 5.23f, 2.18f, 4.00f, 3.27f, 0.79f},
+                                    {24, 128, 64, 2, 5.03f, 1.77f, 2.82f, 2.08f, 0.77f}, {25, 128, 64, 4, 3.33f, 4.96f, 2.50f, 2.15f, 0.78f}}};
+    const float k = 1e-3f * (float)g.Kp;
+    float best = 0.0f;
+    *form = 0;
+    for (const Fit &f : fits[g.fmt == kW4C]) {
+        if (f.parts > 1 && !parts_fit(g.Kp, f.parts)) continue;
+        const int tiles = (g.N + f.channels - 1) / f.channels * ((M + f.tokens - 1) / f.tokens), full = tiles / num_cus, rest = tiles % num_cus;
+        auto work = [&](int n) { return n == 0 ? 0.0f : n == 1 ? f.alone * k : (float)n * f.shared * k; };  // of a compute unit with n tiles
+        float us = f.start + (float)full * f.each + work(full);
+        if (rest > 0) us += f.each + (work(full + 1) - work(full)) * (f.idle + (1.0f - f.idle) * (float)rest / (float)num_cus);
+        if (!staged_store && f.channels * f.tokens == 256 * 128) us += 4.0f;
+        if (*form == 0 || us < best) best = us, *form = f.number;
+    }
+    return best;
+}
 
 hipError_t launch_gemm_i8(const Geometry &g, const void *packed, const int8_t *xq_tiled,
                           const float *sx, int M, int Mp, void *out, int out_mode, const void *residual,
@@ -756,14 +856,16 @@ hipError_t launch_gemm_i8(const Geometry &g, const void *packed, const int8_t *x
     a.M = M;
     a.N = g.N;
     a.Kp = g.Kp;
-    a.n_tiles = a.m_tiles = a.by_tokens = 0;
+    a.n_tiles = a.m_tiles = a.by_tokens = a.share = 0;
     a.gated_act = out_mode == 0 && g.pair_half ? gated_act : -1;
+    int form;
+    int8_tile_us(g, M, out_mode == 0 && g.N % 8 == 0, num_cus, &form);
     if (g.fmt == kW4C) {
         a.sw_mul = 0.0625f;
         a.acc_shift = 4;
-        return out_mode == 0 ? launch_mode_w4<0>(a, num_cus, st) : launch_mode_w4<1>(a, num_cus, st);
+        return out_mode == 0 ? launch_mode_w4<0>(a, form, st) : launch_mode_w4<1>(a, form, st);
     }
-    return out_mode == 0 ? launch_mode<0>(a, num_cus, st) : launch_mode<1>(a, num_cus, st);
+    return out_mode == 0 ? launch_mode<0>(a, form, st) : launch_mode<1>(a, form, st);
 }
 
 }  // namespace qfc

@@ -745,15 +745,13 @@ static int tiles_up_to_k(const Geometry &g, int M, bool int8_activations, int nu
 // rows are cut into blocks, with the time growing with their number.  Both times are estimated: here see estimate_us, which where
 // the two are near each other (65 to 1024 rows, 1500 to 65536 channels, K of 896 to 14336, 721 shapes) is 1 to 7 % high in the median (hence the
 // 1.05) and from 16 % low to 27 % high in eight of ten; tiles
-//   tile_us (binary16 activations), 10 + 10.3 K / 1000 (128 x 128, K that is not whole steps: staged_tiles_us); 4.5 + 4.85 K / 1000 and 4.8 + 4.1 K / 1000
-//   (64 tokens, int8 x int8 and int4), 3.5 + 9.3 K / 1000 (int8 x int4, K of an odd number of 128)
+//   tile_us (binary16 activations), 10 + 10.3 K / 1000 (128 x 128, K that is not whole steps: staged_tiles_us); int8_tile_us, 3.5 + 9.3 K / 1000
+//   (int8 x int4, K of an odd number of 128)
 // Measured (us, weights in HBM, tiles / here): 4096 x 14336 int4, binary16 activations, 77 rows 83 / 24, 300 83 / 63, 512 83 / 76;
 // 2304 x 9216 int4 groups 77 rows 65 / 15, 300 66 / 26, 1000 67 / 65; 18432 x 2304 77 rows 20.3 / 20.2, 200 29 / 40;
 // 11000 x 3008 300 rows 50 / 37; int8, binary16 18432 x 2304 150 rows 24 / 35, 14336 x 4096 640 rows 78 / 118;
-// int8 x int8  6144 x 4096 240 rows 30 / 23, 300 31 / 26, 500 31 / 35; 4096 x 14336 384 rows 85 / 67; 8192 x 2304 150 rows 20.6 / 16.2
-// int8 x int4  6144 x 4096 300 rows 22.0 / 21.2; 2304 x 9216 800 rows 41 / 44; 18432 x 2304 80 rows 17.1 / 16.1, 150 17.6 / 24.0
-// (the estimates of the int8 tiles are of kernels with 32 x 32 MFMAs, which took a few percent longer than the present ones: near the line these
-// kernels are taken where they are up to 8 % slower, as in the second int8 x int4 example).
+// int8 x int8  4096 x 14336 191 rows 39 / 29; 2048 x 14336 1002 rows 55 / 76; 4096 x 9216 214 rows 40 / 29, 516 rows 46 / 56; 6144 x 4096 300 rows 21.9 / 24.8
+// int8 x int4  4096 x 14336 300 rows 39 / 47; 2304 x 9216 300 rows 28.5 / 20.7, 814 rows 30.5 / 41.7; 6144 x 4096 300 rows 17.5 / 20.0
 static float skinny_us(const Geometry &g, int M, bool int8_activations, bool gated, int num_cus) {
     SkinnyArgs a = make_args(g, nullptr, nullptr, nullptr, M, nullptr, nullptr, gated ? 0 : -1);
     choose_blocks(a, g.fmt, int8_activations, num_cus);
@@ -834,7 +832,7 @@ bool skinny_product(const Geometry &g, int M, bool int8_activations, bool gated,
         return here < fmaxf((M <= 16 ? 1.1f : 1.05f) * tiles, tiles + 0.5f);
     }
     const float here = skinny_us(g, M, int8_activations, gated, num_cus);
-    const long n256 = (g.N + 255) / 256, m128 = (M + 127) / 128;
+    const long m128 = (M + 127) / 128;
     if (!int8_activations) {
         // Up to eight wavefronts share the steps here, and the time is that of the one with most (4096 x 14432, 113 steps: 7 % more than
         // 4096 x 14336).  The choice is 0.2 % slower than the faster of both over 319 shapes of 1500 to 65536 channels, K of 1024 to 14432
@@ -853,10 +851,10 @@ bool skinny_product(const Geometry &g, int M, bool int8_activations, bool gated,
         const float fill = (float)((g.N + 127) / 128 * m128) / (float)num_cus;
         return here < 1.04f * (3.5f + 9.3f * k) * (fill <= 1.0f ? 1.0f : 0.12f + ceilf(0.5f * fill));
     }
-    const bool large = 4 * n256 * m128 >= 3L * num_cus || n256 * ((M + 63) / 64) > num_cus;  // tiles of 128 tokens, or two rounds of 64
-    const float tiles = large ? (w8 ? 6.5f + 5.8f * k : 6.0f + 5.2f * k) * fmaxf(1.0f, 1.1f * (float)(n256 * m128) / (float)num_cus)
-                              : (w8 ? 4.5f + 4.85f * k : 4.8f + 4.1f * k);
-    return here < 1.05f * tiles;
+    // (skinny_us put to measured times over 200 shapes of 65 to 1024 rows, standard deviation 9 to 11 %; the choice is 0.4 % slower than the
+    // faster of both.  0.95: where they are level, the tiles)
+    int form;
+    return (w8 ? 5.05f + 0.774f * here : 4.47f + 0.823f * here) < 0.95f * int8_tile_us(g, M, g.N % 8 == 0, num_cus, &form);
 }
 
 hipError_t launch_skinny_f16(const Geometry &g, const void *packed, const void *x, int M, void *y, const void *residual,

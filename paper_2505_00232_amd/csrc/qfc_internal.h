@@ -382,6 +382,8 @@ hipError_t launch_retile_xq(const int8_t *xq, int M, int K, int8_t *tiled, int M
 hipError_t launch_gemm_i8(const Geometry &g, const void *packed, const int8_t *xq_tiled,
                           const float *sx, int M, int Mp, void *out, int out_mode, const void *residual,
                           int gated_act, int num_cus, hipStream_t st);
+// Estimated time of the tiles for int8 activations (gemm_i8.hip) in us and the number of the form they are fastest in.
+float int8_tile_us(const Geometry &g, int M, bool staged_store, int num_cus, int *form);
 // Returns hipErrorNotSupported for a gated output when K is not a multiple of 128.
 hipError_t launch_gemm_f16(const Geometry &g, const void *packed, const void *x, int M, void *y,
                            const void *residual, int gated_act, int num_cus, hipStream_t st);

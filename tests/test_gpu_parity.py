@@ -403,6 +403,39 @@ def test_int8_prefill_int4_weights_tile_shapes_bit_exact(variant):
     layer.close()
 
 
+@pytest.mark.parametrize("fmt,variant,M,N,K", [
+    # two parts of K: the fewest stages, one pair of stages more in the first part, many; ragged channels and token rows, rows stored value by value,
+    # one token tile and more of them than share the prefetch
+    ("w8c", 13, 131, 600, 512), ("w8c", 13, 300, 523, 768), ("w8c", 13, 65, 129, 6144), ("w8c", 13, 2200, 136, 1280), ("w8c", 14, 131, 600, 512),
+    ("w8c", 14, 64, 257, 768), ("w8c", 14, 300, 520, 2304), ("w8c", 14, 1100, 136, 1280), ("w8c", 10, 1930, 257, 768),
+    ("w4c", 24, 131, 600, 512), ("w4c", 24, 64, 257, 768), ("w4c", 24, 300, 523, 2304), ("w4c", 24, 65, 520, 5632),
+    # four parts: one, two and three of them with a pair of stages more
+    ("w4c", 25, 131, 600, 1024), ("w4c", 25, 300, 129, 1280), ("w4c", 25, 65, 523, 1536), ("w4c", 25, 64, 129, 1792), ("w4c", 25, 300, 520, 5120)])
+def test_int8_tiles_parts_of_k_bit_exact(fmt, variant, M, N, K):
+    """The tiles whose groups of wavefronts each take a part of K: sums handed over through LDS, bit for bit, three times (warm
+    caches); with a residual."""
+    print(f"int8 tiles, K in parts, {fmt} variant {variant} M={M} N={N} K={K}", flush=True)
+    wq, sw = synth.weights(4670, M, K, synth.FC("t", K, N, fmt))
+    x = synth.activations(4670, M, K, M, K)
+    xq_ref, sx_ref, acc_ref, y_ref = oracle.fc_int8_act(x, wq, sw)
+    res = synth.activations(4671, M, N, M, N)
+    layer = _layer(wq, sw, fmt, max_m=M, mode=binding.QFC_COMPUTE_INT8_ACT)
+    binding.qfc_tune(2, variant)
+    try:
+        for rep in range(3):
+            acc = torch.full((M, N), -1, dtype=torch.int32, device=DEV)
+            binding.qfc_forward_acc_i32(layer.handle, torch.from_numpy(xq_ref).to(DEV), acc)
+            y = _forward(layer, x)
+            assert np.array_equal(acc.cpu().numpy().astype(np.int64), acc_ref), rep
+            assert _E(y, y_ref) <= TOL, rep
+        out = torch.empty((M, N), dtype=torch.float16, device=DEV)
+        binding.qfc_forward_fused(layer.handle, torch.from_numpy(x).to(DEV), out, residual=torch.from_numpy(res).to(DEV))
+        assert _E(out.cpu().numpy(), y_ref + res.astype(np.float64)) <= TOL
+    finally:
+        binding.qfc_tune(2, 0)
+    layer.close()
+
+
 @pytest.mark.parametrize("fmt,K", [("w4c", 256), ("w4c", 512), ("w4c", 768), ("w4c", 2304), ("w4c", 2560), ("w8c", 256), ("w8c", 512), ("w8c", 2400), ("w8c", 6144), ("w8c", 6400), ("w8c", 7168), ("w8c", 7392)])
 def test_int8_tiles_of_64_tokens_any_even_number_of_stages(fmt, K):
     """The 64-token tiles, which hold the weights of four stages of 128 k (int8 codes with K of less than 6144: of two): whole passes of four, two
