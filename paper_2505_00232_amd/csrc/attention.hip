@@ -941,6 +941,10 @@ int attn_splits(int G, int d, int n_ctx, int num_cus) {
     if (steps <= 4 || num_cus < 1) return 1;
     int s = num_cus / G;
     if (5L * G * s < 3L * num_cus) s = 2 * num_cus / G;
+    // more KV heads than compute units and a last round that is a third full or less: four walks each (us, one / four: 288 heads of 128, 900 positions
+    // 38.1 / 33.2, 1500 59.8 / 47.0; of 256, 3000 226 / 174; 320 of 64, 900 20.3 / 19.4; 528 of 128, 1500 91.6 / 81.1; from half a round on level or
+    // slower, 384 of 64 3000 60.5 / 56.9, 448 of 128 1500 66.2 / 68.9, and so are short walks, 288 of 256 400 37.8 / 41.8)
+    if (G > num_cus && G % num_cus > 0 && 20 * (G % num_cus) <= 7 * num_cus && steps >= 14) s = 4;
     if (s > 24 && s > steps / 2) s = steps / 2 > 24 ? steps / 2 : 24;
     if (s > steps) s = steps;
     if (s > kAttnMaxSplits) s = kAttnMaxSplits;

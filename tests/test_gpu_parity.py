@@ -1401,6 +1401,13 @@ def test_attention_over_the_cache(B, S, h_q, h_kv, d, C, n_ctx):
     assert _E(got.reshape(G * M, d), ref.reshape(G * M, d)) <= TOL
 
 
+# more KV heads than compute units: a last round of few workgroups (cut walks) and 13 steps, one fewer than that asks for
+@pytest.mark.parametrize("B,d,n_ctx", [(65, 64, 897), (65, 64, 832), (86, 128, 900)])
+def test_attention_many_heads_last_round_of_few(B, d, n_ctx):
+    test_attention_over_the_cache(B, 1, 4, 4, d, 960, n_ctx)
+
+
+
 @pytest.mark.parametrize("B,S,h_q,h_kv,d,C,n_ctx", [(1, 1, 4, 1, 64, 640, 577), (2, 1, 8, 2, 128, 704, 700), (1, 3, 4, 1, 256, 384, 321)])
 def test_attention_any_number_of_workgroups_per_head(B, S, h_q, h_kv, d, C, n_ctx):
     """The combination of 1 to 64 partial results (whole and broken groups of eight), workgroups with one step for
