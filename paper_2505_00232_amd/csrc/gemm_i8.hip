@@ -41,7 +41,7 @@ struct GemmI8Args {
     void *out;
     int M, N, Kp, n_tiles, m_tiles;
     int by_tokens;  // order of the tiles (see xcd_tile)
-    int share;      // token tiles that divide the prefetch of the weights among them
+    int share;      // by_tokens: token tiles on an XCD, which divide the early touch of the weights among them
     // 4-bit weights enter the MFMA as 16 q (the code's nibble in the top half of a byte): the sums are
     // 16 times the definition's, exactly; channel scales are multiplied by 1/16, raw sums shifted by 4
     float sw_mul = 1.0f;
@@ -555,7 +555,9 @@ __global__ __launch_bounds__(CG * KS * 64, 2) void gemm_i8_dw_kernel(GemmI8Args 
 
     // the touch of the weights of a stage far ahead (PF): of the 128-byte lines of the wavefront's row tiles, those that fall to this token tile
     constexpr int PFN = PF ? 1 : 0, kLines = 32 * WV;
-    const int per = (kLines + a.share - 1) / a.share, pidx = min((mt % a.share) * per + lane % per, kLines - 1);
+    const int band = a.by_tokens ? 0 : mt / kBand * kBand;  // token tiles that walk the same weights on this XCD, and which of them this is
+    const int share = a.by_tokens ? a.share : min(kBand, a.m_tiles - band), mine = a.by_tokens ? mt % share : mt - band;
+    const int per = (kLines + share - 1) / share, pidx = min(mine * per + lane % per, kLines - 1);
     const uint32_t poff = (uint32_t)((pidx / (8 * WV)) * all * WV * 1024 + (pidx % (8 * WV)) * 128);
     constexpr int kPrefetch = NS - 1 + PW;
     auto prefetch = [&](int kt, const bool bulk) __attribute__((always_inline)) {
@@ -736,7 +738,8 @@ hipError_t launch_dw(GemmI8Args a, hipStream_t st) {
     a.n_tiles = (a.N + 64 * CG - 1) / (64 * CG);
     a.m_tiles = (a.M + 32 * TM - 1) / (32 * TM);
     a.by_tokens = walk_by_tokens(a.n_tiles, a.m_tiles, (W4 ? 32.0f : 64.0f) * CG, 32.0f * TM);
-    a.share = a.m_tiles < 16 ? a.m_tiles : 16;
+    const int width = a.n_tiles < kBand ? a.n_tiles : kBand, per_xcd = (a.n_tiles * a.m_tiles + 7) / 8;
+    a.share = min((per_xcd + width - 1) / width, min(a.m_tiles, 16));
     gemm_i8_dw_kernel<W4, NS, PW, TM, CG, KS, PF, OUT_MODE><<<dim3((unsigned)(a.n_tiles * a.m_tiles)), CG * KS * 64, lds_bytes, st>>>(a);
     return hipGetLastError();
 }
@@ -777,15 +780,20 @@ bool parts_fit(int Kp, int parts) { return Kp / 128 >= 2 * parts; }
 
 // The kernel is chosen by size (int8_tile_us), or by number for tests: 4, 10, 12, 13, 14 (int8 weights), 20, 21, 23, 24, 25 (int4).  A number that
 // names none of the call's kernels leaves the choice.
-// Tiles of 256 x 128 ask for weights ahead of their loads from 16 token tiles on (us without / with: 28672 x 4096 4096 rows 446 / 424, 2304 x 9216 2048
-// rows 71.4 / 65.3, 6144 x 4096 2048 rows 61.0 / 59.9; with fewer tiles, a larger share each, 28672 x 4096 1024 rows 114.1 / 116.3, 11808 x 9216 863 rows 6 % slower).
+// Tiles of 256 x 128 touch their weights early where one round of them leaves latency to hide and a band of token tiles shares the work (us without / with:
+// 2304 x 9216 2048 rows 71.4 / 65.3, 3000 rows 74.6 / 72.5, 2048 x 7168 3438 rows 6 % faster; a second round, 2304 x 9216 4096 rows 122 / 129; few token tiles, 9728 x
+// 10240 423 rows 4 % slower).
 template <int OUT_MODE>
-hipError_t launch_mode(const GemmI8Args &a, int chosen, hipStream_t st) {
+hipError_t launch_mode(const GemmI8Args &a, int chosen, int num_cus, hipStream_t st) {
     int variant = tuning().gemm_variant;
     if (variant != 4 && variant != 10 && variant != 12 && ((variant != 13 && variant != 14) || !parts_fit(a.Kp, 2))) variant = chosen;
     switch (variant) {
         case 4: return launch_staged<128, 128, 3, OUT_MODE>(a, st);
-        case 10: return a.M > 15 * 128 ? launch_dw<false, 4, 2, 4, 4, 1, true, OUT_MODE>(a, st) : launch_dw<false, 4, 2, 4, 4, 1, false, OUT_MODE>(a, st);
+        case 10: {
+            const long n_tiles = (a.N + 255) / 256, m_tiles = (a.M + 127) / 128;
+            return m_tiles >= kBand && n_tiles * m_tiles <= num_cus ? launch_dw<false, 4, 2, 4, 4, 1, true, OUT_MODE>(a, st)
+                                                                    : launch_dw<false, 4, 2, 4, 4, 1, false, OUT_MODE>(a, st);
+        }
         case 13: return launch_dw<false, 4, 2, 4, 2, 2, true, OUT_MODE>(a, st);
         case 14: return launch_dw<false, 4, 2, 2, 2, 2, true, OUT_MODE>(a, st);
     }
@@ -810,9 +818,9 @@ hipError_t launch_mode_w4(const GemmI8Args &a, int chosen, hipStream_t st) {
 
 // Estimated time of the direct-weights kernel (with the quantization of the rows, but for what of it grows with the rows) and the form that it is fastest
 // in, by its number.  A tile takes `each` us and K / 1000 times `alone` on a compute unit of its own, `shared` where several are in flight; of a last
-// round that is not full, the part that grows with K takes at least the share `idle` of a full one's.  Fitted to 290 shapes of 768 to 28672 channels, K of 256 to
-// 14336 and 65 to 4096 rows; the choice is 0.25 % slower than the fastest of the four forms, with int8 weights 1.16 times at worst (20128 x 5632 175
-// rows), int4 1.07.  us, 256 x 128 / 256 x 64 / in parts of K 128 x 128 / 128 x 64, int8 weights: 4096 x 14336 1024 rows 98 / 87 / 68 / 87, 512 rows 96 / 82 / 64 /
+// round that is not full, the part that grows with K takes at least the share `idle` of a full one's.  Fitted to 350 shapes of 768 to 128256 channels, K of 256 to
+// 14336 and 65 to 4096 rows; the choice is 0.05 % (int4 weights 0.25 %) slower than the fastest of the four forms, 1.03 times at worst (int4 32000 x 4096 130
+// rows 1.1).  us, 256 x 128 / 256 x 64 / in parts of K 128 x 128 / 128 x 64, int8 weights: 4096 x 14336 1024 rows 98 / 87 / 68 / 87, 512 rows 96 / 82 / 64 /
 // 55, 2048 rows 110 / 156 / 133 / 171; 2304 x 9216 990 rows 65 / 57 / 45 / 51; 6144 x 4096 1024 rows 34.0 / 45.5 / 44.5 / 42.1; int4 (256 x 128 / 256 x 64 /
 // 128 x 64 in two / in four parts): 2304 x 9216 814 rows 59 / 40 / 32.4 / 30.5, 4096 x 4096 512 rows 31 / 21.9 / 17.7 / 19.0.
 // Outputs that are stored as they lie in the registers (accumulators; rows that are no multiple of 16 bytes) cost tiles of 256 x 128 about 4 us
@@ -822,15 +830,17 @@ float int8_tile_us(const Geometry &g, int M, bool staged_store, int num_cus, int
         int number, channels, tokens, parts;
         float start, each, alone, shared, idle;
     };
-    static const Fit fits[2][4] = {{{10, 256, 128, 1, 3.58f, 4.74f, 7.78f, 5.94f, 0.75f}, {12, 256, 64, 1, 3.88f, 2.73f, 6.21f, 4.43f, 0.81f},
-                                    {13, 128, 128, 2, 2.58f, 6.57f, 4.40f, 3.88f, 0.95f}, {14, 128, 64, 2, 5.34f, 1.75f, 3.68f, 2.85f, 0.94f}},
-                                   {{21, 256, 128, 1, 5.69f, 2.80f, 6.72f, 5.43f, 0.75f}, {23, 256, 64, 1, 5.23f, 2.18f, 4.00f, 3.27f, 0.79f},
-                                    {24, 128, 64, 2, 5.03f, 1.77f, 2.82f, 2.08f, 0.77f}, {25, 128, 64, 4, 3.33f, 4.96f, 2.50f, 2.15f, 0.78f}}};
+    static const Fit fits[2][4] = {{{10, 256, 128, 1, 6.29f, 2.14f, 8.47f, 7.07f, 0.67f}, {12, 256, 64, 1, 4.08f, 2.60f, 6.65f, 4.76f, 0.73f},
+                                    {13, 128, 128, 2, 2.86f, 6.40f, 4.49f, 4.10f, 0.79f}, {14, 128, 64, 2, 5.75f, 1.57f, 3.72f, 3.10f, 0.89f}},
+                                   {{21, 256, 128, 1, 6.06f, 2.51f, 6.66f, 5.52f, 0.75f}, {23, 256, 64, 1, 5.37f, 2.15f, 4.18f, 3.35f, 0.74f},
+                                    {24, 128, 64, 2, 5.26f, 1.73f, 2.79f, 2.10f, 0.76f}, {25, 128, 64, 4, 3.45f, 5.06f, 2.46f, 2.18f, 0.78f}}};
     const float k = 1e-3f * (float)g.Kp;
     float best = 0.0f;
     *form = 0;
     for (const Fit &f : fits[g.fmt == kW4C]) {
         if (f.parts > 1 && !parts_fit(g.Kp, f.parts)) continue;
+        // (one token tile: nobody to share the touch of the weights with; 28672 x 4096 66 rows 44.6, the others 36.4 and 40.3)
+        if (f.number == 13 && M <= f.tokens) continue;
         const int tiles = (g.N + f.channels - 1) / f.channels * ((M + f.tokens - 1) / f.tokens), full = tiles / num_cus, rest = tiles % num_cus;
         auto work = [&](int n) { return n == 0 ? 0.0f : n == 1 ? f.alone * k : (float)n * f.shared * k; };  // of a compute unit with n tiles
         float us = f.start + (float)full * f.each + work(full);
@@ -865,7 +875,7 @@ hipError_t launch_gemm_i8(const Geometry &g, const void *packed, const int8_t *x
         a.acc_shift = 4;
         return out_mode == 0 ? launch_mode_w4<0>(a, form, st) : launch_mode_w4<1>(a, form, st);
     }
-    return out_mode == 0 ? launch_mode<0>(a, form, st) : launch_mode<1>(a, form, st);
+    return out_mode == 0 ? launch_mode<0>(a, form, num_cus, st) : launch_mode<1>(a, form, num_cus, st);
 }
 
 }  // namespace qfc

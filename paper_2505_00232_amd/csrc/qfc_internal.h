@@ -44,6 +44,7 @@
 #include <atomic>
 
 #include "../../include/qfc.h"
+#include "tile_order.h"
 
 namespace qfc {
 
@@ -202,31 +203,6 @@ __device__ __forceinline__ void copy16_to_lds(const void *base, uint32_t lane_of
 __device__ __forceinline__ void copy16_to_lds_at(const void *base, uint32_t lane_offset, uint32_t lds_base, int constant) {
     asm volatile("s_add_u32 m0, %2, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(lane_offset), "s"(base), "s"(lds_base), "i"(constant)
                  : "memory", "m0", "scc");
-}
-
-// Tile of workgroup `b` of a product, in an order whose neighbours run on one XCD (workgroups are dealt to the 8
-// XCDs round robin, each with its own L2): XCD x takes the x-th eighth of the tiles, the first total % 8
-// XCDs one more, channel tile by channel tile or (by_tokens) token tile by token tile.
-// (Tile counts that 8 does not divide: int8 x int8, 9216 x 4096 at 400 rows 46.7 us in launch order, 27.3 like
-// this; 4352 x 4096 at 900 rows 31.3 / 21.3; int8 x int4 9472 x 4096 at 400 rows 34.7 / 27.6; the fp16 kernels are level.)
-__device__ __forceinline__ void xcd_tile(int b, int n_tiles, int m_tiles, int by_tokens, int &nt, int &mt) {
-    const int total = n_tiles * m_tiles, xcd = b % 8;
-    const int i = xcd * (total / 8) + min(xcd, total % 8) + b / 8;
-    const int inner = by_tokens ? n_tiles : m_tiles, o = i / inner, r = i % inner;
-    nt = by_tokens ? r : o;
-    mt = by_tokens ? o : r;
-}
-// The order for which an XCD pulls fewer bytes: its eighth of the tiles covers all tiles of one operand
-// and a few of the other.  (w_bytes, x_bytes: of a channel tile and of a token tile, per k.  Always by channels /
-// like this: 4096 x 14336 int4, binary16 activations, 6000 rows 595 / 567 us, int8 activations 277 / 269; 2304 x 9216 int4
-// groups, 6000 rows 259 / 247; 703 x 12576, 2048 rows 170 / 160.)
-inline int walk_by_tokens(int n_tiles, int m_tiles, float w_bytes, float x_bytes) {
-    const int share = (n_tiles * m_tiles + 7) / 8;
-    auto covered = [&](int inner, int outer, float inner_bytes, float outer_bytes) {
-        const int across = (share + inner - 1) / inner;
-        return (float)(share < inner ? share : inner) * inner_bytes + (float)(across < outer ? across : outer) * outer_bytes;
-    };
-    return covered(n_tiles, m_tiles, w_bytes, x_bytes) < covered(m_tiles, n_tiles, x_bytes, w_bytes) ? 1 : 0;
 }
 
 // ---- per-token int8 quantization steps shared by the kernels that produce quantized activations

@@ -224,6 +224,38 @@ int main() {
     assert r.returncode == 0, r.stdout[-2000:]
 
 
+def test_tile_order_covers_every_tile_once(tmp_path):
+    """The walk over the tiles of a product: every tile once, for grids of one tile to several bands in both directions, the last band
+    of any width and any remainder over the XCDs; and an XCD's neighbours stay within one band, or two where its share crosses over."""
+    src, exe = tmp_path / "order.cpp", str(tmp_path / "order")
+    src.write_text("""#include "tile_order.h"
+#include <cstdio>
+#include <vector>
+int main() {
+    for (int by_tokens = 0; by_tokens < 2; ++by_tokens)
+        for (int n = 1; n <= 40; ++n)
+            for (int m = 1; m <= 40; ++m) {
+                std::vector<int> seen(n * m, 0);
+                for (int b = 0; b < n * m; ++b) {
+                    int nt = -1, mt = -1;
+                    qfc::xcd_tile(b, n, m, by_tokens, nt, mt);
+                    if (nt < 0 || nt >= n || mt < 0 || mt >= m || seen[nt * m + mt]++) return printf("%d x %d by_tokens %d: %d -> %d %d\\n", n, m, by_tokens, b, nt, mt), 1;
+                    if (b >= 8) {
+                        int n0, m0;
+                        qfc::xcd_tile(b - 8, n, m, by_tokens, n0, m0);
+                        const int band = (by_tokens ? nt : mt) / qfc::kBand - (by_tokens ? n0 : m0) / qfc::kBand;
+                        if (band < 0 || band > 1) return printf("%d x %d by_tokens %d: band %d\\n", n, m, by_tokens, band), 1;
+                    }
+                }
+            }
+    return 0;
+}
+""")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-D__host__=", "-D__device__=", "-D__forceinline__=inline", "-I", build.CSRC, str(src), "-o", exe], check=True)
+    r = subprocess.run([exe], capture_output=True, text=True)
+    assert r.returncode == 0, r.stdout[-2000:]
+
+
 # What the dispatch chooses on 256 compute units.  Binary16 activations: format (0 int8, 1 int4 in groups, 2 int4), channels, K, token rows,
 # rows left to the token-row kernels in a second launch (-1: they take them all)
 CHOICES = [
