@@ -13,6 +13,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libqfc.so")
+MARSHAL = os.path.join(HERE, "_marshal.so")
 SOURCES = ["api.hip", "pack.hip", "gemv.hip", "gemv_q8.hip", "actquant.hip", "rmsnorm.hip", "attention.hip", "gemm_i8.hip", "gemm_f16.hip", "gemm_skinny.hip", "probe.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function",
          # packed-fp32 code generation is switched off on purpose
@@ -66,8 +67,22 @@ def _deps_newer(target: str) -> bool:
     return any(os.path.getmtime(d) > t for d in _deps())
 
 
+def _build_marshal() -> None:
+    """The host module behind the binding's most frequent calls, against torch's own headers (no device code)."""
+    import sysconfig
+
+    import torch
+    root = os.path.dirname(torch.__file__)
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           *(f"-I{d}" for d in (f"{root}/include", f"{root}/include/torch/csrc/api/include", sysconfig.get_paths()["include"])),
+           os.path.join(CSRC, "marshal.cpp"), "-o", MARSHAL, f"-L{root}/lib", "-ltorch_python", "-ltorch_cpu", "-lc10", f"-Wl,-rpath,{root}/lib"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError("g++ failed on marshal.cpp:\n" + r.stderr)
+
+
 def build(force: bool = False, verbose: bool = False) -> str:
-    if not force and not _deps_newer(LIB):
+    if not force and not _deps_newer(LIB) and not _deps_newer(MARSHAL):
         return LIB
     os.makedirs(OBJ, exist_ok=True)
     cc = _hipcc()
@@ -92,7 +107,9 @@ def build(force: bool = False, verbose: bool = False) -> str:
         return obj
 
     with ThreadPoolExecutor(max_workers=7) as ex:
+        marshal = ex.submit(_build_marshal)
         objs = list(ex.map(compile_one, SOURCES))
+        marshal.result()
     r = subprocess.run([cc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs],
                        capture_output=True, text=True)
     if r.returncode != 0:

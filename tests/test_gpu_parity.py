@@ -2258,3 +2258,46 @@ def test_rope_qkv_infinite_values():
         odd = ~np.isfinite(ref)
         assert odd.any() and np.array_equal(np.isnan(got), np.isnan(ref))
         assert np.array_equal(got[odd & ~np.isnan(ref)], ref[odd & ~np.isnan(ref)])
+
+
+def test_native_marshalling_takes_what_the_binding_takes(monkeypatch):
+    """The calls that csrc/marshal.cpp lets through give the bits of the other way, and what is not in order is refused alike by both:
+    other types, devices, shapes, strides, no rows; subclasses and parameters are taken by both."""
+    class Sub(torch.Tensor):
+        pass
+
+    N, K, M = 64, 96, 3
+    wq, sw = synth.weights(5200, 0, 0, synth.FC("t", K, N, "w8c"))
+    layer = _layer(wq, sw, "w8c")
+    x = torch.from_numpy(synth.activations(5200, 0, 0, M, K)).to(DEV)
+    res = torch.from_numpy(synth.activations(5201, 0, 0, M, N)).to(DEV)
+    gamma = torch.ones(K, dtype=torch.float16, device=DEV)
+    binding.lib()
+    outs = []
+    for fast in (binding._fast, None):
+        monkeypatch.setattr(binding, "_fast", fast)
+        for xx in (x, x.as_subclass(Sub), torch.nn.Parameter(x, requires_grad=False)):
+            y, z = (torch.empty((M, N), dtype=torch.float16, device=DEV) for _ in range(2))
+            binding.qfc_forward(layer.handle, xx, y)
+            binding.qfc_forward_fused(layer.handle, xx, z, residual=res, norm_gamma=gamma, norm_eps=1e-5, norm_offset=1)
+            outs.append(torch.stack([y, z]))
+        y = torch.empty((M, N), dtype=torch.float16, device=DEV)
+        wide = torch.zeros((M, 2 * K), dtype=torch.float16, device=DEV)
+        for bad in (x.float(), x.cpu(), x[:, :32], wide[:, ::2], x[0], None, x.view(M, K, 1)):
+            with pytest.raises(ValueError):
+                binding.qfc_forward(layer.handle, bad, y)
+            with pytest.raises(ValueError):
+                binding.qfc_forward_fused(layer.handle, bad, y, residual=res)
+        for kw in (dict(residual=res[:2]), dict(residual=res.float()), dict(norm_gamma=gamma[:32]), dict(gate=res)):
+            with pytest.raises(ValueError):
+                binding.qfc_forward_fused(layer.handle, x, y, **kw)
+        with pytest.raises(ValueError):
+            binding.qfc_forward(layer.handle, x, y[:2])
+        with pytest.raises(binding.QfcError):
+            binding.qfc_forward(layer.handle, x[:0], y[:0])
+        with pytest.raises(binding.QfcError):  # 2 bytes off the 16 that the library asks for
+            off = torch.zeros(M * K + 1, dtype=torch.float16, device=DEV)[1:].view(M, K)
+            binding.qfc_forward(layer.handle, off, y)
+    torch.cuda.synchronize()
+    assert all(torch.equal(o, outs[0]) for o in outs[1:])
+    layer.close()
