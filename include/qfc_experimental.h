@@ -26,9 +26,10 @@ extern "C" {
  *   key 1  most row tiles a decode workgroup walks (0 = automatic: 2 up to two token rows, 4 above)
  *   key 2  prefill kernel by number (0 = automatic).  Binary16 activations: 9 the kernel for any K, 31 .. 37 the forms of the main
  *          kernel: 32, 64, 96, 128 token rows per workgroup, and, for K of 256 and more, 128, 64 and 96 with K in two halves.  int8
- *          activations: int8 weights 4 both operands staged, 10 and 12 weights straight into registers with 128 and 64 token rows
- *          per workgroup; int4 weights 20, 21 and 23 the same.  Any number but 0 leaves out the kernels for few token rows; one that
- *          names no kernel of the call's formats and size leaves the choice among the others
+ *          activations: int8 weights 4 both operands staged, 10 and 12 weights straight into registers with 128 and 64 token rows and 256
+ *          channels per workgroup, 13 and 14 the same with 128 channels and K in two parts; int4 weights 20, 21 and 23 as 4, 10 and 12, 24
+ *          and 25 128 channels and 64 token rows with K in two and four parts.  Any number but 0 leaves out the kernels for few token
+ *          rows; one that names no kernel of the call's formats and size leaves the choice among the others
  *   key 3  token rows per workgroup of the activation quantization kernel (0 = automatic; 2, 4, 8)
  *   key 4  half-unit items of the decode kernel (-1 automatic, 0 never, 1 where possible)
  *   key 5  (without effect)

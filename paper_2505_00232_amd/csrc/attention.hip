@@ -85,9 +85,9 @@ __global__ __launch_bounds__(256) void rope_qkv_few_kernel(const _Float16 *__res
 // more than everything else together when every head of a token evaluates them (S = 1024, 40 heads to
 // rotate: 34 us; 6000: 165 us, where reading and writing 147 MB takes 28).  So a workgroup takes T
 // tokens, evaluates their d / 2 angles once into LDS, and rotates all heads with them, 16 bytes of each half
-// of a head per thread.  The rotation itself is done in pairs of fp32 (rotate_pair): with fp64 products, whose conversions and
-// operations kept the vector unit busy for half of the time, the same kernel takes, us, fp64 / fp32 pairs: 1024 tokens of 48 heads of 128
-// 11.8 / 5.7, 6000 42.3 / 19.5 (a copy of the same bytes 19.0), 2048 tokens of 16 heads of 256 14.2 / 7.6, 300 tokens of 48 heads of 128 6.8 / 4.0.
+// of a head per thread.  The rotation itself is done in pairs of fp32 that carry all rounding errors (sum_of_products): with fp64 products, whose
+// conversions and operations kept the vector unit busy for half of the time, the same kernel takes, us, fp64 / fp32 pairs: 1024 tokens of 48 heads of 128
+// 11.8 / 9.2, 6000 42.3 / 34.4, 2048 tokens of 16 heads of 256 14.2 / 11.0.  The results are the same bits (35 million values of five shapes).
 // Few tokens: the heads are split over several workgroups.
 // Values: a workgroup takes the tokens of one block of 64 cache positions of one head, turns them in LDS and
 // writes runs of up to 128 bytes of the transposed cache instead of single values 128 bytes apart.
@@ -97,16 +97,23 @@ __device__ __forceinline__ float2 split_f64(double v) {
     const float hi = (float)v;
     return make_float2(hi, (float)(v - (double)hi));
 }
-// x0 cos - x1 sin and x1 cos + x0 sin, cos = (t.x, t.y), sin = (t.z, t.w): the product that a fused multiply-add rounds is taken again for its
-// error (difference of products after Kahan), so that cancellation costs nothing and the result is within a unit in the last
-// place of fp32.  An infinite x makes the correction NaN: then the plain result stands, as it does in fp64.
+// x0 c + x1 s, c = (c.x, c.y) and s likewise: both products with their rounding errors (fma), their sum with its own (Knuth's
+// two-sum); what the last sum rounds off decides its lowest bit (rounding to odd), so that the conversion to binary16 rounds the real
+// result once, ties included: the bits that fp64 gives.  An infinite x makes the corrections NaN: then
+// the plain sum stands, as it does in fp64.
+__device__ __forceinline__ float sum_of_products(float x0, float2 c, float x1, float2 s) {
+#pragma clang fp contract(off)  // (the two-sum needs its own roundings)
+    const float p = x0 * c.x, q = x1 * s.x, sum = p + q, of_q = sum - p;
+    const float rest = ((p - (sum - of_q)) + (q - of_q)) + (fmaf(x0, c.x, -p) + fmaf(x1, s.x, -q));
+    const float low = fmaf(x0, c.y, fmaf(x1, s.y, rest)), r = sum + low, off = low - (r - sum);
+    const int bits = __float_as_int(r), odd = (bits - ((__float_as_int(off) ^ bits) < 0 ? 1 : 0)) | 1;
+    return r == r ? (off != 0.0f ? __int_as_float(odd) : r) : sum;
+}
+// x0 cos - x1 sin and x1 cos + x0 sin, cos = (t.x, t.y), sin = (t.z, t.w)
 __device__ __forceinline__ void rotate_pair(float x0, float x1, const float4 &t, float &y0, float &y1) {
-    const float w0 = x1 * t.z, w1 = x1 * t.x;
-    const float f0 = fmaf(x0, t.x, -w0), f1 = fmaf(x0, t.z, w1);
-    const float r0 = f0 + fmaf(x0, t.y, fmaf(-x1, t.w, fmaf(-x1, t.z, w0)));
-    const float r1 = f1 + fmaf(x0, t.w, fmaf(x1, t.y, fmaf(x1, t.x, -w1)));
-    y0 = r0 == r0 ? r0 : f0;
-    y1 = r1 == r1 ? r1 : f1;
+    const float2 c = make_float2(t.x, t.y), s = make_float2(t.z, t.w);
+    y0 = sum_of_products(x0, c, -x1, s);
+    y1 = sum_of_products(x1, c, x0, s);
 }
 struct RopeArgs {
     const _Float16 *qkv;
@@ -1047,11 +1054,10 @@ size_t attn_prefill_workspace(int G, int M, int d, int num_cus) {
 hipError_t launch_rope_qkv(const void *qkv, int B, int S, int h_q, int h_kv, int d, int C, int pos0, float base,
                            void *q_out, void *kc, void *vc, hipStream_t st) {
     const long total = (long)B * S;
-    // Few values, and batches of few tokens each (whose values go to the cache one by one anyway): a workgroup that shares the angles
-    // of a token has little else to do (us, this kernel / the other, tokens x heads x values: 400 x 3 x 64 3.1 / 4.3, 17 x 48 x 128 2.9 / 3.7,
-    // 40 x 48 x 128 3.3 / 3.7, 64 sequences of one token x 48 x 128 4.5 / 4.8; 60 x 16 x 256 3.35 / 3.2, 77 x 16 x 256 3.9 / 3.2, 64 x 48 x 128
-    // 3.9 / 3.7, 540 x 8 x 64 4.0 / 3.5, 200 x 48 x 64 5.2 / 3.2; 2000 x 3 x 64 4.4 / 4.6)
-    if (total * (h_q + 2 * h_kv) * d < (240L << 10) || (S < 32 && total < 128)) {
+    // Few tokens, and more of them where their heads are few: a workgroup that shares the angles of a token has little else
+    // to do (us, this kernel / the other, tokens x heads x values: 77 x 16 x 256 3.9 / 4.25, 2000 x 3 x 64 4.4 / 5.7; 300 x 48 x 128 11.4 / 6.5; drawn
+    // with the rotation in fp64: 328 x 6 x 128 4.5 / 5.0, 200 x 16 x 128 5.1 / 4.9, 200 x 48 x 64 5.7 / 5.0)
+    if (total < 128 || total * (h_q + 2 * h_kv) * d < (400L << 10)) {
         const long pairs = total * (h_q + 2 * h_kv) * (d / 2);
         rope_qkv_few_kernel<<<(unsigned)((pairs + 255) / 256), 256, 0, st>>>(
             static_cast<const _Float16 *>(qkv), B, S, h_q, h_kv, d, C, pos0, log((double)base),
@@ -1066,8 +1072,8 @@ hipError_t launch_rope_qkv(const void *qkv, int B, int S, int h_q, int h_kv, int
     a.B = B, a.S = S, a.h_q = h_q, a.h_kv = h_kv, a.d = d, a.C = C, a.pos0 = pos0;
     a.log_base = log((double)base);
     // at most as many tokens per workgroup as one evaluation of an angle per thread covers; fewer, so that there are about four workgroups per
-    // compute unit (1024 tokens x 48 x 128, 1 / 2 / 4 tokens: 5.7 / 6.2 / 6.5 us), unless their heads are too few to keep the threads
-    // busy (2000 x 3 x 64, 1 / 2 / 8 tokens: 7.7 / 5.0 / 4.7)
+    // compute unit (1024 tokens x 48 x 128, 1 / 2 / 4 tokens: 9.2 / 10.3 / 12.7 us), unless their heads are too few to keep the threads
+    // busy (2000 x 3 x 64, 1 / 2 / 8 tokens: 9.9 / 6.1 / 5.7)
     const long most = 512 / d, busy = (256 + (h_q + h_kv) * (d / 16) - 1) / ((h_q + h_kv) * (d / 16));
     long T = busy < total / 256 ? busy : total / 256;
     if (T < total / 1024) T = total / 1024;

@@ -2229,9 +2229,10 @@ def test_rope_qkv_many_tokens(B, S, h_q, h_kv, d, C, pos0):
     test_rope_qkv_layout(B, S, h_q, h_kv, d, C, pos0)
 
 
-# the line at 240 Ki values (60 x 16 x 256 and one token fewer), sequences of 31 and 32 tokens, several tokens per workgroup for want of heads
-@pytest.mark.parametrize("B,S,h_q,h_kv,d,C,pos0", [(1, 59, 8, 4, 256, 128, 30), (1, 60, 8, 4, 256, 128, 30), (4, 31, 8, 4, 128, 64, 3),
-                                                   (4, 32, 16, 8, 128, 64, 3), (1, 2000, 1, 1, 64, 2048, 1), (1, 520, 4, 2, 64, 576, 50)])
+# the lines at 128 tokens and 400 Ki values, several tokens per workgroup for want of heads, one of 1023 and two of 2048
+@pytest.mark.parametrize("B,S,h_q,h_kv,d,C,pos0", [(1, 127, 8, 4, 256, 192, 30), (1, 128, 8, 4, 256, 192, 30), (4, 25, 32, 8, 128, 64, 3),
+                                                   (4, 32, 32, 8, 128, 64, 3), (1, 2134, 1, 1, 64, 2176, 1), (1, 1023, 4, 2, 64, 1088, 50),
+                                                   (1, 2048, 2, 1, 64, 2112, 50)])
 def test_rope_qkv_line_between_kernels(B, S, h_q, h_kv, d, C, pos0):
     test_rope_qkv_layout(B, S, h_q, h_kv, d, C, pos0)
 
