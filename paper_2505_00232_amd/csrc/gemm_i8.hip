@@ -22,6 +22,7 @@
 // on a contiguous range of (weight tile, token tile) pairs and the token tiles
 // that share a weight tile hit the same L2.
 #include "qfc_internal.h"
+#include "tile_waits.h"
 
 namespace qfc {
 namespace {
@@ -488,7 +489,8 @@ __global__ __launch_bounds__(256, 2) void gemm_i8_w4_kernel(GemmI8Args a) {
 // PIPE: the first operands of a stage are read during the MFMAs of the stage before, so its copies must have landed a stage
 // earlier.  For int8 weights in tiles of 64 tokens, which run where a compute unit has one of them: nothing else fills the time between the barrier
 // and the first MFMA.  With 4-bit weights the wait, which then covers more, costs more than it saves (540 x 9984 1434 rows 50.0 / 51.5 us, 4096 x
-// 4096 700 rows 25.5 / 26.1).
+// 4096 700 rows 25.5 / 26.1), and so it does in tiles of 64 tokens with K in two parts, whose ring of four stages would leave four operations
+// outstanding instead of eight (without / with: 4096 x 14336 512 rows 51.8 / 56.6 us, 4096 x 4096 300 rows 20.1 / 21.2, 2304 x 9216 300 rows 37.3 / 40.5).
 //
 // What bounds it: power on real data (see the MFMA rates above), then the operand paths; where the tiles leave most of the chip idle, the latency of a
 // stage.  us with the quantization kernel, 32 x 32 MFMAs (int8 weights: stages of
@@ -512,7 +514,7 @@ __global__ __launch_bounds__(CG * KS * 64, 2) void gemm_i8_dw_kernel(GemmI8Args 
     constexpr int XT = BM / 16 * 2;  // activation tiles (KiB) per stage
     constexpr int CP = XT / CG;      // copies per wavefront and stage
     constexpr int XJ = 2 * TM;   // blocks of 16 token rows
-    constexpr bool PIPE = !W4 && TM == 2;
+    constexpr bool PIPE = !W4 && TM == 2 && !PF;
     static_assert(NS >= 3 && (TM == 2 || TM == 4), "tile shapes");
     extern __shared__ uint4 lds[];  // NS stages of XT tiles x 64 vectors
     const int lane = threadIdx.x & 63;
@@ -562,7 +564,7 @@ __global__ __launch_bounds__(CG * KS * 64, 2) void gemm_i8_dw_kernel(GemmI8Args 
     constexpr int kPrefetch = NS - 1 + PW;
     auto prefetch = [&](int kt, const bool bulk) __attribute__((always_inline)) {
         if (!PF) return;
-        const int kc = bulk || kt < KT ? kt : KT - 1;
+        const int kc = bulk || kt < KT ? kt : min(kt - KT, KT - 1);
         asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dword %0, %1" ::"v"(poff), "s"(wsrc + (size_t)(WV * kc) * 64), "s"(lds0 + kSpare) : "memory", "m0");
     };
 
@@ -583,16 +585,10 @@ __global__ __launch_bounds__(CG * KS * 64, 2) void gemm_i8_dw_kernel(GemmI8Args 
         prefetch(PW + p, kEdge);
     }
 
-    // Waiting.  Copies into LDS and loads into registers share one counter (vmcnt) but do NOT complete
-    // in order relative to each other - only within their own kind (measured: with waits that assumed
-    // one common order, stages were read before their copies had landed).  At the top of iteration kt
-    // a wavefront has issued, after the copies of stage kt, the copies of NS - 2 later stages (CP each),
-    // and after the loads of stage kt the loads of PW - 1 later stages - from iteration 0 on,
-    // thanks to the prologue.  If at most kAllowed operations are outstanding, neither stage kt's copies nor its loads can be
-    // among them: an unfinished copy would have all later copies behind it, an unfinished load all later loads.  With PIPE it is stage kt + 1
-    // whose copies must have landed, which has one stage fewer behind it.
-    constexpr int kAfterCopies = (CP + PFN) * (NS - (PIPE ? 3 : 2)), kAfterLoads = 4 * WV * (PW - 1);
-    constexpr int kAllowed = kAfterCopies < kAfterLoads ? kAfterCopies : kAfterLoads;
+    // Waiting (see dw_waits).  At the top of iteration kt a wavefront has issued, after the copies of stage kt, the copies of NS - 2 later stages
+    // (CP each), and after the loads of stage kt the loads of PW - 1 later stages - from iteration 0 on, thanks to the prologue.  With PIPE it is
+    // stage kt + 1 whose copies must have landed, which has one stage fewer behind it.
+    constexpr DwWaits kWaits = dw_waits(CP, 4 * WV, NS, PW, PIPE);
     // (the most operations a wavefront ever has outstanding: right after the refills of an iteration)
     static_assert((CP + PFN) * (NS - 1) + 4 * WV * PW <= 63, "wait counts must fit the 6-bit counter");
 
@@ -601,7 +597,7 @@ __global__ __launch_bounds__(CG * KS * 64, 2) void gemm_i8_dw_kernel(GemmI8Args 
         fb[j] = __builtin_bit_cast(v4i, ring[(kt % NS) * (XT * 64) + (2 * j + ks) * 64 + lane]);
     };
     if (PIPE) {
-        wait_vmcnt<(CP + PFN) * (NS - 2)>();
+        wait_vmcnt<kWaits.first>();
         asm volatile("s_barrier" ::: "memory");
 #pragma unroll
         for (int j = 0; j < XJ; ++j) read_x(0, 0, j);
@@ -611,9 +607,9 @@ __global__ __launch_bounds__(CG * KS * 64, 2) void gemm_i8_dw_kernel(GemmI8Args 
         for (int u = 0; u < count; ++u) {
             const int kt = kt0 + u;
             if (PIPE)
-                asm volatile("s_waitcnt vmcnt(%0)" ::"n"(kAllowed) : "memory");  // (not the LDS counter: operand reads stay in flight)
+                asm volatile("s_waitcnt vmcnt(%0)" ::"n"(kWaits.allowed) : "memory");  // (not the LDS counter: operand reads stay in flight)
             else
-                wait_vmcnt<kAllowed>();
+                wait_vmcnt<kWaits.allowed>();
             asm volatile("s_barrier" ::: "memory");
 #pragma unroll
             for (int i = 0; i < TN; ++i)

@@ -256,6 +256,55 @@ int main() {
     assert r.returncode == 0, r.stdout[-2000:]
 
 
+def test_int8_tiles_wait_for_what_they_read(tmp_path):
+    """The operations that a wavefront of the direct-weights int8 tiles issues, for every instance in gemm_i8.hip and 2 to 24 stages: where it
+    goes on to read, even if loads, copies and touches of the weights each complete in order but in no order among them, no
+    operation that the stage needs can be among as many as may be outstanding."""
+    text = open(os.path.join(build.CSRC, "gemm_i8.hip")).read()
+    forms = re.findall(r"launch_dw<(true|false), (\d+), (\d+), (\d+), (\d+), \d+, (true|false), OUT_MODE>\(a, st\)", text)
+    assert len(forms) == text.count("launch_dw<") >= 10
+    src, exe = tmp_path / "waits.cpp", str(tmp_path / "waits")
+    src.write_text("""#include "tile_waits.h"
+#include <cstdio>
+#include <vector>
+enum Kind { kLoad, kCopy, kTouch };
+struct Op { Kind kind; int stage; };
+int main() {
+    for (int w4, NS, PW, TM, CG, touch; scanf("%d %d %d %d %d %d", &w4, &NS, &PW, &TM, &CG, &touch) == 6;) {
+        const int copies = 4 * TM / CG, loads = w4 ? 4 : 8;
+        const bool pipe = !w4 && TM == 2 && !touch;
+        const qfc::DwWaits waits = qfc::dw_waits(copies, loads, NS, PW, pipe);
+        for (int KT = 2; KT <= 24; KT += 2) {
+            std::vector<Op> issued;
+            auto issue = [&](Kind kind, int stage, int n) { while (n-- > 0) issued.push_back({kind, stage}); };
+            auto safe = [&](Kind kind, int stage, int allowed) {  // the fewest outstanding with any of the stage's operations among them
+                for (size_t i = 0; i < issued.size(); ++i) {
+                    if (issued[i].kind != kind || issued[i].stage != stage) continue;
+                    int outstanding = 0;
+                    for (size_t j = i; j < issued.size(); ++j) outstanding += issued[j].kind == kind;
+                    if (outstanding <= allowed) return printf("w4 %d NS %d PW %d TM %d CG %d touch %d, %d stages: kind %d of stage %d, %d of %d\\n", w4, NS, PW, TM, CG, touch, KT, kind, stage, outstanding, allowed), false;
+                }
+                return true;
+            };
+            for (int p = 0; p < PW; ++p) issue(kLoad, p, loads);
+            for (int p = 0; p < NS - 1; ++p) issue(kCopy, p, copies), issue(kTouch, PW + p, touch);
+            if (pipe && !safe(kCopy, 0, waits.first)) return 1;
+            for (int kt = 0; kt < KT; ++kt) {
+                if (!safe(kLoad, kt, waits.allowed) || !safe(kCopy, pipe ? kt + 1 : kt, waits.allowed)) return 1;
+                issue(kCopy, kt + NS - 1, copies), issue(kTouch, kt + NS - 1 + PW, touch);
+                issue(kLoad, kt + PW, loads);
+            }
+        }
+    }
+    return 0;
+}
+""")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-I", build.CSRC, str(src), "-o", exe], check=True)
+    asked = "\n".join(" ".join({"true": "1", "false": "0"}.get(v, v) for v in f) for f in forms)
+    r = subprocess.run([exe], input=asked, capture_output=True, text=True)
+    assert r.returncode == 0, r.stdout[-2000:]
+
+
 # What the dispatch chooses on 256 compute units.  Binary16 activations: format (0 int8, 1 int4 in groups, 2 int4), channels, K, token rows,
 # rows left to the token-row kernels in a second launch (-1: they take them all)
 CHOICES = [
