@@ -99,15 +99,15 @@ __device__ __forceinline__ float2 split_f64(double v) {
 }
 // x0 c + x1 s, c = (c.x, c.y) and s likewise: both products with their rounding errors (fma), their sum with its own (Knuth's
 // two-sum); what the last sum rounds off decides its lowest bit (rounding to odd), so that the conversion to binary16 rounds the real
-// result once, ties included: the bits that fp64 gives.  An infinite x makes the corrections NaN: then
-// the plain sum stands, as it does in fp64.
+// result once, ties included: the bits that fp64 gives.  Without a correction the plain sum stands: a zero keeps its sign, and an infinite x,
+// which makes the corrections NaN, gives what it gives in fp64.
 __device__ __forceinline__ float sum_of_products(float x0, float2 c, float x1, float2 s) {
 #pragma clang fp contract(off)  // (the two-sum needs its own roundings)
     const float p = x0 * c.x, q = x1 * s.x, sum = p + q, of_q = sum - p;
     const float rest = ((p - (sum - of_q)) + (q - of_q)) + (fmaf(x0, c.x, -p) + fmaf(x1, s.x, -q));
     const float low = fmaf(x0, c.y, fmaf(x1, s.y, rest)), r = sum + low, off = low - (r - sum);
     const int bits = __float_as_int(r), odd = (bits - ((__float_as_int(off) ^ bits) < 0 ? 1 : 0)) | 1;
-    return r == r ? (off != 0.0f ? __int_as_float(odd) : r) : sum;
+    return low < 0.0f || low > 0.0f ? (off != 0.0f ? __int_as_float(odd) : r) : sum;
 }
 // x0 cos - x1 sin and x1 cos + x0 sin, cos = (t.x, t.y), sin = (t.z, t.w)
 __device__ __forceinline__ void rotate_pair(float x0, float x1, const float4 &t, float &y0, float &y1) {

@@ -2261,6 +2261,38 @@ def test_rope_qkv_infinite_values():
         assert np.array_equal(got[odd & ~np.isnan(ref)], ref[odd & ~np.isnan(ref)])
 
 
+@pytest.mark.parametrize("S,h_q,h_kv,d,base", [(180, 16, 4, 128, 500000.0), (1100, 4, 2, 64, 10000.0), (140, 8, 4, 256, 1e6)])
+def test_rope_qkv_both_kernels_give_the_same_bits(S, h_q, h_kv, d, base):
+    """The kernel for many tokens, which rotates in pairs of fp32, against the one for few, which does in fp64, on the same tokens in
+    calls of 60: every bit, from position 0 on, zeros of both signs, subnormal, largest and infinite values among them
+    (and NaN where the other has one)."""
+    print(f"rope bits S={S} h_q={h_q} h_kv={h_kv} d={d}", flush=True)
+    g, W, C = h_q // h_kv, (h_q + 2 * h_kv) * d, (S + 63) // 64 * 64
+    qkv = synth.activations(3802, S, d, S, W)
+    rng = np.random.default_rng(d)
+    odd = np.array([0.0, -0.0, 6e-8, -6e-8, 3e-5, -6.1e-5, 65504.0, -65504.0, 1.0, -1.0, np.inf, -np.inf, np.nan], dtype=np.float16)
+    share = rng.random(qkv.shape)
+    qkv = np.where(share < 0.1, rng.choice(odd, qkv.shape), np.where(share < 0.4, rng.choice(odd[:10], qkv.shape), qkv)).astype(np.float16)
+    x = torch.from_numpy(qkv).to(DEV)
+    shape = _attn_shape(1, h_q, h_kv, d, C)
+    outs = []
+    for step in (S, 60):
+        assert (step < 128) == (step == 60) and (step == 60 or step * W >= 400 << 10)
+        kc = torch.zeros((h_kv, C, d), dtype=torch.float16, device=DEV)
+        vc = torch.zeros((h_kv, C // 64, d, 64), dtype=torch.float16, device=DEV)
+        q = []
+        for s0 in range(0, S, step):
+            n = min(step, S - s0)
+            q.append(torch.zeros((h_kv, n * g, d), dtype=torch.float16, device=DEV))
+            binding.qfc_rope_qkv(x[s0:s0 + n].view(1, n, W), s0, shape, base, q[-1], kc, vc)
+        torch.cuda.synchronize()
+        outs.append([t.cpu().numpy() for t in (torch.cat(q, 1), kc, vc)])
+    for many, few in zip(*outs):
+        nan = np.isnan(few)
+        assert np.array_equal(np.isnan(many), nan) and (few[~nan].view(np.uint16) == 0x8000).any()
+        assert np.array_equal(many[~nan].view(np.uint16), few[~nan].view(np.uint16))
+
+
 def test_native_marshalling_takes_what_the_binding_takes(monkeypatch):
     """The calls that csrc/marshal.cpp lets through give the bits of the other way, and what is not in order is refused alike by both:
     other types, devices, shapes, strides, no rows; subclasses and parameters are taken by both."""
