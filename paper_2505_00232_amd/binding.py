@@ -1,11 +1,15 @@
 """Thin ctypes binding of libqfc.so: same names as include/qfc.h, argument
 marshalling only.  PyTorch supplies device memory and the stream; every step of
 the path runs in the library's HIP kernels.  There is no fallback: if the
-library is missing or a call fails, an exception is raised."""
+library is missing or a call fails, an exception is raised.  (The two most frequent
+calls pass their arguments through the native module _marshal; where it
+cannot be loaded they go through ctypes like the others.)"""
 from __future__ import annotations
 
 import ctypes
 import os
+import sys
+import warnings
 
 import torch
 
@@ -60,7 +64,24 @@ class QfcError(RuntimeError):
 
 
 _lib = None
-_fast = None  # _marshal (csrc/marshal.cpp), from the first lib() on
+_fast = None  # _marshal (csrc/marshal.cpp), from the first lib() on, where it can be loaded
+
+
+def _built_for() -> str:
+    """What _marshal is tied to: this Python's and this torch's binary interfaces."""
+    return f"Python {sys.version_info[0]}.{sys.version_info[1]}, torch {torch.__version__}"
+
+
+def _load_marshal(L):
+    try:
+        from . import _marshal
+        if _marshal.built_for != _built_for():
+            raise ImportError(f"built for {_marshal.built_for}, this is {_built_for()}")
+    except ImportError as e:
+        warnings.warn(f"_marshal is not used, calls cost about 1 us more ({e}): run `python -m paper_2505_00232_amd.build`", RuntimeWarning, stacklevel=3)
+        return None
+    _marshal.bind(ctypes.cast(L.qfc_forward, ctypes.c_void_p).value, ctypes.cast(L.qfc_forward_fused, ctypes.c_void_p).value, _stream)
+    return _marshal
 
 
 def lib() -> ctypes.CDLL:
@@ -100,11 +121,7 @@ def lib() -> ctypes.CDLL:
         for name in EXPORTS:
             if name != "qfc_status_string":
                 getattr(L, name).restype = ctypes.c_int
-        if not os.path.exists(os.path.join(_HERE, "_marshal.so")):
-            raise RuntimeError("_marshal.so is missing: run `python -m paper_2505_00232_amd.build` first")
-        from . import _marshal
-        _marshal.bind(ctypes.cast(L.qfc_forward, vp).value, ctypes.cast(L.qfc_forward_fused, vp).value)
-        _lib, _fast = L, _marshal
+        _lib, _fast = L, _load_marshal(L)
     return _lib
 
 
@@ -247,7 +264,7 @@ def qfc_quantize_activations(x: torch.Tensor, xq: torch.Tensor, sx: torch.Tensor
 
 def qfc_forward(h, x: torch.Tensor, y: torch.Tensor):
     N, K = _nk(h)
-    if _fast is not None and (status := _fast.forward(h.value, x, y, N, K, _stream())) >= 0:
+    if _fast is not None and (status := _fast.forward(h.value, x, y, N, K)) >= 0:
         if status:
             raise QfcError(status, "qfc_forward")
         return
@@ -268,7 +285,7 @@ def qfc_forward_fused(h, x: torch.Tensor, y: torch.Tensor, gate: torch.Tensor | 
                       gated_output: bool = False, norm_gamma: torch.Tensor | None = None, norm_eps: float = 0.0,
                       norm_offset: float = 0.0):
     N, K = _nk(h)
-    if _fast is not None and (status := _fast.forward_fused(h.value, x, y, N, K, _stream(), gate, activation, residual, gated_output,
+    if _fast is not None and (status := _fast.forward_fused(h.value, x, y, N, K, gate, activation, residual, gated_output,
                                                             norm_gamma, norm_eps, norm_offset)) >= 0:
         if status:
             raise QfcError(status, "qfc_forward_fused")

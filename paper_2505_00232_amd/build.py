@@ -7,13 +7,16 @@ from __future__ import annotations
 import os
 import subprocess
 import sys
+import sysconfig
+import warnings
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libqfc.so")
-MARSHAL = os.path.join(HERE, "_marshal.so")
+MARSHAL = os.path.join(HERE, "_marshal" + sysconfig.get_config_var("EXT_SUFFIX"))  # (another Python does not take it for its own)
+MARSHAL_FOR = os.path.join(OBJ, "marshal_built_for")
 SOURCES = ["api.hip", "pack.hip", "gemv.hip", "gemv_q8.hip", "actquant.hip", "rmsnorm.hip", "attention.hip", "gemm_i8.hip", "gemm_f16.hip", "gemm_skinny.hip", "probe.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function",
          # packed-fp32 code generation is switched off on purpose
@@ -67,25 +70,44 @@ def _deps_newer(target: str) -> bool:
     return any(os.path.getmtime(d) > t for d in _deps())
 
 
-def _build_marshal() -> None:
-    """The host module behind the binding's most frequent calls, against torch's own headers (no device code)."""
-    import sysconfig
+def _marshal_stale() -> bool:
+    """Older than what it is built from, or built against another Python or torch."""
+    from .binding import _built_for
+    if _deps_newer(MARSHAL) or not os.path.exists(MARSHAL_FOR):
+        return True
+    with open(MARSHAL_FOR) as f:
+        return f.read() != _built_for()
 
+
+def _build_marshal() -> None:
+    """The host module behind the binding's most frequent calls, against torch's own headers (no device code).  The library and the binding do without it
+    where it cannot be built."""
     import torch
+
+    from .binding import _built_for
     root = os.path.dirname(torch.__file__)
-    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", f'-DQFC_BUILT_FOR="{_built_for()}"',
            *(f"-I{d}" for d in (f"{root}/include", f"{root}/include/torch/csrc/api/include", sysconfig.get_paths()["include"])),
            os.path.join(CSRC, "marshal.cpp"), "-o", MARSHAL, f"-L{root}/lib", "-ltorch_python", "-ltorch_cpu", "-lc10", f"-Wl,-rpath,{root}/lib"]
-    r = subprocess.run(cmd, capture_output=True, text=True)
-    if r.returncode != 0:
-        raise RuntimeError("g++ failed on marshal.cpp:\n" + r.stderr)
+    try:
+        r = subprocess.run(cmd, capture_output=True, text=True)
+        failed = r.stderr if r.returncode != 0 else ""
+    except OSError as e:
+        failed = str(e)
+    if failed:
+        warnings.warn("marshal.cpp could not be built, calls cost about 1 us more:\n" + failed, RuntimeWarning, stacklevel=2)
+        if os.path.exists(MARSHAL):
+            os.remove(MARSHAL)
+    with open(MARSHAL_FOR, "w") as f:
+        f.write(_built_for())
 
 
 def build(force: bool = False, verbose: bool = False) -> str:
-    if not force and not _deps_newer(LIB) and not _deps_newer(MARSHAL):
+    library, marshal = force or _deps_newer(LIB), force or _marshal_stale()
+    if not library and not marshal:
         return LIB
     os.makedirs(OBJ, exist_ok=True)
-    cc = _hipcc()
+    cc = _hipcc() if library else None
 
     def compile_one(src: str) -> str:
         obj = os.path.join(OBJ, src.replace(".hip", ".o"))
@@ -107,9 +129,12 @@ def build(force: bool = False, verbose: bool = False) -> str:
         return obj
 
     with ThreadPoolExecutor(max_workers=7) as ex:
-        marshal = ex.submit(_build_marshal)
-        objs = list(ex.map(compile_one, SOURCES))
-        marshal.result()
+        module = ex.submit(_build_marshal) if marshal else None
+        objs = list(ex.map(compile_one, SOURCES if library else []))
+        if module:
+            module.result()
+    if not library:
+        return LIB
     r = subprocess.run([cc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs],
                        capture_output=True, text=True)
     if r.returncode != 0:

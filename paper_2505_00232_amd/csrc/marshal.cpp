@@ -8,6 +8,7 @@ namespace {
 
 decltype(&qfc_forward) g_forward = nullptr;
 decltype(&qfc_forward_fused) g_forward_fused = nullptr;
+PyObject *g_stream = nullptr;  // torch's current stream, asked for once the arguments are in order
 
 // Pointer of a contiguous binary16 matrix on a GPU with `cols` columns and (if rows >= 0) that many rows, which are returned; null: something else.
 // Plain tensors with memory of their own only: subclasses and wrappers (tracing, vmap) go the other way.
@@ -28,20 +29,31 @@ void *vector(PyObject *o, int64_t size) {
     return t.mutable_data_ptr();
 }
 
-// bind(address of qfc_forward, address of qfc_forward_fused)
+// False with Python's error set where there is none
+bool current_stream(void *&stream) {
+    PyObject *s = PyObject_CallNoArgs(g_stream);
+    if (!s) return false;
+    stream = PyLong_AsVoidPtr(s);
+    Py_DECREF(s);
+    return !PyErr_Occurred();
+}
+
+// bind(address of qfc_forward, address of qfc_forward_fused, function that returns the current stream)
 PyObject *bind(PyObject *, PyObject *const *a, Py_ssize_t n) {
-    if (n != 2) return PyErr_Format(PyExc_TypeError, "two addresses");
+    if (n != 3) return PyErr_Format(PyExc_TypeError, "two addresses and a function");
     void *f = PyLong_AsVoidPtr(a[0]), *g = PyLong_AsVoidPtr(a[1]);
     if (PyErr_Occurred()) return nullptr;
     g_forward = reinterpret_cast<decltype(g_forward)>(f);
     g_forward_fused = reinterpret_cast<decltype(g_forward_fused)>(g);
+    Py_INCREF(a[2]);
+    Py_XSETREF(g_stream, a[2]);
     Py_RETURN_NONE;
 }
 
-// forward(handle, x, y, N, K, stream) -> status, or -1
+// forward(handle, x, y, N, K) -> status, or -1
 PyObject *forward(PyObject *, PyObject *const *a, Py_ssize_t n) {
-    if (n != 6 || !g_forward) return PyLong_FromLong(-1);
-    void *h = PyLong_AsVoidPtr(a[0]), *stream = PyLong_AsVoidPtr(a[5]);
+    if (n != 5 || !g_forward) return PyLong_FromLong(-1);
+    void *h = PyLong_AsVoidPtr(a[0]);
     const long N = PyLong_AsLong(a[3]), K = PyLong_AsLong(a[4]);
     if (PyErr_Occurred()) {
         PyErr_Clear();
@@ -56,6 +68,8 @@ PyObject *forward(PyObject *, PyObject *const *a, Py_ssize_t n) {
         y = nullptr;
     }
     if (!x || !y || M < 1 || M > INT32_MAX) return PyLong_FromLong(-1);
+    void *stream;
+    if (!current_stream(stream)) return nullptr;
     int status;
     Py_BEGIN_ALLOW_THREADS
     status = g_forward(static_cast<qfc_handle_t>(h), x, (int32_t)M, y, stream);
@@ -63,20 +77,20 @@ PyObject *forward(PyObject *, PyObject *const *a, Py_ssize_t n) {
     return PyLong_FromLong(status);
 }
 
-// forward_fused(handle, x, y, N, K, stream, gate, activation, residual, gated_output, norm_gamma, norm_eps, norm_offset) -> status, or -1
+// forward_fused(handle, x, y, N, K, gate, activation, residual, gated_output, norm_gamma, norm_eps, norm_offset) -> status, or -1
 PyObject *forward_fused(PyObject *, PyObject *const *a, Py_ssize_t n) {
-    if (n != 13 || !g_forward_fused) return PyLong_FromLong(-1);
-    void *h = PyLong_AsVoidPtr(a[0]), *stream = PyLong_AsVoidPtr(a[5]);
-    const long N = PyLong_AsLong(a[3]), K = PyLong_AsLong(a[4]), activation = PyLong_AsLong(a[7]);
-    const int gated = PyObject_IsTrue(a[9]);
+    if (n != 12 || !g_forward_fused) return PyLong_FromLong(-1);
+    void *h = PyLong_AsVoidPtr(a[0]);
+    const long N = PyLong_AsLong(a[3]), K = PyLong_AsLong(a[4]), activation = PyLong_AsLong(a[6]);
+    const int gated = PyObject_IsTrue(a[8]);
     qfc_fusion_t f = {};
-    f.norm_eps = (float)PyFloat_AsDouble(a[11]);
-    f.norm_offset = (float)PyFloat_AsDouble(a[12]);
+    f.norm_eps = (float)PyFloat_AsDouble(a[10]);
+    f.norm_offset = (float)PyFloat_AsDouble(a[11]);
     if (PyErr_Occurred()) {
         PyErr_Clear();  // (an argument of another type: as the other way takes it)
         return PyLong_FromLong(-1);
     }
-    if (activation < INT32_MIN || activation > INT32_MAX || (gated && a[8] != Py_None)) return PyLong_FromLong(-1);
+    if (activation < INT32_MIN || activation > INT32_MAX || (gated && a[7] != Py_None)) return PyLong_FromLong(-1);
     f.activation = (int32_t)activation;
     f.gated_output = gated;
     int64_t M = -1;
@@ -86,13 +100,15 @@ PyObject *forward_fused(PyObject *, PyObject *const *a, Py_ssize_t n) {
         x = matrix(a[1], M, K);
         if (x) y = matrix(a[2], M, gated ? N / 2 : N);
         ok = x && y;
-        if (ok && a[6] != Py_None) ok = (f.gate = matrix(a[6], M, K)) != nullptr;
-        if (ok && a[8] != Py_None) ok = (f.residual = matrix(a[8], M, N)) != nullptr;
-        if (ok && a[10] != Py_None) ok = (f.norm_gamma = vector(a[10], K)) != nullptr;
+        if (ok && a[5] != Py_None) ok = (f.gate = matrix(a[5], M, K)) != nullptr;
+        if (ok && a[7] != Py_None) ok = (f.residual = matrix(a[7], M, N)) != nullptr;
+        if (ok && a[9] != Py_None) ok = (f.norm_gamma = vector(a[9], K)) != nullptr;
     } catch (...) {
         ok = false;
     }
     if (!ok || M < 1 || M > INT32_MAX) return PyLong_FromLong(-1);
+    void *stream;
+    if (!current_stream(stream)) return nullptr;
     int status;
     Py_BEGIN_ALLOW_THREADS
     status = g_forward_fused(static_cast<qfc_handle_t>(h), x, (int32_t)M, y, &f, stream);
@@ -110,4 +126,8 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_marshal", nullptr, -1, methods};
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__marshal() { return PyModule_Create(&module); }
+PyMODINIT_FUNC PyInit__marshal() {
+    PyObject *m = PyModule_Create(&module);
+    if (m && PyModule_AddStringConstant(m, "built_for", QFC_BUILT_FOR) < 0) Py_CLEAR(m);
+    return m;
+}

@@ -5,6 +5,7 @@ import ctypes
 import os
 import re
 import subprocess
+import sys
 
 import pytest
 
@@ -159,6 +160,53 @@ def test_build_sees_changes_of_its_flags_and_headers(tmp_path, monkeypatch):
         stale = build._deps_newer(newest)
         monkeypatch.setattr(build.os.path, "getmtime", real)
         assert stale, changed
+
+
+_IN_A_PROCESS = """import sys, types, warnings
+{0}
+from paper_2505_00232_amd import binding
+with warnings.catch_warnings(record=True) as said:
+    warnings.simplefilter("always")
+    binding.lib()
+assert {1}, (binding._fast, [str(w.message) for w in said])
+assert binding.status_string(0) == "ok"
+for call in (lambda h, x: binding.qfc_forward(h, x, x), lambda h, x: binding.qfc_forward_fused(h, x, x)):
+    import ctypes, torch
+    binding._dims[4096] = (64, 64)
+    try:
+        call(ctypes.c_void_p(4096), torch.zeros(2, 64, dtype=torch.float16))
+    except ValueError as e:
+        assert "CUDA tensor" in str(e)
+    else:
+        raise AssertionError("a host tensor was taken")
+"""
+
+
+@pytest.mark.parametrize("before,after", [
+    ("", "binding._fast is not None and not said"),  # as it is built here
+    ("sys.modules['paper_2505_00232_amd._marshal'] = None", "binding._fast is None and len(said) == 1"),  # missing, or the loader refuses it
+    ("m = types.ModuleType('paper_2505_00232_amd._marshal'); m.built_for = 'Python 3.10, torch 1.0'; sys.modules[m.__name__] = m",
+     "binding._fast is None and len(said) == 1 and 'torch 1.0' in str(said[0].message)")])  # built against another torch
+def test_binding_works_without_the_native_module(L, before, after):
+    """_marshal only shortens the way of two calls: without it the library loads, and every call goes through ctypes."""
+    r = subprocess.run([sys.executable, "-c", _IN_A_PROCESS.format(before, after)], cwd=ROOT, capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr[-2000:]
+
+
+def test_build_sees_another_torch_and_lives_without_the_native_module(tmp_path, monkeypatch):
+    """The native module is built again for another torch, and one that cannot be built is no error, but leaves no old one behind."""
+    build.build()
+    assert not build._marshal_stale()
+    monkeypatch.setattr(binding.torch, "__version__", "99.0")
+    assert build._marshal_stale()
+    so = tmp_path / "_marshal.so"
+    so.write_text("old")
+    monkeypatch.setattr(build, "MARSHAL", str(so))
+    monkeypatch.setattr(build, "MARSHAL_FOR", str(tmp_path / "for"))
+    monkeypatch.setattr(build, "CSRC", str(tmp_path))  # (no marshal.cpp there)
+    with pytest.warns(RuntimeWarning, match="could not be built"):
+        build._build_marshal()
+    assert not so.exists()
 
 
 def test_prefill_walk_copies_land_before_they_are_read_and_end_with_the_walk(tmp_path):
