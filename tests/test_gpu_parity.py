@@ -2334,3 +2334,64 @@ def test_native_marshalling_takes_what_the_binding_takes(monkeypatch):
     torch.cuda.synchronize()
     assert all(torch.equal(o, outs[0]) for o in outs[1:])
     layer.close()
+
+
+def test_native_marshalling_takes_the_calls_in_order():
+    """What csrc/marshal.cpp itself says: plain tensors and parameters in order go through it (status 0), subclasses and anything that is not in
+    order do not (-1); with a gate and with a gated output it gives the bits of the other way."""
+    class Sub(torch.Tensor):
+        pass
+
+    N, K, M = 64, 96, 3
+    wq, sw = synth.weights(5210, 0, 0, synth.FC("t", K, N, "w8c"))
+    layer = _layer(wq, sw, "w8c")
+    pairs = binding.QuantLinear(wq, sw, "w8c", max_m=M, gated_pairs=True)
+    x, gate = (torch.from_numpy(synth.activations(5210 + i, 0, 0, M, K)).to(DEV) for i in range(2))
+    res = torch.from_numpy(synth.activations(5212, 0, 0, M, N)).to(DEV)
+    gamma = torch.ones(K, dtype=torch.float16, device=DEV)
+    y = torch.empty((M, N), dtype=torch.float16, device=DEV)
+    fast = binding._fast
+    assert fast is not None
+
+    def plain(xx, yy):
+        return fast.forward(layer.handle.value, xx, yy, N, K)
+
+    def fused(xx, yy, l=layer, gate=None, act=0, residual=None, gated=False, gamma=None):
+        return fast.forward_fused(l.handle.value, xx, yy, N, K, gate, act, residual, gated, gamma, 1e-5, 0)
+
+    half = torch.empty((M, N // 2), dtype=torch.float16, device=DEV)
+    assert plain(x, y) == 0 and plain(torch.nn.Parameter(x, requires_grad=False), y) == 0 and fused(x, y) == 0
+    assert fused(x, y, gate=gate, act=binding.QFC_ACT_GELU_TANH) == 0 and fused(x, y, residual=res, gamma=gamma) == 0
+    assert fused(x, half, l=pairs, gated=True) == 0
+    assert plain(x[:0], y[:0]) == -1 and fused(x[:0], y[:0]) == -1
+    off = torch.zeros(M * K + 1, dtype=torch.float16, device=DEV)[1:].view(M, K)
+    assert plain(off, y) == binding.QFC_ERR_ALIGNMENT and fused(off, y) == binding.QFC_ERR_ALIGNMENT
+    wide = torch.zeros((M, 2 * K), dtype=torch.float16, device=DEV)
+    for bad in (x.as_subclass(Sub), x.float(), x.cpu(), x[:, :32], wide[:, ::2], x[0], None, x.view(M, K, 1), x[:2]):
+        assert plain(bad, y) == -1 and fused(bad, y) == -1
+        if bad is not None:
+            assert fused(x, y, gate=bad) == -1
+    for bad in (y[:2], y.float(), half, None):
+        assert plain(x, bad) == -1 and fused(x, bad) == -1
+        if bad is not None:
+            assert fused(x, y, residual=bad) == -1
+    for bad in (gamma[:32], gamma.float(), gamma.view(1, K), gamma.as_subclass(Sub)):
+        assert fused(x, y, gamma=bad) == -1
+    assert fused(x, y, l=pairs, gated=True) == -1 and fused(x, half, l=pairs, gated=True, residual=res) == -1
+    assert fused(x, y, act=0.5) == -1 and fused(x, y, act=1 << 31) == -1
+
+    def both(f):
+        outs = []
+        for way in (fast, None):
+            binding._fast = way
+            outs.append(f().clone())
+        return torch.equal(*outs)
+
+    try:
+        assert both(lambda: (binding.qfc_forward_fused(layer.handle, x, y, gate=gate, activation=binding.QFC_ACT_GELU_TANH), y)[1])
+        assert both(lambda: (binding.qfc_forward_fused(layer.handle, x, y, gate=gate, residual=res), y)[1])
+        assert both(lambda: (binding.qfc_forward_fused(pairs.handle, x, half, gated_output=True, norm_gamma=gamma, norm_eps=1e-5), half)[1])
+    finally:
+        binding._fast = fast
+    layer.close()
+    pairs.close()
