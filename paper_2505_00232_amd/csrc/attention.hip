@@ -943,15 +943,19 @@ hipError_t launch_attn(const AttnArgs &a, int G, hipStream_t st) {
 // long as there are 2 workgroups per compute unit): head size 128, G = 8: 1280 positions 8.0 / 8.0 / 9.5, 12001
 // 15.9 / 16.1 / 18.1; G = 56: 3000 21.5 / 21.5 / 25.8, 9000 51.3 / 51.3 / 61.0; G = 256: 300 11.6 / 11.6 /
 // 14.5; head size 256, G = 4: 1280 8.7 / 8.7 / 12.9; G = 20: 9000 40.1 / 40.1 / 51.8; G = 44: 1500 20.0 / 20.0 / 27.6.
-int attn_splits(int G, int d, int n_ctx, int num_cus) {
+int attn_splits(int G, int M, int d, int n_ctx, int num_cus) {
     const int step = d <= 128 ? 64 : 32, steps = (n_ctx + step - 1) / step;
     if (steps <= 4 || num_cus < 1) return 1;
     int s = num_cus / G;
     if (5L * G * s < 3L * num_cus) s = 2 * num_cus / G;
-    // more KV heads than compute units and a last round that is a third full or less: four walks each (us, one / four: 288 heads of 128, 900 positions
-    // 38.1 / 33.2, 1500 59.8 / 47.0; of 256, 3000 226 / 174; 320 of 64, 900 20.3 / 19.4; 528 of 128, 1500 91.6 / 81.1; from half a round on level or
-    // slower, 384 of 64 3000 60.5 / 56.9, 448 of 128 1500 66.2 / 68.9, and so are short walks, 288 of 256 400 37.8 / 41.8)
-    if (G > num_cus && G % num_cus > 0 && 20 * (G % num_cus) <= 7 * num_cus && steps >= 14) s = 4;
+    // More KV heads than compute units and a last round that is a third full or less: four walks each.  What that saves, the idle part of one round, grows with the
+    // positions; the partial results, written and read, grow with the heads and the query rows: taken from positions x idle share = heads x (1.8 + 0.15
+    // rows) on, where it was nowhere slower over 780 combinations of 257 to 4112 heads of 64, 128 and 256, 1 to 16 rows, 448 to 6000 positions (without that
+    // line up to 1.56 times, 4112 heads of 256, 448 positions, 16 rows 389 / 607).  us, one / four: 288 heads of 128, 1 row, 900 positions 38.1 / 33.2, 1500 59.8 /
+    // 47.0; of 256, 3000 226 / 174; 528 of 128, 1500 91.6 / 81.1; 264 of 256, 16 rows, 1500 120.0 / 109.1, and before the line 900 78.4 / 78.0.
+    // From half a round on level or slower (384 of 64 3000 60.5 / 56.9, 448 of 128 1500 66.2 / 68.9), and so are short walks (288 of 256 400 37.8 / 41.8).
+    const int last = G % num_cus;
+    if (G > num_cus && last > 0 && 20 * last <= 7 * num_cus && steps >= 14 && 20L * n_ctx * (num_cus - last) >= (36L + 3L * M) * G * num_cus) s = 4;
     if (s > 24 && s > steps / 2) s = steps / 2 > 24 ? steps / 2 : 24;
     if (s > steps) s = steps;
     if (s > kAttnMaxSplits) s = kAttnMaxSplits;
@@ -1102,7 +1106,7 @@ hipError_t launch_attention(const void *q, const void *kc, const void *vc, int G
     a.S = S;
     a.C = C;
     a.n_ctx = n_ctx;
-    a.splits = tuning().attn_splits > 0 ? (int)tuning().attn_splits : attn_splits(G, d, n_ctx, num_cus);
+    a.splits = tuning().attn_splits > 0 ? (int)tuning().attn_splits : attn_splits(G, a.M, d, n_ctx, num_cus);
     if (num_cus < 1) num_cus = 1;
     a.groups = G;
     a.max_chunks = kPrefillMaxChunks;

@@ -342,7 +342,7 @@ constexpr int kAttnMaxSplits = 64;
 constexpr int kPrefillMaxChunks = 8;  // chunks a block's walk is cut into at most (prefill, few blocks)
 // Bytes of workspace the many-query-rows path needs for G groups of M query rows of d values.
 size_t attn_prefill_workspace(int G, int M, int d, int num_cus);
-int attn_splits(int G, int d, int n_ctx, int num_cus);
+int attn_splits(int G, int M, int d, int n_ctx, int num_cus);
 // cos and sin of pos * base^(-2 i / d) for pos < positions, i < d / 2, evaluated in fp64: [positions][d / 2][2] floats
 hipError_t launch_rope_table(int d, float base, int positions, float *table, hipStream_t st);
 hipError_t launch_rope_qkv(const void *qkv, int B, int S, int h_q, int h_kv, int d, int C, int pos0, float base,

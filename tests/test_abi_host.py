@@ -397,3 +397,21 @@ int main() {
     got = [int(v) for v in r.stdout.split()]
     assert got[:len(CHOICES)] == [c[4] for c in CHOICES]
     assert got[len(CHOICES):] == [s[3] for s in STREAMS]
+
+
+# KV heads, query rows per head, head size, positions: workgroups per KV head on 256 compute units
+WALKS = [(8, 4, 128, 1280, 20), (56, 4, 128, 3000, 4), (256, 4, 128, 3000, 1), (20, 2, 256, 9000, 12),
+         # more KV heads than compute units: four walks from 14 steps and positions x idle share of the last round = heads x (1.8 + 0.15 rows) on, a last
+         # round of 35 % at most
+         (257, 1, 128, 833, 4), (257, 1, 128, 832, 1), (257, 16, 64, 1083, 1), (257, 16, 64, 1084, 4), (257, 16, 256, 1083, 1), (257, 16, 256, 1084, 4), (345, 1, 128, 3000, 4), (346, 1, 128, 3000, 1),
+         (512, 1, 128, 9000, 1), (520, 1, 128, 1500, 4), (520, 16, 128, 1500, 1), (2064, 1, 64, 4294, 4), (2064, 1, 64, 4293, 1),
+         # short walks and many heads (us, one / four: 4112 heads of 256, 448 positions, 16 rows 389 / 607; 264 of 256, 448, 8 rows 12 % slower)
+         (4112, 16, 256, 448, 1), (4112, 1, 256, 448, 1), (264, 8, 256, 448, 1), (2561, 1, 128, 1500, 1)]
+
+
+def test_decode_attention_walks():
+    """Into how many walks the decode attention of a KV head is cut, on both sides of the rule's lines (times beside it)."""
+    binding.lib()
+    splits = ctypes.CDLL(binding.LIB_PATH)._ZN3qfc11attn_splitsEiiiii
+    got = [(*w[:4], splits(*w[:4], 256)) for w in WALKS]
+    assert got == WALKS

@@ -1407,7 +1407,6 @@ def test_attention_many_heads_last_round_of_few(B, d, n_ctx):
     test_attention_over_the_cache(B, 1, 4, 4, d, 960, n_ctx)
 
 
-
 @pytest.mark.parametrize("B,S,h_q,h_kv,d,C,n_ctx", [(1, 1, 4, 1, 64, 640, 577), (2, 1, 8, 2, 128, 704, 700), (1, 3, 4, 1, 256, 384, 321)])
 def test_attention_any_number_of_workgroups_per_head(B, S, h_q, h_kv, d, C, n_ctx):
     """The combination of 1 to 64 partial results (whole and broken groups of eight), workgroups with one step for
@@ -2395,3 +2394,28 @@ def test_native_marshalling_takes_the_calls_in_order():
         binding._fast = fast
     layer.close()
     pairs.close()
+
+
+# more KV heads than compute units, one walk each and four, 16 and 8 query rows per head, all head sizes (head size 256: walks of 32 positions)
+@pytest.mark.parametrize("G,M,d,n_ctx", [(257, 16, 256, 1084), (257, 16, 256, 1083), (258, 8, 128, 900), (257, 16, 64, 1100), (262, 5, 256, 1000), (520, 3, 64, 1301)])
+def test_attention_many_heads_and_rows_sampled(G, M, d, n_ctx):
+    """Sampled KV heads, the first and the last among them, against the oracle; the call's own number of walks and one."""
+    print(f"attention G={G} M={M} d={d} n_ctx={n_ctx}", flush=True)
+    C = (n_ctx + 63) // 64 * 64
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(G + n_ctx)
+    q, kc, vc = (torch.randn(s, generator=gen, device=DEV).half() for s in ((G, M, d), (G, C, d), (G, C // 64, d, 64)))
+    shape = _attn_shape(G, M, 1, d, C)
+    ws = torch.empty(binding.qfc_attention_workspace_size(shape, 1), dtype=torch.uint8, device=DEV)
+    heads = sorted({0, G - 1, *np.random.default_rng(G).integers(0, G, 6).tolist()})
+    ref = oracle.attention(q[heads].cpu().numpy(), kc[heads].cpu().numpy(), binding.vcache_logical(vc[heads]).cpu().numpy(), n_ctx, 1)
+    for walks in (0, 1):
+        out = torch.full((G, M, d), 7.0, dtype=torch.float16, device=DEV)
+        binding.qfc_tune(12, walks)
+        try:
+            binding.qfc_attention(q, kc, vc, 1, n_ctx, shape, ws, out)
+            torch.cuda.synchronize()
+        finally:
+            binding.qfc_tune(12, 0)
+        assert not (out == 7.0).all(-1).any()
+        assert _E(out[heads].cpu().numpy().reshape(-1, d), ref.reshape(-1, d)) <= TOL, walks
