@@ -436,6 +436,39 @@ def test_int8_tiles_parts_of_k_bit_exact(fmt, variant, M, N, K):
     layer.close()
 
 
+@pytest.mark.parametrize("fmt,variant,M,N,K", [
+    # one channel tile and ragged ones, one token tile and ragged ones (whole and half groups without a row to store), parts of K of unequal length; and the forms
+    # with K in one part
+    *[("w8c", v, *s) for v in (13, 14) for s in ((131, 608, 512), (64, 32, 768), (300, 160, 1280), (33, 544, 2304))],
+    *[("w4c", 24, *s) for s in ((131, 608, 512), (64, 32, 768), (300, 160, 1280), (33, 544, 2304))],
+    *[("w4c", 25, *s) for s in ((131, 608, 1024), (64, 32, 1280), (300, 160, 1536), (33, 544, 1792), (300, 544, 2304))],
+    ("w8c", 10, 131, 608, 512), ("w8c", 12, 131, 608, 512), ("w4c", 21, 131, 608, 512), ("w4c", 23, 131, 608, 512),
+    # large enough for the choice by size to go there: forms 14, 13, 24, 25
+    ("w8c", 0, 700, 2048, 2304), ("w8c", 0, 1500, 2048, 4096), ("w4c", 0, 300, 4096, 4096), ("w4c", 0, 814, 2304, 9216)])
+def test_int8_tiles_gated_output(fmt, variant, M, N, K):
+    """act(gate) * up in the store phase of every form of the direct-weights int8 tiles, above all those whose groups of wavefronts hand their sums over
+    and store half of the token rows each; a row past the last stays as it was."""
+    print(f"int8 tiles, gated output, {fmt} variant {variant} M={M} N={N} K={K}", flush=True)
+    wq, sw = synth.weights(4680, M, K, synth.FC("t", K, N, fmt))
+    x = (synth.activations(4680, M, K, M, K) * np.float16(0.125)).astype(np.float16)
+    layer = binding.QuantLinear(wq, sw, fmt, compute_mode=binding.QFC_COMPUTE_INT8_ACT, max_m=M, gated_pairs=True)
+    guard = torch.full((M + 1, N // 2), 77.0, dtype=torch.float16, device=DEV)
+    xd = torch.from_numpy(x).to(DEV)
+    rows = np.arange(M) if M * N * K < 1 << 29 else np.unique(np.concatenate([[0, M - 1], np.random.default_rng(M).integers(0, M, 62)]))
+    ref = oracle.gated_output(oracle.fc_int8_act(x[rows], wq, sw)[3], oracle.SILU)
+    binding.qfc_tune(2, variant)
+    try:
+        for rep in range(2):
+            guard[:M] = 55.0
+            binding.qfc_forward_fused(layer.handle, xd, guard[:M], activation=binding.QFC_ACT_SILU, gated_output=True)
+            torch.cuda.synchronize()
+            assert _E(guard[:M].cpu().numpy()[rows], ref) <= TOL, rep
+            assert bool((guard[M] == 77.0).all())
+    finally:
+        binding.qfc_tune(2, 0)
+    layer.close()
+
+
 @pytest.mark.parametrize("fmt,K", [("w4c", 256), ("w4c", 512), ("w4c", 768), ("w4c", 2304), ("w4c", 2560), ("w8c", 256), ("w8c", 512), ("w8c", 2400), ("w8c", 6144), ("w8c", 6400), ("w8c", 7168), ("w8c", 7392)])
 def test_int8_tiles_of_64_tokens_any_even_number_of_stages(fmt, K):
     """The 64-token tiles, which hold the weights of four stages of 128 k (int8 codes with K of less than 6144: of two): whole passes of four, two
@@ -1081,8 +1114,8 @@ def test_paired_packing_round_trip_and_decode(fmt, N, K):
 @pytest.mark.parametrize("fmt,mode", [("w8c", None), ("w4c", binding.QFC_COMPUTE_INT8_ACT), ("w4g32", None), ("w4c", None)])
 @pytest.mark.parametrize("M,N,K", [(9, 32, 128), (100, 160, 384), (130, 1024, 256), (300, 2080, 1152), (513, 544, 2304)])
 def test_prefill_gated_output(fmt, mode, M, N, K):
-    """act(gate) * up in the store phase of both prefill kernels (layer packed in pairs) against the
-    oracle: the element-wise product of the two halves of the unrounded outputs."""
+    """act(gate) * up in the store phase of the kernels that the sizes lead to (layer packed in pairs; with int8 activations those for few
+    token rows) against the oracle: the element-wise product of the two halves of the unrounded outputs."""
     print(f"prefill gated output {fmt} mode={mode} M={M} N={N} K={K}", flush=True)
     fc = synth.FC("t", K, N, fmt)
     wq, s = synth.weights(3700, M, N, fc)
