@@ -47,7 +47,7 @@ struct GemmF16Args {
     const _Float16 *res;  // [M, N] residual added before the rounding, or null
     const float *sw;  // W4C: fp32 scale per output channel [Np]
     int M, N, K, KT, rt_stride, n_tiles, m_tiles;
-    int by_tokens;  // order of the tiles (see xcd_tile)
+    TileWalk walk;  // order of the tiles (see xcd_tile)
     int gated_act = -1;  // QFC_ACT_*: the layer is packed in pairs and y [M, N/2] = fp16(act(gate) * other)
 };
 
@@ -98,7 +98,7 @@ __global__ __launch_bounds__(256) void gemm_f16_w4_kernel(GemmF16Args a) {
     const int wn = wave & 1, wm = wave >> 1;
 
     int nt, mt;
-    xcd_tile(blockIdx.x, a.n_tiles, a.m_tiles, a.by_tokens, nt, mt);
+    xcd_tile(blockIdx.x, a.n_tiles, a.m_tiles, a.walk, nt, mt);
 
     // weights: thread -> two packed vectors per stage: row tile (tid / 64) and (tid / 64 + 4)
     const int c = lane & 15, q = lane >> 4;
@@ -458,7 +458,7 @@ __global__ __launch_bounds__(256 * KS, KS == 2 ? 2 : JP == 1 ? 4 : JP == 2 ? 3 :
     char *lds_b = lds_all + group * L::kBytes;
     const int c = lane & 15, q = lane >> 4;
     int nt, mt;
-    xcd_tile(blockIdx.x, a.n_tiles, a.m_tiles, a.by_tokens, nt, mt);
+    xcd_tile(blockIdx.x, a.n_tiles, a.m_tiles, a.walk, nt, mt);
     const int m0 = mt * ROWS;
     // half stages of this group (4-bit codes: an even number); the first group has the odd step
     constexpr int kStep = W8 ? 1 : 2;
@@ -713,7 +713,7 @@ hipError_t launch_tile(GemmF16Args a, hipStream_t st) {
     if (const hipError_t e = allow_dynamic_lds<gemm_f16_tile_kernel<FMT, JP, KS>>(bytes); e != hipSuccess) return e;
     a.n_tiles = (a.N + TN - 1) / TN;
     a.m_tiles = (a.M + 32 * JP - 1) / (32 * JP);
-    a.by_tokens = walk_by_tokens(a.n_tiles, a.m_tiles, (FMT == kW8C ? 1.0f : FMT == kW4C ? 0.5f : 0.5625f) * TN, 2.0f * 32 * JP);
+    a.walk = tile_walk(a.n_tiles, a.m_tiles, a.K, false, (FMT == kW8C ? 1.0f : FMT == kW4C ? 0.5f : 0.5625f) * TN, 2.0f * 32 * JP);
     gemm_f16_tile_kernel<FMT, JP, KS><<<dim3((unsigned)(a.n_tiles * a.m_tiles)), 256 * KS, bytes, st>>>(a);
     return hipGetLastError();
 }
@@ -723,7 +723,7 @@ hipError_t launch_fallback(GemmF16Args a, int M, hipStream_t st) {
     if (const hipError_t e = allow_dynamic_lds<gemm_f16_w4_kernel<PC, W8>>(kLdsBytes); e != hipSuccess) return e;
     a.n_tiles = (a.N + BN - 1) / BN;
     a.m_tiles = (M + BM - 1) / BM;
-    a.by_tokens = walk_by_tokens(a.n_tiles, a.m_tiles, (W8 ? 1.0f : PC ? 0.5f : 0.5625f) * BN, 2.0f * BM);
+    a.walk = tile_walk(a.n_tiles, a.m_tiles, a.K, false, (W8 ? 1.0f : PC ? 0.5f : 0.5625f) * BN, 2.0f * BM);
     gemm_f16_w4_kernel<PC, W8><<<dim3((unsigned)(a.n_tiles * a.m_tiles)), 256, kLdsBytes, st>>>(a);
     return hipGetLastError();
 }
@@ -812,7 +812,8 @@ hipError_t launch_gemm_f16(const Geometry &g, const void *packed, const void *x,
     a.K = g.K;
     a.KT = g.KT;
     a.rt_stride = g.rt_stride;
-    a.n_tiles = a.m_tiles = a.by_tokens = 0;
+    a.n_tiles = a.m_tiles = 0;
+    a.walk = {};
     a.gated_act = gated_act;
     if (tile_kernel_takes(g) && (tuning().gemm_variant != 9 || gated_act >= 0)) {
         const int rest = skinny_tail_rows(g, M, gated_act >= 0, num_cus), most = M - rest;

@@ -41,7 +41,7 @@ struct GemmI8Args {
     const _Float16 *res;  // [M, N] residual added before the rounding, or null
     void *out;
     int M, N, Kp, n_tiles, m_tiles;
-    int by_tokens;  // order of the tiles (see xcd_tile)
+    TileWalk walk;  // order of the tiles (see xcd_tile)
     int share;      // by_tokens: token tiles on an XCD, which divide the early touch of the weights among them
     // 4-bit weights enter the MFMA as 16 q (the code's nibble in the top half of a byte): the sums are
     // 16 times the definition's, exactly; channel scales are multiplied by 1/16, raw sums shifted by 4
@@ -269,7 +269,7 @@ __global__ __launch_bounds__(256, 2) void gemm_i8_kernel(GemmI8Args a) {
     const int wn = wave & 1, wm = wave >> 1;
 
     int nt, mt;
-    xcd_tile(blockIdx.x, a.n_tiles, a.m_tiles, a.by_tokens, nt, mt);
+    xcd_tile(blockIdx.x, a.n_tiles, a.m_tiles, a.walk, nt, mt);
     const int KT = a.Kp / 64;
 
     // One wavefront instruction copies one KiB tile: tile t of the stage, t = wave,
@@ -379,7 +379,7 @@ __global__ __launch_bounds__(256, 2) void gemm_i8_w4_kernel(GemmI8Args a) {
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wn = wave & 1, wm = wave >> 1;
     int nt, mt;
-    xcd_tile(blockIdx.x, a.n_tiles, a.m_tiles, a.by_tokens, nt, mt);
+    xcd_tile(blockIdx.x, a.n_tiles, a.m_tiles, a.walk, nt, mt);
     const int stages = a.Kp / 128;
 
     constexpr int NLOAD = (W_TILES + X_TILES) / 4;
@@ -521,7 +521,7 @@ __global__ __launch_bounds__(CG * KS * 64, 2) void gemm_i8_dw_kernel(GemmI8Args 
     const int group = KS == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) / CG;  // which part of K
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) - group * CG;
     int nt, mt;
-    xcd_tile(blockIdx.x, a.n_tiles, a.m_tiles, a.by_tokens, nt, mt);
+    xcd_tile(blockIdx.x, a.n_tiles, a.m_tiles, a.walk, nt, mt);
     // stages: of the layer, before the group's, of the group (an even number; the first groups may have two more)
     const int all = a.Kp / 128, pairs = all / 2, first = 2 * (group * (pairs / KS) + min(group, pairs % KS));
     const int KT = KS == 1 ? all : 2 * (pairs / KS + (group < pairs % KS ? 1 : 0));
@@ -557,8 +557,8 @@ __global__ __launch_bounds__(CG * KS * 64, 2) void gemm_i8_dw_kernel(GemmI8Args 
 
     // the touch of the weights of a stage far ahead (PF): of the 128-byte lines of the wavefront's row tiles, those that fall to this token tile
     constexpr int PFN = PF ? 1 : 0, kLines = 32 * WV;
-    const int band = a.by_tokens ? 0 : mt / kBand * kBand;  // token tiles that walk the same weights on this XCD, and which of them this is
-    const int share = a.by_tokens ? a.share : min(kBand, a.m_tiles - band), mine = a.by_tokens ? mt % share : mt - band;
+    const int band = a.walk.by_tokens ? 0 : mt / a.walk.band * a.walk.band;  // token tiles that walk the same weights on this XCD, and which of them this is
+    const int share = a.walk.by_tokens ? a.share : min(a.walk.band, a.m_tiles - band), mine = a.walk.by_tokens ? mt % share : mt - band;
     const int per = (kLines + share - 1) / share, pidx = min(mine * per + lane % per, kLines - 1);
     const uint32_t poff = (uint32_t)((pidx / (8 * WV)) * all * WV * 1024 + (pidx % (8 * WV)) * 128);
     constexpr int kPrefetch = NS - 1 + PW;
@@ -733,8 +733,8 @@ hipError_t launch_dw(GemmI8Args a, hipStream_t st) {
     if (const hipError_t e = allow_dynamic_lds<gemm_i8_dw_kernel<W4, NS, PW, TM, CG, KS, PF, OUT_MODE>>(lds_bytes); e != hipSuccess) return e;
     a.n_tiles = (a.N + 64 * CG - 1) / (64 * CG);
     a.m_tiles = (a.M + 32 * TM - 1) / (32 * TM);
-    a.by_tokens = walk_by_tokens(a.n_tiles, a.m_tiles, (W4 ? 32.0f : 64.0f) * CG, 32.0f * TM);
-    const int width = a.n_tiles < kBand ? a.n_tiles : kBand, per_xcd = (a.n_tiles * a.m_tiles + 7) / 8;
+    a.walk = tile_walk(a.n_tiles, a.m_tiles, a.Kp, true, (W4 ? 32.0f : 64.0f) * CG, 32.0f * TM);
+    const int width = a.walk.band, per_xcd = (a.n_tiles * a.m_tiles + 7) / 8;
     a.share = min((per_xcd + width - 1) / width, min(a.m_tiles, 16));
     gemm_i8_dw_kernel<W4, NS, PW, TM, CG, KS, PF, OUT_MODE><<<dim3((unsigned)(a.n_tiles * a.m_tiles)), CG * KS * 64, lds_bytes, st>>>(a);
     return hipGetLastError();
@@ -747,7 +747,7 @@ hipError_t launch_staged(GemmI8Args a, hipStream_t st) {
     if (const hipError_t e = allow_dynamic_lds<gemm_i8_kernel<BN, BM, NS, OUT_MODE>>(lds_bytes); e != hipSuccess) return e;
     a.n_tiles = (a.N + BN - 1) / BN;
     a.m_tiles = (a.M + BM - 1) / BM;
-    a.by_tokens = walk_by_tokens(a.n_tiles, a.m_tiles, (float)BN, (float)BM);
+    a.walk = tile_walk(a.n_tiles, a.m_tiles, a.Kp, true, (float)BN, (float)BM);
     gemm_i8_kernel<BN, BM, NS, OUT_MODE><<<dim3((unsigned)(a.n_tiles * a.m_tiles)), 256, lds_bytes, st>>>(a);
     return hipGetLastError();
 }
@@ -760,7 +760,7 @@ hipError_t launch_w4(GemmI8Args a, hipStream_t st) {
     if (const hipError_t e = allow_dynamic_lds<gemm_i8_w4_kernel<BN, BM, NS, OUT_MODE>>(lds_bytes); e != hipSuccess) return e;
     a.n_tiles = (a.N + BN - 1) / BN;
     a.m_tiles = (a.M + BM - 1) / BM;
-    a.by_tokens = walk_by_tokens(a.n_tiles, a.m_tiles, 0.5f * BN, (float)BM);
+    a.walk = tile_walk(a.n_tiles, a.m_tiles, a.Kp, true, 0.5f * BN, (float)BM);
     gemm_i8_w4_kernel<BN, BM, NS, OUT_MODE><<<dim3((unsigned)(a.n_tiles * a.m_tiles)), 256, lds_bytes, st>>>(a);
     return hipGetLastError();
 }
@@ -862,7 +862,8 @@ hipError_t launch_gemm_i8(const Geometry &g, const void *packed, const int8_t *x
     a.M = M;
     a.N = g.N;
     a.Kp = g.Kp;
-    a.n_tiles = a.m_tiles = a.by_tokens = a.share = 0;
+    a.n_tiles = a.m_tiles = a.share = 0;
+    a.walk = {};
     a.gated_act = out_mode == 0 && g.pair_half ? gated_act : -1;
     int form;
     int8_tile_us(g, M, out_mode == 0 && g.N % 8 == 0, num_cus, &form);

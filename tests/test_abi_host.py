@@ -273,35 +273,73 @@ int main() {
 
 
 def test_tile_order_covers_every_tile_once(tmp_path):
-    """The walk over the tiles of a product: every tile once, for grids of one tile to several bands in both directions, the last band
-    of any width and any remainder over the XCDs; and an XCD's neighbours stay within one band, or two where its share crosses over."""
+    """The walk over the tiles of a product: every tile once, for grids of one tile to several bands in both directions, bands of any
+    width and any remainder over the XCDs; an XCD's neighbours stay within one band, or two where its share crosses over; and the walk that is chosen has equal
+    bands, the last at most as many tiles narrower as there are others."""
     src, exe = tmp_path / "order.cpp", str(tmp_path / "order")
     src.write_text("""#include "tile_order.h"
 #include <cstdio>
 #include <vector>
 int main() {
-    for (int by_tokens = 0; by_tokens < 2; ++by_tokens)
-        for (int n = 1; n <= 40; ++n)
-            for (int m = 1; m <= 40; ++m) {
+    for (int n = 1; n <= 40; ++n)
+        for (int m = 1; m <= 40; ++m) {
+            std::vector<qfc::TileWalk> walks = {{0, qfc::kBand}, {1, qfc::kBand}, {0, m}, {1, n}, {0, 5}, {1, 5}};
+            for (int K : {512, 4096, 8192, 1000000})
+                for (int i8 = 0; i8 < 2; ++i8) {
+                    const qfc::TileWalk w = qfc::tile_walk(n, m, K, i8, 256.0f, 128.0f);
+                    const int inner = w.by_tokens ? n : m, bands = (inner + w.band - 1) / w.band, last = inner - (bands - 1) * w.band;
+                    if (w.band < 1 || w.band > inner || last < 1 || w.band - last >= bands + (bands == 1)) return printf("%d x %d: bands of %d, last %d\\n", n, m, w.band, last), 1;
+                    walks.push_back(w);
+                }
+            for (const qfc::TileWalk &walk : walks) {
                 std::vector<int> seen(n * m, 0);
                 for (int b = 0; b < n * m; ++b) {
                     int nt = -1, mt = -1;
-                    qfc::xcd_tile(b, n, m, by_tokens, nt, mt);
-                    if (nt < 0 || nt >= n || mt < 0 || mt >= m || seen[nt * m + mt]++) return printf("%d x %d by_tokens %d: %d -> %d %d\\n", n, m, by_tokens, b, nt, mt), 1;
+                    qfc::xcd_tile(b, n, m, walk, nt, mt);
+                    if (nt < 0 || nt >= n || mt < 0 || mt >= m || seen[nt * m + mt]++) return printf("%d x %d by_tokens %d band %d: %d -> %d %d\\n", n, m, walk.by_tokens, walk.band, b, nt, mt), 1;
                     if (b >= 8) {
                         int n0, m0;
-                        qfc::xcd_tile(b - 8, n, m, by_tokens, n0, m0);
-                        const int band = (by_tokens ? nt : mt) / qfc::kBand - (by_tokens ? n0 : m0) / qfc::kBand;
-                        if (band < 0 || band > 1) return printf("%d x %d by_tokens %d: band %d\\n", n, m, by_tokens, band), 1;
+                        qfc::xcd_tile(b - 8, n, m, walk, n0, m0);
+                        const int band = (walk.by_tokens ? nt : mt) / walk.band - (walk.by_tokens ? n0 : m0) / walk.band;
+                        if (band < 0 || band > 1) return printf("%d x %d by_tokens %d: band %d\\n", n, m, walk.by_tokens, band), 1;
                     }
                 }
             }
+        }
     return 0;
 }
 """)
     subprocess.run(["g++", "-std=c++17", "-O1", "-D__host__=", "-D__device__=", "-D__forceinline__=inline", "-I", build.CSRC, str(src), "-o", exe], check=True)
     r = subprocess.run([exe], capture_output=True, text=True)
     assert r.returncode == 0, r.stdout[-2000:]
+
+
+# channel tiles, token tiles, K, int8 activations, bytes of a channel tile and of a token tile per k: by tokens, tiles of a band
+ORDERS = [
+    # one band of channel tiles and many token tiles: int8 activations walk by tokens from twice (K up to 4096) or three times as many on
+    (9, 18, 4096, 1, 256, 128, 1, 9), (9, 17, 4096, 1, 256, 128, 0, 9), (9, 32, 9216, 1, 256, 128, 1, 9), (9, 26, 9216, 1, 256, 128, 0, 9), (9, 32, 4096, 0, 256, 256, 0, 8),
+    # equal bands: nine token tiles are one, twelve are two, thirteen seven and six
+    (15, 9, 8448, 1, 128, 128, 0, 9), (20, 12, 4096, 1, 256, 128, 0, 6), (20, 13, 4096, 1, 256, 128, 0, 7),
+    # more tiles than an XCD has in flight, several bands in both directions: by tokens, unless the weights are too many for the memory-side cache
+    (112, 32, 4096, 1, 256, 128, 1, 8), (112, 47, 4096, 0, 128, 256, 1, 8), (133, 42, 13568, 1, 256, 128, 0, 42), (112, 8, 4096, 1, 256, 128, 0, 8),
+]
+
+
+def test_tile_order_is_chosen_by_size(tmp_path):
+    """In which order and in bands of how many tiles a product walks, on both sides of the rule's lines (times beside it)."""
+    src, exe = tmp_path / "walk.cpp", str(tmp_path / "walk")
+    src.write_text("""#include "tile_order.h"
+#include <cstdio>
+int main() {
+    for (int n, m, K, i8, w, x; scanf("%d %d %d %d %d %d", &n, &m, &K, &i8, &w, &x) == 6;) {
+        const qfc::TileWalk walk = qfc::tile_walk(n, m, K, i8 != 0, (float)w, (float)x);
+        printf("%d %d\\n", walk.by_tokens, walk.band);
+    }
+}
+""")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-D__host__=", "-D__device__=", "-D__forceinline__=inline", "-I", build.CSRC, str(src), "-o", exe], check=True)
+    r = subprocess.run([exe], input="\n".join(" ".join(map(str, o[:6])) for o in ORDERS), capture_output=True, text=True, check=True)
+    assert [(*o[:6], *map(int, l.split())) for o, l in zip(ORDERS, r.stdout.splitlines())] == ORDERS
 
 
 def test_int8_tiles_wait_for_what_they_read(tmp_path):
