@@ -33,7 +33,19 @@ __host__ __device__ __forceinline__ void xcd_tile(int b, int n_tiles, int m_tile
     nt = walk.by_tokens ? r : o;
     mt = walk.by_tokens ? o : r;
 }
-// w_bytes, x_bytes: of a channel tile and of a token tile, per k.  Put to measured times over 841 shapes of 704 to 60000 channels, K of 256 to 14336 and
+// The order for which an XCD pulls fewer bytes: its eighth of the tiles covers a band of one operand (several, if it is more than one; without bands: all
+// tiles) and tiles of the other.  w_bytes, x_bytes: of a channel tile and of a token tile, per k.
+inline TileWalk fewest_bytes_walk(int n_tiles, int m_tiles, float w_bytes, float x_bytes, bool banded) {
+    const int share = (n_tiles * m_tiles + 7) / 8;
+    auto covered = [&](int inner, int outer, float inner_bytes, float outer_bytes) {
+        const int width = banded ? band_width(inner) : inner, bands = (share + width * outer - 1) / (width * outer);
+        const int across = bands > 1 ? outer : (share + width - 1) / width;
+        return (float)(bands * width < inner ? bands * width : inner) * inner_bytes + (float)(bands * across) * outer_bytes;
+    };
+    const int by_tokens = covered(n_tiles, m_tiles, w_bytes, x_bytes) < covered(m_tiles, n_tiles, x_bytes, w_bytes) ? 1 : 0, inner = by_tokens ? n_tiles : m_tiles;
+    return {by_tokens, banded ? band_width(inner) : inner};
+}
+// Put to measured times over 841 shapes of 704 to 60000 channels, K of 256 to 14336 and
 // 300 to 6000 rows, all formats, against walks without bands and in bands of eight in either direction.  Over 816 others 1.4 % faster than without bands, 27 of them
 // more than 2 % slower (eights and the rest: 0.7 %, 74); the worst int8 6336 x 6144 1481 rows 77 / 84, 51008 x 3328 1125 rows 176 / 188.
 inline TileWalk tile_walk(int n_tiles, int m_tiles, int K, bool int8_activations, float w_bytes, float x_bytes) {
@@ -49,15 +61,7 @@ inline TileWalk tile_walk(int n_tiles, int m_tiles, int K, bool int8_activations
         if ((float)n_tiles * w_bytes * (float)K > 256e6f) return {0, m_tiles};
         return {1, band_width(n_tiles)};
     }
-    // The order for which an XCD pulls fewer bytes: its eighth of the tiles covers a band of one operand (several, if it is more than one) and
-    // tiles of the other.
-    auto covered = [&](int inner, int outer, float inner_bytes, float outer_bytes) {
-        const int width = band_width(inner), bands = (share + width * outer - 1) / (width * outer);
-        const int across = bands > 1 ? outer : (share + width - 1) / width;
-        return (float)(bands * width < inner ? bands * width : inner) * inner_bytes + (float)(bands * across) * outer_bytes;
-    };
-    const int by_tokens = covered(n_tiles, m_tiles, w_bytes, x_bytes) < covered(m_tiles, n_tiles, x_bytes, w_bytes) ? 1 : 0;
-    return {by_tokens, band_width(by_tokens ? n_tiles : m_tiles)};
+    return fewest_bytes_walk(n_tiles, m_tiles, w_bytes, x_bytes, true);
 }
 
 }  // namespace qfc

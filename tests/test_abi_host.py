@@ -290,6 +290,7 @@ int main() {
                     const int inner = w.by_tokens ? n : m, bands = (inner + w.band - 1) / w.band, last = inner - (bands - 1) * w.band;
                     if (w.band < 1 || w.band > inner || last < 1 || w.band - last >= bands + (bands == 1)) return printf("%d x %d: bands of %d, last %d\\n", n, m, w.band, last), 1;
                     walks.push_back(w);
+                    walks.push_back(qfc::fewest_bytes_walk(n, m, 64.0f, 128.0f, false));
                 }
             for (const qfc::TileWalk &walk : walks) {
                 std::vector<int> seen(n * m, 0);
@@ -322,17 +323,19 @@ ORDERS = [
     (15, 9, 8448, 1, 128, 128, 0, 9), (20, 12, 4096, 1, 256, 128, 0, 6), (20, 13, 4096, 1, 256, 128, 0, 7),
     # more tiles than an XCD has in flight, several bands in both directions: by tokens, unless the weights are too many for the memory-side cache
     (112, 32, 4096, 1, 256, 128, 1, 8), (112, 47, 4096, 0, 128, 256, 1, 8), (133, 42, 13568, 1, 256, 128, 0, 42), (112, 8, 4096, 1, 256, 128, 0, 8),
+    # without bands (K 0)
+    (13, 33, 0, 1, 64, 128, 1, 13), (33, 13, 0, 1, 64, 128, 0, 13), (16, 17, 0, 1, 128, 64, 0, 17),
 ]
 
 
 def test_tile_order_is_chosen_by_size(tmp_path):
-    """In which order and in bands of how many tiles a product walks, on both sides of the rule's lines (times beside it)."""
+    """In which order and in bands of how many tiles a product walks, on both sides of the rule's lines (times beside it); and the walk without bands."""
     src, exe = tmp_path / "walk.cpp", str(tmp_path / "walk")
     src.write_text("""#include "tile_order.h"
 #include <cstdio>
 int main() {
     for (int n, m, K, i8, w, x; scanf("%d %d %d %d %d %d", &n, &m, &K, &i8, &w, &x) == 6;) {
-        const qfc::TileWalk walk = qfc::tile_walk(n, m, K, i8 != 0, (float)w, (float)x);
+        const qfc::TileWalk walk = K == 0 ? qfc::fewest_bytes_walk(n, m, (float)w, (float)x, false) : qfc::tile_walk(n, m, K, i8 != 0, (float)w, (float)x);
         printf("%d %d\\n", walk.by_tokens, walk.band);
     }
 }
