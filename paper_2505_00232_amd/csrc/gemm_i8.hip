@@ -817,24 +817,26 @@ hipError_t launch_mode_w4(const GemmI8Args &a, int chosen, hipStream_t st) {
 
 // Estimated time of the direct-weights kernel (with the quantization of the rows, but for what of it grows with the rows) and the form that it is fastest
 // in, by its number.  A tile takes `each` us and K / 1000 times `alone` on a compute unit of its own, `shared` where several are in flight; of a last
-// round that is not full, the part that grows with K takes at least the share `idle` of a full one's.  Fitted to 350 shapes of 768 to 128256 channels, K of 256 to
-// 14336 and 65 to 4096 rows; the choice is 0.05 % (int4 weights 0.25 %) slower than the fastest of the four forms, 1.03 times at worst (int4 32000 x 4096 130
-// rows 1.1).  us, 256 x 128 / 256 x 64 / in parts of K 128 x 128 / 128 x 64, int8 weights: 4096 x 14336 1024 rows 98 / 87 / 68 / 87, 512 rows 96 / 82 / 64 /
-// 55, 2048 rows 110 / 156 / 133 / 171; 2304 x 9216 990 rows 65 / 57 / 45 / 51; 6144 x 4096 1024 rows 34.0 / 45.5 / 44.5 / 42.1; int4 (256 x 128 / 256 x 64 /
-// 128 x 64 in two / in four parts): 2304 x 9216 814 rows 59 / 40 / 32.4 / 30.5, 4096 x 4096 512 rows 31 / 21.9 / 17.7 / 19.0.
-// Outputs that are stored as they lie in the registers (accumulators; rows that are no multiple of 16 bytes) cost tiles of 256 x 128 about 4 us
-// more (int4 9001 x 1024 600 rows, 256 x 128 / 256 x 64, 31.1 / 24.9; int8 4100 x 1024 1211 rows 24.7 / 21.4).
+// round that is not full, the part that grows with K takes at least the share `idle` of a full one's.  Fitted so that the choice costs least, over 2580 shapes of 256 to 40000
+// channels, K of 256 to 14336 and 65 to 4096 rows, weights in HBM: int8 weights 0.22 % behind the fastest form (fitted to 350 aligned shapes before: 0.50 %), 6 of
+// 1301 shapes more than 10 %, int4 weights 0.43 %.  us, 256 x 128 / 256 x 64 / in parts of K 128 x 128 / 128 x 64, int8 weights: 4096 x 14336 1024 rows 98 / 87 / 68 / 87,
+// 512 rows 96 / 82 / 64 / 52, 2048 rows 110 / 156 / 133 / 171; 2112 x 6144 505 rows 44 / 34 / 31 / 24; 1600 x 2048 2026 rows 21.7 / 16.9 / 21.6 / 20.7; 30336 x 12544 96 rows
+// 113 / 102 / 128 / 133; int4 (256 x 128 / 256 x 64 / 128 x 64 in two / in four parts): 2304 x 9216 814 rows 59 / 40 / 32.4 / 30.5, 4096 x 4096 512 rows
+// 31 / 21.9 / 17.7 / 19.0.
+// Outputs that are stored as they lie in the registers (accumulators; rows that are no multiple of 16 bytes) cost tiles of 256 x 128 more than the others: 4 us in
+// the choice (int4 9001 x 1024 600 rows, 256 x 128 / 256 x 64, 31.1 / 24.9; int8 4100 x 1024 1211 rows 24.7 / 21.4).  What that store itself takes is in the time that
+// is returned: 0.11 us per round and token row of a wavefront where single values are stored, 0.05 where four are (K of 256, 256 x 64, 8.3 us; odd channels 15.8).
 float int8_tile_us(const Geometry &g, int M, bool staged_store, int num_cus, int *form) {
     struct Fit {
         int number, channels, tokens, parts;
         float start, each, alone, shared, idle;
     };
-    static const Fit fits[2][4] = {{{10, 256, 128, 1, 6.29f, 2.14f, 8.47f, 7.07f, 0.67f}, {12, 256, 64, 1, 4.08f, 2.60f, 6.65f, 4.76f, 0.73f},
-                                    {13, 128, 128, 2, 2.86f, 6.40f, 4.49f, 4.10f, 0.79f}, {14, 128, 64, 2, 5.75f, 1.57f, 3.72f, 3.10f, 0.89f}},
+    static const Fit fits[2][4] = {{{10, 256, 128, 1, 7.07f, 2.27f, 7.40f, 5.71f, 0.77f}, {12, 256, 64, 1, 4.12f, 2.70f, 5.07f, 4.53f, 0.93f},
+                                    {13, 128, 128, 2, 7.62f, 4.93f, 3.55f, 4.33f, 1.00f}, {14, 128, 64, 2, 3.43f, 2.74f, 2.96f, 3.14f, 0.98f}},
                                    {{21, 256, 128, 1, 6.06f, 2.51f, 6.66f, 5.52f, 0.75f}, {23, 256, 64, 1, 5.37f, 2.15f, 4.18f, 3.35f, 0.74f},
                                     {24, 128, 64, 2, 5.26f, 1.73f, 2.79f, 2.10f, 0.76f}, {25, 128, 64, 4, 3.45f, 5.06f, 2.46f, 2.18f, 0.78f}}};
-    const float k = 1e-3f * (float)g.Kp;
-    float best = 0.0f;
+    const float k = 1e-3f * (float)g.Kp, row_us = g.N % 8 == 0 ? 0.0f : g.N % 4 == 0 ? 0.05f : 0.11f;
+    float best = 0.0f, store = 0.0f;
     *form = 0;
     for (const Fit &f : fits[g.fmt == kW4C]) {
         if (f.parts > 1 && !parts_fit(g.Kp, f.parts)) continue;
@@ -845,9 +847,12 @@ float int8_tile_us(const Geometry &g, int M, bool staged_store, int num_cus, int
         float us = f.start + (float)full * f.each + work(full);
         if (rest > 0) us += f.each + (work(full + 1) - work(full)) * (f.idle + (1.0f - f.idle) * (float)rest / (float)num_cus);
         if (!staged_store && f.channels * f.tokens == 256 * 128) us += 4.0f;
-        if (*form == 0 || us < best) best = us, *form = f.number;
+        if (*form == 0 || us < best) {
+            best = us, *form = f.number;
+            store = row_us * (float)(full + (rest > 0 ? 1 : 0)) * (float)(f.parts > 1 ? f.tokens / 2 : f.tokens);
+        }
     }
-    return best;
+    return best + store;
 }
 
 hipError_t launch_gemm_i8(const Geometry &g, const void *packed, const int8_t *xq_tiled,

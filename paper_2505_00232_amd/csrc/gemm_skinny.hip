@@ -851,10 +851,11 @@ bool skinny_product(const Geometry &g, int M, bool int8_activations, bool gated,
         const float fill = (float)((g.N + 127) / 128 * m128) / (float)num_cus;
         return here < 1.04f * (3.5f + 9.3f * k) * (fill <= 1.0f ? 1.0f : 0.12f + ceilf(0.5f * fill));
     }
-    // (skinny_us put to measured times over 200 shapes of 65 to 1024 rows, standard deviation 9 to 11 %; the choice is 0.4 % slower than the
-    // faster of both.  0.95: where they are level, the tiles)
+    // (skinny_us put to measured times over 1772 shapes of 65 to 1024 rows, standard deviation 9 to 14 %; the choice is 0.35 % slower than the faster of both (0.95 and
+    // 1.1 % with a line drawn where rows are stored in 16 bytes): us, tiles / here, 6875 x 256 77 rows 15.7 / 9.5, 4635 x 1280 420 rows 20.1 / 15.8, int4 8482 x
+    // 1024 230 rows 16.5 / 14.1)
     int form;
-    return (w8 ? 5.05f + 0.774f * here : 4.47f + 0.823f * here) < 0.95f * int8_tile_us(g, M, g.N % 8 == 0, num_cus, &form);
+    return (w8 ? 3.0f + 0.84f * here : 4.75f + 0.88f * here) < int8_tile_us(g, M, g.N % 8 == 0, num_cus, &form);
 }
 
 hipError_t launch_skinny_f16(const Geometry &g, const void *packed, const void *x, int M, void *y, const void *residual,

@@ -412,6 +412,18 @@ STREAMS = [(128256, 4096, 24, 1), (65536, 8192, 9, 1), (31104, 8192, 24, 1), (15
            (33000, 8192, 16, 0), (50304, 8192, 24, 0), (28672, 4096, 20, 0), (250000, 512, 9, 0), (200000, 1024, 16, 0), (131070, 512, 32, 0), (200001, 1024, 32, 0),
            (164748, 992, 10, 0), (99936, 4096, 9, 0), (131758, 4096, 10, 0), (202048, 2048, 24, 0), (128256, 4096, 33, 0)]
 
+# int8 activations, rows past the token-row kernels' own: format, channels, K, token rows, the form of the tiles (0: the token-row kernels)
+INT8_TILES = [
+    # int8 weights: 256 x 128, 256 x 64 and, K in two parts, 128 x 128 and 128 x 64
+    (0, 4096, 14336, 512, 14), (0, 4096, 14336, 1024, 13), (0, 4096, 14336, 1100, 10), (0, 4096, 14336, 2048, 10), (0, 6144, 4096, 1024, 10), (0, 2112, 6144, 505, 14),
+    (0, 1600, 2048, 2026, 12), (0, 30336, 12544, 96, 12), (0, 28672, 4096, 66, 12), (0, 28672, 4096, 129, 10), (0, 4096, 768, 512, 14), (0, 4096, 256, 300, 12),
+    # int4 weights: 256 x 128, 256 x 64, 128 x 64 with K in two and in four parts
+    (2, 28672, 4096, 1024, 21), (2, 9008, 1024, 600, 21), (2, 4096, 4096, 512, 24), (2, 2304, 9216, 814, 25), (2, 4096, 512, 300, 24),
+    # the line between the tiles and the token-row kernels: rows, and rows that are stored value by value
+    (0, 4096, 14336, 191, 0), (0, 4096, 9216, 214, 0), (0, 4096, 9216, 300, 14), (0, 6144, 4096, 150, 0), (0, 6144, 4096, 240, 14), (2, 4096, 14336, 100, 0), (2, 4096, 14336, 300, 25),
+    (2, 2304, 9216, 300, 0), (2, 2304, 9216, 500, 25), (0, 9001, 1024, 600, 0), (0, 9000, 1024, 600, 10), (0, 4635, 1280, 420, 0), (0, 4640, 1280, 420, 12), (2, 8482, 1024, 230, 0),
+]
+
 
 def test_choice_of_kernels(tmp_path):
     """The dispatch's own functions, compiled for the host, on both sides of its lines (times of both beside the rules)."""
@@ -423,8 +435,13 @@ int main() {
         const qfc::Geometry g = qfc::make_geometry(N, K, fmt);
         if (kind == 0)
             printf("%d\\n", qfc::skinny_product(g, M, false, false, 256) ? -1 : qfc::skinny_tail_rows(g, M, false, 256));
-        else
+        else if (kind == 1)
             printf("%d\\n", (int)qfc::stream_takes(qfc::make_args(g, nullptr, nullptr, nullptr, M, nullptr, nullptr, -1), 256));
+        else {
+            int form;
+            qfc::int8_tile_us(g, M, N % 8 == 0, 256, &form);
+            printf("%d\\n", qfc::skinny_product(g, M, true, false, 256) ? 0 : form);
+        }
     }
 }
 """)
@@ -433,11 +450,12 @@ int main() {
     subprocess.run([build._hipcc(), "-std=c++17", "-w", "-O1", "-fPIC", "--offload-arch=gfx950", "--cuda-host-only", "-I", build.CSRC, "-c", str(src), "-o", obj], check=True)
     # (no device code: the kernels' images are never looked up)
     subprocess.run([build._hipcc(), obj, "-o", exe, "-Wl,--unresolved-symbols=ignore-all", "-L", where, "-lqfc", "-Wl,-rpath," + where], check=True)
-    asked = [(0, *c[:4]) for c in CHOICES] + [(1, 0, *s[:3]) for s in STREAMS]
+    asked = [(0, *c[:4]) for c in CHOICES] + [(1, 0, *s[:3]) for s in STREAMS] + [(2, *t[:4]) for t in INT8_TILES]
     r = subprocess.run([exe], input="\n".join(" ".join(map(str, c)) for c in asked), capture_output=True, text=True, check=True)
     got = [int(v) for v in r.stdout.split()]
     assert got[:len(CHOICES)] == [c[4] for c in CHOICES]
-    assert got[len(CHOICES):] == [s[3] for s in STREAMS]
+    assert got[len(CHOICES):len(CHOICES) + len(STREAMS)] == [s[3] for s in STREAMS]
+    assert got[len(CHOICES) + len(STREAMS):] == [t[4] for t in INT8_TILES]
 
 
 # KV heads, query rows per head, head size, positions: workgroups per KV head on 256 compute units
