@@ -1055,6 +1055,18 @@ size_t attn_prefill_workspace(int G, int M, int d, int num_cus) {
     return (size_t)G * M * kPrefillMaxChunks * (d + 2) * sizeof(float);
 }
 
+// Tokens per workgroup of rope_qkv_kernel: at most as many as one evaluation of an angle per thread covers; fewer, so that there are about four
+// workgroups per compute unit (1024 tokens x 48 x 128, 1 / 2 / 4 tokens: 9.2 / 10.3 / 12.7 us), unless their heads leave a quarter of the threads idle and more
+// and there are two per compute unit all the same (1216 x 3 x 128, 1 / 2 tokens: 5.7 / 5.1 us; 4793 x 2 x 64, 4 / 8: 7.1 / 6.8; for the last quarter it does not pay, 816 x
+// 12 x 128, 1 / 3: 5.9 / 7.0, nor with one per compute unit, 1939 x 10 x 64, 3 / 7: 6.1 / 7.2).  Over 2298 shapes 1.5 % behind the best number.
+int rope_tokens(long total, int heads, int d) {
+    const int items = heads * (d / 16);  // (a thread rotates 16 values of a token at a time)
+    const long most = 512 / d, busy = (192 + items - 1) / items;
+    long T = busy < total / 512 ? busy : total / 512;
+    if (T < total / 1024) T = total / 1024;
+    return T < 1 ? 1 : T > most ? (int)most : (int)T;
+}
+
 hipError_t launch_rope_qkv(const void *qkv, int B, int S, int h_q, int h_kv, int d, int C, int pos0, float base,
                            void *q_out, void *kc, void *vc, hipStream_t st) {
     const long total = (long)B * S;
@@ -1075,13 +1087,7 @@ hipError_t launch_rope_qkv(const void *qkv, int B, int S, int h_q, int h_kv, int
     a.vc = static_cast<_Float16 *>(vc);
     a.B = B, a.S = S, a.h_q = h_q, a.h_kv = h_kv, a.d = d, a.C = C, a.pos0 = pos0;
     a.log_base = log((double)base);
-    // at most as many tokens per workgroup as one evaluation of an angle per thread covers; fewer, so that there are about four workgroups per
-    // compute unit (1024 tokens x 48 x 128, 1 / 2 / 4 tokens: 9.2 / 10.3 / 12.7 us), unless their heads are too few to keep the threads
-    // busy (2000 x 3 x 64, 1 / 2 / 8 tokens: 9.9 / 6.1 / 5.7)
-    const long most = 512 / d, busy = (256 + (h_q + h_kv) * (d / 16) - 1) / ((h_q + h_kv) * (d / 16));
-    long T = busy < total / 256 ? busy : total / 256;
-    if (T < total / 1024) T = total / 1024;
-    a.T = T < 1 ? 1 : T > most ? (int)most : (int)T;
+    a.T = rope_tokens(total, h_q + h_kv, d);
     a.rot_wgs = (int)((total + a.T - 1) / a.T);
     a.pblocks = (pos0 + S - 1) / 64 - pos0 / 64 + 1;
     const size_t angles = (size_t)a.T * (d / 2) * sizeof(float4), tile = (size_t)64 * 66 * 2;

@@ -345,6 +345,7 @@ size_t attn_prefill_workspace(int G, int M, int d, int num_cus);
 int attn_splits(int G, int M, int d, int n_ctx, int num_cus);
 // cos and sin of pos * base^(-2 i / d) for pos < positions, i < d / 2, evaluated in fp64: [positions][d / 2][2] floats
 hipError_t launch_rope_table(int d, float base, int positions, float *table, hipStream_t st);
+int rope_tokens(long total, int heads, int d);
 hipError_t launch_rope_qkv(const void *qkv, int B, int S, int h_q, int h_kv, int d, int C, int pos0, float base,
                            void *q_out, void *kc, void *vc, hipStream_t st);
 hipError_t launch_attention(const void *q, const void *kc, const void *vc, int G, int S, int g, int d, int C,

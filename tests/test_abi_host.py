@@ -474,3 +474,15 @@ def test_decode_attention_walks():
     splits = ctypes.CDLL(binding.LIB_PATH)._ZN3qfc11attn_splitsEiiiii
     got = [(*w[:4], splits(*w[:4], 256)) for w in WALKS]
     assert got == WALKS
+
+
+# tokens, heads that are rotated, head size: tokens per workgroup of the rotary embedding of many tokens
+ROTATIONS = [(816, 12, 128, 1), (1939, 10, 64, 3), (1216, 3, 128, 2), (1023, 3, 128, 1), (4793, 2, 64, 8), (1024, 40, 128, 1), (2047, 40, 128, 1), (2048, 40, 128, 2), (6000, 40, 128, 4),
+             (6000, 12, 256, 2), (128, 8, 256, 1), (1100, 6, 64, 2), (100000, 3, 64, 8)]
+
+
+def test_rope_tokens_per_workgroup():
+    """On both sides of the rule's lines (times beside it)."""
+    binding.lib()
+    tokens = ctypes.CDLL(binding.LIB_PATH)._ZN3qfc11rope_tokensElii
+    assert [(*r[:3], tokens(ctypes.c_long(r[0]), *r[1:3])) for r in ROTATIONS] == ROTATIONS
