@@ -75,8 +75,9 @@ def _built_for() -> str:
 def _load_marshal(L):
     try:
         from . import _marshal
-        if _marshal.built_for != _built_for():
-            raise ImportError(f"built for {_marshal.built_for}, this is {_built_for()}")
+        built_for = getattr(_marshal, "built_for", "another version of this package")
+        if built_for != _built_for():
+            raise ImportError(f"built for {built_for}, this is {_built_for()}")
     except ImportError as e:
         warnings.warn(f"_marshal is not used, calls cost about 1 us more ({e}): run `python -m paper_2505_00232_amd.build`", RuntimeWarning, stacklevel=3)
         return None

@@ -186,7 +186,8 @@ for call in (lambda h, x: binding.qfc_forward(h, x, x), lambda h, x: binding.qfc
     ("", "binding._fast is not None and not said"),  # as it is built here
     ("sys.modules['paper_2505_00232_amd._marshal'] = None", "binding._fast is None and len(said) == 1"),  # missing, or the loader refuses it
     ("m = types.ModuleType('paper_2505_00232_amd._marshal'); m.built_for = 'Python 3.10, torch 1.0'; sys.modules[m.__name__] = m",
-     "binding._fast is None and len(said) == 1 and 'torch 1.0' in str(said[0].message)")])  # built against another torch
+     "binding._fast is None and len(said) == 1 and 'torch 1.0' in str(said[0].message)"),  # built against another torch
+    ("m = types.ModuleType('paper_2505_00232_amd._marshal'); sys.modules[m.__name__] = m", "binding._fast is None and len(said) == 1")])  # one that does not say
 def test_binding_works_without_the_native_module(L, before, after):
     """_marshal only shortens the way of two calls: without it the library loads, and every call goes through ctypes."""
     r = subprocess.run([sys.executable, "-c", _IN_A_PROCESS.format(before, after)], cwd=ROOT, capture_output=True, text=True)
