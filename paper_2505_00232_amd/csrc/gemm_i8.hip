@@ -779,9 +779,10 @@ bool parts_fit(int Kp, int parts) { return Kp / 128 >= 2 * parts; }
 
 // The kernel is chosen by size (int8_tile_us), or by number for tests: 4, 10, 12, 13, 14 (int8 weights), 20, 21, 23, 24, 25 (int4).  A number that
 // names none of the call's kernels leaves the choice.
-// Tiles of 256 x 128 touch their weights early where one round of them leaves latency to hide and a band of token tiles shares the work (us without / with:
-// 2304 x 9216 2048 rows 71.4 / 65.3, 3000 rows 74.6 / 72.5, 2048 x 7168 3438 rows 6 % faster; a second round, 2304 x 9216 4096 rows 122 / 129; few token tiles, 9728 x
-// 10240 423 rows 4 % slower).
+// Tiles of 256 x 128 touch their weights early where one round of them leaves latency to hide, K is long enough for it and a band of token tiles shares the work
+// (us without / with: 2304 x 9216 2048 rows 68.9 / 66.5, 4352 x 9728 1096 rows 71.5 / 68.0, 48 shapes with K above 4096 -1.7 %; K of 4096 and less, 109 shapes
+// +2 %, 3392 x 768 2135 rows 17.2 / 17.3, 2240 x 1024 3546 rows 19.6 / 20.8; a second round +3 %, 2304 x 9216 4096 rows 116 / 123; few token tiles +3 %,
+// 9728 x 10240 423 rows 73.3 / 75.5; a walk by tokens, 1344 x 13056 3677 rows 104.6 / 108.5).
 template <int OUT_MODE>
 hipError_t launch_mode(const GemmI8Args &a, int chosen, int num_cus, hipStream_t st) {
     int variant = tuning().gemm_variant;
@@ -790,8 +791,8 @@ hipError_t launch_mode(const GemmI8Args &a, int chosen, int num_cus, hipStream_t
         case 4: return launch_staged<128, 128, 3, OUT_MODE>(a, st);
         case 10: {
             const long n_tiles = (a.N + 255) / 256, m_tiles = (a.M + 127) / 128;
-            return m_tiles >= kBand && n_tiles * m_tiles <= num_cus ? launch_dw<false, 4, 2, 4, 4, 1, true, OUT_MODE>(a, st)
-                                                                    : launch_dw<false, 4, 2, 4, 4, 1, false, OUT_MODE>(a, st);
+            return a.Kp > 4096 && m_tiles >= kBand && m_tiles < 3 * n_tiles && n_tiles * m_tiles <= num_cus ? launch_dw<false, 4, 2, 4, 4, 1, true, OUT_MODE>(a, st)
+                                                                                                            : launch_dw<false, 4, 2, 4, 4, 1, false, OUT_MODE>(a, st);
         }
         case 13: return launch_dw<false, 4, 2, 4, 2, 2, true, OUT_MODE>(a, st);
         case 14: return launch_dw<false, 4, 2, 2, 2, 2, true, OUT_MODE>(a, st);
