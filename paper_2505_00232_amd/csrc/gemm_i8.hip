@@ -480,8 +480,8 @@ __global__ __launch_bounds__(256, 2) void gemm_i8_w4_kernel(GemmI8Args a) {
 // CG wavefronts side by side: tiles of 64 CG channels x 32 TM tokens, 256 or 128 x 128 or 64.  KS groups of them share K (an even number of stages each) and
 // hand their sums over through LDS at the end.  Which form: int8_tile_us.
 // PF: a compute unit has only so many cache lines on their way to it (about 45 KB: 57 GB/s of weights that come from HBM, 126 out of L2), so what bounds a
-// layer of one round of tiles is how long a line is on its way, not the rate of HBM or of the matrix cores (4096 x 14336, 1024 rows, tiles of 256 x 64:
-// 88 us, and 88 without its MFMAs).  The token tiles of the same weights therefore divide among them an early touch of every line, PW + NS - 1 stages
+// layer of one round of tiles is how long a line is on its way, not the rate of HBM or of the matrix cores (4096 x 14336, 1024 rows, tiles of 256 x 64,
+// weights in HBM: 88 us, and 88 without its MFMAs; in the cache 65).  The token tiles of the same weights therefore divide among them an early touch of every line, PW + NS - 1 stages
 // ahead, one instruction per wavefront and stage, and the weights' own loads then find them in L2: 128 x 128 tiles in two parts of K 73.9 / 68.1 us, 2304 x 9216
 // 1024 rows 48.8 / 44.6.  Tiles of 128 x 128 read 3.7 MB each where 256 x 64 read 4.6 (the same shapes 88 / 74 and 57 / 49 without the touch); for 4-bit weights,
 // whose bytes are half as many, 256 x 64 stays the better one and the touch costs more than it saves (62.4 / 63.6).  A touch is a copy into the
@@ -494,7 +494,7 @@ __global__ __launch_bounds__(256, 2) void gemm_i8_w4_kernel(GemmI8Args a) {
 //
 // What bounds it: power on real data (see the MFMA rates above), then the operand paths; where the tiles leave most of the chip idle, the latency of a
 // stage.  us with the quantization kernel, 32 x 32 MFMAs (int8 weights: stages of
-// 64 k) / this, both in one session: 28672 x 4096 int8, 1024 rows 119.6 / 107.6, 4096 rows 461 / 442; int4 gated, 1024 rows 109.0 / 97.0,
+// 64 k) / this, weights in the cache, both in one session: 28672 x 4096 int8, 1024 rows 119.6 / 107.6, 4096 rows 461 / 442; int4 gated, 1024 rows 109.0 / 97.0,
 // 300 rows 50.2 / 47.0; 6144 x 4096 int8, 1024 rows 35.0 / 32.1; 64-token tiles, 1024 rows: 4096 x 4096 int8 26.7 / 25.6, 4096 x 14336 int8
 // 67.9 / 64.8, int4 66.0 / 60.5; 457 x 8960 int8, 1714 rows 49.1 / 49.7, 540 x 9984 int4, 1434 rows 48.2 / 48.2.  (240 shapes of 200 to 32768 channels and
 // 300 to 4096 rows: 0.958 of the time, the worst narrow ones 767 x 4096 int8 1568 rows 33.4 / 34.2 and 1055 x 6144 1049 rows 39.8 / 40.6.  Without reading and
@@ -727,7 +727,7 @@ hipError_t launch_dw(GemmI8Args a, hipStream_t st) {
     constexpr size_t ring_bytes = (size_t)KS * NS * (4 * TM) * 1024;  // + one spare KiB for the copies past the end of K
     constexpr size_t lds_bytes = ring_bytes + 1024;
     static_assert(ring_bytes >= (size_t)CG * (KS > 1 ? 2 : 1) * 32 * (64 + 8) * 2, "the store phase stages its blocks inside the ring, below the spare KiB");
-    static_assert(lds_bytes <= (KS > 1 || NS > 8 ? 160 : 80) * 1024, "two workgroups per compute unit, or one");
+    static_assert(lds_bytes <= (KS > 1 ? 160 : 80) * 1024, "two workgroups per compute unit, or one");
     static_assert(PW == 2 || PW == 4, "an even number of stages is passes of PW and two more");
     if ((a.Kp / 128) % 2 != 0 || a.Kp / 128 < 2 * KS) return hipErrorInvalidValue;
     if (const hipError_t e = allow_dynamic_lds<gemm_i8_dw_kernel<W4, NS, PW, TM, CG, KS, PF, OUT_MODE>>(lds_bytes); e != hipSuccess) return e;
@@ -768,17 +768,14 @@ hipError_t launch_w4(GemmI8Args a, hipStream_t st) {
     return hipGetLastError();
 }
 
-// Tiles of 256 channels x 64 tokens hold the weights of four stages instead of two: an operation more in flight is an
-// operation that the wait of a stage need not see done.  us with the quantization kernel, two / four: int4 4096 x 4096 700 rows 25.3 / 24.4, 3101 x 8192
-// 840 rows 48.9 / 46.6 (the worst 2210 x 512 2197 rows 21.6 / 22.0); int8 375 x 12288 2136 rows 66.1 / 65.4, 1966 x 7680 1399 rows 50.5 / 49.3.  With int8
-// weights the longer start shows at small K: 699 x 768 2364 rows 18.3 / 19.4, 2233 x 1152 2642 rows 28.1 / 29.4, 1344 x 1024 1503 rows 12.8 / 13.1,
-// 4096 x 4096 1024 rows 26.0 / 26.0.
-bool weights_four_stages_ahead(const GemmI8Args &a) { return a.Kp >= 6144; }
-
 bool parts_fit(int Kp, int parts) { return Kp / 128 >= 2 * parts; }
 
 // The kernel is chosen by size (int8_tile_us), or by number for tests: 4, 10, 12, 13, 14 (int8 weights), 20, 21, 23, 24, 25 (int4).  A number that
 // names none of the call's kernels leaves the choice.
+// Tiles of 256 x 64 hold the weights of four stages with int4 codes (an operation more in flight is one that the wait of a stage need not see done; us with the
+// quantization kernel, two / four: 4096 x 4096 700 rows 25.3 / 24.4, 3101 x 8192 840 rows 48.9 / 46.6, the worst 2210 x 512 2197 rows 21.6 / 22.0), of two with
+// int8 codes, where the longer start shows at small K and nothing is gained at large K (the 500 shapes that take these tiles: K up to 512 +4.9 % with
+// four, up to 2048 +3.7 %, up to 4096 +1.6 %, 31 above 6144 level).
 // Tiles of 256 x 128 touch their weights early where one round of them leaves latency to hide, K is long enough for it and a band of token tiles shares the work
 // (us without / with: 2304 x 9216 2048 rows 68.9 / 66.5, 4352 x 9728 1096 rows 71.5 / 68.0, 48 shapes with K above 4096 -1.7 %; K of 4096 and less, 109 shapes
 // +2 %, 3392 x 768 2135 rows 17.2 / 17.3, 2240 x 1024 3546 rows 19.6 / 20.8; a second round +3 %, 2304 x 9216 4096 rows 116 / 123; few token tiles +3 %,
@@ -797,7 +794,7 @@ hipError_t launch_mode(const GemmI8Args &a, int chosen, int num_cus, hipStream_t
         case 13: return launch_dw<false, 4, 2, 4, 2, 2, true, OUT_MODE>(a, st);
         case 14: return launch_dw<false, 4, 2, 2, 2, 2, true, OUT_MODE>(a, st);
     }
-    return weights_four_stages_ahead(a) ? launch_dw<false, 8, 4, 2, 4, 1, false, OUT_MODE>(a, st) : launch_dw<false, 8, 2, 2, 4, 1, false, OUT_MODE>(a, st);
+    return launch_dw<false, 8, 2, 2, 4, 1, false, OUT_MODE>(a, st);
 }
 
 template <int OUT_MODE>

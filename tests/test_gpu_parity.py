@@ -471,7 +471,7 @@ def test_int8_tiles_gated_output(fmt, variant, M, N, K):
 
 @pytest.mark.parametrize("fmt,K", [("w4c", 256), ("w4c", 512), ("w4c", 768), ("w4c", 2304), ("w4c", 2560), ("w8c", 256), ("w8c", 512), ("w8c", 2400), ("w8c", 6144), ("w8c", 6400), ("w8c", 7168), ("w8c", 7392)])
 def test_int8_tiles_of_64_tokens_any_even_number_of_stages(fmt, K):
-    """The 64-token tiles, which hold the weights of four stages of 128 k (int8 codes with K of less than 6144: of two): whole passes of four, two
+    """The 64-token tiles, which hold the weights of four stages of 128 k (int8 codes: of two): whole passes of four, two
     stages more, only two, and K that ends inside a stage; three channel tiles and three token tiles, the last ones ragged; bit for bit,
     and the same again with warm caches."""
     M, N = 131, 600
