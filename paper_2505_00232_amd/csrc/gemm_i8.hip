@@ -479,7 +479,8 @@ __global__ __launch_bounds__(256, 2) void gemm_i8_w4_kernel(GemmI8Args a) {
 // The number of stages must be even.
 // CG wavefronts side by side: tiles of 64 CG channels x 32 TM tokens, 256 or 128 x 128 or 64.  KS groups of them share K (an even number of stages each) and
 // hand their sums over through LDS at the end.  Which form: int8_tile_us.
-// PF: a compute unit has only so many cache lines on their way to it (about 45 KB: 57 GB/s of weights that come from HBM, 126 out of L2), so what bounds a
+// PF: a compute unit has only so many cache lines on their way to it (the product alone draws 58 GB/s per compute unit with weights in HBM, 69 with weights in the
+// memory-side cache), so what bounds a
 // layer of one round of tiles is how long a line is on its way, not the rate of HBM or of the matrix cores (4096 x 14336, 1024 rows, tiles of 256 x 64,
 // weights in HBM: 88 us, and 88 without its MFMAs; in the cache 65).  The token tiles of the same weights therefore divide among them an early touch of every line, PW + NS - 1 stages
 // ahead, one instruction per wavefront and stage, and the weights' own loads then find them in L2: 128 x 128 tiles in two parts of K 73.9 / 68.1 us, 2304 x 9216
