@@ -723,7 +723,7 @@ hipError_t launch_fallback(GemmF16Args a, int M, hipStream_t st) {
     if (const hipError_t e = allow_dynamic_lds<gemm_f16_w4_kernel<PC, W8>>(kLdsBytes); e != hipSuccess) return e;
     a.n_tiles = (a.N + BN - 1) / BN;
     a.m_tiles = (M + BM - 1) / BM;
-    a.walk = tile_walk(a.n_tiles, a.m_tiles, a.K, false, (W8 ? 1.0f : PC ? 0.5f : 0.5625f) * BN, 2.0f * BM);
+    a.walk = staged_tile_walk(a.n_tiles, a.m_tiles, a.K, false, (W8 ? 1.0f : PC ? 0.5f : 0.5625f) * BN, 2.0f * BM);
     gemm_f16_w4_kernel<PC, W8><<<dim3((unsigned)(a.n_tiles * a.m_tiles)), 256, kLdsBytes, st>>>(a);
     return hipGetLastError();
 }

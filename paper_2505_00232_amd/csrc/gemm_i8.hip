@@ -761,10 +761,7 @@ hipError_t launch_w4(GemmI8Args a, hipStream_t st) {
     if (const hipError_t e = allow_dynamic_lds<gemm_i8_w4_kernel<BN, BM, NS, OUT_MODE>>(lds_bytes); e != hipSuccess) return e;
     a.n_tiles = (a.N + BN - 1) / BN;
     a.m_tiles = (a.M + BM - 1) / BM;
-    // (bands from 1024 tiles on: us, without / with, 1600 x 1152 4173 rows, 429 tiles, 23.7 / 27.0, 2432 x 1152 2018 rows 18.1 / 20.2; over 213 shapes 2.2 % faster
-    // than without, one of them more than 3 % slower, and 0.6 % more than with bands everywhere)
-    a.walk = a.n_tiles * a.m_tiles > 1024 ? tile_walk(a.n_tiles, a.m_tiles, a.Kp, true, 0.5f * BN, (float)BM)
-                                          : fewest_bytes_walk(a.n_tiles, a.m_tiles, 0.5f * BN, (float)BM, false);
+    a.walk = staged_tile_walk(a.n_tiles, a.m_tiles, a.Kp, true, 0.5f * BN, (float)BM);
     gemm_i8_w4_kernel<BN, BM, NS, OUT_MODE><<<dim3((unsigned)(a.n_tiles * a.m_tiles)), 256, lds_bytes, st>>>(a);
     return hipGetLastError();
 }

@@ -64,4 +64,11 @@ inline TileWalk tile_walk(int n_tiles, int m_tiles, int K, bool int8_activations
     return fewest_bytes_walk(n_tiles, m_tiles, w_bytes, x_bytes, true);
 }
 
+// Tiles of 128 x 128 that stage both operands, two to a compute unit: bands from 1024 tiles on (us, without / with: int8 x int4 1600 x 1152 4173 rows, 429 tiles, 23.7 /
+// 27.0, 2432 x 1152 2018 rows 18.1 / 20.2, binary16 activations, int4 groups 2880 x 4000 4015 rows, 736 tiles, 127 / 142, int8 137 / 123; up to 1024 tiles binary16 gains 0.2 % by
+// bands, above 0.6 to 3 %).
+inline TileWalk staged_tile_walk(int n_tiles, int m_tiles, int K, bool int8_activations, float w_bytes, float x_bytes) {
+    return n_tiles * m_tiles > 1024 ? tile_walk(n_tiles, m_tiles, K, int8_activations, w_bytes, x_bytes) : fewest_bytes_walk(n_tiles, m_tiles, w_bytes, x_bytes, false);
+}
+
 }  // namespace qfc

@@ -326,6 +326,8 @@ ORDERS = [
     (112, 32, 4096, 1, 256, 128, 1, 8), (112, 47, 4096, 0, 128, 256, 1, 8), (133, 42, 13568, 1, 256, 128, 0, 42), (112, 8, 4096, 1, 256, 128, 0, 8),
     # without bands (K 0)
     (13, 33, 0, 1, 64, 128, 1, 13), (33, 13, 0, 1, 64, 128, 0, 13), (16, 17, 0, 1, 128, 64, 0, 17),
+    # tiles that stage both operands (K negative): bands above 1024 of them
+    (23, 32, -4000, 0, 72, 256, 1, 23), (32, 32, -4000, 0, 72, 256, 1, 32), (32, 33, -4000, 0, 72, 256, 1, 8), (13, 33, -1152, 1, 64, 128, 1, 13),
 ]
 
 
@@ -336,7 +338,8 @@ def test_tile_order_is_chosen_by_size(tmp_path):
 #include <cstdio>
 int main() {
     for (int n, m, K, i8, w, x; scanf("%d %d %d %d %d %d", &n, &m, &K, &i8, &w, &x) == 6;) {
-        const qfc::TileWalk walk = K == 0 ? qfc::fewest_bytes_walk(n, m, (float)w, (float)x, false) : qfc::tile_walk(n, m, K, i8 != 0, (float)w, (float)x);
+        const qfc::TileWalk walk = K == 0 ? qfc::fewest_bytes_walk(n, m, (float)w, (float)x, false) : K < 0 ? qfc::staged_tile_walk(n, m, -K, i8 != 0, (float)w, (float)x)
+                                                                                                                          : qfc::tile_walk(n, m, K, i8 != 0, (float)w, (float)x);
         printf("%d %d\\n", walk.by_tokens, walk.band);
     }
 }
